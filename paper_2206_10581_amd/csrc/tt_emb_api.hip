@@ -45,6 +45,17 @@ bool gsum_block_rows(const Shape&);
 void launch_bwd_mid_mfma(const Plan&, const Workspace&, const float* g1, const float* g2,
                          const float* g3, const float* grad, int B, hipStream_t);
 void launch_gsum_block(const Plan&, const Workspace&, const float* grad, int B, hipStream_t);
+// index-free kernels (tt_emb_direct.hip)
+int direct_capacity(const Shape&);
+void launch_direct_fwd(const Plan&, const DirectBuffers&, const IdSource&, int B, const float* g1,
+                       const float* g2, const float* g3, float* out, bool train, hipStream_t);
+void launch_direct_bwd(const Plan&, const DirectBuffers&, int B, const float* g1, const float* g2,
+                       const float* g3, const float* grad, hipStream_t);
+void launch_direct_apply(const Plan&, const DirectBuffers&, int B, float* g1, float* g2, float* g3,
+                         float lr, const UpdateRule&, hipEvent_t stop, hipStream_t);
+bool table_shape(const Plan&);
+void launch_table(const Plan&, const float* g1, const float* g2, const float* g3, int64_t first,
+                  int64_t count, float* out, hipStream_t);
 hipError_t calibrate(void* buf, size_t bytes, hipStream_t, double* copy_bytes_per_s,
                      double* mfma_flops_per_s, double* gather_bytes_per_s,
                      double* far_gather_bytes_per_s);
@@ -52,7 +63,7 @@ hipError_t calibrate(void* buf, size_t bytes, hipStream_t, double* copy_bytes_pe
 static const char* const kSlotNames[kSlotCount] = {
     "sort_hist", "sort_scan", "sort_scatter", "seg_count", "seg_write",  "group",
     "prefix_fwd", "row_fwd",  "gsum",         "gsum_fix",  "u_bwd",      "dg3",        "prefix_bwd",
-    "sgd",        "event_pair"};
+    "sgd",        "direct_fwd", "direct_bwd", "direct_apply", "table", "event_pair"};
 
 static thread_local std::string g_hip_error = "HIP call failed";
 
@@ -139,6 +150,9 @@ static int make_plan(const tt_emb_config* c, Plan* pl) {
   pl->keyBits = bits_for(s.N);  // the sentinel N itself must be representable
   pl->passes = (pl->keyBits + 10) / 11;
   pl->bitsPerPass = (pl->keyBits + pl->passes - 1) / pl->passes;
+  pl->direct_cap = (c->flags & TT_EMB_FLAG_GENERIC_KERNELS)
+                       ? 0
+                       : (int)std::min<int64_t>(pl->maxB, direct_capacity(s));
   return TT_EMB_OK;
 }
 
@@ -216,6 +230,19 @@ static size_t carve(const Plan& pl, char* base, Workspace* ws /* [kSets] or null
     w.part3 = (float*)take((size_t)pl.maxChunk3 * s.S3 * 4);
     w.part2 = (float*)take((size_t)pl.maxChunk2 * s.S2 * 4);
   }
+  w.direct = DirectBuffers{};
+  if (!lookup_only && pl.direct_cap > 0) {
+    const size_t cap = ((size_t)pl.direct_cap + 7) & ~(size_t)7;
+    DirectBuffers& d = w.direct;
+    d.stride = (int)cap;
+    d.key = (uint32_t*)take(cap * 4);
+    d.dig = (uint16_t*)take(cap * 3 * 2);
+    d.P = (float*)take(cap * s.PN * 4);
+    d.dP = (float*)take(cap * s.PN * 4);
+    d.g1 = (float*)take(cap * s.S1 * 4);
+    d.dg1 = (float*)take(cap * s.S1 * 4);
+    d.dg3 = (float*)take(cap * s.S3 * 4);
+  }
   for (int i = sets; i < kSets; ++i) set[i] = set[0];
   for (int i = 1; i < sets; ++i) {
     set[i].P = w.P;
@@ -226,6 +253,7 @@ static size_t carve(const Plan& pl, char* base, Workspace* ws /* [kSets] or null
     set[i].dg1part = w.dg1part;
     set[i].part3 = w.part3;
     set[i].part2 = w.part2;
+    set[i].direct = w.direct;
   }
   if (ws)
     for (int i = 0; i < kSets; ++i) ws[i] = set[i];
@@ -254,6 +282,7 @@ struct tt_emb {
   int64_t pending_B;  // -1: no forward pending
   int64_t last_B;     // batch size of the latest forward
   bool have_forward;
+  bool direct;        // the latest forward took the index-free kernels
   hipStream_t last_stream;
   // tt_emb_prepare: index pipelines of coming batches on a stream of the library's own
   hipStream_t side[kSets];  // stream of each index set (kSideStreams distinct ones), created on
@@ -279,7 +308,7 @@ struct tt_emb {
 
 static IdSource id_source(const tt_emb* h, const int64_t* ids, int64_t base, bool reindexed) {
   const Plan& pl = h->plan;
-  return IdSource{ids, base, reindexed ? h->reindex : nullptr, reindexed ? h->reindex_n : 0,
+  return IdSource{ids, base, nullptr, reindexed ? h->reindex : nullptr, reindexed ? h->reindex_n : 0,
                   pl.split, pl.user_N, (int64_t)pl.sh.n2 * pl.sh.n3};
 }
 
@@ -355,6 +384,7 @@ static void init_handle(tt_emb* h, const tt_emb_config* cfg, const Plan& pl, flo
   h->pending_B = -1;
   h->last_B = 0;
   h->have_forward = false;
+  h->direct = false;
   h->last_stream = nullptr;
   h->profiling = false;
   h->mfma = pl.mfma;
@@ -434,6 +464,18 @@ static int setup_side_streams(tt_emb* h) {
   return TT_EMB_OK;
 }
 
+// First index set from `from` on that no prepared batch waits in; with all taken, the oldest prepared
+// batch is dropped.
+static int free_set(tt_emb* h, int from) {
+  for (int k = 0; k < kSets; ++k)
+    if (!h->prep[(from + k) % kSets].valid) return (from + k) % kSets;
+  int target = 0;
+  for (int s = 1; s < kSets; ++s)
+    if (h->prep[s].seq < h->prep[target].seq) target = s;
+  h->prep[target].valid = false;
+  return target;
+}
+
 // Index pipeline of one batch into index set `set`, on stream st.
 // how: 0 = everything, including the prefix-ordered schedule of the by-i3 chunks (worth its launch
 // only where the pipeline runs beside other work, as in tt_emb_prepare); 1 = no schedule; 2 = a
@@ -472,6 +514,7 @@ int tt_emb_prepare(tt_emb_t h, const int64_t* ids, int64_t B64, void* hip_stream
     int rc0 = setup_side_streams(h);
     if (rc0) return rc0;
   }
+  if (B64 * h->plan.split <= h->plan.direct_cap) return TT_EMB_OK;  // these need no index work
   // Pick the index set to fill.  A set is free when no backward_update still has to be enqueued for
   // it (that is only `cur`, between a forward and its backward) and no prepared batch waits in it.
   // With all taken, the oldest prepared batch is overwritten.
@@ -545,6 +588,19 @@ static int forward_impl(tt_emb* h, const IdSource& src, int64_t B64, float* out,
   const int B = (int)(B64 * pl.split);  // items of the index pipeline, rows of D/split floats
   h->pending_B = -1;
   int rc;
+  h->direct = B <= pl.direct_cap;
+  if (h->direct) {
+    h->cur = free_set(h, h->cur + 1);  // only names this step for tt_emb_wait_backward
+    h->done_valid[h->cur] = false;
+    rc = run_slot(h, kSlotDirectFwd, st, [&] {
+      launch_direct_fwd(pl, h->ws[0].direct, src, B, h->g1, h->g2, h->g3, out, arm, st);
+    });
+    if (rc) return rc;
+    h->pending_B = arm ? B : -1;
+    h->last_B = B;
+    h->have_forward = true;
+    return TT_EMB_OK;
+  }
   // oldest prepared batch with these ids and this size, if any
   int found = -1;
   for (int s = 0; s < kSets; ++s)
@@ -628,6 +684,13 @@ int tt_emb_materialize(tt_emb_t h, int64_t first_row, int64_t count, float* out,
   if (count > 0 && (out == nullptr || ((uintptr_t)out & (h->mfma ? 15u : 3u)) != 0))
     return TT_EMB_EINVAL;
   if (h->pending_B >= 0) return TT_EMB_ESTATE;  // would overwrite what the pending backward needs
+  if (count > 0 && table_shape(h->plan)) {
+    hipStream_t st = (hipStream_t)hip_stream;
+    if (h->side[0] != nullptr && stream_is_capturing(st)) return TT_EMB_ESTATE;
+    return run_slot(h, kSlotTable, st, [&] {
+      launch_table(h->plan, h->g1, h->g2, h->g3, first_row, count, out, st);
+    });
+  }
   // (every piece starts a multiple of max_batch rows into out: the matrix-core shapes have rows of
   // a multiple of 16 bytes, so the pieces are aligned like out itself)
   const int64_t D = h->plan.user_D;
@@ -746,17 +809,11 @@ int tt_emb_set_reindex(tt_emb_t h, const int32_t* new_id_of, int64_t n_ids) {
   return TT_EMB_OK;
 }
 
-int tt_emb_backward_update(tt_emb_t h, const float* grad_out, float lr, void* hip_stream) {
-  if (h == nullptr) return TT_EMB_EINVAL;
-  if (h->pending_B < 0) return TT_EMB_ESTATE;
-  const int B = (int)h->pending_B;
-  // arguments are checked before any state changes: a rejected call leaves the forward pending
-  if (B > 0 && (grad_out == nullptr || ((uintptr_t)grad_out & (h->mfma ? 15u : 3u)) != 0))
-    return TT_EMB_EINVAL;
-  hipStream_t st = (hipStream_t)hip_stream;
-  if (B > 0 && h->side[0] != nullptr && stream_is_capturing(st)) return TT_EMB_ESTATE;
-  h->pending_B = -1;
-  if (B == 0) return TT_EMB_OK;
+}  // extern "C"
+
+// Backward and update of a batch with index structures.
+static int backward_indexed(tt_emb* h, const float* grad_out, float lr, int B, hipEvent_t stop,
+                            hipStream_t st) {
   const Plan& pl = h->plan;
   const Workspace& ws = h->ws[h->cur];
   int rc;
@@ -793,6 +850,25 @@ int tt_emb_backward_update(tt_emb_t h, const float* grad_out, float lr, void* hi
     });
     if (rc) return rc;
   }
+  return run_slot(h, kSlotSgd, st,
+                  [&] { launch_sgd(pl, ws, h->g1, h->g2, h->g3, lr, h->ada, stop, st); });
+}
+
+extern "C" {
+
+int tt_emb_backward_update(tt_emb_t h, const float* grad_out, float lr, void* hip_stream) {
+  if (h == nullptr) return TT_EMB_EINVAL;
+  if (h->pending_B < 0) return TT_EMB_ESTATE;
+  const int B = (int)h->pending_B;
+  // arguments are checked before any state changes: a rejected call leaves the forward pending
+  if (B > 0 && (grad_out == nullptr || ((uintptr_t)grad_out & (h->mfma ? 15u : 3u)) != 0))
+    return TT_EMB_EINVAL;
+  hipStream_t st = (hipStream_t)hip_stream;
+  if (B > 0 && h->side[0] != nullptr && stream_is_capturing(st)) return TT_EMB_ESTATE;
+  h->pending_B = -1;
+  if (B == 0) return TT_EMB_OK;
+  const Plan& pl = h->plan;
+  int rc = TT_EMB_OK;
   // The update kernel is the last reader of the index set.  Outside stream capture and profiling
   // its completion signal doubles as the set's "done" event.
   // (a handle with side streams is never captured, see forward_impl)
@@ -805,8 +881,17 @@ int tt_emb_backward_update(tt_emb_t h, const float* grad_out, float lr, void* hi
     h->ada.corr1 = (float)(1.0 / (1.0 - std::pow((double)h->ada.beta1, t)));
     h->ada.corr2 = (float)(1.0 / (1.0 - std::pow((double)h->ada.beta2, t)));
   }
-  rc = run_slot(h, kSlotSgd, st,
-                [&] { launch_sgd(pl, ws, h->g1, h->g2, h->g3, lr, h->ada, stop, st); });
+  if (h->direct) {
+    const DirectBuffers& d = h->ws[0].direct;
+    rc = run_slot(h, kSlotDirectBwd, st,
+                  [&] { launch_direct_bwd(pl, d, B, h->g1, h->g2, h->g3, grad_out, st); });
+    if (rc) return rc;
+    rc = run_slot(h, kSlotDirectApply, st, [&] {
+      launch_direct_apply(pl, d, B, h->g1, h->g2, h->g3, lr, h->ada, stop, st);
+    });
+  } else {
+    rc = backward_indexed(h, grad_out, lr, B, stop, st);
+  }
   if (rc) return rc;
   if (h->ada.kind == kUpdateAdam) ++h->adam_step;  // the step counts once its update is enqueued
   if (h->profiling) rc = run_slot(h, kSlotEventPair, st, [] {});
@@ -838,9 +923,21 @@ int tt_emb_get_stats(tt_emb_t h, int64_t* U, int64_t* Q, int64_t* out_of_range) 
   std::memset(&c, 0, sizeof(c));
   int64_t oob = 0;
   if (h->have_forward) {
-    hipError_t e = hipStreamSynchronize(h->last_stream);
+    hipError_t e = hipSuccess;
+    int set = h->cur;
+    if (h->direct) {
+      // the index-free kernels count nothing: the batch's keys, which they keep, are sorted now
+      set = free_set(h, h->cur);
+      if (h->side[set] != nullptr) e = hipStreamSynchronize(h->side[set]);  // a dropped pipeline
+      if (e != hipSuccess) return hip_fail(e);
+      IdSource src = id_source(h, nullptr, 0, false);
+      src.keys = h->ws[0].direct.key;
+      int rc = run_index(h, set, src, (int)h->last_B, h->last_stream, 2);
+      if (rc) return rc;
+    }
+    e = hipStreamSynchronize(h->last_stream);
     if (e != hipSuccess) return hip_fail(e);
-    e = hipMemcpy(&c, h->ws[h->cur].ctr, sizeof(c), hipMemcpyDeviceToHost);
+    e = hipMemcpy(&c, h->ws[set].ctr, sizeof(c), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return hip_fail(e);
     oob = h->last_B - (int64_t)c.nvalid;
   }

@@ -604,10 +604,8 @@ __global__ __launch_bounds__(kThreads) void k_prefix_bwd(Shape sh, const float* 
   }
 }
 
-// Adds up the partial gradients of every touched slice and applies the update: the SGD step, the
-// Adagrad step  S += dG^2,  G -= lr * dG / (sqrt(S) + eps),  or the Adam step
-// m = b1 m + (1-b1) dG,  v = b2 v + (1-b2) dG^2,  G -= lr * (m corr1) / (sqrt(v corr2) + eps)
-// on the same entries (moments of untouched slices are left alone).
+// Adds up the partial gradients of every touched slice and applies the update rule
+// (updated_entry) to its entries; slices and moments the batch does not touch are left alone.
 // A job owns up to 256*VEC consecutive entries of one slice (VEC = 4 when slice sizes allow 16-byte
 // accesses, else 1).  Its threads are arranged as `parts` groups side by side on the entries; the
 // job's list of partials (chunks for G3 and G2, prefixes for G1) is dealt round-robin to the
@@ -717,19 +715,8 @@ __global__ __launch_bounds__(kThreads) void k_sgd(Shape sh, float lr, UpdateRule
     if (part == 0 && active) {
 #pragma unroll
       for (int x = 0; x < VEC; ++x) {
-        if (ADAM) {
-          const float m = fmaf(ada.beta1, St[o + x], (1.f - ada.beta1) * acc[x]);
-          const float v = fmaf(ada.beta2, Vt[o + x], (1.f - ada.beta2) * acc[x] * acc[x]);
-          St[o + x] = m;
-          Vt[o + x] = v;
-          G[o + x] = g_old[x] - lr * (m * ada.corr1) / (sqrtf(v * ada.corr2) + ada.eps);
-        } else if (ADA) {
-          const float sq = fmaf(acc[x], acc[x], St[o + x]);
-          St[o + x] = sq;
-          G[o + x] = g_old[x] - lr * acc[x] / (sqrtf(sq) + ada.eps);
-        } else {
-          G[o + x] = fmaf(-lr, acc[x], g_old[x]);
-        }
+        G[o + x] = updated_entry<RULE>(g_old[x], acc[x], lr, ada, ADA ? St + o + x : nullptr,
+                                       ADAM ? Vt + o + x : nullptr);
       }
     }
     if (parts > 1) __syncthreads();

@@ -1,0 +1,784 @@
+// Kernels that need no index structures (gfx950, fp32).
+//
+// Small batches.  Sorting and grouping a few thousand ids costs a dozen dependent launches of 3 to
+// 10 us each, far more than the arithmetic it saves, so a small batch treats every item (a batch
+// position, or a slab of one) as an id and a prefix of its own and takes three launches in all:
+//   k_direct_fwd     per item: P = G1[i1] G2[i2], E = P G3[i3], row stored; P kept for backward
+//   k_direct_bwd     per item: dP = g G3[i3]^T, its terms of dG3[i3] = P^T g and
+//                    dG1[i1] = dP G2[i2]^T, and a copy of the G1 slice (the next kernel overwrites it)
+//   k_direct_apply   per slice: finds the items that touch it by scanning the batch's digits, adds
+//                    up their terms (for G2: G1^T dP, a contraction over the items) in batch order
+//                    and applies the update rule
+// Every sum runs over the items in batch order, dealt to a fixed number of threads: results are
+// reproducible bit for bit.
+//
+// Table rows.  k_table_* write a run of consecutive rows of the dense table: all n3 rows of a prefix
+// share its product, and no id has to be looked at.
+#include <algorithm>
+#include <type_traits>
+
+#include <hip/hip_ext.h>
+
+#include "tt_emb_internal.h"
+
+namespace ttemb {
+
+typedef float f4 __attribute__((ext_vector_type(4)));
+
+constexpr int kDThreads = 256;
+constexpr int kDWaves = kDThreads / kWave;
+constexpr int kDirectMax = 8192;             // most items of a batch on these kernels
+constexpr size_t kDirectLds = 64 * 1024;     // dynamic LDS of a block of the per-item kernels
+
+// Columns of P = A Bm by a team of TEAM threads: A = d1 x r1 (wavefront-uniform address: scalar
+// loads), Bm = r1 x W row-major.  A thread owns VEC neighbouring columns at a time and four rows;
+// KU rows of Bm are in flight together.  put(row j1, column, value) takes the results.
+template <int TEAM, int VEC, class PUT>
+__device__ __forceinline__ void prefix_columns(int t, int d1, int r1, int W, const float* __restrict__ A,
+                                               const float* __restrict__ Bm, PUT put) {
+  constexpr int KU = 16;
+  for (int j0 = 0; j0 < d1; j0 += 4) {
+    const float* arow[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) arow[x] = A + (size_t)min(j0 + x, d1 - 1) * r1;
+    for (int c = t * VEC; c < W; c += TEAM * VEC) {
+      float acc[4][VEC];
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) acc[x][v] = 0.f;
+      const float* bp = Bm + c;
+      int k = 0;
+      for (; k + KU <= r1; k += KU) {
+        float b[KU][VEC];
+#pragma unroll
+        for (int j = 0; j < KU; ++j)
+#pragma unroll
+          for (int v = 0; v < VEC; ++v) b[j][v] = bp[(size_t)(k + j) * W + v];
+        __builtin_amdgcn_sched_barrier(0);  // the loads of a round are in flight together
+#pragma unroll
+        for (int j = 0; j < KU; ++j)
+#pragma unroll
+          for (int x = 0; x < 4; ++x)
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) acc[x][v] = fmaf(arow[x][k + j], b[j][v], acc[x][v]);
+      }
+      if (k < r1) {  // the last, shorter round: rows past r1 repeat the last one and count zero
+        float b[KU][VEC];
+#pragma unroll
+        for (int j = 0; j < KU; ++j)
+#pragma unroll
+          for (int v = 0; v < VEC; ++v) b[j][v] = bp[(size_t)min(k + j, r1 - 1) * W + v];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < KU; ++j)
+#pragma unroll
+          for (int x = 0; x < 4; ++x) {
+            const float a = k + j < r1 ? arow[x][min(k + j, r1 - 1)] : 0.f;
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) acc[x][v] = fmaf(a, b[j][v], acc[x][v]);
+          }
+      }
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+        if (j0 + x < d1)
+#pragma unroll
+          for (int v = 0; v < VEC; ++v) put(j0 + x, c + v, acc[x][v]);
+    }
+  }
+}
+
+// n floats of global memory, NR per thread in flight at once; fetch starts the loads, put stores
+// them to LDS (and moves what does not fit NR registers per thread).
+template <int TEAM, int NR>
+struct Staged {
+  float v[NR];
+  __device__ __forceinline__ void fetch(const float* __restrict__ src, int n, int t) {
+#pragma unroll
+    for (int i = 0; i < NR; ++i) v[i] = src[min(t + i * TEAM, n - 1)];
+  }
+  template <class PUT>
+  __device__ __forceinline__ void put(const float* __restrict__ src, int n, int t, PUT dst) {
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+      if (t + i * TEAM < n) dst(t + i * TEAM, v[i]);
+    for (int i = t + NR * TEAM; i < n; i += TEAM) dst(i, src[i]);
+  }
+};
+
+template <int TW>
+__device__ __forceinline__ void team_sync() {
+  if constexpr (TW == 1) wave_sync();
+  else __syncthreads();
+}
+
+// LDS floats of a team in the forward and the backward kernel (each part a multiple of four)
+static inline int up4(int n) { return (n + 3) & ~3; }
+static inline int fwd_lds_floats(const Shape& s) { return up4(s.S3) + up4(s.M * (s.r2 + 1)); }
+static inline int bwd_lds_floats(const Shape& s, int team) {
+  return up4(s.D) + up4(s.S3) + up4(s.M * (s.r2 + 1)) + up4(s.PN) + 4 * team;
+}
+
+// ---------------------------------------------------------------------------------------------
+// One item per team of TW wavefronts (one for unfolded G2 slices of up to 128 columns, else four).
+// Bound by latency: ids, then the slices (one round trip, all of an item's loads side by side), then
+// the store.  Measured at 1025 ids, n = 136^3, rank 32: the whole lookup takes one launch of 6 us
+// where the sorted path takes nine launches and 55 us.
+template <int TW, int VEC, bool TRAIN>
+__global__ __launch_bounds__(kDThreads) void k_direct_fwd(
+    Shape sh, IdSource src, int B, const float* __restrict__ g1, const float* __restrict__ g2,
+    const float* __restrict__ g3, uint32_t* __restrict__ keys, uint16_t* __restrict__ dig, int stride,
+    float* __restrict__ P, float* __restrict__ out) {
+  constexpr int TEAM = TW * kWave, TPB = kDThreads / TEAM;
+  extern __shared__ __align__(16) float lds[];
+  const int team = TW == 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave) : 0;
+  const int t = threadIdx.x % TEAM;
+  const int e = blockIdx.x * TPB + team;
+  if (e >= B) return;  // whole teams only, and a block is one team where it has barriers
+  const int ps = sh.r2 + 1;
+  float* cl = lds + (size_t)team * (((sh.S3 + 3) & ~3) + ((sh.M * ps + 3) & ~3));
+  float* pl = cl + ((sh.S3 + 3) & ~3);
+  const uint32_t key = (uint32_t)__builtin_amdgcn_readfirstlane((int)key_of_id(src, e, sh.N));
+  const bool valid = key < sh.N;
+  const uint32_t q = key / sh.n3, i3 = key - q * sh.n3, i1 = q / sh.n2, i2 = q - i1 * sh.n2;
+  if (t == 0 && keys != nullptr) keys[e] = key;
+  if (TRAIN && t == 0) {
+    dig[e] = valid ? (uint16_t)i1 : 0xffffu;
+    dig[stride + e] = valid ? (uint16_t)i2 : 0xffffu;
+    dig[2 * stride + e] = valid ? (uint16_t)i3 : 0xffffu;
+  }
+  float* o = out + (size_t)e * sh.D;
+  if (!valid) {
+    for (int i = t; i < sh.D; i += TEAM) o[i] = 0.f;
+    return;
+  }
+  const float* C = g3 + (size_t)i3 * sh.S3;
+  Staged<TEAM, 4> c;
+  c.fetch(C, sh.S3, t);
+  float* Pe = TRAIN ? P + (size_t)e * sh.PN : nullptr;
+  prefix_columns<TEAM, VEC>(t, sh.d1, sh.r1, sh.W, g1 + (size_t)i1 * sh.S1, g2 + (size_t)i2 * sh.S2,
+                            [&](int j1, int col, float v) {
+                              const int j2 = col / sh.r2;
+                              pl[(j1 * sh.d2 + j2) * ps + col - j2 * sh.r2] = v;
+                              if (TRAIN) Pe[(size_t)j1 * sh.W + col] = v;
+                            });
+  c.put(C, sh.S3, t, [&](int i, float v) { cl[i] = v; });
+  team_sync<TW>();
+  for (int i = t; i < sh.D; i += TEAM) {
+    const int m = i / sh.d3, j3 = i - m * sh.d3;
+    const float *pr = pl + m * ps, *cc = cl + j3;
+    float acc = 0.f;
+#pragma unroll 8
+    for (int k = 0; k < sh.r2; ++k) acc = fmaf(pr[k], cc[k * sh.d3], acc);
+    o[i] = acc;
+  }
+}
+
+template <int TW>
+__global__ __launch_bounds__(kDThreads) void k_direct_bwd(
+    Shape sh, int B, const uint32_t* __restrict__ keys, const float* __restrict__ g1,
+    const float* __restrict__ g2, const float* __restrict__ g3, const float* __restrict__ grad,
+    const float* __restrict__ P, float* __restrict__ dP, float* __restrict__ g1c,
+    float* __restrict__ dg1, float* __restrict__ dg3) {
+  constexpr int TEAM = TW * kWave, TPB = kDThreads / TEAM;
+  extern __shared__ __align__(16) float lds[];
+  const int team = TW == 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave) : 0;
+  const int t = threadIdx.x % TEAM;
+  const int e = blockIdx.x * TPB + team;
+  if (e >= B) return;
+  const uint32_t key = (uint32_t)__builtin_amdgcn_readfirstlane((int)keys[e]);
+  if (key >= sh.N) return;  // no digit row names this item: nothing of it is ever read
+  const uint32_t q = key / sh.n3, i3 = key - q * sh.n3, i1 = q / sh.n2, i2 = q - i1 * sh.n2;
+  const int ps = sh.r2 + 1;
+  const int nD = (sh.D + 3) & ~3, nC = (sh.S3 + 3) & ~3, nP = (sh.M * ps + 3) & ~3,
+            nd = (sh.PN + 3) & ~3;
+  float* gl = lds + (size_t)team * (nD + nC + nP + nd + 4 * TEAM);
+  float* cl = gl + nD;
+  float* pl = cl + nC;
+  float* dl = pl + nP;
+  float* red = dl + nd;
+  const float *G = grad + (size_t)e * sh.D, *C = g3 + (size_t)i3 * sh.S3, *Pe = P + (size_t)e * sh.PN;
+  const float* A = g1 + (size_t)i1 * sh.S1;
+  {
+    Staged<TEAM, 4> g, c;
+    Staged<TEAM, 8> p;
+    Staged<TEAM, 2> a;
+    g.fetch(G, sh.D, t);
+    c.fetch(C, sh.S3, t);
+    p.fetch(Pe, sh.PN, t);
+    a.fetch(A, sh.S1, t);
+    __builtin_amdgcn_sched_barrier(0);
+    g.put(G, sh.D, t, [&](int i, float v) { gl[i] = v; });
+    c.put(C, sh.S3, t, [&](int i, float v) { cl[i] = v; });
+    p.put(Pe, sh.PN, t, [&](int i, float v) { pl[(i / sh.r2) * ps + i % sh.r2] = v; });
+    float* Ac = g1c + (size_t)e * sh.S1;
+    a.put(A, sh.S1, t, [&](int i, float v) { Ac[i] = v; });
+  }
+  team_sync<TW>();
+  // dP[m][b] = sum over j3 of g[m][j3] G3[b][j3]
+  float* de = dP + (size_t)e * sh.PN;
+  for (int i = t; i < sh.PN; i += TEAM) {
+    const int m = i / sh.r2, b = i - m * sh.r2;
+    float acc = 0.f;
+    for (int j = 0; j < sh.d3; ++j) acc = fmaf(gl[m * sh.d3 + j], cl[b * sh.d3 + j], acc);
+    dl[i] = acc;
+    de[i] = acc;
+  }
+  // term of dG3: sum over m of P[m][b] g[m][j3]
+  float* w3 = dg3 + (size_t)e * sh.S3;
+  for (int i = t; i < sh.S3; i += TEAM) {
+    const int b = i / sh.d3, j = i - b * sh.d3;
+    float acc = 0.f;
+    for (int m = 0; m < sh.M; ++m) acc = fmaf(pl[m * ps + b], gl[m * sh.d3 + j], acc);
+    w3[i] = acc;
+  }
+  team_sync<TW>();
+  // term of dG1: dP[j1][c] G2[i2][a][c] summed over the W columns c.  Thread (part, a) walks a share
+  // of the columns of row a, four at a time where rows are 16-byte aligned.
+  const float* Bm = g2 + (size_t)i2 * sh.S2;
+  float* w1 = dg1 + (size_t)e * sh.S1;
+  for (int a0 = 0; a0 < sh.r1; a0 += TEAM) {
+    const int ra = min(TEAM, sh.r1 - a0);
+    const int parts = TEAM / ra, part = t / ra;
+    const int a = a0 + t % ra;
+    const bool on = part < parts;
+    const int quads = (sh.W + 3) / 4, per = (quads + parts - 1) / parts;
+    const int c0 = on ? min(part * per * 4, sh.W) : 0, c1 = on ? min(c0 + per * 4, sh.W) : 0;
+    const float* row = Bm + (size_t)a * sh.W;
+    for (int j0 = 0; j0 < sh.d1; j0 += 4) {
+      float acc[4] = {0.f, 0.f, 0.f, 0.f};
+      const float* dr[4];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) dr[x] = dl + min(j0 + x, sh.d1 - 1) * sh.W;
+      if (sh.W % 4 == 0) {
+        int c = c0;
+        for (; c + 32 <= c1; c += 32) {
+          f4 b[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) b[j] = *(const f4*)(row + c + 4 * j);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+              const f4 d = *(const f4*)(dr[x] + c + 4 * j);
+              acc[x] = fmaf(d.x, b[j].x, acc[x]);
+              acc[x] = fmaf(d.y, b[j].y, acc[x]);
+              acc[x] = fmaf(d.z, b[j].z, acc[x]);
+              acc[x] = fmaf(d.w, b[j].w, acc[x]);
+            }
+        }
+        for (; c < c1; c += 4) {
+          const f4 b = *(const f4*)(row + c);
+#pragma unroll
+          for (int x = 0; x < 4; ++x) {
+            const f4 d = *(const f4*)(dr[x] + c);
+            acc[x] = fmaf(d.x, b.x, acc[x]);
+            acc[x] = fmaf(d.y, b.y, acc[x]);
+            acc[x] = fmaf(d.z, b.z, acc[x]);
+            acc[x] = fmaf(d.w, b.w, acc[x]);
+          }
+        }
+      } else {
+        for (int c = c0; c < c1; ++c) {
+          const float b = row[c];
+#pragma unroll
+          for (int x = 0; x < 4; ++x) acc[x] = fmaf(dr[x][c], b, acc[x]);
+        }
+      }
+#pragma unroll
+      for (int x = 0; x < 4; ++x) red[x * TEAM + t] = acc[x];
+      team_sync<TW>();
+      for (int i = t; i < 4 * ra; i += TEAM) {
+        const int x = i / ra, aa = i - x * ra;
+        if (j0 + x < sh.d1) {
+          float s = 0.f;
+          for (int p = 0; p < parts; ++p) s += red[x * TEAM + p * ra + aa];
+          w1[(size_t)(j0 + x) * sh.r1 + a0 + aa] = s;
+        }
+      }
+      team_sync<TW>();
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Sums and update.  A block owns a run of entries of one slice:
+//   G2 jobs (first, they are the longest): for d1 <= 4 and r1 <= 128 16*CT columns of the slice, as
+//     sum over items of G1^T (r1 x d1) dP (d1 x W), one 16x16x4 matrix-core product per item and
+//     tile (edges masked), the items dealt to the four wavefronts; else kSpan2 entries
+//   G3, then G1 jobs: up to 256*VEC entries, the items dealt to groups of threads
+// The digits of the whole batch are scanned by every block (2 bytes per item, 16 KiB at most): cheaper
+// than a launch that sorts them, and what a block needs comes out in batch order.
+struct DirectList {
+  uint16_t item[kDirectMax];
+  uint32_t wave_n[kDWaves];
+};
+
+__device__ __forceinline__ int direct_list(DirectList& L, const uint16_t* __restrict__ dig, int B, int want) {
+  constexpr int kStep = kWave * 8, kMaxSteps = kDirectMax / (kDWaves * kStep);
+  const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  const int steps = (B + kDWaves * kStep - 1) / (kDWaves * kStep);  // at most kMaxSteps
+  const int base = w * steps * kStep;
+  uint4 d[kMaxSteps];
+#pragma unroll
+  for (int s = 0; s < kMaxSteps; ++s) {
+    const int at = base + s * kStep + lane * 8;
+    d[s] = (s < steps && at < B) ? *(const uint4*)(dig + at) : make_uint4(~0u, ~0u, ~0u, ~0u);
+  }
+  uint32_t mask[kMaxSteps], incl[kMaxSteps], n = 0;
+#pragma unroll
+  for (int s = 0; s < kMaxSteps; ++s) {
+    const int at = base + s * kStep + lane * 8;
+    const uint32_t v[4] = {d[s].x, d[s].y, d[s].z, d[s].w};
+    uint32_t m = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if ((v[j] & 0xffffu) == (uint32_t)want) m |= 1u << (2 * j);
+      if ((v[j] >> 16) == (uint32_t)want) m |= 2u << (2 * j);
+    }
+    if (s >= steps || at >= B) m = 0;
+    else if (at + 8 > B) m &= (1u << (B - at)) - 1u;  // digits past the batch are unwritten
+    mask[s] = m;
+    incl[s] = n + wave_inclusive_scan((uint32_t)__popc(m), lane);
+    n = (uint32_t)__builtin_amdgcn_readlane((int)incl[s], kWave - 1);
+  }
+  if (lane == 0) L.wave_n[w] = n;
+  __syncthreads();
+  uint32_t before = 0, total = 0;
+#pragma unroll
+  for (int k = 0; k < kDWaves; ++k) {
+    before += k < w ? L.wave_n[k] : 0u;
+    total += L.wave_n[k];
+  }
+#pragma unroll
+  for (int s = 0; s < kMaxSteps; ++s) {
+    uint32_t at = before + incl[s] - (uint32_t)__popc(mask[s]);
+    for (uint32_t m = mask[s]; m != 0; m &= m - 1)
+      L.item[at++] = (uint16_t)(base + s * kStep + lane * 8 + __ffs((int)m) - 1);
+  }
+  __syncthreads();
+  return (int)total;
+}
+
+template <int RT, int CT, int RULE>  // RT row tiles of 16 on the matrix cores, or 0
+__global__ __launch_bounds__(kDThreads) void k_direct_apply(
+    Shape sh, int B, float lr, UpdateRule ada, const uint16_t* __restrict__ dig, int stride,
+    const float* __restrict__ g1c, const float* __restrict__ dP, const float* __restrict__ dg1,
+    const float* __restrict__ dg3, float* __restrict__ g1, float* __restrict__ g2,
+    float* __restrict__ g3) {
+  constexpr bool ADA = RULE != kUpdateSgd, ADAM = RULE == kUpdateAdam;
+  constexpr int kSpan2 = 128;  // entries of a G2 job without matrix cores
+  constexpr int kRed = RT > 0 ? kDWaves * RT * CT * 256 : kDThreads * 4;
+  __shared__ DirectList L;
+  __shared__ float red[kRed];
+  const int tid = threadIdx.x;
+  const int per2 = RT > 0 ? (sh.W + 16 * CT - 1) / (16 * CT) : (sh.S2 + kSpan2 - 1) / kSpan2;
+  const int jobs2 = (int)sh.n2 * per2;
+  int job = blockIdx.x;
+  if (job < jobs2) {
+    const int i2 = job / per2, piece = job - i2 * per2;
+    const int n = direct_list(L, dig + stride, B, i2);
+    if (n == 0) return;
+    float* G = g2 + (size_t)i2 * sh.S2;
+    float* St = ADA ? ada.s2 + (size_t)i2 * sh.S2 : nullptr;
+    float* Vt = ADAM ? ada.v2 + (size_t)i2 * sh.S2 : nullptr;
+    if constexpr (RT > 0) {
+      constexpr int U = RT >= 4 ? 4 : 8;  // items in flight per wavefront
+      const int w = tid / kWave, lane = tid % kWave, l16 = lane % 16, kg = lane / 16;
+      const int col0 = piece * 16 * CT;
+      // rows and columns past the slice and rows past d1 read a valid address and count zero
+      const int k1 = min(kg, sh.d1 - 1);
+      int ra[RT], cb[CT];
+#pragma unroll
+      for (int i = 0; i < RT; ++i) ra[i] = k1 * sh.r1 + min(16 * i + l16, sh.r1 - 1);
+#pragma unroll
+      for (int j = 0; j < CT; ++j) cb[j] = k1 * sh.W + min(col0 + 16 * j + l16, sh.W - 1);
+      f4 acc[RT][CT];
+#pragma unroll
+      for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < CT; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+      for (int k = w; k < n; k += kDWaves * U) {
+        float a[U][RT], b[U][CT];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int e = L.item[min(k + u * kDWaves, n - 1)];
+          const float* ap = g1c + (size_t)e * sh.S1;
+          const float* bp = dP + (size_t)e * sh.PN;
+#pragma unroll
+          for (int i = 0; i < RT; ++i) a[u][i] = ap[ra[i]];
+#pragma unroll
+          for (int j = 0; j < CT; ++j) b[u][j] = bp[cb[j]];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (k + u * kDWaves < n)  // wavefront-uniform
+#pragma unroll
+            for (int i = 0; i < RT; ++i)
+#pragma unroll
+              for (int j = 0; j < CT; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(kg < sh.d1 ? a[u][i] : 0.f, b[u][j],
+                                                                 acc[i][j], 0, 0, 0);
+      }
+      // element v of lane (kg, l16) is row 16*i + 4*kg + v, column 16*j + l16
+#pragma unroll
+      for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < CT; ++j)
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            red[((w * RT * 16 + 16 * i + 4 * kg + v) * CT + j) * 16 + l16] = acc[i][j][v];
+      __syncthreads();
+      constexpr int kOut = RT * CT * 256;
+#pragma unroll
+      for (int x = 0; x < kOut / kDThreads; ++x) {
+        const int o = tid + x * kDThreads, row = o / (16 * CT), col = o % (16 * CT);
+        float s = red[o];
+#pragma unroll
+        for (int k = 1; k < kDWaves; ++k) s += red[k * kOut + o];
+        if (row >= sh.r1 || col0 + col >= sh.W) continue;
+        const size_t at = (size_t)row * sh.W + col0 + col;
+        G[at] = updated_entry<RULE>(G[at], s, lr, ada, ADA ? St + at : nullptr, ADAM ? Vt + at : nullptr);
+      }
+    } else {
+      const int o0 = piece * kSpan2, outs = min(kSpan2, sh.S2 - o0);
+      int lanes = 1;
+      while (lanes < outs) lanes <<= 1;  // at most kSpan2
+      const int groups = kDThreads / lanes, lane = tid % lanes, grp = tid / lanes;
+      const int o = o0 + min(lane, outs - 1), a = o / sh.W, c = o - a * sh.W;
+      float acc = 0.f;
+      for (int k = grp; k < n; k += groups) {
+        const int e = L.item[k];
+        const float* ap = g1c + (size_t)e * sh.S1 + a;
+        const float* bp = dP + (size_t)e * sh.PN + c;
+        for (int j1 = 0; j1 < sh.d1; ++j1) acc = fmaf(ap[(size_t)j1 * sh.r1], bp[(size_t)j1 * sh.W], acc);
+      }
+      red[tid] = acc;
+      __syncthreads();
+      if (grp == 0 && lane < outs) {
+        for (int p = 1; p < groups; ++p) acc += red[p * lanes + lane];
+        G[o] = updated_entry<RULE>(G[o], acc, lr, ada, ADA ? St + o : nullptr, ADAM ? Vt + o : nullptr);
+      }
+    }
+    return;
+  }
+  job -= jobs2;
+  const bool three = job < (int)sh.n3 * ((sh.S3 + 1023) / 1024);
+  if (!three) job -= (int)sh.n3 * ((sh.S3 + 1023) / 1024);
+  const int S = three ? sh.S3 : sh.S1, per = (S + 1023) / 1024;
+  const int slice = job / per, o0 = (job - slice * per) * 1024, outs = min(1024, S - o0);
+  const int n = direct_list(L, dig + (three ? 2 * stride : 0), B, slice);
+  if (n == 0) return;
+  const float* src = (three ? dg3 : dg1) + o0;
+  float* G = (three ? g3 : g1) + (size_t)slice * S + o0;
+  float* St = ADA ? (three ? ada.s3 : ada.s1) + (size_t)slice * S + o0 : nullptr;
+  float* Vt = ADAM ? (three ? ada.v3 : ada.v1) + (size_t)slice * S + o0 : nullptr;
+  auto sum = [&](auto vec) {
+    constexpr int VEC = decltype(vec)::value, U = 8;
+    int lanes = 1;
+    while (lanes * VEC < outs && lanes < kDThreads) lanes <<= 1;
+    const int groups = kDThreads / lanes, lane = tid % lanes, grp = tid / lanes;
+    for (int b0 = 0; b0 < outs; b0 += lanes * VEC) {
+      const bool on = b0 + lane * VEC < outs;
+      const int o = on ? b0 + lane * VEC : 0;
+      float acc[VEC];
+#pragma unroll
+      for (int x = 0; x < VEC; ++x) acc[x] = 0.f;
+      int k = grp;
+      for (; k + (U - 1) * groups < n; k += U * groups) {
+        float v[U][VEC];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const float* p = src + (size_t)L.item[k + u * groups] * S + o;
+#pragma unroll
+          for (int x = 0; x < VEC; ++x) v[u][x] = p[x];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int x = 0; x < VEC; ++x) acc[x] += v[u][x];
+      }
+      for (; k < n; k += groups) {
+        const float* p = src + (size_t)L.item[k] * S + o;
+#pragma unroll
+        for (int x = 0; x < VEC; ++x) acc[x] += p[x];
+      }
+#pragma unroll
+      for (int x = 0; x < VEC; ++x) red[tid * VEC + x] = acc[x];
+      __syncthreads();
+      if (grp == 0 && on) {
+        for (int p = 1; p < groups; ++p)
+#pragma unroll
+          for (int x = 0; x < VEC; ++x) acc[x] += red[(p * lanes + lane) * VEC + x];
+#pragma unroll
+        for (int x = 0; x < VEC; ++x)
+          G[o + x] = updated_entry<RULE>(G[o + x], acc[x], lr, ada, ADA ? St + o + x : nullptr,
+                                         ADAM ? Vt + o + x : nullptr);
+      }
+      __syncthreads();
+    }
+  };
+  if (S % 4 == 0) sum(std::integral_constant<int, 4>{});
+  else sum(std::integral_constant<int, 1>{});
+}
+
+// ---------------------------------------------------------------------------------------------
+// Consecutive table rows, shapes with d2 = 4, r1 = r2 = R, d3 in {4, 8} and d1 a multiple of four.
+// A wavefront owns NP neighbouring prefixes (of one slab of four G1 rows each) and a run of i3: it
+// forms their products P (16 x R), keeps them in registers as one matrix-core operand, and streams
+// G3 past them; the product is taken transposed, (i3,j3) x (j1,j2), so that the four accumulator
+// elements of a lane are neighbours in the row and a wavefront's 16-byte stores cover whole rows.
+// Bound by the row stores.
+template <int R>
+constexpr int table_np() { return R >= 128 ? 1 : R >= 64 ? 2 : 4; }
+
+template <int R, int D3>
+__global__ __launch_bounds__(kDThreads) void k_table_mfma(
+    int n2, int n3, int ns, int first, int count, int vp0, int nvp, int nseg, int seg_tiles,
+    const float* __restrict__ g1, const float* __restrict__ g2, const float* __restrict__ g3,
+    float* __restrict__ out) {
+  constexpr int W = 4 * R, S1 = 4 * R, S2 = R * W, S3 = R * D3, D = 16 * D3, UPT = 16 / D3, KQ = R / 4;
+  constexpr int NP = table_np<R>(), PS = R + 4, VEC = W >= 128 ? 2 : 1;
+  __shared__ __align__(16) float pl[kDWaves][16 * PS];
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), lane = threadIdx.x % kWave;
+  const int l16 = lane % 16, kg = lane / 16;
+  const int unit = blockIdx.x * kDWaves + w;
+  const int group = unit / nseg, seg = unit - group * nseg;
+  const int x0 = group * NP;
+  if (x0 >= nvp) return;
+  const int t0 = seg * seg_tiles, t1 = min(t0 + seg_tiles, (n3 + UPT - 1) / UPT);
+  float b[NP][KQ];
+  float* orow[NP];
+  int row0[NP];      // first row of the prefix, counted from `first`
+  bool any = false;
+#pragma unroll
+  for (int x = 0; x < NP; ++x) {
+    const int vp = vp0 + min(x0 + x, nvp - 1);
+    const int prefix = vp / ns, h = vp - prefix * ns;
+    row0[x] = x0 + x < nvp ? prefix * n3 - first : INT32_MIN / 2;
+    orow[x] = out + (ptrdiff_t)(prefix * n3 - first) * ns * D + (size_t)h * D + l16 * D3 + (4 * kg) % D3;
+    // rows [row0 + t0*UPT, row0 + t1*UPT) meet [0, count)
+    any = any || (row0[x] + t0 * UPT < count && row0[x] + t1 * UPT > 0);
+  }
+  if (!any) return;
+#pragma unroll
+  for (int x = 0; x < NP; ++x) {
+    const int vp = vp0 + min(x0 + x, nvp - 1);
+    const int prefix = vp / ns, h = vp - prefix * ns, i1 = prefix / n2, i2 = prefix - i1 * n2;
+    prefix_columns<kWave, VEC>(lane, 4, R, W, g1 + (size_t)(i1 * ns + h) * S1, g2 + (size_t)i2 * S2,
+                               [&](int j1, int col, float v) {
+                                 pl[w][(j1 * 4 + col / R) * PS + col % R] = v;
+                               });
+    wave_sync();
+#pragma unroll
+    for (int j = 0; j < KQ; ++j) b[x][j] = pl[w][l16 * PS + KQ * kg + j];
+    wave_sync();
+  }
+  float a[2][KQ];
+  auto fetch = [&](float (&av)[KQ], int t) {
+    const float* p = g3 + (size_t)min(t * UPT + l16 / D3, n3 - 1) * S3 + (KQ * kg) * D3 + l16 % D3;
+#pragma unroll
+    for (int j = 0; j < KQ; ++j) av[j] = p[j * D3];
+  };
+  auto tile = [&](const float (&av)[KQ], int t) {
+    const int i3 = t * UPT + (4 * kg) / D3;
+#pragma unroll
+    for (int x = 0; x < NP; ++x) {
+      f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < KQ; ++j)
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[j], b[x][j], acc, 0, 0, 0);
+      // lane (kg, l16): rows 4*kg .. 4*kg+3 of the tile = four j3 of one i3, column (j1,j2) = l16
+      const int row = row0[x] + i3;
+      if (i3 < n3 && row >= 0 && row < count)
+        __builtin_nontemporal_store(acc, (f4*)(orow[x] + (size_t)i3 * ns * D));
+    }
+  };
+  fetch(a[0], t0);
+  for (int t = t0; t < t1; t += 2) {
+    fetch(a[1], t + 1);
+    tile(a[0], t);
+    if (t + 1 >= t1) break;
+    fetch(a[0], t + 2);
+    tile(a[1], t + 1);
+  }
+}
+
+// The same for any shape: a block owns one prefix and a run of i3; P and the G3 slices of kTableIds
+// ids at a time sit in LDS, every thread forms outputs of the run's rows in order.
+constexpr int kTableIds = 8;
+
+__global__ __launch_bounds__(kDThreads) void k_table_any(Shape sh, int first, int count, int p0, int nseg,
+                                                         int seg_ids, const float* __restrict__ g1,
+                                                         const float* __restrict__ g2,
+                                                         const float* __restrict__ g3,
+                                                         float* __restrict__ out) {
+  extern __shared__ __align__(16) float lds[];
+  const int prefix = p0 + (int)blockIdx.x / nseg, seg = (int)blockIdx.x % nseg;
+  const int ps = sh.r2 + 1;
+  float* cl = lds;                                  // kTableIds G3 slices
+  float* pl = lds + ((kTableIds * sh.S3 + 3) & ~3);
+  const int row0 = prefix * (int)sh.n3 - first;     // table rows before `first` are negative
+  const int a0 = max(seg * seg_ids, -row0), a1 = min(min((seg + 1) * seg_ids, (int)sh.n3), count - row0);
+  if (a0 >= a1) return;
+  const int i1 = prefix / (int)sh.n2, i2 = prefix - i1 * (int)sh.n2;
+  prefix_columns<kDThreads, 1>((int)threadIdx.x, sh.d1, sh.r1, sh.W, g1 + (size_t)i1 * sh.S1,
+                               g2 + (size_t)i2 * sh.S2, [&](int j1, int col, float v) {
+                                 const int j2 = col / sh.r2;
+                                 pl[(j1 * sh.d2 + j2) * ps + col - j2 * sh.r2] = v;
+                               });
+  for (int i3 = a0; i3 < a1; i3 += kTableIds) {
+    const int ids = min(kTableIds, a1 - i3);
+    __syncthreads();
+    const float* C = g3 + (size_t)i3 * sh.S3;
+    for (int i = threadIdx.x; i < ids * sh.S3; i += kDThreads) cl[i] = C[i];
+    __syncthreads();
+    float* o = out + (size_t)(row0 + i3) * sh.D;
+    for (int i = threadIdx.x; i < ids * sh.D; i += kDThreads) {
+      const int id = i / sh.D, e = i - id * sh.D, m = e / sh.d3, j3 = e - m * sh.d3;
+      const float *pr = pl + m * ps, *cc = cl + id * sh.S3 + j3;
+      float acc = 0.f;
+#pragma unroll 8
+      for (int k = 0; k < sh.r2; ++k) acc = fmaf(pr[k], cc[k * sh.d3], acc);
+      __builtin_nontemporal_store(acc, o + i);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// host side
+
+static inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
+
+static int team_waves(const Shape& s) { return s.W > 2 * kWave ? 4 : 1; }
+
+// Largest batch (in items) that takes the index-free kernels; 0 for shapes they do not hold.
+// Every item reads its whole G2 slice, which the sorted path reads once per sixteen prefixes: past
+// kDirectBytes of slices that costs more than the index launches it saves.
+int direct_capacity(const Shape& s) {
+  constexpr int64_t kDirectBytes = (int64_t)64 << 20;
+  const int tw = team_waves(s), teams = kDWaves / tw;
+  if (s.n1 >= 0xffffu) return 0;  // digits are 16-bit
+  if ((size_t)teams * fwd_lds_floats(s) * 4 > kDirectLds ||
+      (size_t)teams * bwd_lds_floats(s, tw * kWave) * 4 > kDirectLds)
+    return 0;
+  return (int)std::min<int64_t>(kDirectMax, kDirectBytes / ((int64_t)s.S2 * 4));
+}
+
+void launch_direct_fwd(const Plan& pl, const DirectBuffers& d, const IdSource& src, int B,
+                       const float* g1, const float* g2, const float* g3, float* out, bool train,
+                       hipStream_t st) {
+  const Shape& s = pl.sh;
+  const int tw = team_waves(s), grid = cdiv(B, kDWaves / tw);
+  const size_t lds = (size_t)(kDWaves / tw) * fwd_lds_floats(s) * sizeof(float);
+  const bool vec = s.W > tw * kWave && s.r2 % 2 == 0;
+#define TT_DF(TW, V, TR)                                                                          \
+  k_direct_fwd<TW, V, TR><<<grid, kDThreads, lds, st>>>(s, src, B, g1, g2, g3, d.key, d.dig, d.stride, \
+                                                        d.P, out)
+  if (tw == 1) {
+    if (vec) { if (train) TT_DF(1, 2, true); else TT_DF(1, 2, false); }
+    else { if (train) TT_DF(1, 1, true); else TT_DF(1, 1, false); }
+  } else {
+    if (vec) { if (train) TT_DF(4, 2, true); else TT_DF(4, 2, false); }
+    else { if (train) TT_DF(4, 1, true); else TT_DF(4, 1, false); }
+  }
+#undef TT_DF
+}
+
+void launch_direct_bwd(const Plan& pl, const DirectBuffers& d, int B, const float* g1, const float* g2,
+                       const float* g3, const float* grad, hipStream_t st) {
+  const Shape& s = pl.sh;
+  const int tw = team_waves(s), grid = cdiv(B, kDWaves / tw);
+  const size_t lds = (size_t)(kDWaves / tw) * bwd_lds_floats(s, tw * kWave) * sizeof(float);
+  if (tw == 1)
+    k_direct_bwd<1><<<grid, kDThreads, lds, st>>>(s, B, d.key, g1, g2, g3, grad, d.P, d.dP, d.g1, d.dg1,
+                                                  d.dg3);
+  else
+    k_direct_bwd<4><<<grid, kDThreads, lds, st>>>(s, B, d.key, g1, g2, g3, grad, d.P, d.dP, d.g1, d.dg1,
+                                                  d.dg3);
+}
+
+void launch_direct_apply(const Plan& pl, const DirectBuffers& d, int B, float* g1, float* g2, float* g3,
+                         float lr, const UpdateRule& ada, hipEvent_t stop, hipStream_t st) {
+  const Shape& s = pl.sh;
+  const bool mfma = s.d1 <= 4 && s.r1 <= 128;
+  const int rt = !mfma ? 0 : s.r1 <= 16 ? 1 : s.r1 <= 32 ? 2 : s.r1 <= 64 ? 4 : 8;
+  const int ct = rt <= 2 && s.W % 32 == 0 ? 2 : 1;
+  const int per2 = mfma ? cdiv(s.W, 16 * ct) : cdiv(s.S2, 128);
+  const int grid = (int)s.n2 * per2 + (int)s.n3 * cdiv(s.S3, 1024) + (int)s.n1 * cdiv(s.S1, 1024);
+#define TT_DA(RT, CT, RULE)                                                                        \
+  do {                                                                                             \
+    if (stop != nullptr)                                                                           \
+      hipExtLaunchKernelGGL((k_direct_apply<RT, CT, RULE>), dim3(grid), dim3(kDThreads), 0, st,    \
+                            nullptr, stop, 0, s, B, lr, ada, (const uint16_t*)d.dig, d.stride,     \
+                            (const float*)d.g1, (const float*)d.dP, (const float*)d.dg1,           \
+                            (const float*)d.dg3, g1, g2, g3);                                      \
+    else                                                                                           \
+      k_direct_apply<RT, CT, RULE><<<grid, kDThreads, 0, st>>>(s, B, lr, ada, d.dig, d.stride, d.g1, \
+                                                               d.dP, d.dg1, d.dg3, g1, g2, g3);    \
+  } while (0)
+#define TT_DR(RT, CT)                                                                              \
+  do {                                                                                             \
+    if (ada.kind == kUpdateAdam) TT_DA(RT, CT, kUpdateAdam);                                       \
+    else if (ada.kind == kUpdateAdagrad) TT_DA(RT, CT, kUpdateAdagrad);                            \
+    else TT_DA(RT, CT, kUpdateSgd);                                                                \
+  } while (0)
+  if (rt == 0) TT_DR(0, 1);
+  else if (rt == 1) { if (ct == 2) TT_DR(1, 2); else TT_DR(1, 1); }
+  else if (rt == 2) { if (ct == 2) TT_DR(2, 2); else TT_DR(2, 1); }
+  else if (rt == 4) TT_DR(4, 1);
+  else TT_DR(8, 1);
+#undef TT_DR
+#undef TT_DA
+}
+
+// Shapes whose product and kTableIds G3 slices fit a block's LDS (else the caller looks the rows up)
+bool table_shape(const Plan& pl) {
+  const Shape& s = pl.sh;
+  return pl.mfma || ((size_t)((kTableIds * s.S3 + 3) & ~3) + (size_t)s.M * (s.r2 + 1)) * 4 <= kDirectLds;
+}
+
+void launch_table(const Plan& pl, const float* g1, const float* g2, const float* g3, int64_t first,
+                  int64_t count, float* out, hipStream_t st) {
+  const Shape& s = pl.sh;
+  const int n3 = (int)s.n3, p0 = (int)(first / n3), np = (int)((first + count - 1) / n3) - p0 + 1;
+  if (pl.mfma) {
+    // enough wavefronts to fill the chip several times over, but no run so short that forming
+    // the products (about R/8 tiles' worth of work) outweighs it
+    const int upt = 16 / s.d3, tiles = cdiv(n3, upt), nvp = np * pl.split;
+    const int per = s.r1 >= 128 ? 1 : s.r1 >= 64 ? 2 : 4, groups = cdiv(nvp, per);
+    const int want = std::max(1, cdiv(8192, groups));
+    const int seg_tiles = std::min(tiles, std::max(cdiv(tiles, want), std::max(2, s.r1 / 8)));
+    const int nseg = cdiv(tiles, seg_tiles);
+    const int grid = cdiv((int64_t)groups * nseg, kDWaves);
+#define TT_TB(RR)                                                                                   \
+  do {                                                                                              \
+    if (s.d3 == 4)                                                                                  \
+      k_table_mfma<RR, 4><<<grid, kDThreads, 0, st>>>((int)s.n2, n3, pl.split, (int)first, (int)count, \
+                                                      p0 * pl.split, nvp, nseg, seg_tiles, g1, g2, g3, out); \
+    else                                                                                            \
+      k_table_mfma<RR, 8><<<grid, kDThreads, 0, st>>>((int)s.n2, n3, pl.split, (int)first, (int)count, \
+                                                      p0 * pl.split, nvp, nseg, seg_tiles, g1, g2, g3, out); \
+  } while (0)
+    switch (s.r1) {
+      case 8: TT_TB(8); break;
+      case 16: TT_TB(16); break;
+      case 32: TT_TB(32); break;
+      case 64: TT_TB(64); break;
+      default: TT_TB(128); break;
+    }
+#undef TT_TB
+    return;
+  }
+  const int want = std::max(1, cdiv(2048, np));
+  const int seg_ids = cdiv(std::max(cdiv(n3, want), kTableIds), kTableIds) * kTableIds;
+  const int nseg = cdiv(n3, seg_ids);
+  const size_t lds = ((size_t)((kTableIds * s.S3 + 3) & ~3) + (size_t)s.M * (s.r2 + 1)) * sizeof(float);
+  k_table_any<<<np * nseg, kDThreads, lds, st>>>(s, (int)first, (int)count, p0, nseg, seg_ids, g1, g2, g3,
+                                                 out);
+}
+
+}  // namespace ttemb

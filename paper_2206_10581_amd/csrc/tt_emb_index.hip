@@ -15,29 +15,6 @@
 
 namespace ttemb {
 
-__device__ __forceinline__ uint32_t key_of_id(const IdSource& src, int idx, uint32_t N) {
-  int pos = idx, slab = 0;
-  if (src.split > 1) {
-    pos = idx / src.split;
-    slab = idx - pos * src.split;
-  }
-  int64_t id = src.ids != nullptr ? src.ids[pos] : src.base + pos;
-  if (src.reindex != nullptr) {
-    // node re-indexing (paper Section 4.2: ids renumbered so that a partition's nodes are
-    // consecutive): one gather in front of the split
-    if ((uint64_t)id >= (uint64_t)src.n_ids) return N;
-    id = src.reindex[id];
-  }
-  // ids outside the table (negative ones included) become the sentinel N and sort to the end
-  if ((uint64_t)id >= (uint64_t)src.rows) return N;
-  if (src.split > 1) {
-    // first-core index i1 -> split*i1 + slab, the other two coordinates stay
-    const int64_t i1 = id / src.n23;
-    id += ((int64_t)(src.split - 1) * i1 + slab) * src.n23;
-  }
-  return (uint32_t)id;
-}
-
 // band of the prefix range [0, Q) that prefix q falls in (single precision: bands only order a
 // schedule, and both users call this one function)
 __device__ __forceinline__ int chunk_band(int q, int Q) {
@@ -47,30 +24,6 @@ __device__ __forceinline__ int chunk_band(int q, int Q) {
 
 // ---------------------------------------------------------------------------------------------
 // block-wide helpers; ldsw holds at least one word per wavefront of the block
-
-// Inclusive prefix sum over the wavefront: inside every row of 16 lanes with cross-lane moves in
-// the vector ALU (row_shr by 1, 2, 4, 8; lanes without a source add zero), then the totals of the
-// rows before a lane's own are added.
-__device__ __forceinline__ uint32_t row_shr_or_zero(uint32_t v, int by) {
-  // by is a compile-time constant after unrolling
-  switch (by) {
-    case 1: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);
-    case 2: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);
-    case 4: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);
-    default: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);
-  }
-}
-__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v, int lane) {
-  v += row_shr_or_zero(v, 1);
-  v += row_shr_or_zero(v, 2);
-  v += row_shr_or_zero(v, 4);
-  v += row_shr_or_zero(v, 8);
-  const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)v, 15);
-  const uint32_t r1 = (uint32_t)__builtin_amdgcn_readlane((int)v, 31);
-  const uint32_t r2 = (uint32_t)__builtin_amdgcn_readlane((int)v, 47);
-  const int row = lane / 16;
-  return v + (row >= 1 ? r0 : 0u) + (row >= 2 ? r1 : 0u) + (row >= 3 ? r2 : 0u);
-}
 
 // Exclusive prefix of v over the block's threads; *total receives the block sum.
 __device__ __forceinline__ uint32_t block_exclusive_scan_value(uint32_t v, uint32_t* ldsw,

@@ -45,6 +45,7 @@ constexpr int kOrderBands = 1024;  // bands of the prefix range the by-i3 chunks
 struct IdSource {
   const int64_t* ids;      // device [B]; nullptr: the consecutive ids base, base+1, ...
   int64_t base;
+  const uint32_t* keys;    // device [items]: keys that an earlier kernel has formed, or nullptr
   const int32_t* reindex;  // device [n_ids] old id -> table row, or nullptr (ids are table rows)
   int64_t n_ids;
   // Slab split (see Plan::split): item idx of the pipeline is slab idx % split of batch position
@@ -86,6 +87,19 @@ struct Counters {
   int nchunk2;  // partial-sum chunks over the by-i2 grouping of unique prefixes
   int err;      // nonzero: a kernel met an impossible index (bit mask of sites)
   int n_split;  // entries beyond the first of their id (U - n_split distinct ids)
+};
+
+// Scratch of the index-free kernels for small batches (tt_emb_direct.hip), sized for
+// Plan::direct_cap items.
+struct DirectBuffers {
+  uint32_t* key;    // item -> table row, or the sentinel N; kept for tt_emb_get_stats
+  uint16_t* dig;    // [3][stride]: i1, i2, i3 of every item, 0xffff for an out-of-range id
+  int stride;       // items per digit row, a multiple of 8
+  float* P;         // prefix product of every item           [cap][PN]
+  float* dP;        // gradient of that product               [cap][PN]
+  float* g1;        // its G1 slice before the update         [cap][S1]
+  float* dg1;       // its term of dG1[i1]                    [cap][S1]
+  float* dg3;       // its term of dG3[i3]                    [cap][S3]
 };
 
 // All device arrays carved out of the caller's workspace.
@@ -133,6 +147,7 @@ struct Workspace {
   float* dg1part;     // per prefix: its term of dG1[i1]      [maxQ][S1]
   float* part3;       // per chunk: partial dG3 slice         [maxChunk3][S3]
   float* part2;       // per chunk: partial dG2 slice         [maxChunk2][S2]
+  DirectBuffers direct;
 };
 
 struct Plan {
@@ -151,6 +166,7 @@ struct Plan {
   int sortBlocksMax, segBlocksMax, uBlocksMax, qBlocksMax, tilesMax;
   int64_t maxChunk3, maxChunk2;
   int keyBits, passes, bitsPerPass;
+  int direct_cap;  // batches of up to this many items take the index-free kernels (0: never)
   // single-wavefront blocks of the per-chunk matrix-core kernels that the device holds at once
   // (forward, backward); asked of the runtime at the first launch, 0 until then
   mutable int unit_slots[2] = {0, 0};
@@ -178,8 +194,84 @@ enum KernelSlot {
   kSlotDg3,
   kSlotPrefixBwd,
   kSlotSgd,
+  kSlotDirectFwd,   // index-free kernels: rows, per-item gradients, sums and update
+  kSlotDirectBwd,
+  kSlotDirectApply,
+  kSlotTable,
   kSlotEventPair,  // an event pair with nothing between: the cost the timing itself adds to a slot
   kSlotCount
 };
+
+__device__ __forceinline__ uint32_t key_of_id(const IdSource& src, int idx, uint32_t N) {
+  if (src.keys != nullptr) return src.keys[idx];
+  int pos = idx, slab = 0;
+  if (src.split > 1) {
+    pos = idx / src.split;
+    slab = idx - pos * src.split;
+  }
+  int64_t id = src.ids != nullptr ? src.ids[pos] : src.base + pos;
+  if (src.reindex != nullptr) {
+    // node re-indexing (paper Section 4.2: ids renumbered so that a partition's nodes are
+    // consecutive): one gather in front of the split
+    if ((uint64_t)id >= (uint64_t)src.n_ids) return N;
+    id = src.reindex[id];
+  }
+  // ids outside the table (negative ones included) become the sentinel N and sort to the end
+  if ((uint64_t)id >= (uint64_t)src.rows) return N;
+  if (src.split > 1) {
+    // first-core index i1 -> split*i1 + slab, the other two coordinates stay
+    const int64_t i1 = id / src.n23;
+    id += ((int64_t)(src.split - 1) * i1 + slab) * src.n23;
+  }
+  return (uint32_t)id;
+}
+
+// One entry of a core under the update rule: the SGD step, the Adagrad step  S += dG^2,
+// G -= lr * dG / (sqrt(S) + eps),  or the Adam step  m = b1 m + (1-b1) dG,
+// v = b2 v + (1-b2) dG^2,  G -= lr * (m corr1) / (sqrt(v corr2) + eps).  St and Vt point at the
+// entry's state (Adagrad sum or Adam first moment; Adam second moment).
+template <int RULE>
+__device__ __forceinline__ float updated_entry(float g_old, float grad, float lr, const UpdateRule& ada,
+                                               float* St, float* Vt) {
+  if constexpr (RULE == kUpdateAdam) {
+    const float m = fmaf(ada.beta1, *St, (1.f - ada.beta1) * grad);
+    const float v = fmaf(ada.beta2, *Vt, (1.f - ada.beta2) * grad * grad);
+    *St = m;
+    *Vt = v;
+    return g_old - lr * (m * ada.corr1) / (sqrtf(v * ada.corr2) + ada.eps);
+  } else if constexpr (RULE == kUpdateAdagrad) {
+    const float sq = fmaf(grad, grad, *St);
+    *St = sq;
+    return g_old - lr * grad / (sqrtf(sq) + ada.eps);
+  } else {
+    return fmaf(-lr, grad, g_old);
+  }
+}
+
+// Inclusive prefix sum over the wavefront: inside every row of 16 lanes with cross-lane moves in
+// the vector ALU (row_shr by 1, 2, 4, 8; lanes without a source add zero), then the totals of the
+// rows before a lane's own are added.
+template <int BY>
+__device__ __forceinline__ uint32_t row_shr_or_zero(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x110 + BY, 0xf, 0xf, false);
+}
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v, int lane) {
+  v += row_shr_or_zero<1>(v);
+  v += row_shr_or_zero<2>(v);
+  v += row_shr_or_zero<4>(v);
+  v += row_shr_or_zero<8>(v);
+  const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)v, 15);
+  const uint32_t r1 = (uint32_t)__builtin_amdgcn_readlane((int)v, 31);
+  const uint32_t r2 = (uint32_t)__builtin_amdgcn_readlane((int)v, 47);
+  const int row = lane / 16;
+  return v + (row >= 1 ? r0 : 0u) + (row >= 2 ? r1 : 0u) + (row >= 3 ? r2 : 0u);
+}
+
+// LDS writes of a wavefront become visible to its own later reads
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 }  // namespace ttemb

@@ -1,0 +1,60 @@
+"""The kernels that need no index structures (small batches, runs of table rows) at the sizes where
+their work is cut: teams of one and four wavefronts, batch sizes around a block of items and around
+the largest batch they take, dimension factors and ranks that leave tiles part empty, runs of rows
+that begin and end inside a prefix.  Oracle and tolerances are those of test_gpu_parity."""
+import numpy as np
+import pytest
+
+from oracle import tt_oracle as ora
+from oracle.tt_oracle import Shape
+from tests.test_gpu_parity import ROW_TOL, check_against_oracle, row_error
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [((5, 6, 7), (2, 2, 2), (4, 4)), ((9, 11, 13), (4, 4, 8), (8, 8)), ((9, 11, 13), (4, 4, 4), (16, 16)),
+          ((9, 11, 13), (4, 4, 8), (32, 32)), ((7, 5, 9), (8, 4, 4), (64, 64)), ((5, 4, 9), (4, 4, 8), (128, 128)),
+          ((8, 7, 6), (4, 5, 5), (32, 32)), ((8, 7, 6), (4, 5, 5), (16, 16)), ((4, 3, 5), (3, 5, 7), (6, 10)),
+          ((4, 3, 5), (5, 3, 2), (7, 3))]
+
+
+def _inputs(n, d, r, B, seed):
+    s = Shape(n, d, r)
+    rng = np.random.default_rng(seed)
+    cores = tuple((rng.standard_normal(c) / np.sqrt(r[0])).astype(np.float32) for c in s.core_shapes())
+    ids = rng.integers(0, s.N, B).astype(np.int64)
+    ids[: B // 4] = ids[0]                                   # a hot id
+    if B > 8:
+        ids[B // 2: B // 2 + 3] = [-1, s.N, 1 << 40]
+    grad = rng.standard_normal((B, s.D)).astype(np.float32)
+    return s, cores, ids, grad
+
+
+@pytest.mark.parametrize("n,d,r", SHAPES)
+@pytest.mark.parametrize("B", [1, 4, 63, 515])
+def test_small_batches(n, d, r, B):
+    _, cores, ids, grad = _inputs(n, d, r, B, 31 * B + r[0])
+    check_against_oracle(n, d, r, cores, ids, grad, 0.01)
+
+
+@pytest.mark.parametrize("n,d,r,B", [((9, 11, 13), (4, 4, 4), (16, 16), 8192), ((9, 11, 13), (4, 4, 4), (16, 16), 8193),
+                                     ((9, 11, 13), (4, 4, 8), (32, 32), 4096), ((9, 11, 13), (4, 4, 8), (32, 32), 4097),
+                                     ((5, 6, 7), (2, 2, 2), (4, 4), 2049), ((5, 6, 7), (2, 2, 2), (4, 4), 8191)])
+def test_around_the_largest_batch(n, d, r, B):
+    _, cores, ids, grad = _inputs(n, d, r, B, B)
+    check_against_oracle(n, d, r, cores, ids, grad, 0.01)
+
+
+@pytest.mark.parametrize("n,d,r", SHAPES + [((3, 5, 136), (4, 4, 8), (32, 32)), ((3, 4, 200), (4, 5, 5), (32, 32))])
+def test_runs_of_table_rows(n, d, r):
+    import torch
+    from paper_2206_10581_amd import TTEmbedding
+    s, cores, _, _ = _inputs(n, d, r, 16, 5)
+    table = ora.forward(s, *cores, np.arange(s.N, dtype=np.int64))
+    emb = TTEmbedding(n, d, r, 10, cores)
+    for first, count in [(0, s.N), (1, 1), (n[2] - 1, 2), (n[2] + 1, n[2] - 2), (s.N - 3, 3), (2, s.N // 2)]:
+        out = torch.full((count + 2, s.D), 7.0, device="cuda")      # rows around the run stay as they are
+        emb.materialize(first, count, out[1:-1])
+        got = out.cpu().numpy()
+        assert row_error(got[1:-1], table[first:first + count]) <= ROW_TOL, (first, count)
+        assert (got[0] == 7).all() and (got[-1] == 7).all()
+    emb.close()
