@@ -220,9 +220,8 @@ static size_t carve(const Plan& pl, char* base, Workspace* ws /* [kSets] or null
   }
   Workspace& w = set[0];
   w.P = (float*)take(mQ * s.PN * 4);
-  w.Pt = w.gsum = w.carry = w.dPsum = w.dg1part = w.part3 = w.part2 = nullptr;
+  w.gsum = w.carry = w.dPsum = w.dg1part = w.part3 = w.part2 = nullptr;
   if (!lookup_only) {
-    if (pl.mfma && s.r1 >= 64) w.Pt = (float*)take(mQ * s.PN * 4);  // ranks with the two-launch backward
     w.gsum = (float*)take(mB * s.D * 4);
     w.carry = (float*)take((size_t)pl.tilesMax * 2 * s.D * 4);
     w.dPsum = (float*)take(mQ * s.PN * 4);
@@ -246,7 +245,6 @@ static size_t carve(const Plan& pl, char* base, Workspace* ws /* [kSets] or null
   for (int i = sets; i < kSets; ++i) set[i] = set[0];
   for (int i = 1; i < sets; ++i) {
     set[i].P = w.P;
-    set[i].Pt = w.Pt;
     set[i].gsum = w.gsum;
     set[i].carry = w.carry;
     set[i].dPsum = w.dPsum;

@@ -613,7 +613,7 @@ __global__ __launch_bounds__(kThreads) void k_prefix_bwd(Shape sh, const float* 
 // every group walks its share in list order, so the order of each sum is fixed by the list length.
 // Jobs: n3*cdiv(S3, span) for G3, then n2*cdiv(S2, span) for G2, then n1*cdiv(S1, span) for G1.
 template <int VEC, int RULE>
-__global__ __launch_bounds__(kThreads) void k_sgd(Shape sh, float lr, UpdateRule ada,
+__global__ __launch_bounds__(kThreads) void k_sgd(Shape sh, float lr, UpdateRule ada, bool grouped2,
                                                   float* __restrict__ g1,
                                                   float* __restrict__ g2, float* __restrict__ g3,
                                                   const float* __restrict__ part3,
@@ -631,12 +631,13 @@ __global__ __launch_bounds__(kThreads) void k_sgd(Shape sh, float lr, UpdateRule
   const int64_t jobs3 = (int64_t)sh.n3 * sp3, jobs2 = (int64_t)sh.n2 * sp2,
                 jobs1 = (int64_t)sh.n1 * sp1;
   for (int64_t job = blockIdx.x; job < jobs3 + jobs2 + jobs1; job += gridDim.x) {
-    const float* src;  // partial k of the list lives at src + k*S
+    const float* src;  // the partial of list entry k lives at src + k*S
     float* G;
     float* St = nullptr;  // state of the slice: Adagrad sums or Adam first moments
     float* Vt = nullptr;  // Adam second moments
     constexpr bool ADA = RULE != kUpdateSgd, ADAM = RULE == kUpdateAdam;
     int l0, l1, o0, S;
+    int grp = 1;  // partials of G2 may stand for several chunks each (wide_group)
     if (job < jobs3) {
       const int bin = (int)(job / sp3);
       o0 = (int)(job % sp3) * kSpan;
@@ -654,6 +655,7 @@ __global__ __launch_bounds__(kThreads) void k_sgd(Shape sh, float lr, UpdateRule
       l0 = c2_start[bin];
       l1 = c2_start[bin + 1];
       src = part2;
+      if (grouped2) grp = wide_group(ctr->nchunk2, sh.r1);
       S = sh.S2;
       G = g2 + (size_t)bin * sh.S2;
       if (ADA) St = ada.s2 + (size_t)bin * sh.S2;
@@ -671,6 +673,9 @@ __global__ __launch_bounds__(kThreads) void k_sgd(Shape sh, float lr, UpdateRule
       if (ADAM) Vt = ada.v1 + (size_t)i1 * sh.S1;
     }
     if (l1 == l0) continue;  // slice not touched by this batch (uniform for the block)
+    // partial k of the n of this slice: at l0, then at every multiple of grp below l1
+    const int g0 = l0 / grp, n = (l1 - 1) / grp - g0 + 1;
+    auto at = [&](int k) { return (size_t)(k == 0 ? l0 : (g0 + k) * grp) * S; };
     // thread layout: `lanes` threads side by side cover the job's entries, `parts` such groups
     const int cols = min(kSpan, S - o0);
     int lanes = 1;
@@ -686,22 +691,22 @@ __global__ __launch_bounds__(kThreads) void k_sgd(Shape sh, float lr, UpdateRule
       acc[x] = 0.f;
     }
     const float* p = src + o;
-    int k = l0 + part;
-    for (; k + (kUnroll - 1) * parts < l1; k += kUnroll * parts) {
+    int k = part;
+    for (; k + (kUnroll - 1) * parts < n; k += kUnroll * parts) {
       float v[kUnroll][VEC];
 #pragma unroll
       for (int j = 0; j < kUnroll; ++j)
 #pragma unroll
-        for (int x = 0; x < VEC; ++x) v[j][x] = p[(size_t)(k + j * parts) * S + x];
+        for (int x = 0; x < VEC; ++x) v[j][x] = p[at(k + j * parts) + x];
       __builtin_amdgcn_sched_barrier(0);  // all loads of the round are in flight together
 #pragma unroll
       for (int j = 0; j < kUnroll; ++j)
 #pragma unroll
         for (int x = 0; x < VEC; ++x) acc[x] += v[j][x];
     }
-    for (; k < l1; k += parts)
+    for (; k < n; k += parts)
 #pragma unroll
-      for (int x = 0; x < VEC; ++x) acc[x] += p[(size_t)k * S + x];
+      for (int x = 0; x < VEC; ++x) acc[x] += p[at(k) + x];
     if (parts > 1) {
 #pragma unroll
       for (int x = 0; x < VEC; ++x) red[threadIdx.x][x] = acc[x];
@@ -808,18 +813,19 @@ void launch_sgd(const Plan& pl, const Workspace& ws, float* g1, float* g2, float
   const int64_t jobs = (int64_t)s.n3 * cdiv(s.S3, span) + (int64_t)s.n2 * cdiv(s.S2, span) +
                        (int64_t)s.n1 * cdiv(s.S1, span);
   const int grid = grid_for(jobs, 1 << 16);
+  const bool grouped2 = pl.mfma && s.r1 >= 64;  // the shapes of k_prefix_bwd_wide
   // with `stop` the kernel's own completion signal serves as that event: no separate event packet
   // has to pass through the stream behind the kernel
 #define TT_SGD(V, A)                                                                               \
   do {                                                                                             \
     if (stop != nullptr)                                                                           \
       hipExtLaunchKernelGGL((k_sgd<V, A>), dim3(grid), dim3(kThreads), 0, st, nullptr, stop, 0,    \
-                            pl.sh, lr, ada, g1, g2, g3, (const float*)ws.part3,                   \
+                            pl.sh, lr, ada, grouped2, g1, g2, g3, (const float*)ws.part3,         \
                             (const int*)ws.c3_start, (const float*)ws.part2,                      \
                             (const int*)ws.c2_start, (const float*)ws.dg1part,                    \
                             (const int*)ws.g1_first, (const int*)ws.g1_end, ws.ctr);              \
     else                                                                                           \
-      k_sgd<V, A><<<grid, kThreads, 0, st>>>(pl.sh, lr, ada, g1, g2, g3, ws.part3, ws.c3_start,    \
+      k_sgd<V, A><<<grid, kThreads, 0, st>>>(pl.sh, lr, ada, grouped2, g1, g2, g3, ws.part3, ws.c3_start, \
                                              ws.part2, ws.c2_start, ws.dg1part, ws.g1_first,       \
                                              ws.g1_end, ws.ctr);                                   \
   } while (0)

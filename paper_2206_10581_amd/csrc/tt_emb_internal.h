@@ -139,8 +139,6 @@ struct Workspace {
   uint32_t* band_cnt;  // by-i3 chunks per band of their first prefix; directly follows g1_end
   uint32_t* band_cur;  // chunks placed so far per band; directly follows band_cnt [kOrderBands]
   float* P;           // prefix products G1[i1] G2[i2]   [maxQ][PN]
-  float* Pt;          // the same products in the layout the G3-gradient step reads: [maxQ][d2][r2][d1]
-                      // (matrix-core shapes of rank 64 and 128 with a backward pass only, else null)
   float* gsum;        // per unique id, sum of its rows' gradients [maxB][D]
   float* carry;       // per tile: head and tail partial sums [tiles][2][D]
   float* dPsum;       // per prefix: gradient of its product  [maxQ][PN]
@@ -171,6 +169,17 @@ struct Plan {
   // (forward, backward); asked of the runtime at the first launch, 0 until then
   mutable int unit_slots[2] = {0, 0};
 };
+
+// Chunks whose dG2 terms are added up before a partial sum is written, at the ranks of the wide
+// prefix kernels: partials of 64 to 256 KiB each cost more than the products they hold, so a batch
+// with many chunks takes eight per partial, one with few keeps the blocks busy instead.  A partial
+// covers chunks [g*k, g*k+k) of one i2; it is written at the index of its first chunk.
+constexpr int kWideGroup = 8;
+__host__ __device__ inline int wide_group(int nchunk2, int r) {
+  int g = 1;
+  while (g < kWideGroup && nchunk2 * (r / 32) >= 4096 * g) g *= 2;
+  return g;
+}
 
 // The by-i3 chunks are put in prefix order only when the prefix products of a batch of B ids can
 // exceed one XCD's L2 (4 MiB); below that the gathers hit the L2 in any order.

@@ -49,6 +49,9 @@ __device__ __forceinline__ int lane_value(int v, int src) {
   return __builtin_amdgcn_readlane(v, __builtin_amdgcn_readfirstlane(src));
 }
 
+// A value that is the same in all lanes, as a scalar.
+__device__ __forceinline__ int wave_value(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 // One lane's share (VPL consecutive floats, VPL = 1 or 2) of a row, moved with a single
 // non-temporal access: rows of out and grad_out are streamed once and should not displace the
 // intermediates that the path does re-read.
@@ -83,35 +86,30 @@ __device__ __forceinline__ void stream_load(const float* src, float* v) {
 // SIMDs.
 // Units per chunk: two or four side by side over the 32-column tiles of the product (four shorten
 // the kernel at rank 32 by a fifth; splitting the sixteen prefixes of a chunk over units as well
-// only re-reads the G2 slice, which costs more than it gains).
-// (At rank 128 a unit is a single 32 x 32 tile: its two operand strips alone are 128 registers.)
-constexpr int pf_units(int R) { return R >= 128 ? 32 : R >= 32 ? 4 : 2; }
+// only re-reads the G2 slice, which costs more than it gains).  Ranks 64 and 128 take
+// k_prefix_fwd_wide.
+constexpr int pf_units(int R) { return R >= 32 ? 4 : 2; }
 
 template <int R>
 __global__ __launch_bounds__(kWave) void k_prefix_fwd_mfma(
     const float* __restrict__ g1, const float* __restrict__ g2, const int4* __restrict__ c2_item,
-    const int4* __restrict__ c2_desc, float* __restrict__ P, float* __restrict__ Pt,
-    int max_units, const Counters* __restrict__ ctr) {
+    const int4* __restrict__ c2_desc, float* __restrict__ P, const Counters* __restrict__ ctr) {
   constexpr int W = 4 * R, PN = 16 * R, S1 = 4 * R, S2 = R * W, KH = R / 2, NT = W / 32;
   constexpr int kPfUnits = pf_units(R);
   constexpr int UC = kPfUnits < NT ? kPfUnits : NT;  // units side by side over the columns
   constexpr int UM = kPfUnits / UC;                  // 1: both row tiles in one unit, 2: one each
   constexpr int NTH = NT / UC, MTH = 2 / UM;         // column and row tiles of one unit
   const int lane = threadIdx.x, half = lane / 32, l32 = lane % 32;
-  // The grid is sized from an upper bound of the chunk count (the real one is only known on the
-  // device) and capped: a batch with far fewer chunks than its size allows would otherwise spend
-  // its time dispatching empty blocks.  Blocks walk the units with the grid's stride.
-  const int nchunk = ctr->nchunk2;
-  auto do_unit = [&](const int unit) -> bool {  // false: no unit from here on has work
+  // one block per possible unit: the grid never exceeds the tables
+  const int nchunk = ctr->nchunk2, unit = blockIdx.x;
   const int c = unit / kPfUnits, sub = unit % kPfUnits;
   const int nt0 = (sub / UM) * NTH, mt0 = (sub % UM) * MTH;
-  // the chunk's records and descriptor are read together with the count (max_units keeps the
-  // reads inside the tables)
+  // the chunk's records and descriptor are read together with the count
   const int4 item = c2_item[(size_t)c * kChunk2 + lane % kChunk2];
   const int4 desc = c2_desc[c];
-  if (c >= nchunk) return false;
+  if (c >= nchunk) return;
   const int bin = desc.x, cnt = desc.z;
-  if (mt0 * 8 >= cnt) return true;  // the chunk has no prefix in this unit's row tile
+  if (mt0 * 8 >= cnt) return;  // the chunk has no prefix in this unit's row tile
   const float* Bm = g2 + (size_t)bin * S2 + (size_t)(KH * half) * W + nt0 * 32 + l32;
   float b[NTH][KH];
 #pragma unroll
@@ -155,182 +153,246 @@ __global__ __launch_bounds__(kWave) void k_prefix_fwd_mfma(
         const int q = qrow[mt][v / 4];
         if (q >= 0) P[(size_t)q * PN + (v % 4) * W + (nt0 + t) * 32 + l32] = acc[v];
       }
-      // Second copy for the G3-gradient step, which contracts over the 16 rows (j1,j2) of the
-      // product: Pt[q][j2][b][j1], so that a lane of that step finds the four j1 of its (j2, b) in
-      // one 16-byte word.  Accumulator elements 4x .. 4x+3 are j1 = 0..3 of one prefix at column
-      // j2*R + b = (nt0+t)*32 + l32: one vector store per prefix, 512 contiguous bytes per half.
-      if (Pt != nullptr) {
-        const int col = (nt0 + t) * 32 + l32, j2 = col / R, b2 = col % R;
-#pragma unroll
-        for (int x = 0; x < 4; ++x) {
-          const int q = qrow[mt][x];
-          if (q >= 0)
-            *(f4*)&Pt[(size_t)q * PN + j2 * (4 * R) + b2 * 4] =
-                f4{acc[4 * x], acc[4 * x + 1], acc[4 * x + 2], acc[4 * x + 3]};
-        }
-      }
     }
-  }
-  return true;
-  };
-  // rank 64 walks the units with the grid's stride (its grid is capped at what the device holds at
-  // once); the other ranks have one block per possible unit
-  if constexpr (R == 64) {
-    for (int unit = blockIdx.x; unit < max_units; unit += gridDim.x)
-      if (!do_unit(unit)) break;
-  } else {
-    if ((int)blockIdx.x < max_units) (void)do_unit((int)blockIdx.x);
   }
 }
 
 // ---------------------------------------------------------------------------------------------
-// Gradients at prefix level for one by-i2 chunk (<= 16 prefixes q, Bm = G2[i2]).  Work units of a
-// chunk, one single-wavefront block (or one turn of a block's loop) each:
-//   row units  dg1part[q] = dPsum_q Bm^T for the first / second eight prefixes: their dPsum rows
-//              stacked (32 x 4R) times Bm^T (4R x R); at rank 64 one unit per 32 of the R columns
-//   col units  a share of the columns of part2[c] = sum_q G1[i1(q)]^T dPsum_q
-//              ((R x 4 cnt) times (4 cnt x 4R)): halves; eighths at rank 64; at rank 128 halves of
-//              the columns times halves of the rows
-// (Rank 64 is cut finer because its batches often have few chunks: the launch then lasts as long
-// as its longest unit, a chain of dependent load and multiply stages.)
-constexpr int pb_col_units(int R) { return R == 64 ? 8 : 2; }  // units side by side over part2's columns
-constexpr int pb_row_units(int R) { return R == 64 ? 4 : 2; }  // dg1part: two row tiles, at rank 64 times two column tiles
-constexpr int pb_units(int R) { return pb_row_units(R) + pb_col_units(R) * (R >= 128 ? 2 : 1); }
-
+// The same for ranks 64 and 128, where a G2 slice is 64 to 256 KiB and the operand traffic of
+// independent 32 x 32 tiles (8 flops per byte through the L2) is what bounds the kernel.  A block of
+// four wavefronts takes one chunk's 64 rows times 128 columns: the rows are staged in LDS once for
+// all four, every wavefront reads a G2 strip of 32 columns of its own straight into registers and
+// uses each value for both row tiles (32 flops per byte).
+// Rank 128, 308,840 prefixes of n = 480,500,500 (half a million ids, two slabs): 2.83 -> 1.85 ms,
+// 88 TFLOP/s, 2.5 GB written.
 template <int R>
-__global__ __launch_bounds__(kWave) void k_prefix_bwd_mfma(
-    const float* __restrict__ g1, const float* __restrict__ g2, const float* __restrict__ dPsum,
-    const int4* __restrict__ c2_item, const int4* __restrict__ c2_desc, float* __restrict__ dg1part,
-    float* __restrict__ part2, int max_units, Counters* __restrict__ ctr) {
-  constexpr int W = 4 * R, PN = 16 * R, S1 = 4 * R, S2 = R * W;
-  const int lane = threadIdx.x, half = lane / 32, l32 = lane % 32;
-  constexpr int kPbUnits = pb_units(R);
-  // capped grid, units walked with its stride (see k_prefix_fwd_mfma)
-  const int nchunk = ctr->nchunk2;
-  auto do_unit = [&](const int unit) -> bool {  // false: no unit from here on has work
-  const int c = unit / kPbUnits, part = unit % kPbUnits;
-  const int4 item = c2_item[(size_t)c * kChunk2 + lane % kChunk2];
-  const int4 desc = c2_desc[c];
-  if (c >= nchunk) return false;
-  const int bin = desc.x, cnt = desc.z;
-  constexpr int kRowUnits = pb_row_units(R);
-  if (part < kRowUnits && (part % 2) == 1 && cnt <= 8) return true;
-  const bool mine = lane < cnt;  // records past the chunk's count are unwritten
-  const int myq = mine ? item.x : -1;
-  const int myi1 = mine ? item.y : 0;
-  const float* Bm = g2 + (size_t)bin * S2;
-
-  if (part < kRowUnits) {
-    constexpr int KB = W / 64;
-    const int mt = part % 2;
-    const int q = __shfl(myq, mt * 8 + l32 / 4), j1 = l32 % 4;
-    const f4* arow = (const f4*)(dPsum + (size_t)(q >= 0 ? q : 0) * PN + j1 * W + 32 * half);
-    int qrow[4];
+__global__ __launch_bounds__(kMThreads, R >= 128 ? 3 : 4) void k_prefix_fwd_wide(
+    const float* __restrict__ g1, const float* __restrict__ g2, const int4* __restrict__ c2_item,
+    const int4* __restrict__ c2_desc, float* __restrict__ P, const Counters* __restrict__ ctr) {
+  static_assert(R == 64 || R == 128, "columns of a block divide the product");
+  constexpr int W = 4 * R, PN = 16 * R, S1 = 4 * R, S2 = R * W, KH = R / 2;
+  constexpr int UN = W / 128;  // blocks side by side over the columns
+  constexpr int AS = R + 4;    // row stride in LDS: sixteen lanes' 16-byte reads cover all banks
+  __shared__ __align__(16) float As[64 * AS];
+  __shared__ int q_of[kChunk2], i1_of[kChunk2];
+  const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave, half = lane / 32, l32 = lane % 32;
+  const int nunit = ctr->nchunk2 * UN;
+  for (int unit = blockIdx.x; unit < nunit; unit += gridDim.x) {
+    const int c = unit / UN, col = (unit % UN) * 128 + w * 32 + l32;
+    const int4 desc = c2_desc[c];
+    const int cnt = desc.z;
+    __syncthreads();  // the previous unit's readers of As are done
+    if (tid < kChunk2) {
+      // records past the chunk's count are unwritten
+      const int4 item = c2_item[(size_t)c * kChunk2 + min(tid, cnt - 1)];
+      q_of[tid] = item.x;
+      i1_of[tid] = item.y;
+    }
+    const float* Bm = g2 + (size_t)desc.x * S2 + (size_t)(KH * half) * W + col;
+    float b[KH];
 #pragma unroll
-    for (int x = 0; x < 4; ++x) qrow[x] = __shfl(myq, mt * 8 + 2 * x + half);
-    constexpr int NTU = (R + 31) / 32 / (kRowUnits / 2);  // 32-column tiles of this unit
+    for (int j = 0; j < KH; ++j) b[j] = Bm[(size_t)j * W];
+    __syncthreads();
+    // rows of prefixes past the count repeat the last one; they are not stored
+    f4 row[R / 16];
 #pragma unroll
-    for (int nti = 0; nti < NTU; ++nti) {
-      const int n = ((part / 2) * NTU + nti) * 32 + l32;
-      const f4* brow = (const f4*)(Bm + (size_t)(n < R ? n : 0) * W + 32 * half);
-      f4 av[2][8], bv[2][8];
+    for (int i = 0; i < R / 16; ++i) {
+      const int e = tid + i * kMThreads;  // 16-byte word of the 64 rows
+      row[i] = ((const f4*)(g1 + (size_t)wave_value(i1_of[e / R]) * S1))[e % R];
+    }
+    TT_LOADS_DONE();
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        av[0][j] = arow[j];
-        bv[0][j] = brow[j];
-      }
-      TT_LOADS_DONE();
+    for (int i = 0; i < R / 16; ++i) {
+      const int e = (tid + i * kMThreads) * 4;
+      *(f4*)&As[(e / R) * AS + e % R] = row[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) {
+      if (mt * 8 >= cnt) break;
+      const f4* ar = (const f4*)&As[(mt * 32 + l32) * AS + KH * half];
       f16v acc = TT_ZERO16;
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb) {
-        if (kb + 1 < KB) {
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            av[(kb + 1) & 1][j] = arow[(kb + 1) * 16 + j];
-            bv[(kb + 1) & 1][j] = brow[(kb + 1) * 16 + j];
-          }
-          TT_LOADS_DONE();
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          f4 x = av[kb & 1][j], y = bv[kb & 1][j];
-          if (q < 0) x = f4{0.f, 0.f, 0.f, 0.f};
-          if (n >= R) y = f4{0.f, 0.f, 0.f, 0.f};
-          acc = mfma32(x.x, y.x, acc);
-          acc = mfma32(x.y, y.y, acc);
-          acc = mfma32(x.z, y.z, acc);
-          acc = mfma32(x.w, y.w, acc);
-        }
+      for (int j = 0; j < KH / 4; ++j) {
+        const f4 a = ar[j];
+        acc = mfma32(a.x, b[4 * j + 0], acc);
+        acc = mfma32(a.y, b[4 * j + 1], acc);
+        acc = mfma32(a.z, b[4 * j + 2], acc);
+        acc = mfma32(a.w, b[4 * j + 3], acc);
       }
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int qv = qrow[v / 4];
-        if (qv >= 0 && n < R) dg1part[(size_t)qv * S1 + (v % 4) * R + n] = acc[v];
-      }
-    }
-  } else {
-    constexpr int MSPLIT = R >= 128 ? 2 : 1;                // units over the rows of part2
-    constexpr int CU = pb_col_units(R);
-    constexpr int MT = (R + 31) / 32 / MSPLIT, NT = W / 32, NTH = NT / CU;
-    static_assert(NT % CU == 0, "column tiles divide evenly over the units");
-    const int nt0 = ((part - kRowUnits) % CU) * NTH;
-    const int mrow0 = ((part - kRowUnits) / CU) * MT * 32;  // first row of this unit
-    int qh[8], ih[8];  // the eight prefixes whose rows this half of the wavefront feeds as k
-#pragma unroll
-    for (int jq = 0; jq < 8; ++jq) {
-      qh[jq] = __shfl(myq, 8 * half + jq);
-      ih[jq] = __shfl(myi1, 8 * half + jq);
-    }
-    float a[MT][32];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      const int m = mrow0 + mt * 32 + l32;
-#pragma unroll
-      for (int j = 0; j < 32; ++j) a[mt][j] = g1[(size_t)ih[j / 4] * S1 + (j % 4) * R + (m < R ? m : 0)];
-    }
-    float b[2][32];
-#pragma unroll
-    for (int j = 0; j < 32; ++j)
-      b[0][j] = dPsum[(size_t)(qh[j / 4] >= 0 ? qh[j / 4] : 0) * PN + (j % 4) * W + nt0 * 32 + l32];
-    TT_LOADS_DONE();
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      const int m = mrow0 + mt * 32 + l32;
-#pragma unroll
-      for (int j = 0; j < 32; ++j) a[mt][j] = (qh[j / 4] >= 0 && m < R) ? a[mt][j] : 0.f;
-    }
-#pragma unroll
-    for (int t = 0; t < NTH; ++t) {
-      const int n = (nt0 + t) * 32 + l32;
-      if (t + 1 < NTH) {
-#pragma unroll
-        for (int j = 0; j < 32; ++j)
-          b[(t + 1) & 1][j] =
-              dPsum[(size_t)(qh[j / 4] >= 0 ? qh[j / 4] : 0) * PN + (j % 4) * W + n + 32];
-        TT_LOADS_DONE();
-      }
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        f16v acc = TT_ZERO16;
-#pragma unroll
-        for (int j = 0; j < 32; ++j) acc = mfma32(a[mt][j], b[t & 1][j], acc);
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int mrow = mrow0 + mt * 32 + 8 * (v / 4) + 4 * half + (v % 4);
-          if (mrow < R) part2[(size_t)c * S2 + (size_t)mrow * W + n] = acc[v];
-        }
+        const int ql = mt * 8 + 2 * (v / 4) + half;
+        if (ql < cnt) P[(size_t)q_of[ql] * PN + (v % 4) * W + col] = acc[v];
       }
     }
   }
-  return true;
+}
+
+// ---------------------------------------------------------------------------------------------
+// Gradients at prefix level for ranks 64 and 128 (the lower ranks: k_bwd_mid_mfma).  Units of work,
+// one block of four wavefronts each, walked with the grid's stride:
+//   dG2   a group of chunks (wide_group) of one i2 and 128 columns: sum over the prefixes q of
+//         G1[i1(q)]^T dPsum_q, R x 128.  The G1 rows of a chunk are staged in LDS for all four
+//         wavefronts, dPsum goes straight to registers (each value is used for R/32 row tiles and
+//         read once in all), and the sum stays in the accumulators from chunk to chunk.
+//   dG1   a chunk: dg1part[q] = dPsum_q Bm^T, 64 x R with 4R to contract, 64 at a time through LDS
+//         (rows of Bm lie 4R floats apart: read by the lanes directly, every 16-byte load would
+//         touch a line of its own).
+// The dG2 units are the longer ones and come first.
+// Rank 128, 308,840 prefixes of n = 480,500,500: 4.55 -> 3.21 ms (101 TFLOP/s), and the update
+// kernel, which reads an eighth of the dG2 partials, 1.14 -> 0.35 ms.  Rank 64, 1,516 prefixes:
+// 35 -> 25 us.  Two blocks per compute unit at rank 128: three would spill fifty registers.
+template <int R>
+__global__ __launch_bounds__(kMThreads, R >= 128 ? 2 : 3) void k_prefix_bwd_wide(
+    const float* __restrict__ g1, const float* __restrict__ g2, const float* __restrict__ dPsum,
+    const int4* __restrict__ c2_item, const int4* __restrict__ c2_desc, float* __restrict__ dg1part,
+    float* __restrict__ part2, const Counters* __restrict__ ctr) {
+  static_assert(R == 64 || R == 128, "columns of a block divide the slice");
+  constexpr int W = 4 * R, PN = 16 * R, S1 = 4 * R, S2 = R * W, UN = W / 128;
+  constexpr int KD = 64, KS = KD + 4;  // depth of a step of the dG1 product and its LDS row stride
+  constexpr int kLds = 64 * R > (64 + R) * KS ? 64 * R : (64 + R) * KS;
+  __shared__ __align__(16) float L[kLds];
+  __shared__ int q_of[kChunk2], i1_of[kChunk2];
+  const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave, half = lane / 32, l32 = lane % 32;
+  const int nchunk = ctr->nchunk2, grp = wide_group(nchunk, R);
+  const int units2 = (nchunk + grp - 1) / grp * UN, nunit = units2 + nchunk;
+  // records of chunk c; those past its count are unwritten and repeat the last one
+  auto chunk_records = [&](int c, int cnt) {
+    __syncthreads();  // the readers of the previous chunk's records and LDS tiles are done
+    if (tid < kChunk2) {
+      const int4 item = c2_item[(size_t)c * kChunk2 + min(tid, cnt - 1)];
+      q_of[tid] = item.x;
+      i1_of[tid] = item.y;
+    }
+    __syncthreads();
   };
-  // rank 64 walks the units with the grid's stride (its grid is capped at what the device holds at
-  // once); the other ranks have one block per possible unit
-  if constexpr (R == 64) {
-    for (int unit = blockIdx.x; unit < max_units; unit += gridDim.x)
-      if (!do_unit(unit)) break;
-  } else {
-    if ((int)blockIdx.x < max_units) (void)do_unit((int)blockIdx.x);
+  for (int unit = blockIdx.x; unit < nunit; unit += gridDim.x) {
+    if (unit < units2) {
+      constexpr int MT = R / 32;
+      const int c0 = unit / UN * grp, c1 = min(c0 + grp, nchunk);
+      const int col = (unit % UN) * 128 + w * 32 + l32;
+      f16v acc[MT];
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) acc[mt] = TT_ZERO16;
+      int first = c0;  // where the running sum began
+      int4 desc = c2_desc[c0];
+      for (int c = c0; c < c1; ++c) {
+        const int cnt = desc.z, bin = desc.x;
+        chunk_records(c, cnt);
+        // contraction index k = 4*prefix + j1; half h of the wavefront takes k = 2j + h.  Prefixes
+        // past the count count zero (their G1 rows are cleared) and read the last one's dPsum.
+        float b[32];
+#pragma unroll
+        for (int j = 0; j < 32; ++j)
+          b[j] = dPsum[(size_t)wave_value(q_of[j / 2]) * PN + ((2 * j) % 4 + half) * W + col];
+        const int4 next = c2_desc[min(c + 1, nchunk - 1)];
+        f4 row[R / 16];
+#pragma unroll
+        for (int i = 0; i < R / 16; ++i) {
+          const int e = tid + i * kMThreads;
+          row[i] = ((const f4*)(g1 + (size_t)wave_value(i1_of[e / R]) * S1))[e % R];
+          if (e / R >= cnt) row[i] = f4{0.f, 0.f, 0.f, 0.f};
+        }
+        TT_LOADS_DONE();
+        // element (k, m) at L[k*R + (m ^ 32*(k%2))]: the two halves of a read use other banks
+#pragma unroll
+        for (int i = 0; i < R / 16; ++i) {
+          const int e = (tid + i * kMThreads) * 4, k = e / R;
+          *(f4*)&L[k * R + ((e % R) ^ (32 * (k % 2)))] = row[i];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf)
+          if (8 * hf < cnt) {  // uniform: else no prefix of this half of the chunk
+#pragma unroll
+            for (int j = 16 * hf; j < 16 * hf + 16; ++j) {
+#pragma unroll
+              for (int mt = 0; mt < MT; ++mt)
+                acc[mt] = mfma32(L[(2 * j + half) * R + ((mt * 32 + l32) ^ (32 * half))], b[j], acc[mt]);
+              if (j % 4 == 3) TT_LOADS_DONE();  // bounds how far operand reads run ahead (registers)
+            }
+          }
+        if (c + 1 == c1 || next.x != bin) {  // the group or the slice ends here
+          float* dst = part2 + (size_t)first * S2;
+          const uint32_t mine = 4 * half * W + col;
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+              (dst + (mt * 32 + 8 * (v / 4) + v % 4) * W)[mine] = acc[mt][v];
+              acc[mt][v] = 0.f;
+            }
+          first = c + 1;
+        }
+        desc = next;
+      }
+    } else {
+      constexpr int NT = R / 32, MW = NT >= 4 ? 2 : 1;  // row tiles of a wavefront
+      const int c = unit - units2;
+      const int4 desc = c2_desc[c];
+      const int cnt = desc.z;
+      chunk_records(c, cnt);
+      const float* Bm = g2 + (size_t)desc.x * S2;
+      const int nt = w % NT, mt0 = w / NT;
+      float *La = L, *Lb = L + 64 * KS;
+      f4 ra[4], rb[R / 16];
+      auto fetch = [&](int k0) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int e = tid + i * kMThreads, r = e / (KD / 4), k = e % (KD / 4) * 4;
+          ra[i] = *(const f4*)(dPsum + (size_t)wave_value(q_of[r / 4]) * PN + (r % 4) * W + k0 + k);
+        }
+#pragma unroll
+        for (int i = 0; i < R / 16; ++i) {
+          const int e = tid + i * kMThreads, r = e / (KD / 4), k = e % (KD / 4) * 4;
+          rb[i] = *(const f4*)(Bm + (size_t)r * W + k0 + k);
+        }
+      };
+      f16v acc[MW];
+#pragma unroll
+      for (int x = 0; x < MW; ++x) acc[x] = TT_ZERO16;
+      fetch(0);
+#pragma unroll 1
+      for (int k0 = 0; k0 < W; k0 += KD) {
+        if (k0 > 0) __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int e = tid + i * kMThreads;
+          *(f4*)&La[e / (KD / 4) * KS + e % (KD / 4) * 4] = ra[i];
+        }
+#pragma unroll
+        for (int i = 0; i < R / 16; ++i) {
+          const int e = tid + i * kMThreads;
+          *(f4*)&Lb[e / (KD / 4) * KS + e % (KD / 4) * 4] = rb[i];
+        }
+        __syncthreads();
+        if (k0 + KD < W) fetch(k0 + KD);  // in flight while this step is multiplied
+        TT_LOADS_DONE();
+        const f4* br = (const f4*)&Lb[(nt * 32 + l32) * KS + 32 * half];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const f4 y = br[j];
+#pragma unroll
+          for (int x = 0; x < MW; ++x) {
+            const int mt = mt0 + x;
+            const f4 a = ((const f4*)&La[(mt * 32 + l32) * KS + 32 * half])[j];
+            acc[x] = mfma32(a.x, y.x, acc[x]);
+            acc[x] = mfma32(a.y, y.y, acc[x]);
+            acc[x] = mfma32(a.z, y.z, acc[x]);
+            acc[x] = mfma32(a.w, y.w, acc[x]);
+          }
+        }
+      }
+#pragma unroll
+      for (int x = 0; x < MW; ++x)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int ql = (mt0 + x) * 8 + 2 * (v / 4) + half;
+          if (ql < cnt)
+            dg1part[(size_t)q_of[ql] * S1 + (v % 4) * R + nt * 32 + l32] = acc[x][v];
+        }
+    }
   }
 }
 
@@ -466,24 +528,23 @@ __device__ __forceinline__ float row_lane_up(float v) {
 }
 
 // The same partial sum for ranks 64 and 128, where a prefix product is 4 to 8 KiB and the loads
-// above would be 16 to 32 four-byte loads per id.  The contraction runs over the 16 rows m = 4*j1 + j2 of the product; lane group kg takes j2 = kg
-// and the four j1.  The product comes from its second copy Pt[q][j2][b][j1]: one 16-byte load per
-// 16 columns b.  The gradient row (16 x D3, row-major) is read with 4/G loads that together cover
-// it contiguously, G = 16/D3: lane l16 = jj*D3 + j3 of group kg reads g[4*(x*G + jj) + kg][j3], and
-// the lanes j3 < D3 that feed the matrix cores fetch the values of jj > 0 from their row.
+// above would be 16 to 32 four-byte loads per id.  The contraction runs over the 16 rows
+// m = 4*j1 + j2 of the product; lane group kg takes j2 = kg and the four j1.  The columns of the
+// R/16 output tiles are dealt so that a 16-byte load along a row serves four tiles: column l16 of
+// tile 4x + t is b = 64x + 4*l16 + t.  The gradient row (16 x D3, row-major) is read with 4/G loads
+// that together cover it contiguously, G = 16/D3: lane l16 = jj*D3 + j3 of group kg reads
+// g[4*(x*G + jj) + kg][j3], and the lanes j3 < D3 that feed the matrix cores fetch the values of
+// jj > 0 from their row.
 template <int R, int D3, int UB>
-__device__ __forceinline__ void dg3_chunk_pt(
-    int c, const float* __restrict__ Pt, const float* __restrict__ grad,
+__device__ __forceinline__ void dg3_chunk_rows(
+    int c, const float* __restrict__ P, const float* __restrict__ grad,
     const float* __restrict__ gsum, const int2* __restrict__ c3_item,
     const int4* __restrict__ c3_desc, float* __restrict__ part3) {
-  constexpr int PN = 16 * R, S3 = R * D3, D = 16 * D3, NT = (R + 15) / 16;
+  constexpr int PN = 16 * R, S3 = R * D3, D = 16 * D3, NT = R / 16, NX = R / 64;
   constexpr int G = 16 / D3, NL = 4 / G;  // lanes groups per row of 16 lanes; loads per gradient row
   const int lane = threadIdx.x % kWave;
   const int l16 = lane % 16, kg = lane / 16;
   const int j3 = l16 % D3, jj = l16 / D3;
-  // rank 8: half of the 16 columns of the only tile exist; the others load column 0 and are dropped
-  const bool col_on = R >= 16 || l16 < R;
-  const int lcol = col_on ? l16 : 0;
   {
     const int2 item = c3_item[(size_t)c * kChunk3 + lane % kChunk3];
     const int cnt = c3_desc[c].z;
@@ -494,16 +555,18 @@ __device__ __forceinline__ void dg3_chunk_pt(
     for (int nt = 0; nt < NT; ++nt) acc[nt] = f4{0.f, 0.f, 0.f, 0.f};
     for (int i0 = 0; i0 < cnt; i0 += UB) {
       float ld[UB][NL];
-      f4 b[UB][NT];
+      f4 b[UB][NX][4];
 #pragma unroll
       for (int x = 0; x < UB; ++x) {
         const int i = min(i0 + x, cnt - 1);
         const float* gp = grad_row_ptr(lane_value(mycode, i), grad, gsum, D) + kg * D3 + j3;
-        const float* pp = Pt + (size_t)lane_value(myq, i) * PN + kg * (4 * R) + lcol * 4;
+        const float* pp = P + (size_t)lane_value(myq, i) * PN + kg * R + l16 * 4;
 #pragma unroll
         for (int y = 0; y < NL; ++y) ld[x][y] = gp[4 * (y * G + jj) * D3];
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) b[x][nt] = *(const f4*)(pp + nt * 64);
+        for (int y = 0; y < NX; ++y)
+#pragma unroll
+          for (int s = 0; s < 4; ++s) b[x][y][s] = *(const f4*)(pp + y * 64 + s * (4 * R));
       }
       TT_LOADS_DONE();
 #pragma unroll
@@ -525,7 +588,7 @@ __device__ __forceinline__ void dg3_chunk_pt(
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-          for (int s = 0; s < 4; ++s) acc[nt] = mfma16(on ? a[s] : 0.f, b[x][nt][s], acc[nt]);
+          for (int s = 0; s < 4; ++s) acc[nt] = mfma16(on ? a[s] : 0.f, b[x][nt / 4][s][nt % 4], acc[nt]);
       }
     }
     float* dst = part3 + (size_t)c * S3;
@@ -534,7 +597,7 @@ __device__ __forceinline__ void dg3_chunk_pt(
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int o3 = 4 * kg + v;
-        if (o3 < D3 && col_on) dst[(nt * 16 + l16) * D3 + o3] = acc[nt][v];
+        if (o3 < D3) dst[(nt / 4 * 64 + 4 * l16 + nt % 4) * D3 + o3] = acc[nt][v];
       }
   }
 }
@@ -547,7 +610,7 @@ __device__ __forceinline__ void dg3_role(
     const int4* __restrict__ c3_desc, float* __restrict__ part3, const Counters* __restrict__ ctr) {
   const int nchunk = ctr->nchunk3;
   for (int c = wave; c < nchunk; c += nwaves)
-    dg3_chunk_pt<R, D3, UB>(c, P, grad, gsum, c3_item, c3_desc, part3);
+    dg3_chunk_rows<R, D3, UB>(c, P, grad, gsum, c3_item, c3_desc, part3);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1099,45 +1162,45 @@ static int resident_blocks(K kernel, int threads) {
   } else {                                          \
     TT_DISPATCH_R(R_, CALL)                         \
   }
-#define TT_DISPATCH_RD(R_, D3_, CALL)                 \
-  if ((D3_) == 4) {                                   \
-    constexpr int D3 = 4;                             \
-    TT_DISPATCH_R(R_, CALL)                           \
-  } else {                                            \
-    constexpr int D3 = 8;                             \
-    TT_DISPATCH_R(R_, CALL)                           \
-  }
+// Blocks of a wide kernel: no more than the device holds at once, each walks the units with the
+// grid's stride (the bound on the units is known here, their number only on the device: clustered
+// ids leave it thirty times smaller, and dispatching blocks that find nothing costs more than the
+// work).
+template <class K>
+static int wide_grid(int* slots, K kernel, int64_t units) {
+  if (*slots == 0) *slots = resident_blocks(kernel, kMThreads);
+  return grid_cap(units, *slots);
+}
 
 void launch_prefix_fwd_mfma(const Plan& pl, const Workspace& ws, const float* g1, const float* g2,
                             int B, hipStream_t st) {
-  // one block per possible work unit (upper bound from B); blocks past the real count return at once
   const int64_t chunks = cdivi(std::min<int64_t>(B, pl.maxQ), kChunk2) + pl.sh.n2;
-  const int units = (int)(chunks * pf_units(pl.sh.r1));
-  // Rank 64 launches no more blocks than the device holds at once and lets them walk the units: its
-  // batches often have far fewer chunks than their size allows (clustered ids), and the blocks
-  // that would find no work cost more to dispatch than the work itself.  The other ranks measured
-  // better with one block per possible unit.
-  int grid = units;
-  if (pl.sh.r1 == 64) {
-    if (pl.unit_slots[0] == 0) pl.unit_slots[0] = resident_blocks(k_prefix_fwd_mfma<64>, kWave);
-    grid = std::min(units, pl.unit_slots[0]);
+#define TT_PF(RR)                                                                                  \
+  k_prefix_fwd_mfma<RR><<<(int)(chunks * pf_units(RR)), kWave, 0, st>>>(g1, g2, ws.c2_item,        \
+                                                                        ws.c2_desc, ws.P, ws.ctr)
+#define TT_PW(RR)                                                                                  \
+  k_prefix_fwd_wide<RR><<<wide_grid(&pl.unit_slots[0], k_prefix_fwd_wide<RR>, chunks * (4 * RR / 128)), \
+                          kMThreads, 0, st>>>(g1, g2, ws.c2_item, ws.c2_desc, ws.P, ws.ctr)
+  switch (pl.sh.r1) {
+    case 8: TT_PF(8); break;
+    case 16: TT_PF(16); break;
+    case 32: TT_PF(32); break;
+    case 64: TT_PW(64); break;
+    default: TT_PW(128); break;
   }
-  TT_DISPATCH_R8(pl.sh.r1, (k_prefix_fwd_mfma<R><<<grid, kWave, 0, st>>>(
-                               g1, g2, ws.c2_item, ws.c2_desc, ws.P, ws.Pt, units, ws.ctr)));
+#undef TT_PF
+#undef TT_PW
 }
 
 void launch_prefix_bwd_mfma(const Plan& pl, const Workspace& ws, const float* g1, const float* g2,
                             int B, hipStream_t st) {
   const int64_t chunks = cdivi(std::min<int64_t>(B, pl.maxQ), kChunk2) + pl.sh.n2;
-  const int units = (int)(chunks * pb_units(pl.sh.r1));
-  int grid = units;  // as for the forward kernel
-  if (pl.sh.r1 == 64) {
-    if (pl.unit_slots[1] == 0) pl.unit_slots[1] = resident_blocks(k_prefix_bwd_mfma<64>, kWave);
-    grid = std::min(units, pl.unit_slots[1]);
-  }
-  TT_DISPATCH_R(pl.sh.r1, (k_prefix_bwd_mfma<R><<<grid, kWave, 0, st>>>(
-                              g1, g2, ws.dPsum, ws.c2_item, ws.c2_desc, ws.dg1part, ws.part2,
-                              units, ws.ctr)));
+#define TT_PB(RR)                                                                                  \
+  k_prefix_bwd_wide<RR><<<wide_grid(&pl.unit_slots[1], k_prefix_bwd_wide<RR>, chunks * (4 * RR / 128 + 1)), \
+                          kMThreads, 0, st>>>(g1, g2, ws.dPsum, ws.c2_item, ws.c2_desc, ws.dg1part, \
+                                              ws.part2, ws.ctr)
+  if (pl.sh.r1 == 64) TT_PB(64); else TT_PB(128);
+#undef TT_PB
 }
 
 void launch_id_bwd_mfma(const Plan& pl, const Workspace& ws, const float* g3, const float* grad,
@@ -1145,9 +1208,16 @@ void launch_id_bwd_mfma(const Plan& pl, const Workspace& ws, const float* g3, co
   // both roles loop over their work with a stride of half the grid (which must be even)
   const int64_t waves_q = std::min<int64_t>(B, pl.maxQ), waves_c = cdivi(B, chunk3_fill(B)) + (int64_t)pl.sh.n3;
   const int per_role = grid_cap(cdivi(std::max(waves_q, waves_c), kMWaves), kMGridCap);
-  TT_DISPATCH_RD(pl.sh.r1, pl.sh.d3, (k_id_bwd_mfma<R, D3><<<2 * per_role, kMThreads, 0, st>>>(
-                                         g3, ws.Pt, grad, ws.gsum, ws.u_code, ws.u_i3, ws.q_us,
-                                         ws.c3_item, ws.c3_desc, ws.dPsum, ws.part3, ws.ctr)));
+#define TT_ID(RR, DD)                                                                              \
+  k_id_bwd_mfma<RR, DD><<<2 * per_role, kMThreads, 0, st>>>(g3, ws.P, grad, ws.gsum, ws.u_code,    \
+                                                            ws.u_i3, ws.q_us, ws.c3_item,          \
+                                                            ws.c3_desc, ws.dPsum, ws.part3, ws.ctr)
+  if (pl.sh.r1 == 64) {
+    if (pl.sh.d3 == 4) TT_ID(64, 4); else TT_ID(64, 8);
+  } else {
+    if (pl.sh.d3 == 4) TT_ID(128, 4); else TT_ID(128, 8);
+  }
+#undef TT_ID
 }
 
 // true when k_bwd_mid_mfma covers the shape (else: k_id_bwd_mfma followed by k_prefix_bwd_mfma)
