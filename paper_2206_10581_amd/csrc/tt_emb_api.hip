@@ -13,8 +13,8 @@
 namespace ttemb {
 
 // launchers defined next to their kernels
-void launch_sort_pass(const Plan&, const Workspace&, const IdSource& src, int B, int pass, hipStream_t,
-                      int which);
+void launch_sort_pass(const Plan&, const Workspace&, const IdSource& src, int B, int pass, bool beside,
+                      hipStream_t, int which);
 void launch_seg_count(const Plan&, const Workspace&, int B, hipStream_t);
 void launch_seg_write(const Plan&, const Workspace&, int B, hipStream_t);
 void launch_group(const Plan&, const Workspace&, int B, hipStream_t, int which);
@@ -140,10 +140,10 @@ static int make_plan(const tt_emb_config* c, Plan* pl) {
   pl->mfma = mfma_shape(s) && !(c->flags & TT_EMB_FLAG_GENERIC_KERNELS);
   pl->maxB = maxB;
   pl->maxQ = std::min<int64_t>(maxB, n12);
-  pl->sortBlocksMax = (int)cdiv64(pl->maxB, kSortItems);
+  pl->sortBlocksMax = (int)sort_blocks_most(pl->maxB);
   pl->segBlocksMax = (int)cdiv64(pl->maxB, kSegItems);
-  pl->uBlocksMax = (int)cdiv64(pl->maxB, kSortItems);
-  pl->qBlocksMax = (int)cdiv64(pl->maxQ, kSortItems);
+  pl->uBlocksMax = (int)group_blocks_most(pl->maxB, pl->maxB);
+  pl->qBlocksMax = (int)group_blocks_most(pl->maxQ, pl->maxB);
   pl->tilesMax = (int)cdiv64(pl->maxB, kTileSlots);
   pl->maxChunk3 = cdiv64(pl->maxB, kChunk3Min) + s.n3;
   pl->maxChunk2 = cdiv64(pl->maxQ, kChunk2) + s.n2;
@@ -186,7 +186,6 @@ static size_t carve(const Plan& pl, char* base, Workspace* ws /* [kSets] or null
     w.ctr = (Counters*)take(sizeof(Counters));
     for (int k = 0; k < 2; ++k) w.key[k] = (uint32_t*)take(mB * 4);
     for (int k = 0; k < 2; ++k) w.val[k] = (uint32_t*)take(mB * 4);
-    w.cnt = (uint32_t*)take((size_t)pl.sortBlocksMax * kMaxBins * 4);
     w.tot = (uint32_t*)take((size_t)kMaxBins * 4);
     w.seg_nu = (uint32_t*)take((size_t)pl.segBlocksMax * 4);
     w.seg_nq = (uint32_t*)take((size_t)pl.segBlocksMax * 4);
@@ -201,12 +200,16 @@ static size_t carve(const Plan& pl, char* base, Workspace* ws /* [kSets] or null
     w.q_i2 = (int*)take(mQ * 4);
     w.cnt3 = (uint32_t*)take((size_t)pl.uBlocksMax * s.n3 * 4);
     w.cnt2 = (uint32_t*)take((size_t)pl.qBlocksMax * s.n2 * 4);
-    w.g3_list = (int*)take(mB * 4);
+    w.g3_list = lookup_only ? nullptr : (int*)take(mB * 4);
     w.g3_start = (int*)take(((size_t)s.n3 + 1) * 4);
     w.c3_start = (int*)take(((size_t)s.n3 + 1) * 4);
     w.c3_desc = (int4*)take((size_t)pl.maxChunk3 * 16);
-    w.c3_item = (int2*)take((size_t)pl.maxChunk3 * kChunk3 * 8);
-    w.c3_order = (int*)take((size_t)pl.maxChunk3 * 4);
+    // the histograms are last read by the last sort pass, the items first written by the grouping
+    // kernel behind it: one stretch serves both
+    w.c3_item = (int2*)take(std::max((size_t)pl.maxChunk3 * kChunk3 * 8,
+                                     (size_t)pl.sortBlocksMax * kMaxBins * 4));
+    w.cnt = (uint32_t*)w.c3_item;
+    w.c3_order = lookup_only ? nullptr : (int*)take((size_t)pl.maxChunk3 * 4);
     w.g2_list = (int*)take(mQ * 4);
     w.g2_start = (int*)take(((size_t)s.n2 + 1) * 4);
     w.c2_start = (int*)take(((size_t)s.n2 + 1) * 4);
@@ -475,21 +478,21 @@ static int free_set(tt_emb* h, int from) {
 }
 
 // Index pipeline of one batch into index set `set`, on stream st.
-// how: 0 = everything, including the prefix-ordered schedule of the by-i3 chunks (worth its launch
-// only where the pipeline runs beside other work, as in tt_emb_prepare); 1 = no schedule; 2 = a
+// how: 0 = beside other work, as in tt_emb_prepare: everything, including the prefix-ordered schedule
+// of the by-i3 chunks (worth its launch only there), with large sort blocks; 1 = no schedule; 2 = a
 // lookup: the structures that only the backward pass reads (unique ids by i3) are not built either.
 static int run_index(tt_emb* h, int set, const IdSource& src, int B, hipStream_t st, int how) {
   const Plan& pl = h->plan;
   const Workspace& ws = h->ws[set];
   int rc;
   for (int pass = 0; pass < pl.passes; ++pass) {
-    rc = run_slot(h, kSlotSortHist, st, [&] { launch_sort_pass(pl, ws, src, B, pass, st, 0); });
+    rc = run_slot(h, kSlotSortHist, st, [&] { launch_sort_pass(pl, ws, src, B, pass, how == 0, st, 0); });
     if (rc) return rc;
-    if (cdiv64(B, kSortItems) > kFoldScanBlocks) {
-      rc = run_slot(h, kSlotSortScan, st, [&] { launch_sort_pass(pl, ws, src, B, pass, st, 2); });
+    if (!sort_folds(B, how == 0)) {
+      rc = run_slot(h, kSlotSortScan, st, [&] { launch_sort_pass(pl, ws, src, B, pass, how == 0, st, 2); });
       if (rc) return rc;
     }
-    rc = run_slot(h, kSlotSortScatter, st, [&] { launch_sort_pass(pl, ws, src, B, pass, st, 1); });
+    rc = run_slot(h, kSlotSortScatter, st, [&] { launch_sort_pass(pl, ws, src, B, pass, how == 0, st, 1); });
     if (rc) return rc;
   }
   rc = run_slot(h, kSlotSegCount, st, [&] { launch_seg_count(pl, ws, B, st); });

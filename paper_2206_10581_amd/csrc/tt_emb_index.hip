@@ -79,14 +79,15 @@ __device__ __forceinline__ unsigned long long match_digit(int digit, bool valid)
   return ~(((unsigned long long)hi << 32) | lo) & __ballot(valid);
 }
 
+template <int NT>
 struct alignas(16) ScatterLds {
   // per-wavefront bucket counts, later block-local output offsets; two 16-bit buckets per word
-  // (a wavefront owns 256 items and a block 4096, so both fit)
-  uint32_t wh[kSortWaves][kMaxBins / 2];
+  // (a wavefront owns 256 items and a block at most 4096, so both fit)
+  uint32_t wh[NT / kWave][kMaxBins / 2];
   uint32_t tot[kMaxBins];  // bucket totals, then this block's first output per bucket
   uint32_t aux[kMaxBins];  // chunks per bucket, then first chunk per bucket
   uint32_t base[kMaxBins]; // first output of every bucket (all blocks), for chunked passes
-  uint32_t ldsw[kSortWaves];
+  uint32_t ldsw[NT / kWave];
 };
 
 constexpr int kSteps = kSortWaveItems / kWave;  // items per lane
@@ -94,8 +95,8 @@ static_assert((kChunk2 & (kChunk2 - 1)) == 0 && (kChunk3 & (kChunk3 - 1)) == 0 &
                   (kChunk3Min & (kChunk3Min - 1)) == 0,
               "chunk sizes are powers of two: positions inside a bucket are cut with shifts");
 
-// One block's share of a stable counting-sort pass over n_items items (block blk owns items
-// [blk*kSortItems, +kSortItems), wavefront w of it the w-th sixteenth).  With tot != nullptr,
+// One block's share of a stable counting-sort pass over n_items items (block blk of NT threads owns
+// items [blk*4*NT, +4*NT), each of its wavefronts 256 of them in order).  With tot != nullptr,
 // cnt[b][bin] holds, per bucket, the items of blocks before b and tot[bin] the bucket totals (both
 // from a column-scan kernel over the blocks' histograms); with tot == nullptr, cnt holds the
 // blocks' own histograms and every block adds up its columns itself (cheaper than one more launch
@@ -107,21 +108,22 @@ static_assert((kChunk2 & (kChunk2 - 1)) == 0 && (kChunk3 & (kChunk3 - 1)) == 0 &
 // and, for chunk > 0, cuts every bucket into chunks of at most `chunk` items: chunk_desc[c] =
 // {bucket, first item, item count, 0} for all chunks c in bucket order, chunk_starts[bucket] the
 // first chunk of each bucket (bins+1 entries), *n_chunks the number of chunks.
-template <class ItemOps>
-__device__ void stable_scatter_block(ScatterLds& L, int blk, int n_items, int bins,
+template <int NT, class ItemOps>
+__device__ void stable_scatter_block(ScatterLds<NT>& L, int blk, int n_items, int bins,
                                      const uint32_t* __restrict__ cnt,
                                      const uint32_t* __restrict__ tot, ItemOps ops, int* starts,
                                      int chunk, int* chunk_starts, int4* chunk_desc,
                                      int* n_chunks) {
+  constexpr int kItems = sort_items(NT), kWaves = NT / kWave;
   const int tid = threadIdx.x;
-  const int nblk = (n_items + kSortItems - 1) / kSortItems;
+  const int nblk = (n_items + kItems - 1) / kItems;
   const bool publishes = (starts != nullptr && blk == 0);
   const int chunk_sh = chunk > 0 ? 31 - __clz(chunk) : 0;  // chunk sizes are powers of two
   if (blk >= nblk && !publishes) return;  // uniform for the whole block
 
   // items first: their loads overlap the table work below
   const int w = tid / kWave, lane = tid % kWave;
-  const int wbase = blk * kSortItems + w * kSortWaveItems;
+  const int wbase = blk * kItems + w * kSortWaveItems;
   typename ItemOps::Item items[kSteps];
   int digits[kSteps];
 #pragma unroll
@@ -129,10 +131,10 @@ __device__ void stable_scatter_block(ScatterLds& L, int blk, int n_items, int bi
     const int idx = wbase + step * kWave + lane;
     items[step] = ops.load(idx < n_items ? idx : 0);
   }
-  uint32_t before[kMaxBins / kSortThreads];  // items of my buckets in earlier blocks
+  uint32_t before[kMaxBins / NT];  // items of my buckets in earlier blocks
 #pragma unroll
-  for (int k = 0; k < kMaxBins / kSortThreads; ++k) {
-    const int bin = tid + k * kSortThreads;
+  for (int k = 0; k < kMaxBins / NT; ++k) {
+    const int bin = tid + k * NT;
     const int bc = min(bin, bins - 1);
     uint32_t total;
     if (tot != nullptr) {
@@ -171,26 +173,26 @@ __device__ void stable_scatter_block(ScatterLds& L, int blk, int n_items, int bi
   __syncthreads();
   const uint32_t total_items = block_exclusive_scan(L.tot, bins, L.ldsw);
   if (chunk > 0) {
-    for (int bin = tid; bin < bins; bin += kSortThreads) L.base[bin] = L.tot[bin];
+    for (int bin = tid; bin < bins; bin += NT) L.base[bin] = L.tot[bin];
   }
   if (starts != nullptr) {
     if (publishes) {
-      for (int bin = tid; bin < bins; bin += kSortThreads) starts[bin] = (int)L.tot[bin];
+      for (int bin = tid; bin < bins; bin += NT) starts[bin] = (int)L.tot[bin];
       if (tid == 0) starts[bins] = (int)total_items;
     }
     if (chunk > 0) {
       // every participating block takes a share of the chunk descriptors
       const uint32_t total_chunks = block_exclusive_scan(L.aux, bins, L.ldsw);
       if (publishes) {
-        for (int bin = tid; bin < bins; bin += kSortThreads) chunk_starts[bin] = (int)L.aux[bin];
+        for (int bin = tid; bin < bins; bin += NT) chunk_starts[bin] = (int)L.aux[bin];
         if (tid == 0) {
           chunk_starts[bins] = (int)total_chunks;
           *n_chunks = (int)total_chunks;
         }
       }
       const int nshare = max(nblk, 1);
-      for (uint32_t c = (uint32_t)blk * kSortThreads + tid; c < total_chunks;
-           c += (uint32_t)nshare * kSortThreads) {
+      for (uint32_t c = (uint32_t)blk * NT + tid; c < total_chunks;
+           c += (uint32_t)nshare * NT) {
         int lo = 0, hi = bins;  // last bucket whose first chunk is <= c
         while (hi - lo > 1) {
           const int mid = (lo + hi) >> 1;
@@ -206,8 +208,8 @@ __device__ void stable_scatter_block(ScatterLds& L, int blk, int n_items, int bi
   if (blk >= nblk) return;
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < kMaxBins / kSortThreads; ++k) {
-    const int bin = tid + k * kSortThreads;
+  for (int k = 0; k < kMaxBins / NT; ++k) {
+    const int bin = tid + k * NT;
     if (bin < bins) L.tot[bin] += before[k];
   }
   // every wavefront clears its own counters, 16 bytes per lane and write (no barrier: nobody else
@@ -246,10 +248,10 @@ __device__ void stable_scatter_block(ScatterLds& L, int blk, int n_items, int bi
   }
   __syncthreads();
   // per bucket: counts of the wavefronts -> offsets inside the block (one thread per word)
-  for (int word = tid; word < words; word += kSortThreads) {
+  for (int word = tid; word < words; word += NT) {
     uint32_t lo = 0, hi = 0;
 #pragma unroll
-    for (int k = 0; k < kSortWaves; ++k) {
+    for (int k = 0; k < kWaves; ++k) {
       const uint32_t c = L.wh[k][word];
       L.wh[k][word] = lo | (hi << 16);
       lo += c & 0xffffu;
@@ -304,11 +306,11 @@ struct SortOps {
   }
 };
 
-// Bucket counts of one radix digit per block of kSortItems items.  Equal digits inside a
+// Bucket counts of one radix digit per block of sort_items(NT) items.  Equal digits inside a
 // wavefront step are counted with one LDS atomic (a hot id would otherwise serialise thousands of
 // them).  The first pass also clears the tables that later kernels of the same forward add into.
-template <bool FROM_IDS>
-__global__ __launch_bounds__(kSortThreads) void k_sort_hist(
+template <int NT, bool FROM_IDS>
+__global__ __launch_bounds__(NT) void k_sort_hist(
     IdSource src, const uint32_t* __restrict__ kin, int B, uint32_t N, int shift,
     int bits, uint32_t* __restrict__ cnt, uint32_t* zero_a, int zero_a_n, uint32_t* zero_b,
     int zero_b_n, uint32_t* zero_c, int zero_c_n, Counters* ctr) {
@@ -316,7 +318,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_hist(
   const int tid = threadIdx.x, bins = 1 << bits;
   const uint32_t mask = (uint32_t)bins - 1u;
   const int w = tid / kWave, lane = tid % kWave;
-  const int wbase = blockIdx.x * kSortItems + w * kSortWaveItems;
+  const int wbase = blockIdx.x * sort_items(NT) + w * kSortWaveItems;
   uint32_t keys[kSteps];
 #pragma unroll
   for (int step = 0; step < kSteps; ++step) {
@@ -326,7 +328,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_hist(
   }
   __builtin_amdgcn_sched_barrier(0);  // keep the loads together: their latencies overlap
   if (FROM_IDS) {
-    const int gtid = blockIdx.x * kSortThreads + tid, gn = gridDim.x * kSortThreads;
+    const int gtid = blockIdx.x * NT + tid, gn = gridDim.x * NT;
     for (int i = gtid; i < zero_a_n; i += gn) zero_a[i] = 0u;
     for (int i = gtid; i < zero_b_n; i += gn) zero_b[i] = 0u;
     for (int i = gtid; i < zero_c_n; i += gn) zero_c[i] = 0u;
@@ -335,7 +337,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_hist(
       ctr->n_split = 0;
     }
   }
-  for (int i = tid; i < bins; i += kSortThreads) h[i] = 0u;
+  for (int i = tid; i < bins; i += NT) h[i] = 0u;
   __syncthreads();
 #pragma unroll
   for (int step = 0; step < kSteps; ++step) {
@@ -348,51 +350,64 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_hist(
       atomicAdd(&h[digit], (uint32_t)__popcll(peers));
   }
   __syncthreads();
-  for (int i = tid; i < bins; i += kSortThreads) cnt[(size_t)blockIdx.x * bins + i] = h[i];
+  for (int i = tid; i < bins; i += NT) cnt[(size_t)blockIdx.x * bins + i] = h[i];
 }
 
-template <bool FROM_IDS>
-__global__ __launch_bounds__(kSortThreads) void k_sort_scatter(SortOps<FROM_IDS> ops, int B,
+template <int NT, bool FROM_IDS>
+__global__ __launch_bounds__(NT) void k_sort_scatter(SortOps<FROM_IDS> ops, int B,
                                                                int bits,
                                                                const uint32_t* __restrict__ cnt,
                                                                const uint32_t* __restrict__ tot) {
-  __shared__ ScatterLds L;
+  __shared__ ScatterLds<NT> L;
   stable_scatter_block(L, (int)blockIdx.x, B, 1 << bits, cnt, tot, ops, nullptr, 0, nullptr,
                        nullptr, nullptr);
 }
 
 // Turns the blocks' bucket counts cnt[b][bin] into counts of earlier blocks (exclusive scan down
-// each column) and leaves the column totals in tot[bin].  One thread per bucket.
-__device__ __forceinline__ void column_scan(uint32_t* __restrict__ cnt, uint32_t* __restrict__ tot,
-                                            int nblk, int bins, int bin) {
-  uint32_t run = 0;
-  uint32_t* col = cnt + bin;
-  int b2 = 0;
-  for (; b2 + 16 <= nblk; b2 += 16) {
-    uint32_t c[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) c[k] = col[(size_t)(b2 + k) * bins];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      col[(size_t)(b2 + k) * bins] = run;
-      run += c[k];
-    }
-  }
-  for (; b2 < nblk; ++b2) {
-    const uint32_t c = col[(size_t)b2 * bins];
-    col[(size_t)b2 * bins] = run;
-    run += c;
-  }
-  tot[bin] = run;
-}
-
-constexpr int kScanThreads = 64;
-
+// each column) and leaves the column totals in tot[bin].  A block takes 32 buckets (128 bytes of a
+// row) and cuts the rows into 32 runs, one thread per bucket and run: a column of up to 256 rows is
+// eight loads in flight per thread, where one thread per column made a chain of them.
+constexpr int kScanThreads = 1024, kScanBins = 32, kScanRuns = kScanThreads / kScanBins;
+constexpr int kScanRows = 8;  // rows of a run that stay in registers
 __global__ __launch_bounds__(kScanThreads) void k_sort_colscan(uint32_t* __restrict__ cnt,
                                                                uint32_t* __restrict__ tot, int nblk,
                                                                int bins) {
-  const int bin = blockIdx.x * kScanThreads + threadIdx.x;
-  if (bin < bins) column_scan(cnt, tot, nblk, bins, bin);
+  __shared__ uint32_t part[kScanRuns][kScanBins];
+  const int b = threadIdx.x % kScanBins, run = threadIdx.x / kScanBins;
+  const int bin = blockIdx.x * kScanBins + b;
+  const int per = (nblk + kScanRuns - 1) / kScanRuns;
+  const int lo = min(run * per, nblk), hi = min(lo + per, nblk);
+  uint32_t* col = cnt + min(bin, bins - 1);
+  uint32_t c[kScanRows];
+  uint32_t sum = 0;
+  for (int r0 = lo; r0 < hi; r0 += kScanRows) {
+#pragma unroll
+    for (int k = 0; k < kScanRows; ++k) c[k] = col[(size_t)min(r0 + k, hi - 1) * bins];
+#pragma unroll
+    for (int k = 0; k < kScanRows; ++k) sum += r0 + k < hi ? c[k] : 0u;
+  }
+  part[run][b] = sum;
+  __syncthreads();
+  uint32_t before = 0, total = 0;
+#pragma unroll
+  for (int k = 0; k < kScanRuns; ++k) {
+    const uint32_t v = part[k][b];
+    before += k < run ? v : 0u;
+    total += v;
+  }
+  if (bin >= bins) return;
+  if (run == 0) tot[bin] = total;
+  for (int r0 = lo; r0 < hi; r0 += kScanRows) {
+    if (per > kScanRows) {  // a longer run is read again
+#pragma unroll
+      for (int k = 0; k < kScanRows; ++k) c[k] = col[(size_t)min(r0 + k, hi - 1) * bins];
+    }
+#pragma unroll
+    for (int k = 0; k < kScanRows; ++k) {
+      if (r0 + k < hi) col[(size_t)(r0 + k) * bins] = before;
+      before += c[k];
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -454,12 +469,12 @@ __global__ __launch_bounds__(kSegThreads) void k_seg_count(const uint32_t* __res
 }
 
 // Numbers the unique ids and prefixes in sorted order, records their extents and coordinates, and
-// counts them per (block of 4096, i3) resp. (block of 4096, i2) for the grouping pass and per i1.
+// counts them per (group_span, i3) resp. (group_span, i2) for the blocks of the grouping pass and per i1.
 // u_code[u] says where the gradient row of unique id u will be found: >= 0 is the batch position
 // of its only occurrence, -(u+1) means "row u of the per-id sums".
 __global__ __launch_bounds__(kSegThreads) void k_seg_write(
-    const uint32_t* __restrict__ skey, const uint32_t* __restrict__ perm, int B, Shape sh,
-    const uint32_t* __restrict__ seg_nu, const uint32_t* __restrict__ seg_nq, int* __restrict__ s_u,
+    const uint32_t* __restrict__ skey, const uint32_t* __restrict__ perm, int B, int group_span,
+    Shape sh, const uint32_t* __restrict__ seg_nu, const uint32_t* __restrict__ seg_nq, int* __restrict__ s_u,
     int4* __restrict__ s_rec, int* __restrict__ u_rs, int* __restrict__ u_i3, int* __restrict__ u_q, int* __restrict__ u_code,
     int* __restrict__ q_us, int* __restrict__ q_i1, int* __restrict__ q_i2,
     uint32_t* __restrict__ cnt3, uint32_t* __restrict__ cnt2, int* __restrict__ g1_first,
@@ -519,7 +534,7 @@ __global__ __launch_bounds__(kSegThreads) void k_seg_write(
       u_i3[u] = (int)i3;
       u_q[u] = q;
       u_code[u] = f.single[j] ? (int)bpos[j] : -(u + 1);
-      atomicAdd(&cnt3[(size_t)(u / kSortItems) * sh.n3 + i3], 1u);
+      atomicAdd(&cnt3[(size_t)(u / group_span) * sh.n3 + i3], 1u);
     }
     if (f.newq[j]) {
       const uint32_t p = k / sh.n3;  // prefix number i1*n2 + i2
@@ -527,7 +542,7 @@ __global__ __launch_bounds__(kSegThreads) void k_seg_write(
       q_us[q] = u;
       q_i1[q] = (int)i1;
       q_i2[q] = (int)i2;
-      atomicAdd(&cnt2[(size_t)(q / kSortItems) * sh.n2 + i2], 1u);
+      atomicAdd(&cnt2[(size_t)(q / group_span) * sh.n2 + i2], 1u);
       // prefixes are numbered in (i1,i2) order: an i1 owns prefixes [g1_first, g1_end)
       const uint32_t i1_before = (s == 0) ? 0xffffffffu : f.prev[j] / sh.n3 / sh.n2;
       if (i1_before != i1) {
@@ -594,14 +609,15 @@ struct GroupOps2 {
   }
 };
 
-__global__ __launch_bounds__(kSortThreads) void k_group(
+template <int NT>
+__global__ __launch_bounds__(NT) void k_group(
     Shape sh, int u_blocks, int chunk3, const uint32_t* __restrict__ cnt3,
     const uint32_t* __restrict__ cnt2, const int* __restrict__ u_i3, const int* __restrict__ u_code,
     const int* __restrict__ u_q, const int* __restrict__ q_i2, const int* __restrict__ q_i1,
     const int* __restrict__ q_us, int* g3_list, int* g3_start, int* c3_start, int4* c3_desc,
     int2* c3_item, int* g2_list, int* g2_start, int* c2_start, int4* c2_desc, int4* c2_item,
     uint32_t* band_cnt, Counters* ctr) {
-  __shared__ ScatterLds L;
+  __shared__ ScatterLds<NT> L;
   if ((int)blockIdx.x < u_blocks) {
     GroupOps3 ops{u_i3, u_code, u_q, g3_list, c3_item, band_cnt, ctr->Q};
     stable_scatter_block(L, (int)blockIdx.x, ctr->U, (int)sh.n3, cnt3, nullptr, ops, g3_start,
@@ -618,16 +634,15 @@ __global__ __launch_bounds__(kSortThreads) void k_group(
 // gathers one prefix product per id: walking the chunks in this order makes neighbouring
 // wavefronts gather neighbouring products.  Only the schedule depends on it, never a result.
 // The grouping kernel has counted the chunks per band; every block scans those counts for itself.
-__global__ __launch_bounds__(kSortThreads) void k_chunk_order(const int2* __restrict__ c3_item,
+__global__ __launch_bounds__(kOrderBands) void k_chunk_order(const int2* __restrict__ c3_item,
                                                              const uint32_t* __restrict__ band_cnt,
                                                              uint32_t* __restrict__ band_cur,
                                                              int* __restrict__ c3_order,
                                                              const Counters* __restrict__ ctr) {
   __shared__ uint32_t band_at[kOrderBands];
-  __shared__ uint32_t ldsw[kSortWaves];
-  static_assert(kOrderBands == kSortThreads, "one band per thread");
-  const int tid = threadIdx.x, n = ctr->nchunk3, c = blockIdx.x * kSortThreads + tid;
-  if ((int)blockIdx.x * kSortThreads >= n) return;
+  __shared__ uint32_t ldsw[kOrderBands / kWave];
+  const int tid = threadIdx.x, n = ctr->nchunk3, c = blockIdx.x * kOrderBands + tid;
+  if ((int)blockIdx.x * kOrderBands >= n) return;
   const int q = c < n ? c3_item[(size_t)c * kChunk3].y : 0;
   band_at[tid] = band_cnt[tid];
   __syncthreads();
@@ -643,42 +658,49 @@ __global__ __launch_bounds__(kSortThreads) void k_chunk_order(const int2* __rest
 
 static inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
-void launch_sort_pass(const Plan& pl, const Workspace& ws, const IdSource& src, int B, int pass,
-                      hipStream_t st, int which /*0 = histogram, 1 = scatter, 2 = column scan*/) {
-  const int blocks = cdiv(B, kSortItems);
+template <int NT>
+static void sort_pass(const Plan& pl, const Workspace& ws, const IdSource& src, int B, int pass,
+                      bool beside, hipStream_t st, int which) {
+  const int blocks = cdiv(B, sort_items(NT));
   const int shift = pass * pl.bitsPerPass;
   const int bits = std::min(pl.bitsPerPass, pl.keyBits - shift);
   const uint32_t N = pl.sh.N;
-  // with few blocks every scatter block adds up the histogram columns itself: no scan launch
-  const bool folded = blocks <= kFoldScanBlocks;
-  const uint32_t* tot = folded ? nullptr : ws.tot;
+  const uint32_t* tot = sort_folds(B, beside) ? nullptr : ws.tot;
   if (which == 2) {
-    if (!folded)
-      k_sort_colscan<<<cdiv(1 << bits, kScanThreads), kScanThreads, 0, st>>>(ws.cnt, ws.tot, blocks,
-                                                                           1 << bits);
+    k_sort_colscan<<<cdiv(1 << bits, kScanBins), kScanThreads, 0, st>>>(ws.cnt, ws.tot, blocks,
+                                                                       1 << bits);
     return;
   }
   if (pass == 0) {
     if (which == 0) {
-      k_sort_hist<true><<<blocks, kSortThreads, 0, st>>>(
+      k_sort_hist<NT, true><<<blocks, NT, 0, st>>>(
           src, nullptr, B, N, shift, bits, ws.cnt, ws.cnt3, pl.uBlocksMax * (int)pl.sh.n3, ws.cnt2,
           pl.qBlocksMax * (int)pl.sh.n2, (uint32_t*)ws.g1_first,
           2 * (int)pl.sh.n1 + 2 * kOrderBands, ws.ctr);
     } else {
       SortOps<true> ops{src, nullptr, nullptr, ws.key[0], ws.val[0], N, shift, (1u << bits) - 1u};
-      k_sort_scatter<true><<<blocks, kSortThreads, 0, st>>>(ops, B, bits, ws.cnt, tot);
+      k_sort_scatter<NT, true><<<blocks, NT, 0, st>>>(ops, B, bits, ws.cnt, tot);
     }
   } else {
     const int from = (pass - 1) & 1, dst = pass & 1;
     if (which == 0) {
-      k_sort_hist<false><<<blocks, kSortThreads, 0, st>>>(IdSource{}, ws.key[from], B, N, shift, bits,
-                                                          ws.cnt, nullptr, 0, nullptr, 0, nullptr, 0,
-                                                          ws.ctr);
+      k_sort_hist<NT, false><<<blocks, NT, 0, st>>>(IdSource{}, ws.key[from], B, N, shift, bits,
+                                                    ws.cnt, nullptr, 0, nullptr, 0, nullptr, 0,
+                                                    ws.ctr);
     } else {
       SortOps<false> ops{IdSource{}, ws.key[from], ws.val[from], ws.key[dst], ws.val[dst], N, shift,
                          (1u << bits) - 1u};
-      k_sort_scatter<false><<<blocks, kSortThreads, 0, st>>>(ops, B, bits, ws.cnt, tot);
+      k_sort_scatter<NT, false><<<blocks, NT, 0, st>>>(ops, B, bits, ws.cnt, tot);
     }
+  }
+}
+
+void launch_sort_pass(const Plan& pl, const Workspace& ws, const IdSource& src, int B, int pass,
+                      bool beside, hipStream_t st, int which /*0 = histogram, 1 = scatter, 2 = column scan*/) {
+  switch (sort_threads(B, beside)) {
+    case 256: sort_pass<256>(pl, ws, src, B, pass, beside, st, which); break;
+    case 512: sort_pass<512>(pl, ws, src, B, pass, beside, st, which); break;
+    default: sort_pass<1024>(pl, ws, src, B, pass, beside, st, which); break;
   }
 }
 
@@ -691,7 +713,7 @@ void launch_seg_count(const Plan& pl, const Workspace& ws, int B, hipStream_t st
 void launch_seg_write(const Plan& pl, const Workspace& ws, int B, hipStream_t st) {
   const int f = (pl.passes - 1) & 1;
   k_seg_write<<<cdiv(B, kSegItems), kSegThreads, 0, st>>>(
-      ws.key[f], ws.val[f], B, pl.sh, ws.seg_nu, ws.seg_nq, ws.s_u, ws.s_rec, ws.u_rs, ws.u_i3, ws.u_q,
+      ws.key[f], ws.val[f], B, sort_items(group_threads(B)), pl.sh, ws.seg_nu, ws.seg_nq, ws.s_u, ws.s_rec, ws.u_rs, ws.u_i3, ws.u_q,
       ws.u_code, ws.q_us, ws.q_i1, ws.q_i2, ws.cnt3, ws.cnt2, ws.g1_first, ws.g1_end, ws.ctr);
 }
 
@@ -700,15 +722,20 @@ void launch_seg_write(const Plan& pl, const Workspace& ws, int B, hipStream_t st
 // only (all a lookup needs)
 void launch_group(const Plan& pl, const Workspace& ws, int B, hipStream_t st, int which) {
   // blocks are sized from upper bounds (U <= B, Q <= min(B, n1*n2)); surplus blocks return at once
-  const int ub = which == 2 ? 0 : cdiv(B, kSortItems);
-  const int qb = cdiv(std::min((int64_t)B, pl.maxQ), kSortItems);
+  const int threads = group_threads(B), span = sort_items(threads);
+  const int ub = which == 2 ? 0 : cdiv(B, span);
+  const int qb = cdiv(std::min((int64_t)B, pl.maxQ), span);
   const bool ordered = which == 0 && chunks_ordered(pl, B);
-  k_group<<<ub + qb, kSortThreads, 0, st>>>(pl.sh, ub, chunk3_fill(B), ws.cnt3, ws.cnt2, ws.u_i3, ws.u_code, ws.u_q, ws.q_i2, ws.q_i1,
-                                           ws.q_us, ws.g3_list, ws.g3_start, ws.c3_start, ws.c3_desc,
-                                           ws.c3_item, ws.g2_list, ws.g2_start, ws.c2_start,
-                                           ws.c2_desc, ws.c2_item, ordered ? ws.band_cnt : nullptr, ws.ctr);
+  auto launch = [&](auto kernel) {
+    kernel<<<ub + qb, threads, 0, st>>>(
+        pl.sh, ub, chunk3_fill(B), ws.cnt3, ws.cnt2, ws.u_i3, ws.u_code, ws.u_q, ws.q_i2, ws.q_i1,
+        ws.q_us, ws.g3_list, ws.g3_start, ws.c3_start, ws.c3_desc, ws.c3_item, ws.g2_list, ws.g2_start,
+        ws.c2_start, ws.c2_desc, ws.c2_item, ordered ? ws.band_cnt : nullptr, ws.ctr);
+  };
+  if (threads == 512) launch(k_group<512>);
+  else launch(k_group<1024>);
   if (ordered)
-    k_chunk_order<<<cdiv(cdiv(B, chunk3_fill(B)) + (int64_t)pl.sh.n3, kSortThreads), kSortThreads, 0,
+    k_chunk_order<<<cdiv(cdiv(B, chunk3_fill(B)) + (int64_t)pl.sh.n3, kOrderBands), kOrderBands, 0,
                     st>>>(
       ws.c3_item, ws.band_cnt, ws.band_cur, ws.c3_order, ws.ctr);
 }

@@ -11,13 +11,55 @@ namespace ttemb {
 
 constexpr int kWave = 64;
 
-// stable counting-sort blocks: 16 wavefronts, each owning 256 consecutive items of the block
-constexpr int kSortThreads = 1024;
-constexpr int kSortWaves = 16;
+// Stable counting-sort blocks: every wavefront owns 256 consecutive items of its block's run.
 constexpr int kSortWaveItems = 256;
-constexpr int kSortItems = kSortWaves * kSortWaveItems;  // 4096 items per block
+__host__ __device__ constexpr int sort_items(int threads) { return threads / kWave * kSortWaveItems; }
 constexpr int kFoldRows = 16;       // histogram rows a thread keeps in flight while it adds up a column
-constexpr int kFoldScanBlocks = 16;  // sort passes with at most this many blocks need no column-scan launch
+constexpr int kChunk3 = 16;       // record slots per partial sum (chunk) of a G3 slice gradient
+// Batches of up to kSmallBatch rows are cut finer where that puts more wavefronts in flight: by-i3
+// chunks of 8 ids instead of 16 (-3.7 us per step at 200,000 rows, +6..18 us at 500,000), row tiles
+// of 16 slots instead of 32.
+constexpr int kSmallBatch = 1 << 18;
+constexpr int kChunk3Min = 8;
+inline int chunk3_fill(int64_t B) { return B <= kSmallBatch ? kChunk3Min : kChunk3; }
+
+// Threads of a sort block.  A block's time goes into what its wavefronts do between barriers, not
+// into memory: on an idle device smaller blocks on more compute units are faster until the 2048
+// counters per block outweigh them (training step, microseconds with 256 / 512 / 1024 threads:
+// 50,000 ids 113 / - / 118, 100,000 items 126 / - / 139, 200,000 ids 194 / 192 / 197, 500,000 ids
+// - / 404 / 408).  Beside the arithmetic of another batch (tt_emb_prepare) the extra blocks take its
+// compute units instead: 156 / 150 / 145 at 200,000 ids, so there they stay large.
+constexpr int kSort256Most = 1 << 17, kSort512Most = 1 << 19;
+inline int sort_threads(int64_t B, bool beside) {
+  return beside || B > kSort512Most ? 1024 : B > kSort256Most ? 512 : 256;
+}
+// Up to sixteen blocks need no column-scan launch: each adds up the rows itself.
+constexpr int kFoldScanBlocks = 16;
+inline bool sort_folds(int64_t B, bool beside) {
+  return B <= (int64_t)kFoldScanBlocks * sort_items(sort_threads(B, beside));
+}
+inline int64_t sort_blocks(int64_t B) {
+  const int i = sort_items(sort_threads(B, false));
+  return (B + i - 1) / i;
+}
+// most blocks that any batch of up to maxB items is sorted by
+inline int64_t sort_blocks_most(int64_t maxB) {
+  int64_t m = sort_blocks(maxB);
+  for (int64_t b : {(int64_t)kSort256Most, (int64_t)kSort512Most})
+    if (b < maxB && sort_blocks(b) > m) m = sort_blocks(b);
+  return m;
+}
+// Threads of a block of the grouping kernel: 512 where 1024 leave too few blocks (50,000 ids 120 ->
+// 117 us a step, 100,000 items 130 -> 126), 1024 where the blocks, which add up the rows of the
+// histograms themselves, would have twice the rows to add (500,000 ids: 403 against 421).
+inline int group_threads(int64_t B) { return B <= kSmallBatch ? 512 : 1024; }
+// rows that the per-block histograms of `items` list entries can have, for batches of up to maxB
+inline int64_t group_blocks_most(int64_t items, int64_t maxB) {
+  const int64_t most = (items + sort_items(1024) - 1) / sort_items(1024);
+  const int64_t small = items < kSmallBatch ? items : kSmallBatch;
+  const int64_t fine = (small + sort_items(512) - 1) / sort_items(512);
+  return maxB <= kSmallBatch || fine > most ? fine : most;
+}
 constexpr int kMaxBins = 2048;                            // digit / bucket count limit per pass
 
 // The unit of the gradient sums: a run of equal ids is cut at every multiple of kEntrySlots sorted
@@ -31,13 +73,6 @@ constexpr int kSegThreads = 256;
 constexpr int kSegItems = 1024;  // sorted slots per block in the segment kernels (4 per thread)
 
 constexpr int kTileSlots = 32;   // sorted slots per wavefront tile in the row kernels
-constexpr int kChunk3 = 16;       // record slots per partial sum (chunk) of a G3 slice gradient
-// Batches of up to kSmallBatch rows are cut finer where that puts more wavefronts in flight: by-i3
-// chunks of 8 ids instead of 16 (-3.7 us per step at 200,000 rows, +6..18 us at 500,000), row tiles
-// of 16 slots instead of 32.
-constexpr int kSmallBatch = 1 << 18;
-constexpr int kChunk3Min = 8;
-inline int chunk3_fill(int64_t B) { return B <= kSmallBatch ? kChunk3Min : kChunk3; }
 constexpr int kChunk2 = 16;      // unique prefixes per partial sum of a G2 slice gradient
 constexpr int kOrderBands = 1024;  // bands of the prefix range the by-i3 chunks are ordered by
 
@@ -107,7 +142,7 @@ struct Workspace {
   Counters* ctr;
   uint32_t* key[2];   // radix-sort ping-pong keys      [maxB]
   uint32_t* val[2];   // radix-sort ping-pong positions [maxB]
-  uint32_t* cnt;      // per-block digit histograms     [sortBlocks * kMaxBins]
+  uint32_t* cnt;      // per-block digit histograms [sortBlocks * kMaxBins]; shares its memory with c3_item
   uint32_t* tot;      // digit totals of the current pass  [kMaxBins]
   uint32_t* seg_nu;   // new-id flags per segment block     [segBlocks]
   uint32_t* seg_nq;   // new-prefix flags per segment block [segBlocks]
