@@ -159,17 +159,31 @@ __device__ __forceinline__ void wave_gemm(WaveGemmLds& L, int M, int N, int K, F
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = gemm_f4{0.f, 0.f, 0.f, 0.f};
+      // The operands of step k0 + kGemmDepth are fetched while step k0 is multiplied.  Indices are
+      // clamped rather than tested: the loads of a step have no branches between them.
+      float ra[kPer], rb[kPer];
+      auto fetch = [&](int k0) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+          const int e = lane + i * kWave;
+          const int am = m0 + (A_KFAST ? e / kGemmDepth : e % kWaveTile);
+          const int ak = k0 + (A_KFAST ? e % kGemmDepth : e / kWaveTile);
+          const int bn = n0 + (B_KFAST ? e / kGemmDepth : e % kWaveTile);
+          const int bk = k0 + (B_KFAST ? e % kGemmDepth : e / kWaveTile);
+          const float x = fa(min(am, M - 1), min(ak, K - 1)), y = fb(min(bk, K - 1), min(bn, N - 1));
+          ra[i] = am < M && ak < K ? x : 0.f;
+          rb[i] = bn < N && bk < K ? y : 0.f;
+        }
+      };
+      fetch(0);
       for (int k0 = 0; k0 < K; k0 += kGemmDepth) {
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
           const int e = lane + i * kWave;
-          const int ak = A_KFAST ? e % kGemmDepth : e / kWaveTile;
-          const int am = A_KFAST ? e / kGemmDepth : e % kWaveTile;
-          L.a[ak][am] = (m0 + am < M && k0 + ak < K) ? fa(m0 + am, k0 + ak) : 0.f;
-          const int bk = B_KFAST ? e % kGemmDepth : e / kWaveTile;
-          const int bn = B_KFAST ? e / kGemmDepth : e % kWaveTile;
-          L.b[bk][bn] = (n0 + bn < N && k0 + bk < K) ? fb(k0 + bk, n0 + bn) : 0.f;
+          L.a[A_KFAST ? e % kGemmDepth : e / kWaveTile][A_KFAST ? e / kGemmDepth : e % kWaveTile] = ra[i];
+          L.b[B_KFAST ? e % kGemmDepth : e / kWaveTile][B_KFAST ? e / kGemmDepth : e % kWaveTile] = rb[i];
         }
+        if (k0 + kGemmDepth < K) fetch(k0 + kGemmDepth);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -285,37 +299,91 @@ __global__ __launch_bounds__(kThreads) void k_row_fwd(Shape sh, int B, const flo
 //     most two of those): E is formed again per tile, so a hot id's thousand stores are spread
 //     over thirty wavefronts;
 //   * a tile of out-of-range slots (zero rows).
-// Needs D + M*(r2+1) + S3 floats of LDS per wavefront (blocks have as many wavefronts, up to four,
+// With V4 (r2 a multiple of four) operands move sixteen bytes at a time: P_q and the first 256 floats
+// of the G3 slice are all in flight before the first is needed, the slice is kept transposed, and a
+// lane's product reads four contraction indices per LDS access.  Every element is still formed in
+// index order.
+// Needs row_floats() floats of LDS per wavefront (blocks have as many wavefronts, up to four,
 // as the budget allows); shapes too large for even one take k_row_fwd.
+__host__ __device__ inline int row_pad(const Shape& sh, bool v4) { return sh.r2 + (v4 ? 4 : 1); }
+__host__ __device__ inline int row_floats(const Shape& sh, bool v4) {
+  const int n = sh.M * row_pad(sh, v4) + (v4 ? sh.d3 * row_pad(sh, v4) : sh.S3) + sh.D;
+  return v4 ? (n + 3) / 4 * 4 : n;  // every wavefront's share begins on 16 bytes
+}
+template <bool V4>
 __global__ __launch_bounds__(kThreads) void k_row_fwd_staged(
     Shape sh, int B, const float* __restrict__ g3, const float* __restrict__ P,
     const int* __restrict__ s_u, const uint32_t* __restrict__ perm, const int* __restrict__ u_rs,
     const int* __restrict__ u_i3, const int* __restrict__ u_q, float* __restrict__ out,
     Counters* ctr) {
-  extern __shared__ float lds[];
+  extern __shared__ __align__(16) float lds[];
   const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  const int ps = sh.r2 + 1;
-  float* E = lds + (size_t)w * (sh.D + sh.M * ps + sh.S3);
-  float* Pl = E + sh.D;
+  const int ps = row_pad(sh, V4);
+  float* Pl = lds + (size_t)w * row_floats(sh, V4);
   float* Cl = Pl + sh.M * ps;
+  float* E = Cl + (V4 ? sh.d3 * ps : sh.S3);
   const int U = ctr->U, nvalid = ctr->nvalid;
   const int long_tiles = (nvalid + kTileSlots - 1) / kTileSlots;
   const int zero_tiles = (B - nvalid + kTileSlots - 1) / kTileSlots;
   const int wpb = (int)blockDim.x / kWave;  // fewer wavefronts per block when the operands are large
   const int stride = gridDim.x * wpb;
+  // where a lane's operand pieces go in LDS: the same for every row
+  constexpr int kAhead = 4;
+  int p_to[kAhead], c_to[kAhead];
+  if constexpr (V4) {
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) {
+      const int e = lane + k * kWave, rq = sh.r2 / 4;
+      p_to[k] = (e / rq) * ps + 4 * (e % rq);
+      c_to[k] = (e % sh.d3) * ps + e / sh.d3;
+    }
+  }
   // E = reshape(P_q) * G3[i3] of entry u, left in LDS
   auto form_row = [&](int u) {
     const float* Pq = P + (size_t)u_q[u] * sh.PN;
     const float* C = g3 + (size_t)u_i3[u] * sh.S3;
-    for (int e = lane; e < sh.PN; e += kWave) Pl[(e / sh.r2) * ps + e % sh.r2] = Pq[e];
-    for (int e = lane; e < sh.S3; e += kWave) Cl[e] = C[e];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+    if constexpr (V4) {
+      const gemm_f4* P4 = (const gemm_f4*)Pq;
+      const int n4 = sh.PN / 4, rq = sh.r2 / 4;
+      gemm_f4 p[kAhead];
+      float c[kAhead];
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) p[k] = P4[min(lane + k * kWave, n4 - 1)];
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) c[k] = C[min(lane + k * kWave, sh.S3 - 1)];
+      __builtin_amdgcn_sched_barrier(0);  // the loads stay together: their latencies overlap
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k)
+        if (lane + k * kWave < n4) *(gemm_f4*)(Pl + p_to[k]) = p[k];
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k)
+        if (lane + k * kWave < sh.S3) Cl[c_to[k]] = c[k];
+      for (int e = lane + kAhead * kWave; e < n4; e += kWave)
+        *(gemm_f4*)(Pl + (e / rq) * ps + 4 * (e % rq)) = P4[e];
+      for (int e = lane + kAhead * kWave; e < sh.S3; e += kWave)
+        Cl[(e % sh.d3) * ps + e / sh.d3] = C[e];
+    } else {
+      for (int e = lane; e < sh.PN; e += kWave) Pl[(e / sh.r2) * ps + e % sh.r2] = Pq[e];
+      for (int e = lane; e < sh.S3; e += kWave) Cl[e] = C[e];
+    }
+    wave_sync();
     for (int e = lane; e < sh.D; e += kWave) {
-      const float* pr = Pl + (e / sh.d3) * ps;
-      const float* cc = Cl + e % sh.d3;
       float acc = 0.f;
-      for (int c = 0; c < sh.r2; ++c) acc = fmaf(pr[c], cc[c * sh.d3], acc);
+      if constexpr (V4) {
+        const gemm_f4* pr = (const gemm_f4*)(Pl + (e / sh.d3) * ps);
+        const gemm_f4* cc = (const gemm_f4*)(Cl + (e % sh.d3) * ps);
+        for (int c = 0; c < sh.r2 / 4; ++c) {
+          const gemm_f4 x = pr[c], y = cc[c];
+          acc = fmaf(x.x, y.x, acc);
+          acc = fmaf(x.y, y.y, acc);
+          acc = fmaf(x.z, y.z, acc);
+          acc = fmaf(x.w, y.w, acc);
+        }
+      } else {
+        const float* pr = Pl + (e / sh.d3) * ps;
+        const float* cc = Cl + e % sh.d3;
+        for (int c = 0; c < sh.r2; ++c) acc = fmaf(pr[c], cc[c * sh.d3], acc);
+      }
       E[e] = acc;
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -443,8 +511,14 @@ __global__ __launch_bounds__(kThreads) void k_gsum_fix(Shape sh, const int* __re
 }
 
 // dPsum_q = sum over the unique ids u of prefix q of g_u * G3[i3(u)]^T, g_u read as (d1*d2) x d3:
-// one product per prefix whose contraction index runs over (u, j3), one wavefront per prefix.
-__global__ __launch_bounds__(kThreads) void k_u_bwd(Shape sh, const float* __restrict__ g3,
+// one product per prefix whose contraction index runs over (u, j3), one wavefront per prefix.  The
+// wavefront first puts where the rows of its prefix's first 64 ids lie into LDS: an operand element
+// is then one load behind an LDS read, not a chain of two or three.  A contraction index is split
+// into (u, j3) by a multiplication with inv_d3 = ceil(2^20 / d3), exact while index * d3 < 2^20
+// (the host passes 0 for d3 above 64; ids past the table divide).
+constexpr int kIdTable = kWave;
+__global__ __launch_bounds__(kThreads) void k_u_bwd(Shape sh, uint32_t inv_d3,
+                                                    const float* __restrict__ g3,
                                                     const float* __restrict__ grad,
                                                     const float* __restrict__ gsum,
                                                     const int* __restrict__ u_code,
@@ -453,17 +527,38 @@ __global__ __launch_bounds__(kThreads) void k_u_bwd(Shape sh, const float* __res
                                                     float* __restrict__ dPsum,
                                                     const Counters* __restrict__ ctr) {
   __shared__ WaveGemmLds L[kWavesPerBlock];
-  const int Q = ctr->Q, w = threadIdx.x / kWave;
+  __shared__ const float* g_at[kWavesPerBlock][kIdTable];  // gradient row of the prefix's t-th id
+  __shared__ const float* c_at[kWavesPerBlock][kIdTable];  // its G3 slice
+  const int Q = ctr->Q, w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   for (int q = blockIdx.x * kWavesPerBlock + w; q < Q; q += gridDim.x * kWavesPerBlock) {
     const int u0 = q_us[q], u1 = q_us[q + 1];
     float* dst = dPsum + (size_t)q * sh.PN;
-    wave_gemm<true, true>(
-        L[w], sh.M, sh.r2, (u1 - u0) * sh.d3,
-        [&](int m, int k) {
-          return grad_of_unique(u0 + k / sh.d3, u_code, grad, gsum, sh.D)[m * sh.d3 + k % sh.d3];
-        },
-        [&](int k, int n) { return g3[(size_t)u_i3[u0 + k / sh.d3] * sh.S3 + n * sh.d3 + k % sh.d3]; },
-        [&](int m, int n, float v) { dst[m * sh.r2 + n] = v; });
+    if (u0 + lane < u1) {
+      g_at[w][lane] = grad_of_unique(u0 + lane, u_code, grad, gsum, sh.D);
+      c_at[w][lane] = g3 + (size_t)u_i3[u0 + lane] * sh.S3;
+    }
+    wave_sync();
+    auto product = [&](auto ga, auto ca, auto split) {
+      wave_gemm<true, true>(
+          L[w], sh.M, sh.r2, (u1 - u0) * sh.d3,
+          [&](int m, int k) {
+            const int t = split(k);
+            return ga(t)[m * sh.d3 + (k - t * sh.d3)];
+          },
+          [&](int k, int n) {
+            const int t = split(k);
+            return ca(t)[n * sh.d3 + (k - t * sh.d3)];
+          },
+          [&](int m, int n, float v) { dst[m * sh.r2 + n] = v; });
+    };
+    if (u1 - u0 <= kIdTable && inv_d3 != 0)  // uniform for the wavefront
+      product([&](int t) { return g_at[w][t]; }, [&](int t) { return c_at[w][t]; },
+              [&](int k) { return (int)(((uint32_t)k * inv_d3) >> 20); });
+    else
+      product([&](int t) { return grad_of_unique(u0 + t, u_code, grad, gsum, sh.D); },
+              [&](int t) { return g3 + (size_t)u_i3[u0 + t] * sh.S3; },
+              [&](int k) { return k / sh.d3; });
+    wave_sync();  // the table is read before the next prefix overwrites it
   }
 }
 
@@ -749,14 +844,21 @@ void launch_row_fwd(const Plan& pl, const Workspace& ws, const float* g3, int B,
   const int tiles = cdiv(B, kTileSlots);
   const int grid = grid_for(cdiv(tiles, kWavesPerBlock), kGridCap);
   const Shape& s = pl.sh;
-  const size_t per_wave = ((size_t)s.D + (size_t)s.M * (s.r2 + 1) + s.S3) * sizeof(float);
+  const bool v4 = s.r2 % 4 == 0 && (size_t)row_floats(s, true) * sizeof(float) <= kLdsBudget;
+  const size_t per_wave = (size_t)row_floats(s, v4) * sizeof(float);
   if (per_wave <= kLdsBudget) {
     const int wpb = (int)std::min<size_t>(kWavesPerBlock, kLdsBudget / per_wave);
     const size_t staged = wpb * per_wave;
     // one wavefront per distinct id (at most B of them) and per tile of slots
     const int jobs = B + cdiv(B, kTileSlots) + 1;
-    k_row_fwd_staged<<<grid_for(cdiv(jobs, wpb), kGridCap * 4), wpb * kWave, staged, st>>>(
-        s, B, g3, ws.P, ws.s_u, ws.val[(pl.passes - 1) & 1], ws.u_rs, ws.u_i3, ws.u_q, out, ws.ctr);
+    const int blocks = grid_for(cdiv(jobs, wpb), kGridCap * 4);
+    const uint32_t* perm = ws.val[(pl.passes - 1) & 1];
+    if (v4)
+      k_row_fwd_staged<true><<<blocks, wpb * kWave, staged, st>>>(s, B, g3, ws.P, ws.s_u, perm, ws.u_rs,
+                                                                  ws.u_i3, ws.u_q, out, ws.ctr);
+    else
+      k_row_fwd_staged<false><<<blocks, wpb * kWave, staged, st>>>(s, B, g3, ws.P, ws.s_u, perm, ws.u_rs,
+                                                                   ws.u_i3, ws.u_q, out, ws.ctr);
     return;
   }
   const size_t lds = (size_t)kWavesPerBlock * pl.sh.D * sizeof(float);
@@ -781,7 +883,8 @@ void launch_gsum_fix(const Plan& pl, const Workspace& ws, int B, hipStream_t st)
 void launch_u_bwd(const Plan& pl, const Workspace& ws, const float* g3, const float* grad, int B,
                   hipStream_t st) {
   const int grid = grid_for(cdiv(std::min<int64_t>(B, pl.maxQ), kWavesPerBlock), kGridCap * 4);
-  k_u_bwd<<<grid, kThreads, 0, st>>>(pl.sh, g3, grad, ws.gsum, ws.u_code, ws.u_i3, ws.q_us, ws.dPsum,
+  const uint32_t inv = pl.sh.d3 <= 64 ? ((1u << 20) + (uint32_t)pl.sh.d3 - 1) / (uint32_t)pl.sh.d3 : 0u;
+  k_u_bwd<<<grid, kThreads, 0, st>>>(pl.sh, inv, g3, grad, ws.gsum, ws.u_code, ws.u_i3, ws.q_us, ws.dPsum,
                                      ws.ctr);
 }
 
