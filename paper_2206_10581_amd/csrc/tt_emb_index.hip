@@ -713,7 +713,7 @@ void launch_seg_count(const Plan& pl, const Workspace& ws, int B, hipStream_t st
 void launch_seg_write(const Plan& pl, const Workspace& ws, int B, hipStream_t st) {
   const int f = (pl.passes - 1) & 1;
   k_seg_write<<<cdiv(B, kSegItems), kSegThreads, 0, st>>>(
-      ws.key[f], ws.val[f], B, sort_items(group_threads(B)), pl.sh, ws.seg_nu, ws.seg_nq, ws.s_u, ws.s_rec, ws.u_rs, ws.u_i3, ws.u_q,
+      ws.key[f], ws.val[f], B, sort_items(group_threads(pl.sh, B)), pl.sh, ws.seg_nu, ws.seg_nq, ws.s_u, ws.s_rec, ws.u_rs, ws.u_i3, ws.u_q,
       ws.u_code, ws.q_us, ws.q_i1, ws.q_i2, ws.cnt3, ws.cnt2, ws.g1_first, ws.g1_end, ws.ctr);
 }
 
@@ -722,7 +722,7 @@ void launch_seg_write(const Plan& pl, const Workspace& ws, int B, hipStream_t st
 // only (all a lookup needs)
 void launch_group(const Plan& pl, const Workspace& ws, int B, hipStream_t st, int which) {
   // blocks are sized from upper bounds (U <= B, Q <= min(B, n1*n2)); surplus blocks return at once
-  const int threads = group_threads(B), span = sort_items(threads);
+  const int threads = group_threads(pl.sh, B), span = sort_items(threads);
   const int ub = which == 2 ? 0 : cdiv(B, span);
   const int qb = cdiv(std::min((int64_t)B, pl.maxQ), span);
   const bool ordered = which == 0 && chunks_ordered(pl, B);

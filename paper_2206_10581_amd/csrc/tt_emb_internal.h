@@ -49,17 +49,6 @@ inline int64_t sort_blocks_most(int64_t maxB) {
     if (b < maxB && sort_blocks(b) > m) m = sort_blocks(b);
   return m;
 }
-// Threads of a block of the grouping kernel: 512 where 1024 leave too few blocks (50,000 ids 120 ->
-// 117 us a step, 100,000 items 130 -> 126), 1024 where the blocks, which add up the rows of the
-// histograms themselves, would have twice the rows to add (500,000 ids: 403 against 421).
-inline int group_threads(int64_t B) { return B <= kSmallBatch ? 512 : 1024; }
-// rows that the per-block histograms of `items` list entries can have, for batches of up to maxB
-inline int64_t group_blocks_most(int64_t items, int64_t maxB) {
-  const int64_t most = (items + sort_items(1024) - 1) / sort_items(1024);
-  const int64_t small = items < kSmallBatch ? items : kSmallBatch;
-  const int64_t fine = (small + sort_items(512) - 1) / sort_items(512);
-  return maxB <= kSmallBatch || fine > most ? fine : most;
-}
 constexpr int kMaxBins = 2048;                            // digit / bucket count limit per pass
 
 // The unit of the gradient sums: a run of equal ids is cut at every multiple of kEntrySlots sorted
@@ -113,6 +102,22 @@ struct Shape {
   int S3;  // r2*d3       floats of one G3 slice
 };
 
+// Threads of a block of the grouping kernel: 512 where 1024 leave too few blocks (50,000 ids 120 ->
+// 117 us a step, 100,000 items 130 -> 126), 1024 where the blocks, which add up the rows of the
+// histograms themselves, would have twice the rows to add (500,000 ids: 403 against 421).
+// Tables with n2 + n3 near the bucket limit keep 1024: their finer histograms would need more memory.
+inline int group_threads(const Shape& sh, int64_t B) {
+  return B <= kSmallBatch && sh.n2 + sh.n3 <= kMaxBins / 8 * 7 ? 512 : 1024;
+}
+// rows that the per-block histograms of `items` list entries can have, for batches of up to maxB
+inline int64_t group_blocks_most(const Shape& sh, int64_t items, int64_t maxB) {
+  const int64_t most = (items + sort_items(1024) - 1) / sort_items(1024);
+  if (group_threads(sh, 1) == 1024) return most;
+  const int64_t small = items < kSmallBatch ? items : kSmallBatch;
+  const int64_t fine = (small + sort_items(512) - 1) / sort_items(512);
+  return maxB <= kSmallBatch || fine > most ? fine : most;
+}
+
 // Device-side counters of the latest forward (first bytes of the workspace).
 struct Counters {
   int U;        // entries: distinct in-range ids, long runs counted once per kEntrySlots piece
@@ -142,7 +147,7 @@ struct Workspace {
   Counters* ctr;
   uint32_t* key[2];   // radix-sort ping-pong keys      [maxB]
   uint32_t* val[2];   // radix-sort ping-pong positions [maxB]
-  uint32_t* cnt;      // per-block digit histograms [sortBlocks * kMaxBins]; shares its memory with c3_item
+  uint32_t* cnt;      // per-block digit histograms [sortBlocks * kMaxBins]; usually in the memory of c3_item
   uint32_t* tot;      // digit totals of the current pass  [kMaxBins]
   uint32_t* seg_nu;   // new-id flags per segment block     [segBlocks]
   uint32_t* seg_nq;   // new-prefix flags per segment block [segBlocks]
