@@ -214,8 +214,41 @@ __device__ __forceinline__ void wave_gemm(WaveGemmLds& L, int M, int N, int K, F
 // ---------------------------------------------------------------------------------------------
 // forward
 
+// Rows of a by-i2 chunk's stacked d1 x * operands: row r belongs to prefix r / d1 of the chunk, line
+// r % d1 of its slice.  q[r] is the row's number in the per-prefix arrays read as lines (prefix*d1 +
+// line), g1[r] in the first core (i1*d1 + line).
+constexpr int kRowTable = 256;  // chunks of more rows (d1 above 16) divide per element
+struct ChunkRows {
+  int64_t q[kRowTable], g1[kRowTable];
+};
+// Fills the table and calls body(q_line, g1_line), functions of a row number.  For a whole block,
+// with the same chunk in every thread; cnt items of d1 rows each.
+template <class Body>
+__device__ __forceinline__ void with_chunk_rows(ChunkRows& T, const int4* __restrict__ item, int cnt,
+                                                int d1, Body body) {
+  const int rows = cnt * d1;
+  if (rows <= kRowTable) {
+    __syncthreads();  // the previous chunk's rows have been read
+    for (int r = threadIdx.x; r < rows; r += kThreads) {
+      const int t = r / d1, line = r - t * d1;
+      const int4 it = item[t];
+      T.q[r] = (int64_t)it.x * d1 + line;
+      T.g1[r] = (int64_t)it.y * d1 + line;
+    }
+    __syncthreads();
+    body([&](int r) { return T.q[r]; }, [&](int r) { return T.g1[r]; });
+  } else {
+    body([&](int r) { return (int64_t)item[r / d1].x * d1 + r % d1; },
+         [&](int r) { return (int64_t)item[r / d1].y * d1 + r % d1; });
+  }
+}
+
 // P_q = A * Bm, A = G1[i1] (d1 x r1), Bm = G2[i2] (r1 x d2*r2), for the <= 16 prefixes of one
-// by-i2 chunk at a time: their A stacked are the rows of one product with the shared Bm.
+// by-i2 chunk at a time: their A stacked are the rows of one product with the shared Bm.  A block
+// takes one run of kGemmTile columns of a chunk: the kernel is bound by a block's chain of load,
+// barrier and product, and a batch has too few chunks to hide it behind others (38 -> 26 us with
+// 200,000 ids of (125,140,140) x (4,5,5) at rank 32).  The gradients below stay one block per chunk:
+// cut the same way, its parts read the chunk's dPsum through several L2s (100 -> 131 us).
 __global__ __launch_bounds__(kThreads) void k_prefix_fwd(Shape sh, const float* __restrict__ g1,
                                                          const float* __restrict__ g2,
                                                          const int4* __restrict__ c2_desc,
@@ -223,24 +256,20 @@ __global__ __launch_bounds__(kThreads) void k_prefix_fwd(Shape sh, const float* 
                                                          float* __restrict__ P,
                                                          const Counters* __restrict__ ctr) {
   __shared__ GemmLds L;
-  __shared__ int q_of[kChunk2], i1_of[kChunk2];
-  const int nchunk = ctr->nchunk2;
-  for (int c = blockIdx.x; c < nchunk; c += gridDim.x) {
+  __shared__ ChunkRows T;
+  const int tiles = (sh.W + kGemmTile - 1) / kGemmTile;
+  const int64_t jobs = (int64_t)ctr->nchunk2 * tiles;
+  for (int64_t job = blockIdx.x; job < jobs; job += gridDim.x) {
+    const int c = (int)(job / tiles), n0 = (int)(job - (int64_t)c * tiles) * kGemmTile;
     const int4 desc = c2_desc[c];
-    const int cnt = desc.z;
-    __syncthreads();  // the previous chunk's readers of q_of / i1_of are done
-    if ((int)threadIdx.x < cnt) {
-      const int4 it = c2_item[(size_t)c * kChunk2 + threadIdx.x];
-      q_of[threadIdx.x] = it.x;
-      i1_of[threadIdx.x] = it.y;
-    }
-    __syncthreads();
-    const float* Bm = g2 + (size_t)desc.x * sh.S2;
-    block_gemm<true, false>(
-        L, cnt * sh.d1, sh.W, sh.r1,
-        [&](int m, int k) { return g1[(size_t)i1_of[m / sh.d1] * sh.S1 + (m % sh.d1) * sh.r1 + k]; },
-        [&](int k, int n) { return Bm[(size_t)k * sh.W + n]; },
-        [&](int m, int n, float v) { P[(size_t)q_of[m / sh.d1] * sh.PN + (m % sh.d1) * sh.W + n] = v; });
+    const float* Bm = g2 + (size_t)desc.x * sh.S2 + n0;
+    with_chunk_rows(T, c2_item + (size_t)c * kChunk2, desc.z, sh.d1, [&](auto q_line, auto g1_line) {
+      block_gemm<true, false>(
+          L, desc.z * sh.d1, min(kGemmTile, sh.W - n0), sh.r1,
+          [&](int m, int k) { return g1[g1_line(m) * sh.r1 + k]; },
+          [&](int k, int n) { return Bm[(size_t)k * sh.W + n]; },
+          [&](int m, int n, float v) { P[q_line(m) * sh.W + n0 + n] = v; });
+    });
   }
 }
 
@@ -835,7 +864,8 @@ constexpr size_t kLdsBudget = 64 * 1024;  // dynamic LDS a block of the staged k
 
 void launch_prefix_fwd(const Plan& pl, const Workspace& ws, const float* g1, const float* g2, int B,
                        hipStream_t st) {
-  const int grid = grid_for(cdiv(std::min<int64_t>(B, pl.maxQ), kChunk2) + pl.sh.n2, kGridCap);
+  const int64_t chunks = cdiv(std::min<int64_t>(B, pl.maxQ), kChunk2) + (int64_t)pl.sh.n2;
+  const int grid = grid_for(chunks * cdiv(pl.sh.W, kGemmTile), kGridCap * 4);
   k_prefix_fwd<<<grid, kThreads, 0, st>>>(pl.sh, g1, g2, ws.c2_desc, ws.c2_item, ws.P, ws.ctr);
 }
 
