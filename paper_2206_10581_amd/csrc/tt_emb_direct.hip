@@ -63,13 +63,18 @@ __device__ __forceinline__ void prefix_columns(int t, int d1, int r1, int W, con
 #pragma unroll
             for (int v = 0; v < VEC; ++v) acc[x][v] = fmaf(arow[x][k + j], b[j][v], acc[x][v]);
       }
-      if (k < r1) {  // the last, shorter round: rows past r1 repeat the last one and count zero
+      if (k < r1) {  // the last, shorter round: rows past r1 read the last one and count zero, in
+                     // both operands (zero times an infinity would not be zero)
         float b[KU][VEC];
 #pragma unroll
         for (int j = 0; j < KU; ++j)
 #pragma unroll
           for (int v = 0; v < VEC; ++v) b[j][v] = bp[(size_t)min(k + j, r1 - 1) * W + v];
         __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < KU; ++j)
+#pragma unroll
+          for (int v = 0; v < VEC; ++v) b[j][v] = k + j < r1 ? b[j][v] : 0.f;
 #pragma unroll
         for (int j = 0; j < KU; ++j)
 #pragma unroll
@@ -387,7 +392,8 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
       constexpr int U = RT >= 4 ? 4 : 8;  // items in flight per wavefront
       const int w = tid / kWave, lane = tid % kWave, l16 = lane % 16, kg = lane / 16;
       const int col0 = piece * 16 * CT;
-      // rows and columns past the slice and rows past d1 read a valid address and count zero
+      // rows and columns past the slice read a valid address and are not stored; rows past d1 count
+      // zero in both operands (zero times an infinity would not be zero)
       const int k1 = min(kg, sh.d1 - 1);
       int ra[RT], cb[CT];
 #pragma unroll
@@ -419,8 +425,8 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
             for (int i = 0; i < RT; ++i)
 #pragma unroll
               for (int j = 0; j < CT; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(kg < sh.d1 ? a[u][i] : 0.f, b[u][j],
-                                                                 acc[i][j], 0, 0, 0);
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                    kg < sh.d1 ? a[u][i] : 0.f, kg < sh.d1 ? b[u][j] : 0.f, acc[i][j], 0, 0, 0);
       }
       // element v of lane (kg, l16) is row 16*i + 4*kg + v, column 16*j + l16
 #pragma unroll

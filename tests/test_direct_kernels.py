@@ -7,7 +7,7 @@ import pytest
 
 from oracle import tt_oracle as ora
 from oracle.tt_oracle import Shape
-from tests.test_gpu_parity import ROW_TOL, check_against_oracle, row_error
+from tests.test_gpu_parity import ROW_TOL, check_against_oracle, row_error, run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -58,3 +58,36 @@ def test_runs_of_table_rows(n, d, r):
         assert row_error(got[1:-1], table[first:first + count]) <= ROW_TOL, (first, count)
         assert (got[0] == 7).all() and (got[-1] == 7).all()
     emb.close()
+
+
+@pytest.mark.parametrize("flags", [0, 2])
+@pytest.mark.parametrize("n,d,r", [((5, 6, 7), (2, 2, 2), (4, 4)), ((4, 3, 5), (3, 5, 7), (7, 10)),
+                                   ((4, 3, 5), (1, 2, 4), (20, 3)), ((4, 3, 5), (5, 3, 2), (18, 3)),
+                                   ((9, 11, 13), (4, 4, 8), (8, 8))])
+def test_infinities_stay_where_they_belong(n, d, r, flags):
+    """An infinity in the last row of a G2 slice reaches the rows of that slice as an infinity, and one
+    in a gradient the slices of its id: operands padded to the size of a tile or a round of loads add
+    nothing, where zero times the repeated value would make them NaN.  The oracle pads nothing."""
+    s, cores, _, grad = _inputs(n, d, r, 40, 3)
+    ids = np.random.default_rng(4).integers(0, s.N, 40).astype(np.int64)
+    first = int(ids[0])
+    i2 = (first // n[2]) % n[1]
+
+    def same_specials(got, ref):
+        got, ref = np.asarray(got, np.float64), np.asarray(ref, np.float64)
+        np.testing.assert_array_equal(np.isnan(got), np.isnan(ref))
+        np.testing.assert_array_equal(np.where(np.isinf(got), np.sign(got), 0), np.where(np.isinf(ref), np.sign(ref), 0))
+
+    hot = [c.copy() for c in cores]
+    hot[1][i2, r[0] - 1, 0, 0] = np.inf
+    ref = ora.forward(s, *hot, ids)
+    assert np.isinf(ref[0]).any() and not np.isnan(ref).any()
+    out, _, _ = run_gpu(n, d, r, hot, ids, grad, 0.0, flags=flags)
+    same_specials(out, ref)
+    g = grad.copy()
+    g[0, s.D - 1] = np.inf                                   # the last row of the (j1,j2) index
+    ref = ora.backward_update(s, *cores, ids, g, 0.01)
+    assert np.isinf(ref[1]).any() and not np.isnan(ref[1]).any()
+    _, new, _ = run_gpu(n, d, r, cores, ids, g, 0.01, flags=flags)
+    for k in range(3):
+        same_specials(new[k], ref[k])
