@@ -235,7 +235,9 @@ __global__ __launch_bounds__(kMThreads, R >= 128 ? 3 : 4) void k_prefix_fwd_wide
 //   dG2   a group of chunks (wide_group) of one i2 and 128 columns: sum over the prefixes q of
 //         G1[i1(q)]^T dPsum_q, R x 128.  The G1 rows of a chunk are staged in LDS for all four
 //         wavefronts, dPsum goes straight to registers (each value is used for R/32 row tiles and
-//         read once in all), and the sum stays in the accumulators from chunk to chunk.
+//         read once in all), and the sum stays in registers from chunk to chunk: a chunk's 64 terms
+//         are one chain, the chunks another (all in one chain, the error of dG2 was 2.1 times as
+//         large at 200,000 uniform ids of rank 64).
 //   dG1   a chunk: dg1part[q] = dPsum_q Bm^T, 64 x R with 4R to contract, 64 at a time through LDS
 //         (rows of Bm lie 4R floats apart: read by the lanes directly, every 16-byte load would
 //         touch a line of its own).
@@ -272,9 +274,9 @@ __global__ __launch_bounds__(kMThreads, R >= 128 ? 2 : 3) void k_prefix_bwd_wide
       constexpr int MT = R / 32;
       const int c0 = unit / UN * grp, c1 = min(c0 + grp, nchunk);
       const int col = (unit % UN) * 128 + w * 32 + l32;
-      f16v acc[MT];
+      f16v sum[MT];
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) acc[mt] = TT_ZERO16;
+      for (int mt = 0; mt < MT; ++mt) sum[mt] = TT_ZERO16;
       int first = c0;  // where the running sum began
       int4 desc = c2_desc[c0];
       for (int c = c0; c < c1; ++c) {
@@ -283,9 +285,10 @@ __global__ __launch_bounds__(kMThreads, R >= 128 ? 2 : 3) void k_prefix_bwd_wide
         // contraction index k = 4*prefix + j1; half h of the wavefront takes k = 2j + h.  Prefixes
         // past the count count zero (their G1 rows are cleared) and read the last one's dPsum.
         float b[32];
+        const uint32_t bo = half * W + col;  // 32-bit offset of the lane from a scalar address
 #pragma unroll
         for (int j = 0; j < 32; ++j)
-          b[j] = dPsum[(size_t)wave_value(q_of[j / 2]) * PN + ((2 * j) % 4 + half) * W + col];
+          b[j] = (dPsum + (size_t)wave_value(q_of[j / 2]) * PN + ((2 * j) % 4) * W)[bo];
         const int4 next = c2_desc[min(c + 1, nchunk - 1)];
         f4 row[R / 16];
 #pragma unroll
@@ -302,17 +305,24 @@ __global__ __launch_bounds__(kMThreads, R >= 128 ? 2 : 3) void k_prefix_bwd_wide
           *(f4*)&L[k * R + ((e % R) ^ (32 * (k % 2)))] = row[i];
         }
         __syncthreads();
+        // two row tiles at a time: their 32 accumulators and all of `sum` fit the registers
 #pragma unroll
-        for (int hf = 0; hf < 2; ++hf)
-          if (8 * hf < cnt) {  // uniform: else no prefix of this half of the chunk
+        for (int m0 = 0; m0 < MT; m0 += 2) {
+          f16v acc[2] = {TT_ZERO16, TT_ZERO16};
 #pragma unroll
-            for (int j = 16 * hf; j < 16 * hf + 16; ++j) {
+          for (int hf = 0; hf < 2; ++hf)
+            if (8 * hf < cnt) {  // uniform: else no prefix of this half of the chunk
 #pragma unroll
-              for (int mt = 0; mt < MT; ++mt)
-                acc[mt] = mfma32(L[(2 * j + half) * R + ((mt * 32 + l32) ^ (32 * half))], b[j], acc[mt]);
-              if (j % 4 == 3) TT_LOADS_DONE();  // bounds how far operand reads run ahead (registers)
+              for (int j = 16 * hf; j < 16 * hf + 16; ++j) {
+#pragma unroll
+                for (int x = 0; x < 2; ++x)
+                  acc[x] = mfma32(L[(2 * j + half) * R + (((m0 + x) * 32 + l32) ^ (32 * half))], b[j], acc[x]);
+                if (j % 4 == 3) TT_LOADS_DONE();  // bounds how far operand reads run ahead (registers)
+              }
             }
-          }
+#pragma unroll
+          for (int x = 0; x < 2; ++x) sum[m0 + x] += acc[x];
+        }
         if (c + 1 == c1 || next.x != bin) {  // the group or the slice ends here
           float* dst = part2 + (size_t)first * S2;
           const uint32_t mine = 4 * half * W + col;
@@ -320,8 +330,8 @@ __global__ __launch_bounds__(kMThreads, R >= 128 ? 2 : 3) void k_prefix_bwd_wide
           for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-              (dst + (mt * 32 + 8 * (v / 4) + v % 4) * W)[mine] = acc[mt][v];
-              acc[mt][v] = 0.f;
+              (dst + (mt * 32 + 8 * (v / 4) + v % 4) * W)[mine] = sum[mt][v];
+              sum[mt][v] = 0.f;
             }
           first = c + 1;
         }
@@ -329,6 +339,10 @@ __global__ __launch_bounds__(kMThreads, R >= 128 ? 2 : 3) void k_prefix_bwd_wide
       }
     } else {
       constexpr int NT = R / 32, MW = NT >= 4 ? 2 : 1;  // row tiles of a wavefront
+      // the thread number anew: nothing derived from it here is kept in registers across the dG2 units
+      int tid = threadIdx.x;
+      asm volatile("" : "+v"(tid));
+      const int w = tid / kWave, half = tid % kWave / 32, l32 = tid % 32;
       const int c = unit - units2;
       const int4 desc = c2_desc[c];
       const int cnt = desc.z;
