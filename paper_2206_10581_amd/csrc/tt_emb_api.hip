@@ -47,6 +47,7 @@ void launch_bwd_mid_mfma(const Plan&, const Workspace&, const float* g1, const f
 void launch_gsum_block(const Plan&, const Workspace&, const float* grad, int B, hipStream_t);
 // index-free kernels (tt_emb_direct.hip)
 int direct_capacity(const Shape&);
+int direct_train_capacity(const Shape&);
 void launch_direct_fwd(const Plan&, const DirectBuffers&, const IdSource&, int B, const float* g1,
                        const float* g2, const float* g3, float* out, bool train, hipStream_t);
 void launch_direct_bwd(const Plan&, const DirectBuffers&, int B, const float* g1, const float* g2,
@@ -153,6 +154,7 @@ static int make_plan(const tt_emb_config* c, Plan* pl) {
   pl->direct_cap = (c->flags & TT_EMB_FLAG_GENERIC_KERNELS)
                        ? 0
                        : (int)std::min<int64_t>(pl->maxB, direct_capacity(s));
+  pl->direct_train_cap = pl->direct_cap == 0 ? 0 : std::min(pl->direct_cap, direct_train_capacity(s));
   return TT_EMB_OK;
 }
 
@@ -232,6 +234,7 @@ static size_t carve(const Plan& pl, char* base, Workspace* ws /* [kSets] or null
     w.band_cur = w.band_cnt + kOrderBands;
   }
   Workspace& w = set[0];
+  const size_t arithmetic = off;
   w.P = (float*)take(mQ * s.PN * 4);
   w.gsum = w.carry = w.dPsum = w.dg1part = w.part3 = w.part2 = nullptr;
   if (!lookup_only) {
@@ -242,12 +245,16 @@ static size_t carve(const Plan& pl, char* base, Workspace* ws /* [kSets] or null
     w.part3 = (float*)take((size_t)pl.maxChunk3 * s.S3 * 4);
     w.part2 = (float*)take((size_t)pl.maxChunk2 * s.S2 * 4);
   }
+  // A batch takes either these kernels or those with index structures, from its forward to its
+  // backward: what they keep lies in the same memory.
+  const size_t indexed_end = off;
+  off = arithmetic;
   w.direct = DirectBuffers{};
   if (!lookup_only && pl.direct_cap > 0) {
-    const size_t cap = ((size_t)pl.direct_cap + 7) & ~(size_t)7;
+    const size_t cap = ((size_t)pl.direct_train_cap + 7) & ~(size_t)7;
     DirectBuffers& d = w.direct;
     d.stride = (int)cap;
-    d.key = (uint32_t*)take(cap * 4);
+    d.key = (uint32_t*)take((size_t)pl.direct_cap * 4);
     d.dig = (uint16_t*)take(cap * 3 * 2);
     d.P = (float*)take(cap * s.PN * 4);
     d.dP = (float*)take(cap * s.PN * 4);
@@ -255,6 +262,7 @@ static size_t carve(const Plan& pl, char* base, Workspace* ws /* [kSets] or null
     d.dg1 = (float*)take(cap * s.S1 * 4);
     d.dg3 = (float*)take(cap * s.S3 * 4);
   }
+  off = std::max(off, indexed_end);
   for (int i = sets; i < kSets; ++i) set[i] = set[0];
   for (int i = 1; i < sets; ++i) {
     set[i].P = w.P;
@@ -525,7 +533,7 @@ int tt_emb_prepare(tt_emb_t h, const int64_t* ids, int64_t B64, void* hip_stream
     int rc0 = setup_side_streams(h);
     if (rc0) return rc0;
   }
-  if (B64 * h->plan.split <= h->plan.direct_cap) return TT_EMB_OK;  // these need no index work
+  if (B64 * h->plan.split <= h->plan.direct_train_cap) return TT_EMB_OK;  // these need no index work
   // Pick the index set to fill.  A set is free when no backward_update still has to be enqueued for
   // it (that is only `cur`, between a forward and its backward) and no prepared batch waits in it.
   // With all taken, the oldest prepared batch is overwritten.
@@ -599,7 +607,7 @@ static int forward_impl(tt_emb* h, const IdSource& src, int64_t B64, float* out,
   const int B = (int)(B64 * pl.split);  // items of the index pipeline, rows of D/split floats
   h->pending_B = -1;
   int rc;
-  h->direct = B <= pl.direct_cap;
+  h->direct = B <= (arm ? pl.direct_train_cap : pl.direct_cap);
   if (h->direct) {
     h->cur = free_set(h, h->cur + 1);  // only names this step for tt_emb_wait_backward
     h->done_valid[h->cur] = false;

@@ -674,6 +674,15 @@ int direct_capacity(const Shape& s) {
   return (int)std::min<int64_t>(kDirectMax, kDirectBytes / ((int64_t)s.S2 * 4));
 }
 
+// The same for a batch that backward_update follows, which keeps 4 (2 PN + 2 S1 + S3) bytes per item:
+// no more than kDirectKept of them (8192 items at rank 16 of D = 64 keep 24 MiB, 4096 at rank 32 of
+// D = 128 24 MiB; products of thousands of floats would take hundreds).
+int direct_train_capacity(const Shape& s) {
+  constexpr int64_t kDirectKept = (int64_t)32 << 20;
+  const int64_t item = 4 * (2 * (int64_t)s.PN + 2 * (int64_t)s.S1 + s.S3);
+  return (int)std::min<int64_t>(direct_capacity(s), kDirectKept / item);
+}
+
 void launch_direct_fwd(const Plan& pl, const DirectBuffers& d, const IdSource& src, int B,
                        const float* g1, const float* g2, const float* g3, float* out, bool train,
                        hipStream_t st) {

@@ -130,7 +130,7 @@ struct Counters {
 };
 
 // Scratch of the index-free kernels for small batches (tt_emb_direct.hip), sized for
-// Plan::direct_cap items.
+// Plan::direct_train_cap items (the keys for Plan::direct_cap).
 struct DirectBuffers {
   uint32_t* key;    // item -> table row, or the sentinel N; kept for tt_emb_get_stats
   uint16_t* dig;    // [3][stride]: i1, i2, i3 of every item, 0xffff for an out-of-range id
@@ -204,7 +204,8 @@ struct Plan {
   int sortBlocksMax, segBlocksMax, uBlocksMax, qBlocksMax, tilesMax;
   int64_t maxChunk3, maxChunk2;
   int keyBits, passes, bitsPerPass;
-  int direct_cap;  // batches of up to this many items take the index-free kernels (0: never)
+  int direct_cap;        // lookups of up to this many items take the index-free kernels (0: never)
+  int direct_train_cap;  // the same for batches that backward_update follows
   // single-wavefront blocks of the per-chunk matrix-core kernels that the device holds at once
   // (forward, backward); asked of the runtime at the first launch, 0 until then
   mutable int unit_slots[2] = {0, 0};
