@@ -68,10 +68,13 @@ enum {
                                       index stream after what hip_stream holds, only after its own
                                       earlier use of the index set (a pipeline can start a step
                                       earlier, and the caller's stream carries one event less)  */
+  TT_EMB_FLAG_INDEXED_KERNELS = 8u, /* small batches, too, take the kernels with index structures
+                                      (sorted ids, shared prefixes) that larger ones take; for
+                                      comparison and testing                                     */
   TT_EMB_FLAG_GENERIC_KERNELS = 2u /* use the any-shape vector-ALU kernels even for shapes that
                                       have matrix-core kernels (d1 in {4,8,...,32}, d2 = 4,
-                                      r1 = r2 in {8,16,32,64,128}, d3 in {4,8}); for comparison and
-                                      testing                                                    */
+                                      r1 = r2 in {8,16,32,64,128}, d3 in {4,8}), and index structures
+                                      for every batch; for comparison and testing                */
 };
 
 typedef struct {

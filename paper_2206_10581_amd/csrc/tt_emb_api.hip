@@ -151,7 +151,7 @@ static int make_plan(const tt_emb_config* c, Plan* pl) {
   pl->keyBits = bits_for(s.N);  // the sentinel N itself must be representable
   pl->passes = (pl->keyBits + 10) / 11;
   pl->bitsPerPass = (pl->keyBits + pl->passes - 1) / pl->passes;
-  pl->direct_cap = (c->flags & TT_EMB_FLAG_GENERIC_KERNELS)
+  pl->direct_cap = (c->flags & (TT_EMB_FLAG_GENERIC_KERNELS | TT_EMB_FLAG_INDEXED_KERNELS))
                        ? 0
                        : (int)std::min<int64_t>(pl->maxB, direct_capacity(s));
   pl->direct_train_cap = pl->direct_cap == 0 ? 0 : std::min(pl->direct_cap, direct_train_capacity(s));

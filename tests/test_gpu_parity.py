@@ -22,6 +22,10 @@ ROW_TOL = 1e-5
 CORE_TOL = 1e-4
 STEP_TOL = 1e-4
 
+# Batches of a few thousand ids take kernels of their own, which build no index structures; with
+# INDEXED they take the ones that larger batches take.
+GENERIC, IDS_READY, INDEXED = 2, 4, 8
+
 
 def _torch():
     import torch
@@ -115,16 +119,17 @@ def test_config1_tiny_in_full():
     ((9, 8, 7), (3, 7, 5), (5, 3), 2500),      # several 64-wide tiles with ragged edges (D = 105)
     ((4, 6, 5), (20, 1, 9), (70, 2), 900),     # stacked prefixes exceed one tile (16 * d1 = 320 rows)
 ])
-def test_generic_shapes(n, d, r, B):
+@pytest.mark.parametrize("flags", [0, INDEXED])
+def test_generic_shapes(n, d, r, B, flags):
     rng = np.random.default_rng(B)
     s = Shape(n, d, r)
     cores = tuple((rng.standard_normal(cs) * 0.5).astype(np.float32) for cs in s.core_shapes())
     ids = rng.integers(0, s.N, size=B, dtype=np.int64)
     grad = rng.standard_normal((B, s.D)).astype(np.float32)
-    check_against_oracle(n, d, r, cores, ids, grad, 0.01)
+    check_against_oracle(n, d, r, cores, ids, grad, 0.01, flags=flags)
 
 
-@pytest.mark.parametrize("flags", [0, 2])          # 2 = TT_EMB_FLAG_GENERIC_KERNELS
+@pytest.mark.parametrize("flags", [0, GENERIC, INDEXED])
 @pytest.mark.parametrize("R,d3", [(8, 4), (8, 8), (16, 4), (16, 8), (32, 8), (64, 8), (32, 4), (64, 4),
                                   (128, 4), (128, 8)])
 @pytest.mark.parametrize("n,B", [((9, 21, 13), 6000), ((40, 50, 60), 5000), ((3, 2, 700), 3000)])
@@ -141,8 +146,9 @@ def test_matrix_core_shape_family(n, B, R, d3, flags):
     check_against_oracle(n, d, r, cores, ids, grad, 0.01, flags=flags)
 
 
+@pytest.mark.parametrize("flags", [0, INDEXED])
 @pytest.mark.parametrize("n,R,B", [((48, 50, 60), 32, 5000), ((70, 60, 9), 16, 6000)])
-def test_prefix_ordered_chunk_schedule(n, R, B):
+def test_prefix_ordered_chunk_schedule(n, R, B, flags):
     # enough prefixes that the cached products can exceed one L2 (4 MiB): the G3-gradient chunks
     # are then walked in prefix order, one eighth of the order per XCD
     rng = np.random.default_rng(R + B)
@@ -153,18 +159,20 @@ def test_prefix_ordered_chunk_schedule(n, R, B):
     ids = rng.integers(0, s.N, size=B, dtype=np.int64)
     ids[: B // 8] = ids[1]
     grad = rng.standard_normal((B, s.D)).astype(np.float32)
-    check_against_oracle(n, d, r, cores, ids, grad, 0.01)
+    check_against_oracle(n, d, r, cores, ids, grad, 0.01, flags=flags)
 
 
 @pytest.mark.parametrize("B", [1, 2, 31, 32, 33, 63, 64, 65, 1023, 1025, 4095, 4096, 8193])
-def test_ragged_batch_sizes(B):
+@pytest.mark.parametrize("flags", [0, INDEXED])
+def test_ragged_batch_sizes(B, flags):
     w, cores, _, _ = _workload(2)
     ids = wl.make_ids(w, 100 + B, B)
     grad = wl.make_grads(w, 100 + B, B)
-    check_against_oracle(w.n, w.d, w.r, cores, ids, grad, w.lr, max_batch=10_000)
+    check_against_oracle(w.n, w.d, w.r, cores, ids, grad, w.lr, max_batch=10_000, flags=flags)
 
 
-def test_duplicates_out_of_range_and_one_hot_id():
+@pytest.mark.parametrize("flags", [0, INDEXED])
+def test_duplicates_out_of_range_and_one_hot_id(flags):
     w, cores, _, _ = _workload(2)
     rng = np.random.default_rng(5)
     hot = np.full(3000, 12345, dtype=np.int64)                    # one id, thousands of times
@@ -173,12 +181,12 @@ def test_duplicates_out_of_range_and_one_hot_id():
     ids = np.concatenate([hot, near, bad, rng.integers(0, w.N, 2000)]).astype(np.int64)
     rng.shuffle(ids)
     grad = rng.standard_normal((ids.size, w.D)).astype(np.float32)
-    out, _, stats = check_against_oracle(w.n, w.d, w.r, cores, ids, grad, w.lr)
+    out, _, stats = check_against_oracle(w.n, w.d, w.r, cores, ids, grad, w.lr, flags=flags)
     assert stats["out_of_range"] == 5
     assert not out[(ids < 0) | (ids >= w.N)].any()
 
 
-@pytest.mark.parametrize("flags", [0, 2])
+@pytest.mark.parametrize("flags", [0, GENERIC, INDEXED])
 def test_long_runs_cut_at_block_boundaries(flags):
     """Runs of one id longer than the 1024-slot unit of the gradient sums are carried as several
     pieces; the counts still name distinct ids, and pieces of one slot, runs that end exactly on a
@@ -195,15 +203,16 @@ def test_long_runs_cut_at_block_boundaries(flags):
     assert stats["U"] == 305
 
 
-def test_all_ids_out_of_range_and_empty_batch():
+@pytest.mark.parametrize("flags", [0, GENERIC, INDEXED])
+def test_all_ids_out_of_range_and_empty_batch(flags):
     w, cores, _, _ = _workload(1)
     ids = np.array([-5, w.N, w.N + 1], dtype=np.int64)
     grad = np.ones((3, w.D), dtype=np.float32)
-    out, new, stats = run_gpu(w.n, w.d, w.r, cores, ids, grad, w.lr)
+    out, new, stats = run_gpu(w.n, w.d, w.r, cores, ids, grad, w.lr, flags=flags)
     assert not out.any() and stats == {"U": 0, "Q": 0, "out_of_range": 3}
     for a, b in zip(new, cores):
         np.testing.assert_array_equal(a, b)
-    out, new, stats = run_gpu(w.n, w.d, w.r, cores, ids[:0], grad[:0], w.lr)
+    out, new, stats = run_gpu(w.n, w.d, w.r, cores, ids[:0], grad[:0], w.lr, flags=flags)
     assert out.shape == (0, w.D) and stats == {"U": 0, "Q": 0, "out_of_range": 0}
     for a, b in zip(new, cores):
         np.testing.assert_array_equal(a, b)
@@ -305,9 +314,15 @@ def test_bit_reproducible_and_lr_zero():
         np.testing.assert_array_equal(x, y)
 
 
-@pytest.mark.parametrize("flags", [0, 4])
+def _index_launches(emb):
+    """Sort launches since profiling was enabled or last read: none for a batch whose index structures
+    were ready, or that needs none."""
+    return emb.profile_read()["sort_hist"]["launches"]
+
+
+@pytest.mark.parametrize("flags", [0, IDS_READY, INDEXED, INDEXED | IDS_READY])
 def test_prepare_pipeline_matches_oracle_over_three_steps(flags):
-    # flags = 4: the ids are complete in memory at every prepare (they are: synchronised uploads)
+    # IDS_READY: the ids are complete in memory at every prepare (they are: synchronised uploads)
     # the next batch's index work is enqueued between forward and backward of the current one;
     # three different batches, cores carried from step to step on both sides
     torch = _torch()
@@ -368,14 +383,21 @@ def test_prepare_pipeline_matches_oracle_over_three_steps(flags):
         assert torch.equal(outs3[k], outs[k]), f"step {k}"
         assert torch.equal(emb3.cores[k], emb.cores[k])
     snap = [c.clone() for c in emb3.cores]
-    for k in (0, 1, 2, 0):                 # one more than there are sets
+    for k in (0, 1, 2, 1, 0):              # one more than there are sets: the first 0 is overwritten
         emb3.prepare(t_ids[k])
+    torch.cuda.synchronize()
+    emb3.profile(True)
     out_x = emb3.forward(t_ids[1]).clone()  # still waiting: served from its prepared set
+    assert _index_launches(emb3) == 0
+    emb3.forward(t_ids[1])                  # and a second time
+    assert _index_launches(emb3) == 0
     emb3.backward_update(t_grad[1], w.lr)
     after_x = [c.clone() for c in emb3.cores]
     for c, b in zip(emb3.cores, snap):
         c.copy_(b)
     out_y = emb3.forward(t_ids[1]).clone()  # nothing matches any more: index work done in place
+    assert (_index_launches(emb3) > 0) == bool(flags & INDEXED)
+    emb3.profile(False)
     emb3.backward_update(t_grad[1], w.lr)
     torch.cuda.synchronize()
     emb3.stats()
@@ -400,7 +422,7 @@ def test_prepare_pipeline_matches_oracle_over_three_steps(flags):
     emb.close()
 
 
-@pytest.mark.parametrize("flags", [0, 4])
+@pytest.mark.parametrize("flags", [0, IDS_READY, INDEXED, INDEXED | IDS_READY])
 def test_prepare_with_reused_ids_buffers(flags):
     """Ten steps through two ids buffers whose contents change every step (the index sets rotate
     underneath, every set meets every buffer several times), each step against the oracle."""
@@ -426,7 +448,13 @@ def test_prepare_with_reused_ids_buffers(flags):
             bufs[(k + 1) % 2].copy_(torch.from_numpy(batches[k + 1]))
             torch.cuda.synchronize()                      # ids complete before prepare (flag 4)
             emb.prepare(bufs[(k + 1) % 2])
+        if flags & INDEXED:
+            torch.cuda.synchronize()
+            emb.profile(True)
         out = emb.forward(bufs[k % 2]).cpu().numpy()
+        if flags & INDEXED:
+            assert _index_launches(emb) == 0, k           # its index structures were waiting
+            emb.profile(False)
         assert row_error(out, ora.forward(s, *cur, batches[k])) <= ROW_TOL, k
         st = emb.stats(check=False)
         assert st["U"] == np.unique(batches[k]).size, k
@@ -505,7 +533,8 @@ def test_lookup_only_calls_and_dense_materialisation():
     emb.close()
 
 
-def test_slab_split_shape_through_every_entry_point():
+@pytest.mark.parametrize("flags", [0, INDEXED])
+def test_slab_split_shape_through_every_entry_point(flags):
     """d = (8,4,4), rank 16 runs as a table with twice the first-core slices and d1 = 4 (each row
     two half rows); counts, out-of-range handling, the prepared pipeline, the lookup-only calls,
     the re-indexing table and Adagrad must all look as for any other shape."""
@@ -520,12 +549,12 @@ def test_slab_split_shape_through_every_entry_point():
     ids[:500] = ids[0]
     ids[600:606] = [-1, s.N, s.N + 3, 1 << 40, s.N - 1, 0]
     grad = rng.standard_normal((B, s.D)).astype(np.float32)
-    out, new, stats = check_against_oracle(n, d, r, cores, ids, grad, 0.01)
+    out, new, stats = check_against_oracle(n, d, r, cores, ids, grad, 0.01, flags=flags)
     assert stats["out_of_range"] == 4
     with_generic = run_gpu(n, d, r, cores, ids, grad, 0.01, flags=2)     # the any-shape kernels
     assert row_error(out, with_generic[0]) <= ROW_TOL and with_generic[2] == stats
 
-    emb = TTEmbedding(n, d, r, 1000, cores)
+    emb = TTEmbedding(n, d, r, 1000, cores, flags=flags)
     table = emb.materialize().cpu().numpy()                              # 378 rows
     assert row_error(table, ora.forward(s, *cores, np.arange(s.N, dtype=np.int64))) <= ROW_TOL
     part = emb.materialize(100, 200).cpu().numpy()
@@ -608,7 +637,8 @@ def test_node_reindexing_table():
     emb.close()
 
 
-def test_adagrad_update_two_steps():
+@pytest.mark.parametrize("flags", [0, INDEXED])
+def test_adagrad_update_two_steps(flags):
     """Row-sparse Adagrad as the update rule: two steps with the state carried along, against the
     oracle's textbook rule; then back to SGD."""
     torch = _torch()
@@ -617,7 +647,7 @@ def test_adagrad_update_two_steps():
         w, cores, _, _ = _workload(cfg)
         s = Shape(w.n, w.d, w.r)
         lr, eps = 0.05, 1e-8
-        emb = TTEmbedding(w.n, w.d, w.r, B, cores)
+        emb = TTEmbedding(w.n, w.d, w.r, B, cores, flags=flags)
         emb.set_adagrad(eps)
         ref = [c.copy() for c in cores]
         state = [np.zeros_like(c) for c in cores]
@@ -659,7 +689,8 @@ def test_adagrad_update_two_steps():
     ((56, 56, 56), (4, 4, 4), (16, 16), 12_000),     # matrix-core kernels
     ((9, 11, 13), (8, 4, 8), (32, 32), 4_000),       # ... through the slab split
 ])
-def test_adam_update_three_steps(n, d, r, B):
+@pytest.mark.parametrize("flags", [0, INDEXED])
+def test_adam_update_three_steps(n, d, r, B, flags):
     """Row-sparse Adam as the update rule: three steps with the moments carried along (batches that
     leave slices untouched, so that lazily kept moments matter), against the oracle's textbook
     rule; then the moments are handed to a second handle with steps_done and both take a step."""
@@ -670,7 +701,7 @@ def test_adam_update_three_steps(n, d, r, B):
     rng = np.random.default_rng(B)
     cores = [(rng.standard_normal(cs) / np.sqrt(r[0])).astype(np.float32) for cs in s.core_shapes()]
     lr, b1, b2, eps = 0.01, 0.9, 0.99, 1e-6
-    emb = TTEmbedding(n, d, r, B, cores)
+    emb = TTEmbedding(n, d, r, B, cores, flags=flags)
     emb.set_adam(b1, b2, eps)
     ref = [c.copy() for c in cores]
     m = [np.zeros_like(c) for c in cores]
@@ -697,7 +728,7 @@ def test_adam_update_three_steps(n, d, r, B):
             assert core_error(emb.adam_state[1][k].cpu().numpy(), v[k]) <= CORE_TOL
     # a second handle over copies of cores and moments, told that three steps were made
     cores2 = [c.cpu().numpy().copy() for c in emb.cores]
-    emb2 = TTEmbedding(n, d, r, B, cores2)
+    emb2 = TTEmbedding(n, d, r, B, cores2, flags=flags)
     m2 = [t.clone() for t in emb.adam_state[0]]
     v2 = [t.clone() for t in emb.adam_state[1]]
     rc = tt_emb_set_adam(emb2.handle, [t.data_ptr() for t in m2], [t.data_ptr() for t in v2],
@@ -996,7 +1027,7 @@ def test_ttsvd_initialisation_on_the_gpu():
         np.testing.assert_allclose(W.T @ W, np.eye(s.D), atol=1e-4)
 
 
-@pytest.mark.parametrize("flags", [0, 2])
+@pytest.mark.parametrize("flags", [0, GENERIC, INDEXED])
 def test_table_at_the_size_limits(flags):
     """The largest table the library accepts: 2048 values of i2 and of i3 (the bucket limit of the
     grouping passes, eleven-bit digits with the top bit in use) and N just below 2^31 (31-bit sort
@@ -1019,8 +1050,9 @@ def test_table_at_the_size_limits(flags):
     check_against_oracle(n, d, r, cores, ids, grad, 0.01, flags=flags)
 
 
+@pytest.mark.parametrize("flags", [0, INDEXED])
 @pytest.mark.parametrize("seed", range(12))
-def test_random_shapes_and_batches(seed):
+def test_random_shapes_and_batches(seed, flags):
     """Seeded random tables and batches: factors, ranks, batch size, share of repeated ids, of ids
     sharing a prefix and of out-of-range ids all drawn at random; even seeds draw from the shapes
     that have matrix-core kernels (d1 a multiple of 4, d2 = 4, equal ranks), odd seeds from anything."""
@@ -1045,4 +1077,5 @@ def test_random_shapes_and_batches(seed):
     ids[bad] = rng.choice([-1, s.N, s.N + 7, -(1 << 40), 1 << 40], size=int(bad.sum()))
     rng.shuffle(ids)
     grad = rng.standard_normal((B, s.D)).astype(np.float32)
-    check_against_oracle(n, d, r, cores, ids, grad, 0.01, max_batch=B + int(rng.integers(0, 100)))
+    check_against_oracle(n, d, r, cores, ids, grad, 0.01, max_batch=B + int(rng.integers(0, 100)),
+                         flags=flags)
