@@ -313,8 +313,10 @@ __global__ __launch_bounds__(kDThreads) void k_direct_bwd(
 //     sum over items of G1^T (r1 x d1) dP (d1 x W), one 16x16x4 matrix-core product per item and
 //     tile (edges masked), the items dealt to the four wavefronts; else kSpan2 entries
 //   G3, then G1 jobs: up to 256*VEC entries, the items dealt to groups of threads
-// The digits of the whole batch are scanned by every block (2 bytes per item, 16 KiB at most): cheaper
-// than a launch that sorts them, and what a block needs comes out in batch order.
+// Sums have two levels, a short chain of the items that are in flight together and a chain of those
+// rounds, and groups join in pairs.  Error of dG2 for 1024 copies of one id (terms of one sign, 2-norm):
+// 6.5e-8, as on the indexed kernels, where one chain over all of a wavefront's items left 2.5e-7;
+// dG3 of the smallest slices, 128 groups, 6e-8, where joining them in a chain left 2.1e-7.
 struct DirectList {
   uint16_t item[kDirectMax];
   uint32_t wave_n[kDWaves];
@@ -366,6 +368,20 @@ __device__ __forceinline__ int direct_list(DirectList& L, const uint16_t* __rest
   return (int)total;
 }
 
+// Pairwise sums of what `groups` groups (a power of two) of `lanes` threads hold, left in the first group.
+template <int VEC>
+__device__ __forceinline__ void join_groups(float* red, int tid, int lanes, int groups, float* acc) {
+  for (int half = groups / 2; half > 0; half /= 2) {
+    if (tid >= half * lanes && tid < 2 * half * lanes)
+#pragma unroll
+      for (int x = 0; x < VEC; ++x) red[tid * VEC + x] = acc[x];
+    __syncthreads();
+    if (tid < half * lanes)
+#pragma unroll
+      for (int x = 0; x < VEC; ++x) acc[x] += red[(tid + half * lanes) * VEC + x];
+  }
+}
+
 template <int RT, int CT, int RULE>  // RT row tiles of 16 on the matrix cores, or 0
 __global__ __launch_bounds__(kDThreads) void k_direct_apply(
     Shape sh, int B, float lr, UpdateRule ada, const uint16_t* __restrict__ dig, int stride,
@@ -400,11 +416,11 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
       for (int i = 0; i < RT; ++i) ra[i] = k1 * sh.r1 + min(16 * i + l16, sh.r1 - 1);
 #pragma unroll
       for (int j = 0; j < CT; ++j) cb[j] = k1 * sh.W + min(col0 + 16 * j + l16, sh.W - 1);
-      f4 acc[RT][CT];
+      f4 sum[RT][CT];
 #pragma unroll
       for (int i = 0; i < RT; ++i)
 #pragma unroll
-        for (int j = 0; j < CT; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < CT; ++j) sum[i][j] = f4{0.f, 0.f, 0.f, 0.f};
       for (int k = w; k < n; k += kDWaves * U) {
         float a[U][RT], b[U][CT];
 #pragma unroll
@@ -418,6 +434,11 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
           for (int j = 0; j < CT; ++j) b[u][j] = bp[cb[j]];
         }
         __builtin_amdgcn_sched_barrier(0);
+        f4 acc[RT][CT];
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+          for (int j = 0; j < CT; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int u = 0; u < U; ++u)
           if (k + u * kDWaves < n)  // wavefront-uniform
@@ -427,6 +448,10 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
               for (int j = 0; j < CT; ++j)
                 acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(
                     kg < sh.d1 ? a[u][i] : 0.f, kg < sh.d1 ? b[u][j] : 0.f, acc[i][j], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+          for (int j = 0; j < CT; ++j) sum[i][j] += acc[i][j];
       }
       // element v of lane (kg, l16) is row 16*i + 4*kg + v, column 16*j + l16
 #pragma unroll
@@ -435,7 +460,7 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
         for (int j = 0; j < CT; ++j)
 #pragma unroll
           for (int v = 0; v < 4; ++v)
-            red[((w * RT * 16 + 16 * i + 4 * kg + v) * CT + j) * 16 + l16] = acc[i][j][v];
+            red[((w * RT * 16 + 16 * i + 4 * kg + v) * CT + j) * 16 + l16] = sum[i][j][v];
       __syncthreads();
       constexpr int kOut = RT * CT * 256;
 #pragma unroll
@@ -454,17 +479,24 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
       while (lanes < outs) lanes <<= 1;  // at most kSpan2
       const int groups = kDThreads / lanes, lane = tid % lanes, grp = tid / lanes;
       const int o = o0 + min(lane, outs - 1), a = o / sh.W, c = o - a * sh.W;
-      float acc = 0.f;
+      float acc = 0.f, round = 0.f;
+      int left = 8;
       for (int k = grp; k < n; k += groups) {
         const int e = L.item[k];
         const float* ap = g1c + (size_t)e * sh.S1 + a;
         const float* bp = dP + (size_t)e * sh.PN + c;
-        for (int j1 = 0; j1 < sh.d1; ++j1) acc = fmaf(ap[(size_t)j1 * sh.r1], bp[(size_t)j1 * sh.W], acc);
+        float t = 0.f;
+        for (int j1 = 0; j1 < sh.d1; ++j1) t = fmaf(ap[(size_t)j1 * sh.r1], bp[(size_t)j1 * sh.W], t);
+        round += t;
+        if (--left == 0) {
+          acc += round;
+          round = 0.f;
+          left = 8;
+        }
       }
-      red[tid] = acc;
-      __syncthreads();
+      acc += round;
+      join_groups<1>(red, tid, lanes, groups, &acc);
       if (grp == 0 && lane < outs) {
-        for (int p = 1; p < groups; ++p) acc += red[p * lanes + lane];
         G[o] = updated_entry<RULE>(G[o], acc, lr, ada, ADA ? St + o : nullptr, ADAM ? Vt + o : nullptr);
       }
     }
@@ -503,22 +535,24 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+        for (int x = 0; x < VEC; ++x) {
 #pragma unroll
-          for (int x = 0; x < VEC; ++x) acc[x] += v[u][x];
+          for (int u = 1; u < U; ++u) v[0][x] += v[u][x];
+          acc[x] += v[0][x];
+        }
       }
+      float rest[VEC];
+#pragma unroll
+      for (int x = 0; x < VEC; ++x) rest[x] = 0.f;
       for (; k < n; k += groups) {
         const float* p = src + (size_t)L.item[k] * S + o;
 #pragma unroll
-        for (int x = 0; x < VEC; ++x) acc[x] += p[x];
+        for (int x = 0; x < VEC; ++x) rest[x] += p[x];
       }
 #pragma unroll
-      for (int x = 0; x < VEC; ++x) red[tid * VEC + x] = acc[x];
-      __syncthreads();
+      for (int x = 0; x < VEC; ++x) acc[x] += rest[x];
+      join_groups<VEC>(red, tid, lanes, groups, acc);
       if (grp == 0 && on) {
-        for (int p = 1; p < groups; ++p)
-#pragma unroll
-          for (int x = 0; x < VEC; ++x) acc[x] += red[(p * lanes + lane) * VEC + x];
 #pragma unroll
         for (int x = 0; x < VEC; ++x)
           G[o + x] = updated_entry<RULE>(G[o + x], acc[x], lr, ada, ADA ? St + o + x : nullptr,

@@ -91,3 +91,27 @@ def test_infinities_stay_where_they_belong(n, d, r, flags):
     _, new, _ = run_gpu(n, d, r, cores, ids, g, 0.01, flags=flags)
     for k in range(3):
         same_specials(new[k], ref[k])
+
+
+def _core_errors(n, d, r, B, flags=0):
+    """Per core, 2-norm of the error of a step over 2-norm of the step, for a batch of one id with cores
+    and gradients of one sign (nothing cancels) and a step that dwarfs the cores."""
+    s = Shape(n, d, r)
+    rng = np.random.default_rng(B + r[0])
+    cores = tuple((np.abs(rng.standard_normal(c)) / np.sqrt(r[0])).astype(np.float32) for c in s.core_shapes())
+    ids = np.full(B, s.N // 2, dtype=np.int64)
+    grad = (1e4 * np.abs(rng.standard_normal((B, s.D)))).astype(np.float32)
+    _, new, _ = run_gpu(n, d, r, cores, ids, grad, 1.0, flags=flags)
+    ref = [c.astype(np.float64) for c in ora.backward_update(s, *cores, ids, grad, 1.0)]
+    return [np.linalg.norm(new[k] - ref[k]) / np.linalg.norm(cores[k] - ref[k]) for k in range(3)]
+
+
+@pytest.mark.parametrize("n,d,r,B", [((9, 11, 13), (4, 4, 4), (16, 16), 1024), ((9, 11, 13), (4, 4, 8), (32, 32), 1024),
+                                     ((9, 11, 13), (4, 4, 8), (64, 64), 1024), ((4, 3, 5), (5, 3, 2), (7, 3), 2048),
+                                     ((9, 11, 13), (2, 2, 2), (4, 4), 100), ((9, 11, 13), (2, 2, 2), (4, 4), 2048)])
+def test_sums_of_a_hot_id_add_in_two_levels(n, d, r, B):
+    """m roundings of rms 0.41 u each (u = 2^-24) on growing partial sums leave 0.41 u sqrt(m / 3).  Chains
+    are at most 64 rounds long here, two side by side at least: 0.41 u sqrt(64/3/2 + 2) = 8.7e-8 at
+    most with the last additions.  In one chain the 1024 terms of a wavefront's share would leave
+    0.41 u sqrt(1024/3/4) = 2.3e-7."""
+    assert max(_core_errors(n, d, r, B)) <= 1.2e-7
