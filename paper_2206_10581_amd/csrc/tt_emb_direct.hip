@@ -794,30 +794,37 @@ void launch_table(const Plan& pl, const float* g1, const float* g2, const float*
                   int64_t count, float* out, hipStream_t st) {
   const Shape& s = pl.sh;
   const int n3 = (int)s.n3, p0 = (int)(first / n3), np = (int)((first + count - 1) / n3) - p0 + 1;
+  // A launch of 2^32 threads or more is refused: a run of many prefixes takes several launches, each
+  // long enough (a million blocks) for the gap between two not to count.
+  constexpr int64_t kTableBlocks = 1 << 20;
   if (pl.mfma) {
     // enough wavefronts to fill the chip several times over, but no run so short that forming
     // the products (about R/8 tiles' worth of work) outweighs it
     const int upt = 16 / s.d3, tiles = cdiv(n3, upt), nvp = np * pl.split;
-    const int per = s.r1 >= 128 ? 1 : s.r1 >= 64 ? 2 : 4, groups = cdiv(nvp, per);
-    const int want = std::max(1, cdiv(8192, groups));
+    const int per = s.r1 >= 128 ? 1 : s.r1 >= 64 ? 2 : 4;
+    const int want = std::max(1, cdiv(8192, cdiv(nvp, per)));
     const int seg_tiles = std::min(tiles, std::max(cdiv(tiles, want), std::max(2, s.r1 / 8)));
     const int nseg = cdiv(tiles, seg_tiles);
-    const int grid = cdiv((int64_t)groups * nseg, kDWaves);
+    const int most = (int)std::min<int64_t>(nvp, kTableBlocks * kDWaves / nseg * per);
 #define TT_TB(RR)                                                                                   \
   do {                                                                                              \
     if (s.d3 == 4)                                                                                  \
       k_table_mfma<RR, 4><<<grid, kDThreads, 0, st>>>((int)s.n2, n3, pl.split, (int)first, (int)count, \
-                                                      p0 * pl.split, nvp, nseg, seg_tiles, g1, g2, g3, out); \
+                                                      vp, nv, nseg, seg_tiles, g1, g2, g3, out);    \
     else                                                                                            \
       k_table_mfma<RR, 8><<<grid, kDThreads, 0, st>>>((int)s.n2, n3, pl.split, (int)first, (int)count, \
-                                                      p0 * pl.split, nvp, nseg, seg_tiles, g1, g2, g3, out); \
+                                                      vp, nv, nseg, seg_tiles, g1, g2, g3, out);    \
   } while (0)
-    switch (s.r1) {
-      case 8: TT_TB(8); break;
-      case 16: TT_TB(16); break;
-      case 32: TT_TB(32); break;
-      case 64: TT_TB(64); break;
-      default: TT_TB(128); break;
+    for (int64_t done = 0; done < nvp; done += most) {
+      const int vp = (int)(p0 * pl.split + done), nv = (int)std::min<int64_t>(most, nvp - done);
+      const int grid = cdiv((int64_t)cdiv(nv, per) * nseg, kDWaves);
+      switch (s.r1) {
+        case 8: TT_TB(8); break;
+        case 16: TT_TB(16); break;
+        case 32: TT_TB(32); break;
+        case 64: TT_TB(64); break;
+        default: TT_TB(128); break;
+      }
     }
 #undef TT_TB
     return;
@@ -825,9 +832,11 @@ void launch_table(const Plan& pl, const float* g1, const float* g2, const float*
   const int want = std::max(1, cdiv(2048, np));
   const int seg_ids = cdiv(std::max(cdiv(n3, want), kTableIds), kTableIds) * kTableIds;
   const int nseg = cdiv(n3, seg_ids);
+  const int most = (int)std::min<int64_t>(np, kTableBlocks / nseg);
   const size_t lds = ((size_t)((kTableIds * s.S3 + 3) & ~3) + (size_t)s.M * (s.r2 + 1)) * sizeof(float);
-  k_table_any<<<np * nseg, kDThreads, lds, st>>>(s, (int)first, (int)count, p0, nseg, seg_ids, g1, g2, g3,
-                                                 out);
+  for (int64_t done = 0; done < np; done += most)
+    k_table_any<<<(int)std::min<int64_t>(most, np - done) * nseg, kDThreads, lds, st>>>(
+        s, (int)first, (int)count, (int)(p0 + done), nseg, seg_ids, g1, g2, g3, out);
 }
 
 }  // namespace ttemb

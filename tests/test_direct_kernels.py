@@ -115,3 +115,41 @@ def test_sums_of_a_hot_id_add_in_two_levels(n, d, r, B):
     most with the last additions.  In one chain the 1024 terms of a wavefront's share would leave
     0.41 u sqrt(1024/3/4) = 2.3e-7."""
     assert max(_core_errors(n, d, r, B)) <= 1.2e-7
+
+
+@pytest.mark.parametrize("n,d,r", [((16400, 1024, 1), (2, 2, 1), (3, 2)),        # 16.8 million prefixes, a block each
+                                   ((2050, 2048, 1), (4, 4, 4), (128, 128))])   # 4.2 million, a wavefront each
+def test_table_rows_over_several_launches(n, d, r):
+    """One launch holds fewer than 2^32 threads: a run of that many prefixes is cut into launches of a
+    million blocks.  Rows around every cut and a sample of the others, against the oracle."""
+    import torch
+    from paper_2206_10581_amd import TTEmbedding
+    s = Shape(n, d, r)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    cores = [torch.randn(c, generator=gen, device="cuda") / r[0] ** 0.5 for c in s.core_shapes()]
+    emb = TTEmbedding(n, d, r, 10, cores)
+    first, count = 1, s.N - 2
+    out = torch.full((count + 2, s.D), 7.0, device="cuda")
+    emb.materialize(first, count, out[1:-1])
+    cuts = np.arange(0, s.N, 1 << 20)[:, None] + np.arange(-3, 4)
+    rows = np.unique(np.concatenate([cuts.ravel(), np.random.default_rng(2).integers(0, s.N, 20_000), [1, s.N - 2]]))
+    rows = rows[(rows >= first) & (rows < first + count)]
+    got = out[torch.from_numpy(rows).cuda()].cpu().numpy()   # out[0] stands before row 1
+    err = np.abs(got - ora.forward(s, *(c.cpu().numpy() for c in cores), rows)).max(1)
+    # rows of four or 64 elements: relative to a typical row, not to one that may cancel
+    assert err.max() <= ROW_TOL * np.abs(got).max(1).mean()
+    assert (out[0] == 7).all() and (out[-1] == 7).all()
+    emb.close()
+
+
+def test_table_rows_by_lookup():
+    """Products and G3 slices beyond a block's LDS: the run is looked up, max_batch rows at a time."""
+    from paper_2206_10581_amd import TTEmbedding
+    n, d, r = (3, 4, 5), (4, 4, 256), (4, 8)
+    s, cores, _, _ = _inputs(n, d, r, 16, 5)
+    emb = TTEmbedding(n, d, r, 10, cores)
+    emb.profile(True)
+    got = emb.materialize(7, 37).cpu().numpy()
+    assert emb.profile_read()["table"]["launches"] == 0
+    assert row_error(got, ora.forward(s, *cores, np.arange(7, 44, dtype=np.int64))) <= ROW_TOL
+    emb.close()
