@@ -153,3 +153,52 @@ def test_table_rows_by_lookup():
     assert emb.profile_read()["table"]["launches"] == 0
     assert row_error(got, ora.forward(s, *cores, np.arange(7, 44, dtype=np.int64))) <= ROW_TOL
     emb.close()
+
+
+@pytest.mark.parametrize("B", [1, 63, 149, 150, 151, 299, 301])
+@pytest.mark.parametrize("d,r", [((4, 4, 8), (16, 16)), ((5, 3, 2), (7, 3)), ((2, 2, 2), (4, 4))])
+def test_fewer_items_than_slices(d, r, B):
+    """Cores with more slices than the batch has items, with as many, and with fewer: ids that share one
+    coordinate and no other, the first position out of range, the last one's slices its own."""
+    n = (300, 150, 151)
+    s, cores, _, grad = _inputs(n, d, r, B, B)
+    rng = np.random.default_rng(B)
+    i1, i2, i3 = (rng.integers(0, k - 1, B) for k in n)
+    i1[B // 5: B // 3], i2[B // 4: B // 2], i3[B // 3:] = i1[0], i2[-1], i3[B // 2]
+    ids = (i1 * n[1] + i2) * n[2] + i3
+    if B > 1:
+        ids[0] = -1
+    ids[-1] = s.N - 1
+    check_against_oracle(n, d, r, cores, ids.astype(np.int64), grad, 0.01)
+
+
+def test_two_ids_of_a_table_with_two_to_the_31_entries():
+    """A middle core of 2^31 floats: the kernels launch for the two slices that the batch touches."""
+    import torch
+    from paper_2206_10581_amd import TTEmbedding
+    n, d, r = (2, 2048, 2), (1, 1, 1), (1024, 1024)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    cores = [torch.randn((2, 1, 1024), generator=gen, device="cuda"), torch.zeros((2048, 1024, 1, 1024), device="cuda"),
+             torch.randn((2, 1024, 1), generator=gen, device="cuda")]
+    i2 = [5, 2047]
+    cores[1][i2] = torch.randn((2, 1024, 1, 1024), generator=gen, device="cuda") / 32
+    small = [c.cpu().numpy() for c in (cores[0], cores[1][i2], cores[2])]
+    ids = torch.tensor([(0 * 2048 + i2[0]) * 2 + 1, (1 * 2048 + i2[1]) * 2], device="cuda")
+    grad = torch.ones((2, 1), device="cuda")
+    emb = TTEmbedding(n, d, r, 2, cores)
+    emb.profile(True)
+    out = emb.forward(ids)
+    emb.backward_update(grad, 0.01)
+    torch.cuda.synchronize()
+    assert emb.profile_read()["direct_apply"]["launches"] == 1
+    s = Shape((2, 2, 2), d, r)
+    small_ids = np.array([(0 * 2 + 0) * 2 + 1, (1 * 2 + 1) * 2], dtype=np.int64)
+    # rows are about 32: sums of 1024 products of unit scale
+    np.testing.assert_allclose(out.cpu().numpy(), ora.forward(s, *small, small_ids), rtol=0, atol=32 * ROW_TOL)
+    ref = ora.backward_update(s, *small, small_ids, np.ones((2, 1), np.float32), 0.01)
+    for got, want in zip((cores[0], cores[1][i2], cores[2]), ref):
+        np.testing.assert_allclose(got.cpu().numpy(), want, rtol=0, atol=1e-4 * np.abs(want).max())
+    cores[1][i2] = 0
+    assert torch.count_nonzero(cores[1].view(-1)[: 1 << 30]).item() == 0
+    assert torch.count_nonzero(cores[1].view(-1)[1 << 30:]).item() == 0
+    emb.close()
