@@ -309,9 +309,11 @@ __global__ __launch_bounds__(kDThreads) void k_direct_bwd(
 
 // ---------------------------------------------------------------------------------------------
 // Sums and update.  A block owns a run of entries of one slice:
-//   G2 jobs (first, they are the longest): for d1 <= 4 and r1 <= 128 16*CT columns of the slice, as
-//     sum over items of G1^T (r1 x d1) dP (d1 x W), one 16x16x4 matrix-core product per item and
-//     tile (edges masked), the items dealt to the four wavefronts; else kSpan2 entries
+//   G2 jobs (first, they are the longest): 16*RT rows and 16*CT columns of the slice, as sum over
+//     items of G1^T (r1 x d1) dP (d1 x W), one 16x16x4 matrix-core product per item, four rows of
+//     d1 and tile (edges masked), the items dealt to the four wavefronts.  (512 ids of d = (5,3,4) at
+//     rank 16: 20 us a step, 45 with one id in all positions, where a vector-ALU form for d1 > 4
+//     without loads in flight took 30 and 333; the indexed kernels 97 and 77.)
 //   G3, then G1 jobs: up to 256*VEC entries, the items dealt to groups of threads
 // Sums have two levels, a short chain of the items that are in flight together and a chain of those
 // rounds, and groups join in pairs.  Error of dG2 for 1024 copies of one id (terms of one sign, 2-norm):
@@ -397,19 +399,18 @@ __device__ __forceinline__ void join_groups(float* red, int tid, int lanes, int 
   }
 }
 
-template <int RT, int CT, int RULE>  // RT row tiles of 16 on the matrix cores, or 0
+template <int RT, int CT, int RULE>
 __global__ __launch_bounds__(kDThreads) void k_direct_apply(
     Shape sh, int B, float lr, UpdateRule ada, const uint16_t* __restrict__ dig, int stride,
     const float* __restrict__ g1c, const float* __restrict__ dP, const float* __restrict__ dg1,
     const float* __restrict__ dg3, float* __restrict__ g1, float* __restrict__ g2,
     float* __restrict__ g3) {
   constexpr bool ADA = RULE != kUpdateSgd, ADAM = RULE == kUpdateAdam;
-  constexpr int kSpan2 = 128;  // entries of a G2 job without matrix cores
-  constexpr int kRed = RT > 0 ? kDWaves * RT * CT * 256 : kDThreads * 4;
+  constexpr int kRed = std::max(kDWaves * RT * CT * 256, kDThreads * 4);
   __shared__ DirectList L;
   __shared__ float red[kRed];
   const int tid = threadIdx.x;
-  const int per2 = RT > 0 ? (sh.W + 16 * CT - 1) / (16 * CT) : (sh.S2 + kSpan2 - 1) / kSpan2;
+  const int cols2 = (sh.W + 16 * CT - 1) / (16 * CT), per2 = cols2 * ((sh.r1 + 16 * RT - 1) / (16 * RT));
   const int jobs2 = slice_blocks(sh.n2, B) * per2;
   int job = blockIdx.x;
   if (job < jobs2) {
@@ -420,30 +421,31 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
     float* G = g2 + (size_t)i2 * sh.S2;
     float* St = ADA ? ada.s2 + (size_t)i2 * sh.S2 : nullptr;
     float* Vt = ADAM ? ada.v2 + (size_t)i2 * sh.S2 : nullptr;
-    if constexpr (RT > 0) {
-      constexpr int U = RT >= 4 ? 4 : 8;  // items in flight per wavefront
-      const int w = tid / kWave, lane = tid % kWave, l16 = lane % 16, kg = lane / 16;
-      const int col0 = piece * 16 * CT;
-      // rows and columns past the slice read a valid address and are not stored; rows past d1 count
-      // zero in both operands (zero times an infinity would not be zero)
-      const int k1 = min(kg, sh.d1 - 1);
-      int ra[RT], cb[CT];
+    constexpr int U = RT >= 4 ? 4 : 8;  // items in flight per wavefront
+    const int w = tid / kWave, lane = tid % kWave, l16 = lane % 16, kg = lane / 16;
+    const int col0 = piece % cols2 * 16 * CT, row0 = piece / cols2 * 16 * RT;
+    // rows and columns past the slice read a valid address and are not stored; rows past d1 count
+    // zero in both operands (zero times an infinity would not be zero)
+    int ra[RT], cb[CT];
 #pragma unroll
-      for (int i = 0; i < RT; ++i) ra[i] = k1 * sh.r1 + min(16 * i + l16, sh.r1 - 1);
+    for (int i = 0; i < RT; ++i) ra[i] = min(row0 + 16 * i + l16, sh.r1 - 1);
 #pragma unroll
-      for (int j = 0; j < CT; ++j) cb[j] = k1 * sh.W + min(col0 + 16 * j + l16, sh.W - 1);
-      f4 sum[RT][CT];
+    for (int j = 0; j < CT; ++j) cb[j] = min(col0 + 16 * j + l16, sh.W - 1);
+    f4 sum[RT][CT];
 #pragma unroll
-      for (int i = 0; i < RT; ++i)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
-        for (int j = 0; j < CT; ++j) sum[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-      for (int k = w; k < n; k += kDWaves * U) {
+      for (int j = 0; j < CT; ++j) sum[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int k = w; k < n; k += kDWaves * U)
+      for (int j0 = 0; j0 < sh.d1; j0 += 4) {
+        const int j1 = min(j0 + kg, sh.d1 - 1);
+        const bool on = j0 + kg < sh.d1;
         float a[U][RT], b[U][CT];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const int e = L.item[min(k + u * kDWaves, n - 1)];
-          const float* ap = g1c + (size_t)e * sh.S1;
-          const float* bp = dP + (size_t)e * sh.PN;
+          const float* ap = g1c + (size_t)e * sh.S1 + j1 * sh.r1;
+          const float* bp = dP + (size_t)e * sh.PN + j1 * sh.W;
 #pragma unroll
           for (int i = 0; i < RT; ++i) a[u][i] = ap[ra[i]];
 #pragma unroll
@@ -462,59 +464,32 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
             for (int i = 0; i < RT; ++i)
 #pragma unroll
               for (int j = 0; j < CT; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                    kg < sh.d1 ? a[u][i] : 0.f, kg < sh.d1 ? b[u][j] : 0.f, acc[i][j], 0, 0, 0);
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(on ? a[u][i] : 0.f, on ? b[u][j] : 0.f,
+                                                                 acc[i][j], 0, 0, 0);
 #pragma unroll
         for (int i = 0; i < RT; ++i)
 #pragma unroll
           for (int j = 0; j < CT; ++j) sum[i][j] += acc[i][j];
       }
-      // element v of lane (kg, l16) is row 16*i + 4*kg + v, column 16*j + l16
+    // element v of lane (kg, l16) is row 16*i + 4*kg + v, column 16*j + l16
 #pragma unroll
-      for (int i = 0; i < RT; ++i)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
-        for (int j = 0; j < CT; ++j)
+      for (int j = 0; j < CT; ++j)
 #pragma unroll
-          for (int v = 0; v < 4; ++v)
-            red[((w * RT * 16 + 16 * i + 4 * kg + v) * CT + j) * 16 + l16] = sum[i][j][v];
-      __syncthreads();
-      constexpr int kOut = RT * CT * 256;
+        for (int v = 0; v < 4; ++v)
+          red[((w * RT * 16 + 16 * i + 4 * kg + v) * CT + j) * 16 + l16] = sum[i][j][v];
+    __syncthreads();
+    constexpr int kOut = RT * CT * 256;
 #pragma unroll
-      for (int x = 0; x < kOut / kDThreads; ++x) {
-        const int o = tid + x * kDThreads, row = o / (16 * CT), col = o % (16 * CT);
-        float s = red[o];
+    for (int x = 0; x < kOut / kDThreads; ++x) {
+      const int o = tid + x * kDThreads, row = row0 + o / (16 * CT), col = col0 + o % (16 * CT);
+      float s = red[o];
 #pragma unroll
-        for (int k = 1; k < kDWaves; ++k) s += red[k * kOut + o];
-        if (row >= sh.r1 || col0 + col >= sh.W) continue;
-        const size_t at = (size_t)row * sh.W + col0 + col;
-        G[at] = updated_entry<RULE>(G[at], s, lr, ada, ADA ? St + at : nullptr, ADAM ? Vt + at : nullptr);
-      }
-    } else {
-      const int o0 = piece * kSpan2, outs = min(kSpan2, sh.S2 - o0);
-      int lanes = 1;
-      while (lanes < outs) lanes <<= 1;  // at most kSpan2
-      const int groups = kDThreads / lanes, lane = tid % lanes, grp = tid / lanes;
-      const int o = o0 + min(lane, outs - 1), a = o / sh.W, c = o - a * sh.W;
-      float acc = 0.f, round = 0.f;
-      int left = 8;
-      for (int k = grp; k < n; k += groups) {
-        const int e = L.item[k];
-        const float* ap = g1c + (size_t)e * sh.S1 + a;
-        const float* bp = dP + (size_t)e * sh.PN + c;
-        float t = 0.f;
-        for (int j1 = 0; j1 < sh.d1; ++j1) t = fmaf(ap[(size_t)j1 * sh.r1], bp[(size_t)j1 * sh.W], t);
-        round += t;
-        if (--left == 0) {
-          acc += round;
-          round = 0.f;
-          left = 8;
-        }
-      }
-      acc += round;
-      join_groups<1>(red, tid, lanes, groups, &acc);
-      if (grp == 0 && lane < outs) {
-        G[o] = updated_entry<RULE>(G[o], acc, lr, ada, ADA ? St + o : nullptr, ADAM ? Vt + o : nullptr);
-      }
+      for (int p = 1; p < kDWaves; ++p) s += red[p * kOut + o];
+      if (row >= sh.r1 || col >= sh.W) continue;
+      const size_t at = (size_t)row * sh.W + col;
+      G[at] = updated_entry<RULE>(G[at], s, lr, ada, ADA ? St + at : nullptr, ADAM ? Vt + at : nullptr);
     }
     return;
   }
@@ -771,10 +746,9 @@ void launch_direct_bwd(const Plan& pl, const DirectBuffers& d, int B, const floa
 void launch_direct_apply(const Plan& pl, const DirectBuffers& d, int B, float* g1, float* g2, float* g3,
                          float lr, const UpdateRule& ada, hipEvent_t stop, hipStream_t st) {
   const Shape& s = pl.sh;
-  const bool mfma = s.d1 <= 4 && s.r1 <= 128;
-  const int rt = !mfma ? 0 : s.r1 <= 16 ? 1 : s.r1 <= 32 ? 2 : s.r1 <= 64 ? 4 : 8;
+  const int rt = s.r1 <= 16 ? 1 : s.r1 <= 32 ? 2 : s.r1 <= 64 ? 4 : 8;
   const int ct = rt <= 2 && s.W % 32 == 0 ? 2 : 1;
-  const int per2 = mfma ? cdiv(s.W, 16 * ct) : cdiv(s.S2, 128);
+  const int per2 = cdiv(s.W, 16 * ct) * cdiv(s.r1, 16 * rt);
   // at most B times the pieces of a slice: the bounds on B keep that to about a million blocks
   const int grid = slice_blocks(s.n2, B) * per2 + slice_blocks(s.n3, B) * cdiv(s.S3, 1024) +
                    slice_blocks(s.n1, B) * cdiv(s.S1, 1024);
@@ -795,8 +769,7 @@ void launch_direct_apply(const Plan& pl, const DirectBuffers& d, int B, float* g
     else if (ada.kind == kUpdateAdagrad) TT_DA(RT, CT, kUpdateAdagrad);                            \
     else TT_DA(RT, CT, kUpdateSgd);                                                                \
   } while (0)
-  if (rt == 0) TT_DR(0, 1);
-  else if (rt == 1) { if (ct == 2) TT_DR(1, 2); else TT_DR(1, 1); }
+  if (rt == 1) { if (ct == 2) TT_DR(1, 2); else TT_DR(1, 1); }
   else if (rt == 2) { if (ct == 2) TT_DR(2, 2); else TT_DR(2, 1); }
   else if (rt == 4) TT_DR(4, 1);
   else TT_DR(8, 1);

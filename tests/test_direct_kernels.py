@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 SHAPES = [((5, 6, 7), (2, 2, 2), (4, 4)), ((9, 11, 13), (4, 4, 8), (8, 8)), ((9, 11, 13), (4, 4, 4), (16, 16)),
           ((9, 11, 13), (4, 4, 8), (32, 32)), ((7, 5, 9), (8, 4, 4), (64, 64)), ((5, 4, 9), (4, 4, 8), (128, 128)),
           ((8, 7, 6), (4, 5, 5), (32, 32)), ((8, 7, 6), (4, 5, 5), (16, 16)), ((4, 3, 5), (3, 5, 7), (6, 10)),
-          ((4, 3, 5), (5, 3, 2), (7, 3))]
+          ((4, 3, 5), (5, 3, 2), (7, 3)), ((4, 3, 5), (9, 2, 3), (130, 5))]
 
 
 def _inputs(n, d, r, B, seed):
