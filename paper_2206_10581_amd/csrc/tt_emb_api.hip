@@ -607,20 +607,8 @@ static int forward_impl(tt_emb* h, const IdSource& src, int64_t B64, float* out,
   const int B = (int)(B64 * pl.split);  // items of the index pipeline, rows of D/split floats
   h->pending_B = -1;
   int rc;
-  h->direct = B <= (arm ? pl.direct_train_cap : pl.direct_cap);
-  if (h->direct) {
-    h->cur = free_set(h, h->cur + 1);  // only names this step for tt_emb_wait_backward
-    h->done_valid[h->cur] = false;
-    rc = run_slot(h, kSlotDirectFwd, st, [&] {
-      launch_direct_fwd(pl, h->ws[0].direct, src, B, h->g1, h->g2, h->g3, out, arm, st);
-    });
-    if (rc) return rc;
-    h->pending_B = arm ? B : -1;
-    h->last_B = B;
-    h->have_forward = true;
-    return TT_EMB_OK;
-  }
-  // oldest prepared batch with these ids and this size, if any
+  // oldest prepared batch with these ids and this size, if any: this forward consumes it, whichever
+  // kernels run
   int found = -1;
   for (int s = 0; s < kSets; ++s)
     if (ids != nullptr && h->prep[s].valid && h->prep[s].ids == ids && h->prep[s].B == B64 &&
@@ -635,6 +623,21 @@ static int forward_impl(tt_emb* h, const IdSource& src, int64_t B64, float* out,
     hipError_t e = finished ? hipSuccess : hipStreamWaitEvent(st, h->prep[found].ready, 0);
     if (e != hipSuccess) return hip_fail(e);
     h->prep[found].valid = false;
+  }
+  h->direct = B <= (arm ? pl.direct_train_cap : pl.direct_cap);
+  if (h->direct) {
+    h->cur = free_set(h, h->cur + 1);  // only names this step for tt_emb_wait_backward
+    h->done_valid[h->cur] = false;
+    rc = run_slot(h, kSlotDirectFwd, st, [&] {
+      launch_direct_fwd(pl, h->ws[0].direct, src, B, h->g1, h->g2, h->g3, out, arm, st);
+    });
+    if (rc) return rc;
+    h->pending_B = arm ? B : -1;
+    h->last_B = B;
+    h->have_forward = true;
+    return TT_EMB_OK;
+  }
+  if (found >= 0) {
     h->cur = found;
   } else {
     // build the index structures here; take a set no prepared batch waits in, else drop one

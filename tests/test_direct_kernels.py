@@ -202,3 +202,23 @@ def test_two_ids_of_a_table_with_two_to_the_31_entries():
     assert torch.count_nonzero(cores[1].view(-1)[: 1 << 30]).item() == 0
     assert torch.count_nonzero(cores[1].view(-1)[1 << 30:]).item() == 0
     emb.close()
+
+
+def test_lookup_consumes_the_batch_prepared_for_it():
+    """Between the limits of the two directions (some 500 and 8192 ids here) a batch is prepared, but a
+    lookup of it takes the index-free kernels.  The lookup uses up what was prepared all the same: when
+    the caller then fills the same buffer with other ids, the next forward sees those."""
+    import torch
+    from paper_2206_10581_amd import TTEmbedding
+    n, d, r, B = (9, 11, 13), (8, 9, 1), (2, 100), 1000
+    s, cores, ids, _ = _inputs(n, d, r, B, 6)
+    buf = torch.from_numpy(ids).cuda()
+    emb = TTEmbedding(n, d, r, B, cores)
+    emb.prepare(buf)
+    assert row_error(emb.forward_eval(buf).cpu().numpy(), ora.forward(s, *cores, ids)) <= ROW_TOL
+    ids = np.ascontiguousarray(ids[::-1])
+    buf.copy_(torch.from_numpy(ids))
+    emb.profile(True)
+    assert row_error(emb.forward(buf).cpu().numpy(), ora.forward(s, *cores, ids)) <= ROW_TOL
+    assert emb.profile_read()["sort_hist"]["launches"] > 0     # its structures were built for it
+    emb.close()
