@@ -3,6 +3,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -292,7 +293,9 @@ struct tt_emb {
   tt_emb_config cfg;
   Plan plan;
   Workspace ws[kSets];  // index sets over shared arithmetic buffers
-  int cur;            // set of the latest forward (and of the backward that follows it)
+  int cur;            // set of the latest forward with index structures (and of its backward)
+  int step;           // entry of done[] of the latest forward: cur, or for the index-free kernels, which
+                      // take no set, one of kSets entries behind the sets' own, in turn
   float *g1, *g2, *g3;
   const int32_t* reindex;  // old id -> table row applied in front of the split, or nullptr
   UpdateRule ada;          // kind kUpdateSgd: plain SGD
@@ -307,9 +310,10 @@ struct tt_emb {
   hipStream_t side[kSets];  // stream of each index set (kSideStreams distinct ones), created on
                             // first use, default priority
   hipEvent_t ev_fork;   // recorded on the caller's stream, awaited by side
-  hipEvent_t done[kSets];   // recorded on the caller's stream after the last kernel that reads the set
-  bool done_valid[kSets];   // done[s] covers the latest use of set s
-  int recent[kSets];        // index sets of the latest backward_update calls, newest first (-1: none)
+  hipEvent_t done[2 * kSets];  // recorded on the caller's stream after the last kernel of the step,
+                               // which is the last one that reads the set
+  bool done_valid[2 * kSets];  // done[s] covers the latest use of entry s
+  int recent[kSets];           // entries of the latest backward_update calls, newest first (-1: none)
   struct Prepared {
     bool valid;         // this index set holds a batch that no forward has consumed yet
     const int64_t* ids;
@@ -327,7 +331,7 @@ struct tt_emb {
 
 static IdSource id_source(const tt_emb* h, const int64_t* ids, int64_t base, bool reindexed) {
   const Plan& pl = h->plan;
-  return IdSource{ids, base, nullptr, reindexed ? h->reindex : nullptr, reindexed ? h->reindex_n : 0,
+  return IdSource{ids, base, reindexed ? h->reindex : nullptr, reindexed ? h->reindex_n : 0,
                   pl.split, pl.user_N, (int64_t)pl.sh.n2 * pl.sh.n3};
 }
 
@@ -383,10 +387,10 @@ static void init_handle(tt_emb* h, const tt_emb_config* cfg, const Plan& pl, flo
                         float* g3) {
   h->cfg = *cfg;
   h->plan = pl;
-  h->cur = 0;
+  h->cur = h->step = 0;
   for (int i = 0; i < kSets; ++i) h->side[i] = nullptr;
   h->ev_fork = nullptr;
-  for (int i = 0; i < kSets; ++i) {
+  for (int i = 0; i < 2 * kSets; ++i) {
     h->done[i] = nullptr;
     h->done_valid[i] = false;
   }
@@ -454,45 +458,32 @@ static bool stream_is_capturing(hipStream_t st) {
 // half way leaves the handle as it was).
 static int setup_side_streams(tt_emb* h) {
   hipStream_t side[kSideStreams] = {};
-  hipEvent_t ready[kSets] = {}, done[kSets] = {}, fork = nullptr;
+  hipEvent_t ready[kSets] = {}, done[2 * kSets] = {}, fork = nullptr;
   hipError_t e = hipSuccess;
   for (int i = 0; i < kSideStreams && e == hipSuccess; ++i)
     e = hipStreamCreateWithFlags(&side[i], hipStreamNonBlocking);
-  for (int i = 0; i < kSets && e == hipSuccess; ++i) {
+  for (int i = 0; i < kSets && e == hipSuccess; ++i)
     e = hipEventCreateWithFlags(&ready[i], hipEventDisableTiming);
-    // the extended launch of the update kernel records kernel times into this one
-    if (e == hipSuccess) e = hipEventCreate(&done[i]);
-  }
+  // the extended launch of the update kernel records kernel times into these
+  for (int i = 0; i < 2 * kSets && e == hipSuccess; ++i) e = hipEventCreate(&done[i]);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&fork, hipEventDisableTiming);
   if (e != hipSuccess) {
     for (int i = 0; i < kSideStreams; ++i)
       if (side[i] != nullptr) (void)hipStreamDestroy(side[i]);
-    for (int i = 0; i < kSets; ++i) {
+    for (int i = 0; i < kSets; ++i)
       if (ready[i] != nullptr) (void)hipEventDestroy(ready[i]);
+    for (int i = 0; i < 2 * kSets; ++i)
       if (done[i] != nullptr) (void)hipEventDestroy(done[i]);
-    }
     if (fork != nullptr) (void)hipEventDestroy(fork);
     return hip_fail(e);
   }
   for (int i = 0; i < kSets; ++i) {
     h->side[i] = side[i % kSideStreams];
     h->prep[i].ready = ready[i];
-    h->done[i] = done[i];
   }
+  for (int i = 0; i < 2 * kSets; ++i) h->done[i] = done[i];
   h->ev_fork = fork;
   return TT_EMB_OK;
-}
-
-// First index set from `from` on that no prepared batch waits in; with all taken, the oldest prepared
-// batch is dropped.
-static int free_set(tt_emb* h, int from) {
-  for (int k = 0; k < kSets; ++k)
-    if (!h->prep[(from + k) % kSets].valid) return (from + k) % kSets;
-  int target = 0;
-  for (int s = 1; s < kSets; ++s)
-    if (h->prep[s].seq < h->prep[target].seq) target = s;
-  h->prep[target].valid = false;
-  return target;
 }
 
 // Index pipeline of one batch into index set `set`, on stream st.
@@ -537,7 +528,7 @@ int tt_emb_prepare(tt_emb_t h, const int64_t* ids, int64_t B64, void* hip_stream
   // Pick the index set to fill.  A set is free when no backward_update still has to be enqueued for
   // it (that is only `cur`, between a forward and its backward) and no prepared batch waits in it.
   // With all taken, the oldest prepared batch is overwritten.
-  const bool cur_busy = h->pending_B >= 0;
+  const bool cur_busy = h->pending_B >= 0 && !h->direct;
   int target = -1;
   for (int k = 1; k <= kSets && target < 0; ++k) {
     const int s = (h->cur + k) % kSets;
@@ -575,13 +566,13 @@ int tt_emb_prepare(tt_emb_t h, const int64_t* ids, int64_t B64, void* hip_stream
 
 }  // extern "C"
 
-// Records that everything that reads index set cur has been enqueued on st (only once
+// Records that everything of the latest step has been enqueued on st (only once
 // tt_emb_prepare is in use with TT_EMB_FLAG_IDS_READY: that is who waits for it).
 static int mark_set_done(tt_emb* h, hipStream_t st) {
-  if (h->done[h->cur] == nullptr || !(h->cfg.flags & TT_EMB_FLAG_IDS_READY)) return TT_EMB_OK;
-  hipError_t e = hipEventRecord(h->done[h->cur], st);
+  if (h->done[h->step] == nullptr || !(h->cfg.flags & TT_EMB_FLAG_IDS_READY)) return TT_EMB_OK;
+  hipError_t e = hipEventRecord(h->done[h->step], st);
   if (e != hipSuccess) return hip_fail(e);
-  h->done_valid[h->cur] = true;
+  h->done_valid[h->step] = true;
   return TT_EMB_OK;
 }
 
@@ -626,8 +617,8 @@ static int forward_impl(tt_emb* h, const IdSource& src, int64_t B64, float* out,
   }
   h->direct = B <= (arm ? pl.direct_train_cap : pl.direct_cap);
   if (h->direct) {
-    h->cur = free_set(h, h->cur + 1);  // only names this step for tt_emb_wait_backward
-    h->done_valid[h->cur] = false;
+    h->step = h->step < kSets ? kSets : kSets + (h->step + 1) % kSets;
+    h->done_valid[h->step] = false;
     rc = run_slot(h, kSlotDirectFwd, st, [&] {
       launch_direct_fwd(pl, h->ws[0].direct, src, B, h->g1, h->g2, h->g3, out, arm, st);
     });
@@ -662,7 +653,8 @@ static int forward_impl(tt_emb* h, const IdSource& src, int64_t B64, float* out,
     rc = run_index(h, h->cur, src, B, st, arm ? 1 : 2);
     if (rc) return rc;
   }
-  h->done_valid[h->cur] = false;  // a new use of this set begins
+  h->step = h->cur;
+  h->done_valid[h->step] = false;  // a new use of this set begins
   const Workspace& ws = h->ws[h->cur];
   rc = run_slot(h, kSlotPrefixFwd, st, [&] {
     if (h->mfma) launch_prefix_fwd_mfma(pl, ws, h->g1, h->g2, B, st);
@@ -895,8 +887,8 @@ int tt_emb_backward_update(tt_emb_t h, const float* grad_out, float lr, void* hi
   // its completion signal doubles as the set's "done" event.
   // (a handle with side streams is never captured, see forward_impl)
   hipEvent_t stop = nullptr;
-  if (h->done[h->cur] != nullptr && (h->cfg.flags & TT_EMB_FLAG_IDS_READY) && !h->profiling)
-    stop = h->done[h->cur];
+  if (h->done[h->step] != nullptr && (h->cfg.flags & TT_EMB_FLAG_IDS_READY) && !h->profiling)
+    stop = h->done[h->step];
   if (h->ada.kind == kUpdateAdam) {
     // bias corrections of step t = 1, 2, ... (every backward_update with a batch counts)
     const double t = (double)(h->adam_step + 1);
@@ -919,9 +911,9 @@ int tt_emb_backward_update(tt_emb_t h, const float* grad_out, float lr, void* hi
   if (h->profiling) rc = run_slot(h, kSlotEventPair, st, [] {});
   if (rc) return rc;
   for (int i = kSets - 1; i > 0; --i) h->recent[i] = h->recent[i - 1];
-  h->recent[0] = h->cur;
+  h->recent[0] = h->step;
   if (stop != nullptr) {
-    h->done_valid[h->cur] = true;
+    h->done_valid[h->step] = true;
     return TT_EMB_OK;
   }
   return mark_set_done(h, st);
@@ -945,22 +937,26 @@ int tt_emb_get_stats(tt_emb_t h, int64_t* U, int64_t* Q, int64_t* out_of_range) 
   std::memset(&c, 0, sizeof(c));
   int64_t oob = 0;
   if (h->have_forward) {
-    hipError_t e = hipSuccess;
-    int set = h->cur;
+    hipError_t e = hipStreamSynchronize(h->last_stream);
+    if (e != hipSuccess) return hip_fail(e);
     if (h->direct) {
-      // the index-free kernels count nothing: the batch's keys, which they keep, are sorted now
-      set = free_set(h, h->cur);
-      if (h->side[set] != nullptr) e = hipStreamSynchronize(h->side[set]);  // a dropped pipeline
+      // the index-free kernels count nothing, but they keep the keys of the batch
+      const int64_t items = h->last_B;
+      std::unique_ptr<uint32_t[]> key(new (std::nothrow) uint32_t[items]);
+      if (key == nullptr) return TT_EMB_EINVAL;
+      e = hipMemcpy(key.get(), h->ws[0].direct.key, items * sizeof(uint32_t), hipMemcpyDeviceToHost);
       if (e != hipSuccess) return hip_fail(e);
-      IdSource src = id_source(h, nullptr, 0, false);
-      src.keys = h->ws[0].direct.key;
-      int rc = run_index(h, set, src, (int)h->last_B, h->last_stream, 2);
-      if (rc) return rc;
+      std::sort(key.get(), key.get() + items);
+      const Shape& s = h->plan.sh;
+      for (int64_t i = 0; i < items && key[i] < s.N; ++i) {
+        c.nvalid += 1;
+        c.U += i == 0 || key[i] != key[i - 1];
+        c.Q += i == 0 || key[i] / s.n3 != key[i - 1] / s.n3;
+      }
+    } else {
+      e = hipMemcpy(&c, h->ws[h->cur].ctr, sizeof(c), hipMemcpyDeviceToHost);
+      if (e != hipSuccess) return hip_fail(e);
     }
-    e = hipStreamSynchronize(h->last_stream);
-    if (e != hipSuccess) return hip_fail(e);
-    e = hipMemcpy(&c, h->ws[set].ctr, sizeof(c), hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return hip_fail(e);
     oob = h->last_B - (int64_t)c.nvalid;
   }
   // with a slab split every id, prefix and position was counted once per slab
@@ -1017,8 +1013,9 @@ int tt_emb_destroy(tt_emb_t h) {
       if (h->side[i] == nullptr) continue;
       (void)hipStreamSynchronize(h->side[i]);
       if (h->prep[i].ready != nullptr) (void)hipEventDestroy(h->prep[i].ready);
-      if (h->done[i] != nullptr) (void)hipEventDestroy(h->done[i]);
     }
+    for (int i = 0; i < 2 * kSets; ++i)
+      if (h->done[i] != nullptr) (void)hipEventDestroy(h->done[i]);
     for (int i = 0; i < kSideStreams; ++i)
       if (h->side[i] != nullptr) (void)hipStreamDestroy(h->side[i]);
     if (h->ev_fork != nullptr) (void)hipEventDestroy(h->ev_fork);

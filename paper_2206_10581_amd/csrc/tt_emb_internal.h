@@ -69,7 +69,6 @@ constexpr int kOrderBands = 1024;  // bands of the prefix range the by-i3 chunks
 struct IdSource {
   const int64_t* ids;      // device [B]; nullptr: the consecutive ids base, base+1, ...
   int64_t base;
-  const uint32_t* keys;    // device [items]: keys that an earlier kernel has formed, or nullptr
   const int32_t* reindex;  // device [n_ids] old id -> table row, or nullptr (ids are table rows)
   int64_t n_ids;
   // Slab split (see Plan::split): item idx of the pipeline is slab idx % split of batch position
@@ -130,7 +129,7 @@ struct Counters {
 };
 
 // Scratch of the index-free kernels for small batches (tt_emb_direct.hip), sized for
-// Plan::direct_train_cap items (the keys for Plan::direct_cap).
+// Plan::direct_train_cap items (the keys for Plan::direct_cap; tt_emb_get_stats reads them).
 struct DirectBuffers {
   uint32_t* key;    // item -> table row, or the sentinel N; kept for tt_emb_get_stats
   uint16_t* dig;    // [3][stride]: i1, i2, i3 of every item, 0xffff for an out-of-range id
@@ -253,7 +252,6 @@ enum KernelSlot {
 };
 
 __device__ __forceinline__ uint32_t key_of_id(const IdSource& src, int idx, uint32_t N) {
-  if (src.keys != nullptr) return src.keys[idx];
   int pos = idx, slab = 0;
   if (src.split > 1) {
     pos = idx / src.split;

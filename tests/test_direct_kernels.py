@@ -222,3 +222,41 @@ def test_lookup_consumes_the_batch_prepared_for_it():
     assert row_error(emb.forward(buf).cpu().numpy(), ora.forward(s, *cores, ids)) <= ROW_TOL
     assert emb.profile_read()["sort_hist"]["launches"] > 0     # its structures were built for it
     emb.close()
+
+
+def test_small_steps_leave_prepared_batches_alone():
+    """With a batch waiting in every index set, a step on the index-free kernels and the counts of its
+    batch (the host counts them) use up none: all four are served afterwards without a sort.  The
+    profile names the step's own launches only."""
+    import torch
+    from paper_2206_10581_amd import TTEmbedding
+    n, d, r, B, small = (9, 11, 13), (4, 4, 4), (16, 16), 9000, 300
+    s, cores, ids, grad = _inputs(n, d, r, B, 7)
+    emb = TTEmbedding(n, d, r, B, cores, flags=4)             # the ids are in memory at every prepare
+    valid = ids[(ids >= 0) & (ids < s.N)]
+    bufs = [torch.from_numpy(np.roll(ids, k)).cuda() for k in range(4)]
+    t_grad = torch.from_numpy(grad).cuda()
+    torch.cuda.synchronize()
+    for b in bufs:
+        emb.prepare(b)
+    torch.cuda.synchronize()
+    emb.profile(True)
+    few = bufs[1][:small].clone()
+    for _ in range(5):                                        # more steps than there are events for them
+        out = emb.forward(few)
+        emb.backward_update(t_grad[:small], 0.0)
+        emb.wait_backward(1)
+    st = emb.stats(check=False)
+    f = few.cpu().numpy()
+    inside = f[(f >= 0) & (f < s.N)]
+    assert st == {"U": np.unique(inside).size, "Q": np.unique(inside // n[2]).size, "out_of_range": small - inside.size}
+    assert row_error(out.cpu().numpy(), ora.forward(s, *cores, f)) <= ROW_TOL
+    for b in bufs:
+        out = emb.forward(b)
+        emb.backward_update(t_grad, 0.0)
+        assert row_error(out.cpu().numpy(), ora.forward(s, *cores, b.cpu().numpy())) <= ROW_TOL
+        st = emb.stats(check=False)
+        assert st["out_of_range"] == B - valid.size and st["U"] == np.unique(valid).size
+    launches = {k: v["launches"] for k, v in emb.profile_read().items() if v["launches"]}
+    assert launches["direct_fwd"] == 5 and launches["prefix_fwd"] == 4 and "sort_hist" not in launches
+    emb.close()
