@@ -321,6 +321,9 @@ struct tt_emb {
     uint64_t seq;       // order of the prepare calls
     hipEvent_t ready;   // recorded on side when the set is complete
   } prep[kSets];
+  // Batches given to tt_emb_prepare that the index-free kernels will take: no work, but their ids may
+  // still be on the way.  ready is recorded on the stream of the prepare call.
+  Prepared small[kSets];
   uint64_t prep_seq;
   bool profiling;
   bool mfma;  // matrix-core kernels apply to this shape and are not switched off
@@ -396,7 +399,7 @@ static void init_handle(tt_emb* h, const tt_emb_config* cfg, const Plan& pl, flo
   }
   h->prep_seq = 0;
   for (int i = 0; i < kSets; ++i) h->recent[i] = -1;
-  for (int i = 0; i < kSets; ++i) h->prep[i] = tt_emb::Prepared{false, nullptr, 0, 0, nullptr};
+  for (int i = 0; i < kSets; ++i) h->prep[i] = h->small[i] = tt_emb::Prepared{false, nullptr, 0, 0, nullptr};
   h->g1 = g1;
   h->g2 = g2;
   h->g3 = g3;
@@ -458,11 +461,11 @@ static bool stream_is_capturing(hipStream_t st) {
 // half way leaves the handle as it was).
 static int setup_side_streams(tt_emb* h) {
   hipStream_t side[kSideStreams] = {};
-  hipEvent_t ready[kSets] = {}, done[2 * kSets] = {}, fork = nullptr;
+  hipEvent_t ready[2 * kSets] = {}, done[2 * kSets] = {}, fork = nullptr;
   hipError_t e = hipSuccess;
   for (int i = 0; i < kSideStreams && e == hipSuccess; ++i)
     e = hipStreamCreateWithFlags(&side[i], hipStreamNonBlocking);
-  for (int i = 0; i < kSets && e == hipSuccess; ++i)
+  for (int i = 0; i < 2 * kSets && e == hipSuccess; ++i)
     e = hipEventCreateWithFlags(&ready[i], hipEventDisableTiming);
   // the extended launch of the update kernel records kernel times into these
   for (int i = 0; i < 2 * kSets && e == hipSuccess; ++i) e = hipEventCreate(&done[i]);
@@ -470,19 +473,40 @@ static int setup_side_streams(tt_emb* h) {
   if (e != hipSuccess) {
     for (int i = 0; i < kSideStreams; ++i)
       if (side[i] != nullptr) (void)hipStreamDestroy(side[i]);
-    for (int i = 0; i < kSets; ++i)
+    for (int i = 0; i < 2 * kSets; ++i) {
       if (ready[i] != nullptr) (void)hipEventDestroy(ready[i]);
-    for (int i = 0; i < 2 * kSets; ++i)
       if (done[i] != nullptr) (void)hipEventDestroy(done[i]);
+    }
     if (fork != nullptr) (void)hipEventDestroy(fork);
     return hip_fail(e);
   }
   for (int i = 0; i < kSets; ++i) {
     h->side[i] = side[i % kSideStreams];
     h->prep[i].ready = ready[i];
+    h->small[i].ready = ready[kSets + i];
   }
   for (int i = 0; i < 2 * kSets; ++i) h->done[i] = done[i];
   h->ev_fork = fork;
+  return TT_EMB_OK;
+}
+
+// The oldest of kSets prepared batches with these ids and this size is used up, and work enqueued on st
+// from here on comes after what was enqueued for it.  *found: its place, or -1.
+static int take_prepared(tt_emb::Prepared* list, const int64_t* ids, int64_t B, hipStream_t st, int* found) {
+  *found = -1;
+  for (int s = 0; s < kSets; ++s)
+    if (ids != nullptr && list[s].valid && list[s].ids == ids && list[s].B == B &&
+        (*found < 0 || list[s].seq < list[*found].seq))
+      *found = s;
+  if (*found < 0) return TT_EMB_OK;
+  // A pipeline that has already finished needs no wait on the caller's stream (its kernels
+  // have completed, their results are visible to every later launch); one that has not is
+  // awaited on the device.
+  const bool finished = hipEventQuery(list[*found].ready) == hipSuccess;
+  (void)hipGetLastError();  // "not ready" is an answer, not an error
+  const hipError_t e = finished ? hipSuccess : hipStreamWaitEvent(st, list[*found].ready, 0);
+  if (e != hipSuccess) return hip_fail(e);
+  list[*found].valid = false;
   return TT_EMB_OK;
 }
 
@@ -524,7 +548,18 @@ int tt_emb_prepare(tt_emb_t h, const int64_t* ids, int64_t B64, void* hip_stream
     int rc0 = setup_side_streams(h);
     if (rc0) return rc0;
   }
-  if (B64 * h->plan.split <= h->plan.direct_train_cap) return TT_EMB_OK;  // these need no index work
+  if (B64 * h->plan.split <= h->plan.direct_train_cap) {
+    // no index work: all that the forward has to wait for is the ids
+    if (h->cfg.flags & TT_EMB_FLAG_IDS_READY) return TT_EMB_OK;
+    int slot = 0;  // a free place, else that of the oldest
+    for (int s = 1; s < kSets && h->small[slot].valid; ++s)
+      if (!h->small[s].valid || h->small[s].seq < h->small[slot].seq) slot = s;
+    h->small[slot].valid = false;
+    e = hipEventRecord(h->small[slot].ready, st);
+    if (e != hipSuccess) return hip_fail(e);
+    h->small[slot] = tt_emb::Prepared{true, ids, B64, ++h->prep_seq, h->small[slot].ready};
+    return TT_EMB_OK;
+  }
   // Pick the index set to fill.  A set is free when no backward_update still has to be enqueued for
   // it (that is only `cur`, between a forward and its backward) and no prepared batch waits in it.
   // With all taken, the oldest prepared batch is overwritten.
@@ -597,24 +632,12 @@ static int forward_impl(tt_emb* h, const IdSource& src, int64_t B64, float* out,
   if (capturing && h->side[0] != nullptr) return TT_EMB_ESTATE;
   const int B = (int)(B64 * pl.split);  // items of the index pipeline, rows of D/split floats
   h->pending_B = -1;
-  int rc;
-  // oldest prepared batch with these ids and this size, if any: this forward consumes it, whichever
-  // kernels run
-  int found = -1;
-  for (int s = 0; s < kSets; ++s)
-    if (ids != nullptr && h->prep[s].valid && h->prep[s].ids == ids && h->prep[s].B == B64 &&
-        (found < 0 || h->prep[s].seq < h->prep[found].seq))
-      found = s;
-  if (found >= 0) {
-    // A pipeline that has already finished needs no wait on the caller's stream (its kernels
-    // have completed, their results are visible to every later launch); one that has not is
-    // awaited on the device.
-    const bool finished = hipEventQuery(h->prep[found].ready) == hipSuccess;
-    (void)hipGetLastError();  // "not ready" is an answer, not an error
-    hipError_t e = finished ? hipSuccess : hipStreamWaitEvent(st, h->prep[found].ready, 0);
-    if (e != hipSuccess) return hip_fail(e);
-    h->prep[found].valid = false;
-  }
+  // this forward uses up the batch prepared for it, whichever kernels run
+  int found, early;
+  int rc = take_prepared(h->prep, ids, B64, st, &found);
+  if (rc) return rc;
+  rc = take_prepared(h->small, ids, B64, st, &early);
+  if (rc) return rc;
   h->direct = B <= (arm ? pl.direct_train_cap : pl.direct_cap);
   if (h->direct) {
     h->step = h->step < kSets ? kSets : kSets + (h->step + 1) % kSets;
@@ -1013,6 +1036,7 @@ int tt_emb_destroy(tt_emb_t h) {
       if (h->side[i] == nullptr) continue;
       (void)hipStreamSynchronize(h->side[i]);
       if (h->prep[i].ready != nullptr) (void)hipEventDestroy(h->prep[i].ready);
+      if (h->small[i].ready != nullptr) (void)hipEventDestroy(h->small[i].ready);
     }
     for (int i = 0; i < 2 * kSets; ++i)
       if (h->done[i] != nullptr) (void)hipEventDestroy(h->done[i]);

@@ -260,3 +260,33 @@ def test_small_steps_leave_prepared_batches_alone():
     launches = {k: v["launches"] for k, v in emb.profile_read().items() if v["launches"]}
     assert launches["direct_fwd"] == 5 and launches["prefix_fwd"] == 4 and "sort_hist" not in launches
     emb.close()
+
+
+def test_prepare_of_a_small_batch_orders_its_forward():
+    """Small batches need no index work, but prepare still takes over the order of its stream: ids that
+    are on their way on one stream when prepare is called there are awaited by the forward on another.
+    The copies wait behind a kernel that spins for some tens of milliseconds."""
+    import torch
+    from paper_2206_10581_amd import TTEmbedding
+    n, d, r, B = (9, 11, 13), (4, 4, 8), (16, 16), 300
+    s, cores, ids, _ = _inputs(n, d, r, B, 8)
+    emb = TTEmbedding(n, d, r, B, cores)
+    batches = [torch.from_numpy(np.roll(ids, k)).cuda() for k in range(3)]
+    bufs = [torch.zeros_like(b) for b in batches]
+    out = torch.empty((B, s.D), device="cuda")
+    emb.prepare(bufs[0])                                      # streams and events exist from here on
+    emb.forward(bufs[0], out)
+    loader = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(loader):
+        torch.cuda._sleep(50_000_000)
+        for b, src in zip(bufs, batches):
+            b.copy_(src)
+            emb.prepare(b)
+    got = [emb.forward(bufs[0], out).clone()]
+    emb.backward_update(torch.zeros((B, s.D), device="cuda"), 0.0)
+    got += [emb.forward_eval(b).clone() for b in bufs[1:]]
+    torch.cuda.synchronize()
+    for x, b in zip(got, batches):
+        assert row_error(x.cpu().numpy(), ora.forward(s, *cores, b.cpu().numpy())) <= ROW_TOL
+    emb.close()
