@@ -49,6 +49,7 @@ void launch_gsum_block(const Plan&, const Workspace&, const float* grad, int B, 
 // index-free kernels (tt_emb_direct.hip)
 int direct_capacity(const Shape&);
 int direct_train_capacity(const Shape&);
+int direct_pieces(const Shape&);
 void launch_direct_fwd(const Plan&, const DirectBuffers&, const IdSource&, int B, const float* g1,
                        const float* g2, const float* g3, float* out, bool train, hipStream_t);
 void launch_direct_bwd(const Plan&, const DirectBuffers&, int B, const float* g1, const float* g2,
@@ -262,6 +263,10 @@ static size_t carve(const Plan& pl, char* base, Workspace* ws /* [kSets] or null
     d.g1 = (float*)take(cap * s.S1 * 4);
     d.dg1 = (float*)take(cap * s.S1 * 4);
     d.dg3 = (float*)take(cap * s.S3 * 4);
+    const size_t parts = 3 * (size_t)hot_parts((int64_t)cap);
+    d.hot = (int2*)take(parts * 8);
+    d.n_hot = (uint32_t*)take((3 + parts * direct_pieces(s)) * 4);
+    d.hot_sum = (float*)take(2 * parts * std::max({s.S1, s.S2, s.S3}) * 4);
   }
   off = std::max(off, indexed_end);
   for (int i = sets; i < kSets; ++i) set[i] = set[0];

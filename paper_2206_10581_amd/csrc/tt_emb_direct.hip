@@ -179,17 +179,67 @@ __global__ __launch_bounds__(kDThreads) void k_direct_fwd(
   }
 }
 
+// Lists the parts beyond the first of the slices of one core that more than kDirectPart items share, and
+// clears the tickets of those parts; for a whole block, with `bins` words of LDS.  (Counted per item with
+// device atomics, 8192 items of three cores took 56 us.)
+__device__ void list_hot_parts(uint32_t* lds, int bins, const uint16_t* __restrict__ dig, int B, int n,
+                               int2* __restrict__ hot, uint32_t* __restrict__ n_hot, uint32_t* __restrict__ tickets,
+                               int n_tickets) {
+  const int tid = threadIdx.x;
+  uint32_t* listed = lds;  // one word, then the counters
+  uint32_t* cnt = lds + 1;
+  bins -= 1;
+  for (int i = tid; i < n_tickets; i += kDThreads) tickets[i] = 0u;
+  if (tid == 0) *listed = 0u;
+  for (int s0 = 0; s0 < n; s0 += bins) {
+    const int here = min(bins, n - s0);
+    for (int i = tid; i < here; i += kDThreads) cnt[i] = 0u;
+    __syncthreads();
+    constexpr int kLoads = kDirectMax / (kDThreads * 8);
+    uint4 d[kLoads];
+#pragma unroll
+    for (int k = 0; k < kLoads; ++k) {
+      const int at = (k * kDThreads + tid) * 8;
+      d[k] = at < B ? *(const uint4*)(dig + at) : make_uint4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int k = 0; k < kLoads; ++k) {
+      const uint32_t v[4] = {d[k].x, d[k].y, d[k].z, d[k].w};
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        // 0xffff, an out-of-range id, is past every slice
+        const int s = (int)(j % 2 ? v[j / 2] >> 16 : v[j / 2] & 0xffffu) - s0;
+        if ((k * kDThreads + tid) * 8 + j < B && s >= 0 && s < here) atomicAdd(&cnt[s], 1u);
+      }
+    }
+    __syncthreads();
+    for (int i = tid; i < here; i += kDThreads)
+      for (int p = 1; p * kDirectPart < (int)cnt[i]; ++p) hot[atomicAdd(listed, 1u)] = make_int2(s0 + i, p);
+    __syncthreads();
+  }
+  if (tid == 0) *n_hot = *listed;
+}
+
 template <int TW>
 __global__ __launch_bounds__(kDThreads) void k_direct_bwd(
     Shape sh, int B, const uint32_t* __restrict__ keys, const float* __restrict__ g1,
     const float* __restrict__ g2, const float* __restrict__ g3, const float* __restrict__ grad,
     const float* __restrict__ P, float* __restrict__ dP, float* __restrict__ g1c,
-    float* __restrict__ dg1, float* __restrict__ dg3) {
+    float* __restrict__ dg1, float* __restrict__ dg3, const uint16_t* __restrict__ dig, int stride,
+    int lds_words, int max_hot, int hot_pieces, int2* __restrict__ hot, uint32_t* __restrict__ n_hot) {
   constexpr int TEAM = TW * kWave, TPB = kDThreads / TEAM;
   extern __shared__ __align__(16) float lds[];
+  const int listing = max_hot > 0 ? 3 : 0;  // blocks in front, one per core
+  if ((int)blockIdx.x < listing) {
+    const int core = blockIdx.x;
+    list_hot_parts((uint32_t*)lds, lds_words, dig + core * stride, B,
+                   (int)(core == 0 ? sh.n1 : core == 1 ? sh.n2 : sh.n3), hot + core * max_hot, n_hot + core,
+                   n_hot + 3 + core * max_hot * hot_pieces, max_hot * hot_pieces);
+    return;
+  }
   const int team = TW == 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave) : 0;
   const int t = threadIdx.x % TEAM;
-  const int e = blockIdx.x * TPB + team;
+  const int e = ((int)blockIdx.x - listing) * TPB + team;
   if (e >= B) return;
   const uint32_t key = (uint32_t)__builtin_amdgcn_readfirstlane((int)keys[e]);
   if (key >= sh.N) return;  // no digit row names this item: nothing of it is ever read
@@ -315,6 +365,14 @@ __global__ __launch_bounds__(kDThreads) void k_direct_bwd(
 //     rank 16: 20 us a step, 45 with one id in all positions, where a vector-ALU form for d1 > 4
 //     without loads in flight took 30 and 333; the indexed kernels 97 and 77.)
 //   G3, then G1 jobs: up to 256*VEC entries, the items dealt to groups of threads
+// Such a block takes the first kDirectPart items of its slice.  One compute unit fetches some 20 items a
+// microsecond, so a slice that more items share (a hot id, neighbouring ids) is cut into parts: the
+// backward kernel lists those beyond the first, blocks at the front of the grid take them, and the block
+// of a slice's piece that ends last adds the parts up in order and updates.  8192 ids at rank 16 of
+// n = 136^3, one step, in one block -> in parts of 512 (the indexed kernels): one id 397 -> 71 us (79),
+// 200 neighbouring ids 284 -> 67 (131), Zipf 1.2 87 -> 66 (91), uniform 41 -> 42 (98).  Parts of 256 are
+// a few us faster there, but cut slices that one block adds up sooner: n = (40,30,20), d = (5,3,4),
+// uniform ids 58 -> 72 us.
 // Sums have two levels, a short chain of the items that are in flight together and a chain of those
 // rounds, and groups join in pairs.  Error of dG2 for 1024 copies of one id (terms of one sign, 2-norm):
 // 6.5e-8, as on the indexed kernels, where one chain over all of a wavefront's items left 2.5e-7;
@@ -399,28 +457,99 @@ __device__ __forceinline__ void join_groups(float* red, int tid, int lanes, int 
   }
 }
 
-template <int RT, int CT, int RULE>
+// What a block of a slice cut into parts needs to find its siblings; for a whole block.
+struct DirectParts {
+  int slot[kDirectMax / kDirectPart];  // part -> its place among the listed parts of all cores
+  uint32_t last;
+};
+// Leaves in P where the sums of this slice's parts lie.
+__device__ __forceinline__ void find_parts(DirectParts& P, const int2* __restrict__ hot, int first, int n_hot,
+                                           int slice) {
+  for (int i = threadIdx.x; i < n_hot; i += kDThreads) {
+    const int2 h = hot[first + i];
+    if (h.x == slice) P.slot[h.y] = first + i;
+  }
+  __syncthreads();
+}
+// True in the block that is the last of `parts` to come here with this ticket; everything the others
+// stored before is then visible to it.
+__device__ __forceinline__ bool last_part(DirectParts& P, uint32_t* ticket, int parts) {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");  // every wavefront's own stores
+  __syncthreads();
+  if (threadIdx.x == 0)
+    P.last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == (uint32_t)parts;
+  __syncthreads();
+  if (P.last == 0) return false;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  return true;
+}
+
+// PARTS: slices of more than kDirectPart items are cut into parts (the batch has that many)
+template <int RT, int CT, int RULE, bool PARTS>
 __global__ __launch_bounds__(kDThreads) void k_direct_apply(
     Shape sh, int B, float lr, UpdateRule ada, const uint16_t* __restrict__ dig, int stride,
     const float* __restrict__ g1c, const float* __restrict__ dP, const float* __restrict__ dg1,
-    const float* __restrict__ dg3, float* __restrict__ g1, float* __restrict__ g2,
+    const float* __restrict__ dg3, uint32_t* n_hot, const int2* __restrict__ hot, int max_hot, int hot_pieces,
+    float* hot_sum, float* __restrict__ g1, float* __restrict__ g2,
     float* __restrict__ g3) {
   constexpr bool ADA = RULE != kUpdateSgd, ADAM = RULE == kUpdateAdam;
   constexpr int kRed = std::max(kDWaves * RT * CT * 256, kDThreads * 4);
   __shared__ DirectList L;
   __shared__ float red[kRed];
   const int tid = threadIdx.x;
+  __shared__ DirectParts parts_of;
   const int cols2 = (sh.W + 16 * CT - 1) / (16 * CT), per2 = cols2 * ((sh.r1 + 16 * RT - 1) / (16 * RT));
-  const int jobs2 = slice_blocks(sh.n2, B) * per2;
+  const int per3 = (sh.S3 + 1023) / 1024, per1 = (sh.S1 + 1023) / 1024;
+  const int most_s = max(max(sh.S1, sh.S2), sh.S3);
+  // core (0, 1, 2 for G1, G2, G3), slice, piece of the slice and part of its items
+  int core, slice, piece, part = 0, n;
   int job = blockIdx.x;
-  if (job < jobs2) {
-    const int piece = job % per2;
-    int i2;
-    const int n = slice_items(L, dig + stride, sh.n2, B, job / per2, &i2);
-    if (n == 0) return;
-    float* G = g2 + (size_t)i2 * sh.S2;
-    float* St = ADA ? ada.s2 + (size_t)i2 * sh.S2 : nullptr;
-    float* Vt = ADAM ? ada.v2 + (size_t)i2 * sh.S2 : nullptr;
+  const int hot_jobs = PARTS ? 3 * max_hot * hot_pieces : 0;  // blocks of parts beyond the first
+  if (PARTS && job < hot_jobs) {
+    const int listed = job / hot_pieces;
+    core = listed / max_hot, piece = job % hot_pieces;
+    if (listed - core * max_hot >= (int)n_hot[core]) return;
+    slice = hot[listed].x, part = hot[listed].y;
+    if (piece >= (core == 0 ? per1 : core == 1 ? per2 : per3)) return;
+    n = direct_list(L, dig + core * stride, B, slice);
+  } else {
+    job -= hot_jobs;
+    const int jobs2 = slice_blocks(sh.n2, B) * per2, jobs3 = slice_blocks(sh.n3, B) * per3;
+    core = job < jobs2 ? 1 : job < jobs2 + jobs3 ? 2 : 0;
+    job -= core == 1 ? 0 : core == 2 ? jobs2 : jobs2 + jobs3;
+    const int per = core == 1 ? per2 : core == 2 ? per3 : per1;
+    piece = job % per;
+    n = slice_items(L, dig + core * stride, core == 1 ? sh.n2 : core == 2 ? sh.n3 : sh.n1, B, job / per, &slice);
+  }
+  const int parts = PARTS ? (n + kDirectPart - 1) / kDirectPart : 1;
+  const int lo = PARTS ? part * kDirectPart : 0, hi = parts > 1 ? min(n, lo + kDirectPart) : n;
+  if (lo >= hi) return;
+  const int S = core == 0 ? sh.S1 : core == 1 ? sh.S2 : sh.S3;
+  float* G = (core == 0 ? g1 : core == 1 ? g2 : g3) + (size_t)slice * S;
+  float* St = ADA ? (core == 0 ? ada.s1 : core == 1 ? ada.s2 : ada.s3) + (size_t)slice * S : nullptr;
+  float* Vt = ADAM ? (core == 0 ? ada.v1 : core == 1 ? ada.v2 : ada.v3) + (size_t)slice * S : nullptr;
+  if (PARTS && parts > 1) find_parts(parts_of, hot, core * max_hot, (int)n_hot[core], slice);
+  // where part p leaves its sums; entries are taken or summed up by the thread that owns them
+  auto sums_of = [&](int p) {
+    return hot_sum + (size_t)(p > 0 ? parts_of.slot[p] : 3 * max_hot + parts_of.slot[1]) * most_s;
+  };
+  auto update = [&](size_t at, float s) {
+    G[at] = updated_entry<RULE>(G[at], s, lr, ada, ADA ? St + at : nullptr, ADAM ? Vt + at : nullptr);
+  };
+  auto put = [&](size_t at, float s) {
+    if (!PARTS || parts == 1) update(at, s);
+    else sums_of(part)[at] = s;
+  };
+  auto update_from_parts = [&](size_t at) {
+    float s = sums_of(0)[at];
+    for (int p = 1; p < parts; ++p) s += sums_of(p)[at];
+    update(at, s);
+  };
+  auto is_last = [&] {
+    return PARTS && parts > 1 &&
+           last_part(parts_of, &n_hot[3 + parts_of.slot[1] * hot_pieces + piece], parts);
+  };
+  if (core == 1) {
     constexpr int U = RT >= 4 ? 4 : 8;  // items in flight per wavefront
     const int w = tid / kWave, lane = tid % kWave, l16 = lane % 16, kg = lane / 16;
     const int col0 = piece % cols2 * 16 * CT, row0 = piece / cols2 * 16 * RT;
@@ -436,14 +565,14 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
     for (int i = 0; i < RT; ++i)
 #pragma unroll
       for (int j = 0; j < CT; ++j) sum[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-    for (int k = w; k < n; k += kDWaves * U)
+    for (int k = lo + w; k < hi; k += kDWaves * U)
       for (int j0 = 0; j0 < sh.d1; j0 += 4) {
         const int j1 = min(j0 + kg, sh.d1 - 1);
         const bool on = j0 + kg < sh.d1;
         float a[U][RT], b[U][CT];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          const int e = L.item[min(k + u * kDWaves, n - 1)];
+          const int e = L.item[min(k + u * kDWaves, hi - 1)];
           const float* ap = g1c + (size_t)e * sh.S1 + j1 * sh.r1;
           const float* bp = dP + (size_t)e * sh.PN + j1 * sh.W;
 #pragma unroll
@@ -459,7 +588,7 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
           for (int j = 0; j < CT; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int u = 0; u < U; ++u)
-          if (k + u * kDWaves < n)  // wavefront-uniform
+          if (k + u * kDWaves < hi)  // wavefront-uniform
 #pragma unroll
             for (int i = 0; i < RT; ++i)
 #pragma unroll
@@ -481,31 +610,24 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
           red[((w * RT * 16 + 16 * i + 4 * kg + v) * CT + j) * 16 + l16] = sum[i][j][v];
     __syncthreads();
     constexpr int kOut = RT * CT * 256;
+    auto each_entry = [&](auto body) {
 #pragma unroll
-    for (int x = 0; x < kOut / kDThreads; ++x) {
-      const int o = tid + x * kDThreads, row = row0 + o / (16 * CT), col = col0 + o % (16 * CT);
+      for (int x = 0; x < kOut / kDThreads; ++x) {
+        const int o = tid + x * kDThreads, row = row0 + o / (16 * CT), col = col0 + o % (16 * CT);
+        if (row < sh.r1 && col < sh.W) body(o, (size_t)row * sh.W + col);
+      }
+    };
+    each_entry([&](int o, size_t at) {
       float s = red[o];
 #pragma unroll
       for (int p = 1; p < kDWaves; ++p) s += red[p * kOut + o];
-      if (row >= sh.r1 || col >= sh.W) continue;
-      const size_t at = (size_t)row * sh.W + col;
-      G[at] = updated_entry<RULE>(G[at], s, lr, ada, ADA ? St + at : nullptr, ADAM ? Vt + at : nullptr);
-    }
+      put(at, s);
+    });
+    if (is_last()) each_entry([&](int, size_t at) { update_from_parts(at); });
     return;
   }
-  job -= jobs2;
-  const int jobs3 = slice_blocks(sh.n3, B) * ((sh.S3 + 1023) / 1024);
-  const bool three = job < jobs3;
-  if (!three) job -= jobs3;
-  const int S = three ? sh.S3 : sh.S1, per = (S + 1023) / 1024;
-  const int o0 = job % per * 1024, outs = min(1024, S - o0);
-  int slice;
-  const int n = slice_items(L, dig + (three ? 2 * stride : 0), three ? sh.n3 : sh.n1, B, job / per, &slice);
-  if (n == 0) return;
-  const float* src = (three ? dg3 : dg1) + o0;
-  float* G = (three ? g3 : g1) + (size_t)slice * S + o0;
-  float* St = ADA ? (three ? ada.s3 : ada.s1) + (size_t)slice * S + o0 : nullptr;
-  float* Vt = ADAM ? (three ? ada.v3 : ada.v1) + (size_t)slice * S + o0 : nullptr;
+  const int o0 = piece * 1024, outs = min(1024, S - o0);
+  const float* src = (core == 2 ? dg3 : dg1) + o0;
   auto sum = [&](auto vec) {
     constexpr int VEC = decltype(vec)::value, U = 8;
     int lanes = 1;
@@ -517,8 +639,8 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
       float acc[VEC];
 #pragma unroll
       for (int x = 0; x < VEC; ++x) acc[x] = 0.f;
-      int k = grp;
-      for (; k + (U - 1) * groups < n; k += U * groups) {
+      int k = lo + grp;
+      for (; k + (U - 1) * groups < hi; k += U * groups) {
         float v[U][VEC];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -537,7 +659,7 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
       float rest[VEC];
 #pragma unroll
       for (int x = 0; x < VEC; ++x) rest[x] = 0.f;
-      for (; k < n; k += groups) {
+      for (; k < hi; k += groups) {
         const float* p = src + (size_t)L.item[k] * S + o;
 #pragma unroll
         for (int x = 0; x < VEC; ++x) rest[x] += p[x];
@@ -547,15 +669,15 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
       join_groups<VEC>(red, tid, lanes, groups, acc);
       if (grp == 0 && on) {
 #pragma unroll
-        for (int x = 0; x < VEC; ++x)
-          G[o + x] = updated_entry<RULE>(G[o + x], acc[x], lr, ada, ADA ? St + o + x : nullptr,
-                                         ADAM ? Vt + o + x : nullptr);
+        for (int x = 0; x < VEC; ++x) put(o0 + o + x, acc[x]);
       }
       __syncthreads();
     }
   };
   if (S % 4 == 0) sum(std::integral_constant<int, 4>{});
   else sum(std::integral_constant<int, 1>{});
+  if (is_last())
+    for (int o = tid; o < outs; o += kDThreads) update_from_parts(o0 + o);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -690,7 +812,12 @@ static int team_waves(const Shape& s) { return s.W > 2 * kWave ? 4 : 1; }
 
 // Largest batch (in items) that takes the index-free kernels; 0 for shapes they do not hold.
 // Every item reads its whole G2 slice, which the sorted path reads once per sixteen prefixes: past
-// kDirectBytes of slices that costs more than the index launches it saves.
+// kDirectBytes of slices that costs more than the index launches it saves.  A training step on these
+// kernels and on the indexed ones, us, at the largest batches, for uniform ids and for a single one:
+//   rank 8, 8192 ids     40 / 95,  63 / 78        rank 64, 1024 ids    49 / 114, 82 / 81
+//   rank 16, 8192 ids    42 / 98,  71 / 79        rank 128, 256 ids    70 / 144, 70 / 93
+//   rank 32, 4096 ids    45 / 107, 77 / 75        d = (4,5,5) at rank 32, 2048 ids  39 / 141, 72 / 107
+// (n = 136^3, d = (4,4,8)).  A lookup takes 7 to 17 us at these sizes, 50 to 80 on the indexed kernels.
 int direct_capacity(const Shape& s) {
   constexpr int64_t kDirectBytes = (int64_t)64 << 20;
   const int tw = team_waves(s), teams = kDWaves / tw;
@@ -701,12 +828,19 @@ int direct_capacity(const Shape& s) {
   return (int)std::min<int64_t>(kDirectMax, kDirectBytes / ((int64_t)s.S2 * 4));
 }
 
+// Pieces that k_direct_apply cuts a slice of G2 into, and the most of any core's slice.
+static int row_tiles(const Shape& s) { return s.r1 <= 16 ? 1 : s.r1 <= 32 ? 2 : s.r1 <= 64 ? 4 : 8; }
+static int col_tiles(const Shape& s) { return row_tiles(s) <= 2 && s.W % 32 == 0 ? 2 : 1; }
+static int pieces2(const Shape& s) { return cdiv(s.W, 16 * col_tiles(s)) * cdiv(s.r1, 16 * row_tiles(s)); }
+int direct_pieces(const Shape& s) { return std::max({pieces2(s), cdiv(s.S1, 1024), cdiv(s.S3, 1024)}); }
+
 // The same for a batch that backward_update follows, which keeps 4 (2 PN + 2 S1 + S3) bytes per item:
 // no more than kDirectKept of them (8192 items at rank 16 of D = 64 keep 24 MiB, 4096 at rank 32 of
 // D = 128 24 MiB; products of thousands of floats would take hundreds).
 int direct_train_capacity(const Shape& s) {
   constexpr int64_t kDirectKept = (int64_t)32 << 20;
-  const int64_t item = 4 * (2 * (int64_t)s.PN + 2 * (int64_t)s.S1 + s.S3);
+  const int64_t item = 4 * (2 * (int64_t)s.PN + 2 * (int64_t)s.S1 + s.S3) +
+                       4 * 6 * (int64_t)std::max({s.S1, s.S2, s.S3}) / kDirectPart;  // and its share of the parts
   return (int)std::min<int64_t>(direct_capacity(s), kDirectKept / item);
 }
 
@@ -733,47 +867,56 @@ void launch_direct_fwd(const Plan& pl, const DirectBuffers& d, const IdSource& s
 void launch_direct_bwd(const Plan& pl, const DirectBuffers& d, int B, const float* g1, const float* g2,
                        const float* g3, const float* grad, hipStream_t st) {
   const Shape& s = pl.sh;
-  const int tw = team_waves(s), grid = cdiv(B, kDWaves / tw);
+  const int tw = team_waves(s), grid = cdiv(B, kDWaves / tw) + (hot_parts(B) > 0 ? 3 : 0);
   const size_t lds = (size_t)(kDWaves / tw) * bwd_lds_floats(s, tw * kWave) * sizeof(float);
   if (tw == 1)
     k_direct_bwd<1><<<grid, kDThreads, lds, st>>>(s, B, d.key, g1, g2, g3, grad, d.P, d.dP, d.g1, d.dg1,
-                                                  d.dg3);
+                                                  d.dg3, d.dig, d.stride, (int)(lds / 4), hot_parts(B),
+                                                  direct_pieces(s), d.hot, d.n_hot);
   else
     k_direct_bwd<4><<<grid, kDThreads, lds, st>>>(s, B, d.key, g1, g2, g3, grad, d.P, d.dP, d.g1, d.dg1,
-                                                  d.dg3);
+                                                  d.dg3, d.dig, d.stride, (int)(lds / 4), hot_parts(B),
+                                                  direct_pieces(s), d.hot, d.n_hot);
 }
 
 void launch_direct_apply(const Plan& pl, const DirectBuffers& d, int B, float* g1, float* g2, float* g3,
                          float lr, const UpdateRule& ada, hipEvent_t stop, hipStream_t st) {
   const Shape& s = pl.sh;
-  const int rt = s.r1 <= 16 ? 1 : s.r1 <= 32 ? 2 : s.r1 <= 64 ? 4 : 8;
-  const int ct = rt <= 2 && s.W % 32 == 0 ? 2 : 1;
-  const int per2 = cdiv(s.W, 16 * ct) * cdiv(s.r1, 16 * rt);
+  const int rt = row_tiles(s), ct = col_tiles(s), per2 = pieces2(s);
+  const int max_hot = hot_parts(B), hot_pieces = direct_pieces(s);
   // at most B times the pieces of a slice: the bounds on B keep that to about a million blocks
-  const int grid = slice_blocks(s.n2, B) * per2 + slice_blocks(s.n3, B) * cdiv(s.S3, 1024) +
+  const int grid = 3 * max_hot * hot_pieces + slice_blocks(s.n2, B) * per2 + slice_blocks(s.n3, B) * cdiv(s.S3, 1024) +
                    slice_blocks(s.n1, B) * cdiv(s.S1, 1024);
-#define TT_DA(RT, CT, RULE)                                                                        \
+#define TT_DA(RT, CT, RULE, PARTS)                                                                 \
   do {                                                                                             \
+    auto kernel = k_direct_apply<RT, CT, RULE, PARTS>;                                             \
     if (stop != nullptr)                                                                           \
-      hipExtLaunchKernelGGL((k_direct_apply<RT, CT, RULE>), dim3(grid), dim3(kDThreads), 0, st,    \
-                            nullptr, stop, 0, s, B, lr, ada, (const uint16_t*)d.dig, d.stride,     \
-                            (const float*)d.g1, (const float*)d.dP, (const float*)d.dg1,           \
-                            (const float*)d.dg3, g1, g2, g3);                                      \
+      hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(kDThreads), 0, st, nullptr, stop, 0, s, B,    \
+                            lr, ada, (const uint16_t*)d.dig, d.stride, (const float*)d.g1,         \
+                            (const float*)d.dP, (const float*)d.dg1, (const float*)d.dg3, d.n_hot, \
+                            (const int2*)d.hot, max_hot, hot_pieces, d.hot_sum, g1, g2, g3);       \
     else                                                                                           \
-      k_direct_apply<RT, CT, RULE><<<grid, kDThreads, 0, st>>>(s, B, lr, ada, d.dig, d.stride, d.g1, \
-                                                               d.dP, d.dg1, d.dg3, g1, g2, g3);    \
+      kernel<<<grid, kDThreads, 0, st>>>(s, B, lr, ada, d.dig, d.stride, d.g1, d.dP, d.dg1, d.dg3, \
+                                         d.n_hot, d.hot, max_hot, hot_pieces, d.hot_sum, g1, g2,   \
+                                         g3);                                                      \
+  } while (0)
+#define TT_DP(RT, CT, RULE)                                                                        \
+  do {                                                                                             \
+    if (max_hot > 0) TT_DA(RT, CT, RULE, true);                                                    \
+    else TT_DA(RT, CT, RULE, false);                                                               \
   } while (0)
 #define TT_DR(RT, CT)                                                                              \
   do {                                                                                             \
-    if (ada.kind == kUpdateAdam) TT_DA(RT, CT, kUpdateAdam);                                       \
-    else if (ada.kind == kUpdateAdagrad) TT_DA(RT, CT, kUpdateAdagrad);                            \
-    else TT_DA(RT, CT, kUpdateSgd);                                                                \
+    if (ada.kind == kUpdateAdam) TT_DP(RT, CT, kUpdateAdam);                                       \
+    else if (ada.kind == kUpdateAdagrad) TT_DP(RT, CT, kUpdateAdagrad);                            \
+    else TT_DP(RT, CT, kUpdateSgd);                                                                \
   } while (0)
   if (rt == 1) { if (ct == 2) TT_DR(1, 2); else TT_DR(1, 1); }
   else if (rt == 2) { if (ct == 2) TT_DR(2, 2); else TT_DR(2, 1); }
   else if (rt == 4) TT_DR(4, 1);
   else TT_DR(8, 1);
 #undef TT_DR
+#undef TT_DP
 #undef TT_DA
 }
 

@@ -139,7 +139,15 @@ struct DirectBuffers {
   float* g1;        // its G1 slice before the update         [cap][S1]
   float* dg1;       // its term of dG1[i1]                    [cap][S1]
   float* dg3;       // its term of dG3[i3]                    [cap][S3]
+  // parts of slices that many items share (k_direct_apply), listed by the backward kernel
+  int2* hot;        // {slice, part number from 1 on}       [3 cores][hot_parts]
+  uint32_t* n_hot;  // parts listed per core; then tickets  [3] + [3*hot_parts][pieces of a slice]
+  float* hot_sum;   // sums of those parts, then of the first parts  [2*3*hot_parts][largest slice]
 };
+// Items of a slice that one block adds up; the rest are parts of their own.
+constexpr int kDirectPart = 512;
+// most parts beyond the first that the slices of a core have
+inline int hot_parts(int64_t items) { return items > kDirectPart ? (int)(items / kDirectPart) : 0; }
 
 // All device arrays carved out of the caller's workspace.
 struct Workspace {

@@ -290,3 +290,25 @@ def test_prepare_of_a_small_batch_orders_its_forward():
     for x, b in zip(got, batches):
         assert row_error(x.cpu().numpy(), ora.forward(s, *cores, b.cpu().numpy())) <= ROW_TOL
     emb.close()
+
+
+@pytest.mark.parametrize("n,d,r", [((9, 11, 13), (4, 4, 8), (16, 16)), ((9, 11, 13), (4, 4, 4), (64, 64)),
+                                   ((40, 30, 20), (8, 4, 4), (16, 16)), ((9, 11, 300), (5, 3, 2), (7, 300))])
+@pytest.mark.parametrize("hot", [511, 512, 513, 1024, 1025, 1300])
+def test_slices_of_many_items_in_parts(n, d, r, hot):
+    """Slices that 512 items share and slices that more share, one of every core, beside slices with few
+    items and slices with a part and a bit: parts that are full and one item long.  The parts are
+    listed in the order in which the device counts, the sums do not depend on it."""
+    rng, B = np.random.default_rng(hot), 2000 if r[0] < 64 else 1024
+    hot = min(hot, B)
+    i = [rng.integers(0, k, B) for k in n]
+    i[0][:hot], i[1][:hot], i[2][:hot] = 1, 2, 3              # one id
+    i[1][hot:hot + 600] = 4                                   # a shared slice of G2 only
+    ids = ((i[0] * n[1] + i[1]) * n[2] + i[2]).astype(np.int64)
+    rng.shuffle(ids)
+    s, cores, _, grad = _inputs(n, d, r, B, hot)
+    _, new, _ = check_against_oracle(n, d, r, cores, ids, grad, 0.01)
+    for _ in range(3):
+        _, again, _ = run_gpu(n, d, r, cores, ids, grad, 0.01)
+        for a, b in zip(new, again):
+            np.testing.assert_array_equal(a, b)
