@@ -56,7 +56,7 @@ void launch_direct_bwd(const Plan&, const DirectBuffers&, int B, const float* g1
                        const float* g3, const float* grad, hipStream_t);
 void launch_direct_apply(const Plan&, const DirectBuffers&, int B, float* g1, float* g2, float* g3,
                          float lr, const UpdateRule&, hipEvent_t stop, hipStream_t);
-bool table_shape(const Plan&);
+bool table_streamed(const Plan&, int64_t count);
 void launch_table(const Plan&, const float* g1, const float* g2, const float* g3, int64_t first,
                   int64_t count, float* out, hipStream_t);
 hipError_t calibrate(void* buf, size_t bytes, hipStream_t, double* copy_bytes_per_s,
@@ -726,7 +726,7 @@ int tt_emb_materialize(tt_emb_t h, int64_t first_row, int64_t count, float* out,
   if (count > 0 && (out == nullptr || ((uintptr_t)out & (h->mfma ? 15u : 3u)) != 0))
     return TT_EMB_EINVAL;
   if (h->pending_B >= 0) return TT_EMB_ESTATE;  // would overwrite what the pending backward needs
-  if (count > 0 && table_shape(h->plan)) {
+  if (count > 0 && table_streamed(h->plan, count)) {
     hipStream_t st = (hipStream_t)hip_stream;
     if (h->side[0] != nullptr && stream_is_capturing(st)) return TT_EMB_ESTATE;
     return run_slot(h, kSlotTable, st, [&] {

@@ -920,10 +920,25 @@ void launch_direct_apply(const Plan& pl, const DirectBuffers& d, int B, float* g
 #undef TT_DA
 }
 
-// Shapes whose product and kTableIds G3 slices fit a block's LDS (else the caller looks the rows up)
-bool table_shape(const Plan& pl) {
+// Whether a run of `count` rows is streamed by these kernels; else the caller looks the rows up.  The
+// product and kTableIds G3 slices have to fit a block's LDS.  And every wavefront or block forms its
+// prefixes' products by itself, where the lookup shares each G2 slice among sixteen prefixes: with
+// products of many multiplications, few rows for each and many prefixes at a time that decides.  Rows of
+// 31,250 prefixes (4,096 prefixes) with n3 rows each, streamed / looked up, us:
+//   rank 128, d = (4,4,8)   n3 = 1  1129 / 666 (151 / 152)    n3 = 16  1136 / 751 (157 / 153)
+//                           n3 = 32 1162 / 1207 (176 / 209)
+//   rank 128, d = (8,4,4)   n3 = 2  1350 / 884 (168 / 319)    n3 = 32  1706 / 1563 (216 / 268)
+//   rank 128, d = (4,5,5)   n3 = 2  1340 / 1037 (176 / 243)   n3 = 8   1482 / 1498 (212 / 282)
+//   ranks (300,40), d = (4,4,4)  n3 = 1  811 / 694 (94 / 153)
+//   rank 64, d = (4,4,8)    n3 = 1  226 / 494 (35 / 123)
+bool table_streamed(const Plan& pl, int64_t count) {
   const Shape& s = pl.sh;
-  return pl.mfma || ((size_t)((kTableIds * s.S3 + 3) & ~3) + (size_t)s.M * (s.r2 + 1)) * 4 <= kDirectLds;
+  if (!pl.mfma && ((size_t)((kTableIds * s.S3 + 3) & ~3) + (size_t)s.M * (s.r2 + 1)) * 4 > kDirectLds)
+    return false;
+  const int64_t product = (int64_t)s.d1 * s.r1 * s.W;
+  constexpr int64_t kTableProduct = 1 << 17, kTablePrefixes = 1 << 14;
+  return product < kTableProduct || s.n3 > product >> (pl.mfma ? 14 : 16) ||
+         std::min(count, pl.user_maxB) < kTablePrefixes * s.n3;
 }
 
 void launch_table(const Plan& pl, const float* g1, const float* g2, const float* g3, int64_t first,

@@ -312,3 +312,22 @@ def test_slices_of_many_items_in_parts(n, d, r, hot):
         _, again, _ = run_gpu(n, d, r, cores, ids, grad, 0.01)
         for a, b in zip(new, again):
             np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("n,d,max_batch,streamed", [((128, 132, 2), (4, 4, 8), 32_768, False),
+                                                    ((128, 132, 2), (8, 4, 4), 32_768, False),
+                                                    ((128, 132, 2), (4, 4, 8), 32_767, True),
+                                                    ((128, 132, 1), (4, 5, 5), 16_384, False),
+                                                    ((32, 32, 17), (4, 4, 8), 17_408, True)])
+def test_large_products_with_few_rows_are_looked_up(n, d, max_batch, streamed):
+    """Rank 128: rows are streamed unless few of them share a product and many products are asked for at
+    once, where the lookup's sharing of the G2 slices pays."""
+    from paper_2206_10581_amd import TTEmbedding
+    r = (128, 128)
+    s, cores, _, _ = _inputs(n, d, r, 16, 9)
+    emb = TTEmbedding(n, d, r, max_batch, cores)
+    emb.profile(True)
+    got = emb.materialize(1, s.N - 2).cpu().numpy()
+    assert (emb.profile_read()["table"]["launches"] > 0) == streamed
+    assert row_error(got, ora.forward(s, *cores, np.arange(1, s.N - 1, dtype=np.int64))) <= ROW_TOL
+    emb.close()
