@@ -263,7 +263,7 @@ static size_t carve(const Plan& pl, char* base, Workspace* ws /* [kSets] or null
     d.g1 = (float*)take(cap * s.S1 * 4);
     d.dg1 = (float*)take(cap * s.S1 * 4);
     d.dg3 = (float*)take(cap * s.S3 * 4);
-    const size_t parts = 3 * (size_t)hot_parts((int64_t)cap);
+    const size_t parts = 3 * (size_t)hot_parts(s, (int64_t)cap);
     d.hot = (int2*)take(parts * 8);
     d.n_hot = (uint32_t*)take((3 + parts * direct_pieces(s)) * 4);
     d.hot_sum = (float*)take(2 * parts * std::max({s.S1, s.S2, s.S3}) * 4);

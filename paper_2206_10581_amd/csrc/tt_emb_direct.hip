@@ -179,11 +179,11 @@ __global__ __launch_bounds__(kDThreads) void k_direct_fwd(
   }
 }
 
-// Lists the parts beyond the first of the slices of one core that more than kDirectPart items share, and
+// Lists the parts beyond the first of the slices of one core that more than `most` items share, and
 // clears the tickets of those parts; for a whole block, with `bins` words of LDS.  (Counted per item with
 // device atomics, 8192 items of three cores took 56 us.)
 __device__ void list_hot_parts(uint32_t* lds, int bins, const uint16_t* __restrict__ dig, int B, int n,
-                               int2* __restrict__ hot, uint32_t* __restrict__ n_hot, uint32_t* __restrict__ tickets,
+                               int most, int2* __restrict__ hot, uint32_t* __restrict__ n_hot, uint32_t* __restrict__ tickets,
                                int n_tickets) {
   const int tid = threadIdx.x;
   uint32_t* listed = lds;  // one word, then the counters
@@ -214,7 +214,7 @@ __device__ void list_hot_parts(uint32_t* lds, int bins, const uint16_t* __restri
     }
     __syncthreads();
     for (int i = tid; i < here; i += kDThreads)
-      for (int p = 1; p * kDirectPart < (int)cnt[i]; ++p) hot[atomicAdd(listed, 1u)] = make_int2(s0 + i, p);
+      for (int p = 1; p * most < (int)cnt[i]; ++p) hot[atomicAdd(listed, 1u)] = make_int2(s0 + i, p);
     __syncthreads();
   }
   if (tid == 0) *n_hot = *listed;
@@ -233,7 +233,7 @@ __global__ __launch_bounds__(kDThreads) void k_direct_bwd(
   if ((int)blockIdx.x < listing) {
     const int core = blockIdx.x;
     list_hot_parts((uint32_t*)lds, lds_words, dig + core * stride, B,
-                   (int)(core == 0 ? sh.n1 : core == 1 ? sh.n2 : sh.n3), hot + core * max_hot, n_hot + core,
+                   (int)(core == 0 ? sh.n1 : core == 1 ? sh.n2 : sh.n3), direct_part(sh), hot + core * max_hot, n_hot + core,
                    n_hot + 3 + core * max_hot * hot_pieces, max_hot * hot_pieces);
     return;
   }
@@ -365,7 +365,7 @@ __global__ __launch_bounds__(kDThreads) void k_direct_bwd(
 //     rank 16: 20 us a step, 45 with one id in all positions, where a vector-ALU form for d1 > 4
 //     without loads in flight took 30 and 333; the indexed kernels 97 and 77.)
 //   G3, then G1 jobs: up to 256*VEC entries, the items dealt to groups of threads
-// Such a block takes the first kDirectPart items of its slice.  One compute unit fetches some 20 items a
+// Such a block takes the first direct_part() items of its slice.  One compute unit fetches some 20 items a
 // microsecond, so a slice that more items share (a hot id, neighbouring ids) is cut into parts: the
 // backward kernel lists those beyond the first, blocks at the front of the grid take them, and the block
 // of a slice's piece that ends last adds the parts up in order and updates.  8192 ids at rank 16 of
@@ -459,7 +459,7 @@ __device__ __forceinline__ void join_groups(float* red, int tid, int lanes, int 
 
 // What a block of a slice cut into parts needs to find its siblings; for a whole block.
 struct DirectParts {
-  int slot[kDirectMax / kDirectPart];  // part -> its place among the listed parts of all cores
+  int slot[kDirectMax / kDirectPartLeast];  // part -> its place among the listed parts of all cores
   uint32_t last;
 };
 // Leaves in P where the sums of this slice's parts lie.
@@ -484,7 +484,7 @@ __device__ __forceinline__ bool last_part(DirectParts& P, uint32_t* ticket, int 
   return true;
 }
 
-// PARTS: slices of more than kDirectPart items are cut into parts (the batch has that many)
+// PARTS: slices of more than direct_part() items are cut into parts (the batch has that many)
 template <int RT, int CT, int RULE, bool PARTS>
 __global__ __launch_bounds__(kDThreads) void k_direct_apply(
     Shape sh, int B, float lr, UpdateRule ada, const uint16_t* __restrict__ dig, int stride,
@@ -521,8 +521,8 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
     piece = job % per;
     n = slice_items(L, dig + core * stride, core == 1 ? sh.n2 : core == 2 ? sh.n3 : sh.n1, B, job / per, &slice);
   }
-  const int parts = PARTS ? (n + kDirectPart - 1) / kDirectPart : 1;
-  const int lo = PARTS ? part * kDirectPart : 0, hi = parts > 1 ? min(n, lo + kDirectPart) : n;
+  const int most = direct_part(sh), parts = PARTS ? (n + most - 1) / most : 1;
+  const int lo = PARTS ? part * most : 0, hi = parts > 1 ? min(n, lo + most) : n;
   if (lo >= hi) return;
   const int S = core == 0 ? sh.S1 : core == 1 ? sh.S2 : sh.S3;
   float* G = (core == 0 ? g1 : core == 1 ? g2 : g3) + (size_t)slice * S;
@@ -840,7 +840,7 @@ int direct_pieces(const Shape& s) { return std::max({pieces2(s), cdiv(s.S1, 1024
 int direct_train_capacity(const Shape& s) {
   constexpr int64_t kDirectKept = (int64_t)32 << 20;
   const int64_t item = 4 * (2 * (int64_t)s.PN + 2 * (int64_t)s.S1 + s.S3) +
-                       4 * 6 * (int64_t)std::max({s.S1, s.S2, s.S3}) / kDirectPart;  // and its share of the parts
+                       4 * 6 * (int64_t)std::max({s.S1, s.S2, s.S3}) / direct_part(s);  // and its share of the parts
   return (int)std::min<int64_t>(direct_capacity(s), kDirectKept / item);
 }
 
@@ -867,15 +867,15 @@ void launch_direct_fwd(const Plan& pl, const DirectBuffers& d, const IdSource& s
 void launch_direct_bwd(const Plan& pl, const DirectBuffers& d, int B, const float* g1, const float* g2,
                        const float* g3, const float* grad, hipStream_t st) {
   const Shape& s = pl.sh;
-  const int tw = team_waves(s), grid = cdiv(B, kDWaves / tw) + (hot_parts(B) > 0 ? 3 : 0);
+  const int tw = team_waves(s), grid = cdiv(B, kDWaves / tw) + (hot_parts(s, B) > 0 ? 3 : 0);
   const size_t lds = (size_t)(kDWaves / tw) * bwd_lds_floats(s, tw * kWave) * sizeof(float);
   if (tw == 1)
     k_direct_bwd<1><<<grid, kDThreads, lds, st>>>(s, B, d.key, g1, g2, g3, grad, d.P, d.dP, d.g1, d.dg1,
-                                                  d.dg3, d.dig, d.stride, (int)(lds / 4), hot_parts(B),
+                                                  d.dg3, d.dig, d.stride, (int)(lds / 4), hot_parts(s, B),
                                                   direct_pieces(s), d.hot, d.n_hot);
   else
     k_direct_bwd<4><<<grid, kDThreads, lds, st>>>(s, B, d.key, g1, g2, g3, grad, d.P, d.dP, d.g1, d.dg1,
-                                                  d.dg3, d.dig, d.stride, (int)(lds / 4), hot_parts(B),
+                                                  d.dg3, d.dig, d.stride, (int)(lds / 4), hot_parts(s, B),
                                                   direct_pieces(s), d.hot, d.n_hot);
 }
 
@@ -883,7 +883,7 @@ void launch_direct_apply(const Plan& pl, const DirectBuffers& d, int B, float* g
                          float lr, const UpdateRule& ada, hipEvent_t stop, hipStream_t st) {
   const Shape& s = pl.sh;
   const int rt = row_tiles(s), ct = col_tiles(s), per2 = pieces2(s);
-  const int max_hot = hot_parts(B), hot_pieces = direct_pieces(s);
+  const int max_hot = hot_parts(s, B), hot_pieces = direct_pieces(s);
   // at most B times the pieces of a slice: the bounds on B keep that to about a million blocks
   const int grid = 3 * max_hot * hot_pieces + slice_blocks(s.n2, B) * per2 + slice_blocks(s.n3, B) * cdiv(s.S3, 1024) +
                    slice_blocks(s.n1, B) * cdiv(s.S1, 1024);

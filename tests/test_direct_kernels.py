@@ -293,10 +293,10 @@ def test_prepare_of_a_small_batch_orders_its_forward():
 
 
 @pytest.mark.parametrize("n,d,r", [((9, 11, 13), (4, 4, 8), (16, 16)), ((9, 11, 13), (4, 4, 4), (64, 64)),
-                                   ((40, 30, 20), (8, 4, 4), (16, 16)), ((9, 11, 300), (5, 3, 2), (7, 300))])
-@pytest.mark.parametrize("hot", [511, 512, 513, 1024, 1025, 1300])
+                                   ((40, 30, 20), (8, 4, 4), (16, 16)), ((9, 11, 300), (5, 3, 2), (7, 300)), ((9, 8, 7), (20, 1, 9), (70, 2))])
+@pytest.mark.parametrize("hot", [64, 65, 256, 257, 511, 512, 513, 1024, 1025, 1300])
 def test_slices_of_many_items_in_parts(n, d, r, hot):
-    """Slices that 512 items share and slices that more share, one of every core, beside slices with few
+    """Slices that as many items share as a part holds (64 to 512) and slices that more share, one of every core, beside slices with few
     items and slices with a part and a bit: parts that are full and one item long.  The parts are
     listed in the order in which the device counts, the sums do not depend on it."""
     rng, B = np.random.default_rng(hot), 2000 if r[0] < 64 else 1024
