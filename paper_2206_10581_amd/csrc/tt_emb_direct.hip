@@ -812,20 +812,27 @@ static int team_waves(const Shape& s) { return s.W > 2 * kWave ? 4 : 1; }
 
 // Largest batch (in items) that takes the index-free kernels; 0 for shapes they do not hold.
 // Every item reads its whole G2 slice, which the sorted path reads once per sixteen prefixes: past
-// kDirectBytes of slices that costs more than the index launches it saves.  A training step on these
+// kDirectBytes of slices that costs more than the index launches it saves.  And it forms a product of
+// its own: the same bound holds for those (d = (8,9,1), r = (2,100), 28 KiB each: a lookup of 2048 ids 38
+// us against 61 to 91, of 8192 125 against 63 to 155).  And it waits for its rounds of loads one after
+// the other: past kDirectRounds of them the limit falls (d = (20,1,9), r = (70,2), 25 rounds: 8000 ids 70
+// us against 51 to 68).  A training step on these
 // kernels and on the indexed ones, us, at the largest batches, for uniform ids and for a single one:
-//   rank 8, 8192 ids     40 / 95,  63 / 78        rank 64, 1024 ids    49 / 114, 82 / 81
+//   rank 8, 8192 ids     40 / 95,  63 / 78        rank 64, 1024 ids    49 / 114, 71 / 81
 //   rank 16, 8192 ids    42 / 98,  71 / 79        rank 128, 256 ids    70 / 144, 70 / 93
 //   rank 32, 4096 ids    45 / 107, 77 / 75        d = (4,5,5) at rank 32, 2048 ids  39 / 141, 72 / 107
 // (n = 136^3, d = (4,4,8)).  A lookup takes 7 to 17 us at these sizes, 50 to 80 on the indexed kernels.
 int direct_capacity(const Shape& s) {
   constexpr int64_t kDirectBytes = (int64_t)64 << 20;
+  constexpr int64_t kDirectRounds = 16;
   const int tw = team_waves(s), teams = kDWaves / tw;
   if (s.n1 >= 0xffffu) return 0;  // digits are 16-bit
   if ((size_t)teams * fwd_lds_floats(s) * 4 > kDirectLds ||
       (size_t)teams * bwd_lds_floats(s, tw * kWave) * 4 > kDirectLds)
     return 0;
-  return (int)std::min<int64_t>(kDirectMax, kDirectBytes / ((int64_t)s.S2 * 4));
+  const int64_t rounds = (int64_t)cdiv(s.d1, 4) * cdiv(s.r1, 16) * cdiv(s.W, 2 * tw * kWave);
+  return (int)std::min<int64_t>(kDirectMax * kDirectRounds / std::max(rounds, kDirectRounds),
+                                kDirectBytes / ((int64_t)std::max(s.S2, s.PN) * 4));
 }
 
 // Pieces that k_direct_apply cuts a slice of G2 into, and the most of any core's slice.

@@ -146,7 +146,7 @@ struct DirectBuffers {
 };
 // Items of a slice that one block adds up; the rest are parts of their own.  A block takes about 50 ns per
 // item at ranks up to 32, 85 to 115 at larger ones and 400 at d1 = 20, r1 = 70: parts of 20 to 30 us each
-// (700 copies of one id there: 344 us a step in parts of 512, 72 in parts of 64; the indexed kernels 103).
+// (700 copies of one id there: 344 us a step in parts of 512, 104 in parts of 64; the indexed kernels 103).
 __host__ __device__ inline int direct_part(const Shape& s) {
   return 512 >> ((s.r1 > 32 ? 1 : 0) + (s.d1 > 8 ? 2 : 0));
 }
