@@ -331,7 +331,8 @@ __global__ __launch_bounds__(kThreads) void k_row_fwd(Shape sh, int B, const flo
 // With V4 (r2 a multiple of four) operands move sixteen bytes at a time: P_q and the first 256 floats
 // of the G3 slice are all in flight before the first is needed, the slice is kept transposed, and a
 // lane's product reads four contraction indices per LDS access.  Every element is still formed in
-// index order.
+// index order.  It is for products of 256 floats on: smaller ones leave most lanes of those loads idle
+// (D = 8, r2 = 4: 42 -> 54 us at 600,000 ids).
 // Needs row_floats() floats of LDS per wavefront (blocks have as many wavefronts, up to four,
 // as the budget allows); shapes too large for even one take k_row_fwd.
 __host__ __device__ inline int row_pad(const Shape& sh, bool v4) { return sh.r2 + (v4 ? 4 : 1); }
@@ -874,7 +875,7 @@ void launch_row_fwd(const Plan& pl, const Workspace& ws, const float* g3, int B,
   const int tiles = cdiv(B, kTileSlots);
   const int grid = grid_for(cdiv(tiles, kWavesPerBlock), kGridCap);
   const Shape& s = pl.sh;
-  const bool v4 = s.r2 % 4 == 0 && (size_t)row_floats(s, true) * sizeof(float) <= kLdsBudget;
+  const bool v4 = s.r2 % 4 == 0 && s.PN >= 4 * kWave && (size_t)row_floats(s, true) * sizeof(float) <= kLdsBudget;
   const size_t per_wave = (size_t)row_floats(s, v4) * sizeof(float);
   if (per_wave <= kLdsBudget) {
     const int wpb = (int)std::min<size_t>(kWavesPerBlock, kLdsBudget / per_wave);
