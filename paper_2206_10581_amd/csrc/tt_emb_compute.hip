@@ -148,7 +148,7 @@ struct WaveGemmLds {
   float b[kGemmDepth][kWaveStride];
 };
 
-template <bool A_KFAST, bool B_KFAST, class FA, class FB, class FC>
+template <bool AHEAD, bool A_KFAST, bool B_KFAST, class FA, class FB, class FC>
 __device__ __forceinline__ void wave_gemm(WaveGemmLds& L, int M, int N, int K, FA fa, FB fb, FC fc) {
   constexpr int kPer = kWaveTile * kGemmDepth / kWave;  // operand elements a lane stages
   const int lane = threadIdx.x % kWave, l16 = lane % 16, kg = lane / 16;
@@ -159,8 +159,9 @@ __device__ __forceinline__ void wave_gemm(WaveGemmLds& L, int M, int N, int K, F
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = gemm_f4{0.f, 0.f, 0.f, 0.f};
-      // The operands of step k0 + kGemmDepth are fetched while step k0 is multiplied.  Indices are
-      // clamped rather than tested: the loads of a step have no branches between them.
+      // With AHEAD the operands of step k0 + kGemmDepth are fetched while step k0 is multiplied, and
+      // indices are clamped rather than tested: the loads of a step have no branches between them.
+      // Without it only what exists is loaded, and half the registers do.
       float ra[kPer], rb[kPer];
       auto fetch = [&](int k0) {
 #pragma unroll
@@ -175,15 +176,23 @@ __device__ __forceinline__ void wave_gemm(WaveGemmLds& L, int M, int N, int K, F
           rb[i] = bn < N && bk < K ? y : 0.f;
         }
       };
-      fetch(0);
+      if constexpr (AHEAD) fetch(0);
       for (int k0 = 0; k0 < K; k0 += kGemmDepth) {
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
           const int e = lane + i * kWave;
-          L.a[A_KFAST ? e % kGemmDepth : e / kWaveTile][A_KFAST ? e / kGemmDepth : e % kWaveTile] = ra[i];
-          L.b[B_KFAST ? e % kGemmDepth : e / kWaveTile][B_KFAST ? e / kGemmDepth : e % kWaveTile] = rb[i];
+          const int am = A_KFAST ? e / kGemmDepth : e % kWaveTile, ak = A_KFAST ? e % kGemmDepth : e / kWaveTile;
+          const int bn = B_KFAST ? e / kGemmDepth : e % kWaveTile, bk = B_KFAST ? e % kGemmDepth : e / kWaveTile;
+          if constexpr (AHEAD) {
+            L.a[ak][am] = ra[i];
+            L.b[bk][bn] = rb[i];
+          } else {
+            L.a[ak][am] = m0 + am < M && k0 + ak < K ? fa(m0 + am, k0 + ak) : 0.f;
+            L.b[bk][bn] = n0 + bn < N && k0 + bk < K ? fb(k0 + bk, n0 + bn) : 0.f;
+          }
         }
-        if (k0 + kGemmDepth < K) fetch(k0 + kGemmDepth);
+        if constexpr (AHEAD)
+          if (k0 + kGemmDepth < K) fetch(k0 + kGemmDepth);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -547,6 +556,7 @@ __global__ __launch_bounds__(kThreads) void k_gsum_fix(Shape sh, const int* __re
 // into (u, j3) by a multiplication with inv_d3 = ceil(2^20 / d3), exact while index * d3 < 2^20
 // (the host passes 0 for d3 above 64; ids past the table divide).
 constexpr int kIdTable = kWave;
+template <bool TABLE>
 __global__ __launch_bounds__(kThreads) void k_u_bwd(Shape sh, uint32_t inv_d3,
                                                     const float* __restrict__ g3,
                                                     const float* __restrict__ grad,
@@ -557,19 +567,19 @@ __global__ __launch_bounds__(kThreads) void k_u_bwd(Shape sh, uint32_t inv_d3,
                                                     float* __restrict__ dPsum,
                                                     const Counters* __restrict__ ctr) {
   __shared__ WaveGemmLds L[kWavesPerBlock];
-  __shared__ const float* g_at[kWavesPerBlock][kIdTable];  // gradient row of the prefix's t-th id
-  __shared__ const float* c_at[kWavesPerBlock][kIdTable];  // its G3 slice
+  __shared__ const float* g_at[TABLE ? kWavesPerBlock : 1][kIdTable];  // gradient row of the prefix's t-th id
+  __shared__ const float* c_at[TABLE ? kWavesPerBlock : 1][kIdTable];  // its G3 slice
   const int Q = ctr->Q, w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   for (int q = blockIdx.x * kWavesPerBlock + w; q < Q; q += gridDim.x * kWavesPerBlock) {
     const int u0 = q_us[q], u1 = q_us[q + 1];
     float* dst = dPsum + (size_t)q * sh.PN;
-    if (u0 + lane < u1) {
+    if (TABLE && u0 + lane < u1) {
       g_at[w][lane] = grad_of_unique(u0 + lane, u_code, grad, gsum, sh.D);
       c_at[w][lane] = g3 + (size_t)u_i3[u0 + lane] * sh.S3;
     }
-    wave_sync();
+    if (TABLE) wave_sync();
     auto product = [&](auto ga, auto ca, auto split) {
-      wave_gemm<true, true>(
+      wave_gemm<TABLE, true, true>(
           L[w], sh.M, sh.r2, (u1 - u0) * sh.d3,
           [&](int m, int k) {
             const int t = split(k);
@@ -581,14 +591,14 @@ __global__ __launch_bounds__(kThreads) void k_u_bwd(Shape sh, uint32_t inv_d3,
           },
           [&](int m, int n, float v) { dst[m * sh.r2 + n] = v; });
     };
-    if (u1 - u0 <= kIdTable && inv_d3 != 0)  // uniform for the wavefront
+    if (TABLE && u1 - u0 <= kIdTable && inv_d3 != 0)  // uniform for the wavefront
       product([&](int t) { return g_at[w][t]; }, [&](int t) { return c_at[w][t]; },
               [&](int k) { return (int)(((uint32_t)k * inv_d3) >> 20); });
     else
       product([&](int t) { return grad_of_unique(u0 + t, u_code, grad, gsum, sh.D); },
               [&](int t) { return g3 + (size_t)u_i3[u0 + t] * sh.S3; },
               [&](int k) { return k / sh.d3; });
-    wave_sync();  // the table is read before the next prefix overwrites it
+    if (TABLE) wave_sync();  // the table is read before the next prefix overwrites it
   }
 }
 
@@ -911,12 +921,31 @@ void launch_gsum_fix(const Plan& pl, const Workspace& ws, int B, hipStream_t st)
   k_gsum_fix<<<grid, kThreads, 0, st>>>(pl.sh, ws.s_u, ws.u_rs, ws.carry, ws.gsum, ws.ctr);
 }
 
+// Where rows lie in a table and operands are fetched ahead (see k_u_bwd), a wavefront needs 113 registers
+// instead of 66 and loads a whole tile's worth at once; products of up to 64 elements whose prefixes have
+// few ids do not repay that.  Times of the kernel with and without, 200,000 uniform ids, us:
+//   d, r                      n = (3000,400,20): 1 id each    n = (40,40,40): 55 ids each
+//   (2,2,2), 4                219 / 145                       17 / 17
+//   (2,2,2), 16               218 / 177                       21 / 21
+//   (4,4,4), 4                220 / 189                       25 / 36
+//   (4,4,4), 12               236 / 259                       25 / 40
+//   (4,5,5), 32               288 / 434                       32 / 90
+// (4,4,4), 4 with three ids each: 91 / 81.
+static bool u_bwd_table(const Plan& pl, int B) {
+  const Shape& s = pl.sh;
+  return s.PN > 64 || (s.M > 4 && B >= 8 * (int64_t)s.n1 * s.n2);
+}
+
 void launch_u_bwd(const Plan& pl, const Workspace& ws, const float* g3, const float* grad, int B,
                   hipStream_t st) {
   const int grid = grid_for(cdiv(std::min<int64_t>(B, pl.maxQ), kWavesPerBlock), kGridCap * 4);
   const uint32_t inv = pl.sh.d3 <= 64 ? ((1u << 20) + (uint32_t)pl.sh.d3 - 1) / (uint32_t)pl.sh.d3 : 0u;
-  k_u_bwd<<<grid, kThreads, 0, st>>>(pl.sh, inv, g3, grad, ws.gsum, ws.u_code, ws.u_i3, ws.q_us, ws.dPsum,
-                                     ws.ctr);
+  auto launch = [&](auto kernel) {
+    kernel<<<grid, kThreads, 0, st>>>(pl.sh, inv, g3, grad, ws.gsum, ws.u_code, ws.u_i3, ws.q_us, ws.dPsum,
+                                      ws.ctr);
+  };
+  if (u_bwd_table(pl, B)) launch(k_u_bwd<true>);
+  else launch(k_u_bwd<false>);
 }
 
 void launch_dg3(const Plan& pl, const Workspace& ws, const float* grad, int B, hipStream_t st) {

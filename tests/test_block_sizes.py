@@ -51,6 +51,15 @@ def test_any_shape_rows_and_prefix_gradients(d, r):
     _check((40, 45, 20), d, r, 9_001, seed=1)  # and here a handful
 
 
+@pytest.mark.parametrize("n,d,r", [((9, 8, 150), (2, 2, 4), (4, 16)), ((9, 8, 150), (4, 4, 4), (4, 4)),
+                                   ((9, 8, 150), (2, 4, 8), (4, 9)), ((70, 60, 5), (4, 4, 4), (4, 4)),
+                                   ((70, 60, 5), (3, 3, 3), (6, 7))])
+def test_small_prefix_gradients(n, d, r):
+    """Products of up to 64 elements and one above, of prefixes with many ids and with few: with and
+    without the id table."""
+    _check(n, d, r, 9_001)
+
+
 @pytest.mark.parametrize("d,r", [((4, 5, 5), (32, 32)), ((16, 2, 3), (5, 32)), ((17, 2, 3), (5, 33)),
                                  ((3, 5, 4), (70, 13)), ((2, 1, 9), (1, 1))])
 def test_prefix_products_by_columns(d, r):
