@@ -53,9 +53,11 @@ HBM_PEAK = 8.0e12        # bytes/s, MI355X HBM3E
 FP32_PEAK = 157.3e12     # flop/s, MI355X fp32 (fp32 MFMA; the vector ALUs reach it with packed ops only)
 ROW_TOL, CORE_TOL, STEP_TOL = 1e-5, 1e-4, 1e-4   # the tolerances of tests/test_gpu_parity.py
 
-# kernel slot of the library's timing hooks -> kernel name in the rocprofv3 summaries
-SLOT_KERNEL = {"row_fwd": "k_row_fwd_mfma", "gsum": "k_gsum_block", "u_bwd": "k_bwd_mid_mfma",
-               "prefix_fwd": "k_prefix_fwd_mfma", "sgd": "k_sgd", "prefix_bwd": "k_prefix_bwd_mfma"}
+# kernel slot of the library's timing hooks -> kernel names in the rocprofv3 summaries (the first for
+# ranks up to 32, the last for ranks 64 and 128)
+SLOT_KERNEL = {"row_fwd": ("k_row_fwd_mfma",), "gsum": ("k_gsum_block",), "sgd": ("k_sgd",),
+               "u_bwd": ("k_bwd_mid_mfma", "k_id_bwd_mfma"),
+               "prefix_fwd": ("k_prefix_fwd_mfma", "k_prefix_fwd_wide"), "prefix_bwd": ("k_prefix_bwd_wide",)}
 
 
 def measured_traffic(config: int, slot: str):
@@ -63,12 +65,12 @@ def measured_traffic(config: int, slot: str):
     counter summary under profiles/ (scaled FETCH_SIZE + WRITE_SIZE columns); None if that
     workload or kernel has no summary."""
     path = os.path.join(ROOT, "profiles", f"step_config{config}_hbm_traffic.md")
-    kernel = SLOT_KERNEL.get(slot)
-    if kernel is None or not os.path.exists(path):
+    kernels = SLOT_KERNEL.get(slot)
+    if kernels is None or not os.path.exists(path):
         return None
     for line in open(path):
         m = re.match(r"\|\s*`(k_[a-z0-9_]+)[^`]*`\s*\|(.*)\|\s*$", line)
-        if m and m.group(1) == kernel:
+        if m and m.group(1) in kernels:
             cols = [c.strip() for c in m.group(2).split("|")]
             try:
                 return (float(cols[-2]) + float(cols[-1])) * 1e6

@@ -155,7 +155,8 @@ int tt_emb_lookup_static(const tt_emb_config* cfg, const float* g1, const float*
 /*
  * Writes the rows first_row .. first_row+count-1 of the table W itself (Section 3, Eq. "tt-matrix":
  * the dense matrix the cores stand for) to out, device fp32[count][D]; count may exceed max_batch
- * (the rows are produced max_batch at a time).  Row numbers are table rows: a re-indexing table is
+ * (tables whose products are large and shared by few rows are looked up max_batch rows at a time, all
+ * others are streamed).  Row numbers are table rows: a re-indexing table is
  * not applied.  0 <= first_row, first_row + count <= N.  TT_EMB_ESTATE while a forward is pending.
  */
 int tt_emb_materialize(tt_emb_t h, int64_t first_row, int64_t count, float* out, void* hip_stream);
@@ -220,7 +221,9 @@ int tt_emb_wait_backward(tt_emb_t h, int age);
  * backward_update(...) - the index
  * work of coming batches then overlaps this batch's arithmetic (minibatch samplers know the next
  * ids early).  An ids buffer must keep its contents until the forward that uses it has been enqueued.
- * Results are identical with or without it.  tt_emb_get_stats refers to the latest forward only
+ * Results are identical with or without it.  Small batches (a few thousand ids and fewer) take kernels
+ * that need no index structures: for them the call only orders the forward, which waits for what was
+ * enqueued on hip_stream before it, and takes no index set.  tt_emb_get_stats refers to the latest forward only
  * until the next tt_emb_prepare.
  */
 int tt_emb_prepare(tt_emb_t h, const int64_t* ids, int64_t B, void* hip_stream);
@@ -230,7 +233,9 @@ int tt_emb_prepare(tt_emb_t h, const int64_t* ids, int64_t B, void* hip_stream);
  * batch of the latest forward.  Forms dG1, dG2, dG3 of L = sum_b <grad_out[b], out[b]> from the
  * cores as they are when the call starts (all positions add, no averaging), then applies
  * Gk[s] <- Gk[s] - lr*dGk[s] to every slice s the batch touches; other slices are not written.
- * Sums are formed in a fixed order: the same inputs give bit-identical cores.  Consumes the
+ * Sums are formed in a fixed order: the same inputs give bit-identical cores.  (The order, and with it
+ * the last bits, may differ between batch sizes, between forward, forward_eval and materialize, and
+ * with the flags that choose kernels.)  Consumes the
  * pending forward (a second call without a new forward returns TT_EMB_ESTATE); a call that is
  * rejected for its arguments (TT_EMB_EINVAL) leaves the forward pending.
  */

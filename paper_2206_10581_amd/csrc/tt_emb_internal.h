@@ -222,8 +222,8 @@ struct Plan {
   int keyBits, passes, bitsPerPass;
   int direct_cap;        // lookups of up to this many items take the index-free kernels (0: never)
   int direct_train_cap;  // the same for batches that backward_update follows
-  // single-wavefront blocks of the per-chunk matrix-core kernels that the device holds at once
-  // (forward, backward); asked of the runtime at the first launch, 0 until then
+  // blocks of the prefix kernels for ranks 64 and 128 that the device holds at once (forward,
+  // backward); asked of the runtime at the first launch, 0 until then
   mutable int unit_slots[2] = {0, 0};
 };
 

@@ -1234,7 +1234,7 @@ void launch_id_bwd_mfma(const Plan& pl, const Workspace& ws, const float* g3, co
 #undef TT_ID
 }
 
-// true when k_bwd_mid_mfma covers the shape (else: k_id_bwd_mfma followed by k_prefix_bwd_mfma)
+// true when k_bwd_mid_mfma covers the shape (else: k_id_bwd_mfma followed by k_prefix_bwd_wide)
 bool mfma_fused_mid(const Shape& s) { return mfma_shape(s) && s.r1 <= 32; }
 
 void launch_bwd_mid_mfma(const Plan& pl, const Workspace& ws, const float* g1, const float* g2,
