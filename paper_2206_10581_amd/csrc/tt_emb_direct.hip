@@ -433,15 +433,6 @@ __device__ __forceinline__ int direct_list(DirectList& L, const uint16_t* __rest
 // launches more than its items can fill: a single id at n = (60000,20,20) takes 18 us instead of 65
 // (the indexed kernels: 119), and no grid grows with the table.
 __host__ __device__ inline int slice_blocks(uint32_t n, int B) { return B < (int)n ? B : (int)n; }
-// Slice of block b and its items (none: nothing to do); dig are the core's digits.
-__device__ __forceinline__ int slice_items(DirectList& L, const uint16_t* __restrict__ dig, uint32_t n, int B,
-                                           int b, int* slice) {
-  const bool by_item = B < (int)n;
-  *slice = by_item ? (int)dig[b] : b;
-  if (*slice == 0xffff) return 0;  // an out-of-range id
-  const int items = direct_list(L, dig, B, *slice);
-  return by_item && (int)L.item[0] != b ? 0 : items;
-}
 
 // Pairwise sums of what `groups` groups (a power of two) of `lanes` threads hold, left in the first group.
 template <int VEC>
@@ -502,7 +493,8 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
   const int per3 = (sh.S3 + 1023) / 1024, per1 = (sh.S1 + 1023) / 1024;
   const int most_s = max(max(sh.S1, sh.S2), sh.S3);
   // core (0, 1, 2 for G1, G2, G3), slice, piece of the slice and part of its items
-  int core, slice, piece, part = 0, n;
+  int core, slice, piece, part = 0;
+  int first = -1;  // a block that stands for an item: the item, which has to be its slice's first
   int job = blockIdx.x;
   const int hot_jobs = PARTS ? 3 * max_hot * hot_pieces : 0;  // blocks of parts beyond the first
   if (PARTS && job < hot_jobs) {
@@ -511,7 +503,6 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
     if (listed - core * max_hot >= (int)n_hot[core]) return;
     slice = hot[listed].x, part = hot[listed].y;
     if (piece >= (core == 0 ? per1 : core == 1 ? per2 : per3)) return;
-    n = direct_list(L, dig + core * stride, B, slice);
   } else {
     job -= hot_jobs;
     const int jobs2 = slice_blocks(sh.n2, B) * per2, jobs3 = slice_blocks(sh.n3, B) * per3;
@@ -519,9 +510,17 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
     job -= core == 1 ? 0 : core == 2 ? jobs2 : jobs2 + jobs3;
     const int per = core == 1 ? per2 : core == 2 ? per3 : per1;
     piece = job % per;
-    n = slice_items(L, dig + core * stride, core == 1 ? sh.n2 : core == 2 ? sh.n3 : sh.n1, B, job / per, &slice);
+    slice = job / per;
+    if (B < (int)(core == 1 ? sh.n2 : core == 2 ? sh.n3 : sh.n1)) {
+      first = slice;
+      slice = (int)dig[core * stride + first];
+      if (slice == 0xffff) return;  // an out-of-range id
+    }
   }
-  const int most = direct_part(sh), parts = PARTS ? (n + most - 1) / most : 1;
+  int n = direct_list(L, dig + core * stride, B, slice);
+  if (first >= 0 && (int)L.item[0] != first) return;
+  n = __builtin_amdgcn_readfirstlane(n);  // the same in all threads
+  const int most = direct_part(sh), parts = PARTS && n > most ? (n + most - 1) / most : 1;
   const int lo = PARTS ? part * most : 0, hi = parts > 1 ? min(n, lo + most) : n;
   if (lo >= hi) return;
   const int S = core == 0 ? sh.S1 : core == 1 ? sh.S2 : sh.S3;
@@ -533,17 +532,17 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
   auto sums_of = [&](int p) {
     return hot_sum + (size_t)(p > 0 ? parts_of.slot[p] : 3 * max_hot + parts_of.slot[1]) * most_s;
   };
-  auto update = [&](size_t at, float s) {
-    G[at] = updated_entry<RULE>(G[at], s, lr, ada, ADA ? St + at : nullptr, ADAM ? Vt + at : nullptr);
+  auto update = [&](size_t at, float old, float s) {
+    G[at] = updated_entry<RULE>(old, s, lr, ada, ADA ? St + at : nullptr, ADAM ? Vt + at : nullptr);
   };
-  auto put = [&](size_t at, float s) {
-    if (!PARTS || parts == 1) update(at, s);
+  auto put = [&](size_t at, float old, float s) {
+    if (!PARTS || parts == 1) update(at, old, s);
     else sums_of(part)[at] = s;
   };
   auto update_from_parts = [&](size_t at) {
     float s = sums_of(0)[at];
     for (int p = 1; p < parts; ++p) s += sums_of(p)[at];
-    update(at, s);
+    update(at, G[at], s);
   };
   auto is_last = [&] {
     return PARTS && parts > 1 &&
@@ -560,6 +559,19 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
     for (int i = 0; i < RT; ++i) ra[i] = min(row0 + 16 * i + l16, sh.r1 - 1);
 #pragma unroll
     for (int j = 0; j < CT; ++j) cb[j] = min(col0 + 16 * j + l16, sh.W - 1);
+    constexpr int kOut = RT * CT * 256;
+    auto each_entry = [&](auto body) {
+#pragma unroll
+      for (int x = 0; x < kOut / kDThreads; ++x) {
+        const int o = tid + x * kDThreads, row = row0 + o / (16 * CT), col = col0 + o % (16 * CT);
+        if (row < sh.r1 && col < sh.W) body(x, o, (size_t)row * sh.W + col);
+      }
+    };
+    // The entries as they are, all at once: read before the first is written.  (With the eight row tiles of
+    // rank 128 their registers cost a block per compute unit: 250 ids 69 -> 76 us a step.)
+    constexpr bool kAhead = RT < 8;
+    float old[kAhead ? kOut / kDThreads : 1];
+    if constexpr (kAhead) each_entry([&](int x, int, size_t at) { old[x] = G[at]; });
     f4 sum[RT][CT];
 #pragma unroll
     for (int i = 0; i < RT; ++i)
@@ -609,21 +621,13 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
         for (int v = 0; v < 4; ++v)
           red[((w * RT * 16 + 16 * i + 4 * kg + v) * CT + j) * 16 + l16] = sum[i][j][v];
     __syncthreads();
-    constexpr int kOut = RT * CT * 256;
-    auto each_entry = [&](auto body) {
-#pragma unroll
-      for (int x = 0; x < kOut / kDThreads; ++x) {
-        const int o = tid + x * kDThreads, row = row0 + o / (16 * CT), col = col0 + o % (16 * CT);
-        if (row < sh.r1 && col < sh.W) body(o, (size_t)row * sh.W + col);
-      }
-    };
-    each_entry([&](int o, size_t at) {
+    each_entry([&](int x, int o, size_t at) {
       float s = red[o];
 #pragma unroll
       for (int p = 1; p < kDWaves; ++p) s += red[p * kOut + o];
-      put(at, s);
+      put(at, kAhead ? old[kAhead ? x : 0] : G[at], s);
     });
-    if (is_last()) each_entry([&](int, size_t at) { update_from_parts(at); });
+    if (is_last()) each_entry([&](int, int, size_t at) { update_from_parts(at); });
     return;
   }
   const int o0 = piece * 1024, outs = min(1024, S - o0);
@@ -669,7 +673,7 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
       join_groups<VEC>(red, tid, lanes, groups, acc);
       if (grp == 0 && on) {
 #pragma unroll
-        for (int x = 0; x < VEC; ++x) put(o0 + o + x, acc[x]);
+        for (int x = 0; x < VEC; ++x) put(o0 + o + x, G[o0 + o + x], acc[x]);
       }
       __syncthreads();
     }

@@ -27,11 +27,11 @@ inline int chunk3_fill(int64_t B) { return B <= kSmallBatch ? kChunk3Min : kChun
 // into memory: on an idle device smaller blocks on more compute units are faster until the 2048
 // counters per block outweigh them (training step, microseconds with 256 / 512 / 1024 threads:
 // 50,000 ids 113 / - / 118, 100,000 items 126 / - / 139, 200,000 ids 194 / 192 / 197, 500,000 ids
-// - / 404 / 408).  Up to kSort1024First items a block or two of 1024 threads are faster again: their
-// threads have an eighth of the counters each (a pass over 700 items 9.8 against 11.2 us, 3,000 items 18.7
-// against 20.3, 8,000 items 19.3 against 20.0).  Beside the arithmetic of another batch (tt_emb_prepare) the extra blocks take its
+// - / 404 / 408).  Up to kSort1024First items, one block of either kind, 1024 threads have an eighth of
+// the counters each: a pass over 700 items 9.8 against 11.2 us (5,000 uniform ids are slower with them, a
+// step 99 against 93).  Beside the arithmetic of another batch (tt_emb_prepare) the extra blocks take its
 // compute units instead: 156 / 150 / 145 at 200,000 ids, so there they stay large.
-constexpr int kSort1024First = 1 << 13, kSort256Most = 1 << 17, kSort512Most = 1 << 19;
+constexpr int kSort1024First = 1 << 10, kSort256Most = 1 << 17, kSort512Most = 1 << 19;
 inline int sort_threads(int64_t B, bool beside) {
   return beside || B <= kSort1024First || B > kSort512Most ? 1024 : B > kSort256Most ? 512 : 256;
 }
@@ -153,9 +153,12 @@ __host__ __device__ inline int direct_part(const Shape& s) {
   return 512 >> ((s.r1 > 32 ? 1 : 0) + (s.d1 > 8 ? 2 : 0));
 }
 constexpr int kDirectPartLeast = 64;
-// most parts beyond the first that the slices of a core have
+// Most parts beyond the first that the slices of a core have.  Batches of no more than two parts' items
+// are not cut: listing parts and looking for them costs every batch a few per cent (700 uniform ids at
+// rank 32 31.5 -> 35 us a step), and a single id 1024 times at rank 32 takes 70 us in one block, 72 on the
+// indexed kernels.
 inline int hot_parts(const Shape& s, int64_t items) {
-  return items > direct_part(s) ? (int)(items / direct_part(s)) : 0;
+  return items > 2 * direct_part(s) ? (int)(items / direct_part(s)) : 0;
 }
 
 // All device arrays carved out of the caller's workspace.

@@ -299,7 +299,7 @@ def test_slices_of_many_items_in_parts(n, d, r, hot):
     """Slices that as many items share as a part holds (64 to 512) and slices that more share, one of every core, beside slices with few
     items and slices with a part and a bit: parts that are full and one item long.  The parts are
     listed in the order in which the device counts, the sums do not depend on it."""
-    rng, B = np.random.default_rng(hot), 2000 if r[0] < 64 else 1024
+    rng, B = np.random.default_rng(hot), 2000 if r[0] < 64 else 1024   # more than two parts of every shape
     hot = min(hot, B)
     i = [rng.integers(0, k, B) for k in n]
     i[0][:hot], i[1][:hot], i[2][:hot] = 1, 2, 3              # one id
