@@ -369,8 +369,8 @@ __global__ __launch_bounds__(kDThreads) void k_direct_bwd(
 // microsecond, so a slice that more items share (a hot id, neighbouring ids) is cut into parts: the
 // backward kernel lists those beyond the first, blocks at the front of the grid take them, and the block
 // of a slice's piece that ends last adds the parts up in order and updates.  8192 ids at rank 16 of
-// n = 136^3, one step, in one block -> in parts of 512 (the indexed kernels): one id 397 -> 71 us (79),
-// 200 neighbouring ids 284 -> 67 (131), Zipf 1.2 87 -> 66 (91), uniform 41 -> 42 (98).  Parts of 256 are
+// n = 136^3, one step, in one block -> in parts of 512 (the indexed kernels): one id 397 -> 67 us (79),
+// 200 neighbouring ids 284 -> 66 (131), Zipf 1.2 87 -> 64 (91), uniform 41 -> 42 (98).  Parts of 256 are
 // a few us faster there, but cut slices that one block adds up sooner: n = (40,30,20), d = (5,3,4),
 // uniform ids 58 -> 72 us.
 // Sums have two levels, a short chain of the items that are in flight together and a chain of those
@@ -462,17 +462,24 @@ __device__ __forceinline__ void find_parts(DirectParts& P, const int2* __restric
   }
   __syncthreads();
 }
-// True in the block that is the last of `parts` to come here with this ticket; everything the others
-// stored before is then visible to it.
+// Sums of a part go past the L2 of this block's XCD and are read past the reader's: stores and loads at
+// agent scope.  A store that has completed (s_waitcnt) is therefore visible to every block, and no cache
+// has to be written back or invalidated (fences that do took 5 to 10 us per part).
+__device__ __forceinline__ void put_sum(float* p, float v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float get_sum(const float* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// True in the block that is the last of `parts` to come here with this ticket: all parts' sums are
+// there.
 __device__ __forceinline__ bool last_part(DirectParts& P, uint32_t* ticket, int parts) {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");  // every wavefront's own stores
-  __syncthreads();
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's sums are stored
+  __syncthreads();                                  // and those of the others of the block
   if (threadIdx.x == 0)
     P.last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == (uint32_t)parts;
   __syncthreads();
-  if (P.last == 0) return false;
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  return true;
+  return P.last != 0;
 }
 
 // PARTS: slices of more than direct_part() items are cut into parts (the batch has that many)
@@ -537,11 +544,11 @@ __global__ __launch_bounds__(kDThreads) void k_direct_apply(
   };
   auto put = [&](size_t at, float old, float s) {
     if (!PARTS || parts == 1) update(at, old, s);
-    else sums_of(part)[at] = s;
+    else put_sum(sums_of(part) + at, s);
   };
   auto update_from_parts = [&](size_t at) {
-    float s = sums_of(0)[at];
-    for (int p = 1; p < parts; ++p) s += sums_of(p)[at];
+    float s = get_sum(sums_of(0) + at);
+    for (int p = 1; p < parts; ++p) s += get_sum(sums_of(p) + at);
     update(at, G[at], s);
   };
   auto is_last = [&] {
@@ -822,8 +829,8 @@ static int team_waves(const Shape& s) { return s.W > 2 * kWave ? 4 : 1; }
 // the other: past kDirectRounds of them the limit falls (d = (20,1,9), r = (70,2), 25 rounds: 8000 ids 70
 // us against 51 to 68).  A training step on these
 // kernels and on the indexed ones, us, at the largest batches, for uniform ids and for a single one:
-//   rank 8, 8192 ids     40 / 95,  63 / 78        rank 64, 1024 ids    49 / 114, 71 / 81
-//   rank 16, 8192 ids    42 / 98,  71 / 79        rank 128, 256 ids    70 / 144, 70 / 93
+//   rank 8, 8192 ids     40 / 95,  63 / 78        rank 64, 1024 ids    48 / 114, 66 / 81
+//   rank 16, 8192 ids    42 / 98,  67 / 79        rank 128, 256 ids    70 / 144, 70 / 93
 //   rank 32, 4096 ids    45 / 107, 77 / 75        d = (4,5,5) at rank 32, 2048 ids  39 / 141, 72 / 107
 // (n = 136^3, d = (4,4,8)).  A lookup takes 7 to 17 us at these sizes, 50 to 80 on the indexed kernels.
 int direct_capacity(const Shape& s) {
