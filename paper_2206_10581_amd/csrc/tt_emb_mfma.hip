@@ -242,7 +242,7 @@ __global__ __launch_bounds__(kMThreads, R >= 128 ? 3 : 4) void k_prefix_fwd_wide
 //         (rows of Bm lie 4R floats apart: read by the lanes directly, every 16-byte load would
 //         touch a line of its own).
 // The dG2 units are the longer ones and come first.
-// Rank 128, 308,840 prefixes of n = 480,500,500: 4.55 -> 3.21 ms (101 TFLOP/s), and the update
+// Rank 128, 308,840 prefixes of n = 480,500,500: 4.55 -> 3.29 ms (99 TFLOP/s), and the update
 // kernel, which reads an eighth of the dG2 partials, 1.14 -> 0.35 ms.  Rank 64, 1,516 prefixes:
 // 35 -> 25 us.  Two blocks per compute unit at rank 128: three would spill fifty registers.
 template <int R>
