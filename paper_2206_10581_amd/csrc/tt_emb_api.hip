@@ -14,8 +14,9 @@
 namespace ttemb {
 
 // launchers defined next to their kernels
-void launch_sort_pass(const Plan&, const Workspace&, const IdSource& src, int B, int pass, bool beside,
-                      hipStream_t, int which);
+void launch_sort_pass(const Plan&, const Workspace&, const SortKeys&, const IdSource* src, int B, int pass,
+                      bool beside, bool clear, hipStream_t, int which);
+void launch_count_keys(const Workspace&, const SortKeys&, int i3_bits, int B, hipStream_t);
 void launch_seg_count(const Plan&, const Workspace&, int B, hipStream_t);
 void launch_seg_write(const Plan&, const Workspace&, int B, hipStream_t);
 void launch_group(const Plan&, const Workspace&, int B, hipStream_t, int which);
@@ -46,6 +47,10 @@ bool gsum_block_rows(const Shape&);
 void launch_bwd_mid_mfma(const Plan&, const Workspace&, const float* g1, const float* g2,
                          const float* g3, const float* grad, int B, hipStream_t);
 void launch_gsum_block(const Plan&, const Workspace&, const float* grad, int B, hipStream_t);
+// lookups of ids sorted by prefix (tt_emb_lookup.hip)
+bool lookup_shape(const Shape&);
+void launch_lookup(const Plan&, const Workspace&, const float* g1, const float* g2, const float* g3, int B,
+                   float* out, hipStream_t);
 // index-free kernels (tt_emb_direct.hip)
 int direct_capacity(const Shape&);
 int direct_train_capacity(const Shape&);
@@ -66,7 +71,7 @@ hipError_t calibrate(void* buf, size_t bytes, hipStream_t, double* copy_bytes_pe
 static const char* const kSlotNames[kSlotCount] = {
     "sort_hist", "sort_scan", "sort_scatter", "seg_count", "seg_write",  "group",
     "prefix_fwd", "row_fwd",  "gsum",         "gsum_fix",  "u_bwd",      "dg3",        "prefix_bwd",
-    "sgd",        "direct_fwd", "direct_bwd", "direct_apply", "table", "event_pair"};
+    "sgd",        "direct_fwd", "direct_bwd", "direct_apply", "table", "lookup", "event_pair"};
 
 static thread_local std::string g_hip_error = "HIP call failed";
 
@@ -76,6 +81,12 @@ static int bits_for(uint32_t v) {  // number of bits needed to write v (at least
   int b = 1;
   while ((v >> b) != 0 && b < 32) ++b;
   return b;
+}
+
+// Passes over the bits of a key from `low` on; the sentinel itself must be representable.
+static SortKeys sort_keys(uint32_t sentinel, int low) {
+  const int bits = bits_for(sentinel >> low), passes = (bits + 10) / 11;
+  return SortKeys{sentinel, low, bits, passes, (bits + passes - 1) / passes, 1};
 }
 
 static int make_plan(const tt_emb_config* c, Plan* pl) {
@@ -150,9 +161,16 @@ static int make_plan(const tt_emb_config* c, Plan* pl) {
   pl->tilesMax = (int)cdiv64(pl->maxB, kTileSlots);
   pl->maxChunk3 = cdiv64(pl->maxB, kChunk3Min) + s.n3;
   pl->maxChunk2 = cdiv64(pl->maxQ, kChunk2) + s.n2;
-  pl->keyBits = bits_for(s.N);  // the sentinel N itself must be representable
-  pl->passes = (pl->keyBits + 10) / 11;
-  pl->bitsPerPass = (pl->keyBits + pl->passes - 1) / pl->passes;
+  pl->keys = sort_keys(s.N, 0);
+  // lookups by prefix: the caller's table, whatever slabs the other kernels see
+  const int i3_bits = bits_for(s.n3 - 1);
+  pl->lookup_i3_bits = 0;
+  pl->user_n1 = (uint32_t)c->n[0];
+  if (pl->mfma && lookup_shape(s) && !(c->flags & TT_EMB_FLAG_INDEXED_KERNELS)) {
+    // 2^i3_bits is at most 2*n3, so keys stay below 2*N and fit 32 bits
+    pl->lookup_keys = sort_keys((uint32_t)((c->n[0] * c->n[1]) << i3_bits), i3_bits);
+    pl->lookup_i3_bits = i3_bits;
+  }
   pl->direct_cap = (c->flags & (TT_EMB_FLAG_GENERIC_KERNELS | TT_EMB_FLAG_INDEXED_KERNELS))
                        ? 0
                        : (int)std::min<int64_t>(pl->maxB, direct_capacity(s));
@@ -310,6 +328,8 @@ struct tt_emb {
   int64_t last_B;     // batch size of the latest forward
   bool have_forward;
   bool direct;        // the latest forward took the index-free kernels
+  bool lookup;        // the latest forward was a lookup by prefix
+  bool counted;       // and its counters have been made
   hipStream_t last_stream;
   // tt_emb_prepare: index pipelines of coming batches on a stream of the library's own
   hipStream_t side[kSets];  // stream of each index set (kSideStreams distinct ones), created on
@@ -340,7 +360,7 @@ struct tt_emb {
 static IdSource id_source(const tt_emb* h, const int64_t* ids, int64_t base, bool reindexed) {
   const Plan& pl = h->plan;
   return IdSource{ids, base, reindexed ? h->reindex : nullptr, reindexed ? h->reindex_n : 0,
-                  pl.split, pl.user_N, (int64_t)pl.sh.n2 * pl.sh.n3};
+                  pl.split, pl.user_N, (int64_t)pl.sh.n2 * pl.sh.n3, 0, 0, 0, 0};
 }
 
 static int hip_fail(hipError_t e) {
@@ -416,6 +436,7 @@ static void init_handle(tt_emb* h, const tt_emb_config* cfg, const Plan& pl, flo
   h->last_B = 0;
   h->have_forward = false;
   h->direct = false;
+  h->lookup = h->counted = false;
   h->last_stream = nullptr;
   h->profiling = false;
   h->mfma = pl.mfma;
@@ -515,6 +536,23 @@ static int take_prepared(tt_emb::Prepared* list, const int64_t* ids, int64_t B, 
   return TT_EMB_OK;
 }
 
+// The passes of a sort; src == nullptr: of keys that are in the input buffer already.
+static int run_sort(tt_emb* h, const Workspace& ws, const SortKeys& sk, const IdSource* src, int B, bool beside,
+                    bool clear, hipStream_t st) {
+  const Plan& pl = h->plan;
+  for (int pass = 0; pass < sk.passes; ++pass) {
+    const IdSource* from = pass == 0 ? src : nullptr;
+    auto part = [&](int slot, int which) {
+      return run_slot(h, slot, st, [&] { launch_sort_pass(pl, ws, sk, from, B, pass, beside, clear, st, which); });
+    };
+    int rc = part(kSlotSortHist, 0);
+    if (!rc && !sort_folds(B, beside)) rc = part(kSlotSortScan, 2);
+    if (!rc) rc = part(kSlotSortScatter, 1);
+    if (rc) return rc;
+  }
+  return TT_EMB_OK;
+}
+
 // Index pipeline of one batch into index set `set`, on stream st.
 // how: 0 = beside other work, as in tt_emb_prepare: everything, including the prefix-ordered schedule
 // of the by-i3 chunks (worth its launch only there), with large sort blocks; 1 = no schedule; 2 = a
@@ -522,23 +560,45 @@ static int take_prepared(tt_emb::Prepared* list, const int64_t* ids, int64_t B, 
 static int run_index(tt_emb* h, int set, const IdSource& src, int B, hipStream_t st, int how) {
   const Plan& pl = h->plan;
   const Workspace& ws = h->ws[set];
-  int rc;
-  for (int pass = 0; pass < pl.passes; ++pass) {
-    rc = run_slot(h, kSlotSortHist, st, [&] { launch_sort_pass(pl, ws, src, B, pass, how == 0, st, 0); });
-    if (rc) return rc;
-    if (!sort_folds(B, how == 0)) {
-      rc = run_slot(h, kSlotSortScan, st, [&] { launch_sort_pass(pl, ws, src, B, pass, how == 0, st, 2); });
-      if (rc) return rc;
-    }
-    rc = run_slot(h, kSlotSortScatter, st, [&] { launch_sort_pass(pl, ws, src, B, pass, how == 0, st, 1); });
-    if (rc) return rc;
-  }
+  int rc = run_sort(h, ws, pl.keys, &src, B, how == 0, true, st);
+  if (rc) return rc;
   rc = run_slot(h, kSlotSegCount, st, [&] { launch_seg_count(pl, ws, B, st); });
   if (rc) return rc;
   rc = run_slot(h, kSlotSegWrite, st, [&] { launch_seg_write(pl, ws, B, st); });
   if (rc) return rc;
   h->ws[set].has_order = how == 0;
   return run_slot(h, kSlotGroup, st, [&] { launch_group(pl, ws, B, st, how); });
+}
+
+// Lookup of ids sorted by prefix: no index structures behind the sort, no products in memory.
+static int run_lookup(tt_emb* h, IdSource src, int B, float* out, hipStream_t st) {
+  const Plan& pl = h->plan;
+  const Workspace& ws = h->ws[h->cur];
+  src.split = 1;
+  src.i3_bits = pl.lookup_i3_bits;
+  src.n1 = pl.user_n1;
+  src.n2 = pl.sh.n2;
+  src.n3 = pl.sh.n3;
+  int rc = run_sort(h, ws, pl.lookup_keys, &src, B, false, false, st);
+  if (rc) return rc;
+  return run_slot(h, kSlotLookup, st, [&] { launch_lookup(pl, ws, h->g1, h->g2, h->g3, B, out, st); });
+}
+
+// Counters of the latest lookup by prefix: its keys, sorted by prefix, are sorted in full and counted.
+static int count_lookup(tt_emb* h, hipStream_t st) {
+  const Workspace& ws = h->ws[h->cur];
+  const int B = (int)(h->last_B / h->plan.split);
+  SortKeys sk = h->plan.lookup_keys;
+  const int in = sk.sorted();
+  sk = sort_keys(sk.sentinel, 0);
+  sk.input = in;
+  const int rc = run_sort(h, ws, sk, nullptr, B, false, false, st);
+  if (rc) return rc;
+  launch_count_keys(ws, sk, h->plan.lookup_i3_bits, B, st);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return hip_fail(e);
+  h->counted = true;
+  return TT_EMB_OK;
 }
 
 int tt_emb_prepare(tt_emb_t h, const int64_t* ids, int64_t B64, void* hip_stream) {
@@ -644,6 +704,7 @@ static int forward_impl(tt_emb* h, const IdSource& src, int64_t B64, float* out,
   rc = take_prepared(h->small, ids, B64, st, &early);
   if (rc) return rc;
   h->direct = B <= (arm ? pl.direct_train_cap : pl.direct_cap);
+  h->lookup = false;
   if (h->direct) {
     h->step = h->step < kSets ? kSets : kSets + (h->step + 1) % kSets;
     h->done_valid[h->step] = false;
@@ -678,6 +739,17 @@ static int forward_impl(tt_emb* h, const IdSource& src, int64_t B64, float* out,
       if (e != hipSuccess) return hip_fail(e);
     }
     h->cur = target;
+    if (!arm && pl.lookup_i3_bits > 0) {
+      h->step = h->cur;
+      h->done_valid[h->step] = false;
+      rc = run_lookup(h, src, (int)B64, out, st);
+      if (rc) return rc;
+      h->lookup = true;
+      h->counted = false;
+      h->last_B = B;
+      h->have_forward = true;
+      return mark_set_done(h, st);
+    }
     rc = run_index(h, h->cur, src, B, st, arm ? 1 : 2);
     if (rc) return rc;
   }
@@ -982,13 +1054,19 @@ int tt_emb_get_stats(tt_emb_t h, int64_t* U, int64_t* Q, int64_t* out_of_range) 
         c.Q += i == 0 || key[i] / s.n3 != key[i - 1] / s.n3;
       }
     } else {
+      if (h->lookup && !h->counted) {
+        const int rc = count_lookup(h, h->last_stream);
+        if (rc) return rc;
+        e = hipStreamSynchronize(h->last_stream);
+        if (e != hipSuccess) return hip_fail(e);
+      }
       e = hipMemcpy(&c, h->ws[h->cur].ctr, sizeof(c), hipMemcpyDeviceToHost);
       if (e != hipSuccess) return hip_fail(e);
     }
-    oob = h->last_B - (int64_t)c.nvalid;
+    oob = (h->lookup ? h->last_B / h->plan.split : h->last_B) - (int64_t)c.nvalid;
   }
-  // with a slab split every id, prefix and position was counted once per slab
-  const int k = h->plan.split;
+  // with a slab split every id, prefix and position was counted once per slab (not in a lookup by prefix)
+  const int k = h->lookup ? 1 : h->plan.split;
   oob /= k;
   if (U) *U = (c.U - c.n_split) / k;
   if (Q) *Q = c.Q / k;

@@ -893,7 +893,7 @@ void launch_row_fwd(const Plan& pl, const Workspace& ws, const float* g3, int B,
     // one wavefront per distinct id (at most B of them) and per tile of slots
     const int jobs = B + cdiv(B, kTileSlots) + 1;
     const int blocks = grid_for(cdiv(jobs, wpb), kGridCap * 4);
-    const uint32_t* perm = ws.val[(pl.passes - 1) & 1];
+    const uint32_t* perm = ws.val[pl.keys.sorted()];
     if (v4)
       k_row_fwd_staged<true><<<blocks, wpb * kWave, staged, st>>>(s, B, g3, ws.P, ws.s_u, perm, ws.u_rs,
                                                                   ws.u_i3, ws.u_q, out, ws.ctr);
@@ -903,14 +903,14 @@ void launch_row_fwd(const Plan& pl, const Workspace& ws, const float* g3, int B,
     return;
   }
   const size_t lds = (size_t)kWavesPerBlock * pl.sh.D * sizeof(float);
-  k_row_fwd<<<grid, kThreads, lds, st>>>(pl.sh, B, g3, ws.P, ws.s_u, ws.val[(pl.passes - 1) & 1],
+  k_row_fwd<<<grid, kThreads, lds, st>>>(pl.sh, B, g3, ws.P, ws.s_u, ws.val[pl.keys.sorted()],
                                          ws.u_i3, ws.u_q, out, ws.ctr);
 }
 
 void launch_gsum(const Plan& pl, const Workspace& ws, const float* grad, int B, hipStream_t st) {
   const int tiles = cdiv(B, kTileSlots);
   const int grid = grid_for(cdiv(tiles, kWavesPerBlock), kGridCap);
-  const uint32_t* perm = ws.val[(pl.passes - 1) & 1];
+  const uint32_t* perm = ws.val[pl.keys.sorted()];
   const size_t lds = (size_t)kWavesPerBlock * pl.sh.D * sizeof(float);
   k_gsum<<<grid, kThreads, lds, st>>>(pl.sh, B, grad, ws.s_u, perm, ws.u_rs, ws.gsum, ws.carry,
                                       ws.ctr);

@@ -283,22 +283,17 @@ struct KV {
   uint32_t key, val;
 };
 
-template <bool FROM_IDS>
+template <bool FIRST>
 struct SortOps {
   using Item = KV;
   static constexpr bool kChunked = false;
-  IdSource src;
   const uint32_t* kin;
   const uint32_t* vin;
   uint32_t* kout;
   uint32_t* vout;
-  uint32_t N;
   int shift;
   uint32_t mask;
-  __device__ Item load(int idx) const {
-    if (FROM_IDS) return KV{key_of_id(src, idx, N), (uint32_t)idx};
-    return KV{kin[idx], vin[idx]};
-  }
+  __device__ Item load(int idx) const { return KV{kin[idx], FIRST ? (uint32_t)idx : vin[idx]}; }
   __device__ int digit(Item it) const { return (int)((it.key >> shift) & mask); }
   __device__ void emit(uint32_t pos, Item it) const {
     kout[pos] = it.key;
@@ -308,10 +303,11 @@ struct SortOps {
 
 // Bucket counts of one radix digit per block of sort_items(NT) items.  Equal digits inside a
 // wavefront step are counted with one LDS atomic (a hot id would otherwise serialise thousands of
-// them).  The first pass also clears the tables that later kernels of the same forward add into.
+// them).  The first pass also clears the tables that later kernels of the same forward add into, and
+// leaves the keys for its scatter, which need not split and renumber the ids again.
 template <int NT, bool FROM_IDS>
 __global__ __launch_bounds__(NT) void k_sort_hist(
-    IdSource src, const uint32_t* __restrict__ kin, int B, uint32_t N, int shift,
+    IdSource src, uint32_t* keys_io, int B, uint32_t N, int shift,
     int bits, uint32_t* __restrict__ cnt, uint32_t* zero_a, int zero_a_n, uint32_t* zero_b,
     int zero_b_n, uint32_t* zero_c, int zero_c_n, Counters* ctr) {
   __shared__ uint32_t h[kMaxBins];
@@ -324,10 +320,15 @@ __global__ __launch_bounds__(NT) void k_sort_hist(
   for (int step = 0; step < kSteps; ++step) {
     const int idx = wbase + step * kWave + lane;
     const int ic = min(idx, B - 1);
-    keys[step] = FROM_IDS ? key_of_id(src, ic, N) : kin[ic];
+    keys[step] = FROM_IDS ? key_of_id(src, ic, N) : keys_io[ic];
   }
   __builtin_amdgcn_sched_barrier(0);  // keep the loads together: their latencies overlap
   if (FROM_IDS) {
+#pragma unroll
+    for (int step = 0; step < kSteps; ++step) {
+      const int idx = wbase + step * kWave + lane;
+      if (idx < B) keys_io[idx] = keys[step];
+    }
     const int gtid = blockIdx.x * NT + tid, gn = gridDim.x * NT;
     for (int i = gtid; i < zero_a_n; i += gn) zero_a[i] = 0u;
     for (int i = gtid; i < zero_b_n; i += gn) zero_b[i] = 0u;
@@ -561,6 +562,44 @@ __global__ __launch_bounds__(kSegThreads) void k_seg_write(
   }
 }
 
+// Counters of a batch from its sorted keys (prefix << i3_bits | i3), by one block: for tt_emb_get_stats
+// after a lookup, which itself counts nothing.
+__global__ __launch_bounds__(1024) void k_count_keys(const uint32_t* __restrict__ skey, int B, uint32_t sentinel,
+                                                     int i3_bits, Counters* __restrict__ ctr) {
+  constexpr int kLoads = 8;
+  __shared__ uint32_t sum[3];
+  if (threadIdx.x < 3) sum[threadIdx.x] = 0u;
+  __syncthreads();
+  uint32_t u = 0, q = 0, valid = 0;
+  for (int s0 = (int)threadIdx.x; s0 < B; s0 += kLoads * 1024) {
+    uint32_t k[kLoads], before[kLoads];
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) {
+      const int s = min(s0 + j * 1024, B - 1);
+      k[j] = skey[s];
+      before[j] = skey[max(s - 1, 0)];
+    }
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) {
+      const int s = s0 + j * 1024;
+      const bool ok = s < B && k[j] < sentinel;
+      valid += ok;
+      u += ok && (s == 0 || k[j] != before[j]);
+      q += ok && (s == 0 || k[j] >> i3_bits != before[j] >> i3_bits);
+    }
+  }
+  atomicAdd(&sum[0], u);
+  atomicAdd(&sum[1], q);
+  atomicAdd(&sum[2], valid);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    ctr->U = (int)sum[0];
+    ctr->Q = (int)sum[1];
+    ctr->nvalid = (int)sum[2];
+    ctr->n_split = 0;
+  }
+}
+
 // ---------------------------------------------------------------------------------------------
 // Grouping: unique ids by i3 (for the G3 gradient), prefixes by i2 (for G2 and the prefix product)
 
@@ -658,60 +697,61 @@ __global__ __launch_bounds__(kOrderBands) void k_chunk_order(const int2* __restr
 
 static inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
+// One of the three kernels of a pass.  clear: the first one also clears the tables that the steps
+// behind the sort add into (lookups have none).
 template <int NT>
-static void sort_pass(const Plan& pl, const Workspace& ws, const IdSource& src, int B, int pass,
-                      bool beside, hipStream_t st, int which) {
+static void sort_pass(const Plan& pl, const Workspace& ws, const SortKeys& sk, const IdSource* src, int B,
+                      int pass, bool beside, bool clear, hipStream_t st, int which) {
   const int blocks = cdiv(B, sort_items(NT));
-  const int shift = pass * pl.bitsPerPass;
-  const int bits = std::min(pl.bitsPerPass, pl.keyBits - shift);
-  const uint32_t N = pl.sh.N;
+  const int shift = sk.low + pass * sk.per;
+  const int bits = std::min(sk.per, sk.bits - pass * sk.per);
   const uint32_t* tot = sort_folds(B, beside) ? nullptr : ws.tot;
+  const int in = (sk.input + pass) & 1;
+  uint32_t *kin = ws.key[in], *vin = ws.val[in], *kout = ws.key[in ^ 1], *vout = ws.val[in ^ 1];
   if (which == 2) {
     k_sort_colscan<<<cdiv(1 << bits, kScanBins), kScanThreads, 0, st>>>(ws.cnt, ws.tot, blocks,
                                                                        1 << bits);
-    return;
-  }
-  if (pass == 0) {
-    if (which == 0) {
+  } else if (which == 0) {
+    if (src != nullptr)
       k_sort_hist<NT, true><<<blocks, NT, 0, st>>>(
-          src, nullptr, B, N, shift, bits, ws.cnt, ws.cnt3, pl.uBlocksMax * (int)pl.sh.n3, ws.cnt2,
-          pl.qBlocksMax * (int)pl.sh.n2, (uint32_t*)ws.g1_first,
-          2 * (int)pl.sh.n1 + 2 * kOrderBands, ws.ctr);
-    } else {
-      SortOps<true> ops{src, nullptr, nullptr, ws.key[0], ws.val[0], N, shift, (1u << bits) - 1u};
-      k_sort_scatter<NT, true><<<blocks, NT, 0, st>>>(ops, B, bits, ws.cnt, tot);
-    }
+          *src, kin, B, sk.sentinel, shift, bits, ws.cnt, ws.cnt3, clear ? pl.uBlocksMax * (int)pl.sh.n3 : 0,
+          ws.cnt2, clear ? pl.qBlocksMax * (int)pl.sh.n2 : 0, (uint32_t*)ws.g1_first,
+          clear ? 2 * (int)pl.sh.n1 + 2 * kOrderBands : 0, ws.ctr);
+    else
+      k_sort_hist<NT, false><<<blocks, NT, 0, st>>>(IdSource{}, kin, B, sk.sentinel, shift, bits, ws.cnt,
+                                                    nullptr, 0, nullptr, 0, nullptr, 0, ws.ctr);
+  } else if (pass == 0) {
+    SortOps<true> ops{kin, nullptr, kout, vout, shift, (1u << bits) - 1u};
+    k_sort_scatter<NT, true><<<blocks, NT, 0, st>>>(ops, B, bits, ws.cnt, tot);
   } else {
-    const int from = (pass - 1) & 1, dst = pass & 1;
-    if (which == 0) {
-      k_sort_hist<NT, false><<<blocks, NT, 0, st>>>(IdSource{}, ws.key[from], B, N, shift, bits,
-                                                    ws.cnt, nullptr, 0, nullptr, 0, nullptr, 0,
-                                                    ws.ctr);
-    } else {
-      SortOps<false> ops{IdSource{}, ws.key[from], ws.val[from], ws.key[dst], ws.val[dst], N, shift,
-                         (1u << bits) - 1u};
-      k_sort_scatter<NT, false><<<blocks, NT, 0, st>>>(ops, B, bits, ws.cnt, tot);
-    }
+    SortOps<false> ops{kin, vin, kout, vout, shift, (1u << bits) - 1u};
+    k_sort_scatter<NT, false><<<blocks, NT, 0, st>>>(ops, B, bits, ws.cnt, tot);
   }
 }
 
-void launch_sort_pass(const Plan& pl, const Workspace& ws, const IdSource& src, int B, int pass,
-                      bool beside, hipStream_t st, int which /*0 = histogram, 1 = scatter, 2 = column scan*/) {
+// src: where the keys of the first pass come from; nullptr where they are in its input buffer
+void launch_sort_pass(const Plan& pl, const Workspace& ws, const SortKeys& sk, const IdSource* src, int B,
+                      int pass, bool beside, bool clear, hipStream_t st,
+                      int which /*0 = histogram, 1 = scatter, 2 = column scan*/) {
   switch (sort_threads(B, beside)) {
-    case 256: sort_pass<256>(pl, ws, src, B, pass, beside, st, which); break;
-    case 512: sort_pass<512>(pl, ws, src, B, pass, beside, st, which); break;
-    default: sort_pass<1024>(pl, ws, src, B, pass, beside, st, which); break;
+    case 256: sort_pass<256>(pl, ws, sk, src, B, pass, beside, clear, st, which); break;
+    case 512: sort_pass<512>(pl, ws, sk, src, B, pass, beside, clear, st, which); break;
+    default: sort_pass<1024>(pl, ws, sk, src, B, pass, beside, clear, st, which); break;
   }
+}
+
+void launch_count_keys(const Workspace& ws, const SortKeys& sk, int i3_bits, int B, hipStream_t st) {
+  k_count_keys<<<1, 1024, 0, st>>>(ws.key[sk.sorted()], B, sk.sentinel, i3_bits, ws.ctr);
 }
 
 void launch_seg_count(const Plan& pl, const Workspace& ws, int B, hipStream_t st) {
-  const uint32_t* skey = ws.key[(pl.passes - 1) & 1];
+  const uint32_t* skey = ws.key[pl.keys.sorted()];
   k_seg_count<<<cdiv(B, kSegItems), kSegThreads, 0, st>>>(skey, B, pl.sh.N, pl.sh.n3, ws.seg_nu,
                                                          ws.seg_nq);
 }
 
 void launch_seg_write(const Plan& pl, const Workspace& ws, int B, hipStream_t st) {
-  const int f = (pl.passes - 1) & 1;
+  const int f = pl.keys.sorted();
   k_seg_write<<<cdiv(B, kSegItems), kSegThreads, 0, st>>>(
       ws.key[f], ws.val[f], B, sort_items(group_threads(pl.sh, B)), pl.sh, ws.seg_nu, ws.seg_nq, ws.s_u, ws.s_rec, ws.u_rs, ws.u_i3, ws.u_q,
       ws.u_code, ws.q_us, ws.q_i1, ws.q_i2, ws.cnt3, ws.cnt2, ws.g1_first, ws.g1_end, ws.ctr);

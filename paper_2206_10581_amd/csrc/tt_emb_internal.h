@@ -77,6 +77,18 @@ struct IdSource {
   // idx / split; rows is the caller's table size N and n23 = n2*n3.
   int split;
   int64_t rows, n23;
+  // i3_bits > 0: the key is not the table row but (i2*n1 + i1) << i3_bits | i3, see Plan::lookup_keys
+  int i3_bits;
+  uint32_t n1, n2, n3;
+};
+
+// What a sort orders by: `bits` bits of the key above the lowest `low`, `per` of them a pass.
+// Out-of-range ids have the key `sentinel`, above every other.  The first pass reads key buffer
+// `input` (which its histogram fills from the ids) and writes the other, the next one back, and so on.
+struct SortKeys {
+  uint32_t sentinel;
+  int low, bits, passes, per, input;
+  int sorted() const { return (input + passes) & 1; }  // buffer of the sorted keys
 };
 
 // Update rule of the update kernel and its caller-owned state (arrays shaped like the cores).
@@ -222,7 +234,12 @@ struct Plan {
   int64_t maxB, maxQ;
   int sortBlocksMax, segBlocksMax, uBlocksMax, qBlocksMax, tilesMax;
   int64_t maxChunk3, maxChunk2;
-  int keyBits, passes, bitsPerPass;
+  SortKeys keys;         // sort by table row (the batches that train)
+  // Lookups at ranks up to 32 (k_lookup_mfma): caller's ids, not slabs, sorted by prefix only, and that
+  // with i2 in front, so that neighbours share a G2 slice.  i3_bits = 0: other shapes.
+  SortKeys lookup_keys;
+  int lookup_i3_bits;
+  uint32_t user_n1;
   int direct_cap;        // lookups of up to this many items take the index-free kernels (0: never)
   int direct_train_cap;  // the same for batches that backward_update follows
   // blocks of the prefix kernels for ranks 64 and 128 that the device holds at once (forward,
@@ -267,6 +284,7 @@ enum KernelSlot {
   kSlotDirectBwd,
   kSlotDirectApply,
   kSlotTable,
+  kSlotLookup,
   kSlotEventPair,  // an event pair with nothing between: the cost the timing itself adds to a slot
   kSlotCount
 };
@@ -286,6 +304,11 @@ __device__ __forceinline__ uint32_t key_of_id(const IdSource& src, int idx, uint
   }
   // ids outside the table (negative ones included) become the sentinel N and sort to the end
   if ((uint64_t)id >= (uint64_t)src.rows) return N;
+  if (src.i3_bits > 0) {
+    const uint32_t row = (uint32_t)id, p = row / src.n3, i3 = row - p * src.n3;
+    const uint32_t i1 = p / src.n2, i2 = p - i1 * src.n2;
+    return ((i2 * src.n1 + i1) << src.i3_bits) | i3;
+  }
   if (src.split > 1) {
     // first-core index i1 -> split*i1 + slab, the other two coordinates stay
     const int64_t i1 = id / src.n23;

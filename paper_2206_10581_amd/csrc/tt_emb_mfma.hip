@@ -1280,7 +1280,7 @@ void launch_row_fwd_mfma(const Plan& pl, const Workspace& ws, const float* g3, i
 void launch_gsum_block(const Plan& pl, const Workspace& ws, const float* grad, int B,
                        hipStream_t st) {
   const int grid = grid_cap(cdivi(B, kGsumBlockSlots), kMGridCap);
-  const uint32_t* perm = ws.val[(pl.passes - 1) & 1];
+  const uint32_t* perm = ws.val[pl.keys.sorted()];
   const int D = pl.sh.D;
   if (D == 64)
     k_gsum_block<1><<<grid, kGsumThreads, 0, st>>>(B, D, grad, ws.s_u, perm, ws.gsum, ws.ctr);
