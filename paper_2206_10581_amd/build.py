@@ -8,7 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 SOURCES = ["tt_emb_index.hip", "tt_emb_compute.hip", "tt_emb_mfma.hip", "tt_emb_direct.hip", "tt_emb_lookup.hip",
-           "tt_emb_calib.hip", "tt_emb_api.hip"]
+           "tt_emb_any.hip", "tt_emb_calib.hip", "tt_emb_api.hip"]
 LIB = os.path.join(HERE, "libtt_emb.so")
 
 
