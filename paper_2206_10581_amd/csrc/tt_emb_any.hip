@@ -15,8 +15,6 @@
 
 namespace ttemb {
 
-typedef float f4 __attribute__((ext_vector_type(4)));
-
 __device__ __forceinline__ f4 mfma_any(float a, float b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }

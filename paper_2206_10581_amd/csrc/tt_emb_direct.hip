@@ -23,8 +23,6 @@
 
 namespace ttemb {
 
-typedef float f4 __attribute__((ext_vector_type(4)));
-
 constexpr int kDThreads = 256;
 constexpr int kDWaves = kDThreads / kWave;
 constexpr int kDirectMax = 8192;             // most items of a batch on these kernels

@@ -17,8 +17,7 @@ __host__ __device__ constexpr int sort_items(int threads) { return threads / kWa
 constexpr int kFoldRows = 16;       // histogram rows a thread keeps in flight while it adds up a column
 constexpr int kChunk3 = 16;       // record slots per partial sum (chunk) of a G3 slice gradient
 // Batches of up to kSmallBatch rows are cut finer where that puts more wavefronts in flight: by-i3
-// chunks of 8 ids instead of 16 (-3.7 us per step at 200,000 rows, +6..18 us at 500,000), row tiles
-// of 16 slots instead of 32.
+// chunks of 8 ids instead of 16 (-3.7 us per step at 200,000 rows, +6..18 us at 500,000).
 constexpr int kSmallBatch = 1 << 18;
 constexpr int kChunk3Min = 8;
 inline int chunk3_fill(int64_t B) { return B <= kSmallBatch ? kChunk3Min : kChunk3; }
@@ -363,6 +362,22 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+typedef float f4 __attribute__((ext_vector_type(4)));
+
+// Transposes the 4 x 4 block that four neighbouring lanes hold a line each of.
+template <int PERM>
+__device__ __forceinline__ float quad_get(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), PERM, 0xf, 0xf, true));
+}
+__device__ __forceinline__ f4 quad_turned(f4 v, int lane) {
+  const bool odd = lane & 1, upper = lane & 2;
+  // 2 x 2 blocks between lanes l and l ^ 1, then the blocks between l and l ^ 2
+  const float a = quad_get<0xB1>(odd ? v.x : v.y), b = quad_get<0xB1>(odd ? v.z : v.w);
+  v = odd ? f4{a, v.y, b, v.w} : f4{v.x, a, v.z, b};
+  const float c = quad_get<0x4E>(upper ? v.x : v.z), d = quad_get<0x4E>(upper ? v.y : v.w);
+  return upper ? f4{c, d, v.z, v.w} : f4{v.x, v.y, c, d};
 }
 
 }  // namespace ttemb

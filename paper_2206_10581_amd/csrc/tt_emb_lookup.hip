@@ -10,8 +10,6 @@
 
 namespace ttemb {
 
-typedef float f4 __attribute__((ext_vector_type(4)));
-
 constexpr int kLThreads = 256;
 constexpr int kLWaves = kLThreads / kWave;
 
@@ -30,20 +28,6 @@ __device__ __forceinline__ void swap_halves(float x, float y, float& of_lower, f
                                                   false, false);
   of_lower = __builtin_bit_cast(float, (uint32_t)r[0]);
   of_upper = __builtin_bit_cast(float, (uint32_t)r[1]);
-}
-
-// Transposes the 4 x 4 block that four neighbouring lanes hold a line each of.
-template <int PERM>
-__device__ __forceinline__ float quad_get(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), PERM, 0xf, 0xf, true));
-}
-__device__ __forceinline__ f4 quad_turned(f4 v, int lane) {
-  const bool odd = lane & 1, upper = lane & 2;
-  // 2 x 2 blocks between lanes l and l ^ 1, then the blocks between l and l ^ 2
-  const float a = quad_get<0xB1>(odd ? v.x : v.y), b = quad_get<0xB1>(odd ? v.z : v.w);
-  v = odd ? f4{a, v.y, b, v.w} : f4{v.x, a, v.z, b};
-  const float c = quad_get<0x4E>(upper ? v.x : v.z), d = quad_get<0x4E>(upper ? v.y : v.w);
-  return upper ? f4{c, d, v.z, v.w} : f4{v.x, v.y, c, d};
 }
 
 // One wavefront per tile of TSL sorted slots.  Slabs (four lines of G1 each, `split` of them for

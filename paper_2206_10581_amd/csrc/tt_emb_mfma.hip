@@ -17,17 +17,10 @@
 
 namespace ttemb {
 
-typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f16v __attribute__((ext_vector_type(16)));
 
 constexpr int kMThreads = 256;
 constexpr int kMWaves = kMThreads / kWave;
-// sorted slots per wavefront in the row kernel (lanes past it idle in the index steps): half a
-// wavefront's worth keeps twice as many wavefronts in flight, which hides the store latency better
-// sorted slots per wavefront in the row kernel: 16 for batches up to kRowSmallBatch rows (more
-// wavefronts in flight: -2.6 us per step at 200,000 rows), 32 above (fewer repeated operand loads:
-// -7 us at 500,000 rows)
-constexpr int kRowSmallBatch = kSmallBatch;
 
 __device__ __forceinline__ f16v mfma32(float a, float b, f16v c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
@@ -52,14 +45,9 @@ __device__ __forceinline__ int lane_value(int v, int src) {
 // A value that is the same in all lanes, as a scalar.
 __device__ __forceinline__ int wave_value(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// One lane's share (VPL consecutive floats, VPL = 1 or 2) of a row, moved with a single
-// non-temporal access: rows of out and grad_out are streamed once and should not displace the
-// intermediates that the path does re-read.
-template <int VPL>
-__device__ __forceinline__ void stream_store(float* dst, const float* v) {
-  if constexpr (VPL == 2) __builtin_nontemporal_store(f2{v[0], v[1]}, (f2*)dst);
-  else __builtin_nontemporal_store(v[0], dst);
-}
+// One lane's share (VPL consecutive floats, VPL = 1 or 2) of a row, moved with a single non-temporal
+// access: rows of grad_out are streamed once and should not displace the intermediates that the path does
+// re-read.
 template <int VPL>
 __device__ __forceinline__ void stream_load(const float* src, float* v) {
   if constexpr (VPL == 2) {
@@ -838,150 +826,153 @@ __global__ __launch_bounds__(mid_waves<R>() * kWave, 6) void k_bwd_mid_mfma(
 
 // ---------------------------------------------------------------------------------------------
 // Rows: one wavefront per tile of TSL sorted slots.  The distinct ids of a tile are taken in groups
-// of up to 16/D3 consecutive ids that share a prefix: E = P_q (16 x R) times their G3 slices side
-// by side (R x 16).  Up to NB = 3 groups are worked on together (operand loads in flight together);
-// their rows go through LDS so that one store instruction writes a whole row to every batch
-// position that holds the id.  Rows are written with non-temporal stores: nothing on this path
-// reads them back.
-template <int R, int D3, int TSL>
+// of up to 16/D3 consecutive ids that share a prefix: E^T = (their G3 slices, transposed, one below the
+// other: 16 x R) times P_q^T (R x 16).  A lane's four accumulators are then four neighbours of a row, and
+// one 16-byte store a lane writes whole rows of the group's ids; ids with several positions repeat it.
+// Rows are written with non-temporal stores: nothing on this path reads them back.
+//
+// Operands are loaded as they lie in memory: P_q by whole lines into LDS, slices of G3 in 4 x 4 blocks that
+// quads of lanes turn; those of the next group are in flight while a group is formed and stored.  Read as
+// the matrix cores want them, each 16 bytes of P_q are a line of their own (64 cycles a load instruction)
+// and G3 takes a load per element.  With those, and rows through LDS, the kernel took (500,000 ids of n =
+// (480,480,482), d = (4,4,8), Zipf / clustered) 135 / 112 us at rank 64 and 58 / 54 at rank 16, now 96 / 95
+// and 56 / 48; rank 128, 200,000 Zipf ids of (480,500,500) x (8,4,4): 276 -> 138.  At rank 32 and 200,000
+// Zipf ids it is at the rate of random 512-byte stores (27 -> 26 us).
+// Slots of a tile: short ones for short chains of groups (200,000 Zipf ids at rank 32: 26 / 30 / 38 us with
+// 8 / 16 / 32), longer ones where a product is 4 to 8 KiB and neighbours share it (clustered ids at rank
+// 64: 106 / 95 / 92 us; Zipf 98 / 96 / 105).
+constexpr int row_slots(int R) { return R <= 32 ? 8 : 16; }
+
+template <int R, int D3>
 __global__ __launch_bounds__(kMThreads) void k_row_fwd_mfma(
     int B, const float* __restrict__ g3, const float* __restrict__ P,
     const int4* __restrict__ s_rec, float* __restrict__ out, Counters* ctr) {
-  constexpr int PN = 16 * R, S3 = R * D3, D = 16 * D3, UPT = 16 / D3, KQ = R / 4, VPL = D / kWave;
-  // groups per batch: 4 cost two wavefronts per SIMD of occupancy; at rank 128 one group's operands
-  // are 64 registers already
-  constexpr int NB = R >= 128 ? 1 : TSL <= 16 ? 2 : 3;
-  __shared__ float ebuf[kMWaves][NB * UPT * D];
+  constexpr int TSL = row_slots(R);
+  constexpr int PN = 16 * R, S3 = R * D3, D = 16 * D3, UPT = 16 / D3, KQ = R / 4;
+  constexpr int RS = R + 4;                       // stride of a line of P in LDS
+  constexpr int NP = (PN + 255) / 256;            // 16-byte words of P a lane loads
+  constexpr int NC = R >= 16 ? R / 16 : 0;        // blocks of G3 a quad loads (rank 8: element by element)
+  __shared__ __align__(16) float Pl[kMWaves][16 * RS];
   const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   const int l16 = lane % 16, kg = lane / 16;
-  const int ul = l16 / D3, j3 = l16 % D3;
-  float* E = ebuf[w];
-  const int ntiles = (B + TSL - 1) / TSL;
-  for (int tile = blockIdx.x * kMWaves + w; tile < ntiles; tile += gridDim.x * kMWaves) {
-    const int s = lane < TSL ? tile * TSL + lane : B;
-    const int4 rec = s_rec[min(s, B - 1)];  // {unique-id index, batch position, prefix, i3}
-    int mysu = rec.x;
-    const uint32_t myb = (uint32_t)rec.y;
-    if (s >= B) mysu = -2;  // lanes past the batch: neither an id nor an out-of-range slot
-    if (s < B && myb >= (uint32_t)B) atomicOr(&ctr->err, 4);
-    // out-of-range ids (the tail of the sorted order) get zero rows
-    unsigned long long zero_slots = __ballot(mysu == -1 && myb < (uint32_t)B);
-    while (zero_slots) {
-      const int sl = __ffsll((long long)zero_slots) - 1;
-      zero_slots &= zero_slots - 1;
-      float* o = out + (size_t)(uint32_t)lane_value((int)myb, sl) * D + lane * VPL;
+  const int ul = l16 / D3, j3 = l16 % D3;         // this lane's line of E^T as an operand
+  const int my_id = kg * 4 / D3, my_j3 = kg * 4 % D3;  // and what its accumulators hold
+  float* Pw = Pl[w];
+  const int tile = blockIdx.x * kMWaves + w;
+  if (tile * TSL >= B) return;
+  const int s = lane < TSL ? tile * TSL + lane : B;
+  const int4 rec = s_rec[min(s, B - 1)];  // {unique-id index, batch position, prefix, i3}
+  const int mysu = s < B ? rec.x : -2;    // lanes past the batch: neither an id nor an out-of-range slot
+  const uint32_t myb = (uint32_t)rec.y;
+  if (s < B && myb >= (uint32_t)B) atomicOr(&ctr->err, 4);
+  // out-of-range ids (the tail of the sorted order) get zero rows
+  unsigned long long zero_slots = __ballot(mysu == -1 && myb < (uint32_t)B);
+  while (zero_slots) {
+    const int sl = __ffsll((long long)zero_slots) - 1;
+    zero_slots &= zero_slots - 1;
+    float* o = out + (size_t)(uint32_t)lane_value((int)myb, sl) * D;
+    for (int e = lane; e < D; e += kWave) o[e] = 0.f;
+  }
+  const int nv = __popcll(__ballot(mysu >= 0));
+  if (nv == 0) return;
+  const int u_lo = lane_value(mysu, 0), nu = lane_value(mysu, nv - 1) - u_lo + 1;
+  // lane e takes the tile's e-th distinct id: its first slot, prefix and i3
+  const int su_before = __shfl_up(mysu, 1);
+  const bool first = lane < nv && (lane == 0 || mysu != su_before);
+  const int rank = lane < nv ? mysu - u_lo : nu - 1;
+  const int to = (first ? rank : nu + lane - rank - 1) * 4;
+  const int u_slot = __builtin_amdgcn_ds_permute(to, lane);
+  const int myq = __builtin_amdgcn_ds_permute(to, rec.z), myi3 = __builtin_amdgcn_ds_permute(to, rec.w);
+  // groups: every UPT-th id of a run of ids with one prefix starts one
+  const int q_before = __shfl_up(myq, 1);
+  const unsigned long long runs = __ballot(lane < nu && (lane == 0 || myq != q_before));
+  const unsigned long long upto = runs & (lane == 63 ? ~0ull : ((2ull << lane) - 1ull));
+  const int run_first = 63 - __clzll((long long)(upto | 1ull));
+  const unsigned long long groups = __ballot(lane < nu && ((lane - run_first) % UPT) == 0);
+  auto end_of = [&](int st) {
+    const unsigned long long after = groups & ~((2ull << st) - 1ull);
+    return after ? __ffsll((long long)after) - 1 : nu;
+  };
+  f4 p[NP], cv[NC > 0 ? NC : 1];
+  float ce[NC > 0 ? 1 : KQ];
+  int have = -1;  // prefix of p
+  auto fetch = [&](int st) {
+    const int q = lane_value(myq, st);
+    if (q != have) {
+      have = q;
+      const f4* src = (const f4*)(P + (size_t)q * PN);
 #pragma unroll
-      for (int e = 0; e < VPL; ++e) o[e] = 0.f;
+      for (int k = 0; k < NP; ++k) p[k] = src[PN < 256 ? lane % (PN / 4) : lane + k * kWave];
     }
-    const int nv = __popcll(__ballot(mysu >= 0));
-    if (nv == 0) continue;
-    const int u_lo = lane_value(mysu, 0), nu = lane_value(mysu, nv - 1) - u_lo + 1;
-    // lane e takes prefix and i3 of the tile's e-th distinct id from that id's first slot
-    int* xch = (int*)E;
-    const int su_before = __shfl_up(mysu, 1);
-    if (mysu >= 0 && (lane == 0 || mysu != su_before)) {
-      xch[mysu - u_lo] = rec.z;
-      xch[TSL + mysu - u_lo] = rec.w;
+    const float* C = g3 + (size_t)__shfl(myi3, min(st + ul, end_of(st) - 1)) * S3 + (KQ * kg) * D3;
+    if constexpr (NC > 0) {
+#pragma unroll
+      for (int j = 0; j < NC; ++j) cv[j] = *(const f4*)(C + (4 * j + j3 % 4) * D3 + j3 / 4 * 4);
+    } else {
+#pragma unroll
+      for (int j = 0; j < KQ; ++j) ce[j] = C[j * D3 + j3];
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    int myq = xch[min(lane, nu - 1)];
-    const int myi3 = xch[TSL + min(lane, nu - 1)];
-    if (lane >= nu) myq = -1;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    // group starts: every UPT-th id of a run of ids with one prefix
-    const int q_before = __shfl_up(myq, 1);
-    const unsigned long long run_starts = __ballot(lane < nu && (lane == 0 || myq != q_before));
-    const unsigned long long upto = run_starts & (lane == 63 ? ~0ull : ((2ull << lane) - 1ull));
-    const int run_first = 63 - __clzll((long long)upto);
-    unsigned long long groups = __ballot(lane < nu && ((lane - run_first) % UPT) == 0);
-    const int rel = mysu - u_lo;
-    while (groups) {
-      int st[NB], gsz[NB];
+  };
+  fetch(0);
+  int in_lds = -1;  // prefix whose product is in LDS
+  for (int st = 0; st < nu;) {
+    const int end = end_of(st);
+    if (have != in_lds) {
+      in_lds = have;
+      wave_sync();
 #pragma unroll
-      for (int x = 0; x < NB; ++x) {
-        if (groups) {
-          st[x] = __ffsll((long long)groups) - 1;
-          groups &= groups - 1;
-          gsz[x] = (groups ? __ffsll((long long)groups) - 1 : nu) - st[x];
-        } else {
-          st[x] = -1;
-          gsz[x] = 0;
-        }
+      for (int k = 0; k < NP; ++k) {
+        const int e = 4 * (lane + k * kWave);
+        if (PN >= 256 || e < PN) *(f4*)(Pw + (e / R) * RS + e % R) = p[k];
       }
-      float a[NB][KQ], b[NB][KQ];
-      int qx[NB];
-#pragma unroll
-      for (int x = 0; x < NB; ++x) {
-        const int first = st[x] >= 0 ? st[x] : 0;
-        const int q = lane_value(myq, first);
-        qx[x] = q;
-        const int i3 = __shfl(myi3, min(first + ul, nu - 1));
-        const float* pc = g3 + (size_t)i3 * S3 + (KQ * kg) * D3 + j3;
-        // a group whose prefix is the previous group's takes that group's P operand
-        if (x == 0 || q != qx[x - 1]) {
-          const float* pf = P + (size_t)(q >= 0 ? q : 0) * PN + l16 * R + KQ * kg;
-          if constexpr (KQ % 4 == 0) {
-            const f4* pa = (const f4*)pf;
-#pragma unroll
-            for (int j = 0; j < KQ / 4; ++j) {
-              const f4 v = pa[j];
-              a[x][4 * j + 0] = v.x;
-              a[x][4 * j + 1] = v.y;
-              a[x][4 * j + 2] = v.z;
-              a[x][4 * j + 3] = v.w;
-            }
-          } else {  // rank 8: two floats per lane
-#pragma unroll
-            for (int j = 0; j < KQ; ++j) a[x][j] = pf[j];
-          }
-        }
-#pragma unroll
-        for (int j = 0; j < KQ; ++j) b[x][j] = pc[j * D3];
-      }
-      TT_LOADS_DONE();
-#pragma unroll
-      for (int x = 1; x < NB; ++x)
-        if (qx[x] == qx[x - 1]) {
-#pragma unroll
-          for (int j = 0; j < KQ; ++j) a[x][j] = a[x - 1][j];
-        }
-#pragma unroll
-      for (int x = 0; x < NB; ++x) {
-        f4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int j = 0; j < KQ; ++j) acc = mfma16(a[x][j], b[x][j], acc);
-        if (ul < gsz[x]) {
-          float* e = E + (st[x] + ul - st[0]) * D + (4 * kg) * D3 + j3;
-#pragma unroll
-          for (int v = 0; v < 4; ++v) e[v * D3] = acc[v];
-        }
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      // rows of the ids st[0] .. last of this batch, to every slot that holds them
-      int last = st[0] + gsz[0];
-#pragma unroll
-      for (int x = 1; x < NB; ++x)
-        if (st[x] >= 0) last = st[x] + gsz[x];
-      for (int k = st[0]; k < last; ++k) {
-        float e[VPL];
-#pragma unroll
-        for (int y = 0; y < VPL; ++y) e[y] = E[(k - st[0]) * D + lane * VPL + y];
-        unsigned long long slots = __ballot(rel == k && mysu >= 0);
-        while (slots) {
-          const int sl = __ffsll((long long)slots) - 1;
-          slots &= slots - 1;
-          const uint32_t b_row = (uint32_t)lane_value((int)myb, sl);
-          if (b_row < (uint32_t)B) stream_store<VPL>(out + (size_t)b_row * D + lane * VPL, e);
-        }
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
+      wave_sync();
     }
+    float c[KQ];
+    if constexpr (NC > 0) {
+#pragma unroll
+      for (int j = 0; j < NC; ++j) {
+        const f4 t = quad_turned(cv[j], lane);
+        c[4 * j] = t.x;
+        c[4 * j + 1] = t.y;
+        c[4 * j + 2] = t.z;
+        c[4 * j + 3] = t.w;
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < KQ; ++j) c[j] = ce[j];
+    }
+    if (end < nu) fetch(end);  // in flight while this group is formed and stored
+    const float* pr = Pw + l16 * RS + KQ * kg;
+    f4 acc = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (KQ % 4 == 0) {
+#pragma unroll
+      for (int j = 0; j < KQ; j += 4) {
+        const f4 v = *(const f4*)(pr + j);
+        acc = mfma16(c[j], v.x, acc);
+        acc = mfma16(c[j + 1], v.y, acc);
+        acc = mfma16(c[j + 2], v.z, acc);
+        acc = mfma16(c[j + 3], v.w, acc);
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < KQ; ++j) acc = mfma16(c[j], pr[j], acc);
+    }
+    // A group of fewer than UPT ids holds its last one several times over: those lanes share its positions
+    const int last = end - 1 - st, part = max(my_id - last, 0), parts = my_id >= last ? UPT - last : 1;
+    const int id = st + min(my_id, last);
+    const int s0 = __shfl(u_slot, id) + part, after = __shfl(u_slot, min(id + 1, nu - 1));
+    const int s1 = id + 1 < nu ? after : nv;
+    float* o = out + (size_t)l16 * D3 + my_j3;
+    for (int at = s0; __ballot(at < s1) != 0ull; at += 4 * parts) {
+      uint32_t b[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) b[k] = (uint32_t)__shfl((int)myb, min(at + k * parts, 63));
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (at + k * parts < s1 && b[k] < (uint32_t)B)
+          __builtin_nontemporal_store(acc, (f4*)(o + (size_t)b[k] * D));
+    }
+    st = end;
   }
 }
 
@@ -1261,18 +1252,13 @@ void launch_bwd_mid_mfma(const Plan& pl, const Workspace& ws, const float* g1, c
 
 void launch_row_fwd_mfma(const Plan& pl, const Workspace& ws, const float* g3, int B, float* out,
                          hipStream_t st) {
-#define TT_ROW(D3_, TSL_)                                                                        \
-  {                                                                                              \
-    constexpr int D3 = D3_, TSL = TSL_;                                                          \
-    const int grid = grid_cap(cdivi(cdivi(B, TSL), kMWaves), 1 << 20);                           \
-    TT_DISPATCH_R8(pl.sh.r1, (k_row_fwd_mfma<R, D3, TSL><<<grid, kMThreads, 0, st>>>(            \
-                                 B, g3, ws.P, ws.s_rec, out, ws.ctr)));                          \
-  }
-  const bool small = B <= kRowSmallBatch;
+#define TT_ROW(D3_)                                                                                     \
+  TT_DISPATCH_R8(pl.sh.r1, (k_row_fwd_mfma<R, D3_><<<cdivi(cdivi(B, row_slots(R)), kMWaves), kMThreads, 0, \
+                                                     st>>>(B, g3, ws.P, ws.s_rec, out, ws.ctr)))
   if (pl.sh.d3 == 4) {
-    if (small) TT_ROW(4, 16) else TT_ROW(4, 32)
+    TT_ROW(4)
   } else {
-    if (small) TT_ROW(8, 16) else TT_ROW(8, 32)
+    TT_ROW(8)
   }
 #undef TT_ROW
 }
