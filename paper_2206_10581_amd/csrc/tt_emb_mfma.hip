@@ -1,4 +1,4 @@
-// Matrix-core (MFMA, fp32) kernels for the table shapes d1 = d2 = 4, r1 = r2 = R in {16, 32, 64},
+// Matrix-core (MFMA) kernels for the table shapes d1 = d2 = 4, r1 = r2 = R in {16, 32, 64},
 // d3 in {4, 8}: the partial product of a row is then 16 x R, and once ids that share an (i1,i2)
 // prefix, an i2 or an i3 are stacked (paper Section 4.2: they share core slices) every step of the
 // path is a dense contraction with a 16- or 32-wide side.
@@ -146,22 +146,88 @@ __global__ __launch_bounds__(kWave) void k_prefix_fwd_mfma(
 }
 
 // ---------------------------------------------------------------------------------------------
-// The same for ranks 64 and 128, where a G2 slice is 64 to 256 KiB and the operand traffic of
-// independent 32 x 32 tiles (8 flops per byte through the L2) is what bounds the kernel.  A block of
-// four wavefronts takes one chunk's 64 rows times 128 columns: the rows are staged in LDS once for
-// all four, every wavefront reads a G2 strip of 32 columns of its own straight into registers and
-// uses each value for both row tiles (32 flops per byte).
-// Rank 128, 308,840 prefixes of n = 480,500,500 (half a million ids, two slabs): 2.83 -> 1.85 ms,
-// 88 TFLOP/s, 2.5 GB written.
+// Ranks 64 and 128: a G2 slice has 64 to 256 KiB, and the products of the prefixes are large enough for
+// the rate of the matrix cores to count.  An fp32 number is the sum of three bf16 numbers (8 + 8 + 8
+// significant bits, each rounded to nearest), and bf16 products run sixteen times as fast as fp32 ones, so
+// a product of two such sums is formed as its six largest terms: hi*hi, hi*mid, mid*hi, mid*mid, hi*lo,
+// lo*hi, each exact and added up in fp32.  What is left out is below 2^-25 of a term and of either sign;
+// the error against 64 bits is that of the fp32 instructions or less (relative 2-norms, fp32 -> this: rank
+// 128, 20,000 uniform ids of (60,50,40) x (8,4,4), rows 2.87e-7 -> 2.61e-7, G1 4.30e-7 -> 4.16e-7, G2 1.83e-7 ->
+// 1.59e-7, G3 3.26e-7 -> 2.98e-7; with all numbers of one sign 1.72e-7 -> 1.72e-7 and 6.8e-8 -> 6.2e-8 for G2).
+//
+// Splits do not hold for infinities, for numbers that round up to one, and for numbers so small that their
+// lower parts leave the range of bf16.  Such an operand leaves NaN, an infinity or a very small number in
+// the result (recheck); a wavefront that finds one forms its tile anew with fp32 instructions.
+typedef __bf16 h2 __attribute__((ext_vector_type(2)));
+typedef __bf16 h4 __attribute__((ext_vector_type(4)));
+typedef __bf16 h8 __attribute__((ext_vector_type(8)));
+template <class V>
+struct Split {
+  V hi, mid, lo;
+};
+__device__ __forceinline__ void split_two(float x, float y, h2& hi, h2& mid, h2& lo) {
+  const f2 v = {x, y};
+  hi = __builtin_convertvector(v, h2);
+  const f2 r = v - __builtin_convertvector(hi, f2);  // exact, as is the next one
+  mid = __builtin_convertvector(r, h2);
+  lo = __builtin_convertvector(r - __builtin_convertvector(mid, f2), h2);
+}
+__device__ __forceinline__ Split<h4> split_four(f4 v) {
+  h2 a[3], b[3];
+  split_two(v.x, v.y, a[0], a[1], a[2]);
+  split_two(v.z, v.w, b[0], b[1], b[2]);
+  return {__builtin_shufflevector(a[0], b[0], 0, 1, 2, 3), __builtin_shufflevector(a[1], b[1], 0, 1, 2, 3),
+          __builtin_shufflevector(a[2], b[2], 0, 1, 2, 3)};
+}
+__device__ __forceinline__ Split<h8> split_eight(const float* v) {
+  const Split<h4> a = split_four(f4{v[0], v[1], v[2], v[3]}), b = split_four(f4{v[4], v[5], v[6], v[7]});
+  return {__builtin_shufflevector(a.hi, b.hi, 0, 1, 2, 3, 4, 5, 6, 7),
+          __builtin_shufflevector(a.mid, b.mid, 0, 1, 2, 3, 4, 5, 6, 7),
+          __builtin_shufflevector(a.lo, b.lo, 0, 1, 2, 3, 4, 5, 6, 7)};
+}
+// acc += A B, 32 x 16 times 16 x 32: half a wavefront holds eight k each, A[i][k]: i = lane%32, B[k][j]:
+// j = lane%32, D as of v_mfma_f32_32x32x2f32
+__device__ __forceinline__ f16v mfma_split(const Split<h8>& a, const Split<h8>& b, f16v acc) {
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.lo, b.hi, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi, b.lo, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.mid, b.mid, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.mid, b.hi, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi, b.mid, acc, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi, b.hi, acc, 0, 0, 0);
+}
+// Whether some entry is not finite, or below 2^-80 and not zero: all finite operands whose splits are not
+// exact are below 2^-102 (or round to an infinity), and make an entry that large only with factors of 2^22.
+__device__ __forceinline__ bool recheck(const f16v& acc) {
+  uint32_t most = 0u, least = ~0u;  // of the magnitudes, of those that are not zero less one
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const float f = acc[v];  // (a vector's element is not cast in place: the compiler casts its first one)
+    const uint32_t x = __builtin_bit_cast(uint32_t, f) & 0x7fffffffu;
+    most = max(most, x);
+    least = min(least, x - 1u);
+  }
+  return __ballot(most >= 0x7f800000u || least + 1u < (127u - 80u) << 23 && least != ~0u) != 0ull;
+}
+// Eight bf16 of a line in LDS, of each of the three planes
+template <int PLANE>
+__device__ __forceinline__ Split<h8> split_from(const __bf16* at) {
+  return {*(const h8*)at, *(const h8*)(at + PLANE), *(const h8*)(at + 2 * PLANE)};
+}
+
+// P_q for the <= 16 prefixes of a by-i2 chunk.  A block of four wavefronts takes a chunk's 64 lines times
+// 128 columns: the lines are split and staged in LDS once for all four, every wavefront takes a strip of 32
+// columns of G2 straight to registers, splits it and uses it for both tiles of 32 lines.  At most as many
+// blocks as the device holds walk the units: the grid is sized for the most chunks a batch could have, and
+// dispatching blocks that find nothing cost more than the work.
 template <int R>
-__global__ __launch_bounds__(kMThreads, R >= 128 ? 3 : 4) void k_prefix_fwd_wide(
+__global__ __launch_bounds__(kMThreads, 3) void k_prefix_fwd_wide(
     const float* __restrict__ g1, const float* __restrict__ g2, const int4* __restrict__ c2_item,
     const int4* __restrict__ c2_desc, float* __restrict__ P, const Counters* __restrict__ ctr) {
   static_assert(R == 64 || R == 128, "columns of a block divide the product");
-  constexpr int W = 4 * R, PN = 16 * R, S1 = 4 * R, S2 = R * W, KH = R / 2;
+  constexpr int W = 4 * R, PN = 16 * R, S1 = 4 * R, S2 = R * W, KT = R / 16;
   constexpr int UN = W / 128;  // blocks side by side over the columns
-  constexpr int AS = R + 4;    // row stride in LDS: sixteen lanes' 16-byte reads cover all banks
-  __shared__ __align__(16) float As[64 * AS];
+  constexpr int AS = R + 8, PL = 64 * AS;  // stride of a line and of a plane in LDS
+  __shared__ __align__(16) __bf16 As[3 * PL];
   __shared__ int q_of[kChunk2], i1_of[kChunk2];
   const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave, half = lane / 32, l32 = lane % 32;
   const int nunit = ctr->nchunk2 * UN;
@@ -176,77 +242,84 @@ __global__ __launch_bounds__(kMThreads, R >= 128 ? 3 : 4) void k_prefix_fwd_wide
       q_of[tid] = item.x;
       i1_of[tid] = item.y;
     }
-    const float* Bm = g2 + (size_t)desc.x * S2 + (size_t)(KH * half) * W + col;
-    float b[KH];
+    const float* Bm = g2 + (size_t)desc.x * S2 + col;
+    float b[KT][8];
 #pragma unroll
-    for (int j = 0; j < KH; ++j) b[j] = Bm[(size_t)j * W];
+    for (int t = 0; t < KT; ++t)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) b[t][j] = Bm[(size_t)(16 * t + 8 * half + j) * W];
     __syncthreads();
-    // rows of prefixes past the count repeat the last one; they are not stored
+    // lines of prefixes past the count repeat the last one; they are not stored
     f4 row[R / 16];
 #pragma unroll
     for (int i = 0; i < R / 16; ++i) {
-      const int e = tid + i * kMThreads;  // 16-byte word of the 64 rows
+      const int e = tid + i * kMThreads;  // 16-byte word of the 64 lines
       row[i] = ((const f4*)(g1 + (size_t)wave_value(i1_of[e / R]) * S1))[e % R];
     }
     TT_LOADS_DONE();
 #pragma unroll
     for (int i = 0; i < R / 16; ++i) {
       const int e = (tid + i * kMThreads) * 4;
-      *(f4*)&As[(e / R) * AS + e % R] = row[i];
+      const Split<h4> x = split_four(row[i]);
+      __bf16* to = As + (e / R) * AS + e % R;
+      *(h4*)to = x.hi;
+      *(h4*)(to + PL) = x.mid;
+      *(h4*)(to + 2 * PL) = x.lo;
     }
     __syncthreads();
+    f16v acc[2] = {TT_ZERO16, TT_ZERO16};
+    const bool two = cnt > 8;  // uniform: the second tile has a prefix
+#pragma unroll
+    for (int t = 0; t < KT; ++t) {
+      const Split<h8> y = split_eight(b[t]);
+      const __bf16* at = As + l32 * AS + 16 * t + 8 * half;
+      acc[0] = mfma_split(split_from<PL>(at), y, acc[0]);
+      if (two) acc[1] = mfma_split(split_from<PL>(at + 32 * AS), y, acc[1]);
+    }
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
       if (mt * 8 >= cnt) break;
-      const f4* ar = (const f4*)&As[(mt * 32 + l32) * AS + KH * half];
-      f16v acc = TT_ZERO16;
-#pragma unroll
-      for (int j = 0; j < KH / 4; ++j) {
-        const f4 a = ar[j];
-        acc = mfma32(a.x, b[4 * j + 0], acc);
-        acc = mfma32(a.y, b[4 * j + 1], acc);
-        acc = mfma32(a.z, b[4 * j + 2], acc);
-        acc = mfma32(a.w, b[4 * j + 3], acc);
+      if (recheck(acc[mt])) {
+        const float* ar = g1 + (size_t)i1_of[mt * 8 + l32 / 4] * S1 + (l32 % 4) * R + half * (R / 2);
+        const float* br = Bm + (size_t)(half * (R / 2)) * W;
+        acc[mt] = TT_ZERO16;
+#pragma unroll 4
+        for (int j = 0; j < R / 2; ++j) acc[mt] = mfma32(ar[j], br[(size_t)j * W], acc[mt]);
       }
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int ql = mt * 8 + 2 * (v / 4) + half;
-        if (ql < cnt) P[(size_t)q_of[ql] * PN + (v % 4) * W + col] = acc[v];
+        if (ql < cnt) P[(size_t)q_of[ql] * PN + (v % 4) * W + col] = acc[mt][v];
       }
     }
   }
 }
 
-// ---------------------------------------------------------------------------------------------
-// Gradients at prefix level for ranks 64 and 128 (the lower ranks: k_bwd_mid_mfma).  Units of work,
-// one block of four wavefronts each, walked with the grid's stride:
+// Gradients at prefix level.  Units of work, one block of four wavefronts each, walked with the grid's
+// stride:
 //   dG2   a group of chunks (wide_group) of one i2 and 128 columns: sum over the prefixes q of
-//         G1[i1(q)]^T dPsum_q, R x 128.  The G1 rows of a chunk are staged in LDS for all four
-//         wavefronts, dPsum goes straight to registers (each value is used for R/32 row tiles and
-//         read once in all), and the sum stays in registers from chunk to chunk: a chunk's 64 terms
-//         are one chain, the chunks another (all in one chain, the error of dG2 was 2.1 times as
-//         large at 200,000 uniform ids of rank 64).
-//   dG1   a chunk: dg1part[q] = dPsum_q Bm^T, 64 x R with 4R to contract, 64 at a time through LDS
-//         (rows of Bm lie 4R floats apart: read by the lanes directly, every 16-byte load would
-//         touch a line of its own).
-// The dG2 units are the longer ones and come first.
-// Rank 128, 308,840 prefixes of n = 480,500,500: 4.55 -> 3.29 ms (99 TFLOP/s), and the update
-// kernel, which reads an eighth of the dG2 partials, 1.14 -> 0.35 ms.  Rank 64, 1,516 prefixes:
-// 35 -> 25 us.  Two blocks per compute unit at rank 128: three would spill fifty registers.
+//         G1[i1(q)]^T dPsum_q, R x 128.  The G1 lines of a chunk are split and staged in LDS, transposed,
+//         for all four wavefronts, dPsum goes straight to registers (each value is used for R/32 tiles),
+//         and the sum stays in registers from chunk to chunk: a chunk's 64 terms are one chain, the
+//         chunks another (all in one chain, the error of dG2 was 2.1 times as large at 200,000 uniform
+//         ids of rank 64).
+//   dG1   a chunk: dg1part[q] = dPsum_q Bm^T, 64 x R with 4R to contract, 32 at a time through LDS.
+// The units of a group follow each other, dG2 first: dPsum is then read again while it is near.
 template <int R>
-__global__ __launch_bounds__(kMThreads, R >= 128 ? 2 : 3) void k_prefix_bwd_wide(
+__global__ __launch_bounds__(kMThreads, 2) void k_prefix_bwd_wide(
     const float* __restrict__ g1, const float* __restrict__ g2, const float* __restrict__ dPsum,
     const int4* __restrict__ c2_item, const int4* __restrict__ c2_desc, float* __restrict__ dg1part,
     float* __restrict__ part2, const Counters* __restrict__ ctr) {
   static_assert(R == 64 || R == 128, "columns of a block divide the slice");
   constexpr int W = 4 * R, PN = 16 * R, S1 = 4 * R, S2 = R * W, UN = W / 128;
-  constexpr int KD = 64, KS = KD + 4;  // depth of a step of the dG1 product and its LDS row stride
-  constexpr int kLds = 64 * R > (64 + R) * KS ? 64 * R : (64 + R) * KS;
-  __shared__ __align__(16) float L[kLds];
+  constexpr int KD = 32, KS = KD + 8;  // depth of a step of the dG1 product, stride of its lines in LDS
+  constexpr int TS = 64 + 8;           // stride of a column of G1 in LDS
+  constexpr int PL2 = R * TS, PL1 = (64 + R) * KS, kLds = 3 * (PL2 > PL1 ? PL2 : PL1);
+  __shared__ __align__(16) __bf16 L[kLds];
   __shared__ int q_of[kChunk2], i1_of[kChunk2];
   const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave, half = lane / 32, l32 = lane % 32;
   const int nchunk = ctr->nchunk2, grp = wide_group(nchunk, R);
-  const int units2 = (nchunk + grp - 1) / grp * UN, nunit = units2 + nchunk;
+  const int per_group = UN + grp, nunit = (nchunk + grp - 1) / grp * per_group;
   // records of chunk c; those past its count are unwritten and repeat the last one
   auto chunk_records = [&](int c, int cnt) {
     __syncthreads();  // the readers of the previous chunk's records and LDS tiles are done
@@ -258,10 +331,10 @@ __global__ __launch_bounds__(kMThreads, R >= 128 ? 2 : 3) void k_prefix_bwd_wide
     __syncthreads();
   };
   for (int unit = blockIdx.x; unit < nunit; unit += gridDim.x) {
-    if (unit < units2) {
+    const int c0 = unit / per_group * grp, c1 = min(c0 + grp, nchunk), sub = unit % per_group;
+    if (sub < UN) {
       constexpr int MT = R / 32;
-      const int c0 = unit / UN * grp, c1 = min(c0 + grp, nchunk);
-      const int col = (unit % UN) * 128 + w * 32 + l32;
+      const int col = sub * 128 + w * 32 + l32;
       f16v sum[MT];
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) sum[mt] = TT_ZERO16;
@@ -270,46 +343,62 @@ __global__ __launch_bounds__(kMThreads, R >= 128 ? 2 : 3) void k_prefix_bwd_wide
       for (int c = c0; c < c1; ++c) {
         const int cnt = desc.z, bin = desc.x;
         chunk_records(c, cnt);
-        // contraction index k = 4*prefix + j1; half h of the wavefront takes k = 2j + h.  Prefixes
-        // past the count count zero (their G1 rows are cleared) and read the last one's dPsum.
-        float b[32];
-        const uint32_t bo = half * W + col;  // 32-bit offset of the lane from a scalar address
+        // contraction index k = 4*prefix + j1; of the sixteen of a step half h takes eight: two prefixes.
+        // Prefixes past the count count zero (their G1 lines are cleared) and read the last one's dPsum.
+        float b[4][8];
 #pragma unroll
-        for (int j = 0; j < 32; ++j)
-          b[j] = (dPsum + (size_t)wave_value(q_of[j / 2]) * PN + ((2 * j) % 4) * W)[bo];
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+          for (int x = 0; x < 2; ++x) {
+            const float* src = dPsum + (size_t)q_of[4 * t + 2 * half + x] * PN + col;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) b[t][4 * x + j] = src[j * W];
+          }
         const int4 next = c2_desc[min(c + 1, nchunk - 1)];
-        f4 row[R / 16];
+        // eight lines of a column a thread, R/32 times
+        float a[R / 32][8];
 #pragma unroll
-        for (int i = 0; i < R / 16; ++i) {
-          const int e = tid + i * kMThreads;
-          row[i] = ((const f4*)(g1 + (size_t)wave_value(i1_of[e / R]) * S1))[e % R];
-          if (e / R >= cnt) row[i] = f4{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < R / 32; ++i) {
+          const int e = tid + i * kMThreads, m = e % R, k8 = e / R;  // column; eight lines: two prefixes
+#pragma unroll
+          for (int x = 0; x < 2; ++x) {
+            const bool on = 2 * k8 + x < cnt;
+            const float* src = g1 + (size_t)i1_of[2 * k8 + x] * S1 + m;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const float v = src[j * R];
+              a[i][4 * x + j] = on ? v : 0.f;
+            }
+          }
         }
         TT_LOADS_DONE();
-        // element (k, m) at L[k*R + (m ^ 32*(k%2))]: the two halves of a read use other banks
 #pragma unroll
-        for (int i = 0; i < R / 16; ++i) {
-          const int e = (tid + i * kMThreads) * 4, k = e / R;
-          *(f4*)&L[k * R + ((e % R) ^ (32 * (k % 2)))] = row[i];
+        for (int i = 0; i < R / 32; ++i) {
+          const int e = tid + i * kMThreads, m = e % R, k8 = e / R;
+          const Split<h8> x = split_eight(a[i]);
+          __bf16* to = L + m * TS + k8 * 8;
+          *(h8*)to = x.hi;
+          *(h8*)(to + PL2) = x.mid;
+          *(h8*)(to + 2 * PL2) = x.lo;
         }
+        Split<h8> y[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) y[t] = split_eight(b[t]);
         __syncthreads();
-        // two row tiles at a time: their 32 accumulators and all of `sum` fit the registers
 #pragma unroll
-        for (int m0 = 0; m0 < MT; m0 += 2) {
-          f16v acc[2] = {TT_ZERO16, TT_ZERO16};
+        for (int mt = 0; mt < MT; ++mt) {
+          f16v acc = TT_ZERO16;
 #pragma unroll
-          for (int hf = 0; hf < 2; ++hf)
-            if (8 * hf < cnt) {  // uniform: else no prefix of this half of the chunk
-#pragma unroll
-              for (int j = 16 * hf; j < 16 * hf + 16; ++j) {
-#pragma unroll
-                for (int x = 0; x < 2; ++x)
-                  acc[x] = mfma32(L[(2 * j + half) * R + (((m0 + x) * 32 + l32) ^ (32 * half))], b[j], acc[x]);
-                if (j % 4 == 3) TT_LOADS_DONE();  // bounds how far operand reads run ahead (registers)
-              }
-            }
-#pragma unroll
-          for (int x = 0; x < 2; ++x) sum[m0 + x] += acc[x];
+          for (int t = 0; t < 4; ++t)
+            if (4 * t < cnt)  // uniform: else no prefix of this step
+              acc = mfma_split(split_from<PL2>(L + (mt * 32 + l32) * TS + 16 * t + 8 * half), y[t], acc);
+          if (recheck(acc)) {
+            acc = TT_ZERO16;
+            for (int k = half; k < 4 * cnt; k += 2)
+              acc = mfma32(g1[(size_t)i1_of[k / 4] * S1 + (k % 4) * R + mt * 32 + l32],
+                           dPsum[(size_t)q_of[k / 4] * PN + (k % 4) * W + col], acc);
+          }
+          sum[mt] += acc;
         }
         if (c + 1 == c1 || next.x != bin) {  // the group or the slice ends here
           float* dst = part2 + (size_t)first * S2;
@@ -326,27 +415,23 @@ __global__ __launch_bounds__(kMThreads, R >= 128 ? 2 : 3) void k_prefix_bwd_wide
         desc = next;
       }
     } else {
-      constexpr int NT = R / 32, MW = NT >= 4 ? 2 : 1;  // row tiles of a wavefront
-      // the thread number anew: nothing derived from it here is kept in registers across the dG2 units
-      int tid = threadIdx.x;
-      asm volatile("" : "+v"(tid));
-      const int w = tid / kWave, half = tid % kWave / 32, l32 = tid % 32;
-      const int c = unit - units2;
+      const int c = c0 + sub - UN;
+      if (c >= c1) continue;  // uniform for the block
+      constexpr int NT = R / 32, MW = NT >= 4 ? 2 : 1;  // tiles of 32 lines of a wavefront
       const int4 desc = c2_desc[c];
       const int cnt = desc.z;
       chunk_records(c, cnt);
       const float* Bm = g2 + (size_t)desc.x * S2;
       const int nt = w % NT, mt0 = w / NT;
-      float *La = L, *Lb = L + 64 * KS;
-      f4 ra[4], rb[R / 16];
+      f4 ra[2], rb[R / 32];
       auto fetch = [&](int k0) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < 2; ++i) {
           const int e = tid + i * kMThreads, r = e / (KD / 4), k = e % (KD / 4) * 4;
-          ra[i] = *(const f4*)(dPsum + (size_t)wave_value(q_of[r / 4]) * PN + (r % 4) * W + k0 + k);
+          ra[i] = *(const f4*)(dPsum + (size_t)q_of[r / 4] * PN + (r % 4) * W + k0 + k);
         }
 #pragma unroll
-        for (int i = 0; i < R / 16; ++i) {
+        for (int i = 0; i < R / 32; ++i) {
           const int e = tid + i * kMThreads, r = e / (KD / 4), k = e % (KD / 4) * 4;
           rb[i] = *(const f4*)(Bm + (size_t)r * W + k0 + k);
         }
@@ -358,42 +443,45 @@ __global__ __launch_bounds__(kMThreads, R >= 128 ? 2 : 3) void k_prefix_bwd_wide
 #pragma unroll 1
       for (int k0 = 0; k0 < W; k0 += KD) {
         if (k0 > 0) __syncthreads();
+        auto put = [&](int line, int e, f4 v) {
+          const Split<h4> x = split_four(v);
+          __bf16* to = L + (line + e / (KD / 4)) * KS + e % (KD / 4) * 4;
+          *(h4*)to = x.hi;
+          *(h4*)(to + PL1) = x.mid;
+          *(h4*)(to + 2 * PL1) = x.lo;
+        };
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int e = tid + i * kMThreads;
-          *(f4*)&La[e / (KD / 4) * KS + e % (KD / 4) * 4] = ra[i];
-        }
+        for (int i = 0; i < 2; ++i) put(0, tid + i * kMThreads, ra[i]);
 #pragma unroll
-        for (int i = 0; i < R / 16; ++i) {
-          const int e = tid + i * kMThreads;
-          *(f4*)&Lb[e / (KD / 4) * KS + e % (KD / 4) * 4] = rb[i];
-        }
+        for (int i = 0; i < R / 32; ++i) put(64, tid + i * kMThreads, rb[i]);
         __syncthreads();
         if (k0 + KD < W) fetch(k0 + KD);  // in flight while this step is multiplied
         TT_LOADS_DONE();
-        const f4* br = (const f4*)&Lb[(nt * 32 + l32) * KS + 32 * half];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const f4 y = br[j];
+        for (int t = 0; t < KD / 16; ++t) {
+          const Split<h8> y = split_from<PL1>(L + (64 + nt * 32 + l32) * KS + 16 * t + 8 * half);
 #pragma unroll
-          for (int x = 0; x < MW; ++x) {
-            const int mt = mt0 + x;
-            const f4 a = ((const f4*)&La[(mt * 32 + l32) * KS + 32 * half])[j];
-            acc[x] = mfma32(a.x, y.x, acc[x]);
-            acc[x] = mfma32(a.y, y.y, acc[x]);
-            acc[x] = mfma32(a.z, y.z, acc[x]);
-            acc[x] = mfma32(a.w, y.w, acc[x]);
-          }
+          for (int x = 0; x < MW; ++x)
+            acc[x] = mfma_split(split_from<PL1>(L + ((mt0 + x) * 32 + l32) * KS + 16 * t + 8 * half), y, acc[x]);
         }
       }
 #pragma unroll
-      for (int x = 0; x < MW; ++x)
+      for (int x = 0; x < MW; ++x) {
+        const int mt = mt0 + x;
+        if (mt * 8 < cnt && recheck(acc[x])) {
+          const float* ar = dPsum + (size_t)q_of[mt * 8 + l32 / 4] * PN + (l32 % 4) * W + half * (W / 2);
+          const float* br = Bm + (size_t)(nt * 32 + l32) * W + half * (W / 2);
+          acc[x] = TT_ZERO16;
+#pragma unroll 4
+          for (int j = 0; j < W / 2; ++j) acc[x] = mfma32(ar[j], br[j], acc[x]);
+        }
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          const int ql = (mt0 + x) * 8 + 2 * (v / 4) + half;
+          const int ql = mt * 8 + 2 * (v / 4) + half;
           if (ql < cnt)
             dg1part[(size_t)q_of[ql] * S1 + (v % 4) * R + nt * 32 + l32] = acc[x][v];
         }
+      }
     }
   }
 }
