@@ -304,7 +304,12 @@ __global__ __launch_bounds__(kMThreads, 3) void k_prefix_fwd_wide(
 //         chunks another (all in one chain, the error of dG2 was 2.1 times as large at 200,000 uniform
 //         ids of rank 64).
 //   dG1   a chunk: dg1part[q] = dPsum_q Bm^T, 64 x R with 4R to contract, 32 at a time through LDS.
-// The units of a group follow each other, dG2 first: dPsum is then read again while it is near.
+// The units of a group follow each other, dG2 first: dPsum is then read again while it is near (rank 64,
+// 500,000 uniform ids: all dG2 units first 530 us, so 510).  Measured with fp32 instructions before / bf16
+// parts now: rank 128, 500,000 ids of (480,500,500) x (8,4,4), uniform 4440 / 3420 us, Zipf 970 / 700; rank
+// 64, (480,480,482) x (4,4,8), uniform 563 / 456, Zipf 145 / 121.  The matrix cores are busy a third of the
+// time; neither loads a chunk ahead nor two chunks side by side changed it: what remains is dPsum, read
+// twice in pieces of 128 bytes to 2 KiB.
 template <int R>
 __global__ __launch_bounds__(kMThreads, 2) void k_prefix_bwd_wide(
     const float* __restrict__ g1, const float* __restrict__ g2, const float* __restrict__ dPsum,
@@ -343,40 +348,36 @@ __global__ __launch_bounds__(kMThreads, 2) void k_prefix_bwd_wide(
       for (int c = c0; c < c1; ++c) {
         const int cnt = desc.z, bin = desc.x;
         chunk_records(c, cnt);
-        // contraction index k = 4*prefix + j1; of the sixteen of a step half h takes eight: two prefixes.
-        // Prefixes past the count count zero (their G1 lines are cleared) and read the last one's dPsum.
+        // a step contracts four prefixes; half h takes lines 2h and 2h + 1 of each, so that addresses are a
+        // scalar and a lane's offset.  Prefixes past the count count zero (their G1 lines are cleared) and
+        // read the last one's dPsum.
         float b[4][8];
+        const uint32_t bo = 2 * half * W + col;
 #pragma unroll
         for (int t = 0; t < 4; ++t)
 #pragma unroll
-          for (int x = 0; x < 2; ++x) {
-            const float* src = dPsum + (size_t)q_of[4 * t + 2 * half + x] * PN + col;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[t][4 * x + j] = src[j * W];
-          }
+          for (int j = 0; j < 8; ++j)
+            b[t][j] = (dPsum + (size_t)wave_value(q_of[4 * t + j / 2]) * PN + j % 2 * W)[bo];
         const int4 next = c2_desc[min(c + 1, nchunk - 1)];
-        // eight lines of a column a thread, R/32 times
+        // eight lines of a column a thread, R/32 times: those of half k8 % 2 in step k8 / 2
         float a[R / 32][8];
+        const uint32_t ao = tid % R;
 #pragma unroll
         for (int i = 0; i < R / 32; ++i) {
-          const int e = tid + i * kMThreads, m = e % R, k8 = e / R;  // column; eight lines: two prefixes
+          const int k8 = wave_value((tid + i * kMThreads) / R);
 #pragma unroll
-          for (int x = 0; x < 2; ++x) {
-            const bool on = 2 * k8 + x < cnt;
-            const float* src = g1 + (size_t)i1_of[2 * k8 + x] * S1 + m;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              const float v = src[j * R];
-              a[i][4 * x + j] = on ? v : 0.f;
-            }
+          for (int j = 0; j < 8; ++j) {
+            const int t = k8 / 2 * 4 + j / 2;
+            const float v = (g1 + (size_t)wave_value(i1_of[t]) * S1 + (k8 % 2 * 2 + j % 2) * R)[ao];
+            a[i][j] = t < cnt ? v : 0.f;
           }
         }
         TT_LOADS_DONE();
 #pragma unroll
         for (int i = 0; i < R / 32; ++i) {
-          const int e = tid + i * kMThreads, m = e % R, k8 = e / R;
+          const int k8 = wave_value((tid + i * kMThreads) / R);
           const Split<h8> x = split_eight(a[i]);
-          __bf16* to = L + m * TS + k8 * 8;
+          __bf16* to = L + tid % R * TS + k8 * 8;
           *(h8*)to = x.hi;
           *(h8*)(to + PL2) = x.mid;
           *(h8*)(to + 2 * PL2) = x.lo;
@@ -418,6 +419,10 @@ __global__ __launch_bounds__(kMThreads, 2) void k_prefix_bwd_wide(
       const int c = c0 + sub - UN;
       if (c >= c1) continue;  // uniform for the block
       constexpr int NT = R / 32, MW = NT >= 4 ? 2 : 1;  // tiles of 32 lines of a wavefront
+      // the thread number anew: nothing derived from it here is kept in registers across the dG2 units
+      int tid = threadIdx.x;
+      asm volatile("" : "+v"(tid));
+      const int w = tid / kWave, half = tid % kWave / 32, l32 = tid % 32;
       const int4 desc = c2_desc[c];
       const int cnt = desc.z;
       chunk_records(c, cnt);
