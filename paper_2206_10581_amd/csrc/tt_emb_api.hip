@@ -165,7 +165,7 @@ static int make_plan(const tt_emb_config* c, Plan* pl) {
   pl->maxB = maxB;
   pl->maxQ = std::min<int64_t>(maxB, n12);
   pl->sortBlocksMax = (int)sort_blocks_most(pl->maxB);
-  pl->segBlocksMax = (int)cdiv64(pl->maxB, kSegItems);
+  pl->segBlocksMax = (int)cdiv64(pl->maxB, 4 * kSegThreads);
   pl->uBlocksMax = (int)group_blocks_most(s, pl->maxB, pl->maxB);
   pl->qBlocksMax = (int)group_blocks_most(s, pl->maxQ, pl->maxB);
   pl->tilesMax = (int)cdiv64(pl->maxB, kTileSlots);

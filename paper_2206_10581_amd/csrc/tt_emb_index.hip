@@ -414,22 +414,24 @@ __global__ __launch_bounds__(kScanThreads) void k_sort_colscan(uint32_t* __restr
 // ---------------------------------------------------------------------------------------------
 // Segment discovery over the sorted keys
 
+template <int ITEMS>
 struct SegFlags {
-  uint32_t key[4], prev[4];
-  bool valid[4], newu[4], newq[4], last_valid[4], single[4], split[4];
+  uint32_t key[ITEMS], prev[ITEMS];
+  bool valid[ITEMS], newu[ITEMS], newq[ITEMS], last_valid[ITEMS], single[ITEMS], split[ITEMS];
 };
 
-__device__ __forceinline__ SegFlags seg_flags(const uint32_t* __restrict__ skey, int B, uint32_t N,
-                                              uint32_t n3, int s0) {
-  SegFlags f;
-  uint32_t k[6];  // keys of slots s0-1 .. s0+4
+template <int ITEMS>
+__device__ __forceinline__ SegFlags<ITEMS> seg_flags(const uint32_t* __restrict__ skey, int B, uint32_t N,
+                                                     uint32_t n3, int s0) {
+  SegFlags<ITEMS> f;
+  uint32_t k[ITEMS + 2];  // keys of slots s0-1 .. s0+ITEMS
 #pragma unroll
-  for (int j = 0; j < 6; ++j) {
+  for (int j = 0; j < ITEMS + 2; ++j) {
     const int s = s0 - 1 + j;
     k[j] = (s >= 0 && s < B) ? skey[s] : 0xffffffffu;
   }
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < ITEMS; ++j) {
     const int s = s0 + j;
     const uint32_t key = k[j + 1], prev = k[j], next = k[j + 2];
     f.key[j] = key;
@@ -448,15 +450,17 @@ __device__ __forceinline__ SegFlags seg_flags(const uint32_t* __restrict__ skey,
   return f;
 }
 
+template <int ITEMS>
 __global__ __launch_bounds__(kSegThreads) void k_seg_count(const uint32_t* __restrict__ skey, int B,
                                                            uint32_t N, uint32_t n3,
                                                            uint32_t* __restrict__ seg_nu,
                                                            uint32_t* __restrict__ seg_nq) {
   __shared__ uint32_t lds4[kSegThreads / kWave];
-  const SegFlags f = seg_flags(skey, B, N, n3, (int)blockIdx.x * kSegItems + (int)threadIdx.x * 4);
+  const SegFlags<ITEMS> f =
+      seg_flags<ITEMS>(skey, B, N, n3, ((int)blockIdx.x * kSegThreads + (int)threadIdx.x) * ITEMS);
   uint32_t cu = 0, cq = 0;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < ITEMS; ++j) {
     cu += f.newu[j];
     cq += f.newq[j];
   }
@@ -473,6 +477,7 @@ __global__ __launch_bounds__(kSegThreads) void k_seg_count(const uint32_t* __res
 // counts them per (group_span, i3) resp. (group_span, i2) for the blocks of the grouping pass and per i1.
 // u_code[u] says where the gradient row of unique id u will be found: >= 0 is the batch position
 // of its only occurrence, -(u+1) means "row u of the per-id sums".
+template <int ITEMS>
 __global__ __launch_bounds__(kSegThreads) void k_seg_write(
     const uint32_t* __restrict__ skey, const uint32_t* __restrict__ perm, int B, int group_span,
     Shape sh, const uint32_t* __restrict__ seg_nu, const uint32_t* __restrict__ seg_nq, int* __restrict__ s_u,
@@ -482,11 +487,11 @@ __global__ __launch_bounds__(kSegThreads) void k_seg_write(
     int* __restrict__ g1_end, Counters* __restrict__ ctr) {
   __shared__ uint32_t lds4[kSegThreads / kWave];
   const int tid = threadIdx.x, blk = blockIdx.x;
-  const int s0 = blk * kSegItems + tid * 4;
-  const SegFlags f = seg_flags(skey, B, sh.N, sh.n3, s0);
-  uint32_t bpos[4];
+  const int s0 = (blk * kSegThreads + tid) * ITEMS;
+  const SegFlags<ITEMS> f = seg_flags<ITEMS>(skey, B, sh.N, sh.n3, s0);
+  uint32_t bpos[ITEMS];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) bpos[j] = (s0 + j < B) ? perm[s0 + j] : 0u;
+  for (int j = 0; j < ITEMS; ++j) bpos[j] = (s0 + j < B) ? perm[s0 + j] : 0u;
   uint32_t pu = 0, pq = 0;
   for (int b2 = tid; b2 < blk; b2 += kSegThreads) {
     pu += seg_nu[b2];
@@ -498,7 +503,7 @@ __global__ __launch_bounds__(kSegThreads) void k_seg_write(
 
   uint32_t cu = 0, cq = 0;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < ITEMS; ++j) {
     cu += f.newu[j];
     cq += f.newq[j];
   }
@@ -513,7 +518,7 @@ __global__ __launch_bounds__(kSegThreads) void k_seg_write(
     q_us[0] = 0;
   }
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < ITEMS; ++j) {
     const int s = s0 + j;
     if (s >= B) break;
     if (!f.valid[j]) {
@@ -744,17 +749,36 @@ void launch_count_keys(const Workspace& ws, const SortKeys& sk, int i3_bits, int
   k_count_keys<<<1, 1024, 0, st>>>(ws.key[sk.sorted()], B, sk.sentinel, i3_bits, ws.ctr);
 }
 
+// The blocks' counts: those of fine blocks lie in the digit totals of the sort, which is over, so that the
+// need of a batch does not depend on the block size.
+struct SegCounts {
+  uint32_t *nu, *nq;
+};
+static SegCounts seg_counts(const Workspace& ws, int items) {
+  static_assert(kSegFine / kSegThreads <= kMaxBins / 2, "two rows of counts fit the totals");
+  return items == kSegThreads ? SegCounts{ws.tot, ws.tot + kMaxBins / 2} : SegCounts{ws.seg_nu, ws.seg_nq};
+}
+
 void launch_seg_count(const Plan& pl, const Workspace& ws, int B, hipStream_t st) {
   const uint32_t* skey = ws.key[pl.keys.sorted()];
-  k_seg_count<<<cdiv(B, kSegItems), kSegThreads, 0, st>>>(skey, B, pl.sh.N, pl.sh.n3, ws.seg_nu,
-                                                         ws.seg_nq);
+  const int items = seg_items(B);
+  const SegCounts n = seg_counts(ws, items);
+  auto launch = [&](auto kernel) {
+    kernel<<<cdiv(B, items), kSegThreads, 0, st>>>(skey, B, pl.sh.N, pl.sh.n3, n.nu, n.nq);
+  };
+  items == kSegThreads ? launch(k_seg_count<1>) : launch(k_seg_count<4>);
 }
 
 void launch_seg_write(const Plan& pl, const Workspace& ws, int B, hipStream_t st) {
-  const int f = pl.keys.sorted();
-  k_seg_write<<<cdiv(B, kSegItems), kSegThreads, 0, st>>>(
-      ws.key[f], ws.val[f], B, sort_items(group_threads(pl.sh, B)), pl.sh, ws.seg_nu, ws.seg_nq, ws.s_u, ws.s_rec, ws.u_rs, ws.u_i3, ws.u_q,
-      ws.u_code, ws.q_us, ws.q_i1, ws.q_i2, ws.cnt3, ws.cnt2, ws.g1_first, ws.g1_end, ws.ctr);
+  const int f = pl.keys.sorted(), items = seg_items(B);
+  const SegCounts n = seg_counts(ws, items);
+  auto launch = [&](auto kernel) {
+    kernel<<<cdiv(B, items), kSegThreads, 0, st>>>(
+        ws.key[f], ws.val[f], B, sort_items(group_threads(pl.sh, B)), pl.sh, n.nu, n.nq, ws.s_u,
+        ws.s_rec, ws.u_rs, ws.u_i3, ws.u_q, ws.u_code, ws.q_us, ws.q_i1, ws.q_i2, ws.cnt3, ws.cnt2, ws.g1_first,
+        ws.g1_end, ws.ctr);
+  };
+  items == kSegThreads ? launch(k_seg_write<1>) : launch(k_seg_write<4>);
 }
 
 // which: 0 = both groupings and the chunk schedule; 1 = both groupings, no schedule (c3_order is

@@ -56,11 +56,18 @@ constexpr int kMaxBins = 2048;                            // digit / bucket coun
 // slots, and each piece ("entry") is carried through the backward pass like an id of its own - all
 // gradient steps are linear in the row gradient, so the pieces of an id simply add up in the same
 // matrix-core accumulations that add up the ids of a prefix or of an i3 group.  A block of the
-// gradient-sum kernel owns kEntrySlots slots, so no sum ever crosses a block.
+// gradient-sum kernel owns kEntrySlots slots, so no sum ever crosses a block.  (Pieces of 256 shorten
+// that kernel, 21 -> 18 us at 200,000 Zipf ids, but the hot prefix's pieces queue up behind each other in
+// the next one, 50 -> 88.)
 constexpr int kEntrySlots = 1024;
 
 constexpr int kSegThreads = 256;
-constexpr int kSegItems = 1024;  // sorted slots per block in the segment kernels (4 per thread)
+// Sorted slots of a block in the segment kernels.  Their time is the atomics of the new ids (one or two a
+// slot), which wait on each other inside a compute unit: blocks of 256 slots put them on four times as many
+// units, 7.1 -> 5.2 us at 50,000 uniform ids, 6.6 -> 4.3 at 100,000, 9.2 -> 7.6 at 262,144.  Beyond that
+// blocks of 1024 cover the chip, and every block adds up the counts of the blocks before it.
+constexpr int kSegFine = 1 << 18;
+inline int seg_items(int64_t B) { return B <= kSegFine ? kSegThreads : 4 * kSegThreads; }
 
 constexpr int kTileSlots = 32;   // sorted slots per wavefront tile in the row kernels
 constexpr int kChunk2 = 16;      // unique prefixes per partial sum of a G2 slice gradient

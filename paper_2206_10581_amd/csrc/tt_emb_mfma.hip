@@ -1077,9 +1077,15 @@ __global__ __launch_bounds__(kMThreads) void k_row_fwd_mfma(
 // kernels read their row from grad_out directly.  Pieces of runs that cross wavefronts are joined
 // in LDS.  No run crosses a block: the index pipeline cuts long runs of one id into entries at
 // every multiple of kEntrySlots slots, which is the block size here.
+// A wavefront with at most kSparseSlots slots to load goes from one of them to the next instead of
+// looking at all 64: with uniform ids the looking was the time (24 -> 4.5 us at 500,000 ids of 111 million
+// rows, 12.8 -> 5.7 at 200,000 of 2.4 million, 13 -> 8.4 at 50,000 of 169,343).  Above that the walk over
+// all slots is as fast or faster (Zipf ids: 20.5 / 44 us at 200,000 / 500,000 either way, and 21.5 / 45
+// where every wavefront with a slot left out took the other path).
 constexpr int kGsumWaves = 16;
 constexpr int kGsumThreads = kGsumWaves * kWave;
 constexpr int kGsumBlockSlots = kGsumWaves * kWave;  // 1024
+constexpr int kSparseSlots = 48;
 static_assert(kGsumBlockSlots == kEntrySlots, "a block must own exactly one entry span");
 
 template <int VPL>
@@ -1087,9 +1093,9 @@ struct LaneVec {
   float v[VPL];
 };
 
-// RAGGED: rows of Drt <= 64*VPL floats (any length); lanes past the end of a row carry zeros, and
-// rows are read with plain dword loads (their starts need not be 8-byte aligned).
-template <int VPL, bool RAGGED = false>
+// RAGGED: rows of Drt <= 64*VPL floats (any length), read with plain dword loads (their starts need not
+// be 8-byte aligned).
+template <int VPL, bool RAGGED>
 __global__ __launch_bounds__(kGsumThreads) void k_gsum_block(int B, int Drt,
                                                           const float* __restrict__ grad,
                                                           const int* __restrict__ s_u,
@@ -1146,46 +1152,92 @@ __global__ __launch_bounds__(kGsumThreads) void k_gsum_block(int B, int Drt,
         }
       }
     };
-    for (int half = 0; half < kWave / kRows; ++half) {
-      if (half * kRows >= nv) break;
-      LaneVec<VPL> r[kRows];
+    if (__popcll(need_mask) <= kSparseSlots) {
+      // the slots there are, in order; of a round with fewer the last one is read again and not added
+      unsigned long long left = need_mask;
+      int end = 0;
+      auto round = [&](auto rows) {
+        constexpr int ROWS = decltype(rows)::value;
+        LaneVec<VPL> r[ROWS];
+        int slot[ROWS];
+        const int n = min(__popcll(left), ROWS);
 #pragma unroll
-      for (int k = 0; k < kRows; ++k) {
-        const int slot = half * kRows + k;
-        const uint32_t b_row = (uint32_t)lane_value((int)myb, slot);
-        if ((need_mask >> slot) & 1ull) {
+        for (int k = 0; k < ROWS; ++k) {
+          slot[k] = __ffsll((long long)left) - 1;
+          if (k + 1 < n) left &= left - 1;
+          const uint32_t b_row = (uint32_t)lane_value((int)myb, slot[k]);
           if constexpr (RAGGED) {
 #pragma unroll
-            for (int x = 0; x < VPL; ++x)
-              r[k].v[x] = lane * VPL + x < D
-                              ? __builtin_nontemporal_load(grad + (size_t)b_row * D + lane * VPL + x)
-                              : 0.f;
+            for (int x = 0; x < VPL; ++x)  // lanes past the row's end read its last float; nothing stores them
+              r[k].v[x] = __builtin_nontemporal_load(grad + (size_t)b_row * D + min(lane * VPL + x, D - 1));
           } else {
             stream_load<VPL>(grad + (size_t)b_row * D + lane * VPL, r[k].v);
           }
-        } else {
-#pragma unroll
-          for (int x = 0; x < VPL; ++x) r[k].v[x] = 0.f;
         }
-      }
 #pragma unroll
-      for (int k = 0; k < kRows; ++k) {
-        const int slot = half * kRows + k;
-        if (slot < nv) {
-          const int u = lane_value(mysu, slot);
-          if (u != cur) {
-            flush(slot);
-            cur = u;
-            cur_first = slot;
+        for (int k = 0; k < ROWS; ++k)
+          if (k < n) {  // uniform
+            const int u = lane_value(mysu, slot[k]);
+            if (u != cur) {
+              flush(end);
+              cur = u;
+              cur_first = slot[k];
 #pragma unroll
-            for (int x = 0; x < VPL; ++x) acc.v[x] = 0.f;
+              for (int x = 0; x < VPL; ++x) acc.v[x] = 0.f;
+            }
+            end = slot[k] + 1;
+#pragma unroll
+            for (int x = 0; x < VPL; ++x) acc.v[x] += r[k].v[x];
           }
+        left &= left - 1;
+      };
+      while (left) {
+        if (__popcll(left) > 8) round(std::integral_constant<int, 16>{});
+        else round(std::integral_constant<int, 8>{});
+      }
+      flush(end);
+    } else {
+      for (int half = 0; half < kWave / kRows; ++half) {
+        if (half * kRows >= nv) break;
+        LaneVec<VPL> r[kRows];
 #pragma unroll
-          for (int x = 0; x < VPL; ++x) acc.v[x] += r[k].v[x];
+        for (int k = 0; k < kRows; ++k) {
+          const int slot = half * kRows + k;
+          const uint32_t b_row = (uint32_t)lane_value((int)myb, slot);
+          if ((need_mask >> slot) & 1ull) {
+            if constexpr (RAGGED) {
+#pragma unroll
+              for (int x = 0; x < VPL; ++x)
+                r[k].v[x] = lane * VPL + x < D
+                                ? __builtin_nontemporal_load(grad + (size_t)b_row * D + lane * VPL + x)
+                                : 0.f;
+            } else {
+              stream_load<VPL>(grad + (size_t)b_row * D + lane * VPL, r[k].v);
+            }
+          } else {
+#pragma unroll
+            for (int x = 0; x < VPL; ++x) r[k].v[x] = 0.f;
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < kRows; ++k) {
+          const int slot = half * kRows + k;
+          if (slot < nv) {
+            const int u = lane_value(mysu, slot);
+            if (u != cur) {
+              flush(slot);
+              cur = u;
+              cur_first = slot;
+#pragma unroll
+              for (int x = 0; x < VPL; ++x) acc.v[x] = 0.f;
+            }
+#pragma unroll
+            for (int x = 0; x < VPL; ++x) acc.v[x] += r[k].v[x];
+          }
         }
       }
+      flush(nv);
     }
-    flush(nv);
     __syncthreads();
     // join the pieces inside the block, in wave order
     // (a) the run that begins in this wave's tail
@@ -1361,16 +1413,14 @@ void launch_gsum_block(const Plan& pl, const Workspace& ws, const float* grad, i
   const int grid = grid_cap(cdivi(B, kGsumBlockSlots), kMGridCap);
   const uint32_t* perm = ws.val[pl.keys.sorted()];
   const int D = pl.sh.D;
-  if (D == 64)
-    k_gsum_block<1><<<grid, kGsumThreads, 0, st>>>(B, D, grad, ws.s_u, perm, ws.gsum, ws.ctr);
-  else if (D == 128)
-    k_gsum_block<2><<<grid, kGsumThreads, 0, st>>>(B, D, grad, ws.s_u, perm, ws.gsum, ws.ctr);
-  else if (D <= 64)
-    k_gsum_block<1, true><<<grid, kGsumThreads, 0, st>>>(B, D, grad, ws.s_u, perm, ws.gsum, ws.ctr);
-  else if (D <= 128)
-    k_gsum_block<2, true><<<grid, kGsumThreads, 0, st>>>(B, D, grad, ws.s_u, perm, ws.gsum, ws.ctr);
-  else
-    k_gsum_block<4, true><<<grid, kGsumThreads, 0, st>>>(B, D, grad, ws.s_u, perm, ws.gsum, ws.ctr);
+  auto launch = [&](auto kernel) {
+    kernel<<<grid, kGsumThreads, 0, st>>>(B, D, grad, ws.s_u, perm, ws.gsum, ws.ctr);
+  };
+  if (D == 64) launch(k_gsum_block<1, false>);
+  else if (D == 128) launch(k_gsum_block<2, false>);
+  else if (D <= 64) launch(k_gsum_block<1, true>);
+  else if (D <= 128) launch(k_gsum_block<2, true>);
+  else launch(k_gsum_block<4, true>);
 }
 
 // rows this long have a block version of the gradient sums (any shape)
