@@ -728,26 +728,32 @@ __global__ __launch_bounds__(kMThreads) void k_id_bwd_mfma(
 
 // ---------------------------------------------------------------------------------------------
 // Ranks up to 32: the whole middle of the backward pass in one launch, without dPsum ever leaving
-// the chip.  A block of eight wavefronts owns one by-i2 chunk (<= 16 prefixes q, Bm = G2[i2]):
-//   (i)   dPsum_q = sum over the ids u of q of g_u G3[i3(u)]^T, each wavefront two prefixes, four
-//         ids of each in flight together; results go to an LDS tile of 64 rows
-//         (row = 4*prefix + j1) by 4R columns, Bm sits in LDS beside it
+// the chip.  A block owns one by-i2 chunk (<= 16 prefixes q, Bm = G2[i2]):
+//   (i)   dPsum_q = sum over the ids u of q of g_u G3[i3(u)]^T; results go to an LDS tile of 64 rows
+//         (row = 4*prefix + j1) by 4R columns, Bm is put into LDS beside it
 //   (ii)  wavefronts 0..3: dg1part[q] = dPsum_q Bm^T for four prefixes each (operands from LDS)
-//   (iii) wavefronts 4..7: 32 columns each of part2[c] = sum_q G1[i1(q)]^T dPsum_q
+//   (iii) other wavefronts: 32 columns each of part2[c] = sum_q G1[i1(q)]^T dPsum_q
 // Blocks past the chunk range take the by-i3 chunks of the G3 gradient (dg3_role), one per
 // wavefront; that step only needs the per-id gradient sums and the cached prefix products, so
 // both run side by side.
-// Rank 16 needs half the LDS, so its blocks have four wavefronts and twice as many fit a compute
-// unit: in (i) each takes four prefixes, two ids of each in flight together (the same eight id
-// slots per round; tables with many prefixes and few ids per prefix are what these ranks meet, and
-// one pass over four prefixes has half the dependent round trips of two passes over two), then
-// (ii), then wavefronts 0 and 1 take (iii).
-template <int R>
-constexpr int mid_waves() { return R >= 32 ? 8 : 4; }
+//
+// (i) is bound by round trips to memory: a wavefront takes 16 / WAVES prefixes, SO ids in flight, and its
+// longest prefix sets the time.  With skewed ids one prefix of a chunk has hundreds of ids and the others a
+// few, so the long ones are taken first by the whole block, one after the other, WAVES * SC ids in flight;
+// the wavefronts' sums meet in LDS and are added in their order.  Which are long is the choice that takes
+// the fewest rounds.  With every prefix left to its wavefront the kernel took, Zipf / clustered ids:
+// 182 / 198 us at 500,000 ids of n = (480,480,482), d = (4,4,8), rank 16, now 55 / 113; 29 / 36 at 50,000 of
+// (55,55,56) x (8,4,4), rank 16, now 19 / 27; 50 / 77 at 200,000 of (136,136,136) x (4,4,8), rank 32, now
+// 39 / 79.  Uniform ids: 242 -> 243, 27.6 -> 25, 113 -> 113.
+//
+// WAVES: eight.  Four at ranks up to 16 where the batch has fewer than four ids per prefix of the table: a
+// round then is mostly one or two ids a prefix, and two blocks of four hold twice the prefixes (uniform ids
+// of (480,480,482), eight / four wavefronts: 268 / 243 us at 500,000 ids and d = (4,4,8), 170 / 137 at 300,000
+// and (4,4,4); with 37 ids a prefix, n = (40,40,500), 27 / 33).
 constexpr int kXcds = 8;
 
-template <int R, int D3>
-__global__ __launch_bounds__(mid_waves<R>() * kWave, 6) void k_bwd_mid_mfma(
+template <int R, int D3, int WAVES>
+__global__ __launch_bounds__(WAVES * kWave, 6) void k_bwd_mid_mfma(
     const float* __restrict__ g1, const float* __restrict__ g2, const float* __restrict__ g3,
     const float* __restrict__ P, const float* __restrict__ grad, const float* __restrict__ gsum,
     const int* __restrict__ u_code, const int* __restrict__ u_i3, const int4* __restrict__ c2_item,
@@ -759,10 +765,9 @@ __global__ __launch_bounds__(mid_waves<R>() * kWave, 6) void k_bwd_mid_mfma(
   constexpr int W = 4 * R, S1 = 4 * R, S2 = R * W, S3 = R * D3, D = 16 * D3;
   constexpr int TS = W + 4;  // padded row stride of the LDS tiles (keeps 16-byte alignment)
   constexpr int NT16 = (R + 15) / 16, KS = D3 / 4;
+  constexpr int kMidThreads = WAVES * kWave, kParts = WAVES * NT16 * 256;
   __shared__ __align__(16) float T[64 * TS];
-  __shared__ __align__(16) float Bl[R * TS];
-  __shared__ int q_of[16], i1_of[16], u0_of[16], u1_of[16];
-  constexpr int kMidWaves = mid_waves<R>(), kMidThreads = kMidWaves * kWave;
+  __shared__ __align__(16) float Bl[R * TS > kParts ? R * TS : kParts];  // wavefronts' sums of a long prefix, then Bm
   const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
   // Blocks past the by-i2 chunk range take the by-i3 chunks, one per wavefront, in the order of
   // the chunks' first prefixes.  Workgroups go to the eight XCDs round robin, so XCD x takes the
@@ -770,75 +775,152 @@ __global__ __launch_bounds__(mid_waves<R>() * kWave, 6) void k_bwd_mid_mfma(
   // were then just read by its neighbours through the same L2.
   if ((int)blockIdx.x >= chunk_blocks) {
     const int rel = (int)blockIdx.x - chunk_blocks, xcd = (int)blockIdx.x % kXcds;
-    const int per_xcd = ((int)gridDim.x - chunk_blocks) / kXcds * kMidWaves;
+    const int per_xcd = ((int)gridDim.x - chunk_blocks) / kXcds * WAVES;
     const int n = ctr->nchunk3;
     const int lo = (int)((long long)n * xcd / kXcds), hi = (int)((long long)n * (xcd + 1) / kXcds);
-    for (int i = lo + rel / kXcds * kMidWaves + w; i < hi; i += per_xcd)
+    for (int i = lo + rel / kXcds * WAVES + w; i < hi; i += per_xcd)
       dg3_chunk<R, D3, 4>(c3_order ? c3_order[i] : i, P, grad, gsum, c3_item, c3_desc, part3);
     return;
   }
   // records, descriptor and chunk count are read together (the grid never exceeds the tables)
   const int c = blockIdx.x;
-  const int4 item = c2_item[(size_t)c * kChunk2 + tid % kChunk2];
+  const int l16 = lane % 16, kg = lane / 16;
+  int4 item = c2_item[(size_t)c * kChunk2 + l16];
   const int4 desc = c2_desc[c];
   if (c >= ctr->nchunk2) return;
-  const int bin = desc.x, cnt = desc.z;
-  const float* Bm = g2 + (size_t)bin * S2;
-  if (tid < 16) {
-    const bool on = tid < cnt;  // records past the chunk's count are unwritten
-    q_of[tid] = on ? item.x : -1;
-    i1_of[tid] = on ? item.y : 0;
-    u0_of[tid] = on ? item.z : 0;
-    u1_of[tid] = on ? item.w : 0;
-  }
-  for (int i = tid; i < R * W / 4; i += kMidThreads) {
-    const f4 v = ((const f4*)Bm)[i];
-    *(f4*)&Bl[((i * 4) / W) * TS + (i * 4) % W] = v;
-  }
-  __syncthreads();
-
-  const int l16 = lane % 16, kg = lane / 16;
+  if (l16 >= desc.z) item = int4{-1, 0, 0, 0};  // records past the chunk's count are unwritten
+  // Bm is needed behind the barrier only: below rank 32 its words wait in registers, at rank 32 they are
+  // loaded behind (i), where registers are free
+  const f4* Bm = (const f4*)(g2 + (size_t)desc.x * S2);
+  constexpr int NB = (R * W / 4 + kMidThreads - 1) / kMidThreads;
+  f4 bm[NB];
+  auto load_bm = [&] {
+#pragma unroll
+    for (int k = 0; k < NB; ++k) bm[k] = Bm[min(tid + k * kMidThreads, R * W / 4 - 1)];
+  };
+  if constexpr (R < 32) load_bm();
   // rank 8: rows / columns 8..15 of the only 16-wide tile do not exist; such lanes read row 0 and
   // their results are dropped
   const bool rank_on = R >= 16 || l16 < R;
   const int lrow = rank_on ? l16 : 0;
-  // (i) this wavefront's G prefixes (local numbers G*w .. G*w+G-1; two with eight wavefronts, four
-  // with four) in one pass: eight id slots per round, 8/G ids of each prefix.  Lanes 0..7 hold the
-  // round's slots: prefix g = lane / UB of the wavefront, id r*UB + lane % UB of its list.
+  // (i): SC ids of a long prefix in flight together, SO of the others (what 80 registers hold; eight
+  // wavefronts of two prefixes take two ids of each where rows are 128 floats).  Lane x holds where the
+  // gradient row and the G3 slice of the round's id x are.
+  constexpr int SC = R <= 16 && KS == 1 ? 16 : 8, SO = WAVES == 4 || R == 32 || KS == 1 ? 8 : 4;
+  constexpr bool kAhead = R < 32 || KS == 1;  // registers for the next round's codes
+  auto load_ids = [&](int mycode, int myi3, auto& a, auto& b) {
+#pragma unroll
+    for (int sl = 0; sl < (int)(sizeof(a) / sizeof(a[0])); ++sl) {
+      const float* gp = grad_row_ptr(lane_value(mycode, sl), grad, gsum, D) + l16 * D3 + KS * kg;
+      const float* cp = g3 + (size_t)lane_value(myi3, sl) * S3 + lrow * D3 + KS * kg;
+#pragma unroll
+      for (int k = 0; k < KS; ++k) a[sl][k] = gp[k];
+#pragma unroll
+      for (int nt = 0; nt < NT16; ++nt)
+#pragma unroll
+        for (int k = 0; k < KS; ++k) b[sl][nt][k] = cp[nt * 16 * D3 + k];
+    }
+    TT_LOADS_DONE();
+  };
+  // accumulator element v of lane (kg, l16) is dPsum_q[m = 4*kg + v][n = nt*16 + l16], i.e. row
+  // j1 = kg of the prefix and column j2*R + n with j2 = v
+  auto put_sum = [&](int p, const f4 (&sum)[NT16]) {
+#pragma unroll
+    for (int nt = 0; nt < NT16; ++nt)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (rank_on) T[(p * 4 + kg) * TS + v * R + nt * 16 + l16] = sum[nt][v];
+  };
+  int ids = item.w - item.z;
+  uint32_t longs = 0;  // prefixes taken by the whole block
+  if (__ballot(ids > 16)) {
+    constexpr int UB = SO * WAVES / 16;
+    // rounds in all if the prefixes with more ids than this lane's are long; one stands for the barriers
+    const int mine = (ids + SC * WAVES - 1) / (SC * WAVES) + 1;
+    int cost = (ids + UB - 1) / UB;
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+      if (lane_value(ids, k) > ids) cost += lane_value(mine, k);
+    int least = cost;
+#pragma unroll
+    for (int o = 1; o < 16; o *= 2) least = min(least, __shfl_xor(least, o));
+    const int limit = lane_value(ids, __ffsll((long long)__ballot(cost == least)) - 1);
+    longs = (uint32_t)__ballot(ids > limit) & 0xffffu;
+  }
+  for (uint32_t left = longs; left; left &= left - 1) {
+    const int p = __ffs((int)left) - 1;
+    const int n = lane_value(ids, p), u0 = lane_value(item.z, p);
+    f4 acc[NT16];
+#pragma unroll
+    for (int nt = 0; nt < NT16; ++nt) acc[nt] = f4{0.f, 0.f, 0.f, 0.f};
+    auto id_of = [&](int i0) { return u0 + min(i0 + lane % SC, n - 1); };
+    int mycode = u_code[id_of(w * SC)], myi3 = u_i3[id_of(w * SC)];
+    for (int i0 = w * SC; i0 < n; i0 += WAVES * SC) {
+      const int next = id_of(i0 + WAVES * SC);
+      const int next_code = u_code[next], next_i3 = u_i3[next];
+      float a[SC][KS], b[SC][NT16][KS];
+      load_ids(mycode, myi3, a, b);
+#pragma unroll
+      for (int sl = 0; sl < SC; ++sl)
+        if (i0 + sl < n) {
+#pragma unroll
+          for (int nt = 0; nt < NT16; ++nt)
+#pragma unroll
+            for (int k = 0; k < KS; ++k) acc[nt] = mfma16(a[sl][k], b[sl][nt][k], acc[nt]);
+        }
+      mycode = next_code;
+      myi3 = next_i3;
+    }
+    f4* part = (f4*)Bl;
+#pragma unroll
+    for (int nt = 0; nt < NT16; ++nt) part[(w * NT16 + nt) * kWave + lane] = acc[nt];
+    __syncthreads();
+    if (p % WAVES == w) {
+#pragma unroll
+      for (int nt = 0; nt < NT16; ++nt) {
+        f4 sum = part[nt * kWave + lane];
+#pragma unroll
+        for (int k = 1; k < WAVES; ++k) sum += part[(k * NT16 + nt) * kWave + lane];
+        acc[nt] = sum;
+      }
+      put_sum(p, acc);
+    }
+    __syncthreads();
+  }
   {
-    constexpr int G = 16 / kMidWaves, UB = 8 / G;
+    constexpr int G = 16 / WAVES, UB = SO / G;
+    if ((longs >> l16) & 1) ids = 0;
     f4 acc[G][NT16];
 #pragma unroll
     for (int g = 0; g < G; ++g)
 #pragma unroll
       for (int nt = 0; nt < NT16; ++nt) acc[g][nt] = f4{0.f, 0.f, 0.f, 0.f};
-    int nmax = 0;
+    int most = 0;
 #pragma unroll
-    for (int g = 0; g < G; ++g) nmax = max(nmax, u1_of[G * w + g] - u0_of[G * w + g]);
-    const int myp = G * w + (lane % 8) / UB;  // the prefix of this lane's slot
-    const int myu0 = u0_of[myp], myn = u1_of[myp] - myu0;
-    const int rounds = (nmax + UB - 1) / UB;
+    for (int g = 0; g < G; ++g) most = max(most, lane_value(ids, G * w + g));
+    const int myp = G * w + (lane % SO) / UB;  // the prefix of this lane's slot
+    const int myu0 = __shfl(item.z, myp), myn = __shfl(ids, myp);
+    const int rounds = (most + UB - 1) / UB;
+    // the next round's codes are on their way while this round's rows are
+    auto slot_on = [&](int r) { return r * UB + lane % UB < myn && lane < SO; };
+    auto id_of = [&](int r) { return slot_on(r) ? myu0 + r * UB + lane % UB : 0; };
+    int mycode = 0, myi3 = 0;
+    if (kAhead) {
+      mycode = u_code[id_of(0)];
+      myi3 = u_i3[id_of(0)];
+    }
     for (int r = 0; r < rounds; ++r) {
-      const int si = r * UB + lane % UB;
-      const bool slot_on = lane < 8 && si < myn;
-      const int uu = slot_on ? myu0 + si : 0;
-      const int mycode = u_code[uu], myi3 = u_i3[uu];
-      float a[8][KS], b[8][NT16][KS];
-#pragma unroll
-      for (int sl = 0; sl < 8; ++sl) {
-        const float* gp = grad_row_ptr(lane_value(mycode, sl), grad, gsum, D) + l16 * D3 + KS * kg;
-        const float* cp = g3 + (size_t)lane_value(myi3, sl) * S3 + lrow * D3 + KS * kg;
-#pragma unroll
-        for (int k = 0; k < KS; ++k) a[sl][k] = gp[k];
-#pragma unroll
-        for (int nt = 0; nt < NT16; ++nt)
-#pragma unroll
-          for (int k = 0; k < KS; ++k) b[sl][nt][k] = cp[nt * 16 * D3 + k];
+      const unsigned long long on_mask = __ballot(slot_on(r));
+      const int at = id_of(kAhead ? r + 1 : r);
+      const int next_code = u_code[at], next_i3 = u_i3[at];
+      if (!kAhead) {
+        mycode = next_code;
+        myi3 = next_i3;
       }
-      TT_LOADS_DONE();
-      const unsigned long long on_mask = __ballot(slot_on);
+      float a[SO][KS], b[SO][NT16][KS];
+      load_ids(mycode, myi3, a, b);
 #pragma unroll
-      for (int sl = 0; sl < 8; ++sl) {
+      for (int sl = 0; sl < SO; ++sl) {
         // wavefront-uniform: empty slots cost no matrix-core time
         if ((on_mask >> sl) & 1ull) {
 #pragma unroll
@@ -848,16 +930,20 @@ __global__ __launch_bounds__(mid_waves<R>() * kWave, 6) void k_bwd_mid_mfma(
               acc[sl / UB][nt] = mfma16(a[sl][k], b[sl][nt][k], acc[sl / UB][nt]);
         }
       }
+      if (kAhead) {
+        mycode = next_code;
+        myi3 = next_i3;
+      }
     }
-    // accumulator element v of lane (kg, l16) is dPsum_q[m = 4*kg + v][n = nt*16 + l16], i.e. row
-    // j1 = kg of the prefix and column j2*R + n with j2 = v
+    if constexpr (R >= 32) load_bm();
 #pragma unroll
     for (int g = 0; g < G; ++g)
+      if (!((longs >> (G * w + g)) & 1)) put_sum(G * w + g, acc[g]);
 #pragma unroll
-      for (int nt = 0; nt < NT16; ++nt)
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          if (rank_on) T[((G * w + g) * 4 + kg) * TS + v * R + nt * 16 + l16] = acc[g][nt][v];
+    for (int k = 0; k < NB; ++k) {
+      const int i = tid + k * kMidThreads;
+      if (R * W / 4 % kMidThreads == 0 || i < R * W / 4) *(f4*)&Bl[((i * 4) / W) * TS + (i * 4) % W] = bm[k];
+    }
   }
   __syncthreads();
 
@@ -882,7 +968,7 @@ __global__ __launch_bounds__(mid_waves<R>() * kWave, 6) void k_bwd_mid_mfma(
       }
     }
     // accumulator element v: tile row 4*kg + v = prefix 4w + kg, j1 = v; column n = 16*nt + l16
-    const int qv = q_of[4 * w + kg];
+    const int qv = __shfl(item.x, 4 * w + kg);
     if (qv >= 0) {
 #pragma unroll
       for (int nt = 0; nt < NT16; ++nt)
@@ -891,7 +977,7 @@ __global__ __launch_bounds__(mid_waves<R>() * kWave, 6) void k_bwd_mid_mfma(
           if (rank_on) dg1part[(size_t)qv * S1 + v * R + 16 * nt + l16] = acc[nt][v];
     }
   }
-  const int w3 = kMidWaves == 8 ? w - 4 : w;
+  const int w3 = WAVES == 8 ? w - 4 : w;
   if (w3 >= 0 && w3 < W / 32) {
     // (iii) G1 rows of the sixteen prefixes (as the contraction index) times 32 columns of the tile
     const int half = lane / 32, l32 = lane % 32;
@@ -899,12 +985,12 @@ __global__ __launch_bounds__(mid_waves<R>() * kWave, 6) void k_bwd_mid_mfma(
 #pragma unroll
     for (int j = 0; j < 32; ++j) {
       const int ql = 8 * half + j / 4;
-      a[j] = g1[(size_t)i1_of[ql] * S1 + (j % 4) * R + (l32 < R ? l32 : 0)];
+      a[j] = g1[(size_t)__shfl(item.y, ql) * S1 + (j % 4) * R + (l32 < R ? l32 : 0)];
     }
     TT_LOADS_DONE();
 #pragma unroll
     for (int j = 0; j < 32; ++j)
-      if (q_of[8 * half + j / 4] < 0 || l32 >= R) a[j] = 0.f;
+      if (__shfl(item.x, 8 * half + j / 4) < 0 || l32 >= R) a[j] = 0.f;
     const int n = w3 * 32 + l32;
     f16v acc = TT_ZERO16;
 #pragma unroll
@@ -1376,23 +1462,27 @@ bool mfma_fused_mid(const Shape& s) { return mfma_shape(s) && s.r1 <= 32; }
 void launch_bwd_mid_mfma(const Plan& pl, const Workspace& ws, const float* g1, const float* g2,
                          const float* g3, const float* grad, int B, hipStream_t st) {
   const int chunk_blocks = cdivi(std::min<int64_t>(B, pl.maxQ), kChunk2) + (int)pl.sh.n2;
-  const int waves = pl.sh.r1 <= 16 ? mid_waves<16>() : mid_waves<32>();
+  // fewer than four ids per prefix of the table: blocks of four wavefronts (figures at the kernel)
+  const bool narrow = pl.sh.r1 <= 16 && B < 4 * (int64_t)pl.sh.n1 * pl.sh.n2;
+  const int waves = narrow ? 4 : 8;
   const int* order = (ws.has_order && chunks_ordered(pl, B)) ? ws.c3_order : nullptr;
   // the same number of by-i3 blocks on every XCD
   const int dg3_blocks =
       kXcds * cdivi(cdivi(cdivi(B, chunk3_fill(B)) + (int64_t)pl.sh.n3, kXcds), waves);
-#define TT_MID(RR, DD)                                                                            \
-  k_bwd_mid_mfma<RR, DD><<<chunk_blocks + dg3_blocks, waves * kWave, 0, st>>>(                    \
-      g1, g2, g3, ws.P, grad, ws.gsum, ws.u_code, ws.u_i3, ws.c2_item, ws.c2_desc, ws.c3_item,    \
-      ws.c3_desc, order, ws.dg1part, ws.part2, ws.part3, chunk_blocks, ws.ctr)
+  auto launch = [&](auto kernel) {
+    kernel<<<chunk_blocks + dg3_blocks, waves * kWave, 0, st>>>(
+        g1, g2, g3, ws.P, grad, ws.gsum, ws.u_code, ws.u_i3, ws.c2_item, ws.c2_desc, ws.c3_item, ws.c3_desc,
+        order, ws.dg1part, ws.part2, ws.part3, chunk_blocks, ws.ctr);
+  };
   if (pl.sh.r1 == 8) {
-    if (pl.sh.d3 == 4) TT_MID(8, 4); else TT_MID(8, 8);
+    if (narrow) pl.sh.d3 == 4 ? launch(k_bwd_mid_mfma<8, 4, 4>) : launch(k_bwd_mid_mfma<8, 8, 4>);
+    else pl.sh.d3 == 4 ? launch(k_bwd_mid_mfma<8, 4, 8>) : launch(k_bwd_mid_mfma<8, 8, 8>);
   } else if (pl.sh.r1 == 16) {
-    if (pl.sh.d3 == 4) TT_MID(16, 4); else TT_MID(16, 8);
+    if (narrow) pl.sh.d3 == 4 ? launch(k_bwd_mid_mfma<16, 4, 4>) : launch(k_bwd_mid_mfma<16, 8, 4>);
+    else pl.sh.d3 == 4 ? launch(k_bwd_mid_mfma<16, 4, 8>) : launch(k_bwd_mid_mfma<16, 8, 8>);
   } else {
-    if (pl.sh.d3 == 4) TT_MID(32, 4); else TT_MID(32, 8);
+    pl.sh.d3 == 4 ? launch(k_bwd_mid_mfma<32, 4, 8>) : launch(k_bwd_mid_mfma<32, 8, 8>);
   }
-#undef TT_MID
 }
 
 void launch_row_fwd_mfma(const Plan& pl, const Workspace& ws, const float* g3, int B, float* out,
