@@ -129,8 +129,8 @@ int tt_emb_forward_eval(tt_emb_t h, const int64_t* ids, int64_t B, float* out, v
 /*
  * Lookup for callers that cannot allocate device memory or keep a workspace: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Computes what tt_emb_forward_eval
- * computes (same kernels, bit-identical rows) without a handle and without a caller workspace: the
- * index structures and prefix products of the batch go to a 64 MiB device array that is part of
+ * computes (same kernels, bit-identical rows) without a handle and without a caller workspace: what
+ * the kernels keep of the batch (sorted keys, index structures, products) goes to a 64 MiB device array that is part of
  * the library's code object (every GPU the library runs on holds its own copy until the process
  * ends).  Nothing is allocated or freed, on the device or through any library, by this call.
  *   cfg      shape, ranks and flags as for tt_emb_create (no re-indexing table, no slab-split
@@ -244,7 +244,7 @@ int tt_emb_backward_update(tt_emb_t h, const float* grad_out, float lr, void* hi
 /*
  * Counters of the latest forward: U = distinct in-range ids, Q = distinct (i1,i2) prefixes,
  * out_of_range = number of ids outside [0, N).  Any pointer may be null.  Synchronises the stream
- * of that forward.  Returns TT_EMB_ERANGE (flag CHECK_RANGE set and out_of_range > 0) or
+ * of that forward (after a lookup at ranks up to 32, which needs no counts, it first counts them there).  Returns TT_EMB_ERANGE (flag CHECK_RANGE set and out_of_range > 0) or
  * TT_EMB_EINTERNAL after filling the outputs.
  */
 int tt_emb_get_stats(tt_emb_t h, int64_t* U, int64_t* Q, int64_t* out_of_range);

@@ -923,7 +923,8 @@ void launch_gsum_fix(const Plan& pl, const Workspace& ws, int B, hipStream_t st)
 
 // Where rows lie in a table and operands are fetched ahead (see k_u_bwd), a wavefront needs 113 registers
 // instead of 66 and loads a whole tile's worth at once; products of up to 64 elements whose prefixes have
-// few ids do not repay that.  Times of the kernel with and without, 200,000 uniform ids, us:
+// few ids do not repay that.  Times of the kernel with and without, 200,000 uniform ids, us (taken with
+// shapes that have since gone to k_any_mid; what is left here has more rows or higher ranks):
 //   d, r                      n = (3000,400,20): 1 id each    n = (40,40,40): 55 ids each
 //   (2,2,2), 4                219 / 145                       17 / 17
 //   (2,2,2), 16               218 / 177                       21 / 21
