@@ -36,7 +36,7 @@ void launch_sgd(const Plan&, const Workspace&, float* g1, float* g2, float* g3, 
 bool mfma_shape(const Shape&);
 void launch_prefix_fwd_mfma(const Plan&, const Workspace&, const float* g1, const float* g2, int B,
                             hipStream_t);
-void launch_row_fwd_mfma(const Plan&, const Workspace&, const float* g3, int B, float* out,
+void launch_row_fwd_mfma(const Plan&, const Workspace&, const float* g3, int B, bool beside, float* out,
                          hipStream_t);
 void launch_id_bwd_mfma(const Plan&, const Workspace&, const float* g3, const float* grad, int B,
                         hipStream_t);
@@ -773,7 +773,7 @@ static int forward_impl(tt_emb* h, const IdSource& src, int64_t B64, float* out,
   });
   if (rc) return rc;
   rc = run_slot(h, kSlotRowFwd, st, [&] {
-    if (h->mfma) launch_row_fwd_mfma(pl, ws, h->g3, B, out, st);
+    if (h->mfma) launch_row_fwd_mfma(pl, ws, h->g3, B, found >= 0, out, st);
     else if (any_row_shape(pl.sh)) launch_any_row(pl, ws, h->g3, B, out, st);
     else launch_row_fwd(pl, ws, h->g3, B, out, st);
   });

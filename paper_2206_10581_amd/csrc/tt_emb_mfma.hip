@@ -1021,12 +1021,17 @@ __global__ __launch_bounds__(WAVES * kWave, 6) void k_bwd_mid_mfma(
 // 8 / 16 / 32), longer ones where a product is 4 to 8 KiB and neighbours share it (clustered ids at rank
 // 64: 106 / 95 / 92 us; Zipf 98 / 96 / 105).
 constexpr int row_slots(int R) { return R <= 32 ? 8 : 16; }
+// Where the index kernels of a coming batch run beside this one, four times the wavefronts take the compute
+// units from them: 500,000 Zipf ids at rank 16, look-ahead step 344 / 334 / 325 us with 8 / 16 / 32 slots,
+// plain step 385 / 387 / 391; look-ahead at rank 32, 500,000 ids of (480,480,482) and 400,000 of (136,136,136),
+// 8 / 32 slots: 499 / 489 and 255 / 247.  (Ids whose order keeps hot ones together: 324 / 334 at rank 16.)  Batches of up to 262,144 rows keep the short tiles (200,000 at rank 32: 124 us
+// in the look-ahead loop, 126 with 16 slots before).
+constexpr int kRowSlotsBeside = 32;
 
-template <int R, int D3>
+template <int R, int D3, int TSL>
 __global__ __launch_bounds__(kMThreads) void k_row_fwd_mfma(
     int B, const float* __restrict__ g3, const float* __restrict__ P,
     const int4* __restrict__ s_rec, float* __restrict__ out, Counters* ctr) {
-  constexpr int TSL = row_slots(R);
   constexpr int PN = 16 * R, S3 = R * D3, D = 16 * D3, UPT = 16 / D3, KQ = R / 4;
   constexpr int RS = R + 4;                       // stride of a line of P in LDS
   constexpr int NP = (PN + 255) / 256;            // 16-byte words of P a lane loads
@@ -1485,11 +1490,21 @@ void launch_bwd_mid_mfma(const Plan& pl, const Workspace& ws, const float* g1, c
   }
 }
 
-void launch_row_fwd_mfma(const Plan& pl, const Workspace& ws, const float* g3, int B, float* out,
+void launch_row_fwd_mfma(const Plan& pl, const Workspace& ws, const float* g3, int B, bool beside, float* out,
                          hipStream_t st) {
-#define TT_ROW(D3_)                                                                                     \
-  TT_DISPATCH_R8(pl.sh.r1, (k_row_fwd_mfma<R, D3_><<<cdivi(cdivi(B, row_slots(R)), kMWaves), kMThreads, 0, \
-                                                     st>>>(B, g3, ws.P, ws.s_rec, out, ws.ctr)))
+  const bool large = beside && pl.sh.r1 <= 32 && B > (1 << 18);
+  auto launch = [&](auto kernel, int slots) {
+    kernel<<<cdivi(cdivi(B, slots), kMWaves), kMThreads, 0, st>>>(B, g3, ws.P, ws.s_rec, out, ws.ctr);
+  };
+#define TT_ROW(D3_)                                                                                  \
+  TT_DISPATCH_R8(pl.sh.r1, {                                                                         \
+    if constexpr (R <= 32) {                                                                         \
+      if (large) launch(k_row_fwd_mfma<R, D3_, kRowSlotsBeside>, kRowSlotsBeside);                   \
+      else launch(k_row_fwd_mfma<R, D3_, row_slots(R)>, row_slots(R));                               \
+    } else {                                                                                         \
+      launch(k_row_fwd_mfma<R, D3_, row_slots(R)>, row_slots(R));                                    \
+    }                                                                                                \
+  })
   if (pl.sh.d3 == 4) {
     TT_ROW(4)
   } else {
