@@ -224,7 +224,7 @@ int tt_emb_wait_backward(tt_emb_t h, int age);
  * Results are identical with or without it.  Small batches (a few thousand ids and fewer) take kernels
  * that need no index structures: for them the call only orders the forward, which waits for what was
  * enqueued on hip_stream before it, and takes no index set.  tt_emb_get_stats refers to the latest forward only
- * until the next tt_emb_prepare.
+ * until the next tt_emb_prepare (zeros once a prepared batch has taken the index set of a lookup).
  */
 int tt_emb_prepare(tt_emb_t h, const int64_t* ids, int64_t B, void* hip_stream);
 

@@ -650,6 +650,8 @@ int tt_emb_prepare(tt_emb_t h, const int64_t* ids, int64_t B64, void* hip_stream
         target = s;
   }
   h->prep[target].valid = false;
+  // the counters of a lookup are made from the keys in its set: they go with it
+  if (target == h->cur && h->lookup) h->have_forward = false;
   // everything that used this set earlier (its backward_update, or an index pipeline that is now
   // dropped) is ordered before: the set's stream is in order, and the fork event covers hip_stream
   if ((h->cfg.flags & TT_EMB_FLAG_IDS_READY) && h->done_valid[target]) {
