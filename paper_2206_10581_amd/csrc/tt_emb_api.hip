@@ -14,9 +14,8 @@
 namespace ttemb {
 
 // launchers defined next to their kernels
-void launch_sort_pass(const Plan&, const Workspace&, const SortKeys&, const IdSource* src, int B, int pass,
+void launch_sort_pass(const Plan&, const Workspace&, const SortKeys&, const IdSource& src, int B, int pass,
                       bool beside, bool clear, hipStream_t, int which);
-void launch_count_keys(const Workspace&, const SortKeys&, int i3_bits, int B, hipStream_t);
 void launch_seg_count(const Plan&, const Workspace&, int B, hipStream_t);
 void launch_seg_write(const Plan&, const Workspace&, int B, hipStream_t);
 void launch_group(const Plan&, const Workspace&, int B, hipStream_t, int which);
@@ -61,6 +60,7 @@ void launch_any_dg3(const Plan&, const Workspace&, const float* grad, int B, hip
 bool lookup_shape(const Shape&);
 void launch_lookup(const Plan&, const Workspace&, const float* g1, const float* g2, const float* g3, int B,
                    float* out, hipStream_t);
+void launch_count_lookup(const Plan&, const Workspace&, int B, hipStream_t);
 // index-free kernels (tt_emb_direct.hip)
 int direct_capacity(const Shape&);
 int direct_train_capacity(const Shape&);
@@ -96,7 +96,7 @@ static int bits_for(uint32_t v) {  // number of bits needed to write v (at least
 // Passes over the bits of a key from `low` on; the sentinel itself must be representable.
 static SortKeys sort_keys(uint32_t sentinel, int low) {
   const int bits = bits_for(sentinel >> low), passes = (bits + 10) / 11;
-  return SortKeys{sentinel, low, bits, passes, (bits + passes - 1) / passes, 1};
+  return SortKeys{sentinel, low, bits, passes, (bits + passes - 1) / passes};
 }
 
 static int make_plan(const tt_emb_config* c, Plan* pl) {
@@ -339,7 +339,6 @@ struct tt_emb {
   bool have_forward;
   bool direct;        // the latest forward took the index-free kernels
   bool lookup;        // the latest forward was a lookup by prefix
-  bool counted;       // and its counters have been made
   hipStream_t last_stream;
   // tt_emb_prepare: index pipelines of coming batches on a stream of the library's own
   hipStream_t side[kSets];  // stream of each index set (kSideStreams distinct ones), created on
@@ -446,7 +445,7 @@ static void init_handle(tt_emb* h, const tt_emb_config* cfg, const Plan& pl, flo
   h->last_B = 0;
   h->have_forward = false;
   h->direct = false;
-  h->lookup = h->counted = false;
+  h->lookup = false;
   h->last_stream = nullptr;
   h->profiling = false;
   h->mfma = pl.mfma;
@@ -546,14 +545,12 @@ static int take_prepared(tt_emb::Prepared* list, const int64_t* ids, int64_t B, 
   return TT_EMB_OK;
 }
 
-// The passes of a sort; src == nullptr: of keys that are in the input buffer already.
-static int run_sort(tt_emb* h, const Workspace& ws, const SortKeys& sk, const IdSource* src, int B, bool beside,
+static int run_sort(tt_emb* h, const Workspace& ws, const SortKeys& sk, const IdSource& src, int B, bool beside,
                     bool clear, hipStream_t st) {
   const Plan& pl = h->plan;
   for (int pass = 0; pass < sk.passes; ++pass) {
-    const IdSource* from = pass == 0 ? src : nullptr;
     auto part = [&](int slot, int which) {
-      return run_slot(h, slot, st, [&] { launch_sort_pass(pl, ws, sk, from, B, pass, beside, clear, st, which); });
+      return run_slot(h, slot, st, [&] { launch_sort_pass(pl, ws, sk, src, B, pass, beside, clear, st, which); });
     };
     int rc = part(kSlotSortHist, 0);
     if (!rc && !sort_folds(B, beside)) rc = part(kSlotSortScan, 2);
@@ -570,7 +567,7 @@ static int run_sort(tt_emb* h, const Workspace& ws, const SortKeys& sk, const Id
 static int run_index(tt_emb* h, int set, const IdSource& src, int B, hipStream_t st, int how) {
   const Plan& pl = h->plan;
   const Workspace& ws = h->ws[set];
-  int rc = run_sort(h, ws, pl.keys, &src, B, how == 0, true, st);
+  int rc = run_sort(h, ws, pl.keys, src, B, how == 0, true, st);
   if (rc) return rc;
   rc = run_slot(h, kSlotSegCount, st, [&] { launch_seg_count(pl, ws, B, st); });
   if (rc) return rc;
@@ -589,26 +586,9 @@ static int run_lookup(tt_emb* h, IdSource src, int B, float* out, hipStream_t st
   src.n1 = pl.user_n1;
   src.n2 = pl.sh.n2;
   src.n3 = pl.sh.n3;
-  int rc = run_sort(h, ws, pl.lookup_keys, &src, B, false, false, st);
+  int rc = run_sort(h, ws, pl.lookup_keys, src, B, false, false, st);
   if (rc) return rc;
   return run_slot(h, kSlotLookup, st, [&] { launch_lookup(pl, ws, h->g1, h->g2, h->g3, B, out, st); });
-}
-
-// Counters of the latest lookup by prefix: its keys, sorted by prefix, are sorted in full and counted.
-static int count_lookup(tt_emb* h, hipStream_t st) {
-  const Workspace& ws = h->ws[h->cur];
-  const int B = (int)(h->last_B / h->plan.split);
-  SortKeys sk = h->plan.lookup_keys;
-  const int in = sk.sorted();
-  sk = sort_keys(sk.sentinel, 0);
-  sk.input = in;
-  const int rc = run_sort(h, ws, sk, nullptr, B, false, false, st);
-  if (rc) return rc;
-  launch_count_keys(ws, sk, h->plan.lookup_i3_bits, B, st);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return hip_fail(e);
-  h->counted = true;
-  return TT_EMB_OK;
 }
 
 int tt_emb_prepare(tt_emb_t h, const int64_t* ids, int64_t B64, void* hip_stream) {
@@ -757,7 +737,6 @@ static int forward_impl(tt_emb* h, const IdSource& src, int64_t B64, float* out,
       rc = run_lookup(h, src, (int)B64, out, st);
       if (rc) return rc;
       h->lookup = true;
-      h->counted = false;
       h->last_B = B;
       h->have_forward = true;
       return mark_set_done(h, st);
@@ -1074,10 +1053,11 @@ int tt_emb_get_stats(tt_emb_t h, int64_t* U, int64_t* Q, int64_t* out_of_range) 
         c.Q += i == 0 || key[i] / s.n3 != key[i - 1] / s.n3;
       }
     } else {
-      if (h->lookup && !h->counted) {
-        const int rc = count_lookup(h, h->last_stream);
-        if (rc) return rc;
-        e = hipStreamSynchronize(h->last_stream);
+      if (h->lookup) {
+        // counted anew at every call: a captured lookup leaves other keys at each replay
+        launch_count_lookup(h->plan, h->ws[h->cur], (int)(h->last_B / h->plan.split), h->last_stream);
+        e = hipGetLastError();
+        if (e == hipSuccess) e = hipStreamSynchronize(h->last_stream);
         if (e != hipSuccess) return hip_fail(e);
       }
       e = hipMemcpy(&c, h->ws[h->cur].ctr, sizeof(c), hipMemcpyDeviceToHost);

@@ -567,44 +567,6 @@ __global__ __launch_bounds__(kSegThreads) void k_seg_write(
   }
 }
 
-// Counters of a batch from its sorted keys (prefix << i3_bits | i3), by one block: for tt_emb_get_stats
-// after a lookup, which itself counts nothing.
-__global__ __launch_bounds__(1024) void k_count_keys(const uint32_t* __restrict__ skey, int B, uint32_t sentinel,
-                                                     int i3_bits, Counters* __restrict__ ctr) {
-  constexpr int kLoads = 8;
-  __shared__ uint32_t sum[3];
-  if (threadIdx.x < 3) sum[threadIdx.x] = 0u;
-  __syncthreads();
-  uint32_t u = 0, q = 0, valid = 0;
-  for (int s0 = (int)threadIdx.x; s0 < B; s0 += kLoads * 1024) {
-    uint32_t k[kLoads], before[kLoads];
-#pragma unroll
-    for (int j = 0; j < kLoads; ++j) {
-      const int s = min(s0 + j * 1024, B - 1);
-      k[j] = skey[s];
-      before[j] = skey[max(s - 1, 0)];
-    }
-#pragma unroll
-    for (int j = 0; j < kLoads; ++j) {
-      const int s = s0 + j * 1024;
-      const bool ok = s < B && k[j] < sentinel;
-      valid += ok;
-      u += ok && (s == 0 || k[j] != before[j]);
-      q += ok && (s == 0 || k[j] >> i3_bits != before[j] >> i3_bits);
-    }
-  }
-  atomicAdd(&sum[0], u);
-  atomicAdd(&sum[1], q);
-  atomicAdd(&sum[2], valid);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    ctr->U = (int)sum[0];
-    ctr->Q = (int)sum[1];
-    ctr->nvalid = (int)sum[2];
-    ctr->n_split = 0;
-  }
-}
-
 // ---------------------------------------------------------------------------------------------
 // Grouping: unique ids by i3 (for the G3 gradient), prefixes by i2 (for G2 and the prefix product)
 
@@ -705,21 +667,21 @@ static inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 // One of the three kernels of a pass.  clear: the first one also clears the tables that the steps
 // behind the sort add into (lookups have none).
 template <int NT>
-static void sort_pass(const Plan& pl, const Workspace& ws, const SortKeys& sk, const IdSource* src, int B,
+static void sort_pass(const Plan& pl, const Workspace& ws, const SortKeys& sk, const IdSource& src, int B,
                       int pass, bool beside, bool clear, hipStream_t st, int which) {
   const int blocks = cdiv(B, sort_items(NT));
   const int shift = sk.low + pass * sk.per;
   const int bits = std::min(sk.per, sk.bits - pass * sk.per);
   const uint32_t* tot = sort_folds(B, beside) ? nullptr : ws.tot;
-  const int in = (sk.input + pass) & 1;
+  const int in = (pass + 1) & 1;
   uint32_t *kin = ws.key[in], *vin = ws.val[in], *kout = ws.key[in ^ 1], *vout = ws.val[in ^ 1];
   if (which == 2) {
     k_sort_colscan<<<cdiv(1 << bits, kScanBins), kScanThreads, 0, st>>>(ws.cnt, ws.tot, blocks,
                                                                        1 << bits);
   } else if (which == 0) {
-    if (src != nullptr)
+    if (pass == 0)
       k_sort_hist<NT, true><<<blocks, NT, 0, st>>>(
-          *src, kin, B, sk.sentinel, shift, bits, ws.cnt, ws.cnt3, clear ? pl.uBlocksMax * (int)pl.sh.n3 : 0,
+          src, kin, B, sk.sentinel, shift, bits, ws.cnt, ws.cnt3, clear ? pl.uBlocksMax * (int)pl.sh.n3 : 0,
           ws.cnt2, clear ? pl.qBlocksMax * (int)pl.sh.n2 : 0, (uint32_t*)ws.g1_first,
           clear ? 2 * (int)pl.sh.n1 + 2 * kOrderBands : 0, ws.ctr);
     else
@@ -734,8 +696,7 @@ static void sort_pass(const Plan& pl, const Workspace& ws, const SortKeys& sk, c
   }
 }
 
-// src: where the keys of the first pass come from; nullptr where they are in its input buffer
-void launch_sort_pass(const Plan& pl, const Workspace& ws, const SortKeys& sk, const IdSource* src, int B,
+void launch_sort_pass(const Plan& pl, const Workspace& ws, const SortKeys& sk, const IdSource& src, int B,
                       int pass, bool beside, bool clear, hipStream_t st,
                       int which /*0 = histogram, 1 = scatter, 2 = column scan*/) {
   switch (sort_threads(B, beside)) {
@@ -743,10 +704,6 @@ void launch_sort_pass(const Plan& pl, const Workspace& ws, const SortKeys& sk, c
     case 512: sort_pass<512>(pl, ws, sk, src, B, pass, beside, clear, st, which); break;
     default: sort_pass<1024>(pl, ws, sk, src, B, pass, beside, clear, st, which); break;
   }
-}
-
-void launch_count_keys(const Workspace& ws, const SortKeys& sk, int i3_bits, int B, hipStream_t st) {
-  k_count_keys<<<1, 1024, 0, st>>>(ws.key[sk.sorted()], B, sk.sentinel, i3_bits, ws.ctr);
 }
 
 // The blocks' counts: those of fine blocks lie in the digit totals of the sort, which is over, so that the

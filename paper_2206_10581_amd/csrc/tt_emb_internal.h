@@ -89,12 +89,12 @@ struct IdSource {
 };
 
 // What a sort orders by: `bits` bits of the key above the lowest `low`, `per` of them a pass.
-// Out-of-range ids have the key `sentinel`, above every other.  The first pass reads key buffer
-// `input` (which its histogram fills from the ids) and writes the other, the next one back, and so on.
+// Out-of-range ids have the key `sentinel`, above every other.  The first pass reads key buffer 1 (which
+// its histogram fills from the ids) and writes the other, the next one back, and so on.
 struct SortKeys {
   uint32_t sentinel;
-  int low, bits, passes, per, input;
-  int sorted() const { return (input + passes) & 1; }  // buffer of the sorted keys
+  int low, bits, passes, per;
+  int sorted() const { return (passes + 1) & 1; }  // buffer of the sorted keys
 };
 
 // Update rule of the update kernel and its caller-owned state (arrays shaped like the cores).

@@ -218,6 +218,69 @@ __global__ __launch_bounds__(kLThreads) void k_lookup_mfma(
   }
 }
 
+// Counters of a lookup from its keys, sorted by prefix only, for tt_emb_get_stats; the keys are only read.
+// A wavefront counts the prefixes that begin in its run of slots, 64 slots at a time.  Whether an id was met
+// before: inside the 64 by comparing keys, in a prefix that goes on from slots before them by one bit of LDS
+// for each i3.
+constexpr int kCountSteps = 8;
+
+__global__ __launch_bounds__(kLThreads) void k_count_lookup(const uint32_t* __restrict__ skey, int B,
+                                                            uint32_t sentinel, int i3_bits,
+                                                            Counters* __restrict__ ctr) {
+  __shared__ uint32_t met[kLWaves][kMaxBins / 32];
+  const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  const int begin = (blockIdx.x * kLWaves + w) * kCountSteps * kWave, end = min(begin + kCountSteps * kWave, B);
+  if (begin >= B) return;
+  uint32_t* bits = met[w];
+  uint32_t u = 0, q = 0, valid = 0;
+  bool open = false, more = true;  // a prefix of this wavefront goes on; something is left to count
+  uint32_t last = begin > 0 ? skey[begin - 1] : sentinel;  // key in front of the 64 (the first of all: none)
+  for (int at0 = begin; more; at0 += kCountSteps * kWave) {
+    uint32_t keys[kCountSteps];
+#pragma unroll
+    for (int j = 0; j < kCountSteps; ++j) keys[j] = skey[min(at0 + j * kWave + lane, B - 1)];
+    for (int j = 0; j < kCountSteps && more; ++j) {
+      const int at = at0 + j * kWave;
+      uint32_t key = keys[0];
+#pragma unroll
+      for (int k = 1; k < kCountSteps; ++k) key = j == k ? keys[k] : key;
+      const bool on = at + lane < B && key < sentinel;  // in-range ids lie in front
+      uint32_t before = __shfl_up(key, 1);
+      if (lane == 0) before = last;
+      last = (uint32_t)value_at((int)key, 63);
+      const unsigned long long starts = __ballot(on && (at + lane == 0 || key >> i3_bits != before >> i3_bits));
+      const int nv = __popcll(__ballot(on)), first = starts ? __ffsll((long long)starts) - 1 : nv;
+      const uint32_t i3 = key & ((1u << i3_bits) - 1u), word = i3 / 32 % (kMaxBins / 32), bit = 1u << i3 % 32;
+      if (open && lane < first) u += !(atomicOr(&bits[word], bit) & bit);
+      if (at < end) {
+        bool seen = false;
+        for (int k = 0; k < 63; ++k) seen |= k < lane && (uint32_t)value_at((int)key, k) == key;
+        u += on && lane >= first && !seen;
+        q += (starts >> lane) & 1ull;
+        valid += on;
+        if (starts) {  // the last prefix may go on
+          wave_sync();
+          for (int k = lane; k < kMaxBins / 32; k += kWave) bits[k] = 0u;
+          wave_sync();
+          if (on && lane >= 63 - __clzll((long long)starts)) atomicOr(&bits[word], bit);
+          open = true;
+        }
+      }
+      more = nv == kWave && (at + kWave < end || (open && !(at >= end && starts)));
+    }
+  }
+  u = wave_inclusive_scan(u, lane);
+  q = wave_inclusive_scan(q, lane);
+  valid = wave_inclusive_scan(valid, lane);
+  if (lane == 63) {
+    atomicAdd((uint32_t*)&ctr->U, u);
+    atomicAdd((uint32_t*)&ctr->Q, q);
+    atomicAdd((uint32_t*)&ctr->nvalid, valid);
+  }
+}
+
+__global__ void k_clear_counts(Counters* ctr) { ctr->U = ctr->Q = ctr->nvalid = 0; }
+
 bool lookup_shape(const Shape& s) { return s.r1 <= 32; }
 
 // Slots of a wavefront's tile.  Short tiles put more wavefronts in flight and shorten the chain of batches
@@ -247,6 +310,13 @@ void launch_lookup(const Plan& pl, const Workspace& ws, const float* g1, const f
     default: if (tile == 16) TT_TILE(32, 16); else if (tile == 32) TT_TILE(32, 32); else TT_TILE(32, 64);
   }
 #undef TT_TILE
+}
+
+void launch_count_lookup(const Plan& pl, const Workspace& ws, int B, hipStream_t st) {
+  constexpr int kSlots = kLWaves * kCountSteps * kWave;
+  k_clear_counts<<<1, 1, 0, st>>>(ws.ctr);
+  k_count_lookup<<<(B + kSlots - 1) / kSlots, kLThreads, 0, st>>>(ws.key[pl.lookup_keys.sorted()], B,
+                                                                 pl.lookup_keys.sentinel, pl.lookup_i3_bits, ws.ctr);
 }
 
 }  // namespace ttemb
