@@ -369,7 +369,7 @@ struct tt_emb {
 static IdSource id_source(const tt_emb* h, const int64_t* ids, int64_t base, bool reindexed) {
   const Plan& pl = h->plan;
   return IdSource{ids, base, reindexed ? h->reindex : nullptr, reindexed ? h->reindex_n : 0,
-                  pl.split, pl.user_N, (int64_t)pl.sh.n2 * pl.sh.n3, 0, 0, 0, 0};
+                  pl.split, pl.user_N, (int64_t)pl.sh.n2 * pl.sh.n3};
 }
 
 static int hip_fail(hipError_t e) {
@@ -581,11 +581,7 @@ static int run_index(tt_emb* h, int set, const IdSource& src, int B, hipStream_t
 static int run_lookup(tt_emb* h, IdSource src, int B, float* out, hipStream_t st) {
   const Plan& pl = h->plan;
   const Workspace& ws = h->ws[h->cur];
-  src.split = 1;
-  src.i3_bits = pl.lookup_i3_bits;
-  src.n1 = pl.user_n1;
-  src.n2 = pl.sh.n2;
-  src.n3 = pl.sh.n3;
+  src.split = 1;  // caller's ids, not slabs
   int rc = run_sort(h, ws, pl.lookup_keys, src, B, false, false, st);
   if (rc) return rc;
   return run_slot(h, kSlotLookup, st, [&] { launch_lookup(pl, ws, h->g1, h->g2, h->g3, B, out, st); });

@@ -10,6 +10,7 @@
 // Everything here is integer work and is bit-exact; all orders are stable, so the floating-point
 // sums that later follow these lists are formed in a fixed order.
 #include <algorithm>
+#include <type_traits>
 
 #include "tt_emb_internal.h"
 
@@ -301,15 +302,18 @@ struct SortOps {
   }
 };
 
+struct KeysInPlace {};  // source of the passes behind the first
+
 // Bucket counts of one radix digit per block of sort_items(NT) items.  Equal digits inside a
 // wavefront step are counted with one LDS atomic (a hot id would otherwise serialise thousands of
 // them).  The first pass also clears the tables that later kernels of the same forward add into, and
 // leaves the keys for its scatter, which need not split and renumber the ids again.
-template <int NT, bool FROM_IDS>
+template <int NT, class SRC>
 __global__ __launch_bounds__(NT) void k_sort_hist(
-    IdSource src, uint32_t* keys_io, int B, uint32_t N, int shift,
+    SRC src, uint32_t* keys_io, int B, uint32_t N, int shift,
     int bits, uint32_t* __restrict__ cnt, uint32_t* zero_a, int zero_a_n, uint32_t* zero_b,
     int zero_b_n, uint32_t* zero_c, int zero_c_n, Counters* ctr) {
+  constexpr bool FROM_IDS = !std::is_same_v<SRC, KeysInPlace>;
   __shared__ uint32_t h[kMaxBins];
   const int tid = threadIdx.x, bins = 1 << bits;
   const uint32_t mask = (uint32_t)bins - 1u;
@@ -320,7 +324,8 @@ __global__ __launch_bounds__(NT) void k_sort_hist(
   for (int step = 0; step < kSteps; ++step) {
     const int idx = wbase + step * kWave + lane;
     const int ic = min(idx, B - 1);
-    keys[step] = FROM_IDS ? key_of_id(src, ic, N) : keys_io[ic];
+    if constexpr (FROM_IDS) keys[step] = key_of_id(src, ic, N);
+    else keys[step] = keys_io[ic];
   }
   __builtin_amdgcn_sched_barrier(0);  // keep the loads together: their latencies overlap
   if (FROM_IDS) {
@@ -679,14 +684,19 @@ static void sort_pass(const Plan& pl, const Workspace& ws, const SortKeys& sk, c
     k_sort_colscan<<<cdiv(1 << bits, kScanBins), kScanThreads, 0, st>>>(ws.cnt, ws.tot, blocks,
                                                                        1 << bits);
   } else if (which == 0) {
-    if (pass == 0)
-      k_sort_hist<NT, true><<<blocks, NT, 0, st>>>(
-          src, kin, B, sk.sentinel, shift, bits, ws.cnt, ws.cnt3, clear ? pl.uBlocksMax * (int)pl.sh.n3 : 0,
+    auto first = [&](auto from) {
+      k_sort_hist<NT><<<blocks, NT, 0, st>>>(
+          from, kin, B, sk.sentinel, shift, bits, ws.cnt, ws.cnt3, clear ? pl.uBlocksMax * (int)pl.sh.n3 : 0,
           ws.cnt2, clear ? pl.qBlocksMax * (int)pl.sh.n2 : 0, (uint32_t*)ws.g1_first,
           clear ? 2 * (int)pl.sh.n1 + 2 * kOrderBands : 0, ws.ctr);
+    };
+    if (pass > 0)
+      k_sort_hist<NT><<<blocks, NT, 0, st>>>(KeysInPlace{}, kin, B, sk.sentinel, shift, bits, ws.cnt, nullptr, 0,
+                                             nullptr, 0, nullptr, 0, ws.ctr);
+    else if (sk.low > 0)  // by prefix
+      first(PrefixSource{src, sk.low, pl.user_n1, pl.sh.n2, pl.sh.n3});
     else
-      k_sort_hist<NT, false><<<blocks, NT, 0, st>>>(IdSource{}, kin, B, sk.sentinel, shift, bits, ws.cnt,
-                                                    nullptr, 0, nullptr, 0, nullptr, 0, ws.ctr);
+      first(src);
   } else if (pass == 0) {
     SortOps<true> ops{kin, nullptr, kout, vout, shift, (1u << bits) - 1u};
     k_sort_scatter<NT, true><<<blocks, NT, 0, st>>>(ops, B, bits, ws.cnt, tot);
