@@ -1,5 +1,6 @@
 // Any-shape kernels with their products on the matrix cores (gfx950, fp32): prefixes of up to 32 lines
-// d1*d2, ranks up to 64, d3 up to 16.  Larger shapes take the kernels of tt_emb_compute.hip.
+// d1*d2, ranks up to 64, d3 up to 16.  Larger shapes, and forms of these that are slower here (any_*_takes),
+// take the kernels of tt_emb_compute.hip.
 //
 // The products of this path are small and of any size, so every operand goes from memory (or an LDS tile)
 // straight to the registers of v_mfma_f32_16x16x4f32, whose lane (kg, l16) = (lane/16, lane%16) holds
@@ -372,8 +373,8 @@ __global__ __launch_bounds__(256) void k_any_dg3(
 // ---------------------------------------------------------------------------------------------
 // P_q of a by-i2 chunk: one wavefront per 16 columns of the chunk's product, its G2 strip in registers,
 // four tiles of 16 lines (d1 = 4: all sixteen prefixes) in flight together.  KQ = r1/4 rounded up: lane
-// group kg takes indices KQ*kg ..
-template <int KQ>
+// group kg takes indices KQ*kg ..  VEC: r1 is a multiple of four, lines of G1 are read by 16-byte words.
+template <int KQ, bool VEC>
 __global__ __launch_bounds__(kWave) void k_any_prefix(Shape sh, uint32_t inv_d1, int tiles,
                                                       const float* __restrict__ g1, const float* __restrict__ g2,
                                                       const int4* __restrict__ c2_desc,
@@ -399,10 +400,11 @@ __global__ __launch_bounds__(kWave) void k_any_prefix(Shape sh, uint32_t inv_d1,
     for (int mt = 0; mt < MT; ++mt) {
       const int r = min(r0 + 16 * mt + l16, rows - 1), t = divided(r, inv_d1);
       const float* line = g1 + (size_t)__shfl(item.y, t) * sh.S1 + (r - t * sh.d1) * sh.r1;
-      if (KQ % 4 == 0 && sh.r1 == 4 * KQ) {
+      if constexpr (VEC) {
 #pragma unroll
         for (int j = 0; j < KQ / 4; ++j) {
-          const f4 v = ((const f4*)(line + KQ * kg))[j];
+          f4 v = *(const f4*)(line + min(KQ * kg + 4 * j, sh.r1 - 4));
+          if (KQ * kg + 4 * j >= sh.r1) v = f4{0.f, 0.f, 0.f, 0.f};
           a[mt][4 * j] = v.x;
           a[mt][4 * j + 1] = v.y;
           a[mt][4 * j + 2] = v.z;
@@ -624,14 +626,57 @@ __global__ __launch_bounds__(256) void k_any_row(Shape sh, int B, uint32_t inv_d
 static inline int cdiva(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 constexpr size_t kAnyLds = 96 * 1024;  // most LDS of a block
 
-bool any_mid_shape(const Shape& s) {
-  return s.M <= 32 && s.r1 <= 64 && s.r2 <= 64 && s.d1 <= 16 && s.d3 <= 32 &&
-         s.D + s.S3 <= AnyMidLds::kWords * kWave &&
-         AnyMidLds(s).floats() * sizeof(float) <= kAnyLds;
+// Which of these kernels a batch takes; the others are those of tt_emb_compute.hip.  Times of a kernel in us,
+// those / these, 60,000 ids: "many" uniform ids of n = 40^3, "few" Zipf ids of 140^3, "fewer" uniform ids of
+// (400,400,30), i.e. 37, 3 and 0.4 per prefix of the table.
+static bool many_ids(const Plan& pl, int B) { return B >= 8 * (int64_t)pl.sh.n1 * pl.sh.n2; }
+
+// Against k_u_bwd and k_prefix_bwd together:
+//   d, r             ids of a fill   many       few        fewer
+//   (4,5,5), 32      4               55 / 40    95 / 43    314 / 124
+//   (4,5,5), 30      4, not words    55 / 65    96 / 52    312 / 149
+//   (2,3,12), 24     2               55 / 65    62 / 33    175 / 88
+//   (2,3,12), 33     2               91 / 128   87 / 88    246 / 255
+//   (2,2,2), 60      12              41 / 27    78 / 38    243 / 108
+//   (2,2,2), 63      11, not words   40 / 50    78 / 50    245 / 145
+//   (4,5,5), 33      4, not words    72 / 195   118 / 139  377 / 423
+// (the last with 96 accumulator registers and as many spilled ones: more than 16 lines and ranks above 32).
+bool any_mid_takes(const Plan& pl, int B) {
+  const Shape& s = pl.sh;
+  if (s.M > 32 || s.r1 > 64 || s.r2 > 64 || s.d1 > 16 || s.d3 > 32 ||
+      s.D + s.S3 > AnyMidLds::kWords * kWave || AnyMidLds(s).floats() * sizeof(float) > kAnyLds)
+    return false;
+  const bool wide = std::max(s.r1, s.r2) > 32, words = s.D % 4 == 0 && s.S3 % 4 == 0;
+  const int fill = AnyMidLds(s).fill;
+  if (wide && (s.M > 16 || fill < 3)) return false;
+  return !many_ids(pl, B) || (fill >= 3 && (words || !wide));
 }
-bool any_dg3_shape(const Shape& s) { return s.r2 <= 64 && s.d3 <= 16 && s.M <= 64; }
-bool any_prefix_shape(const Shape& s) { return s.r1 <= 64 && s.d1 <= 16; }
-bool any_row_shape(const Shape& s) { return s.M <= 32 && s.r2 <= 64 && s.d3 <= 16; }
+// Better in every form: (4,5,5), rank 32: many 45 / 21, few 28 / 17, fewer 68 / 35; (2,2,2), 4: 15 / 9, 11 / 7,
+// 21 / 11; (4,4,4), 48: 46 / 30, 26 / 20, 66 / 45; (3,7,3), 63: 76 / 45, 39 / 30, 122 / 87.
+bool any_dg3_takes(const Plan& pl) { return pl.sh.r2 <= 64 && pl.sh.d3 <= 16 && pl.sh.M <= 64; }
+// Ranks that are no multiple of four read lines of G1 element by element.  Few / fewer ids, those, these:
+//   (4,5,5): rank 15 17 / 41, 14 / 31;  24 21 / 55, 18 / 45;  30 27 / 77, 27 / 84;  33 32 / 97, 47 / 165;
+//            40 39 / 124, 28 / 91;  64 56 / 187, 47 / 182
+//   (4,4,4): rank 15 13 / 25, 13 / 25;  28 21 / 54, 17 / 42;  30 21 / 56, 23 / 66;  48 32 / 96, 26 / 85
+bool any_prefix_takes(const Plan& pl) {
+  const Shape& s = pl.sh;
+  return s.d1 <= 16 && (s.r1 <= 16 || (s.r1 <= 64 && s.r1 % 4 == 0));
+}
+// A wavefront stages a product for few rows, or many:
+//   d, r           many       few        fewer
+//   (4,5,5), 32    34 / 21    29 / 25    45 / 42
+//   (4,5,5), 6     24 / 21    22 / 27    29 / 41
+//   (4,5,5), 30    47 / 36    39 / 51    70 / 78
+//   (4,5,5), 48    38 / 33    32 / 47    51 / 69
+//   (4,5,5), 33    51 / 96    41 / 154   78 / 238
+//   (4,4,4), 48    31 / 21    26 / 33    41 / 50
+//   (2,2,2), 6     18 / 12    18 / 20    23 / 25
+bool any_row_takes(const Plan& pl, int B) {
+  const Shape& s = pl.sh;
+  if (s.M > 32 || s.r2 > 64 || s.d3 > 16) return false;
+  if (s.r2 <= 4 || (s.r2 <= 32 && s.r2 % 4 == 0)) return true;
+  return many_ids(pl, B) && (s.r2 <= 32 || s.r2 % 4 == 0);
+}
 
 void launch_any_mid(const Plan& pl, const Workspace& ws, const float* g1, const float* g2, const float* g3,
                     const float* grad, int B, hipStream_t st) {
@@ -652,8 +697,7 @@ void launch_any_mid(const Plan& pl, const Workspace& ws, const float* g1, const 
     else TT_ANY_MID(1, 4);
   } else {
     if (nt == 1) TT_ANY_MID(2, 1);
-    else if (nt == 2) TT_ANY_MID(2, 2);
-    else TT_ANY_MID(2, 4);
+    else TT_ANY_MID(2, 2);
   }
 #undef TT_ANY_MID
 }
@@ -677,10 +721,11 @@ void launch_any_prefix(const Plan& pl, const Workspace& ws, const float* g1, con
   auto launch = [&](auto kernel) {
     kernel<<<chunks * tiles, kWave, 0, st>>>(s, inverse_of(s.d1), tiles, g1, g2, ws.c2_desc, ws.c2_item, ws.P, ws.ctr);
   };
-  if (s.r1 <= 4) launch(k_any_prefix<1>);
-  else if (s.r1 <= 16) launch(k_any_prefix<4>);
-  else if (s.r1 <= 32) launch(k_any_prefix<8>);
-  else launch(k_any_prefix<16>);
+  if (s.r1 <= 4) launch(k_any_prefix<1, false>);
+  else if (s.r1 <= 16) s.r1 % 4 == 0 ? launch(k_any_prefix<4, true>) : launch(k_any_prefix<4, false>);
+  else if (s.r1 <= 32) launch(k_any_prefix<8, true>);
+  else if (s.r1 <= 48) launch(k_any_prefix<12, true>);
+  else launch(k_any_prefix<16, true>);
 }
 
 template <int MT, int KQ>

@@ -47,10 +47,10 @@ void launch_bwd_mid_mfma(const Plan&, const Workspace&, const float* g1, const f
                          const float* g3, const float* grad, int B, hipStream_t);
 void launch_gsum_block(const Plan&, const Workspace&, const float* grad, int B, hipStream_t);
 // any-shape kernels on the matrix cores (tt_emb_any.hip)
-bool any_prefix_shape(const Shape&);
-bool any_row_shape(const Shape&);
-bool any_mid_shape(const Shape&);
-bool any_dg3_shape(const Shape&);
+bool any_prefix_takes(const Plan&);
+bool any_row_takes(const Plan&, int B);
+bool any_mid_takes(const Plan&, int B);
+bool any_dg3_takes(const Plan&);
 void launch_any_prefix(const Plan&, const Workspace&, const float* g1, const float* g2, int B, hipStream_t);
 void launch_any_row(const Plan&, const Workspace&, const float* g3, int B, float* out, hipStream_t);
 void launch_any_mid(const Plan&, const Workspace&, const float* g1, const float* g2, const float* g3,
@@ -745,13 +745,13 @@ static int forward_impl(tt_emb* h, const IdSource& src, int64_t B64, float* out,
   const Workspace& ws = h->ws[h->cur];
   rc = run_slot(h, kSlotPrefixFwd, st, [&] {
     if (h->mfma) launch_prefix_fwd_mfma(pl, ws, h->g1, h->g2, B, st);
-    else if (any_prefix_shape(pl.sh)) launch_any_prefix(pl, ws, h->g1, h->g2, B, st);
+    else if (any_prefix_takes(pl)) launch_any_prefix(pl, ws, h->g1, h->g2, B, st);
     else launch_prefix_fwd(pl, ws, h->g1, h->g2, B, st);
   });
   if (rc) return rc;
   rc = run_slot(h, kSlotRowFwd, st, [&] {
     if (h->mfma) launch_row_fwd_mfma(pl, ws, h->g3, B, found >= 0, out, st);
-    else if (any_row_shape(pl.sh)) launch_any_row(pl, ws, h->g3, B, out, st);
+    else if (any_row_takes(pl, B)) launch_any_row(pl, ws, h->g3, B, out, st);
     else launch_row_fwd(pl, ws, h->g3, B, out, st);
   });
   if (rc) return rc;
@@ -943,14 +943,14 @@ static int backward_indexed(tt_emb* h, const float* grad_out, float lr, int B, h
     rc = run_slot(h, kSlotPrefixBwd, st, [&] { launch_prefix_bwd_mfma(pl, ws, h->g1, h->g2, B, st); });
     if (rc) return rc;
   } else {
-    const bool mid = any_mid_shape(pl.sh);  // the steps on dPsum in one launch
+    const bool mid = any_mid_takes(pl, B);  // the steps on dPsum in one launch
     rc = run_slot(h, kSlotUBwd, st, [&] {
       if (mid) launch_any_mid(pl, ws, h->g1, h->g2, h->g3, grad_out, B, st);
       else launch_u_bwd(pl, ws, h->g3, grad_out, B, st);
     });
     if (rc) return rc;
     rc = run_slot(h, kSlotDg3, st, [&] {
-      if (any_dg3_shape(pl.sh)) launch_any_dg3(pl, ws, grad_out, B, st);
+      if (any_dg3_takes(pl)) launch_any_dg3(pl, ws, grad_out, B, st);
       else launch_dg3(pl, ws, grad_out, B, st);
     });
     if (rc) return rc;

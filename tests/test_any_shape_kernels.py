@@ -82,3 +82,44 @@ def test_an_infinity_stays_where_it_is():
         assert bad[i[100]] and bad.sum() == 1, k
     emb.close()
     emb2.close()
+
+
+def _slots(n, d, r, B, ids, grad, cores):
+    """Launches of a profiled step: without prefix_bwd the middle of the backward pass was one launch."""
+    emb = TTEmbedding(n, d, r, B, cores, flags=8)
+    emb.profile(True)
+    emb.forward(torch.from_numpy(ids).cuda())
+    emb.backward_update(torch.from_numpy(grad).cuda(), 0.0)
+    slots = {k: v["launches"] for k, v in emb.profile_read().items()}
+    emb.close()
+    return slots
+
+
+# r1 and r2 that fill a run of 4, 8, 12 or 16 indices of each lane group in part, in whole words and not; with
+# many ids per prefix, with one fewer than that, and with few; fused: the middle is one launch (many, few)
+@pytest.mark.parametrize("d,r,fused", [
+    ((4, 5, 5), (20, 28), (1, 1)), ((4, 5, 5), (24, 32), (1, 1)), ((3, 5, 4), (36, 44), (1, 1)),
+    ((4, 4, 4), (44, 36), (1, 1)), ((2, 2, 4), (52, 60), (1, 1)), ((2, 2, 3), (60, 52), (1, 1)),
+    ((4, 5, 5), (30, 31), (1, 1)), ((4, 4, 3), (18, 17), (1, 1)), ((2, 3, 12), (24, 24), (0, 1)),
+    ((2, 3, 12), (33, 32), (0, 0)), ((2, 2, 2), (33, 63), (0, 1)), ((4, 5, 5), (33, 35), (0, 0)),
+    ((3, 7, 2), (48, 56), (0, 0))])
+def test_ranks_between_runs(d, r, fused):
+    for n, B, many in (((33, 34, 9), 8_976, True), ((33, 34, 9), 8_975, False), ((70, 61, 5), 8_999, False)):
+        s, cores, ids, grad = _inputs(n, d, r, B, r[0] + r[1])
+        check_against_oracle(n, d, r, cores, ids, grad, 0.01, flags=8)
+        slots = _slots(n, d, r, B, ids, grad, cores)
+        assert slots["u_bwd"] == slots["dg3"] == 1 and slots["prefix_bwd"] == 1 - fused[0 if many else 1]
+
+
+# What is left to the kernels of tt_emb_compute: more than 32 lines, ranks above 64, d3 above 16, d1 above 16.
+# Prefix gradients with and without the id table (products of up to 64 elements and one line more; lines and ids
+# per prefix on both sides of its rule), staged rows with and without whole words, products cut by columns.
+@pytest.mark.parametrize("d,r", [((17, 2, 3), (4, 1)), ((33, 1, 2), (3, 2)), ((11, 3, 2), (6, 2)), ((5, 1, 33), (6, 4)),
+                                 ((4, 1, 33), (6, 4)), ((5, 1, 33), (3, 13)), ((1, 1, 40), (1, 1)), ((6, 7, 2), (12, 8)),
+                                 ((5, 7, 3), (9, 6)), ((3, 3, 5), (70, 72)), ((3, 3, 5), (66, 67)),
+                                 ((17, 2, 17), (20, 66)), ((4, 9, 5), (65, 68))])
+def test_larger_shapes(d, r):
+    for n, B in (((9, 8, 150), 9_001), ((70, 61, 5), 8_999)):
+        s, cores, ids, grad = _inputs(n, d, r, B, d[0] + r[1])
+        check_against_oracle(n, d, r, cores, ids, grad, 0.01, flags=8)
+        assert _slots(n, d, r, B, ids, grad, cores)["prefix_bwd"] == 1
