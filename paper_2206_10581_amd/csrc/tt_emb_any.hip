@@ -629,6 +629,11 @@ constexpr size_t kAnyLds = 96 * 1024;  // most LDS of a block
 // Which of these kernels a batch takes; the others are those of tt_emb_compute.hip.  Times of a kernel in us,
 // those / these, 60,000 ids: "many" uniform ids of n = 40^3, "few" Zipf ids of 140^3, "fewer" uniform ids of
 // (400,400,30), i.e. 37, 3 and 0.4 per prefix of the table.
+// A launch holds fewer than 2^32 threads: the grid of one that would hold more wraps without an error.  The
+// kernels of tt_emb_compute.hip walk their work with a bounded grid.
+static bool launchable(int64_t blocks, int threads) { return blocks * threads < (int64_t)1 << 32; }
+static int64_t chunks_most(const Plan& pl, int B) { return cdiva(std::min<int64_t>(B, pl.maxQ), kChunk2) + (int64_t)pl.sh.n2; }
+
 static bool many_ids(const Plan& pl, int B) { return B >= 8 * (int64_t)pl.sh.n1 * pl.sh.n2; }
 
 // Against k_u_bwd and k_prefix_bwd together:
@@ -644,7 +649,8 @@ static bool many_ids(const Plan& pl, int B) { return B >= 8 * (int64_t)pl.sh.n1 
 bool any_mid_takes(const Plan& pl, int B) {
   const Shape& s = pl.sh;
   if (s.M > 32 || s.r1 > 64 || s.r2 > 64 || s.d1 > 16 || s.d3 > 32 ||
-      s.D + s.S3 > AnyMidLds::kWords * kWave || AnyMidLds(s).floats() * sizeof(float) > kAnyLds)
+      s.D + s.S3 > AnyMidLds::kWords * kWave || AnyMidLds(s).floats() * sizeof(float) > kAnyLds ||
+      !launchable(chunks_most(pl, B), kAnyWaves * kWave))
     return false;
   const bool wide = std::max(s.r1, s.r2) > 32, words = s.D % 4 == 0 && s.S3 % 4 == 0;
   const int fill = AnyMidLds(s).fill;
@@ -653,14 +659,18 @@ bool any_mid_takes(const Plan& pl, int B) {
 }
 // Better in every form: (4,5,5), rank 32: many 45 / 21, few 28 / 17, fewer 68 / 35; (2,2,2), 4: 15 / 9, 11 / 7,
 // 21 / 11; (4,4,4), 48: 46 / 30, 26 / 20, 66 / 45; (3,7,3), 63: 76 / 45, 39 / 30, 122 / 87.
-bool any_dg3_takes(const Plan& pl) { return pl.sh.r2 <= 64 && pl.sh.d3 <= 16 && pl.sh.M <= 64; }
+bool any_dg3_takes(const Plan& pl, int B) {
+  const Shape& s = pl.sh;
+  return s.r2 <= 64 && s.d3 <= 16 && s.M <= 64 && launchable(cdiva(cdiva(B, chunk3_fill(B)) + (int64_t)s.n3, 4), 256);
+}
 // Ranks that are no multiple of four read lines of G1 element by element.  Few / fewer ids, those, these:
 //   (4,5,5): rank 15 17 / 41, 14 / 31;  24 21 / 55, 18 / 45;  30 27 / 77, 27 / 84;  33 32 / 97, 47 / 165;
 //            40 39 / 124, 28 / 91;  64 56 / 187, 47 / 182
 //   (4,4,4): rank 15 13 / 25, 13 / 25;  28 21 / 54, 17 / 42;  30 21 / 56, 23 / 66;  48 32 / 96, 26 / 85
-bool any_prefix_takes(const Plan& pl) {
+bool any_prefix_takes(const Plan& pl, int B) {
   const Shape& s = pl.sh;
-  return s.d1 <= 16 && (s.r1 <= 16 || (s.r1 <= 64 && s.r1 % 4 == 0));
+  return s.d1 <= 16 && (s.r1 <= 16 || (s.r1 <= 64 && s.r1 % 4 == 0)) &&
+         launchable(chunks_most(pl, B) * cdiva(s.W, 16), kWave);
 }
 // A wavefront stages a product for few rows, or many:
 //   d, r           many       few        fewer
@@ -673,7 +683,7 @@ bool any_prefix_takes(const Plan& pl) {
 //   (2,2,2), 6     18 / 12    18 / 20    23 / 25
 bool any_row_takes(const Plan& pl, int B) {
   const Shape& s = pl.sh;
-  if (s.M > 32 || s.r2 > 64 || s.d3 > 16) return false;
+  if (s.M > 32 || s.r2 > 64 || s.d3 > 16 || !launchable(cdiva(B, 4 * kAnyRowSlots), 256)) return false;
   if (s.r2 <= 4 || (s.r2 <= 32 && s.r2 % 4 == 0)) return true;
   return many_ids(pl, B) && (s.r2 <= 32 || s.r2 % 4 == 0);
 }
@@ -681,7 +691,7 @@ bool any_row_takes(const Plan& pl, int B) {
 void launch_any_mid(const Plan& pl, const Workspace& ws, const float* g1, const float* g2, const float* g3,
                     const float* grad, int B, hipStream_t st) {
   const Shape& s = pl.sh;
-  const int grid = cdiva(std::min<int64_t>(B, pl.maxQ), kChunk2) + (int)s.n2;
+  const int grid = (int)chunks_most(pl, B);
   const size_t lds = AnyMidLds(s).floats() * sizeof(float);
   auto launch = [&](auto kernel) {
     kernel<<<grid, kAnyWaves * kWave, lds, st>>>(s, inverse_of(s.d1), inverse_of(s.d2), g1, g2, g3, grad, ws.gsum,
@@ -717,7 +727,7 @@ void launch_any_dg3(const Plan& pl, const Workspace& ws, const float* grad, int 
 
 void launch_any_prefix(const Plan& pl, const Workspace& ws, const float* g1, const float* g2, int B, hipStream_t st) {
   const Shape& s = pl.sh;
-  const int chunks = cdiva(std::min<int64_t>(B, pl.maxQ), kChunk2) + (int)s.n2, tiles = cdiva(s.W, 16);
+  const int chunks = (int)chunks_most(pl, B), tiles = cdiva(s.W, 16);
   auto launch = [&](auto kernel) {
     kernel<<<chunks * tiles, kWave, 0, st>>>(s, inverse_of(s.d1), tiles, g1, g2, ws.c2_desc, ws.c2_item, ws.P, ws.ctr);
   };

@@ -47,10 +47,10 @@ void launch_bwd_mid_mfma(const Plan&, const Workspace&, const float* g1, const f
                          const float* g3, const float* grad, int B, hipStream_t);
 void launch_gsum_block(const Plan&, const Workspace&, const float* grad, int B, hipStream_t);
 // any-shape kernels on the matrix cores (tt_emb_any.hip)
-bool any_prefix_takes(const Plan&);
+bool any_prefix_takes(const Plan&, int B);
 bool any_row_takes(const Plan&, int B);
 bool any_mid_takes(const Plan&, int B);
-bool any_dg3_takes(const Plan&);
+bool any_dg3_takes(const Plan&, int B);
 void launch_any_prefix(const Plan&, const Workspace&, const float* g1, const float* g2, int B, hipStream_t);
 void launch_any_row(const Plan&, const Workspace&, const float* g3, int B, float* out, hipStream_t);
 void launch_any_mid(const Plan&, const Workspace&, const float* g1, const float* g2, const float* g3,
@@ -745,7 +745,7 @@ static int forward_impl(tt_emb* h, const IdSource& src, int64_t B64, float* out,
   const Workspace& ws = h->ws[h->cur];
   rc = run_slot(h, kSlotPrefixFwd, st, [&] {
     if (h->mfma) launch_prefix_fwd_mfma(pl, ws, h->g1, h->g2, B, st);
-    else if (any_prefix_takes(pl)) launch_any_prefix(pl, ws, h->g1, h->g2, B, st);
+    else if (any_prefix_takes(pl, B)) launch_any_prefix(pl, ws, h->g1, h->g2, B, st);
     else launch_prefix_fwd(pl, ws, h->g1, h->g2, B, st);
   });
   if (rc) return rc;
@@ -950,7 +950,7 @@ static int backward_indexed(tt_emb* h, const float* grad_out, float lr, int B, h
     });
     if (rc) return rc;
     rc = run_slot(h, kSlotDg3, st, [&] {
-      if (any_dg3_takes(pl)) launch_any_dg3(pl, ws, grad_out, B, st);
+      if (any_dg3_takes(pl, B)) launch_any_dg3(pl, ws, grad_out, B, st);
       else launch_dg3(pl, ws, grad_out, B, st);
     });
     if (rc) return rc;
