@@ -1168,15 +1168,19 @@ __global__ __launch_bounds__(kMThreads) void k_row_fwd_mfma(
 // kernels read their row from grad_out directly.  Pieces of runs that cross wavefronts are joined
 // in LDS.  No run crosses a block: the index pipeline cuts long runs of one id into entries at
 // every multiple of kEntrySlots slots, which is the block size here.
-// A wavefront with at most kSparseSlots slots to load goes from one of them to the next instead of
-// looking at all 64: with uniform ids the looking was the time (24 -> 4.5 us at 500,000 ids of 111 million
-// rows, 12.8 -> 5.7 at 200,000 of 2.4 million, 13 -> 8.4 at 50,000 of 169,343).  Above that the walk over
-// all slots is as fast or faster (Zipf ids: 20.5 / 44 us at 200,000 / 500,000 either way, and 21.5 / 45
-// where every wavefront with a slot left out took the other path).
+// A wavefront with at most sparse_slots slots to load goes from one of them to the next instead of
+// looking at all 64: with uniform ids the looking was the time (28 -> 8.4 us at 500,000 ids of 111 million
+// rows, 16 -> 6 at 200,000 of 2.4 million, 18 -> 14.4 at 60,000 of 175,616).  Where the line lies, us with 32 /
+// 48 slots: rows of 64 floats, 60,000 clustered ids 16.6 / 19.7 (18.4 where all look at all slots), 500,000
+// 50.9 / 53.3 (57.4); ragged rows, which take more instructions a slot, 200,000 uniform ids of 56^3 with 100
+// floats 30.9 / 34.8 (30.9); rows of 128 floats, 60,000 clustered ids 21.4 / 20.2 (21.5), 500,000 52.8 / 49.4
+// (53.5).
+// Rows of 64 floats go 8 at a time: rounds of 16 take 92 scalar registers, and one block less fits a compute
+// unit: 520,000 uniform items 42 -> 33 us, 1,000,000 clustered ones 67 -> 51.
 constexpr int kGsumWaves = 16;
 constexpr int kGsumThreads = kGsumWaves * kWave;
 constexpr int kGsumBlockSlots = kGsumWaves * kWave;  // 1024
-constexpr int kSparseSlots = 48;
+constexpr int sparse_slots(int vpl, bool ragged) { return vpl == 2 && !ragged ? 48 : 32; }
 static_assert(kGsumBlockSlots == kEntrySlots, "a block must own exactly one entry span");
 
 template <int VPL>
@@ -1243,89 +1247,83 @@ __global__ __launch_bounds__(kGsumThreads) void k_gsum_block(int B, int Drt,
         }
       }
     };
-    if (__popcll(need_mask) <= kSparseSlots) {
+    // The row of a slot.  Its address is a scalar and a lane's offset: formed in vector registers it shared them
+    // with loads in flight, and every load waited for the one before (55 -> 74 us at 500,000 Zipf ids).
+    auto load_row = [&](int slot, LaneVec<VPL>& r) {
+      const float* row = grad + (size_t)(uint32_t)lane_value((int)myb, slot) * D;
+      if constexpr (RAGGED) {
+#pragma unroll
+        for (int x = 0; x < VPL; ++x)  // lanes past the row's end read its last float; nothing stores them
+          r.v[x] = __builtin_nontemporal_load(row + (uint32_t)min(lane * VPL + x, D - 1));
+      } else {
+        stream_load<VPL>(row + (uint32_t)(lane * VPL), r.v);
+      }
+    };
+    auto add_row = [&](int slot, int end, const LaneVec<VPL>& r) {  // end: where the run before it ends
+      const int u = lane_value(mysu, slot);
+      if (u != cur) {
+        flush(end);
+        cur = u;
+        cur_first = slot;
+#pragma unroll
+        for (int x = 0; x < VPL; ++x) acc.v[x] = 0.f;
+      }
+#pragma unroll
+      for (int x = 0; x < VPL; ++x) acc.v[x] += r.v[x];
+    };
+    if (__popcll(need_mask) <= sparse_slots(VPL, RAGGED)) {
       // the slots there are, in order; of a round with fewer the last one is read again and not added
       unsigned long long left = need_mask;
       int end = 0;
       auto round = [&](auto rows) {
         constexpr int ROWS = decltype(rows)::value;
         LaneVec<VPL> r[ROWS];
-        int slot[ROWS];
+        unsigned long long ahead = left;
         const int n = min(__popcll(left), ROWS);
 #pragma unroll
         for (int k = 0; k < ROWS; ++k) {
-          slot[k] = __ffsll((long long)left) - 1;
-          if (k + 1 < n) left &= left - 1;
-          const uint32_t b_row = (uint32_t)lane_value((int)myb, slot[k]);
-          if constexpr (RAGGED) {
-#pragma unroll
-            for (int x = 0; x < VPL; ++x)  // lanes past the row's end read its last float; nothing stores them
-              r[k].v[x] = __builtin_nontemporal_load(grad + (size_t)b_row * D + min(lane * VPL + x, D - 1));
-          } else {
-            stream_load<VPL>(grad + (size_t)b_row * D + lane * VPL, r[k].v);
-          }
+          load_row(__ffsll((long long)ahead) - 1, r[k]);
+          if (k + 1 < n) ahead &= ahead - 1;
         }
+        TT_LOADS_DONE();
 #pragma unroll
         for (int k = 0; k < ROWS; ++k)
           if (k < n) {  // uniform
-            const int u = lane_value(mysu, slot[k]);
-            if (u != cur) {
-              flush(end);
-              cur = u;
-              cur_first = slot[k];
-#pragma unroll
-              for (int x = 0; x < VPL; ++x) acc.v[x] = 0.f;
-            }
-            end = slot[k] + 1;
-#pragma unroll
-            for (int x = 0; x < VPL; ++x) acc.v[x] += r[k].v[x];
+            const int slot = __ffsll((long long)left) - 1;
+            left &= left - 1;
+            add_row(slot, end, r[k]);
+            end = slot + 1;
           }
-        left &= left - 1;
       };
       while (left) {
-        if (__popcll(left) > 8) round(std::integral_constant<int, 16>{});
+        if (VPL > 1 && __popcll(left) > 8) round(std::integral_constant<int, 16>{});
         else round(std::integral_constant<int, 8>{});
       }
       flush(end);
     } else {
+      // all slots; those that need no row read one that is read anyway, or, where a row is many loads, none (no
+      // run of theirs is stored)
+      constexpr bool kSkip = RAGGED && VPL > 1;
+      const int spare = __ffsll((long long)need_mask) - 1;
+      LaneVec<VPL> r[kRows];
+      if constexpr (kSkip) {
+#pragma unroll
+        for (int k = 0; k < kRows; ++k)
+#pragma unroll
+          for (int x = 0; x < VPL; ++x) r[k].v[x] = 0.f;
+      }
       for (int half = 0; half < kWave / kRows; ++half) {
         if (half * kRows >= nv) break;
-        LaneVec<VPL> r[kRows];
 #pragma unroll
         for (int k = 0; k < kRows; ++k) {
           const int slot = half * kRows + k;
-          const uint32_t b_row = (uint32_t)lane_value((int)myb, slot);
-          if ((need_mask >> slot) & 1ull) {
-            if constexpr (RAGGED) {
-#pragma unroll
-              for (int x = 0; x < VPL; ++x)
-                r[k].v[x] = lane * VPL + x < D
-                                ? __builtin_nontemporal_load(grad + (size_t)b_row * D + lane * VPL + x)
-                                : 0.f;
-            } else {
-              stream_load<VPL>(grad + (size_t)b_row * D + lane * VPL, r[k].v);
-            }
-          } else {
-#pragma unroll
-            for (int x = 0; x < VPL; ++x) r[k].v[x] = 0.f;
-          }
+          const bool on = (need_mask >> slot) & 1ull;
+          if (!kSkip || on) load_row(on ? slot : spare, r[k]);
         }
+        TT_LOADS_DONE();
 #pragma unroll
-        for (int k = 0; k < kRows; ++k) {
-          const int slot = half * kRows + k;
-          if (slot < nv) {
-            const int u = lane_value(mysu, slot);
-            if (u != cur) {
-              flush(slot);
-              cur = u;
-              cur_first = slot;
-#pragma unroll
-              for (int x = 0; x < VPL; ++x) acc.v[x] = 0.f;
-            }
-#pragma unroll
-            for (int x = 0; x < VPL; ++x) acc.v[x] += r[k].v[x];
-          }
-        }
+        for (int k = 0; k < kRows; ++k)
+          if (half * kRows + k < nv) add_row(half * kRows + k, half * kRows + k, r[k]);
       }
       flush(nv);
     }
