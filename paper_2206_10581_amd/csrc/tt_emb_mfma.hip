@@ -1019,8 +1019,11 @@ __global__ __launch_bounds__(WAVES * kWave, 6) void k_bwd_mid_mfma(
 // Zipf ids it is at the rate of random 512-byte stores (27 -> 26 us).
 // Slots of a tile: short ones for short chains of groups (200,000 Zipf ids at rank 32: 26 / 30 / 38 us with
 // 8 / 16 / 32), longer ones where a product is 4 to 8 KiB and neighbours share it (clustered ids at rank
-// 64: 106 / 95 / 92 us; Zipf 98 / 96 / 105).
-constexpr int row_slots(int R) { return R <= 32 ? 8 : 16; }
+// 64: 106 / 95 / 92 us; Zipf 98 / 96 / 105), and for large batches of 64-float rows, four ids a group: 8 / 16
+// slots, 400,000 items of (272,136,136) 35.9 / 34.0 us Zipf ids at rank 16, 59.3 / 53.8 uniform at 32; 1,000,000
+// clustered ones of (960,480,482) 64.8 / 51.0 at 16, 85.6 / 68.5 at 32; 1,000,000 Zipf ones 79.0 / 69.3 at 8.
+// (Up to 131,072 rows 8: 100,000 uniform ids of 136^3 15.2 / 14.7, Zipf 15.4 / 15.9, 20,000 10.7 / 13.7.)
+constexpr int row_slots(int R, int D3, bool large) { return R > 32 || (D3 == 4 && large) ? 16 : 8; }
 // Where the index kernels of a coming batch run beside this one, four times the wavefronts take the compute
 // units from them: 500,000 Zipf ids at rank 16, look-ahead step 344 / 334 / 325 us with 8 / 16 / 32 slots,
 // plain step 385 / 387 / 391; look-ahead at rank 32, 500,000 ids of (480,480,482) and 400,000 of (136,136,136),
@@ -1496,11 +1499,14 @@ void launch_row_fwd_mfma(const Plan& pl, const Workspace& ws, const float* g3, i
   };
 #define TT_ROW(D3_)                                                                                  \
   TT_DISPATCH_R8(pl.sh.r1, {                                                                         \
+    constexpr int kShort = row_slots(R, D3_, false);                                                 \
+    constexpr int kLong = row_slots(R, D3_, true);                                                   \
     if constexpr (R <= 32) {                                                                         \
       if (large) launch(k_row_fwd_mfma<R, D3_, kRowSlotsBeside>, kRowSlotsBeside);                   \
-      else launch(k_row_fwd_mfma<R, D3_, row_slots(R)>, row_slots(R));                               \
+      else if (B > (1 << 17)) launch(k_row_fwd_mfma<R, D3_, kLong>, kLong);                          \
+      else launch(k_row_fwd_mfma<R, D3_, kShort>, kShort);                                           \
     } else {                                                                                         \
-      launch(k_row_fwd_mfma<R, D3_, row_slots(R)>, row_slots(R));                                    \
+      launch(k_row_fwd_mfma<R, D3_, kShort>, kShort);                                                \
     }                                                                                                \
   })
   if (pl.sh.d3 == 4) {
