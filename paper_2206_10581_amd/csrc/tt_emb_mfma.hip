@@ -741,15 +741,25 @@ __global__ __launch_bounds__(kMThreads) void k_id_bwd_mfma(
 // longest prefix sets the time.  With skewed ids one prefix of a chunk has hundreds of ids and the others a
 // few, so the long ones are taken first by the whole block, one after the other, WAVES * SC ids in flight;
 // the wavefronts' sums meet in LDS and are added in their order.  Which are long is the choice that takes
-// the fewest rounds.  With every prefix left to its wavefront the kernel took, Zipf / clustered ids:
-// 182 / 198 us at 500,000 ids of n = (480,480,482), d = (4,4,8), rank 16, now 55 / 113; 29 / 36 at 50,000 of
-// (55,55,56) x (8,4,4), rank 16, now 19 / 27; 50 / 77 at 200,000 of (136,136,136) x (4,4,8), rank 32, now
-// 39 / 79.  Uniform ids: 242 -> 243, 27.6 -> 25, 113 -> 113.
+// the fewest rounds, a long one counted with its barriers and, where it loads twice the ids, as two (at one
+// each, 60,000 clustered ids of 136^3, d = (8,4,4), rank 16 took 79 us, and 500,000 of (480,480,482) 275).
+// The kernel with every prefix left to its wavefront / now, us; Zipf: hot ids together, as in tables renumbered by
+// partition.
+//   n, d, rank, ids                          Zipf        clustered   uniform
+//   (480,480,482), (4,4,8), 16, 500,000      310 /  92   210 / 126   241 / 241
+//   (480,480,482), (4,4,8), 32, 500,000      285 / 191   196 / 147   474 / 470
+//   (480,480,482), (8,4,4), 16, 500,000      376 / 173   278 / 230   420 / 416
+//   (136,136,136), (4,4,8), 32, 200,000       85 /  57    80 /  81   117 / 116
+//   (136,136,136), (8,4,4), 16,  60,000       80 /  40    69 /  60    49 /  49
+//   (55,55,56),    (8,4,4), 16,  50,000       48 /  34    41 /  30    32 /  30
+// The chunk's records wait in LDS for the steps behind (i): in registers they made the form of rank 32 and d3 = 8
+// spill four (uniform ids of the second line 507 us).
 //
 // WAVES: eight.  Four at ranks up to 16 where the batch has fewer than four ids per prefix of the table: a
 // round then is mostly one or two ids a prefix, and two blocks of four hold twice the prefixes (uniform ids
 // of (480,480,482), eight / four wavefronts: 268 / 243 us at 500,000 ids and d = (4,4,8), 170 / 137 at 300,000
-// and (4,4,4); with 37 ids a prefix, n = (40,40,500), 27 / 33).
+// and (4,4,4); with 37 ids a prefix, n = (40,40,500), 27 / 33).  The line is one for all ids: at 13 items a
+// prefix, 250,000 ids of 136^3 with d = (8,4,4), rank 16, clustered ones take 93 / 110, Zipf ones 52 / 49.
 constexpr int kXcds = 8;
 
 template <int R, int D3, int WAVES>
@@ -766,6 +776,7 @@ __global__ __launch_bounds__(WAVES * kWave, 6) void k_bwd_mid_mfma(
   constexpr int TS = W + 4;  // padded row stride of the LDS tiles (keeps 16-byte alignment)
   constexpr int NT16 = (R + 15) / 16, KS = D3 / 4;
   constexpr int kMidThreads = WAVES * kWave, kParts = WAVES * NT16 * 256;
+  __shared__ int q_of[kChunk2], i1_of[kChunk2];  // records of the chunk's prefixes for the steps behind (i)
   __shared__ __align__(16) float T[64 * TS];
   __shared__ __align__(16) float Bl[R * TS > kParts ? R * TS : kParts];  // wavefronts' sums of a long prefix, then Bm
   const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
@@ -789,6 +800,10 @@ __global__ __launch_bounds__(WAVES * kWave, 6) void k_bwd_mid_mfma(
   const int4 desc = c2_desc[c];
   if (c >= ctr->nchunk2) return;
   if (l16 >= desc.z) item = int4{-1, 0, 0, 0};  // records past the chunk's count are unwritten
+  if (tid < kChunk2) {
+    q_of[tid] = item.x;
+    i1_of[tid] = item.y;
+  }
   // Bm is needed behind the barrier only: below rank 32 its words wait in registers, at rank 32 they are
   // loaded behind (i), where registers are free
   const f4* Bm = (const f4*)(g2 + (size_t)desc.x * S2);
@@ -807,6 +822,7 @@ __global__ __launch_bounds__(WAVES * kWave, 6) void k_bwd_mid_mfma(
   // wavefronts of two prefixes take two ids of each where rows are 128 floats).  Lane x holds where the
   // gradient row and the G3 slice of the round's id x are.
   constexpr int SC = R <= 16 && KS == 1 ? 16 : 8, SO = WAVES == 4 || R == 32 || KS == 1 ? 8 : 4;
+  constexpr int kBarriers = KS == 2 ? 1 : R <= 16 ? 4 : 2;
   constexpr bool kAhead = R < 32 || KS == 1;  // registers for the next round's codes
   auto load_ids = [&](int mycode, int myi3, auto& a, auto& b) {
 #pragma unroll
@@ -835,8 +851,9 @@ __global__ __launch_bounds__(WAVES * kWave, 6) void k_bwd_mid_mfma(
   uint32_t longs = 0;  // prefixes taken by the whole block
   if (__ballot(ids > 16)) {
     constexpr int UB = SO * WAVES / 16;
-    // rounds in all if the prefixes with more ids than this lane's are long; one stands for the barriers
-    const int mine = (ids + SC * WAVES - 1) / (SC * WAVES) + 1;
+    // rounds in all if the prefixes with more ids than this lane's are long; kBarriers stands for the barriers and,
+    // where SC is twice SO, for the longer rounds
+    const int mine = (ids + SC * WAVES - 1) / (SC * WAVES) + kBarriers;
     int cost = (ids + UB - 1) / UB;
 #pragma unroll
     for (int k = 0; k < 16; ++k)
@@ -854,10 +871,18 @@ __global__ __launch_bounds__(WAVES * kWave, 6) void k_bwd_mid_mfma(
 #pragma unroll
     for (int nt = 0; nt < NT16; ++nt) acc[nt] = f4{0.f, 0.f, 0.f, 0.f};
     auto id_of = [&](int i0) { return u0 + min(i0 + lane % SC, n - 1); };
-    int mycode = u_code[id_of(w * SC)], myi3 = u_i3[id_of(w * SC)];
+    int mycode = 0, myi3 = 0;
+    if (kAhead) {
+      mycode = u_code[id_of(w * SC)];
+      myi3 = u_i3[id_of(w * SC)];
+    }
     for (int i0 = w * SC; i0 < n; i0 += WAVES * SC) {
-      const int next = id_of(i0 + WAVES * SC);
-      const int next_code = u_code[next], next_i3 = u_i3[next];
+      const int at = id_of(kAhead ? i0 + WAVES * SC : i0);
+      const int next_code = u_code[at], next_i3 = u_i3[at];
+      if (!kAhead) {
+        mycode = next_code;
+        myi3 = next_i3;
+      }
       float a[SC][KS], b[SC][NT16][KS];
       load_ids(mycode, myi3, a, b);
 #pragma unroll
@@ -868,8 +893,10 @@ __global__ __launch_bounds__(WAVES * kWave, 6) void k_bwd_mid_mfma(
 #pragma unroll
             for (int k = 0; k < KS; ++k) acc[nt] = mfma16(a[sl][k], b[sl][nt][k], acc[nt]);
         }
-      mycode = next_code;
-      myi3 = next_i3;
+      if (kAhead) {
+        mycode = next_code;
+        myi3 = next_i3;
+      }
     }
     f4* part = (f4*)Bl;
 #pragma unroll
@@ -968,7 +995,7 @@ __global__ __launch_bounds__(WAVES * kWave, 6) void k_bwd_mid_mfma(
       }
     }
     // accumulator element v: tile row 4*kg + v = prefix 4w + kg, j1 = v; column n = 16*nt + l16
-    const int qv = __shfl(item.x, 4 * w + kg);
+    const int qv = q_of[4 * w + kg];
     if (qv >= 0) {
 #pragma unroll
       for (int nt = 0; nt < NT16; ++nt)
@@ -985,12 +1012,12 @@ __global__ __launch_bounds__(WAVES * kWave, 6) void k_bwd_mid_mfma(
 #pragma unroll
     for (int j = 0; j < 32; ++j) {
       const int ql = 8 * half + j / 4;
-      a[j] = g1[(size_t)__shfl(item.y, ql) * S1 + (j % 4) * R + (l32 < R ? l32 : 0)];
+      a[j] = g1[(size_t)i1_of[ql] * S1 + (j % 4) * R + (l32 < R ? l32 : 0)];
     }
     TT_LOADS_DONE();
 #pragma unroll
     for (int j = 0; j < 32; ++j)
-      if (__shfl(item.x, 8 * half + j / 4) < 0 || l32 >= R) a[j] = 0.f;
+      if (q_of[8 * half + j / 4] < 0 || l32 >= R) a[j] = 0.f;
     const int n = w3 * 32 + l32;
     f16v acc = TT_ZERO16;
 #pragma unroll
