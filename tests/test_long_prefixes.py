@@ -29,4 +29,4 @@ def test_long_and_short_prefixes(n, d, r):
     cores = tuple((rng.standard_normal(c) / np.sqrt(r)).astype(np.float32) for c in s.core_shapes())
     grad = (rng.standard_normal((len(ids), s.D)) / np.sqrt(len(ids))).astype(np.float32)
     order = rng.permutation(len(ids))
-    check_against_oracle(n, d, (r, r), cores, ids[order], grad, 0.01, flags=2)
+    check_against_oracle(n, d, (r, r), cores, ids[order], grad, 0.01, flags=8)
