@@ -1050,13 +1050,23 @@ __global__ __launch_bounds__(WAVES * kWave, 6) void k_bwd_mid_mfma(
 // slots, 400,000 items of (272,136,136) 35.9 / 34.0 us Zipf ids at rank 16, 59.3 / 53.8 uniform at 32; 1,000,000
 // clustered ones of (960,480,482) 64.8 / 51.0 at 16, 85.6 / 68.5 at 32; 1,000,000 Zipf ones 79.0 / 69.3 at 8.
 // (Up to 131,072 rows 8: 100,000 uniform ids of 136^3 15.2 / 14.7, Zipf 15.4 / 15.9, 20,000 10.7 / 13.7.)
-constexpr int row_slots(int R, int D3, bool large) { return R > 32 || (D3 == 4 && large) ? 16 : 8; }
 // Where the index kernels of a coming batch run beside this one, four times the wavefronts take the compute
-// units from them: 500,000 Zipf ids at rank 16, look-ahead step 344 / 334 / 325 us with 8 / 16 / 32 slots,
-// plain step 385 / 387 / 391; look-ahead at rank 32, 500,000 ids of (480,480,482) and 400,000 of (136,136,136),
-// 8 / 32 slots: 499 / 489 and 255 / 247.  (Ids whose order keeps hot ones together: 324 / 334 at rank 16.)  Batches of up to 262,144 rows keep the short tiles (200,000 at rank 32: 124 us
-// in the look-ahead loop, 126 with 16 slots before).
-constexpr int kRowSlotsBeside = 32;
+// units from them (look-ahead steps in us, each loop a process of its own):
+//   ids, n, rank                                8 / 16 / 32 slots
+//   500,000 Zipf, (480,480,482), 16              - / 345 / 336
+//   500,000 Zipf, (480,480,482), 8               - / 272 / 264
+//   500,000 Zipf, (136,136,136), 32              - / 266 / 259
+//   250,000 Zipf, (480,480,482), 8             171 / 165 / 162
+//   200,000 Zipf, (480,480,482), 8             144 / 141 / 140
+//   200,000 Zipf, hot ids together, the same   177 / 184 / 199
+//   200,000 Zipf, (136,136,136), 32            140 / 140 / 143
+//   140,000 Zipf, (480,480,482), 32            247 / 251 / 255
+constexpr int kRowsSome = 1 << 17, kRowsMany = 1 << 18;
+__host__ constexpr int row_slots(int R, int D3, bool beside, int B) {
+  if (R > 32) return 16;
+  if (beside && B > kRowsMany) return 32;
+  return B > kRowsSome && (D3 == 4 || (beside && R <= 16)) ? 16 : 8;
+}
 
 template <int R, int D3, int TSL>
 __global__ __launch_bounds__(kMThreads) void k_row_fwd_mfma(
@@ -1520,20 +1530,18 @@ void launch_bwd_mid_mfma(const Plan& pl, const Workspace& ws, const float* g1, c
 
 void launch_row_fwd_mfma(const Plan& pl, const Workspace& ws, const float* g3, int B, bool beside, float* out,
                          hipStream_t st) {
-  const bool large = beside && pl.sh.r1 <= 32 && B > (1 << 18);
-  auto launch = [&](auto kernel, int slots) {
+  const int slots = row_slots(pl.sh.r1, pl.sh.d3, beside, B);
+  auto launch = [&](auto kernel) {
     kernel<<<cdivi(cdivi(B, slots), kMWaves), kMThreads, 0, st>>>(B, g3, ws.P, ws.s_rec, out, ws.ctr);
   };
 #define TT_ROW(D3_)                                                                                  \
   TT_DISPATCH_R8(pl.sh.r1, {                                                                         \
-    constexpr int kShort = row_slots(R, D3_, false);                                                 \
-    constexpr int kLong = row_slots(R, D3_, true);                                                   \
     if constexpr (R <= 32) {                                                                         \
-      if (large) launch(k_row_fwd_mfma<R, D3_, kRowSlotsBeside>, kRowSlotsBeside);                   \
-      else if (B > (1 << 17)) launch(k_row_fwd_mfma<R, D3_, kLong>, kLong);                          \
-      else launch(k_row_fwd_mfma<R, D3_, kShort>, kShort);                                           \
+      if (slots == 8) launch(k_row_fwd_mfma<R, D3_, 8>);                                             \
+      else if (slots == 16) launch(k_row_fwd_mfma<R, D3_, 16>);                                      \
+      else launch(k_row_fwd_mfma<R, D3_, 32>);                                                       \
     } else {                                                                                         \
-      launch(k_row_fwd_mfma<R, D3_, kShort>, kShort);                                                \
+      launch(k_row_fwd_mfma<R, D3_, 16>);                                                            \
     }                                                                                                \
   })
   if (pl.sh.d3 == 4) {

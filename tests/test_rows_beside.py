@@ -16,7 +16,7 @@ def test_rows_of_prepared_batches(r, d3):
     shapes = ((n[0], 4, r), (n[1], r, 4, r), (n[2], r, d3))
     cores = [(rng.standard_normal(s) / np.sqrt(r)).astype(np.float32) for s in shapes]
     emb = TTEmbedding(n, d, (r, r), most, cores)
-    for B in (262_144, 262_145, most):
+    for B in (131_072, 131_073, 262_144, 262_145, most):
         ids = rng.integers(0, n[0] * n[1] * n[2], B)
         ids[: B // 4] = 59_999
         ids[B // 2: B // 2 + 3] = [-1, 60_000, 1 << 40]
