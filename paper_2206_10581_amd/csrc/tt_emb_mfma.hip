@@ -150,14 +150,17 @@ __global__ __launch_bounds__(kWave) void k_prefix_fwd_mfma(
 // the rate of the matrix cores to count.  An fp32 number is the sum of three bf16 numbers (8 + 8 + 8
 // significant bits, each rounded to nearest), and bf16 products run sixteen times as fast as fp32 ones, so
 // a product of two such sums is formed as its six largest terms: hi*hi, hi*mid, mid*hi, mid*mid, hi*lo,
-// lo*hi, each exact and added up in fp32.  What is left out is below 2^-25 of a term and of either sign;
+// lo*hi, each exact and added up in fp32.  What is left out is at most 2^-24.2 of a term (rms 2^-27.5), of
+// either sign;
 // the error against 64 bits is that of the fp32 instructions or less (relative 2-norms, fp32 -> this: rank
 // 128, 20,000 uniform ids of (60,50,40) x (8,4,4), rows 2.87e-7 -> 2.61e-7, G1 4.30e-7 -> 4.16e-7, G2 1.83e-7 ->
 // 1.59e-7, G3 3.26e-7 -> 2.98e-7; with all numbers of one sign 1.72e-7 -> 1.72e-7 and 6.8e-8 -> 6.2e-8 for G2).
 //
 // Splits do not hold for infinities, for numbers that round up to one, and for numbers so small that their
-// lower parts leave the range of bf16.  Such an operand leaves NaN, an infinity or a very small number in
-// the result (recheck); a wavefront that finds one forms its tile anew with fp32 instructions.
+// lower parts leave the range of bf16 (below 2^-102 and not zero).  The first two leave NaN or an infinity in the
+// result, and so that products stay in range it is looked at for very small numbers as well (recheck); the last
+// are found where they are split (some_inexact).  A wavefront that finds either forms its tile anew with fp32
+// instructions.
 typedef __bf16 h2 __attribute__((ext_vector_type(2)));
 typedef __bf16 h4 __attribute__((ext_vector_type(4)));
 typedef __bf16 h8 __attribute__((ext_vector_type(8)));
@@ -195,8 +198,36 @@ __device__ __forceinline__ f16v mfma_split(const Split<h8>& a, const Split<h8>& 
   acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi, b.mid, acc, 0, 0, 0);
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi, b.hi, acc, 0, 0, 0);
 }
-// Whether some entry is not finite, or below 2^-80 and not zero: all finite operands whose splits are not
-// exact are below 2^-102 (or round to an infinity), and make an entry that large only with factors of 2^22.
+// Whether one of N operands is below 2^-102 and not zero.  Half an instruction each (the smallest magnitude of all
+// in pairs) unless one is that small or zero; compared one by one they cost the kernels 3 to 5 %.
+constexpr float kExactFrom = 0x1p-102f;
+template <int N>
+__device__ __forceinline__ bool some_inexact(const float* v) {
+  static_assert(N % 2 == 0, "in pairs");
+  float least = kExactFrom;
+#pragma unroll
+  for (int i = 0; i < N; i += 2) asm("v_min3_f32 %0, |%1|, |%2|, %0" : "+v"(least) : "v"(v[i]), "v"(v[i + 1]));
+  bool found = false;
+  if (least < kExactFrom) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) found |= v[i] != 0.f && fabsf(v[i]) < kExactFrom;
+  }
+  return found;
+}
+// The same without a branch, from the leading parts of operands that come step by step: least keeps the smallest,
+// as twice its bits less one (zero: the largest).  Numbers below 2^-134, whose leading part is zero, count as zero.
+// (Tested at every step like the others, the product's loads had to come before its first split: 5 %, this 1 to
+// 2 %.)
+typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+typedef unsigned short us4 __attribute__((ext_vector_type(4)));
+constexpr uint32_t kSmallHi = ((127u - 102u) << 8);
+__device__ __forceinline__ us2 see_small(h4 hi, us2 least) {
+  const us4 u = __builtin_bit_cast(us4, hi);
+  const us4 k = u * (unsigned short)2 - (unsigned short)1;
+  const us2 a = {k.x, k.y}, b = {k.z, k.w};
+  return __builtin_elementwise_min(__builtin_elementwise_min(a, b), least);
+}
+// Whether some entry is not finite, or below 2^-80 and not zero.
 __device__ __forceinline__ bool recheck(const f16v& acc) {
   uint32_t most = 0u, least = ~0u;  // of the magnitudes, of those that are not zero less one
 #pragma unroll
@@ -228,7 +259,7 @@ __global__ __launch_bounds__(kMThreads, 3) void k_prefix_fwd_wide(
   constexpr int UN = W / 128;  // blocks side by side over the columns
   constexpr int AS = R + 8, PL = 64 * AS;  // stride of a line and of a plane in LDS
   __shared__ __align__(16) __bf16 As[3 * PL];
-  __shared__ int q_of[kChunk2], i1_of[kChunk2];
+  __shared__ int q_of[kChunk2], i1_of[kChunk2], inexact;
   const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave, half = lane / 32, l32 = lane % 32;
   const int nunit = ctr->nchunk2 * UN;
   for (int unit = blockIdx.x; unit < nunit; unit += gridDim.x) {
@@ -242,6 +273,7 @@ __global__ __launch_bounds__(kMThreads, 3) void k_prefix_fwd_wide(
       q_of[tid] = item.x;
       i1_of[tid] = item.y;
     }
+    if (tid == 0) inexact = 0;
     const float* Bm = g2 + (size_t)desc.x * S2 + col;
     float b[KT][8];
 #pragma unroll
@@ -257,6 +289,8 @@ __global__ __launch_bounds__(kMThreads, 3) void k_prefix_fwd_wide(
       row[i] = ((const f4*)(g1 + (size_t)wave_value(i1_of[e / R]) * S1))[e % R];
     }
     TT_LOADS_DONE();
+    if (some_inexact<R / 4>((const float*)row)) inexact = 1;
+    const bool small_cols = __ballot(some_inexact<KT * 8>(&b[0][0])) != 0ull;
 #pragma unroll
     for (int i = 0; i < R / 16; ++i) {
       const int e = (tid + i * kMThreads) * 4;
@@ -279,7 +313,7 @@ __global__ __launch_bounds__(kMThreads, 3) void k_prefix_fwd_wide(
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
       if (mt * 8 >= cnt) break;
-      if (recheck(acc[mt])) {
+      if (recheck(acc[mt]) || small_cols || inexact) {
         const float* ar = g1 + (size_t)i1_of[mt * 8 + l32 / 4] * S1 + (l32 % 4) * R + half * (R / 2);
         const float* br = Bm + (size_t)(half * (R / 2)) * W;
         acc[mt] = TT_ZERO16;
@@ -321,7 +355,7 @@ __global__ __launch_bounds__(kMThreads, 2) void k_prefix_bwd_wide(
   constexpr int TS = 64 + 8;           // stride of a column of G1 in LDS
   constexpr int PL2 = R * TS, PL1 = (64 + R) * KS, kLds = 3 * (PL2 > PL1 ? PL2 : PL1);
   __shared__ __align__(16) __bf16 L[kLds];
-  __shared__ int q_of[kChunk2], i1_of[kChunk2];
+  __shared__ int q_of[kChunk2], i1_of[kChunk2], inexact;
   const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave, half = lane / 32, l32 = lane % 32;
   const int nchunk = ctr->nchunk2, grp = wide_group(nchunk, R);
   const int per_group = UN + grp, nunit = (nchunk + grp - 1) / grp * per_group;
@@ -333,6 +367,7 @@ __global__ __launch_bounds__(kMThreads, 2) void k_prefix_bwd_wide(
       q_of[tid] = item.x;
       i1_of[tid] = item.y;
     }
+    if (tid == 0) inexact = 0;
     __syncthreads();
   };
   for (int unit = blockIdx.x; unit < nunit; unit += gridDim.x) {
@@ -366,16 +401,17 @@ __global__ __launch_bounds__(kMThreads, 2) void k_prefix_bwd_wide(
         for (int i = 0; i < R / 32; ++i) {
           const int k8 = wave_value((tid + i * kMThreads) / R);
 #pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const int t = k8 / 2 * 4 + j / 2;
-            const float v = (g1 + (size_t)wave_value(i1_of[t]) * S1 + (k8 % 2 * 2 + j % 2) * R)[ao];
-            a[i][j] = t < cnt ? v : 0.f;
-          }
+          for (int j = 0; j < 8; ++j)
+            a[i][j] = (g1 + (size_t)wave_value(i1_of[k8 / 2 * 4 + j / 2]) * S1 + (k8 % 2 * 2 + j % 2) * R)[ao];
         }
         TT_LOADS_DONE();
+        if (some_inexact<R / 4>(&a[0][0])) inexact = 1;
+        const bool small_cols = __ballot(some_inexact<32>(&b[0][0])) != 0ull;
 #pragma unroll
         for (int i = 0; i < R / 32; ++i) {
           const int k8 = wave_value((tid + i * kMThreads) / R);
+#pragma unroll
+          for (int j = 0; j < 8; ++j) a[i][j] = k8 / 2 * 4 + j / 2 < cnt ? a[i][j] : 0.f;
           const Split<h8> x = split_eight(a[i]);
           __bf16* to = L + tid % R * TS + k8 * 8;
           *(h8*)to = x.hi;
@@ -393,7 +429,7 @@ __global__ __launch_bounds__(kMThreads, 2) void k_prefix_bwd_wide(
           for (int t = 0; t < 4; ++t)
             if (4 * t < cnt)  // uniform: else no prefix of this step
               acc = mfma_split(split_from<PL2>(L + (mt * 32 + l32) * TS + 16 * t + 8 * half), y[t], acc);
-          if (recheck(acc)) {
+          if (recheck(acc) || small_cols || inexact) {
             acc = TT_ZERO16;
             for (int k = half; k < 4 * cnt; k += 2)
               acc = mfma32(g1[(size_t)i1_of[k / 4] * S1 + (k % 4) * R + mt * 32 + l32],
@@ -445,6 +481,7 @@ __global__ __launch_bounds__(kMThreads, 2) void k_prefix_bwd_wide(
 #pragma unroll
       for (int x = 0; x < MW; ++x) acc[x] = TT_ZERO16;
       fetch(0);
+      us2 least = {0xffff, 0xffff};
 #pragma unroll 1
       for (int k0 = 0; k0 < W; k0 += KD) {
         if (k0 > 0) __syncthreads();
@@ -454,6 +491,7 @@ __global__ __launch_bounds__(kMThreads, 2) void k_prefix_bwd_wide(
           *(h4*)to = x.hi;
           *(h4*)(to + PL1) = x.mid;
           *(h4*)(to + 2 * PL1) = x.lo;
+          least = see_small(x.hi, least);
         };
 #pragma unroll
         for (int i = 0; i < 2; ++i) put(0, tid + i * kMThreads, ra[i]);
@@ -470,10 +508,12 @@ __global__ __launch_bounds__(kMThreads, 2) void k_prefix_bwd_wide(
             acc[x] = mfma_split(split_from<PL1>(L + ((mt0 + x) * 32 + l32) * KS + 16 * t + 8 * half), y, acc[x]);
         }
       }
+      if (least.x < kSmallHi || least.y < kSmallHi) inexact = 1;
+      __syncthreads();
 #pragma unroll
       for (int x = 0; x < MW; ++x) {
         const int mt = mt0 + x;
-        if (mt * 8 < cnt && recheck(acc[x])) {
+        if (mt * 8 < cnt && (recheck(acc[x]) || inexact)) {
           const float* ar = dPsum + (size_t)q_of[mt * 8 + l32 / 4] * PN + (l32 % 4) * W + half * (W / 2);
           const float* br = Bm + (size_t)(nt * 32 + l32) * W + half * (W / 2);
           acc[x] = TT_ZERO16;

@@ -41,23 +41,49 @@ def _ref(cores, ids, grad, r):
     return out.detach().numpy(), [c.grad.numpy() for c in (c1, c2, c3)]
 
 
+def _check_steps(old, new, ref, lr):
+    """The steps the cores took, recovered from them.  2e-6: sums of at most 900 * 64 terms of random signs, whose
+    roundings add up to a few 2^-24, and the rounding of the core that the step is added to."""
+    for o, g, x in zip(old, ref, new):
+        step = lr * g
+        assert np.linalg.norm((o.astype(np.float64) - x) - step) <= 2e-6 * max(np.linalg.norm(step), np.linalg.norm(o))
+        assert np.linalg.norm(step) >= 0.2 * np.linalg.norm(o)      # (the bound is one on the step)
+
+
 @pytest.mark.parametrize("r", [64, 128])
-@pytest.mark.parametrize("scale", [1.0, 2.0 ** -100, 2.0 ** -118, 2.0 ** 60])
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** -100, 2.0 ** -110, 2.0 ** -118, 2.0 ** 60])
 def test_scaled_gradients(r, scale):
-    """Gradients of G1 and G2 follow the scale of the upstream gradients down to the end of the normal range.
-    1e-6: the sums have at most 900 * 64 terms of random signs, their roundings add up to a few 2^-24."""
+    """Gradients of G1 and G2 keep their accuracy down to the end of the normal range, where the lower parts of
+    their operands are no bf16 numbers any more.  (The leading part alone is off by 2^-10 of a step.)"""
     cores, ids, grad = _case(r)
     grad *= np.float32(scale)
     old = [c.copy() for c in cores]
-    # the step is added to cores of zero where it would not show: take the gradient from two steps' difference
-    lr = float(2.0 ** 100) if scale < 1 else 1.0
-    _, new = _gpu(cores, ids, grad, r, lr)
+    _, new = _gpu(cores, ids, grad, r, 1.0 / scale)
     _, ref = _ref(cores, ids, grad, r)
-    for o, g, x in zip(old, ref, new):
-        want = o.astype(np.float64) - lr * g
-        assert np.linalg.norm(x - want) <= 1e-6 * max(np.linalg.norm(want), np.linalg.norm(lr * g))
-        if scale == 2.0 ** -100:
-            assert np.linalg.norm((o - x) - lr * g) <= 2e-6 * np.linalg.norm(lr * g)
+    _check_steps(old, new, ref, 1.0 / scale)
+
+
+@pytest.mark.parametrize("r", [64, 128])
+@pytest.mark.parametrize("small,large", [(-106, 40), (-112, 60), (-118, 80), (-124, 100)])
+def test_small_numbers_with_large_factors(r, small, large):
+    """Small operands whose products are ordinary numbers: nothing in the results tells of the parts they lost."""
+    cores, ids, grad = _case(r, 3)
+    # prefix products: G1 small, G2 large, and the other way round
+    for k in (0, 1):
+        c = [x.copy() for x in cores]
+        c[k] *= np.float32(2.0 ** small)
+        c[1 - k] *= np.float32(2.0 ** large)
+        out, _ = _gpu(c, ids, grad, r, 0.0)
+        want = _ref(c, ids, grad, r)[0]
+        assert np.linalg.norm(out - want) <= 1e-6 * np.linalg.norm(want)
+    # gradients of one core: small dPsum times a large core, step by step in units of its own
+    for k in (0, 1):
+        c, g = [x.copy() for x in cores], grad * np.float32(2.0 ** small)
+        c[1 - k] *= np.float32(2.0 ** large)
+        lr = 2.0 ** -(small + large)
+        _, new = _gpu(c, ids, g, r, lr)
+        _, ref = _ref(c, ids, g, r)
+        _check_steps([c[k]], [new[k]], [ref[k]], lr)
 
 
 @pytest.mark.parametrize("r", [64, 128])
