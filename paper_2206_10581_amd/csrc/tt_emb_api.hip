@@ -329,6 +329,7 @@ struct tt_emb {
   int cur;            // set of the latest forward with index structures (and of its backward)
   int step;           // entry of done[] of the latest forward: cur, or for the index-free kernels, which
                       // take no set, one of kSets entries behind the sets' own, in turn
+  int direct_step;    // the latest of those
   float *g1, *g2, *g3;
   const int32_t* reindex;  // old id -> table row applied in front of the split, or nullptr
   UpdateRule ada;          // kind kUpdateSgd: plain SGD
@@ -424,7 +425,7 @@ static void init_handle(tt_emb* h, const tt_emb_config* cfg, const Plan& pl, flo
                         float* g3) {
   h->cfg = *cfg;
   h->plan = pl;
-  h->cur = h->step = 0;
+  h->cur = h->step = h->direct_step = 0;
   for (int i = 0; i < kSets; ++i) h->side[i] = nullptr;
   h->ev_fork = nullptr;
   for (int i = 0; i < 2 * kSets; ++i) {
@@ -694,7 +695,8 @@ static int forward_impl(tt_emb* h, const IdSource& src, int64_t B64, float* out,
   h->direct = B <= (arm ? pl.direct_train_cap : pl.direct_cap);
   h->lookup = false;
   if (h->direct) {
-    h->step = h->step < kSets ? kSets : kSets + (h->step + 1) % kSets;
+    h->direct_step = (h->direct_step + 1) % kSets;  // goes on over steps of the other kind in between
+    h->step = kSets + h->direct_step;
     h->done_valid[h->step] = false;
     rc = run_slot(h, kSlotDirectFwd, st, [&] {
       launch_direct_fwd(pl, h->ws[0].direct, src, B, h->g1, h->g2, h->g3, out, arm, st);
