@@ -341,6 +341,7 @@ __global__ __launch_bounds__(NT) void k_sort_hist(
     if (gtid == 0) {
       ctr->err = 0;
       ctr->n_split = 0;
+      ctr->small = 0;
     }
   }
   for (int i = tid; i < bins; i += NT) h[i] = 0u;

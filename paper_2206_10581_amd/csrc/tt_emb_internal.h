@@ -152,6 +152,7 @@ struct Counters {
   int nchunk2;  // partial-sum chunks over the by-i2 grouping of unique prefixes
   int err;      // nonzero: a kernel met an impossible index (bit mask of sites)
   int n_split;  // entries beyond the first of their id (U - n_split distinct ids)
+  int small;    // ranks 64 and 128: an operand of the prefix kernels is below 2^-102 and not zero
 };
 
 // Scratch of the index-free kernels for small batches (tt_emb_direct.hip), sized for

@@ -159,8 +159,9 @@ __global__ __launch_bounds__(kWave) void k_prefix_fwd_mfma(
 // Splits do not hold for infinities, for numbers that round up to one, and for numbers so small that their
 // lower parts leave the range of bf16 (below 2^-102 and not zero).  The first two leave NaN or an infinity in the
 // result, and so that products stay in range it is looked at for very small numbers as well (recheck); the last
-// are found where they are split (some_inexact).  A wavefront that finds either forms its tile anew with fp32
-// instructions.
+// are found before they are split (some_inexact).  A wavefront that finds either forms its tile anew with fp32
+// instructions.  The gradient kernel is bound by the vector ALUs and looks for small operands only if the forward
+// has met one in the cores or u_bwd_role in dPsum (Counters::small); looking always cost it 7 %.
 typedef __bf16 h2 __attribute__((ext_vector_type(2)));
 typedef __bf16 h4 __attribute__((ext_vector_type(4)));
 typedef __bf16 h8 __attribute__((ext_vector_type(8)));
@@ -199,7 +200,7 @@ __device__ __forceinline__ f16v mfma_split(const Split<h8>& a, const Split<h8>& 
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi, b.hi, acc, 0, 0, 0);
 }
 // Whether one of N operands is below 2^-102 and not zero.  Half an instruction each (the smallest magnitude of all
-// in pairs) unless one is that small or zero; compared one by one they cost the kernels 3 to 5 %.
+// in pairs) unless one is that small or zero.
 constexpr float kExactFrom = 0x1p-102f;
 template <int N>
 __device__ __forceinline__ bool some_inexact(const float* v) {
@@ -213,19 +214,6 @@ __device__ __forceinline__ bool some_inexact(const float* v) {
     for (int i = 0; i < N; ++i) found |= v[i] != 0.f && fabsf(v[i]) < kExactFrom;
   }
   return found;
-}
-// The same without a branch, from the leading parts of operands that come step by step: least keeps the smallest,
-// as twice its bits less one (zero: the largest).  Numbers below 2^-134, whose leading part is zero, count as zero.
-// (Tested at every step like the others, the product's loads had to come before its first split: 5 %, this 1 to
-// 2 %.)
-typedef unsigned short us2 __attribute__((ext_vector_type(2)));
-typedef unsigned short us4 __attribute__((ext_vector_type(4)));
-constexpr uint32_t kSmallHi = ((127u - 102u) << 8);
-__device__ __forceinline__ us2 see_small(h4 hi, us2 least) {
-  const us4 u = __builtin_bit_cast(us4, hi);
-  const us4 k = u * (unsigned short)2 - (unsigned short)1;
-  const us2 a = {k.x, k.y}, b = {k.z, k.w};
-  return __builtin_elementwise_min(__builtin_elementwise_min(a, b), least);
 }
 // Whether some entry is not finite, or below 2^-80 and not zero.
 __device__ __forceinline__ bool recheck(const f16v& acc) {
@@ -253,7 +241,7 @@ __device__ __forceinline__ Split<h8> split_from(const __bf16* at) {
 template <int R>
 __global__ __launch_bounds__(kMThreads, 3) void k_prefix_fwd_wide(
     const float* __restrict__ g1, const float* __restrict__ g2, const int4* __restrict__ c2_item,
-    const int4* __restrict__ c2_desc, float* __restrict__ P, const Counters* __restrict__ ctr) {
+    const int4* __restrict__ c2_desc, float* __restrict__ P, Counters* __restrict__ ctr) {
   static_assert(R == 64 || R == 128, "columns of a block divide the product");
   constexpr int W = 4 * R, PN = 16 * R, S1 = 4 * R, S2 = R * W, KT = R / 16;
   constexpr int UN = W / 128;  // blocks side by side over the columns
@@ -290,7 +278,6 @@ __global__ __launch_bounds__(kMThreads, 3) void k_prefix_fwd_wide(
     }
     TT_LOADS_DONE();
     if (some_inexact<R / 4>((const float*)row)) inexact = 1;
-    const bool small_cols = __ballot(some_inexact<KT * 8>(&b[0][0])) != 0ull;
 #pragma unroll
     for (int i = 0; i < R / 16; ++i) {
       const int e = (tid + i * kMThreads) * 4;
@@ -300,7 +287,9 @@ __global__ __launch_bounds__(kMThreads, 3) void k_prefix_fwd_wide(
       *(h4*)(to + PL) = x.mid;
       *(h4*)(to + 2 * PL) = x.lo;
     }
+    const bool small_cols = __ballot(some_inexact<KT * 8>(&b[0][0])) != 0ull;
     __syncthreads();
+    if ((small_cols || inexact) && lane == 0) atomicOr(&ctr->small, 1);
     f16v acc[2] = {TT_ZERO16, TT_ZERO16};
     const bool two = cnt > 8;  // uniform: the second tile has a prefix
 #pragma unroll
@@ -358,6 +347,7 @@ __global__ __launch_bounds__(kMThreads, 2) void k_prefix_bwd_wide(
   __shared__ int q_of[kChunk2], i1_of[kChunk2], inexact;
   const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave, half = lane / 32, l32 = lane % 32;
   const int nchunk = ctr->nchunk2, grp = wide_group(nchunk, R);
+  const bool look = ctr->small != 0;  // for small operands
   const int per_group = UN + grp, nunit = (nchunk + grp - 1) / grp * per_group;
   // records of chunk c; those past its count are unwritten and repeat the last one
   auto chunk_records = [&](int c, int cnt) {
@@ -405,8 +395,7 @@ __global__ __launch_bounds__(kMThreads, 2) void k_prefix_bwd_wide(
             a[i][j] = (g1 + (size_t)wave_value(i1_of[k8 / 2 * 4 + j / 2]) * S1 + (k8 % 2 * 2 + j % 2) * R)[ao];
         }
         TT_LOADS_DONE();
-        if (some_inexact<R / 4>(&a[0][0])) inexact = 1;
-        const bool small_cols = __ballot(some_inexact<32>(&b[0][0])) != 0ull;
+        if (look && some_inexact<R / 4>(&a[0][0])) inexact = 1;
 #pragma unroll
         for (int i = 0; i < R / 32; ++i) {
           const int k8 = wave_value((tid + i * kMThreads) / R);
@@ -418,6 +407,7 @@ __global__ __launch_bounds__(kMThreads, 2) void k_prefix_bwd_wide(
           *(h8*)(to + PL2) = x.mid;
           *(h8*)(to + 2 * PL2) = x.lo;
         }
+        const bool small_cols = look && __ballot(some_inexact<32>(&b[0][0])) != 0ull;
         Split<h8> y[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) y[t] = split_eight(b[t]);
@@ -481,17 +471,16 @@ __global__ __launch_bounds__(kMThreads, 2) void k_prefix_bwd_wide(
 #pragma unroll
       for (int x = 0; x < MW; ++x) acc[x] = TT_ZERO16;
       fetch(0);
-      us2 least = {0xffff, 0xffff};
 #pragma unroll 1
       for (int k0 = 0; k0 < W; k0 += KD) {
         if (k0 > 0) __syncthreads();
+        if (look && (some_inexact<8>((const float*)ra) || some_inexact<R / 8>((const float*)rb))) inexact = 1;
         auto put = [&](int line, int e, f4 v) {
           const Split<h4> x = split_four(v);
           __bf16* to = L + (line + e / (KD / 4)) * KS + e % (KD / 4) * 4;
           *(h4*)to = x.hi;
           *(h4*)(to + PL1) = x.mid;
           *(h4*)(to + 2 * PL1) = x.lo;
-          least = see_small(x.hi, least);
         };
 #pragma unroll
         for (int i = 0; i < 2; ++i) put(0, tid + i * kMThreads, ra[i]);
@@ -508,8 +497,6 @@ __global__ __launch_bounds__(kMThreads, 2) void k_prefix_bwd_wide(
             acc[x] = mfma_split(split_from<PL1>(L + ((mt0 + x) * 32 + l32) * KS + 16 * t + 8 * half), y, acc[x]);
         }
       }
-      if (least.x < kSmallHi || least.y < kSmallHi) inexact = 1;
-      __syncthreads();
 #pragma unroll
       for (int x = 0; x < MW; ++x) {
         const int mt = mt0 + x;
@@ -538,7 +525,7 @@ template <int R, int D3>
 __device__ __forceinline__ void u_bwd_role(
     int block, int nblocks, const float* __restrict__ g3, const float* __restrict__ grad,
     const float* __restrict__ gsum, const int* __restrict__ u_code, const int* __restrict__ u_i3,
-    const int* __restrict__ q_us, float* __restrict__ dPsum, const Counters* __restrict__ ctr) {
+    const int* __restrict__ q_us, float* __restrict__ dPsum, Counters* __restrict__ ctr) {
   constexpr int PN = 16 * R, S3 = R * D3, D = 16 * D3, NT = R / 16, KS = D3 / 4, UB = 4;
   const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   const int l16 = lane % 16, kg = lane / 16;
@@ -583,6 +570,7 @@ __device__ __forceinline__ void u_bwd_role(
         for (; i0 + 16 <= n; i0 += 16) round(std::integral_constant<int, 16>{}, i0);
       for (; i0 < n; i0 += UB) round(std::integral_constant<int, UB>{}, i0);
     }
+    if (__ballot(some_inexact<4 * NT>((const float*)acc)) && lane == 0) atomicOr(&ctr->small, 1);
     float* dst = dPsum + (size_t)q * PN;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
@@ -757,7 +745,7 @@ __global__ __launch_bounds__(kMThreads) void k_id_bwd_mfma(
     const float* __restrict__ gsum, const int* __restrict__ u_code, const int* __restrict__ u_i3,
     const int* __restrict__ q_us, const int2* __restrict__ c3_item,
     const int4* __restrict__ c3_desc, float* __restrict__ dPsum, float* __restrict__ part3,
-    const Counters* __restrict__ ctr) {
+    Counters* __restrict__ ctr) {
   const int role = blockIdx.x & 1, block = blockIdx.x >> 1, nblocks = gridDim.x >> 1;
   if (role == 0)
     u_bwd_role<R, D3>(block, nblocks, g3, grad, gsum, u_code, u_i3, q_us, dPsum, ctr);
