@@ -923,18 +923,21 @@ void launch_gsum_fix(const Plan& pl, const Workspace& ws, int B, hipStream_t st)
 
 // Where rows lie in a table and operands are fetched ahead (see k_u_bwd), a wavefront needs 113 registers
 // instead of 66 and loads a whole tile's worth at once; products of up to 64 elements whose prefixes have
-// few ids do not repay that.  Times of the kernel with and without, 200,000 uniform ids, us (taken with
-// shapes that have since gone to k_any_mid; what is left here has more rows or higher ranks):
-//   d, r                      n = (3000,400,20): 1 id each    n = (40,40,40): 55 ids each
-//   (2,2,2), 4                219 / 145                       17 / 17
-//   (2,2,2), 16               218 / 177                       21 / 21
-//   (4,4,4), 4                220 / 189                       25 / 36
-//   (4,4,4), 12               236 / 259                       25 / 40
-//   (4,5,5), 32               288 / 434                       32 / 90
-// (4,4,4), 4 with three ids each: 91 / 81.
+// few ids do not repay that.  Times of the kernel with and without, 60,000 ids, us, of shapes that k_any_mid leaves
+// here: uniform ids of 40^3 (37 per prefix of the table), Zipf ids of 140^3 (3), uniform of (400,400,30) (0.4):
+//   d, r               37           3          0.4
+//   (17,2,3), 1        28 /  54     36 / 39    111 / 105
+//   (33,1,2), 2        22 /  39     36 / 36    110 / 102
+//   (1,1,40), 2       118 / 134     58 / 50    149 / 114
+//   (4,1,33), 8       102 / 132     56 / 55    148 / 123
+//   (5,1,33), 4       103 / 136     56 / 56    148 / 126
+//   (8,1,33), 8        99 / 144     56 / 59    148 / 137
+//   (2,3,12), 33       75 / 132     48 / 58    125 / 129
+//   (3,3,5), 72        58 / 107     48 / 61    152 / 175
+//   (4,5,5), 48        42 / 106     38 / 56    123 / 180
 static bool u_bwd_table(const Plan& pl, int B) {
   const Shape& s = pl.sh;
-  return s.PN > 64 || (s.M > 4 && B >= 8 * (int64_t)s.n1 * s.n2);
+  return s.PN > 64 || B >= 8 * (int64_t)s.n1 * s.n2;
 }
 
 void launch_u_bwd(const Plan& pl, const Workspace& ws, const float* g3, const float* grad, int B,
