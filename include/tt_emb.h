@@ -71,8 +71,8 @@ enum {
   TT_EMB_FLAG_INDEXED_KERNELS = 8u, /* small batches, too, take the kernels with index structures
                                       (sorted ids, shared prefixes) that larger ones take; for
                                       comparison and testing                                     */
-  TT_EMB_FLAG_GENERIC_KERNELS = 2u /* use the any-shape vector-ALU kernels even for shapes that
-                                      have matrix-core kernels (d1 in {4,8,...,32}, d2 = 4,
+  TT_EMB_FLAG_GENERIC_KERNELS = 2u /* use the any-shape kernels even for shapes that have
+                                      matrix-core kernels of their own (d1 in {4,8,...,32}, d2 = 4,
                                       r1 = r2 in {8,16,32,64,128}, d3 in {4,8}), and index structures
                                       for every batch; for comparison and testing                */
 };
@@ -139,9 +139,9 @@ int tt_emb_forward_eval(tt_emb_t h, const int64_t* ids, int64_t B, float* out, v
  *   g1..g3   device, the cores (read only)          ids   device int64[B]
  *   out      device fp32[B][D]                      B     0 <= B <= cfg->max_batch
  * The scratch need grows with the batch: about 100 bytes per id plus 4*d1*d2*r2 bytes per distinct
- * (i1,i2) prefix the batch could hold (min(B, n1*n2) of them) plus tables of a few n2, n3 words;
- * a batch that needs more than 64 MiB returns TT_EMB_ENOSPC (a 136 x 136 x 136 table at rank 32
- * has 18,496 prefixes of 2 KiB and fits batches of up to about 250,000 ids; a 480 x 480 x 482
+ * (i1,i2) prefix the batch could hold (min(B, n1*n2) of them) plus tables of a few n2, n3 words, counted
+ * for all kernels alike (lookups at ranks up to 32 use a part of it); a batch that needs more than 64 MiB
+ * returns TT_EMB_ENOSPC (a 136 x 136 x 136 table at rank 32 has 18,496 prefixes of 2 KiB and fits batches of up to about 250,000 ids; a 480 x 480 x 482
  * table at rank 16 can meet a new 1 KiB prefix with every id and fits about 55,000).  TT_EMB_EINVAL for null or misaligned pointers, a bad configuration, or a current
  * device other than cfg->device.  The first call on a device looks the array's address up
  * (hipGetSymbolAddress); make that call outside graph capture - a call with B = 0 does only that.
@@ -221,7 +221,9 @@ int tt_emb_wait_backward(tt_emb_t h, int age);
  * backward_update(...) - the index
  * work of coming batches then overlaps this batch's arithmetic (minibatch samplers know the next
  * ids early).  An ids buffer must keep its contents until the forward that uses it has been enqueued.
- * Results are identical with or without it.  Small batches (a few thousand ids and fewer) take kernels
+ * Results are identical with or without it.  It pays for batches that train: a prepared lookup runs on the index
+ * structures, and at ranks up to 32 lookups are faster without any (500,000 Zipf ids of 480 x 480 x 482 at
+ * rank 16: 178 us prepared, 111 not).  Small batches (a few thousand ids and fewer) take kernels
  * that need no index structures: for them the call only orders the forward, which waits for what was
  * enqueued on hip_stream before it, and takes no index set.  tt_emb_get_stats refers to the latest forward only
  * until the next tt_emb_prepare (zeros once a prepared batch has taken the index set of a lookup).

@@ -305,7 +305,9 @@ __global__ __launch_bounds__(kAnyWaves * kWave, 4) void k_any_mid(
 // part3[c] = sum over the unique ids u of by-i3 chunk c of P_q(u)^T g_u (r2 x d3), one wavefront per chunk;
 // the contraction runs over the lines of the products, four at a time, five steps of two ids in flight.
 // 60 -> 23 us at 200,000 Zipf ids of (125,140,140) x (4,5,5), rank 32 (operands through LDS, products on the
-// vector ALUs before); 17 us is what its 139 MB take at the rate of gathers beyond an L2.
+// vector ALUs before); 17 us is what its 139 MB take at the rate of gathers beyond an L2.  Five steps are the 20
+// lines of that product; of 4 or 16 lines, or a second round of a few, some are loaded for nothing (figures of
+// such shapes at any_dg3_takes).
 // VEC: r2 = 16*NT, and a lane's loads along a line of P serve the NT tiles (column NT*l16 + t of tile t).
 template <int NT, bool VEC>
 __global__ __launch_bounds__(256) void k_any_dg3(

@@ -676,8 +676,8 @@ static int forward_impl(tt_emb* h, const IdSource& src, int64_t B64, float* out,
     h->have_forward = false;
     return TT_EMB_OK;
   }
-  // the matrix-core kernels store rows with 8- and 16-byte accesses; the any-shape kernels store
-  // float by float
+  // the matrix-core kernels store rows with 8- and 16-byte accesses; the any-shape kernels do where rows and out
+  // allow it, else float by float
   if (out == nullptr || ((uintptr_t)out & (h->mfma ? 15u : 3u)) != 0) return TT_EMB_EINVAL;
   const Plan& pl = h->plan;
   // A handle that has used tt_emb_prepare orders its index sets through events on streams of its

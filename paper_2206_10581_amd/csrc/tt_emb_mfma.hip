@@ -1,4 +1,4 @@
-// Matrix-core (MFMA) kernels for the table shapes d1 = d2 = 4, r1 = r2 = R in {16, 32, 64},
+// Matrix-core (MFMA) kernels for the table shapes d1 = d2 = 4, r1 = r2 = R in {8, 16, 32, 64, 128},
 // d3 in {4, 8}: the partial product of a row is then 16 x R, and once ids that share an (i1,i2)
 // prefix, an i2 or an i3 are stacked (paper Section 4.2: they share core slices) every step of the
 // path is a dense contraction with a 16- or 32-wide side.
