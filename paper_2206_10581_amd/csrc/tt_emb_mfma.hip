@@ -347,7 +347,6 @@ __global__ __launch_bounds__(kMThreads, 2) void k_prefix_bwd_wide(
   __shared__ int q_of[kChunk2], i1_of[kChunk2], inexact;
   const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave, half = lane / 32, l32 = lane % 32;
   const int nchunk = ctr->nchunk2, grp = wide_group(nchunk, R);
-  const bool look = ctr->small != 0;  // for small operands
   const int per_group = UN + grp, nunit = (nchunk + grp - 1) / grp * per_group;
   // records of chunk c; those past its count are unwritten and repeat the last one
   auto chunk_records = [&](int c, int cnt) {
@@ -360,162 +359,168 @@ __global__ __launch_bounds__(kMThreads, 2) void k_prefix_bwd_wide(
     if (tid == 0) inexact = 0;
     __syncthreads();
   };
-  for (int unit = blockIdx.x; unit < nunit; unit += gridDim.x) {
-    const int c0 = unit / per_group * grp, c1 = min(c0 + grp, nchunk), sub = unit % per_group;
-    if (sub < UN) {
-      constexpr int MT = R / 32;
-      const int col = sub * 128 + w * 32 + l32;
-      f16v sum[MT];
+  // look for small operands or not: one form with a test at every product took 4 % longer (500,000 Zipf ids of
+  // (480,500,500) x (8,4,4), rank 128; without any test 2376 us, one form 2410, two 2315)
+  auto walk = [&](auto look) {
+    for (int unit = blockIdx.x; unit < nunit; unit += gridDim.x) {
+      const int c0 = unit / per_group * grp, c1 = min(c0 + grp, nchunk), sub = unit % per_group;
+      if (sub < UN) {
+        constexpr int MT = R / 32;
+        const int col = sub * 128 + w * 32 + l32;
+        f16v sum[MT];
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) sum[mt] = TT_ZERO16;
-      int first = c0;  // where the running sum began
-      int4 desc = c2_desc[c0];
-      for (int c = c0; c < c1; ++c) {
-        const int cnt = desc.z, bin = desc.x;
-        chunk_records(c, cnt);
-        // a step contracts four prefixes; half h takes lines 2h and 2h + 1 of each, so that addresses are a
-        // scalar and a lane's offset.  Prefixes past the count count zero (their G1 lines are cleared) and
-        // read the last one's dPsum.
-        float b[4][8];
-        const uint32_t bo = 2 * half * W + col;
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-          for (int j = 0; j < 8; ++j)
-            b[t][j] = (dPsum + (size_t)wave_value(q_of[4 * t + j / 2]) * PN + j % 2 * W)[bo];
-        const int4 next = c2_desc[min(c + 1, nchunk - 1)];
-        // eight lines of a column a thread, R/32 times: those of half k8 % 2 in step k8 / 2
-        float a[R / 32][8];
-        const uint32_t ao = tid % R;
-#pragma unroll
-        for (int i = 0; i < R / 32; ++i) {
-          const int k8 = wave_value((tid + i * kMThreads) / R);
-#pragma unroll
-          for (int j = 0; j < 8; ++j)
-            a[i][j] = (g1 + (size_t)wave_value(i1_of[k8 / 2 * 4 + j / 2]) * S1 + (k8 % 2 * 2 + j % 2) * R)[ao];
-        }
-        TT_LOADS_DONE();
-        if (look && some_inexact<R / 4>(&a[0][0])) inexact = 1;
-#pragma unroll
-        for (int i = 0; i < R / 32; ++i) {
-          const int k8 = wave_value((tid + i * kMThreads) / R);
-#pragma unroll
-          for (int j = 0; j < 8; ++j) a[i][j] = k8 / 2 * 4 + j / 2 < cnt ? a[i][j] : 0.f;
-          const Split<h8> x = split_eight(a[i]);
-          __bf16* to = L + tid % R * TS + k8 * 8;
-          *(h8*)to = x.hi;
-          *(h8*)(to + PL2) = x.mid;
-          *(h8*)(to + 2 * PL2) = x.lo;
-        }
-        const bool small_cols = look && __ballot(some_inexact<32>(&b[0][0])) != 0ull;
-        Split<h8> y[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) y[t] = split_eight(b[t]);
-        __syncthreads();
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-          f16v acc = TT_ZERO16;
+        for (int mt = 0; mt < MT; ++mt) sum[mt] = TT_ZERO16;
+        int first = c0;  // where the running sum began
+        int4 desc = c2_desc[c0];
+        for (int c = c0; c < c1; ++c) {
+          const int cnt = desc.z, bin = desc.x;
+          chunk_records(c, cnt);
+          // a step contracts four prefixes; half h takes lines 2h and 2h + 1 of each, so that addresses are a
+          // scalar and a lane's offset.  Prefixes past the count count zero (their G1 lines are cleared) and
+          // read the last one's dPsum.
+          float b[4][8];
+          const uint32_t bo = 2 * half * W + col;
 #pragma unroll
           for (int t = 0; t < 4; ++t)
-            if (4 * t < cnt)  // uniform: else no prefix of this step
-              acc = mfma_split(split_from<PL2>(L + (mt * 32 + l32) * TS + 16 * t + 8 * half), y[t], acc);
-          if (recheck(acc) || small_cols || inexact) {
-            acc = TT_ZERO16;
-            for (int k = half; k < 4 * cnt; k += 2)
-              acc = mfma32(g1[(size_t)i1_of[k / 4] * S1 + (k % 4) * R + mt * 32 + l32],
-                           dPsum[(size_t)q_of[k / 4] * PN + (k % 4) * W + col], acc);
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+              b[t][j] = (dPsum + (size_t)wave_value(q_of[4 * t + j / 2]) * PN + j % 2 * W)[bo];
+          const int4 next = c2_desc[min(c + 1, nchunk - 1)];
+          // eight lines of a column a thread, R/32 times: those of half k8 % 2 in step k8 / 2
+          float a[R / 32][8];
+          const uint32_t ao = tid % R;
+#pragma unroll
+          for (int i = 0; i < R / 32; ++i) {
+            const int k8 = wave_value((tid + i * kMThreads) / R);
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+              a[i][j] = (g1 + (size_t)wave_value(i1_of[k8 / 2 * 4 + j / 2]) * S1 + (k8 % 2 * 2 + j % 2) * R)[ao];
           }
-          sum[mt] += acc;
-        }
-        if (c + 1 == c1 || next.x != bin) {  // the group or the slice ends here
-          float* dst = part2 + (size_t)first * S2;
-          const uint32_t mine = 4 * half * W + col;
+          TT_LOADS_DONE();
+          if (look.value && some_inexact<R / 4>(&a[0][0])) inexact = 1;
 #pragma unroll
-          for (int mt = 0; mt < MT; ++mt)
+          for (int i = 0; i < R / 32; ++i) {
+            const int k8 = wave_value((tid + i * kMThreads) / R);
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-              (dst + (mt * 32 + 8 * (v / 4) + v % 4) * W)[mine] = sum[mt][v];
-              sum[mt][v] = 0.f;
+            for (int j = 0; j < 8; ++j) a[i][j] = k8 / 2 * 4 + j / 2 < cnt ? a[i][j] : 0.f;
+            const Split<h8> x = split_eight(a[i]);
+            __bf16* to = L + tid % R * TS + k8 * 8;
+            *(h8*)to = x.hi;
+            *(h8*)(to + PL2) = x.mid;
+            *(h8*)(to + 2 * PL2) = x.lo;
+          }
+          const bool small_cols = look.value && __ballot(some_inexact<32>(&b[0][0])) != 0ull;
+          Split<h8> y[4];
+#pragma unroll
+          for (int t = 0; t < 4; ++t) y[t] = split_eight(b[t]);
+          __syncthreads();
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) {
+            f16v acc = TT_ZERO16;
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+              if (4 * t < cnt)  // uniform: else no prefix of this step
+                acc = mfma_split(split_from<PL2>(L + (mt * 32 + l32) * TS + 16 * t + 8 * half), y[t], acc);
+            if (recheck(acc) || small_cols || inexact) {
+              acc = TT_ZERO16;
+              for (int k = half; k < 4 * cnt; k += 2)
+                acc = mfma32(g1[(size_t)i1_of[k / 4] * S1 + (k % 4) * R + mt * 32 + l32],
+                             dPsum[(size_t)q_of[k / 4] * PN + (k % 4) * W + col], acc);
             }
-          first = c + 1;
-        }
-        desc = next;
-      }
-    } else {
-      const int c = c0 + sub - UN;
-      if (c >= c1) continue;  // uniform for the block
-      constexpr int NT = R / 32, MW = NT >= 4 ? 2 : 1;  // tiles of 32 lines of a wavefront
-      // the thread number anew: nothing derived from it here is kept in registers across the dG2 units
-      int tid = threadIdx.x;
-      asm volatile("" : "+v"(tid));
-      const int w = tid / kWave, half = tid % kWave / 32, l32 = tid % 32;
-      const int4 desc = c2_desc[c];
-      const int cnt = desc.z;
-      chunk_records(c, cnt);
-      const float* Bm = g2 + (size_t)desc.x * S2;
-      const int nt = w % NT, mt0 = w / NT;
-      f4 ra[2], rb[R / 32];
-      auto fetch = [&](int k0) {
+            sum[mt] += acc;
+          }
+          if (c + 1 == c1 || next.x != bin) {  // the group or the slice ends here
+            float* dst = part2 + (size_t)first * S2;
+            const uint32_t mine = 4 * half * W + col;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          const int e = tid + i * kMThreads, r = e / (KD / 4), k = e % (KD / 4) * 4;
-          ra[i] = *(const f4*)(dPsum + (size_t)q_of[r / 4] * PN + (r % 4) * W + k0 + k);
-        }
+            for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int i = 0; i < R / 32; ++i) {
-          const int e = tid + i * kMThreads, r = e / (KD / 4), k = e % (KD / 4) * 4;
-          rb[i] = *(const f4*)(Bm + (size_t)r * W + k0 + k);
+              for (int v = 0; v < 16; ++v) {
+                (dst + (mt * 32 + 8 * (v / 4) + v % 4) * W)[mine] = sum[mt][v];
+                sum[mt][v] = 0.f;
+              }
+            first = c + 1;
+          }
+          desc = next;
         }
-      };
-      f16v acc[MW];
+      } else {
+        const int c = c0 + sub - UN;
+        if (c >= c1) continue;  // uniform for the block
+        constexpr int NT = R / 32, MW = NT >= 4 ? 2 : 1;  // tiles of 32 lines of a wavefront
+        // the thread number anew: nothing derived from it here is kept in registers across the dG2 units
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const int w = tid / kWave, half = tid % kWave / 32, l32 = tid % 32;
+        const int4 desc = c2_desc[c];
+        const int cnt = desc.z;
+        chunk_records(c, cnt);
+        const float* Bm = g2 + (size_t)desc.x * S2;
+        const int nt = w % NT, mt0 = w / NT;
+        f4 ra[2], rb[R / 32];
+        auto fetch = [&](int k0) {
 #pragma unroll
-      for (int x = 0; x < MW; ++x) acc[x] = TT_ZERO16;
-      fetch(0);
-#pragma unroll 1
-      for (int k0 = 0; k0 < W; k0 += KD) {
-        if (k0 > 0) __syncthreads();
-        if (look && (some_inexact<8>((const float*)ra) || some_inexact<R / 8>((const float*)rb))) inexact = 1;
-        auto put = [&](int line, int e, f4 v) {
-          const Split<h4> x = split_four(v);
-          __bf16* to = L + (line + e / (KD / 4)) * KS + e % (KD / 4) * 4;
-          *(h4*)to = x.hi;
-          *(h4*)(to + PL1) = x.mid;
-          *(h4*)(to + 2 * PL1) = x.lo;
+          for (int i = 0; i < 2; ++i) {
+            const int e = tid + i * kMThreads, r = e / (KD / 4), k = e % (KD / 4) * 4;
+            ra[i] = *(const f4*)(dPsum + (size_t)q_of[r / 4] * PN + (r % 4) * W + k0 + k);
+          }
+#pragma unroll
+          for (int i = 0; i < R / 32; ++i) {
+            const int e = tid + i * kMThreads, r = e / (KD / 4), k = e % (KD / 4) * 4;
+            rb[i] = *(const f4*)(Bm + (size_t)r * W + k0 + k);
+          }
         };
+        f16v acc[MW];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) put(0, tid + i * kMThreads, ra[i]);
+        for (int x = 0; x < MW; ++x) acc[x] = TT_ZERO16;
+        fetch(0);
+#pragma unroll 1
+        for (int k0 = 0; k0 < W; k0 += KD) {
+          if (k0 > 0) __syncthreads();
+          if (look.value && (some_inexact<8>((const float*)ra) || some_inexact<R / 8>((const float*)rb))) inexact = 1;
+          auto put = [&](int line, int e, f4 v) {
+            const Split<h4> x = split_four(v);
+            __bf16* to = L + (line + e / (KD / 4)) * KS + e % (KD / 4) * 4;
+            *(h4*)to = x.hi;
+            *(h4*)(to + PL1) = x.mid;
+            *(h4*)(to + 2 * PL1) = x.lo;
+          };
 #pragma unroll
-        for (int i = 0; i < R / 32; ++i) put(64, tid + i * kMThreads, rb[i]);
-        __syncthreads();
-        if (k0 + KD < W) fetch(k0 + KD);  // in flight while this step is multiplied
-        TT_LOADS_DONE();
+          for (int i = 0; i < 2; ++i) put(0, tid + i * kMThreads, ra[i]);
 #pragma unroll
-        for (int t = 0; t < KD / 16; ++t) {
-          const Split<h8> y = split_from<PL1>(L + (64 + nt * 32 + l32) * KS + 16 * t + 8 * half);
+          for (int i = 0; i < R / 32; ++i) put(64, tid + i * kMThreads, rb[i]);
+          __syncthreads();
+          if (k0 + KD < W) fetch(k0 + KD);  // in flight while this step is multiplied
+          TT_LOADS_DONE();
 #pragma unroll
-          for (int x = 0; x < MW; ++x)
-            acc[x] = mfma_split(split_from<PL1>(L + ((mt0 + x) * 32 + l32) * KS + 16 * t + 8 * half), y, acc[x]);
+          for (int t = 0; t < KD / 16; ++t) {
+            const Split<h8> y = split_from<PL1>(L + (64 + nt * 32 + l32) * KS + 16 * t + 8 * half);
+#pragma unroll
+            for (int x = 0; x < MW; ++x)
+              acc[x] = mfma_split(split_from<PL1>(L + ((mt0 + x) * 32 + l32) * KS + 16 * t + 8 * half), y, acc[x]);
+          }
         }
-      }
 #pragma unroll
-      for (int x = 0; x < MW; ++x) {
-        const int mt = mt0 + x;
-        if (mt * 8 < cnt && (recheck(acc[x]) || inexact)) {
-          const float* ar = dPsum + (size_t)q_of[mt * 8 + l32 / 4] * PN + (l32 % 4) * W + half * (W / 2);
-          const float* br = Bm + (size_t)(nt * 32 + l32) * W + half * (W / 2);
-          acc[x] = TT_ZERO16;
+        for (int x = 0; x < MW; ++x) {
+          const int mt = mt0 + x;
+          if (mt * 8 < cnt && (recheck(acc[x]) || inexact)) {
+            const float* ar = dPsum + (size_t)q_of[mt * 8 + l32 / 4] * PN + (l32 % 4) * W + half * (W / 2);
+            const float* br = Bm + (size_t)(nt * 32 + l32) * W + half * (W / 2);
+            acc[x] = TT_ZERO16;
 #pragma unroll 4
-          for (int j = 0; j < W / 2; ++j) acc[x] = mfma32(ar[j], br[j], acc[x]);
-        }
+            for (int j = 0; j < W / 2; ++j) acc[x] = mfma32(ar[j], br[j], acc[x]);
+          }
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int ql = mt * 8 + 2 * (v / 4) + half;
-          if (ql < cnt)
-            dg1part[(size_t)q_of[ql] * S1 + (v % 4) * R + nt * 32 + l32] = acc[x][v];
+          for (int v = 0; v < 16; ++v) {
+            const int ql = mt * 8 + 2 * (v / 4) + half;
+            if (ql < cnt)
+              dg1part[(size_t)q_of[ql] * S1 + (v % 4) * R + nt * 32 + l32] = acc[x][v];
+          }
         }
       }
     }
-  }
+  };
+  if (ctr->small != 0) walk(std::true_type{});
+  else walk(std::false_type{});
 }
 
 // ---------------------------------------------------------------------------------------------
