@@ -1,8 +1,9 @@
 """Sizes at which the index pipeline and the any-shape kernels change how they cut their work: the
 largest batch of every sort block size and the one above it (with a hot id, out-of-range ids, and
 tables of one, two and three sort passes, one of them with factors near the bucket limit); row
-products with and without 16-byte operands; prefixes of more ids than the id table of the prefix-gradient kernel holds, and rows too long for its split of
-the contraction index.  Oracle and tolerances are those of test_gpu_parity."""
+products with and without 16-byte operands; shapes at the limits of the any-shape kernels of both kinds
+(what only those without matrix-core tiles take is in test_any_shape_kernels).  Oracle and tolerances are
+those of test_gpu_parity."""
 import numpy as np
 import pytest
 
@@ -55,14 +56,14 @@ def test_any_shape_rows_and_prefix_gradients(d, r):
                                    ((9, 8, 150), (2, 4, 8), (4, 9)), ((70, 60, 5), (4, 4, 4), (4, 4)),
                                    ((70, 60, 5), (3, 3, 3), (6, 7))])
 def test_small_prefix_gradients(n, d, r):
-    """Products of up to 64 elements and one above, of prefixes with many ids and with few: with and
-    without the id table."""
+    """Products of up to 64 elements and one above, of prefixes with many ids and with few: the smallest
+    tiles of the middle kernel."""
     _check(n, d, r, 9_001)
 
 
 @pytest.mark.parametrize("d,r", [((4, 5, 5), (32, 32)), ((16, 2, 3), (5, 32)), ((17, 2, 3), (5, 33)),
                                  ((3, 5, 4), (70, 13)), ((2, 1, 9), (1, 1))])
 def test_prefix_products_by_columns(d, r):
-    """Chunks of up to 16 prefixes cut by columns: one run, several, a ragged last one; as many rows
-    as the row table holds and more."""
+    """Chunks of up to 16 prefixes cut by columns: one run, several, a ragged last one; the largest d1 that
+    the matrix-core tiles take and the next one, ranks they take and one they leave."""
     _check((70, 6, 5), d, r, 9_001)
