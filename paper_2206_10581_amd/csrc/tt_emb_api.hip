@@ -165,9 +165,7 @@ static int make_plan(const tt_emb_config* c, Plan* pl) {
   pl->maxB = maxB;
   pl->maxQ = std::min<int64_t>(maxB, n12);
   pl->sortBlocksMax = (int)sort_blocks_most(pl->maxB);
-  pl->segBlocksMax = (int)cdiv64(pl->maxB, 4 * kSegThreads);
-  pl->uBlocksMax = (int)group_blocks_most(s, pl->maxB, pl->maxB);
-  pl->qBlocksMax = (int)group_blocks_most(s, pl->maxQ, pl->maxB);
+  pl->slotBlocksMax = (int)cdiv64(pl->maxB, 1024);
   pl->tilesMax = (int)cdiv64(pl->maxB, kTileSlots);
   pl->maxChunk3 = cdiv64(pl->maxB, kChunk3Min) + s.n3;
   pl->maxChunk2 = cdiv64(pl->maxQ, kChunk2) + s.n2;
@@ -219,8 +217,8 @@ static size_t carve(const Plan& pl, char* base, Workspace* ws /* [kSets] or null
     for (int k = 0; k < 2; ++k) w.key[k] = (uint32_t*)take(mB * 4);
     for (int k = 0; k < 2; ++k) w.val[k] = (uint32_t*)take(mB * 4);
     w.tot = (uint32_t*)take((size_t)kMaxBins * 4);
-    w.seg_nu = (uint32_t*)take((size_t)pl.segBlocksMax * 4);
-    w.seg_nq = (uint32_t*)take((size_t)pl.segBlocksMax * 4);
+    w.seg_nu = (uint32_t*)take((size_t)pl.slotBlocksMax * 4);
+    w.seg_nq = (uint32_t*)take((size_t)pl.slotBlocksMax * 4);
     w.s_u = (int*)take(mB * 4);
     w.s_rec = (int4*)take(mB * 16);
     w.u_rs = (int*)take((mB + 1) * 4);
@@ -230,30 +228,25 @@ static size_t carve(const Plan& pl, char* base, Workspace* ws /* [kSets] or null
     w.q_us = (int*)take((mQ + 1) * 4);
     w.q_i1 = (int*)take(mQ * 4);
     w.q_i2 = (int*)take(mQ * 4);
-    // The histograms of the sort lie in the chunk records where those are large enough: the last
-    // sort pass reads them last, the grouping kernel behind it writes the records first.  What is
-    // taken here is what histograms per 4096 items need, which also holds the finer ones of the
-    // grouping kernel (group_threads): the need of a batch does not depend on the block sizes.
-    auto al = [](size_t bytes) { return (bytes + 255) & ~size_t(255); };
-    const size_t hist = al((size_t)pl.sortBlocksMax * kMaxBins * 4);
+    // The histograms of the sort lie in the chunk records where those are large enough (batches of more
+    // than 1024 rows): the last sort pass reads them last, the grouping kernel behind it writes the records
+    // first.  Else they share the memory of the counts per block of slots, which are made after the sort.
+    const size_t hist = (size_t)pl.sortBlocksMax * kMaxBins * 4;
     const bool shared = (size_t)pl.maxChunk3 * kChunk3 * 8 >= hist;
+    auto al = [](size_t bytes) { return (bytes + 255) & ~size_t(255); };
     const size_t coarse_u = (size_t)cdiv64(pl.maxB, sort_items(1024)),
                  coarse_q = (size_t)cdiv64(pl.maxQ, sort_items(1024));
-    const size_t c3_bytes = al((size_t)pl.uBlocksMax * s.n3 * 4),
-                 c2_bytes = al((size_t)pl.qBlocksMax * s.n2 * 4);
-    char* counts = take(std::max(al(coarse_u * kMaxBins * 4) + al(coarse_u * s.n3 * 4) + al(coarse_q * s.n2 * 4),
-                                 c3_bytes + c2_bytes + (shared ? 0 : hist)));
-    w.cnt3 = (uint32_t*)counts;
-    w.cnt2 = (uint32_t*)(counts + c3_bytes);
-    w.g3_list = (int*)take(mB * 4);
-    w.g3_start = (int*)take(((size_t)s.n3 + 1) * 4);
+    char* counts = take(al(coarse_u * kMaxBins * 4) + al(coarse_u * s.n3 * 4) + al(coarse_q * s.n2 * 4));
+    w.seg_rows = (uint16_t*)counts;
+    w.seg_base = (int4*)take(mB * 4);
+    take(((size_t)s.n3 + 1) * 4);
     w.c3_start = (int*)take(((size_t)s.n3 + 1) * 4);
     w.c3_desc = (int4*)take((size_t)pl.maxChunk3 * 16);
     w.c3_item = (int2*)take((size_t)pl.maxChunk3 * kChunk3 * 8);
-    w.cnt = (uint32_t*)(shared ? (char*)w.c3_item : counts + c3_bytes + c2_bytes);
+    w.cnt = (uint32_t*)(shared ? (char*)w.c3_item : counts);
     w.c3_order = (int*)take((size_t)pl.maxChunk3 * 4);
-    w.g2_list = (int*)take(mQ * 4);
-    w.g2_start = (int*)take(((size_t)s.n2 + 1) * 4);
+    take(mQ * 4);
+    take(((size_t)s.n2 + 1) * 4);
     w.c2_start = (int*)take(((size_t)s.n2 + 1) * 4);
     w.c2_desc = (int4*)take((size_t)pl.maxChunk2 * 16);
     w.c2_item = (int4*)take((size_t)pl.maxChunk2 * kChunk2 * 16);

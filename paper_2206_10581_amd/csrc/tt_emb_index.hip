@@ -80,21 +80,78 @@ __device__ __forceinline__ unsigned long long match_digit(int digit, bool valid)
   return ~(((unsigned long long)hi << 32) | lo) & __ballot(valid);
 }
 
-template <int NT>
-struct alignas(16) ScatterLds {
-  // per-wavefront bucket counts, later block-local output offsets; two 16-bit buckets per word
-  // (a wavefront owns 256 items and a block at most 4096, so both fit)
-  uint32_t wh[NT / kWave][kMaxBins / 2];
-  uint32_t tot[kMaxBins];  // bucket totals, then this block's first output per bucket
-  uint32_t aux[kMaxBins];  // chunks per bucket, then first chunk per bucket
-  uint32_t base[kMaxBins]; // first output of every bucket (all blocks), for chunked passes
-  uint32_t ldsw[NT / kWave];
-};
-
-constexpr int kSteps = kSortWaveItems / kWave;  // items per lane
+constexpr int kSteps = kSortWaveItems / kWave;  // most items per lane
 static_assert((kChunk2 & (kChunk2 - 1)) == 0 && (kChunk3 & (kChunk3 - 1)) == 0 &&
                   (kChunk3Min & (kChunk3Min - 1)) == 0,
               "chunk sizes are powers of two: positions inside a bucket are cut with shifts");
+
+// Stable ranks of a block's items in their buckets.  Every wavefront holds up to 256 consecutive items,
+// 64 a step (digit -1: no item); the wavefronts' runs follow each other.  wh: one row of row_words words
+// (a multiple of four) per wavefront, two 16-bit buckets a word: a wavefront owns 256 items and a block at
+// most 4096, so both fit.
+template <int NT>
+__device__ __forceinline__ void block_ranks(uint32_t* wh, int row_words, const int (&digits)[kSteps],
+                                            uint32_t (&rank)[kSteps]) {
+  const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
+  uint32_t* mine = wh + w * row_words;
+  // every wavefront clears its own counters, 16 bytes per lane and write (no barrier: nobody else
+  // touches them before the next one)
+  for (int i = lane; i < row_words / 4; i += kWave) ((uint4*)mine)[i] = make_uint4(0u, 0u, 0u, 0u);
+
+  // Each wavefront walks its items in order, 64 at a time.  Lanes holding the same digit find each
+  // other by ballots; the lowest of them advances the wavefront's bucket counter for all, which
+  // gives every item its rank among the wavefront's items of that bucket.
+  const unsigned long long lt_mask = (1ull << lane) - 1ull;
+  unsigned long long peers[kSteps];
+#pragma unroll
+  for (int step = 0; step < kSteps; ++step) {
+    const bool valid = digits[step] >= 0;
+    peers[step] = 0ull;
+    if (__ballot(valid) != 0ull) peers[step] = match_digit(digits[step], valid);  // wave-uniform
+  }
+  // the counter updates of the steps go out back to back (the LDS keeps a wavefront's atomics in
+  // program order, which is what makes the ranks stable), their results are picked up afterwards
+  uint32_t old[kSteps];
+#pragma unroll
+  for (int step = 0; step < kSteps; ++step) {
+    const int digit = digits[step];
+    old[step] = 0;
+    if (digit >= 0 && lane == __ffsll((long long)peers[step]) - 1)
+      old[step] = atomicAdd(&mine[digit >> 1], (uint32_t)__popcll(peers[step]) << (16 * (digit & 1)));
+  }
+#pragma unroll
+  for (int step = 0; step < kSteps; ++step) {
+    const int digit = digits[step];
+    const int leader = digit >= 0 ? (__ffsll((long long)peers[step]) - 1) : lane;
+    rank[step] = ((__shfl(old[step], leader) >> (16 * (digit & 1))) & 0xffffu) +
+                 (uint32_t)__popcll(peers[step] & lt_mask);
+  }
+  __syncthreads();
+  // per bucket: counts of the wavefronts -> offsets inside the block (one thread per word)
+  for (int word = tid; word < row_words; word += NT) {
+    uint32_t lo = 0, hi = 0;
+#pragma unroll
+    for (int k = 0; k < NT / kWave; ++k) {
+      const uint32_t c = wh[k * row_words + word];
+      wh[k * row_words + word] = lo | (hi << 16);
+      lo += c & 0xffffu;
+      hi += c >> 16;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int step = 0; step < kSteps; ++step) {
+    const int digit = digits[step];
+    if (digit >= 0) rank[step] += (mine[digit >> 1] >> (16 * (digit & 1))) & 0xffffu;
+  }
+}
+
+template <int NT>
+struct alignas(16) ScatterLds {
+  uint32_t wh[NT / kWave][kMaxBins / 2];  // counters of block_ranks
+  uint32_t tot[kMaxBins];                 // bucket totals, then this block's first output per bucket
+  uint32_t ldsw[NT / kWave];
+};
 
 // One block's share of a stable counting-sort pass over n_items items (block blk of NT threads owns
 // items [blk*4*NT, +4*NT), each of its wavefronts 256 of them in order).  With tot != nullptr,
@@ -102,25 +159,14 @@ static_assert((kChunk2 & (kChunk2 - 1)) == 0 && (kChunk3 & (kChunk3 - 1)) == 0 &
 // from a column-scan kernel over the blocks' histograms); with tot == nullptr, cnt holds the
 // blocks' own histograms and every block adds up its columns itself (cheaper than one more launch
 // when there are few blocks).
-// ItemOps: Item load(int idx); int digit(Item); void emit(uint32_t pos, Item); and, for chunked
-// passes, void emit_chunked(uint32_t pos, uint32_t chunk, uint32_t t, Item): item is the t-th of
-// chunk `chunk` (its record goes to chunk*chunk_size + t of a per-chunk table).
-// With starts != nullptr the pass also publishes the bucket offsets (bins+1 entries, by block 0)
-// and, for chunk > 0, cuts every bucket into chunks of at most `chunk` items: chunk_desc[c] =
-// {bucket, first item, item count, 0} for all chunks c in bucket order, chunk_starts[bucket] the
-// first chunk of each bucket (bins+1 entries), *n_chunks the number of chunks.
+// ItemOps: Item load(int idx); int digit(Item); void emit(uint32_t pos, Item).
 template <int NT, class ItemOps>
 __device__ void stable_scatter_block(ScatterLds<NT>& L, int blk, int n_items, int bins,
                                      const uint32_t* __restrict__ cnt,
-                                     const uint32_t* __restrict__ tot, ItemOps ops, int* starts,
-                                     int chunk, int* chunk_starts, int4* chunk_desc,
-                                     int* n_chunks) {
-  constexpr int kItems = sort_items(NT), kWaves = NT / kWave;
+                                     const uint32_t* __restrict__ tot, ItemOps ops) {
+  constexpr int kItems = sort_items(NT);
   const int tid = threadIdx.x;
   const int nblk = (n_items + kItems - 1) / kItems;
-  const bool publishes = (starts != nullptr && blk == 0);
-  const int chunk_sh = chunk > 0 ? 31 - __clz(chunk) : 0;  // chunk sizes are powers of two
-  if (blk >= nblk && !publishes) return;  // uniform for the whole block
 
   // items first: their loads overlap the table work below
   const int w = tid / kWave, lane = tid % kWave;
@@ -159,10 +205,7 @@ __device__ void stable_scatter_block(ScatterLds<NT>& L, int blk, int n_items, in
       total = tsum;
       before[k] = bsum;
     }
-    if (bin < bins) {
-      L.tot[bin] = total;
-      if (chunk > 0) L.aux[bin] = (total + chunk - 1) >> chunk_sh;
-    }
+    if (bin < bins) L.tot[bin] = total;
   }
   __builtin_amdgcn_sched_barrier(0);  // keep the loads together: their latencies overlap
 #pragma unroll
@@ -172,109 +215,17 @@ __device__ void stable_scatter_block(ScatterLds<NT>& L, int blk, int n_items, in
   for (int step = 0; step < kSteps; ++step)
     if (wbase + step * kWave + lane >= n_items) digits[step] = -1;
   __syncthreads();
-  const uint32_t total_items = block_exclusive_scan(L.tot, bins, L.ldsw);
-  if (chunk > 0) {
-    for (int bin = tid; bin < bins; bin += NT) L.base[bin] = L.tot[bin];
-  }
-  if (starts != nullptr) {
-    if (publishes) {
-      for (int bin = tid; bin < bins; bin += NT) starts[bin] = (int)L.tot[bin];
-      if (tid == 0) starts[bins] = (int)total_items;
-    }
-    if (chunk > 0) {
-      // every participating block takes a share of the chunk descriptors
-      const uint32_t total_chunks = block_exclusive_scan(L.aux, bins, L.ldsw);
-      if (publishes) {
-        for (int bin = tid; bin < bins; bin += NT) chunk_starts[bin] = (int)L.aux[bin];
-        if (tid == 0) {
-          chunk_starts[bins] = (int)total_chunks;
-          *n_chunks = (int)total_chunks;
-        }
-      }
-      const int nshare = max(nblk, 1);
-      for (uint32_t c = (uint32_t)blk * NT + tid; c < total_chunks;
-           c += (uint32_t)nshare * NT) {
-        int lo = 0, hi = bins;  // last bucket whose first chunk is <= c
-        while (hi - lo > 1) {
-          const int mid = (lo + hi) >> 1;
-          if (L.aux[mid] <= c) lo = mid; else hi = mid;
-        }
-        const uint32_t first = L.tot[lo];
-        const uint32_t end = (lo + 1 < bins) ? L.tot[lo + 1] : total_items;
-        const uint32_t k0 = first + (c - L.aux[lo]) * (uint32_t)chunk;
-        chunk_desc[c] = make_int4(lo, (int)k0, (int)min((uint32_t)chunk, end - k0), 0);
-      }
-    }
-  }
-  if (blk >= nblk) return;
-  __syncthreads();
+  block_exclusive_scan(L.tot, bins, L.ldsw);
 #pragma unroll
   for (int k = 0; k < kMaxBins / NT; ++k) {
     const int bin = tid + k * NT;
     if (bin < bins) L.tot[bin] += before[k];
   }
-  // every wavefront clears its own counters, 16 bytes per lane and write (no barrier: nobody else
-  // touches them before the next one)
-  const int words = (bins + 1) / 2;
-  for (int i = lane; i < (words + 3) / 4; i += kWave) ((uint4*)L.wh[w])[i] = make_uint4(0u, 0u, 0u, 0u);
-
-  // Each wavefront walks its items in order, 64 at a time.  Lanes holding the same digit find each
-  // other by ballots; the lowest of them advances the wavefront's bucket counter for all, which
-  // gives every item its rank among the wavefront's items of that bucket.
-  const unsigned long long lt_mask = (1ull << lane) - 1ull;
   uint32_t rank[kSteps];
-  unsigned long long peers[kSteps];
+  block_ranks<NT>(&L.wh[0][0], max((bins / 2 + 3) & ~3, 4), digits, rank);
 #pragma unroll
-  for (int step = 0; step < kSteps; ++step) {
-    const bool valid = digits[step] >= 0;
-    peers[step] = 0ull;
-    if (__ballot(valid) != 0ull) peers[step] = match_digit(digits[step], valid);  // wave-uniform
-  }
-  // the counter updates of the steps go out back to back (the LDS keeps a wavefront's atomics in
-  // program order, which is what makes the ranks stable), their results are picked up afterwards
-  uint32_t old[kSteps];
-#pragma unroll
-  for (int step = 0; step < kSteps; ++step) {
-    const int digit = digits[step];
-    old[step] = 0;
-    if (digit >= 0 && lane == __ffsll((long long)peers[step]) - 1)
-      old[step] = atomicAdd(&L.wh[w][digit >> 1], (uint32_t)__popcll(peers[step]) << (16 * (digit & 1)));
-  }
-#pragma unroll
-  for (int step = 0; step < kSteps; ++step) {
-    const int digit = digits[step];
-    const int leader = digit >= 0 ? (__ffsll((long long)peers[step]) - 1) : lane;
-    rank[step] = ((__shfl(old[step], leader) >> (16 * (digit & 1))) & 0xffffu) +
-                 (uint32_t)__popcll(peers[step] & lt_mask);
-  }
-  __syncthreads();
-  // per bucket: counts of the wavefronts -> offsets inside the block (one thread per word)
-  for (int word = tid; word < words; word += NT) {
-    uint32_t lo = 0, hi = 0;
-#pragma unroll
-    for (int k = 0; k < kWaves; ++k) {
-      const uint32_t c = L.wh[k][word];
-      L.wh[k][word] = lo | (hi << 16);
-      lo += c & 0xffffu;
-      hi += c >> 16;
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int step = 0; step < kSteps; ++step) {
-    const int digit = digits[step];
-    if (digit >= 0) {
-      const uint32_t off = (L.wh[w][digit >> 1] >> (16 * (digit & 1))) & 0xffffu;
-      const uint32_t pos = L.tot[digit] + off + rank[step];
-      if constexpr (ItemOps::kChunked) {
-        const uint32_t in_bucket = pos - L.base[digit];
-        ops.emit_chunked(pos, L.aux[digit] + (in_bucket >> chunk_sh), in_bucket & (uint32_t)(chunk - 1),
-                         items[step]);
-      } else {
-        ops.emit(pos, items[step]);
-      }
-    }
-  }
+  for (int step = 0; step < kSteps; ++step)
+    if (digits[step] >= 0) ops.emit(L.tot[digits[step]] + rank[step], items[step]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -287,7 +238,6 @@ struct KV {
 template <bool FIRST>
 struct SortOps {
   using Item = KV;
-  static constexpr bool kChunked = false;
   const uint32_t* kin;
   const uint32_t* vin;
   uint32_t* kout;
@@ -311,8 +261,7 @@ struct KeysInPlace {};  // source of the passes behind the first
 template <int NT, class SRC>
 __global__ __launch_bounds__(NT) void k_sort_hist(
     SRC src, uint32_t* keys_io, int B, uint32_t N, int shift,
-    int bits, uint32_t* __restrict__ cnt, uint32_t* zero_a, int zero_a_n, uint32_t* zero_b,
-    int zero_b_n, uint32_t* zero_c, int zero_c_n, Counters* ctr) {
+    int bits, uint32_t* __restrict__ cnt, uint32_t* zero, int zero_n, Counters* ctr) {
   constexpr bool FROM_IDS = !std::is_same_v<SRC, KeysInPlace>;
   __shared__ uint32_t h[kMaxBins];
   const int tid = threadIdx.x, bins = 1 << bits;
@@ -335,9 +284,7 @@ __global__ __launch_bounds__(NT) void k_sort_hist(
       if (idx < B) keys_io[idx] = keys[step];
     }
     const int gtid = blockIdx.x * NT + tid, gn = gridDim.x * NT;
-    for (int i = gtid; i < zero_a_n; i += gn) zero_a[i] = 0u;
-    for (int i = gtid; i < zero_b_n; i += gn) zero_b[i] = 0u;
-    for (int i = gtid; i < zero_c_n; i += gn) zero_c[i] = 0u;
+    for (int i = gtid; i < zero_n; i += gn) zero[i] = 0u;
     if (gtid == 0) {
       ctr->err = 0;
       ctr->n_split = 0;
@@ -366,8 +313,7 @@ __global__ __launch_bounds__(NT) void k_sort_scatter(SortOps<FROM_IDS> ops, int 
                                                                const uint32_t* __restrict__ cnt,
                                                                const uint32_t* __restrict__ tot) {
   __shared__ ScatterLds<NT> L;
-  stable_scatter_block(L, (int)blockIdx.x, B, 1 << bits, cnt, tot, ops, nullptr, 0, nullptr,
-                       nullptr, nullptr);
+  stable_scatter_block(L, (int)blockIdx.x, B, 1 << bits, cnt, tot, ops);
 }
 
 // Turns the blocks' bucket counts cnt[b][bin] into counts of earlier blocks (exclusive scan down
@@ -420,180 +366,202 @@ __global__ __launch_bounds__(kScanThreads) void k_sort_colscan(uint32_t* __restr
 // ---------------------------------------------------------------------------------------------
 // Segment discovery over the sorted keys
 
-template <int ITEMS>
-struct SegFlags {
-  uint32_t key[ITEMS], prev[ITEMS];
-  bool valid[ITEMS], newu[ITEMS], newq[ITEMS], last_valid[ITEMS], single[ITEMS], split[ITEMS];
+// What a sorted slot begins and ends.
+struct SlotFlags {
+  uint32_t key, prev;
+  bool valid, newu, newq, last_valid, single, split;
 };
 
-template <int ITEMS>
-__device__ __forceinline__ SegFlags<ITEMS> seg_flags(const uint32_t* __restrict__ skey, int B, uint32_t N,
-                                                     uint32_t n3, int s0) {
-  SegFlags<ITEMS> f;
-  uint32_t k[ITEMS + 2];  // keys of slots s0-1 .. s0+ITEMS
-#pragma unroll
-  for (int j = 0; j < ITEMS + 2; ++j) {
-    const int s = s0 - 1 + j;
-    k[j] = (s >= 0 && s < B) ? skey[s] : 0xffffffffu;
-  }
-#pragma unroll
-  for (int j = 0; j < ITEMS; ++j) {
-    const int s = s0 + j;
-    const uint32_t key = k[j + 1], prev = k[j], next = k[j + 2];
-    f.key[j] = key;
-    f.prev[j] = prev;
-    f.valid[j] = (s < B) && (key < N);
-    const bool first = (s == 0);
-    // a new entry: a new id, or the next kEntrySlots piece of a long run of one id
-    const bool cut = (s % kEntrySlots) == 0;
-    f.newu[j] = f.valid[j] && (first || key != prev || cut);
-    f.split[j] = f.valid[j] && !first && key == prev && cut;
-    f.newq[j] = f.valid[j] && (first || (key / n3) != (prev / n3));
-    f.last_valid[j] = f.valid[j] && !(next < N);
-    // the entry holds exactly one slot: its gradient row is read where it lies
-    f.single[j] = f.newu[j] && (next != key || ((s + 1) % kEntrySlots) == 0);
-  }
+__device__ __forceinline__ SlotFlags slot_flags(const uint32_t* __restrict__ skey, int B, uint32_t N,
+                                                uint32_t n3, int s) {
+  SlotFlags f;
+  const uint32_t key = s < B ? skey[s] : 0xffffffffu;
+  const uint32_t prev = s > 0 && s - 1 < B ? skey[s - 1] : 0xffffffffu;
+  const uint32_t next = s + 1 < B ? skey[s + 1] : 0xffffffffu;
+  f.key = key;
+  f.prev = prev;
+  f.valid = (s < B) && (key < N);
+  const bool first = (s == 0);
+  // a new entry: a new id, or the next kEntrySlots piece of a long run of one id
+  const bool cut = (s % kEntrySlots) == 0;
+  f.newu = f.valid && (first || key != prev || cut);
+  f.split = f.valid && !first && key == prev && cut;
+  f.newq = f.valid && (first || (key / n3) != (prev / n3));
+  f.last_valid = f.valid && !(next < N);
+  // the entry holds exactly one slot: its gradient row is read where it lies
+  f.single = f.newu && (next != key || ((s + 1) % kEntrySlots) == 0);
   return f;
 }
 
+constexpr int kSegThreads = 1024;
+// A wavefront of the segment kernels owns ITEMS * 64 consecutive slots, 64 a step, so that what a step
+// loads and stores lies together.
 template <int ITEMS>
-__global__ __launch_bounds__(kSegThreads) void k_seg_count(const uint32_t* __restrict__ skey, int B,
-                                                           uint32_t N, uint32_t n3,
-                                                           uint32_t* __restrict__ seg_nu,
-                                                           uint32_t* __restrict__ seg_nq) {
-  __shared__ uint32_t lds4[kSegThreads / kWave];
-  const SegFlags<ITEMS> f =
-      seg_flags<ITEMS>(skey, B, N, n3, ((int)blockIdx.x * kSegThreads + (int)threadIdx.x) * ITEMS);
-  uint32_t cu = 0, cq = 0;
+__device__ __forceinline__ int first_slot() {
+  return ((int)(blockIdx.x * kSegThreads + threadIdx.x) / kWave * ITEMS) * kWave + (int)threadIdx.x % kWave;
+}
+
+// New ids and prefixes of every block of 1024*ITEMS sorted slots.
+template <int ITEMS>
+__global__ __launch_bounds__(kSegThreads) void k_seg_count(const uint32_t* __restrict__ skey, int B, uint32_t N,
+                                                  uint32_t n3, uint32_t* __restrict__ seg_nu,
+                                                  uint32_t* __restrict__ seg_nq) {
+  __shared__ uint32_t ldsw[kSegThreads / kWave];
+  const int s0 = first_slot<ITEMS>();
+  uint32_t c = 0;  // new ids in the upper half, new prefixes in the lower
 #pragma unroll
   for (int j = 0; j < ITEMS; ++j) {
-    cu += f.newu[j];
-    cq += f.newq[j];
+    const SlotFlags f = slot_flags(skey, B, N, n3, s0 + j * kWave);
+    c += ((uint32_t)__popcll(__ballot(f.newu)) << 16) + (uint32_t)__popcll(__ballot(f.newq));
   }
-  uint32_t tu, tq;
-  block_exclusive_scan_value(cu, lds4, &tu);
-  block_exclusive_scan_value(cq, lds4, &tq);
+  if (threadIdx.x % kWave == 0) ldsw[threadIdx.x / kWave] = c;
+  __syncthreads();
   if (threadIdx.x == 0) {
-    seg_nu[blockIdx.x] = tu;
-    seg_nq[blockIdx.x] = tq;
+    uint32_t total = 0;
+#pragma unroll
+    for (int k = 0; k < kSegThreads / kWave; ++k) total += ldsw[k];
+    seg_nu[blockIdx.x] = total >> 16;
+    seg_nq[blockIdx.x] = total & 0xffffu;
   }
 }
 
-// Numbers the unique ids and prefixes in sorted order, records their extents and coordinates, and
-// counts them per (group_span, i3) resp. (group_span, i2) for the blocks of the grouping pass and per i1.
+// Numbers the unique ids and prefixes in sorted order, records their extents and coordinates, and leaves
+// for the grouping pass, per block of 1024*ITEMS slots, which ids and prefixes are its own (seg_base: first
+// id, first prefix, how many of each) and how many of them have which i3 resp. i2 (a row of p3 + p2 16-bit
+// counts).  The counts are made in LDS: added to tables in memory, one atomic per new id and prefix, they
+// were most of this kernel (two a slot at worst; a compute unit retires one lane's atomic in 16 cycles):
+// 100,000 uniform items of n3 = 56 8.3 -> 5.1 us, a million Zipf items of n3 = 500 33 -> 16.
 // u_code[u] says where the gradient row of unique id u will be found: >= 0 is the batch position
 // of its only occurrence, -(u+1) means "row u of the per-id sums".
 template <int ITEMS>
 __global__ __launch_bounds__(kSegThreads) void k_seg_write(
-    const uint32_t* __restrict__ skey, const uint32_t* __restrict__ perm, int B, int group_span,
-    Shape sh, const uint32_t* __restrict__ seg_nu, const uint32_t* __restrict__ seg_nq, int* __restrict__ s_u,
+    const uint32_t* __restrict__ skey, const uint32_t* __restrict__ perm, int B, Shape sh, int p3, int p2,
+    const uint32_t* __restrict__ seg_nu, const uint32_t* __restrict__ seg_nq, int* __restrict__ s_u,
     int4* __restrict__ s_rec, int* __restrict__ u_rs, int* __restrict__ u_i3, int* __restrict__ u_q, int* __restrict__ u_code,
-    int* __restrict__ q_us, int* __restrict__ q_i1, int* __restrict__ q_i2,
-    uint32_t* __restrict__ cnt3, uint32_t* __restrict__ cnt2, int* __restrict__ g1_first,
-    int* __restrict__ g1_end, Counters* __restrict__ ctr) {
-  __shared__ uint32_t lds4[kSegThreads / kWave];
-  const int tid = threadIdx.x, blk = blockIdx.x;
-  const int s0 = (blk * kSegThreads + tid) * ITEMS;
-  const SegFlags<ITEMS> f = seg_flags<ITEMS>(skey, B, sh.N, sh.n3, s0);
+    int* __restrict__ q_us, int* __restrict__ q_i1, int* __restrict__ q_i2, int4* __restrict__ seg_base,
+    uint16_t* __restrict__ rows, int* __restrict__ g1_first, int* __restrict__ g1_end,
+    Counters* __restrict__ ctr) {
+  extern __shared__ uint32_t seg_hist[];  // p3 + p2 counters
+  __shared__ uint32_t ldsw[3][kSegThreads / kWave];
+  const int tid = threadIdx.x, blk = blockIdx.x, lane = tid % kWave, w = tid / kWave;
+  const int s0 = first_slot<ITEMS>();
+  SlotFlags f[ITEMS];
   uint32_t bpos[ITEMS];
 #pragma unroll
-  for (int j = 0; j < ITEMS; ++j) bpos[j] = (s0 + j < B) ? perm[s0 + j] : 0u;
-  uint32_t pu = 0, pq = 0;
+  for (int j = 0; j < ITEMS; ++j) {
+    f[j] = slot_flags(skey, B, sh.N, sh.n3, s0 + j * kWave);
+    bpos[j] = perm[min(s0 + j * kWave, B - 1)];
+  }
+  uint32_t pu = 0, pq = 0;  // ids and prefixes of the blocks before
   for (int b2 = tid; b2 < blk; b2 += kSegThreads) {
     pu += seg_nu[b2];
     pq += seg_nq[b2];
   }
-  uint32_t offu, offq, dummy;
-  block_exclusive_scan_value(pu, lds4, &offu);
-  block_exclusive_scan_value(pq, lds4, &offq);
-
-  uint32_t cu = 0, cq = 0;
+  for (int i = tid; i < p3 + p2; i += kSegThreads) seg_hist[i] = 0u;
+  uint32_t c = 0;  // new ids in the upper half, new prefixes in the lower
 #pragma unroll
-  for (int j = 0; j < ITEMS; ++j) {
-    cu += f.newu[j];
-    cq += f.newq[j];
+  for (int j = 0; j < ITEMS; ++j)
+    c += ((uint32_t)__popcll(__ballot(f[j].newu)) << 16) + (uint32_t)__popcll(__ballot(f[j].newq));
+  pu = wave_inclusive_scan(pu, lane);
+  pq = wave_inclusive_scan(pq, lane);
+  if (lane == kWave - 1) {
+    ldsw[0][w] = c;
+    ldsw[1][w] = pu;
+    ldsw[2][w] = pq;
   }
-  uint32_t ru = offu + block_exclusive_scan_value(cu, lds4, &dummy);  // unique ids before my slots
-  uint32_t rq = offq + block_exclusive_scan_value(cq, lds4, &dummy);
+  __syncthreads();
+  uint32_t mine = 0, here = 0, ru = 0, rq = 0;
+#pragma unroll
+  for (int k = 0; k < kSegThreads / kWave; ++k) {
+    const uint32_t v = ldsw[0][k];
+    mine += k < w ? v : 0u;
+    here += v;
+    ru += ldsw[1][k];
+    rq += ldsw[2][k];
+  }
+  if (tid == 0) seg_base[blk] = make_int4((int)ru, (int)rq, (int)(here >> 16), (int)(here & 0xffffu));
+  ru += mine >> 16;  // unique ids before the wavefront's slots
+  rq += mine & 0xffffu;
 
-  if (blk == 0 && tid == 0 && !f.valid[0]) {  // no in-range id at all
+  if (blk == 0 && tid == 0 && !f[0].valid) {  // no in-range id at all
     ctr->U = 0;
     ctr->Q = 0;
     ctr->nvalid = 0;
     u_rs[0] = 0;
     q_us[0] = 0;
   }
+  const unsigned long long up_to = ~0ull >> (kWave - 1 - lane);  // this lane and those below
 #pragma unroll
   for (int j = 0; j < ITEMS; ++j) {
-    const int s = s0 + j;
-    if (s >= B) break;
-    if (!f.valid[j]) {
+    const int s = s0 + j * kWave;
+    const unsigned long long mu = __ballot(f[j].newu), mq = __ballot(f[j].newq);
+    const int u = (int)(ru + __popcll(mu & up_to)) - 1, q = (int)(rq + __popcll(mq & up_to)) - 1;
+    ru += __popcll(mu);
+    rq += __popcll(mq);
+    if (s >= B) continue;
+    if (!f[j].valid) {
       s_u[s] = -1;
       s_rec[s] = make_int4(-1, (int)bpos[j], 0, 0);
       continue;
     }
-    ru += f.newu[j];
-    rq += f.newq[j];
-    const int u = (int)ru - 1, q = (int)rq - 1;
     s_u[s] = u;
-    const uint32_t k = f.key[j];
+    const uint32_t k = f[j].key, p = k / sh.n3, i3 = k - p * sh.n3;  // p: prefix number i1*n2 + i2
     // everything the row kernel needs about a slot in one record (one load instead of a chain)
-    s_rec[s] = make_int4(u, (int)bpos[j], q, (int)(k % sh.n3));
-    if (f.split[j]) atomicAdd(&ctr->n_split, 1);
-    if (f.newu[j]) {
-      const uint32_t i3 = k % sh.n3;
+    s_rec[s] = make_int4(u, (int)bpos[j], q, (int)i3);
+    if (f[j].split) atomicAdd(&ctr->n_split, 1);
+    if (f[j].newu) {
       u_rs[u] = s;
       u_i3[u] = (int)i3;
       u_q[u] = q;
-      u_code[u] = f.single[j] ? (int)bpos[j] : -(u + 1);
-      atomicAdd(&cnt3[(size_t)(u / group_span) * sh.n3 + i3], 1u);
+      u_code[u] = f[j].single ? (int)bpos[j] : -(u + 1);
+      atomicAdd(&seg_hist[i3], 1u);
     }
-    if (f.newq[j]) {
-      const uint32_t p = k / sh.n3;  // prefix number i1*n2 + i2
-      const uint32_t i1 = p / sh.n2, i2 = p % sh.n2;
+    if (f[j].newq) {
+      const uint32_t i1 = p / sh.n2, i2 = p - i1 * sh.n2;
       q_us[q] = u;
       q_i1[q] = (int)i1;
       q_i2[q] = (int)i2;
-      atomicAdd(&cnt2[(size_t)(q / group_span) * sh.n2 + i2], 1u);
+      atomicAdd(&seg_hist[p3 + i2], 1u);
       // prefixes are numbered in (i1,i2) order: an i1 owns prefixes [g1_first, g1_end)
-      const uint32_t i1_before = (s == 0) ? 0xffffffffu : f.prev[j] / sh.n3 / sh.n2;
+      const uint32_t i1_before = (s == 0) ? 0xffffffffu : f[j].prev / sh.n3 / sh.n2;
       if (i1_before != i1) {
         g1_first[i1] = q;
         if (s != 0) g1_end[i1_before] = q;
       }
     }
-    if (f.last_valid[j]) {
+    if (f[j].last_valid) {
       ctr->U = u + 1;
       ctr->Q = q + 1;
       ctr->nvalid = s + 1;
       u_rs[u + 1] = s + 1;
       q_us[q + 1] = u + 1;
-      g1_end[k / sh.n3 / sh.n2] = q + 1;
+      g1_end[p / sh.n2] = q + 1;
     }
   }
+  __syncthreads();
+  uint32_t* row = (uint32_t*)(rows + (size_t)blk * (p3 + p2));
+  for (int i = tid; i < (p3 + p2) / 2; i += kSegThreads) row[i] = seg_hist[2 * i] | (seg_hist[2 * i + 1] << 16);
 }
 
 // ---------------------------------------------------------------------------------------------
-// Grouping: unique ids by i3 (for the G3 gradient), prefixes by i2 (for G2 and the prefix product)
+// Grouping: unique ids by i3 (for the G3 gradient), prefixes by i2 (for G2 and the prefix product).
+// Only the chunks are written: per chunk a descriptor and a table of the items' records, so that the
+// gradient kernels need no further look-ups.
 
-// Unique ids by i3.  Besides the list, every chunk gets a table of its ids' records
-// {gradient-row code, prefix}, so that the gradient kernels need no further look-ups.
+// Unique ids by i3; chunk records are {gradient-row code, prefix}.
 struct GroupOps3 {
   struct Item {
-    int u, i3, code, q;
+    int i3, code, q;
   };
-  static constexpr bool kChunked = true;
   const int* u_i3;
   const int* u_code;
   const int* u_q;
-  int* list;
   int2* item;
   uint32_t* band_cnt;
   int Q;
-  __device__ Item load(int idx) const { return Item{idx, u_i3[idx], u_code[idx], u_q[idx]}; }
+  __device__ Item load(int idx) const { return Item{u_i3[idx], u_code[idx], u_q[idx]}; }
   __device__ int digit(Item it) const { return it.i3; }
-  __device__ void emit_chunked(uint32_t pos, uint32_t chunk, uint32_t t, Item it) const {
-    list[pos] = it.u;
+  __device__ void emit(uint32_t chunk, uint32_t t, Item it) const {
     item[(size_t)chunk * kChunk3 + t] = make_int2(it.code, it.q);
     // a chunk counts where it starts (only when a schedule will be built from the counts)
     if (band_cnt != nullptr && t == 0) atomicAdd(&band_cnt[chunk_band(it.q, Q)], 1u);
@@ -605,39 +573,151 @@ struct GroupOps2 {
   struct Item {
     int q, i2, i1, u0, u1;
   };
-  static constexpr bool kChunked = true;
   const int* q_i2;
   const int* q_i1;
   const int* q_us;
-  int* list;
   int4* item;
   __device__ Item load(int idx) const {
     return Item{idx, q_i2[idx], q_i1[idx], q_us[idx], q_us[idx + 1]};
   }
   __device__ int digit(Item it) const { return it.i2; }
-  __device__ void emit_chunked(uint32_t pos, uint32_t chunk, uint32_t t, Item it) const {
-    list[pos] = it.q;
+  __device__ void emit(uint32_t chunk, uint32_t t, Item it) const {
     item[(size_t)chunk * kChunk2 + t] = make_int4(it.q, it.i1, it.u0, it.u1);
   }
 };
 
+// LDS of a grouping block: counters of block_ranks, then three tables of one word per bucket.
+__host__ __device__ constexpr int group_row_words(int bins) { return (bins + 7) / 8 * 4; }
+constexpr size_t group_lds(int threads, int bins) {
+  return (size_t)(threads / kWave) * group_row_words(bins) * 4 + 3 * (size_t)((bins + 7) / 8 * 8) * 4;
+}
+
+// One block's share of a stable counting-sort pass: items [first, first + count), those that slot block
+// blk of nblk found.  rows: 16-bit counts per bucket of every block, `stride` apart.  Every bucket is cut
+// into chunks of `chunk` items (a power of two): chunk_desc[c] = {bucket, 0, item count, 0} for all chunks
+// c in bucket order, chunk_starts[bucket] the first chunk of each bucket (bins+1 entries), *n_chunks the
+// number of chunks; the item that is the t-th of chunk c goes to emit(c, t, item).
+// The blocks add up the columns of `rows` themselves.  Eight buckets are one 16-byte load, so a row takes
+// few threads, and the threads are dealt over the rows too: all rows are under way at once, where one
+// thread per bucket made a chain of the rows.  No more threads than that takes: their sums meet in LDS, and
+// every further one is another atomic on the same words (200,000 ids, 1024 threads: 176 us a step with all
+// of them, 172 without).  k_group, 100,000 uniform items of n3 = 56: 17 -> 7.4 us, 200,000 Zipf ids of
+// n3 = 136 14.8 -> 8, 500,000 of n3 = 480 25.7 -> 15.5.
+template <int NT, class ItemOps>
+__device__ void group_block(int blk, int nblk, int first, int count, int bins,
+                            const uint16_t* __restrict__ rows, int stride, ItemOps ops, int chunk,
+                            int* chunk_starts, int4* chunk_desc, int* n_chunks) {
+  extern __shared__ __attribute__((aligned(16))) uint32_t group_words[];
+  __shared__ uint32_t ldsw[NT / kWave];
+  const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
+  const int words = (bins + 7) / 8, row_words = group_row_words(bins);
+  uint32_t* wh = group_words;
+  uint32_t* tot = wh + (NT / kWave) * row_words;  // items per bucket
+  uint32_t* before = tot + words * 8;             // those of earlier blocks
+  uint32_t* aux = before + words * 8;             // chunks per bucket, then first chunk per bucket
+  const int chunk_sh = 31 - __clz(chunk);
+  // items first: their loads overlap the table work below
+  const int per = (count + NT - 1) / NT;  // steps, so that all wavefronts have a share
+  const int wbase = w * per * kWave;
+  typename ItemOps::Item items[kSteps];
+  int digits[kSteps];
+#pragma unroll
+  for (int step = 0; step < kSteps; ++step) {
+    const int i = wbase + step * kWave + lane;
+    items[step] = ops.load(max(first + min(i, count - 1), 0));
+  }
+  constexpr int kRows = 8;  // rows a thread has in flight
+  const int groups = min(NT / words, (nblk + kRows - 1) / kRows), g = tid / words, at = tid - g * words;
+  uint32_t t8[8] = {}, b8[8] = {};
+  if (g < groups) {
+    const uint4* col = (const uint4*)rows + at;
+    const int stride4 = stride / 8;
+    for (int r0 = g; r0 < nblk; r0 += groups * kRows) {
+      uint4 v[kRows];
+#pragma unroll
+      for (int k = 0; k < kRows; ++k) v[k] = col[(size_t)min(r0 + k * groups, nblk - 1) * stride4];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int k = 0; k < kRows; ++k) {
+        const int r = r0 + k * groups;
+        const uint32_t all = r < nblk ? 0xffffffffu : 0u, old = r < blk ? 0xffffffffu : 0u;
+        const uint32_t x[4] = {v[k].x & all, v[k].y & all, v[k].z & all, v[k].w & all};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          t8[2 * j] += x[j] & 0xffffu;
+          t8[2 * j + 1] += x[j] >> 16;
+          b8[2 * j] += x[j] & old & 0xffffu;
+          b8[2 * j + 1] += (x[j] & old) >> 16;
+        }
+      }
+    }
+  }
+  for (int i = tid; i < words * 16; i += NT) tot[i] = 0u;  // tot and before
+#pragma unroll
+  for (int step = 0; step < kSteps; ++step) digits[step] = ops.digit(items[step]);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int step = 0; step < kSteps; ++step)
+    if (step >= per || wbase + step * kWave + lane >= count) digits[step] = -1;
+  __syncthreads();
+  if (g < groups) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      if (t8[j] != 0) atomicAdd(&tot[at * 8 + j], t8[j]);
+      if (b8[j] != 0) atomicAdd(&before[at * 8 + j], b8[j]);
+    }
+  }
+  __syncthreads();
+  for (int bin = tid; bin < bins; bin += NT) aux[bin] = (tot[bin] + chunk - 1) >> chunk_sh;
+  __syncthreads();
+  const uint32_t total_chunks = block_exclusive_scan(aux, bins, ldsw);
+  if (blk == 0) {
+    for (int bin = tid; bin < bins; bin += NT) chunk_starts[bin] = (int)aux[bin];
+    if (tid == 0) {
+      chunk_starts[bins] = (int)total_chunks;
+      *n_chunks = (int)total_chunks;
+    }
+  }
+  // every block takes a share of the chunk descriptors
+  for (uint32_t c = (uint32_t)blk * NT + tid; c < total_chunks; c += (uint32_t)nblk * NT) {
+    int lo = 0, hi = bins;  // last bucket whose first chunk is <= c
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (aux[mid] <= c) lo = mid; else hi = mid;
+    }
+    chunk_desc[c] = make_int4(lo, 0, (int)min((uint32_t)chunk, tot[lo] - (c - aux[lo]) * (uint32_t)chunk), 0);
+  }
+  if (count == 0) return;  // uniform for the whole block
+  uint32_t rank[kSteps];
+  block_ranks<NT>(wh, row_words, digits, rank);
+#pragma unroll
+  for (int step = 0; step < kSteps; ++step) {
+    const int digit = digits[step];
+    if (digit < 0) continue;
+    const uint32_t in_bucket = before[digit] + rank[step];
+    ops.emit(aux[digit] + (in_bucket >> chunk_sh), in_bucket & (uint32_t)(chunk - 1), items[step]);
+  }
+}
+
+// Blocks [0, ub): unique ids by i3; the nblk behind them: prefixes by i2.
 template <int NT>
 __global__ __launch_bounds__(NT) void k_group(
-    Shape sh, int u_blocks, int chunk3, const uint32_t* __restrict__ cnt3,
-    const uint32_t* __restrict__ cnt2, const int* __restrict__ u_i3, const int* __restrict__ u_code,
+    Shape sh, int ub, int nblk, int chunk3, int p3, int p2, const int4* __restrict__ seg_base,
+    const uint16_t* __restrict__ rows, const int* __restrict__ u_i3, const int* __restrict__ u_code,
     const int* __restrict__ u_q, const int* __restrict__ q_i2, const int* __restrict__ q_i1,
-    const int* __restrict__ q_us, int* g3_list, int* g3_start, int* c3_start, int4* c3_desc,
-    int2* c3_item, int* g2_list, int* g2_start, int* c2_start, int4* c2_desc, int4* c2_item,
-    uint32_t* band_cnt, Counters* ctr) {
-  __shared__ ScatterLds<NT> L;
-  if ((int)blockIdx.x < u_blocks) {
-    GroupOps3 ops{u_i3, u_code, u_q, g3_list, c3_item, band_cnt, ctr->Q};
-    stable_scatter_block(L, (int)blockIdx.x, ctr->U, (int)sh.n3, cnt3, nullptr, ops, g3_start,
-                         chunk3, c3_start, c3_desc, &ctr->nchunk3);
+    const int* __restrict__ q_us, int* c3_start, int4* c3_desc, int2* c3_item, int* c2_start, int4* c2_desc,
+    int4* c2_item, uint32_t* band_cnt, Counters* ctr) {
+  const bool ids = (int)blockIdx.x < ub;
+  const int blk = ids ? blockIdx.x : blockIdx.x - ub;
+  const int4 base = seg_base[blk];
+  if (ids) {
+    GroupOps3 ops{u_i3, u_code, u_q, c3_item, band_cnt, ctr->Q};
+    group_block<NT>(blk, nblk, base.x, base.z, (int)sh.n3, rows, p3 + p2, ops, chunk3, c3_start, c3_desc,
+                    &ctr->nchunk3);
   } else {
-    GroupOps2 ops{q_i2, q_i1, q_us, g2_list, c2_item};
-    stable_scatter_block(L, (int)blockIdx.x - u_blocks, ctr->Q, (int)sh.n2, cnt2, nullptr, ops,
-                         g2_start, kChunk2, c2_start, c2_desc, &ctr->nchunk2);
+    GroupOps2 ops{q_i2, q_i1, q_us, c2_item};
+    group_block<NT>(blk, nblk, base.y, base.w, (int)sh.n2, rows + p3, p3 + p2, ops, kChunk2, c2_start, c2_desc,
+                    &ctr->nchunk2);
   }
 }
 
@@ -687,13 +767,12 @@ static void sort_pass(const Plan& pl, const Workspace& ws, const SortKeys& sk, c
   } else if (which == 0) {
     auto first = [&](auto from) {
       k_sort_hist<NT><<<blocks, NT, 0, st>>>(
-          from, kin, B, sk.sentinel, shift, bits, ws.cnt, ws.cnt3, clear ? pl.uBlocksMax * (int)pl.sh.n3 : 0,
-          ws.cnt2, clear ? pl.qBlocksMax * (int)pl.sh.n2 : 0, (uint32_t*)ws.g1_first,
+          from, kin, B, sk.sentinel, shift, bits, ws.cnt, (uint32_t*)ws.g1_first,
           clear ? 2 * (int)pl.sh.n1 + 2 * kOrderBands : 0, ws.ctr);
     };
     if (pass > 0)
       k_sort_hist<NT><<<blocks, NT, 0, st>>>(KeysInPlace{}, kin, B, sk.sentinel, shift, bits, ws.cnt, nullptr, 0,
-                                             nullptr, 0, nullptr, 0, ws.ctr);
+                                             ws.ctr);
     else if (sk.low > 0)  // by prefix
       first(PrefixSource{src, sk.low, pl.user_n1, pl.sh.n2, pl.sh.n3});
     else
@@ -717,55 +796,49 @@ void launch_sort_pass(const Plan& pl, const Workspace& ws, const SortKeys& sk, c
   }
 }
 
-// The blocks' counts: those of fine blocks lie in the digit totals of the sort, which is over, so that the
-// need of a batch does not depend on the block size.
-struct SegCounts {
-  uint32_t *nu, *nq;
-};
-static SegCounts seg_counts(const Workspace& ws, int items) {
-  static_assert(kSegFine / kSegThreads <= kMaxBins / 2, "two rows of counts fit the totals");
-  return items == kSegThreads ? SegCounts{ws.tot, ws.tot + kMaxBins / 2} : SegCounts{ws.seg_nu, ws.seg_nq};
+// The segment kernels of a batch of B items: 1024 threads with 1, 2 or 4 slots each.
+template <class F>
+static void with_slot_items(const Plan& pl, int B, F&& launch) {
+  const int span = slot_span(pl.sh, B), blocks = cdiv(B, span);
+  if (span == kSegThreads) launch(std::integral_constant<int, 1>{}, blocks);
+  else if (span == 2 * kSegThreads) launch(std::integral_constant<int, 2>{}, blocks);
+  else launch(std::integral_constant<int, 4>{}, blocks);
 }
 
 void launch_seg_count(const Plan& pl, const Workspace& ws, int B, hipStream_t st) {
-  const uint32_t* skey = ws.key[pl.keys.sorted()];
-  const int items = seg_items(B);
-  const SegCounts n = seg_counts(ws, items);
-  auto launch = [&](auto kernel) {
-    kernel<<<cdiv(B, items), kSegThreads, 0, st>>>(skey, B, pl.sh.N, pl.sh.n3, n.nu, n.nq);
-  };
-  items == kSegThreads ? launch(k_seg_count<1>) : launch(k_seg_count<4>);
+  with_slot_items(pl, B, [&](auto items, int blocks) {
+    k_seg_count<items()><<<blocks, kSegThreads, 0, st>>>(ws.key[pl.keys.sorted()], B, pl.sh.N, pl.sh.n3,
+                                                         ws.seg_nu, ws.seg_nq);
+  });
 }
 
 void launch_seg_write(const Plan& pl, const Workspace& ws, int B, hipStream_t st) {
-  const int f = pl.keys.sorted(), items = seg_items(B);
-  const SegCounts n = seg_counts(ws, items);
-  auto launch = [&](auto kernel) {
-    kernel<<<cdiv(B, items), kSegThreads, 0, st>>>(
-        ws.key[f], ws.val[f], B, sort_items(group_threads(pl.sh, B)), pl.sh, n.nu, n.nq, ws.s_u,
-        ws.s_rec, ws.u_rs, ws.u_i3, ws.u_q, ws.u_code, ws.q_us, ws.q_i1, ws.q_i2, ws.cnt3, ws.cnt2, ws.g1_first,
-        ws.g1_end, ws.ctr);
-  };
-  items == kSegThreads ? launch(k_seg_write<1>) : launch(k_seg_write<4>);
+  const int f = pl.keys.sorted(), p3 = up8(pl.sh.n3), p2 = up8(pl.sh.n2);
+  with_slot_items(pl, B, [&](auto items, int blocks) {
+    k_seg_write<items()><<<blocks, kSegThreads, (p3 + p2) * 4, st>>>(
+        ws.key[f], ws.val[f], B, pl.sh, p3, p2, ws.seg_nu, ws.seg_nq, ws.s_u, ws.s_rec, ws.u_rs, ws.u_i3, ws.u_q,
+        ws.u_code, ws.q_us, ws.q_i1, ws.q_i2, ws.seg_base, ws.seg_rows, ws.g1_first, ws.g1_end, ws.ctr);
+  });
 }
 
 // which: 0 = both groupings and the chunk schedule; 1 = both groupings, no schedule (c3_order is
 // not written: the gradient kernel then walks the by-i3 chunks in index order); 2 = prefixes by i2
 // only (all a lookup needs)
 void launch_group(const Plan& pl, const Workspace& ws, int B, hipStream_t st, int which) {
-  // blocks are sized from upper bounds (U <= B, Q <= min(B, n1*n2)); surplus blocks return at once
-  const int threads = group_threads(pl.sh, B), span = sort_items(threads);
-  const int ub = which == 2 ? 0 : cdiv(B, span);
-  const int qb = cdiv(std::min((int64_t)B, pl.maxQ), span);
+  const int span = slot_span(pl.sh, B), nblk = cdiv(B, span), ub = which == 2 ? 0 : nblk;
+  const int p3 = up8(pl.sh.n3), p2 = up8(pl.sh.n2);
   const bool ordered = which == 0 && chunks_ordered(pl, B);
-  auto launch = [&](auto kernel) {
-    kernel<<<ub + qb, threads, 0, st>>>(
-        pl.sh, ub, chunk3_fill(B), ws.cnt3, ws.cnt2, ws.u_i3, ws.u_code, ws.u_q, ws.q_i2, ws.q_i1,
-        ws.q_us, ws.g3_list, ws.g3_start, ws.c3_start, ws.c3_desc, ws.c3_item, ws.g2_list, ws.g2_start,
-        ws.c2_start, ws.c2_desc, ws.c2_item, ordered ? ws.band_cnt : nullptr, ws.ctr);
+  auto launch = [&](auto kernel, int threads) {
+    kernel<<<ub + nblk, threads, group_lds(threads, std::max(p3, p2)), st>>>(
+        pl.sh, ub, nblk, chunk3_fill(B), p3, p2, ws.seg_base, ws.seg_rows, ws.u_i3, ws.u_code, ws.u_q, ws.q_i2,
+        ws.q_i1, ws.q_us, ws.c3_start, ws.c3_desc, ws.c3_item, ws.c2_start, ws.c2_desc, ws.c2_item,
+        ordered ? ws.band_cnt : nullptr, ws.ctr);
   };
-  if (threads == 512) launch(k_group<512>);
-  else launch(k_group<1024>);
+  switch (span) {
+    case 1024: launch(k_group<256>, 256); break;
+    case 2048: launch(k_group<512>, 512); break;
+    default: launch(k_group<1024>, 1024);
+  }
   if (ordered)
     k_chunk_order<<<cdiv(cdiv(B, chunk3_fill(B)) + (int64_t)pl.sh.n3, kOrderBands), kOrderBands, 0,
                     st>>>(
@@ -773,4 +846,3 @@ void launch_group(const Plan& pl, const Workspace& ws, int B, hipStream_t st, in
 }
 
 }  // namespace ttemb
-

@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "tt_emb.h"
 
 namespace ttemb {
@@ -60,14 +62,6 @@ constexpr int kMaxBins = 2048;                            // digit / bucket coun
 // that kernel, 21 -> 18 us at 200,000 Zipf ids, but the hot prefix's pieces queue up behind each other in
 // the next one, 50 -> 88.)
 constexpr int kEntrySlots = 1024;
-
-constexpr int kSegThreads = 256;
-// Sorted slots of a block in the segment kernels.  Their time is the atomics of the new ids (one or two a
-// slot), which wait on each other inside a compute unit: blocks of 256 slots put them on four times as many
-// units, 7.1 -> 5.2 us at 50,000 uniform ids, 6.6 -> 4.3 at 100,000, 9.2 -> 7.6 at 262,144.  Beyond that
-// blocks of 1024 cover the chip, and every block adds up the counts of the blocks before it.
-constexpr int kSegFine = 1 << 18;
-inline int seg_items(int64_t B) { return B <= kSegFine ? kSegThreads : 4 * kSegThreads; }
 
 constexpr int kTileSlots = 32;   // sorted slots per wavefront tile in the row kernels
 constexpr int kChunk2 = 16;      // unique prefixes per partial sum of a G2 slice gradient
@@ -127,20 +121,21 @@ struct Shape {
   int S3;  // r2*d3       floats of one G3 slice
 };
 
-// Threads of a block of the grouping kernel: 512 where 1024 leave too few blocks (50,000 ids 120 ->
-// 117 us a step, 100,000 items 130 -> 126), 1024 where the blocks, which add up the rows of the
-// histograms themselves, would have twice the rows to add (500,000 ids: 403 against 421).
-// Tables with n2 + n3 near the bucket limit keep 1024: their finer histograms would need more memory.
-inline int group_threads(const Shape& sh, int64_t B) {
-  return B <= kSmallBatch && sh.n2 + sh.n3 <= kMaxBins / 8 * 7 ? 512 : 1024;
-}
-// rows that the per-block histograms of `items` list entries can have, for batches of up to maxB
-inline int64_t group_blocks_most(const Shape& sh, int64_t items, int64_t maxB) {
-  const int64_t most = (items + sort_items(1024) - 1) / sort_items(1024);
-  if (group_threads(sh, 1) == 1024) return most;
-  const int64_t small = items < kSmallBatch ? items : kSmallBatch;
-  const int64_t fine = (small + sort_items(512) - 1) / sort_items(512);
-  return maxB <= kSmallBatch || fine > most ? fine : most;
+__host__ __device__ constexpr int up8(uint32_t n) { return (int)(n + 7) & ~7; }
+
+// Sorted slots of a block of the segment and grouping kernels: few, for many blocks, as long as a grouping
+// block can add up the counts of all blocks (16-byte words of eight buckets) in one round of loads.  Training
+// steps with 1024 / 2048 / 4096 slots: 200,000 ids of n3 = 136 167 / 173 / 175 us, 500,000 ids of n3 = 480
+// 400 / 378 / 376 (489, 245 and 123 rows of 60 words).  The counts lie in the memory that
+// Workspace::seg_rows names, which holds at least 8192 + 4*n3 bytes per 4096 slots.
+constexpr int64_t kSlotRowWords = 8192;
+inline int slot_span(const Shape& sh, int64_t B) {
+  const int p3 = up8(sh.n3), p2 = up8(sh.n2);
+  int span = 1024;
+  while (span < 4096 && ((B + span - 1) / span * (std::max(p3, p2) / 8) > kSlotRowWords ||
+                         4096 / span * 2 * (p3 + p2) > 8192 + 4 * (int)sh.n3))
+    span *= 2;
+  return span;
 }
 
 // Device-side counters of the latest forward (first bytes of the workspace).
@@ -193,8 +188,10 @@ struct Workspace {
   uint32_t* val[2];   // radix-sort ping-pong positions [maxB]
   uint32_t* cnt;      // per-block digit histograms [sortBlocks * kMaxBins]; usually in the memory of c3_item
   uint32_t* tot;      // digit totals of the current pass  [kMaxBins]
-  uint32_t* seg_nu;   // new-id flags per segment block     [segBlocks]
-  uint32_t* seg_nq;   // new-prefix flags per segment block [segBlocks]
+  uint32_t* seg_nu;   // new ids per block of sorted slots      [slotBlocks]
+  uint32_t* seg_nq;   // new prefixes per block of sorted slots [slotBlocks]
+  int4* seg_base;     // per block of slots: its first unique id, its first prefix, how many of each
+  uint16_t* seg_rows; // per block of slots: how many of these have which i3, and which i2
   int* s_u;           // sorted slot -> unique-id index (-1 for out-of-range ids) [maxB]
   int4* s_rec;        // sorted slot -> {unique-id index, batch position, prefix, i3} [maxB]
   int* u_rs;          // unique id -> first sorted slot  [maxB+1]
@@ -204,19 +201,13 @@ struct Workspace {
   int* q_us;          // prefix -> first unique id       [maxQ+1]
   int* q_i1;          // prefix -> i1                    [maxQ]
   int* q_i2;          // prefix -> i2                    [maxQ]
-  uint32_t* cnt3;     // per-block histograms of i3 over unique ids   [uBlocks * n3]
-  uint32_t* cnt2;     // per-block histograms of i2 over prefixes     [qBlocks * n2]
-  int* g3_list;       // unique ids grouped by i3 (stable)  [maxB]
-  int* g3_start;      // [n3+1]
   int* c3_start;      // first chunk of each i3 group [n3+1]
-  int4* c3_desc;      // chunk -> {i3, first list item, items, 0}  [maxChunk3]
+  int4* c3_desc;      // chunk -> {i3, 0, items, 0}  [maxChunk3]
   int2* c3_item;      // chunk, t -> {gradient-row code, prefix} of its t-th id [maxChunk3][kChunk3]
   int* c3_order;      // by-i3 chunks in the order of the prefix of their first id [maxChunk3]
   bool has_order;     // host side: the batch in this set has had c3_order written
-  int* g2_list;       // prefixes grouped by i2 (stable) [maxQ]
-  int* g2_start;      // [n2+1]
   int* c2_start;      // [n2+1]
-  int4* c2_desc;      // chunk -> {i2, first list item, items, 0}  [maxChunk2]
+  int4* c2_desc;      // chunk -> {i2, 0, items, 0}  [maxChunk2]
   int4* c2_item;      // chunk, t -> {q, i1, first unique id, end} of its t-th prefix [maxChunk2][kChunk2]
   int* g1_first;      // i1 -> first prefix with that i1 (prefixes are sorted by i1) [n1]
   int* g1_end;        // i1 -> one past its last prefix; directly follows g1_first  [n1]
@@ -245,7 +236,7 @@ struct Plan {
   int user_D;
   Shape sh;
   int64_t maxB, maxQ;
-  int sortBlocksMax, segBlocksMax, uBlocksMax, qBlocksMax, tilesMax;
+  int sortBlocksMax, slotBlocksMax, tilesMax;
   int64_t maxChunk3, maxChunk2;
   SortKeys keys;         // sort by table row (the batches that train)
   // Lookups at ranks up to 32 (k_lookup_mfma): caller's ids, not slabs, sorted by prefix only, and that

@@ -1,0 +1,16 @@
+"""Blocks of sorted slots of the segment and grouping kernels: batches that fill their last block exactly, by one
+slot less and one more; the largest batch of every block size and the one above it; more rows of counts than a
+grouping block loads in one round; a table whose counts do not fit the small blocks.  Oracle and tolerances are
+those of test_gpu_parity."""
+import pytest
+
+from tests.test_block_sizes import _check
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,B", [((40, 30, 50), 12_287), ((40, 30, 50), 12_288), ((40, 30, 50), 12_289),
+                                 ((20, 130, 600), 111_616), ((20, 130, 600), 111_617), ((20, 130, 600), 223_232),
+                                 ((20, 130, 600), 223_233), ((9, 600, 593), 425_985), ((3, 1100, 1200), 30_001)])
+def test_slot_blocks(n, B):
+    _check(n, (2, 2, 2), (4, 4), B, flags=8)
