@@ -85,6 +85,64 @@ static_assert((kChunk2 & (kChunk2 - 1)) == 0 && (kChunk3 & (kChunk3 - 1)) == 0 &
                   (kChunk3Min & (kChunk3Min - 1)) == 0,
               "chunk sizes are powers of two: positions inside a bucket are cut with shifts");
 
+// Column sums over the rows of 16-bit bucket counts that the nblk blocks of a pass left, `stride` counts
+// apart: per bucket the items of all blocks (tot) and those of blocks before blk (before).  Eight buckets are
+// one 16-byte load (`words` of them a row), so a row takes few threads, and the threads are dealt over the
+// rows too: all rows are under way at once, where one thread per bucket makes a chain of the rows.  No more
+// threads than that takes: their sums meet in LDS, and every further one is another atomic on the same words
+// (200,000 ids, 1024 threads in the grouping kernel: 176 us a step with all of them, 172 without).
+template <int ROWS>  // rows a thread has in flight
+struct ColumnSums {
+  uint32_t t8[8], b8[8];
+  int at;  // this thread's word of a row, or -1
+  __device__ __forceinline__ void load(const uint16_t* __restrict__ rows, int stride, int words, int nblk, int blk) {
+    const int groups = min((int)blockDim.x / words, (nblk + ROWS - 1) / ROWS), g = (int)threadIdx.x / words;
+    at = g < groups ? (int)threadIdx.x - g * words : -1;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) t8[j] = b8[j] = 0u;
+    if (at < 0) return;
+    const uint4* col = (const uint4*)rows + at;
+    const int stride4 = stride / 8;
+    for (int r0 = g; r0 < nblk; r0 += groups * ROWS) {
+      uint4 v[ROWS];
+#pragma unroll
+      for (int k = 0; k < ROWS; ++k) v[k] = col[(size_t)min(r0 + k * groups, nblk - 1) * stride4];
+      __builtin_amdgcn_sched_barrier(0);
+      // Eight rows are added two counts to a word: eight times at most 4096 items stay below 2^16.
+#pragma unroll
+      for (int k0 = 0; k0 < ROWS; k0 += 8) {
+        uint32_t t[4] = {}, b[4] = {};
+#pragma unroll
+        for (int k = k0; k < k0 + 8; ++k) {
+          const int r = r0 + k * groups;
+          const uint32_t x[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            t[j] += r < nblk ? x[j] : 0u;
+            b[j] += r < blk ? x[j] : 0u;
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          t8[2 * j] += t[j] & 0xffffu;
+          t8[2 * j + 1] += t[j] >> 16;
+          b8[2 * j] += b[j] & 0xffffu;
+          b8[2 * j + 1] += b[j] >> 16;
+        }
+      }
+    }
+  }
+  // tot and before have been cleared, with a barrier behind it; the caller's next barrier ends the sums
+  __device__ __forceinline__ void add_to(uint32_t* tot, uint32_t* before) const {
+    if (at < 0) return;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      if (t8[j] != 0) atomicAdd(&tot[at * 8 + j], t8[j]);
+      if (b8[j] != 0) atomicAdd(&before[at * 8 + j], b8[j]);
+    }
+  }
+};
+
 // Stable ranks of a block's items in their buckets.  Every wavefront holds up to 256 consecutive items,
 // 64 a step (digit -1: no item); the wavefronts' runs follow each other.  wh: one row of row_words words
 // (a multiple of four) per wavefront, two 16-bit buckets a word: a wavefront owns 256 items and a block at
@@ -149,24 +207,26 @@ __device__ __forceinline__ void block_ranks(uint32_t* wh, int row_words, const i
 template <int NT>
 struct alignas(16) ScatterLds {
   uint32_t wh[NT / kWave][kMaxBins / 2];  // counters of block_ranks
-  uint32_t tot[kMaxBins];                 // bucket totals, then this block's first output per bucket
+  uint32_t tot[kMaxBins];                 // bucket totals, then first output per bucket
+  uint32_t before[kMaxBins];              // items of earlier blocks per bucket, then this block's first output
   uint32_t ldsw[NT / kWave];
 };
+
+// Words of eight 16-bit counts in a row of a sort block.
+__host__ __device__ constexpr int sort_row_words(int bins) { return bins < 8 ? 1 : bins / 8; }
 
 // One block's share of a stable counting-sort pass over n_items items (block blk of NT threads owns
 // items [blk*4*NT, +4*NT), each of its wavefronts 256 of them in order).  With tot != nullptr,
 // cnt[b][bin] holds, per bucket, the items of blocks before b and tot[bin] the bucket totals (both
 // from a column-scan kernel over the blocks' histograms); with tot == nullptr, cnt holds the
-// blocks' own histograms and every block adds up its columns itself (cheaper than one more launch
-// when there are few blocks).
+// blocks' own histograms as rows of 16-bit counts and every block adds up its columns itself.
 // ItemOps: Item load(int idx); int digit(Item); void emit(uint32_t pos, Item).
 template <int NT, class ItemOps>
-__device__ void stable_scatter_block(ScatterLds<NT>& L, int blk, int n_items, int bins,
+__device__ void stable_scatter_block(ScatterLds<NT>& L, int blk, int nblk, int n_items, int bins,
                                      const uint32_t* __restrict__ cnt,
                                      const uint32_t* __restrict__ tot, ItemOps ops) {
   constexpr int kItems = sort_items(NT);
   const int tid = threadIdx.x;
-  const int nblk = (n_items + kItems - 1) / kItems;
 
   // items first: their loads overlap the table work below
   const int w = tid / kWave, lane = tid % kWave;
@@ -178,34 +238,29 @@ __device__ void stable_scatter_block(ScatterLds<NT>& L, int blk, int n_items, in
     const int idx = wbase + step * kWave + lane;
     items[step] = ops.load(idx < n_items ? idx : 0);
   }
-  uint32_t before[kMaxBins / NT];  // items of my buckets in earlier blocks
+  if (tot != nullptr) {
+    uint32_t total[kMaxBins / NT], earlier[kMaxBins / NT];
 #pragma unroll
-  for (int k = 0; k < kMaxBins / NT; ++k) {
-    const int bin = tid + k * NT;
-    const int bc = min(bin, bins - 1);
-    uint32_t total;
-    if (tot != nullptr) {
-      total = tot[bc];
-      before[k] = cnt[(size_t)blk * bins + bc];
-    } else {
-      // column sums over the blocks' histograms, kFoldRows rows in flight
-      uint32_t bsum = 0, tsum = 0;
-      for (int b0 = 0; b0 < nblk; b0 += kFoldRows) {
-        uint32_t v[kFoldRows];
-#pragma unroll
-        for (int j = 0; j < kFoldRows; ++j) v[j] = cnt[(size_t)min(b0 + j, nblk - 1) * bins + bc];
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int j = 0; j < kFoldRows; ++j) {
-          const uint32_t x = (b0 + j < nblk) ? v[j] : 0u;
-          tsum += x;
-          bsum += (b0 + j < blk) ? x : 0u;
-        }
-      }
-      total = tsum;
-      before[k] = bsum;
+    for (int k = 0; k < kMaxBins / NT; ++k) {
+      const int bc = min(tid + k * NT, bins - 1);
+      total[k] = tot[bc];
+      earlier[k] = cnt[(size_t)blk * bins + bc];
     }
-    if (bin < bins) L.tot[bin] = total;
+#pragma unroll
+    for (int k = 0; k < kMaxBins / NT; ++k) {
+      const int bin = tid + k * NT;
+      if (bin < bins) {
+        L.tot[bin] = total[k];
+        L.before[bin] = earlier[k];
+      }
+    }
+  } else {
+    const int words = sort_row_words(bins);
+    ColumnSums<NT == 256 ? 32 : 16> sums;
+    sums.load((const uint16_t*)cnt, words * 8, words, nblk, blk);
+    for (int i = tid; i < words * 8; i += NT) L.tot[i] = L.before[i] = 0u;
+    __syncthreads();
+    sums.add_to(L.tot, L.before);
   }
   __builtin_amdgcn_sched_barrier(0);  // keep the loads together: their latencies overlap
 #pragma unroll
@@ -216,16 +271,12 @@ __device__ void stable_scatter_block(ScatterLds<NT>& L, int blk, int n_items, in
     if (wbase + step * kWave + lane >= n_items) digits[step] = -1;
   __syncthreads();
   block_exclusive_scan(L.tot, bins, L.ldsw);
-#pragma unroll
-  for (int k = 0; k < kMaxBins / NT; ++k) {
-    const int bin = tid + k * NT;
-    if (bin < bins) L.tot[bin] += before[k];
-  }
+  for (int bin = tid; bin < bins; bin += NT) L.before[bin] += L.tot[bin];
   uint32_t rank[kSteps];
   block_ranks<NT>(&L.wh[0][0], max((bins / 2 + 3) & ~3, 4), digits, rank);
 #pragma unroll
   for (int step = 0; step < kSteps; ++step)
-    if (digits[step] >= 0) ops.emit(L.tot[digits[step]] + rank[step], items[step]);
+    if (digits[step] >= 0) ops.emit(L.before[digits[step]] + rank[step], items[step]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -261,7 +312,7 @@ struct KeysInPlace {};  // source of the passes behind the first
 template <int NT, class SRC>
 __global__ __launch_bounds__(NT) void k_sort_hist(
     SRC src, uint32_t* keys_io, int B, uint32_t N, int shift,
-    int bits, uint32_t* __restrict__ cnt, uint32_t* zero, int zero_n, Counters* ctr) {
+    int bits, bool folds, uint32_t* __restrict__ cnt, uint32_t* zero, int zero_n, Counters* ctr) {
   constexpr bool FROM_IDS = !std::is_same_v<SRC, KeysInPlace>;
   __shared__ uint32_t h[kMaxBins];
   const int tid = threadIdx.x, bins = 1 << bits;
@@ -291,7 +342,8 @@ __global__ __launch_bounds__(NT) void k_sort_hist(
       ctr->small = 0;
     }
   }
-  for (int i = tid; i < bins; i += NT) h[i] = 0u;
+  const int padded = sort_row_words(bins) * 8;
+  for (int i = tid; i < padded; i += NT) h[i] = 0u;
   __syncthreads();
 #pragma unroll
   for (int step = 0; step < kSteps; ++step) {
@@ -304,7 +356,12 @@ __global__ __launch_bounds__(NT) void k_sort_hist(
       atomicAdd(&h[digit], (uint32_t)__popcll(peers));
   }
   __syncthreads();
-  for (int i = tid; i < bins; i += NT) cnt[(size_t)blockIdx.x * bins + i] = h[i];
+  if (folds) {  // a row of 16-bit counts (a block has at most 4096 items)
+    uint32_t* row = cnt + (size_t)blockIdx.x * (padded / 2);
+    for (int i = tid; i < padded / 2; i += NT) row[i] = h[2 * i] | (h[2 * i + 1] << 16);
+  } else {
+    for (int i = tid; i < bins; i += NT) cnt[(size_t)blockIdx.x * bins + i] = h[i];
+  }
 }
 
 template <int NT, bool FROM_IDS>
@@ -313,7 +370,7 @@ __global__ __launch_bounds__(NT) void k_sort_scatter(SortOps<FROM_IDS> ops, int 
                                                                const uint32_t* __restrict__ cnt,
                                                                const uint32_t* __restrict__ tot) {
   __shared__ ScatterLds<NT> L;
-  stable_scatter_block(L, (int)blockIdx.x, B, 1 << bits, cnt, tot, ops);
+  stable_scatter_block(L, (int)blockIdx.x, (int)gridDim.x, B, 1 << bits, cnt, tot, ops);
 }
 
 // Turns the blocks' bucket counts cnt[b][bin] into counts of earlier blocks (exclusive scan down
@@ -597,12 +654,8 @@ constexpr size_t group_lds(int threads, int bins) {
 // into chunks of `chunk` items (a power of two): chunk_desc[c] = {bucket, 0, item count, 0} for all chunks
 // c in bucket order, chunk_starts[bucket] the first chunk of each bucket (bins+1 entries), *n_chunks the
 // number of chunks; the item that is the t-th of chunk c goes to emit(c, t, item).
-// The blocks add up the columns of `rows` themselves.  Eight buckets are one 16-byte load, so a row takes
-// few threads, and the threads are dealt over the rows too: all rows are under way at once, where one
-// thread per bucket made a chain of the rows.  No more threads than that takes: their sums meet in LDS, and
-// every further one is another atomic on the same words (200,000 ids, 1024 threads: 176 us a step with all
-// of them, 172 without).  k_group, 100,000 uniform items of n3 = 56: 17 -> 7.4 us, 200,000 Zipf ids of
-// n3 = 136 14.8 -> 8, 500,000 of n3 = 480 25.7 -> 15.5.
+// The blocks add up the columns of `rows` themselves (ColumnSums): k_group, 100,000 uniform items of n3 = 56
+// 17 -> 7.4 us, 200,000 Zipf ids of n3 = 136 14.8 -> 8, 500,000 of n3 = 480 25.7 -> 15.5.
 template <int NT, class ItemOps>
 __device__ void group_block(int blk, int nblk, int first, int count, int bins,
                             const uint16_t* __restrict__ rows, int stride, ItemOps ops, int chunk,
@@ -626,32 +679,8 @@ __device__ void group_block(int blk, int nblk, int first, int count, int bins,
     const int i = wbase + step * kWave + lane;
     items[step] = ops.load(max(first + min(i, count - 1), 0));
   }
-  constexpr int kRows = 8;  // rows a thread has in flight
-  const int groups = min(NT / words, (nblk + kRows - 1) / kRows), g = tid / words, at = tid - g * words;
-  uint32_t t8[8] = {}, b8[8] = {};
-  if (g < groups) {
-    const uint4* col = (const uint4*)rows + at;
-    const int stride4 = stride / 8;
-    for (int r0 = g; r0 < nblk; r0 += groups * kRows) {
-      uint4 v[kRows];
-#pragma unroll
-      for (int k = 0; k < kRows; ++k) v[k] = col[(size_t)min(r0 + k * groups, nblk - 1) * stride4];
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int k = 0; k < kRows; ++k) {
-        const int r = r0 + k * groups;
-        const uint32_t all = r < nblk ? 0xffffffffu : 0u, old = r < blk ? 0xffffffffu : 0u;
-        const uint32_t x[4] = {v[k].x & all, v[k].y & all, v[k].z & all, v[k].w & all};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          t8[2 * j] += x[j] & 0xffffu;
-          t8[2 * j + 1] += x[j] >> 16;
-          b8[2 * j] += x[j] & old & 0xffffu;
-          b8[2 * j + 1] += (x[j] & old) >> 16;
-        }
-      }
-    }
-  }
+  ColumnSums<8> sums;
+  sums.load(rows, stride, words, nblk, blk);
   for (int i = tid; i < words * 16; i += NT) tot[i] = 0u;  // tot and before
 #pragma unroll
   for (int step = 0; step < kSteps; ++step) digits[step] = ops.digit(items[step]);
@@ -660,13 +689,7 @@ __device__ void group_block(int blk, int nblk, int first, int count, int bins,
   for (int step = 0; step < kSteps; ++step)
     if (step >= per || wbase + step * kWave + lane >= count) digits[step] = -1;
   __syncthreads();
-  if (g < groups) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      if (t8[j] != 0) atomicAdd(&tot[at * 8 + j], t8[j]);
-      if (b8[j] != 0) atomicAdd(&before[at * 8 + j], b8[j]);
-    }
-  }
+  sums.add_to(tot, before);
   __syncthreads();
   for (int bin = tid; bin < bins; bin += NT) aux[bin] = (tot[bin] + chunk - 1) >> chunk_sh;
   __syncthreads();
@@ -750,6 +773,13 @@ __global__ __launch_bounds__(kOrderBands) void k_chunk_order(const int2* __restr
 
 static inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
+// Whether the scatter blocks add up the histograms' columns themselves, or a column-scan launch does it: every
+// block reads all rows, so the line lies at a number of 16-byte words of them.  Training steps, the launch
+// against the sums: 49 blocks of 64 words 87.4 / 84.1 us, 98 of 128 104.4 / 103.7, beside another batch's
+// arithmetic 49 of 256 121.1 / 122.8, 98 of 256 163.4 / 168.6 (and 245 of 64 even).
+constexpr int kFoldWords = 8192;
+static bool sort_folds(int blocks, int bins) { return (int64_t)blocks * sort_row_words(bins) <= kFoldWords; }
+
 // One of the three kernels of a pass.  clear: the first one also clears the tables that the steps
 // behind the sort add into (lookups have none).
 template <int NT>
@@ -758,20 +788,22 @@ static void sort_pass(const Plan& pl, const Workspace& ws, const SortKeys& sk, c
   const int blocks = cdiv(B, sort_items(NT));
   const int shift = sk.low + pass * sk.per;
   const int bits = std::min(sk.per, sk.bits - pass * sk.per);
-  const uint32_t* tot = sort_folds(B, beside) ? nullptr : ws.tot;
+  const bool folds = sort_folds(blocks, 1 << bits);
+  const uint32_t* tot = folds ? nullptr : ws.tot;
   const int in = (pass + 1) & 1;
   uint32_t *kin = ws.key[in], *vin = ws.val[in], *kout = ws.key[in ^ 1], *vout = ws.val[in ^ 1];
   if (which == 2) {
+    if (folds) return;
     k_sort_colscan<<<cdiv(1 << bits, kScanBins), kScanThreads, 0, st>>>(ws.cnt, ws.tot, blocks,
                                                                        1 << bits);
   } else if (which == 0) {
     auto first = [&](auto from) {
       k_sort_hist<NT><<<blocks, NT, 0, st>>>(
-          from, kin, B, sk.sentinel, shift, bits, ws.cnt, (uint32_t*)ws.g1_first,
+          from, kin, B, sk.sentinel, shift, bits, folds, ws.cnt, (uint32_t*)ws.g1_first,
           clear ? 2 * (int)pl.sh.n1 + 2 * kOrderBands : 0, ws.ctr);
     };
     if (pass > 0)
-      k_sort_hist<NT><<<blocks, NT, 0, st>>>(KeysInPlace{}, kin, B, sk.sentinel, shift, bits, ws.cnt, nullptr, 0,
+      k_sort_hist<NT><<<blocks, NT, 0, st>>>(KeysInPlace{}, kin, B, sk.sentinel, shift, bits, folds, ws.cnt, nullptr, 0,
                                              ws.ctr);
     else if (sk.low > 0)  // by prefix
       first(PrefixSource{src, sk.low, pl.user_n1, pl.sh.n2, pl.sh.n3});

@@ -16,7 +16,6 @@ constexpr int kWave = 64;
 // Stable counting-sort blocks: every wavefront owns 256 consecutive items of its block's run.
 constexpr int kSortWaveItems = 256;
 __host__ __device__ constexpr int sort_items(int threads) { return threads / kWave * kSortWaveItems; }
-constexpr int kFoldRows = 16;       // histogram rows a thread keeps in flight while it adds up a column
 constexpr int kChunk3 = 16;       // record slots per partial sum (chunk) of a G3 slice gradient
 // Batches of up to kSmallBatch rows are cut finer where that puts more wavefronts in flight: by-i3
 // chunks of 8 ids instead of 16 (-3.7 us per step at 200,000 rows, +6..18 us at 500,000).
@@ -35,11 +34,6 @@ inline int chunk3_fill(int64_t B) { return B <= kSmallBatch ? kChunk3Min : kChun
 constexpr int kSort1024First = 1 << 10, kSort256Most = 1 << 17, kSort512Most = 1 << 19;
 inline int sort_threads(int64_t B, bool beside) {
   return beside || B <= kSort1024First || B > kSort512Most ? 1024 : B > kSort256Most ? 512 : 256;
-}
-// Up to sixteen blocks need no column-scan launch: each adds up the rows itself.
-constexpr int kFoldScanBlocks = 16;
-inline bool sort_folds(int64_t B, bool beside) {
-  return B <= (int64_t)kFoldScanBlocks * sort_items(sort_threads(B, beside));
 }
 inline int64_t sort_blocks(int64_t B) {
   const int i = sort_items(sort_threads(B, false));

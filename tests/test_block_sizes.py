@@ -32,7 +32,7 @@ def test_sort_block_sizes(B):
 @pytest.mark.parametrize("B", [5, 255, 1023, 1024, 1025, 4096, 4097, 8192, 8193, 16_384, 16_385])
 def test_small_batches_with_indices(B):
     """Flag 2 keeps small batches on the index structures: histograms beside the chunk records and in
-    their memory, the largest batch sorted without a column scan and the one above it."""
+    their memory."""
     _check((40, 30, 50), (2, 2, 2), (4, 4), B, flags=2)
 
 

@@ -14,3 +14,11 @@ pytestmark = pytest.mark.gpu
                                  ((20, 130, 600), 223_233), ((9, 600, 593), 425_985), ((3, 1100, 1200), 30_001)])
 def test_slot_blocks(n, B):
     _check(n, (2, 2, 2), (4, 4), B, flags=8)
+
+
+@pytest.mark.parametrize("n,B", [((100, 100, 50), 65_536), ((100, 100, 50), 65_537), ((9, 600, 593), 32_768),
+                                 ((9, 600, 593), 32_769), ((60, 60, 60), 262_144), ((60, 60, 60), 262_145)])
+def test_sorts_with_and_without_a_column_scan(n, B):
+    """As many rows of counts as the scatter adds up itself, and one more: digits of 1024 and 2048 values in blocks
+    of 1024 ids, of 512 values in blocks of 2048."""
+    _check(n, (2, 2, 2), (4, 4), B, flags=8)
