@@ -18,7 +18,7 @@ void launch_sort_pass(const Plan&, const Workspace&, const SortKeys&, const IdSo
                       bool beside, bool clear, hipStream_t, int which);
 void launch_seg_count(const Plan&, const Workspace&, int B, hipStream_t);
 void launch_seg_write(const Plan&, const Workspace&, int B, hipStream_t);
-void launch_group(const Plan&, const Workspace&, int B, hipStream_t, int which);
+void launch_group(const Plan&, const Workspace&, int B, hipStream_t, bool prefixes_only);
 void launch_prefix_fwd(const Plan&, const Workspace&, const float* g1, const float* g2, int B,
                        hipStream_t);
 void launch_row_fwd(const Plan&, const Workspace&, const float* g3, int B, float* out, hipStream_t);
@@ -212,7 +212,6 @@ static size_t carve(const Plan& pl, char* base, Workspace* ws /* [kSets] or null
   Workspace set[kSets];
   for (int i = 0; i < sets; ++i) {
     Workspace& w = set[i];
-    w.has_order = false;
     w.ctr = (Counters*)take(sizeof(Counters));
     for (int k = 0; k < 2; ++k) w.key[k] = (uint32_t*)take(mB * 4);
     for (int k = 0; k < 2; ++k) w.val[k] = (uint32_t*)take(mB * 4);
@@ -238,23 +237,21 @@ static size_t carve(const Plan& pl, char* base, Workspace* ws /* [kSets] or null
                  coarse_q = (size_t)cdiv64(pl.maxQ, sort_items(1024));
     char* counts = take(al(coarse_u * kMaxBins * 4) + al(coarse_u * s.n3 * 4) + al(coarse_q * s.n2 * 4));
     w.seg_rows = (uint16_t*)counts;
-    w.seg_base = (int4*)take(mB * 4);
-    take(((size_t)s.n3 + 1) * 4);
+    w.seg_base = (int4*)take(mB * 4);  // 16 bytes per 1024 rows or more
     w.c3_start = (int*)take(((size_t)s.n3 + 1) * 4);
     w.c3_desc = (int4*)take((size_t)pl.maxChunk3 * 16);
     w.c3_item = (int2*)take((size_t)pl.maxChunk3 * kChunk3 * 8);
     w.cnt = (uint32_t*)(shared ? (char*)w.c3_item : counts);
-    w.c3_order = (int*)take((size_t)pl.maxChunk3 * 4);
-    take(mQ * 4);
-    take(((size_t)s.n2 + 1) * 4);
     w.c2_start = (int*)take(((size_t)s.n2 + 1) * 4);
     w.c2_desc = (int4*)take((size_t)pl.maxChunk2 * 16);
     w.c2_item = (int4*)take((size_t)pl.maxChunk2 * kChunk2 * 16);
-    // g1_first[n1], g1_end[n1], band_cnt, band_cur: one stretch, cleared by the first sort pass
-    w.g1_first = (int*)take((size_t)s.n1 * 8 + 2 * kOrderBands * 4);
+    // g1_first[n1], g1_end[n1]: one stretch, cleared by the first sort pass
+    w.g1_first = (int*)take((size_t)s.n1 * 8);
     w.g1_end = w.g1_first + s.n1;
-    w.band_cnt = (uint32_t*)(w.g1_end + s.n1);
-    w.band_cur = w.band_cnt + kOrderBands;
+    // The largest batch that tt_emb_lookup_static takes follows from this size and is what it was when there were
+    // lists of ids and prefixes and an order of the chunks here.
+    off += al(((size_t)s.n3 + 1) * 4) + al(((size_t)s.n2 + 1) * 4) + al(mQ * 4) + al((size_t)pl.maxChunk3 * 4) +
+           al((size_t)s.n1 * 8 + 8192) - al((size_t)s.n1 * 8);
   }
   Workspace& w = set[0];
   const size_t arithmetic = off;
@@ -555,9 +552,8 @@ static int run_sort(tt_emb* h, const Workspace& ws, const SortKeys& sk, const Id
 }
 
 // Index pipeline of one batch into index set `set`, on stream st.
-// how: 0 = beside other work, as in tt_emb_prepare: everything, including the prefix-ordered schedule
-// of the by-i3 chunks (worth its launch only there), with large sort blocks; 1 = no schedule; 2 = a
-// lookup: the structures that only the backward pass reads (unique ids by i3) are not built either.
+// how: 0 = beside other work, as in tt_emb_prepare, with large sort blocks; 1 = on the caller's stream; 2 = a
+// lookup there: the structures that only the backward pass reads (unique ids by i3) are not built.
 static int run_index(tt_emb* h, int set, const IdSource& src, int B, hipStream_t st, int how) {
   const Plan& pl = h->plan;
   const Workspace& ws = h->ws[set];
@@ -567,8 +563,7 @@ static int run_index(tt_emb* h, int set, const IdSource& src, int B, hipStream_t
   if (rc) return rc;
   rc = run_slot(h, kSlotSegWrite, st, [&] { launch_seg_write(pl, ws, B, st); });
   if (rc) return rc;
-  h->ws[set].has_order = how == 0;
-  return run_slot(h, kSlotGroup, st, [&] { launch_group(pl, ws, B, st, how); });
+  return run_slot(h, kSlotGroup, st, [&] { launch_group(pl, ws, B, st, how == 2); });
 }
 
 // Lookup of ids sorted by prefix: no index structures behind the sort, no products in memory.

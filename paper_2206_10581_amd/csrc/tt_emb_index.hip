@@ -16,13 +16,6 @@
 
 namespace ttemb {
 
-// band of the prefix range [0, Q) that prefix q falls in (single precision: bands only order a
-// schedule, and both users call this one function)
-__device__ __forceinline__ int chunk_band(int q, int Q) {
-  const float b = (float)max(q, 0) * ((float)kOrderBands / (float)max(Q, 1));
-  return min((int)b, kOrderBands - 1);
-}
-
 // ---------------------------------------------------------------------------------------------
 // block-wide helpers; ldsw holds at least one word per wavefront of the block
 
@@ -614,14 +607,10 @@ struct GroupOps3 {
   const int* u_code;
   const int* u_q;
   int2* item;
-  uint32_t* band_cnt;
-  int Q;
   __device__ Item load(int idx) const { return Item{u_i3[idx], u_code[idx], u_q[idx]}; }
   __device__ int digit(Item it) const { return it.i3; }
   __device__ void emit(uint32_t chunk, uint32_t t, Item it) const {
     item[(size_t)chunk * kChunk3 + t] = make_int2(it.code, it.q);
-    // a chunk counts where it starts (only when a schedule will be built from the counts)
-    if (band_cnt != nullptr && t == 0) atomicAdd(&band_cnt[chunk_band(it.q, Q)], 1u);
   }
 };
 
@@ -659,9 +648,9 @@ constexpr size_t group_lds(int threads, int bins) {
 template <int NT, class ItemOps>
 __device__ void group_block(int blk, int nblk, int first, int count, int bins,
                             const uint16_t* __restrict__ rows, int stride, ItemOps ops, int chunk,
-                            int* chunk_starts, int4* chunk_desc, int* n_chunks) {
+                            int* chunk_starts, int4* chunk_desc, int* n_chunks, int* most) {
   extern __shared__ __attribute__((aligned(16))) uint32_t group_words[];
-  __shared__ uint32_t ldsw[NT / kWave];
+  __shared__ uint32_t ldsw[NT / kWave], most_chunks;
   const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
   const int words = (bins + 7) / 8, row_words = group_row_words(bins);
   uint32_t* wh = group_words;
@@ -690,8 +679,14 @@ __device__ void group_block(int blk, int nblk, int first, int count, int bins,
     if (step >= per || wbase + step * kWave + lane >= count) digits[step] = -1;
   __syncthreads();
   sums.add_to(tot, before);
+  if (tid == 0) most_chunks = 0u;
   __syncthreads();
-  for (int bin = tid; bin < bins; bin += NT) aux[bin] = (tot[bin] + chunk - 1) >> chunk_sh;
+  uint32_t my_most = 0;
+  for (int bin = tid; bin < bins; bin += NT) {
+    aux[bin] = (tot[bin] + chunk - 1) >> chunk_sh;
+    my_most = max(my_most, aux[bin]);
+  }
+  if (blk == 0 && my_most > 0) atomicMax(&most_chunks, my_most);
   __syncthreads();
   const uint32_t total_chunks = block_exclusive_scan(aux, bins, ldsw);
   if (blk == 0) {
@@ -699,6 +694,7 @@ __device__ void group_block(int blk, int nblk, int first, int count, int bins,
     if (tid == 0) {
       chunk_starts[bins] = (int)total_chunks;
       *n_chunks = (int)total_chunks;
+      if (most != nullptr) *most = (int)most_chunks;
     }
   }
   // every block takes a share of the chunk descriptors
@@ -729,42 +725,18 @@ __global__ __launch_bounds__(NT) void k_group(
     const uint16_t* __restrict__ rows, const int* __restrict__ u_i3, const int* __restrict__ u_code,
     const int* __restrict__ u_q, const int* __restrict__ q_i2, const int* __restrict__ q_i1,
     const int* __restrict__ q_us, int* c3_start, int4* c3_desc, int2* c3_item, int* c2_start, int4* c2_desc,
-    int4* c2_item, uint32_t* band_cnt, Counters* ctr) {
+    int4* c2_item, Counters* ctr) {
   const bool ids = (int)blockIdx.x < ub;
   const int blk = ids ? blockIdx.x : blockIdx.x - ub;
   const int4 base = seg_base[blk];
   if (ids) {
-    GroupOps3 ops{u_i3, u_code, u_q, c3_item, band_cnt, ctr->Q};
+    GroupOps3 ops{u_i3, u_code, u_q, c3_item};
     group_block<NT>(blk, nblk, base.x, base.z, (int)sh.n3, rows, p3 + p2, ops, chunk3, c3_start, c3_desc,
-                    &ctr->nchunk3);
+                    &ctr->nchunk3, &ctr->most3);
   } else {
     GroupOps2 ops{q_i2, q_i1, q_us, c2_item};
     group_block<NT>(blk, nblk, base.y, base.w, (int)sh.n2, rows + p3, p3 + p2, ops, kChunk2, c2_start, c2_desc,
-                    &ctr->nchunk2);
-  }
-}
-
-// The by-i3 chunks in the order of the prefix of their first id, bucketed into kOrderBands bands of
-// the prefix range (the order inside a band is whatever the atomics give).  The G3-gradient step
-// gathers one prefix product per id: walking the chunks in this order makes neighbouring
-// wavefronts gather neighbouring products.  Only the schedule depends on it, never a result.
-// The grouping kernel has counted the chunks per band; every block scans those counts for itself.
-__global__ __launch_bounds__(kOrderBands) void k_chunk_order(const int2* __restrict__ c3_item,
-                                                             const uint32_t* __restrict__ band_cnt,
-                                                             uint32_t* __restrict__ band_cur,
-                                                             int* __restrict__ c3_order,
-                                                             const Counters* __restrict__ ctr) {
-  __shared__ uint32_t band_at[kOrderBands];
-  __shared__ uint32_t ldsw[kOrderBands / kWave];
-  const int tid = threadIdx.x, n = ctr->nchunk3, c = blockIdx.x * kOrderBands + tid;
-  if ((int)blockIdx.x * kOrderBands >= n) return;
-  const int q = c < n ? c3_item[(size_t)c * kChunk3].y : 0;
-  band_at[tid] = band_cnt[tid];
-  __syncthreads();
-  block_exclusive_scan(band_at, kOrderBands, ldsw);
-  if (c < n) {
-    const int b = chunk_band(q, ctr->Q);
-    c3_order[band_at[b] + atomicAdd(&band_cur[b], 1u)] = c;
+                    &ctr->nchunk2, nullptr);
   }
 }
 
@@ -800,7 +772,7 @@ static void sort_pass(const Plan& pl, const Workspace& ws, const SortKeys& sk, c
     auto first = [&](auto from) {
       k_sort_hist<NT><<<blocks, NT, 0, st>>>(
           from, kin, B, sk.sentinel, shift, bits, folds, ws.cnt, (uint32_t*)ws.g1_first,
-          clear ? 2 * (int)pl.sh.n1 + 2 * kOrderBands : 0, ws.ctr);
+          clear ? 2 * (int)pl.sh.n1 : 0, ws.ctr);
     };
     if (pass > 0)
       k_sort_hist<NT><<<blocks, NT, 0, st>>>(KeysInPlace{}, kin, B, sk.sentinel, shift, bits, folds, ws.cnt, nullptr, 0,
@@ -853,28 +825,21 @@ void launch_seg_write(const Plan& pl, const Workspace& ws, int B, hipStream_t st
   });
 }
 
-// which: 0 = both groupings and the chunk schedule; 1 = both groupings, no schedule (c3_order is
-// not written: the gradient kernel then walks the by-i3 chunks in index order); 2 = prefixes by i2
-// only (all a lookup needs)
-void launch_group(const Plan& pl, const Workspace& ws, int B, hipStream_t st, int which) {
-  const int span = slot_span(pl.sh, B), nblk = cdiv(B, span), ub = which == 2 ? 0 : nblk;
+// prefixes_only: prefixes by i2, all a lookup needs, and not the unique ids by i3
+void launch_group(const Plan& pl, const Workspace& ws, int B, hipStream_t st, bool prefixes_only) {
+  const int span = slot_span(pl.sh, B), nblk = cdiv(B, span), ub = prefixes_only ? 0 : nblk;
   const int p3 = up8(pl.sh.n3), p2 = up8(pl.sh.n2);
-  const bool ordered = which == 0 && chunks_ordered(pl, B);
   auto launch = [&](auto kernel, int threads) {
     kernel<<<ub + nblk, threads, group_lds(threads, std::max(p3, p2)), st>>>(
         pl.sh, ub, nblk, chunk3_fill(B), p3, p2, ws.seg_base, ws.seg_rows, ws.u_i3, ws.u_code, ws.u_q, ws.q_i2,
         ws.q_i1, ws.q_us, ws.c3_start, ws.c3_desc, ws.c3_item, ws.c2_start, ws.c2_desc, ws.c2_item,
-        ordered ? ws.band_cnt : nullptr, ws.ctr);
+        ws.ctr);
   };
   switch (span) {
     case 1024: launch(k_group<256>, 256); break;
     case 2048: launch(k_group<512>, 512); break;
     default: launch(k_group<1024>, 1024);
   }
-  if (ordered)
-    k_chunk_order<<<cdiv(cdiv(B, chunk3_fill(B)) + (int64_t)pl.sh.n3, kOrderBands), kOrderBands, 0,
-                    st>>>(
-      ws.c3_item, ws.band_cnt, ws.band_cur, ws.c3_order, ws.ctr);
 }
 
 }  // namespace ttemb

@@ -59,7 +59,6 @@ constexpr int kEntrySlots = 1024;
 
 constexpr int kTileSlots = 32;   // sorted slots per wavefront tile in the row kernels
 constexpr int kChunk2 = 16;      // unique prefixes per partial sum of a G2 slice gradient
-constexpr int kOrderBands = 1024;  // bands of the prefix range the by-i3 chunks are ordered by
 
 // Where the ids of a batch come from, passed to the first sort pass by value.
 struct IdSource {
@@ -141,6 +140,7 @@ struct Counters {
   int nchunk2;  // partial-sum chunks over the by-i2 grouping of unique prefixes
   int err;      // nonzero: a kernel met an impossible index (bit mask of sites)
   int n_split;  // entries beyond the first of their id (U - n_split distinct ids)
+  int most3;    // chunks of the i3 with the most ids
   int small;    // ranks 64 and 128: an operand of the prefix kernels is below 2^-102 and not zero
 };
 
@@ -198,15 +198,11 @@ struct Workspace {
   int* c3_start;      // first chunk of each i3 group [n3+1]
   int4* c3_desc;      // chunk -> {i3, 0, items, 0}  [maxChunk3]
   int2* c3_item;      // chunk, t -> {gradient-row code, prefix} of its t-th id [maxChunk3][kChunk3]
-  int* c3_order;      // by-i3 chunks in the order of the prefix of their first id [maxChunk3]
-  bool has_order;     // host side: the batch in this set has had c3_order written
   int* c2_start;      // [n2+1]
   int4* c2_desc;      // chunk -> {i2, 0, items, 0}  [maxChunk2]
   int4* c2_item;      // chunk, t -> {q, i1, first unique id, end} of its t-th prefix [maxChunk2][kChunk2]
   int* g1_first;      // i1 -> first prefix with that i1 (prefixes are sorted by i1) [n1]
   int* g1_end;        // i1 -> one past its last prefix; directly follows g1_first  [n1]
-  uint32_t* band_cnt;  // by-i3 chunks per band of their first prefix; directly follows g1_end
-  uint32_t* band_cur;  // chunks placed so far per band; directly follows band_cnt [kOrderBands]
   float* P;           // prefix products G1[i1] G2[i2]   [maxQ][PN]
   float* gsum;        // per unique id, sum of its rows' gradients [maxB][D]
   float* carry;       // per tile: head and tail partial sums [tiles][2][D]
@@ -254,13 +250,6 @@ __host__ __device__ inline int wide_group(int nchunk2, int r) {
   int g = 1;
   while (g < kWideGroup && nchunk2 * (r / 32) >= 4096 * g) g *= 2;
   return g;
-}
-
-// The by-i3 chunks are put in prefix order only when the prefix products of a batch of B ids can
-// exceed one XCD's L2 (4 MiB); below that the gathers hit the L2 in any order.
-inline bool chunks_ordered(const Plan& pl, int64_t B) {
-  const int64_t q = B < pl.maxQ ? B : pl.maxQ;
-  return q * pl.sh.PN * 4 > (int64_t)4 << 20;
 }
 
 enum KernelSlot {

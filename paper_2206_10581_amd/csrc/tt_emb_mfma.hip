@@ -793,7 +793,30 @@ __global__ __launch_bounds__(kMThreads) void k_id_bwd_mfma(
 // of (480,480,482), eight / four wavefronts: 268 / 243 us at 500,000 ids and d = (4,4,8), 170 / 137 at 300,000
 // and (4,4,4); with 37 ids a prefix, n = (40,40,500), 27 / 33).  The line is one for all ids: at 13 items a
 // prefix, 250,000 ids of 136^3 with d = (8,4,4), rank 16, clustered ones take 93 / 110, Zipf ones 52 / 49.
+// Blocks past the by-i2 chunk range take the by-i3 chunks of the G3 gradient, one per wavefront, which gather a
+// prefix product per id.  A group's chunks are in prefix order: workgroups go to the eight XCDs round robin, and
+// XCD x takes the x-th eighth of every group and walks the eighths of all groups side by side, so that the
+// products it gathers at one time are few, and its own.  Against an eighth of all chunks in index order, training
+// steps: 200,000 Zipf ids of 136^3 at rank 32 172 -> 169 us, look-ahead 137.2 -> 135.7 (where a list of the chunks
+// by prefix, 4 to 6 us of the index pipeline, took 138), 500,000 of 480x480x482 at rank 16 376.1 -> 375.6, 50,000
+// uniform ids of (55,55,56) x (8,4,4) 101.7 -> 102.1.  Groups of very different sizes are walked in index order.
 constexpr int kXcds = 8;
+template <class F>
+__device__ __forceinline__ void walk_chunks3(int xcd, int wave, int nwaves, int n3, const int* __restrict__ c3_start,
+                                             const Counters* __restrict__ ctr, F take) {
+  const int n = ctr->nchunk3, steps = (ctr->most3 + kXcds - 1) / kXcds;  // steps: chunks of a group's eighth
+  if ((long long)steps * kXcds * n3 <= 2ll * n) {
+    for (int i = wave; i < steps * n3; i += nwaves) {
+      const int j = (int)((uint32_t)i / (uint32_t)n3), i3 = i - j * n3;
+      const int s = c3_start[i3], cnt = c3_start[i3 + 1] - s;
+      const int c = s + cnt * xcd / kXcds + j;
+      if (c < s + cnt * (xcd + 1) / kXcds) take(c);
+    }
+  } else {
+    const int lo = (int)((long long)n * xcd / kXcds), hi = (int)((long long)n * (xcd + 1) / kXcds);
+    for (int c = lo + wave; c < hi; c += nwaves) take(c);
+  }
+}
 
 template <int R, int D3, int WAVES>
 __global__ __launch_bounds__(WAVES * kWave, 6) void k_bwd_mid_mfma(
@@ -801,7 +824,7 @@ __global__ __launch_bounds__(WAVES * kWave, 6) void k_bwd_mid_mfma(
     const float* __restrict__ P, const float* __restrict__ grad, const float* __restrict__ gsum,
     const int* __restrict__ u_code, const int* __restrict__ u_i3, const int4* __restrict__ c2_item,
     const int4* __restrict__ c2_desc, const int2* __restrict__ c3_item,
-    const int4* __restrict__ c3_desc, const int* __restrict__ c3_order,
+    const int4* __restrict__ c3_desc, const int* __restrict__ c3_start, int n3,
     float* __restrict__ dg1part, float* __restrict__ part2, float* __restrict__ part3,
     int chunk_blocks, const Counters* __restrict__ ctr) {
   static_assert(R == 8 || R == 16 || R == 32, "the LDS tiles are sized for ranks up to 32");
@@ -813,17 +836,10 @@ __global__ __launch_bounds__(WAVES * kWave, 6) void k_bwd_mid_mfma(
   __shared__ __align__(16) float T[64 * TS];
   __shared__ __align__(16) float Bl[R * TS > kParts ? R * TS : kParts];  // wavefronts' sums of a long prefix, then Bm
   const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
-  // Blocks past the by-i2 chunk range take the by-i3 chunks, one per wavefront, in the order of
-  // the chunks' first prefixes.  Workgroups go to the eight XCDs round robin, so XCD x takes the
-  // x-th eighth of that order and walks it front to back: the prefix products a chunk gathers
-  // were then just read by its neighbours through the same L2.
   if ((int)blockIdx.x >= chunk_blocks) {
-    const int rel = (int)blockIdx.x - chunk_blocks, xcd = (int)blockIdx.x % kXcds;
-    const int per_xcd = ((int)gridDim.x - chunk_blocks) / kXcds * WAVES;
-    const int n = ctr->nchunk3;
-    const int lo = (int)((long long)n * xcd / kXcds), hi = (int)((long long)n * (xcd + 1) / kXcds);
-    for (int i = lo + rel / kXcds * WAVES + w; i < hi; i += per_xcd)
-      dg3_chunk<R, D3, 4>(c3_order ? c3_order[i] : i, P, grad, gsum, c3_item, c3_desc, part3);
+    const int rel = (int)blockIdx.x - chunk_blocks;
+    walk_chunks3((int)blockIdx.x % kXcds, rel / kXcds * WAVES + w, ((int)gridDim.x - chunk_blocks) / kXcds * WAVES, n3,
+                 c3_start, ctr, [&](int c) { dg3_chunk<R, D3, 4>(c, P, grad, gsum, c3_item, c3_desc, part3); });
     return;
   }
   // records, descriptor and chunk count are read together (the grid never exceeds the tables)
@@ -1541,14 +1557,13 @@ void launch_bwd_mid_mfma(const Plan& pl, const Workspace& ws, const float* g1, c
   // fewer than four ids per prefix of the table: blocks of four wavefronts (figures at the kernel)
   const bool narrow = pl.sh.r1 <= 16 && B < 4 * (int64_t)pl.sh.n1 * pl.sh.n2;
   const int waves = narrow ? 4 : 8;
-  const int* order = (ws.has_order && chunks_ordered(pl, B)) ? ws.c3_order : nullptr;
   // the same number of by-i3 blocks on every XCD
   const int dg3_blocks =
       kXcds * cdivi(cdivi(cdivi(B, chunk3_fill(B)) + (int64_t)pl.sh.n3, kXcds), waves);
   auto launch = [&](auto kernel) {
     kernel<<<chunk_blocks + dg3_blocks, waves * kWave, 0, st>>>(
         g1, g2, g3, ws.P, grad, ws.gsum, ws.u_code, ws.u_i3, ws.c2_item, ws.c2_desc, ws.c3_item, ws.c3_desc,
-        order, ws.dg1part, ws.part2, ws.part3, chunk_blocks, ws.ctr);
+        ws.c3_start, (int)pl.sh.n3, ws.dg1part, ws.part2, ws.part3, chunk_blocks, ws.ctr);
   };
   if (pl.sh.r1 == 8) {
     if (narrow) pl.sh.d3 == 4 ? launch(k_bwd_mid_mfma<8, 4, 4>) : launch(k_bwd_mid_mfma<8, 8, 4>);
