@@ -525,62 +525,94 @@ __global__ __launch_bounds__(kMThreads, 2) void k_prefix_bwd_wide(
 
 // ---------------------------------------------------------------------------------------------
 // dPsum_q = sum over the unique ids u of prefix q of g_u G3[i3(u)]^T  (16 x D3 times D3 x R).
-// One wavefront per prefix; the ids of a prefix extend the contraction index, UB at a time.
-template <int R, int D3>
+// One wavefront per prefix, or where prefixes have many ids a block: its wavefronts take runs of MOST ids in
+// turn, their sums meet in LDS and are added in their order.  The ids of a prefix extend the contraction index:
+// 16 / D3 of them (a group) are one step, lane group kg holds four neighbours of a row of one id, so that a load
+// instruction brings 16 bytes a lane and as many lines as it has to.
+template <int R, int D3, int MOST>
 __device__ __forceinline__ void u_bwd_role(
-    int block, int nblocks, const float* __restrict__ g3, const float* __restrict__ grad,
-    const float* __restrict__ gsum, const int* __restrict__ u_code, const int* __restrict__ u_i3,
-    const int* __restrict__ q_us, float* __restrict__ dPsum, Counters* __restrict__ ctr) {
-  constexpr int PN = 16 * R, S3 = R * D3, D = 16 * D3, NT = R / 16, KS = D3 / 4, UB = 4;
-  const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    int block, int nblocks, bool by_block, f4 (*part)[R / 16][kWave], const float* __restrict__ g3,
+    const float* __restrict__ grad, const float* __restrict__ gsum, const int* __restrict__ u_code,
+    const int* __restrict__ u_i3, const int* __restrict__ q_us, float* __restrict__ dPsum,
+    Counters* __restrict__ ctr) {
+  constexpr int PN = 16 * R, S3 = R * D3, D = 16 * D3, NT = R / 16, KS = D3 / 4, IPG = 4 / KS;
+  const int w = wave_value(threadIdx.x / kWave), lane = threadIdx.x % kWave;
   const int l16 = lane % 16, kg = lane / 16;
   const int Q = ctr->Q;
-  for (int q = block * kMWaves + w; q < Q; q += nblocks * kMWaves) {
-    const int u0 = q_us[q], u1 = q_us[q + 1];
+  const int step = by_block ? nblocks : nblocks * kMWaves, hop = by_block ? kMWaves * MOST : MOST;
+  for (int q = by_block ? block : block * kMWaves + w; q < Q; q += step) {
+    const int u0 = wave_value(q_us[q]), u1 = wave_value(q_us[q + 1]);
     f4 acc[NT];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) acc[nt] = f4{0.f, 0.f, 0.f, 0.f};
-    for (int ub = u0; ub < u1; ub += kWave) {
-      const int n = min(kWave, u1 - ub);
-      const int myi3 = u_i3[ub + min(lane, n - 1)];
-      const int mycode = u_code[ub + min(lane, n - 1)];
-      // UBX ids per round: their operand loads are in flight together
-      auto round = [&](auto ubx, int i0) {
-        constexpr int UBX = decltype(ubx)::value;
-        float a[UBX][KS], b[UBX][NT][KS];
+    const int first = u0 + (by_block ? w * MOST : 0);
+    auto id_of = [&](int ub) { return min(ub + lane % MOST, u1 - 1); };
+    int next_i3 = u_i3[id_of(first)], next_code = u_code[id_of(first)];
+    for (int ub = first; ub < u1; ub += hop) {
+      const int n = min(MOST, u1 - ub);
+      const int myi3 = next_i3, mycode = next_code;
+      next_i3 = u_i3[id_of(ub + hop)];  // on their way while this round's rows are
+      next_code = u_code[id_of(ub + hop)];
+      auto round = [&](auto groups, int i0) {
+        constexpr int NG = decltype(groups)::value;
+        f4 a[NG], b[NG][NT];
 #pragma unroll
-        for (int x = 0; x < UBX; ++x) {
-          const int i = min(i0 + x, n - 1);
-          const float* gp = grad_row_ptr(lane_value(mycode, i), grad, gsum, D) + l16 * D3 + KS * kg;
-          const float* cp = g3 + (size_t)lane_value(myi3, i) * S3 + l16 * D3 + KS * kg;
+        for (int x = 0; x < NG; ++x) {
+          const int i = min(i0 + x * IPG + kg / KS, n - 1);
+          const float* gp = grad_row_ptr(__shfl(mycode, i), grad, gsum, D) + l16 * D3 + kg % KS * 4;
+          const float* cp = g3 + (size_t)(uint32_t)__shfl(myi3, i) * S3 + l16 * D3 + kg % KS * 4;
+          a[x] = *(const f4*)gp;
 #pragma unroll
-          for (int s = 0; s < KS; ++s) a[x][s] = gp[s];
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int s = 0; s < KS; ++s) b[x][nt][s] = cp[nt * 16 * D3 + s];
+          for (int nt = 0; nt < NT; ++nt) b[x][nt] = *(const f4*)(cp + nt * 16 * D3);
         }
         TT_LOADS_DONE();
 #pragma unroll
-        for (int x = 0; x < UBX; ++x) {
-          const bool on = i0 + x < n;
+        for (int x = 0; x < NG; ++x) {
+          // lanes without an id: both factors are zero, whatever the last one holds
+          if (i0 + (x + 1) * IPG > n) {
+            const bool on = i0 + x * IPG + kg / KS < n;
 #pragma unroll
-          for (int nt = 0; nt < NT; ++nt)
+            for (int s = 0; s < 4; ++s) {
+              a[x][s] = on ? a[x][s] : 0.f;
 #pragma unroll
-            for (int s = 0; s < KS; ++s) acc[nt] = mfma16(on ? a[x][s] : 0.f, b[x][nt][s], acc[nt]);
+              for (int nt = 0; nt < NT; ++nt) b[x][nt][s] = on ? b[x][nt][s] : 0.f;
+            }
+          }
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) acc[nt] = mfma16(a[x][s], b[x][nt][s], acc[nt]);
         }
       };
-      int i0 = 0;
-      if constexpr (R <= 64)  // sixteen ids in flight: 288 registers at rank 128
-        for (; i0 + 16 <= n; i0 += 16) round(std::integral_constant<int, 16>{}, i0);
-      for (; i0 < n; i0 += UB) round(std::integral_constant<int, UB>{}, i0);
+      if (MOST > IPG && n > MOST / 2) round(std::integral_constant<int, MOST / IPG>{}, 0);
+      else
+        for (int i0 = 0; i0 < n; i0 += IPG) round(std::integral_constant<int, 1>{}, i0);
     }
-    if (__ballot(some_inexact<4 * NT>((const float*)acc)) && lane == 0) atomicOr(&ctr->small, 1);
+    if (by_block) {
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) part[w][nt][lane] = acc[nt];
+      __syncthreads();
+      // wavefront w adds up and stores every kMWaves-th tile
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+        if (nt % kMWaves == w) {
+          f4 sum = part[0][nt][lane];
+#pragma unroll
+          for (int k = 1; k < kMWaves; ++k) sum += part[k][nt][lane];
+          acc[nt] = sum;
+        }
+      __syncthreads();
+    }
     float* dst = dPsum + (size_t)q * PN;
+    bool inexact = false;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
+      if (!by_block || nt % kMWaves == w) {
+        inexact |= some_inexact<4>((const float*)&acc[nt]);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) dst[(4 * kg + v) * R + nt * 16 + l16] = acc[nt][v];
+        for (int v = 0; v < 4; ++v) dst[(4 * kg + v) * R + nt * 16 + l16] = acc[nt][v];
+      }
+    if (__ballot(inexact) && lane == 0) atomicOr(&ctr->small, 1);
   }
 }
 
@@ -730,20 +762,20 @@ __device__ __forceinline__ void dg3_chunk_rows(
   }
 }
 
-// chunks wave, wave + nwaves, ... in index order
-template <int R, int D3, int UB>
-__device__ __forceinline__ void dg3_role(
-    int wave, int nwaves, const float* __restrict__ P, const float* __restrict__ grad,
-    const float* __restrict__ gsum, const int2* __restrict__ c3_item,
-    const int4* __restrict__ c3_desc, float* __restrict__ part3, const Counters* __restrict__ ctr) {
-  const int nchunk = ctr->nchunk3;
-  for (int c = wave; c < nchunk; c += nwaves)
-    dg3_chunk_rows<R, D3, UB>(c, P, grad, gsum, c3_item, c3_desc, part3);
-}
+constexpr int kXcds = 8;
 
 // ---------------------------------------------------------------------------------------------
-// The two gradient steps that only need the per-id gradient sums run side by side in one launch:
-// even blocks form dPsum per prefix, odd blocks the partial G3 gradients per by-i3 chunk.
+// The two gradient steps that only need the per-id gradient sums in one launch: dPsum per prefix, and the
+// partial G3 gradients per by-i3 chunk, half of the blocks each.  Where prefixes have a few ids, the first is
+// bound by its stores (a product per prefix) and the second by its gathers (one per id), so that the roles
+// alternate, eight blocks at a time, one to an XCD; where they have many, a block takes a prefix, and that role
+// goes first: alternating, its blocks wait for compute units and are the kernel's end.
+//   ids, n, d, rank                                 alternating   one after the other
+//   500,000 Zipf, (480,500,500), (8,4,4), 128       1272          1490 us
+//   500,000 clustered, (480,480,482), (4,4,8), 64    233           207
+// Operands in 16-byte loads of several ids took the first line from 1700 us to this, the second from 231.
+constexpr int kManyIds = 16;  // ids per prefix of the batch
+
 template <int R, int D3>
 __global__ __launch_bounds__(kMThreads) void k_id_bwd_mfma(
     const float* __restrict__ g3, const float* __restrict__ P, const float* __restrict__ grad,
@@ -751,12 +783,20 @@ __global__ __launch_bounds__(kMThreads) void k_id_bwd_mfma(
     const int* __restrict__ q_us, const int2* __restrict__ c3_item,
     const int4* __restrict__ c3_desc, float* __restrict__ dPsum, float* __restrict__ part3,
     Counters* __restrict__ ctr) {
-  const int role = blockIdx.x & 1, block = blockIdx.x >> 1, nblocks = gridDim.x >> 1;
-  if (role == 0)
-    u_bwd_role<R, D3>(block, nblocks, g3, grad, gsum, u_code, u_i3, q_us, dPsum, ctr);
-  else
-    dg3_role<R, D3, (R >= 128) ? 2 : (R == 64) ? 4 : 8>(block * kMWaves + (int)threadIdx.x / kWave, nblocks * kMWaves,
-                                       P, grad, gsum, c3_item, c3_desc, part3, ctr);
+  constexpr int kIds = 4;                  // ids of a wavefront's round (more: fewer wavefronts, 219 us against 207)
+  constexpr int UB = R >= 128 ? 2 : 4;
+  __shared__ f4 part[kMWaves][R / 16][kWave];
+  const bool many = ctr->U >= (int64_t)kManyIds * ctr->Q;
+  const int b = blockIdx.x, half = gridDim.x / 2;  // a multiple of eight
+  const bool ids = many ? b < half : b / kXcds % 2 == 0;
+  const int block = many ? (ids ? b : b - half) : b / (2 * kXcds) * kXcds + b % kXcds;
+  if (ids) {
+    u_bwd_role<R, D3, kIds>(block, half, many, part, g3, grad, gsum, u_code, u_i3, q_us, dPsum, ctr);
+  } else {
+    const int nchunk = ctr->nchunk3;
+    for (int c = block * kMWaves + (int)threadIdx.x / kWave; c < nchunk; c += half * kMWaves)
+      dg3_chunk_rows<R, D3, UB>(c, P, grad, gsum, c3_item, c3_desc, part3);
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -800,7 +840,6 @@ __global__ __launch_bounds__(kMThreads) void k_id_bwd_mfma(
 // steps: 200,000 Zipf ids of 136^3 at rank 32 172 -> 169 us, look-ahead 137.2 -> 135.7 (where a list of the chunks
 // by prefix, 4 to 6 us of the index pipeline, took 138), 500,000 of 480x480x482 at rank 16 376.1 -> 375.6, 50,000
 // uniform ids of (55,55,56) x (8,4,4) 101.7 -> 102.1.  Groups of very different sizes are walked in index order.
-constexpr int kXcds = 8;
 template <class F>
 __device__ __forceinline__ void walk_chunks3(int xcd, int wave, int nwaves, int n3, const int* __restrict__ c3_start,
                                              const Counters* __restrict__ ctr, F take) {
@@ -1533,9 +1572,9 @@ void launch_prefix_bwd_mfma(const Plan& pl, const Workspace& ws, const float* g1
 
 void launch_id_bwd_mfma(const Plan& pl, const Workspace& ws, const float* g3, const float* grad,
                         int B, hipStream_t st) {
-  // both roles loop over their work with a stride of half the grid (which must be even)
+  // both roles loop over their work with a stride of half the grid
   const int64_t waves_q = std::min<int64_t>(B, pl.maxQ), waves_c = cdivi(B, chunk3_fill(B)) + (int64_t)pl.sh.n3;
-  const int per_role = grid_cap(cdivi(std::max(waves_q, waves_c), kMWaves), kMGridCap);
+  const int per_role = kXcds * grid_cap(cdivi(std::max(waves_q, waves_c), kMWaves * kXcds), kMGridCap / kXcds);
 #define TT_ID(RR, DD)                                                                              \
   k_id_bwd_mfma<RR, DD><<<2 * per_role, kMThreads, 0, st>>>(g3, ws.P, grad, ws.gsum, ws.u_code,    \
                                                             ws.u_i3, ws.q_us, ws.c3_item,          \
