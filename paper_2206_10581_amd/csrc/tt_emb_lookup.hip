@@ -45,7 +45,7 @@ __device__ __forceinline__ void swap_halves(float x, float y, float& of_lower, f
 // of arithmetic behind 166 us of index work, 366 us a lookup; here 90 behind 45.  Bound by the vector
 // memory path where prefixes have one or two ids: lines of G1 and G3 loaded element by element took 134
 // us instead of 113 with uniform ids.
-template <int R, int D3, int TSL>
+template <int R, int D3, int TSL, bool AHEAD>
 __global__ __launch_bounds__(kLThreads) void k_lookup_mfma(
     int B, int split, uint32_t n1, uint32_t sentinel, int i3_bits, const float* __restrict__ g1,
     const float* __restrict__ g2, const float* __restrict__ g3, const uint32_t* __restrict__ skey,
@@ -98,12 +98,60 @@ __global__ __launch_bounds__(kLThreads) void k_lookup_mfma(
   const int wide = split < 4 ? split : 4;      // slabs of a prefix in a batch
   const int most = 4 / wide;                   // prefixes in a batch
   const int id = D3 == 4 ? kg : kg / 2;        // id of a row product that this lane stores
+  // G1 lines of prefixes [pi, pi + nq), slabs from h0 on, as they lie in memory: line l16 is prefix pi +
+  // l16/4/wide, slab h0 + l16/4%wide (absent ones repeat one that is there); lanes kg and kg + 2 load a quarter
+  // line each (rank 8 element by element)
+  constexpr int NV = KQ % 4 == 0 ? KQ / 4 : 1;
+  const int my_q = l16 / 4 / wide, my_h = l16 / 4 - my_q * wide;
+  f4 av[NV];
+  auto load_lines = [&](int pi, int nq, int h0) {
+    const int qi = min(pi + my_q, pi + nq - 1), h = min(h0 + my_h, split - 1);
+    const float* line = g1 + ((size_t)__shfl(q_i1, qi) * split + h) * S1 + (l16 % 4) * R;
+    if constexpr (KQ % 4 == 0) {
+#pragma unroll
+      for (int j = 0; j < KQ / 4; ++j) av[j] = ((const f4*)(line + (kg % 2) * (R / 2) + (kg / 2) * KQ))[j];
+    } else {
+#pragma unroll
+      for (int j = 0; j < KQ; ++j) av[0][j] = line[k0 + 2 * j];
+    }
+  };
+  // slices of G3 of the row product whose first slot is `at`, as they lie in memory: a quad loads a 4 x 4 block by
+  // lines
+  f4 cv[NV];
+  auto end_of = [&](int at) {  // the next product's first slot or the next prefix's
+    const unsigned long long after = groups & ~((2ull << at) - 1ull);
+    return after ? __ffsll((long long)after) - 1 : nv;
+  };
+  const int j3 = l16 % D3;
+  auto load_slices = [&](int at) {
+    const int slot = min(at + l16 / D3, end_of(at) - 1);
+    const float* C = g3 + (size_t)__shfl(i3, slot) * S3 + (KQ * kg) * D3;
+    if constexpr (KQ % 4 == 0) {
+#pragma unroll
+      for (int j = 0; j < KQ / 4; ++j) cv[j] = *(const f4*)(C + (4 * j + j3 % 4) * D3 + j3 / 4 * 4);
+    } else {
+#pragma unroll
+      for (int j = 0; j < KQ; ++j) cv[0][j] = C[j * D3 + j3];
+    }
+  };
+  auto prefixes_from = [&](int pi) {
+    int nq = 1;
+    if (pi < np) {
+      const int bin = value_at(q_i2, pi);
+      while (nq < most && pi + nq < np && value_at(q_i2, pi + nq) == bin) ++nq;
+    }
+    return nq;
+  };
+
   f4 b2[NX][KQ];
   int have = -1;  // i2 of b2
+  int nq = prefixes_from(0);
+  if constexpr (AHEAD) {
+    load_lines(0, nq, 0);
+    load_slices(0);
+  }
   for (int pi = 0; pi < np;) {
     const int bin = value_at(q_i2, pi);
-    int nq = 1;
-    while (nq < most && pi + nq < np && value_at(q_i2, pi + nq) == bin) ++nq;
     if (bin != have) {
       have = bin;
       const float* Bm = g2 + (size_t)bin * S2;
@@ -116,25 +164,25 @@ __global__ __launch_bounds__(kLThreads) void k_lookup_mfma(
     // slots of the batch
     const int f0 = value_at(q_slot, pi), f1 = pi + nq < np ? value_at(q_slot, pi + nq) : nv;
     const unsigned long long here = groups & (f1 >= 64 ? ~0ull : (1ull << f1) - 1ull) & ~((1ull << f0) - 1ull);
+    const int next_nq = prefixes_from(pi + nq);
     for (int h0 = 0; h0 < split; h0 += wide) {  // one round up to d1 = 16
       {
-        // G1 line l16: prefix pi + l16/4/wide, slab h0 + l16/4%wide (absent ones repeat one that is there)
-        const int qi = min(pi + l16 / 4 / wide, pi + nq - 1), h = min(h0 + l16 / 4 % wide, split - 1);
-        const float* line = g1 + ((size_t)__shfl(q_i1, qi) * split + h) * S1 + (l16 % 4) * R;
+        if constexpr (!AHEAD) load_lines(pi, nq, h0);
         float a[KQ];
         if constexpr (KQ % 4 == 0) {
-          // lanes kg and kg + 2 load a quarter line each, then trade its odd for its even elements
-          f4 v[KQ / 4];
-#pragma unroll
-          for (int j = 0; j < KQ / 4; ++j) v[j] = ((const f4*)(line + (kg % 2) * (R / 2) + (kg / 2) * KQ))[j];
+          // lanes kg and kg + 2 trade the odd elements of one for the even ones of the other
 #pragma unroll
           for (int j = 0; j < KQ / 4; ++j) {
-            swap_halves(v[j].x, v[j].y, a[2 * j], a[KQ / 2 + 2 * j]);
-            swap_halves(v[j].z, v[j].w, a[2 * j + 1], a[KQ / 2 + 2 * j + 1]);
+            swap_halves(av[j].x, av[j].y, a[2 * j], a[KQ / 2 + 2 * j]);
+            swap_halves(av[j].z, av[j].w, a[2 * j + 1], a[KQ / 2 + 2 * j + 1]);
           }
         } else {
 #pragma unroll
-          for (int j = 0; j < KQ; ++j) a[j] = line[k0 + 2 * j];
+          for (int j = 0; j < KQ; ++j) a[j] = av[0][j];
+        }
+        if constexpr (AHEAD) {  // the next lines are in flight while these are used
+          if (h0 + wide < split) load_lines(pi, nq, h0 + wide);
+          else if (pi + nq < np) load_lines(pi + nq, next_nq, 0);
         }
         f4 acc[NX][4];
 #pragma unroll
@@ -161,22 +209,14 @@ __global__ __launch_bounds__(kLThreads) void k_lookup_mfma(
         wave_sync();
       }
       for (unsigned long long todo = here; todo; todo &= todo - 1) {
-        const int at = __ffsll((long long)todo) - 1;
-        // ends at the next product's first slot or the next prefix's
-        const unsigned long long after = groups & ~((2ull << at) - 1ull);
-        const int end = after ? __ffsll((long long)after) - 1 : nv, n = end - at;
+        const int at = __ffsll((long long)todo) - 1, end = end_of(at), n = end - at;
         const int qi = value_at(rank, at) - 1 - pi;
-        const int slot = min(at + l16 / D3, end - 1), j3 = l16 % D3;
-        const float* C = g3 + (size_t)__shfl(i3, slot) * S3 + (KQ * kg) * D3;
+        if constexpr (!AHEAD) load_slices(at);
         float c[KQ];  // c[j] = G3[KQ*kg + j][j3]
         if constexpr (KQ % 4 == 0) {
-          // a quad loads a 4 x 4 block by lines and turns it
-          f4 v[KQ / 4];
-#pragma unroll
-          for (int j = 0; j < KQ / 4; ++j) v[j] = *(const f4*)(C + (4 * j + j3 % 4) * D3 + j3 / 4 * 4);
 #pragma unroll
           for (int j = 0; j < KQ / 4; ++j) {
-            const f4 t = quad_turned(v[j], lane);
+            const f4 t = quad_turned(cv[j], lane);
             c[4 * j] = t.x;
             c[4 * j + 1] = t.y;
             c[4 * j + 2] = t.z;
@@ -184,7 +224,12 @@ __global__ __launch_bounds__(kLThreads) void k_lookup_mfma(
           }
         } else {
 #pragma unroll
-          for (int j = 0; j < KQ; ++j) c[j] = C[j * D3 + j3];
+          for (int j = 0; j < KQ; ++j) c[j] = cv[0][j];
+        }
+        if constexpr (AHEAD) {
+          // products follow each other in slot order; a further round of slabs begins with this batch's first
+          if ((todo & (todo - 1)) == 0 && h0 + wide < split) load_slices(f0);
+          else if (end < nv) load_slices(end);
         }
         const uint32_t row = (uint32_t)__shfl((int)pos, min(at + id, 63));
         const bool on = id < n && row < (uint32_t)B;
@@ -215,6 +260,7 @@ __global__ __launch_bounds__(kLThreads) void k_lookup_mfma(
       }
     }
     pi += nq;
+    nq = next_nq;
   }
 }
 
@@ -292,6 +338,14 @@ static int lookup_tile(const Shape& s, int B) {
   if (s.r1 <= 16) return B <= kSmallBatch ? 16 : 32;
   return B <= kSmallBatch / 16 ? 16 : B <= kSmallBatch ? 32 : 64;
 }
+// Up to kAheadMost ids and kAheadSlabs slabs the next batch's lines of G1 and the next product's slices of G3 are
+// loaded ahead: few wavefronts a compute unit, whose chain of loads is the time.  Above, other wavefronts fill the
+// waits, and what keeping loads in flight takes in instructions is lost.  Lookups in us without / with: rank 8,
+// 50,000 uniform ids of (55,55,56) x (8,4,4) 32.9 / 30.5, 120,000 clustered ones of 480x480x482 40.6 / 38.4; rank 16,
+// 20,000 Zipf ids of 136^3 36.2 / 34.5, 100,000 41.4 / 39.6, of (480,500,500) x (8,4,4) 80,000 Zipf ones 61.5 / 60.2
+// and uniform ones 130,000 82.8 / 84.1, 200,000 98 / 104; rank 32, 136^3, 12,000 Zipf ids 42.6 / 38.6, 120,000
+// uniform ones 64.8 / 63.5, 200,000 Zipf ones 79.5 / 89.
+constexpr int kAheadMost = 1 << 17, kAheadSlabs = 3 << 16;
 
 void launch_lookup(const Plan& pl, const Workspace& ws, const float* g1, const float* g2, const float* g3, int B,
                    float* out, hipStream_t st) {
@@ -302,13 +356,21 @@ void launch_lookup(const Plan& pl, const Workspace& ws, const float* g1, const f
         out, ws.ctr);
   };
   const int tile = lookup_tile(pl.sh, B);
+  const bool ahead = B <= kAheadMost && (int64_t)B * pl.split <= kAheadSlabs;
   auto by_d3 = [&](auto k4, auto k8) { pl.sh.d3 == 4 ? launch(k4, tile) : launch(k8, tile); };
-#define TT_TILE(R_, T_) by_d3(k_lookup_mfma<R_, 4, T_>, k_lookup_mfma<R_, 8, T_>)
+#define TT_TILE(R_, T_, A_) by_d3(k_lookup_mfma<R_, 4, T_, A_>, k_lookup_mfma<R_, 8, T_, A_>)
+#define TT_RANK(R_) \
+  if (ahead) TT_TILE(R_, 16, true); else if (tile == 16) TT_TILE(R_, 16, false); else TT_TILE(R_, 32, false)
   switch (pl.sh.r1) {
-    case 8: if (tile == 16) TT_TILE(8, 16); else TT_TILE(8, 32); break;
-    case 16: if (tile == 16) TT_TILE(16, 16); else TT_TILE(16, 32); break;
-    default: if (tile == 16) TT_TILE(32, 16); else if (tile == 32) TT_TILE(32, 32); else TT_TILE(32, 64);
+    case 8: TT_RANK(8); break;
+    case 16: TT_RANK(16); break;
+    default:
+      if (tile == 16) TT_TILE(32, 16, true);  // d1 = 32 has eight slabs an id: 2^17 at most
+      else if (tile == 32 && ahead) TT_TILE(32, 32, true);
+      else if (tile == 32) TT_TILE(32, 32, false);
+      else TT_TILE(32, 64, false);
   }
+#undef TT_RANK
 #undef TT_TILE
 }
 

@@ -65,6 +65,13 @@ def test_slabs(r, d3, d1):
     _compare((41, 37, 19), (d1, 4, d3), r, 17_003, "uniform", reindex=True)
 
 
+# with and without loads ahead: the most ids and slabs that have them, and more; slabs in two rounds without
+@pytest.mark.parametrize("d1,r,d3,B", [(4, 32, 8, 131_072), (4, 16, 4, 131_073), (8, 8, 4, 98_304), (8, 32, 8, 98_305),
+                                       (20, 16, 4, 40_001)])
+def test_loads_ahead(d1, r, d3, B):
+    _compare((41, 37, 19), (d1, 4, d3), r, B, "hot")
+
+
 # one prefix in all, one i2, one i3, few ids of a large table
 @pytest.mark.parametrize("n", [(1, 1, 50), (60, 1, 1), (1, 70, 1), (400, 900, 7), (3, 1000, 900)])
 def test_table_forms(n):
