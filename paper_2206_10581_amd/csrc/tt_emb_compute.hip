@@ -839,9 +839,23 @@ __global__ __launch_bounds__(kThreads) void k_sgd(Shape sh, float lr, UpdateRule
 #pragma unroll
         for (int x = 0; x < VEC; ++x) acc[x] += v[j][x];
     }
-    for (; k < n; k += parts)
+    // the rest of a list four at a time, the last one repeated and not added: one by one, up to seven round trips
+    // to memory (200,000 Zipf ids at rank 32 9.8 -> 8.7 us, 50,000 uniform ones with Adam 6.2 -> 5.0)
+    constexpr int kRest = 4;
+    for (; k < n; k += kRest * parts) {
+      float v[kRest][VEC];
 #pragma unroll
-      for (int x = 0; x < VEC; ++x) acc[x] += p[at(k) + x];
+      for (int j = 0; j < kRest; ++j)
+#pragma unroll
+        for (int x = 0; x < VEC; ++x) v[j][x] = p[at(min(k + j * parts, n - 1)) + x];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < kRest; ++j)
+        if (k + j * parts < n) {
+#pragma unroll
+          for (int x = 0; x < VEC; ++x) acc[x] += v[j][x];
+        }
+    }
     if (parts > 1) {
 #pragma unroll
       for (int x = 0; x < VEC; ++x) red[threadIdx.x][x] = acc[x];

@@ -137,14 +137,14 @@ struct ColumnSums {
 };
 
 // Stable ranks of a block's items in their buckets.  Every wavefront holds up to 256 consecutive items,
-// 64 a step (digit -1: no item); the wavefronts' runs follow each other.  wh: one row of row_words words
-// (a multiple of four) per wavefront, two 16-bit buckets a word: a wavefront owns 256 items and a block at
-// most 4096, so both fit.
+// 64 a step (digit -1: no item); the wavefronts' runs follow each other.  wh: a row per wavefront, stride words
+// apart, of row_words words (both multiples of four), two 16-bit buckets a word: a wavefront owns 256 items and a
+// block at most 4096, so both fit.
 template <int NT>
-__device__ __forceinline__ void block_ranks(uint32_t* wh, int row_words, const int (&digits)[kSteps],
+__device__ __forceinline__ void block_ranks(uint32_t* wh, int stride, int row_words, const int (&digits)[kSteps],
                                             uint32_t (&rank)[kSteps]) {
   const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
-  uint32_t* mine = wh + w * row_words;
+  uint32_t* mine = wh + w * stride;
   // every wavefront clears its own counters, 16 bytes per lane and write (no barrier: nobody else
   // touches them before the next one)
   for (int i = lane; i < row_words / 4; i += kWave) ((uint4*)mine)[i] = make_uint4(0u, 0u, 0u, 0u);
@@ -183,8 +183,8 @@ __device__ __forceinline__ void block_ranks(uint32_t* wh, int row_words, const i
     uint32_t lo = 0, hi = 0;
 #pragma unroll
     for (int k = 0; k < NT / kWave; ++k) {
-      const uint32_t c = wh[k * row_words + word];
-      wh[k * row_words + word] = lo | (hi << 16);
+      const uint32_t c = wh[k * stride + word];
+      wh[k * stride + word] = lo | (hi << 16);
       lo += c & 0xffffu;
       hi += c >> 16;
     }
@@ -197,11 +197,11 @@ __device__ __forceinline__ void block_ranks(uint32_t* wh, int row_words, const i
   }
 }
 
-template <int NT>
+template <int NT, bool FOLDS>
 struct alignas(16) ScatterLds {
   uint32_t wh[NT / kWave][kMaxBins / 2];  // counters of block_ranks
-  uint32_t tot[kMaxBins];                 // bucket totals, then first output per bucket
-  uint32_t before[kMaxBins];              // items of earlier blocks per bucket, then this block's first output
+  uint32_t tot[kMaxBins];                 // bucket totals, then this block's first output per bucket
+  uint32_t before[FOLDS ? kMaxBins : 1];  // items of earlier blocks per bucket
   uint32_t ldsw[NT / kWave];
 };
 
@@ -209,13 +209,13 @@ struct alignas(16) ScatterLds {
 __host__ __device__ constexpr int sort_row_words(int bins) { return bins < 8 ? 1 : bins / 8; }
 
 // One block's share of a stable counting-sort pass over n_items items (block blk of NT threads owns
-// items [blk*4*NT, +4*NT), each of its wavefronts 256 of them in order).  With tot != nullptr,
-// cnt[b][bin] holds, per bucket, the items of blocks before b and tot[bin] the bucket totals (both
-// from a column-scan kernel over the blocks' histograms); with tot == nullptr, cnt holds the
-// blocks' own histograms as rows of 16-bit counts and every block adds up its columns itself.
+// items [blk*4*NT, +4*NT), each of its wavefronts 256 of them in order).  FOLDS: cnt holds the blocks'
+// own histograms as rows of 16-bit counts, and every block adds up its columns itself; else cnt[b][bin]
+// holds, per bucket, the items of blocks before b and tot[bin] the bucket totals (both from a
+// column-scan kernel over the blocks' histograms).
 // ItemOps: Item load(int idx); int digit(Item); void emit(uint32_t pos, Item).
-template <int NT, class ItemOps>
-__device__ void stable_scatter_block(ScatterLds<NT>& L, int blk, int nblk, int n_items, int bins,
+template <int NT, bool FOLDS, class ItemOps>
+__device__ void stable_scatter_block(ScatterLds<NT, FOLDS>& L, int blk, int nblk, int n_items, int bins,
                                      const uint32_t* __restrict__ cnt,
                                      const uint32_t* __restrict__ tot, ItemOps ops) {
   constexpr int kItems = sort_items(NT);
@@ -231,8 +231,9 @@ __device__ void stable_scatter_block(ScatterLds<NT>& L, int blk, int nblk, int n
     const int idx = wbase + step * kWave + lane;
     items[step] = ops.load(idx < n_items ? idx : 0);
   }
-  if (tot != nullptr) {
-    uint32_t total[kMaxBins / NT], earlier[kMaxBins / NT];
+  uint32_t earlier[kMaxBins / NT];  // items of my buckets in earlier blocks
+  if constexpr (!FOLDS) {
+    uint32_t total[kMaxBins / NT];
 #pragma unroll
     for (int k = 0; k < kMaxBins / NT; ++k) {
       const int bc = min(tid + k * NT, bins - 1);
@@ -240,13 +241,8 @@ __device__ void stable_scatter_block(ScatterLds<NT>& L, int blk, int nblk, int n
       earlier[k] = cnt[(size_t)blk * bins + bc];
     }
 #pragma unroll
-    for (int k = 0; k < kMaxBins / NT; ++k) {
-      const int bin = tid + k * NT;
-      if (bin < bins) {
-        L.tot[bin] = total[k];
-        L.before[bin] = earlier[k];
-      }
-    }
+    for (int k = 0; k < kMaxBins / NT; ++k)
+      if (tid + k * NT < bins) L.tot[tid + k * NT] = total[k];
   } else {
     const int words = sort_row_words(bins);
     ColumnSums<NT == 256 ? 32 : 16> sums;
@@ -264,12 +260,19 @@ __device__ void stable_scatter_block(ScatterLds<NT>& L, int blk, int nblk, int n
     if (wbase + step * kWave + lane >= n_items) digits[step] = -1;
   __syncthreads();
   block_exclusive_scan(L.tot, bins, L.ldsw);
-  for (int bin = tid; bin < bins; bin += NT) L.before[bin] += L.tot[bin];
+#pragma unroll
+  for (int k = 0; k < kMaxBins / NT; ++k) {
+    const int bin = tid + k * NT;
+    if (bin < bins) {
+      if constexpr (FOLDS) L.tot[bin] += L.before[bin];
+      else L.tot[bin] += earlier[k];
+    }
+  }
   uint32_t rank[kSteps];
-  block_ranks<NT>(&L.wh[0][0], max((bins / 2 + 3) & ~3, 4), digits, rank);
+  block_ranks<NT>(&L.wh[0][0], kMaxBins / 2, max((bins / 2 + 3) & ~3, 4), digits, rank);
 #pragma unroll
   for (int step = 0; step < kSteps; ++step)
-    if (digits[step] >= 0) ops.emit(L.before[digits[step]] + rank[step], items[step]);
+    if (digits[step] >= 0) ops.emit(L.tot[digits[step]] + rank[step], items[step]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -357,13 +360,13 @@ __global__ __launch_bounds__(NT) void k_sort_hist(
   }
 }
 
-template <int NT, bool FROM_IDS>
+template <int NT, bool FROM_IDS, bool FOLDS>
 __global__ __launch_bounds__(NT) void k_sort_scatter(SortOps<FROM_IDS> ops, int B,
                                                                int bits,
                                                                const uint32_t* __restrict__ cnt,
                                                                const uint32_t* __restrict__ tot) {
-  __shared__ ScatterLds<NT> L;
-  stable_scatter_block(L, (int)blockIdx.x, (int)gridDim.x, B, 1 << bits, cnt, tot, ops);
+  __shared__ ScatterLds<NT, FOLDS> L;
+  stable_scatter_block<NT, FOLDS>(L, (int)blockIdx.x, (int)gridDim.x, B, 1 << bits, cnt, tot, ops);
 }
 
 // Turns the blocks' bucket counts cnt[b][bin] into counts of earlier blocks (exclusive scan down
@@ -708,7 +711,7 @@ __device__ void group_block(int blk, int nblk, int first, int count, int bins,
   }
   if (count == 0) return;  // uniform for the whole block
   uint32_t rank[kSteps];
-  block_ranks<NT>(wh, row_words, digits, rank);
+  block_ranks<NT>(wh, row_words, row_words, digits, rank);
 #pragma unroll
   for (int step = 0; step < kSteps; ++step) {
     const int digit = digits[step];
@@ -761,7 +764,6 @@ static void sort_pass(const Plan& pl, const Workspace& ws, const SortKeys& sk, c
   const int shift = sk.low + pass * sk.per;
   const int bits = std::min(sk.per, sk.bits - pass * sk.per);
   const bool folds = sort_folds(blocks, 1 << bits);
-  const uint32_t* tot = folds ? nullptr : ws.tot;
   const int in = (pass + 1) & 1;
   uint32_t *kin = ws.key[in], *vin = ws.val[in], *kout = ws.key[in ^ 1], *vout = ws.val[in ^ 1];
   if (which == 2) {
@@ -781,12 +783,15 @@ static void sort_pass(const Plan& pl, const Workspace& ws, const SortKeys& sk, c
       first(PrefixSource{src, sk.low, pl.user_n1, pl.sh.n2, pl.sh.n3});
     else
       first(src);
-  } else if (pass == 0) {
-    SortOps<true> ops{kin, nullptr, kout, vout, shift, (1u << bits) - 1u};
-    k_sort_scatter<NT, true><<<blocks, NT, 0, st>>>(ops, B, bits, ws.cnt, tot);
   } else {
-    SortOps<false> ops{kin, vin, kout, vout, shift, (1u << bits) - 1u};
-    k_sort_scatter<NT, false><<<blocks, NT, 0, st>>>(ops, B, bits, ws.cnt, tot);
+    auto scatter = [&](auto kernel, auto ops) { kernel<<<blocks, NT, 0, st>>>(ops, B, bits, ws.cnt, ws.tot); };
+    if (pass == 0) {
+      SortOps<true> ops{kin, nullptr, kout, vout, shift, (1u << bits) - 1u};
+      folds ? scatter(k_sort_scatter<NT, true, true>, ops) : scatter(k_sort_scatter<NT, true, false>, ops);
+    } else {
+      SortOps<false> ops{kin, vin, kout, vout, shift, (1u << bits) - 1u};
+      folds ? scatter(k_sort_scatter<NT, false, true>, ops) : scatter(k_sort_scatter<NT, false, false>, ops);
+    }
   }
 }
 
