@@ -675,91 +675,105 @@ __device__ __forceinline__ void dg3_chunk(
 }
 
 // ---------------------------------------------------------------------------------------------
-// Value of v in the lane `by` places further on in the same row of 16 lanes (a cross-lane move in
-// the vector ALU; lanes whose source falls outside the row get their own value back, and are not
-// used).
-template <int BY>
-__device__ __forceinline__ float row_lane_up(float v) {
-  if constexpr (BY == 0) return v;
-  else
-    return __builtin_bit_cast(
-        float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, v), __builtin_bit_cast(int, v),
-                                           0x100 + BY /* row_shl:BY */, 0xf, 0xf, false));
+// Sixteen 4 x 4 products, one term: tile b = lane/4, A[i] in lane i of the tile, B[j] in lane j, D[i][j] in
+// accumulator i of lane j.  The four tiles of a run of sixteen lanes share the A of the run's tile FROM.
+template <int FROM>
+__device__ __forceinline__ f4 mfma_shared(float a, float b, f4 c) {
+  return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 2, FROM, 0);
 }
 
-// The same partial sum for ranks 64 and 128, where a prefix product is 4 to 8 KiB and the loads
-// above would be 16 to 32 four-byte loads per id.  The contraction runs over the 16 rows
-// m = 4*j1 + j2 of the product; lane group kg takes j2 = kg and the four j1.  The columns of the
-// R/16 output tiles are dealt so that a 16-byte load along a row serves four tiles: column l16 of
-// tile 4x + t is b = 64x + 4*l16 + t.  The gradient row (16 x D3, row-major) is read with 4/G loads
-// that together cover it contiguously, G = 16/D3: lane l16 = jj*D3 + j3 of group kg reads
-// g[4*(x*G + jj) + kg][j3], and the lanes j3 < D3 that feed the matrix cores fetch the values of
-// jj > 0 from their row.
+// x of lanes l and l ^ 32 added up in the lower half of the lanes, y of both in the upper; the same for lanes l and
+// l ^ 16: x in the lower sixteen lanes of a half, y in the upper.
+__device__ __forceinline__ float add_halves(float x, float y) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, y),
+                                                  false, false);
+  return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+__device__ __forceinline__ float add_rows(float x, float y) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, y),
+                                                  false, false);
+  return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+
+// The same partial sum for ranks 64 and 128, where a prefix product is 4 to 8 KiB and the loads above would be 16 to
+// 32 four-byte loads per id.  The contraction runs over the 16 rows m = 4*j1 + j2 of the product; lane group kg
+// takes j2 = kg and the four j1, 16 bytes along a row: columns 64x + 4*l16 + t.  Products of 4 x 4, D3/4 of them
+// over the height of g^T: 16 x 16 tiles would be half (D3 = 8) or three quarters (D3 = 4) empty.  The gradient row
+// (16 x D3, row-major) is read with NL loads that together cover it contiguously: lane l16 = jj*D3 + j3 of group kg
+// has g[4*(y*G + jj) + kg][j3], and the quad that holds four j3 of a row feeds all quads of its group.  The groups'
+// sums are added up at the end, which leaves each with one column of four.
 template <int R, int D3, int UB>
 __device__ __forceinline__ void dg3_chunk_rows(
     int c, const float* __restrict__ P, const float* __restrict__ grad,
     const float* __restrict__ gsum, const int2* __restrict__ c3_item,
     const int4* __restrict__ c3_desc, float* __restrict__ part3) {
-  constexpr int PN = 16 * R, S3 = R * D3, D = 16 * D3, NT = R / 16, NX = R / 64;
-  constexpr int G = 16 / D3, NL = 4 / G;  // lanes groups per row of 16 lanes; loads per gradient row
+  constexpr int PN = 16 * R, S3 = R * D3, D = 16 * D3, NX = R / 64, JH = D3 / 4;
+  constexpr int G = 16 / D3, NL = 4 / G;  // rows of g in sixteen lanes; loads per gradient row
   const int lane = threadIdx.x % kWave;
   const int l16 = lane % 16, kg = lane / 16;
-  const int j3 = l16 % D3, jj = l16 / D3;
-  {
-    const int2 item = c3_item[(size_t)c * kChunk3 + lane % kChunk3];
-    const int cnt = c3_desc[c].z;
-    // records past the chunk's count are unwritten; only lanes below cnt are ever read
-    const int mycode = item.x, myq = item.y;
-    f4 acc[NT];
+  const int2 item = c3_item[(size_t)c * kChunk3 + lane % kChunk3];
+  const int cnt = wave_value(c3_desc[c].z);
+  // records past the chunk's count are unwritten; only lanes below cnt are ever read
+  const int mycode = item.x, myq = item.y;
+  f4 acc[NX][4][JH];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[nt] = f4{0.f, 0.f, 0.f, 0.f};
-    for (int i0 = 0; i0 < cnt; i0 += UB) {
-      float ld[UB][NL];
-      f4 b[UB][NX][4];
+  for (int y = 0; y < NX; ++y)
 #pragma unroll
-      for (int x = 0; x < UB; ++x) {
-        const int i = min(i0 + x, cnt - 1);
-        const float* gp = grad_row_ptr(lane_value(mycode, i), grad, gsum, D) + kg * D3 + j3;
-        const float* pp = P + (size_t)lane_value(myq, i) * PN + kg * R + l16 * 4;
+    for (int t = 0; t < 4; ++t)
 #pragma unroll
-        for (int y = 0; y < NL; ++y) ld[x][y] = gp[4 * (y * G + jj) * D3];
+      for (int jh = 0; jh < JH; ++jh) acc[y][t][jh] = f4{0.f, 0.f, 0.f, 0.f};
+  for (int i0 = 0; i0 < cnt; i0 += UB) {
+    float g[UB][NL];
+    f4 b[UB][NX][4];
 #pragma unroll
-        for (int y = 0; y < NX; ++y)
+    for (int x = 0; x < UB; ++x) {
+      const int i = min(i0 + x, cnt - 1);
+      const float* gp = grad_row_ptr(lane_value(mycode, i), grad, gsum, D) + kg * D3 + l16 % D3;
+      const float* pp = P + (size_t)lane_value(myq, i) * PN + kg * R + l16 * 4;
 #pragma unroll
-          for (int s = 0; s < 4; ++s) b[x][y][s] = *(const f4*)(pp + y * 64 + s * (4 * R));
-      }
-      TT_LOADS_DONE();
+      for (int y = 0; y < NL; ++y) g[x][y] = gp[4 * (y * G + l16 / D3) * D3];
 #pragma unroll
-      for (int x = 0; x < UB; ++x) {
-        const bool on = (i0 + x < cnt) && (l16 < D3);
-        float a[4];  // a[j1] = g[4*j1 + kg][j3]
+      for (int y = 0; y < NX; ++y)
 #pragma unroll
-        for (int y = 0; y < NL; ++y) {
-          if constexpr (G == 2) {
-            a[2 * y] = ld[x][y];
-            a[2 * y + 1] = row_lane_up<8>(ld[x][y]);
-          } else {
-            a[0] = ld[x][y];
-            a[1] = row_lane_up<4>(ld[x][y]);
-            a[2] = row_lane_up<8>(ld[x][y]);
-            a[3] = row_lane_up<12>(ld[x][y]);
-          }
-        }
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-          for (int s = 0; s < 4; ++s) acc[nt] = mfma16(on ? a[s] : 0.f, b[x][nt / 4][s][nt % 4], acc[nt]);
-      }
+        for (int j1 = 0; j1 < 4; ++j1) b[x][y][j1] = *(const f4*)(pp + y * 64 + j1 * (4 * R));
     }
-    float* dst = part3 + (size_t)c * S3;
+    TT_LOADS_DONE();
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
+    for (int x = 0; x < UB; ++x) {
+      if (i0 + x >= cnt) break;  // uniform
+      auto term = [&](auto row, auto height) {
+        constexpr int j1 = decltype(row)::value, jh = decltype(height)::value;
+        if constexpr (jh < JH) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int o3 = 4 * kg + v;
-        if (o3 < D3) dst[(nt / 4 * 64 + 4 * l16 + nt % 4) * D3 + o3] = acc[nt][v];
-      }
+          for (int y = 0; y < NX; ++y)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+              acc[y][t][jh] = mfma_shared<j1 % G * JH + jh>(g[x][j1 / G], b[x][y][j1][t], acc[y][t][jh]);
+        }
+      };
+      auto terms = [&](auto row) {
+        term(row, std::integral_constant<int, 0>{});
+        term(row, std::integral_constant<int, 1>{});
+      };
+      terms(std::integral_constant<int, 0>{});
+      terms(std::integral_constant<int, 1>{});
+      terms(std::integral_constant<int, 2>{});
+      terms(std::integral_constant<int, 3>{});
+    }
   }
+  // group kg ends with t = 0, 2, 1, 3
+  const int t = kg == 1 ? 2 : kg == 2 ? 1 : kg;
+  float* dst = part3 + (size_t)c * S3 + (4 * l16 + t) * D3;
+#pragma unroll
+  for (int y = 0; y < NX; ++y)
+#pragma unroll
+    for (int jh = 0; jh < JH; ++jh) {
+      f4 sum;
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        sum[v] = add_rows(add_halves(acc[y][0][jh][v], acc[y][1][jh][v]), add_halves(acc[y][2][jh][v], acc[y][3][jh][v]));
+      *(f4*)(dst + y * 64 * D3 + 4 * jh) = sum;
+    }
 }
 
 constexpr int kXcds = 8;
