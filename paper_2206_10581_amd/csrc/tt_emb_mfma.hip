@@ -798,7 +798,8 @@ __global__ __launch_bounds__(kMThreads) void k_id_bwd_mfma(
     const int4* __restrict__ c3_desc, float* __restrict__ dPsum, float* __restrict__ part3,
     Counters* __restrict__ ctr) {
   constexpr int kIds = 4;                  // ids of a wavefront's round (more: fewer wavefronts, 219 us against 207)
-  constexpr int UB = R >= 128 ? 2 : 4;
+  constexpr int UB = R >= 128 ? 1 : 2;     // ids of a round of the other role (twice as many: rank 128 977 us a step,
+                                           // against 967, at 100,000 uniform ids of 136^3 x (8,4,4))
   __shared__ f4 part[kMWaves][R / 16][kWave];
   const bool many = ctr->U >= (int64_t)kManyIds * ctr->Q;
   const int b = blockIdx.x, half = gridDim.x / 2;  // a multiple of eight
