@@ -544,7 +544,7 @@ static int run_sort(tt_emb* h, const Workspace& ws, const SortKeys& sk, const Id
       return run_slot(h, slot, st, [&] { launch_sort_pass(pl, ws, sk, src, B, pass, beside, clear, st, which); });
     };
     int rc = part(kSlotSortHist, 0);
-    if (!rc) rc = part(kSlotSortScan, 2);
+    if (!rc && !sort_folds(sk, B, pass, beside)) rc = part(kSlotSortScan, 2);
     if (!rc) rc = part(kSlotSortScatter, 1);
     if (rc) return rc;
   }

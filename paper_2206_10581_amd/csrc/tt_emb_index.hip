@@ -205,9 +205,6 @@ struct alignas(16) ScatterLds {
   uint32_t ldsw[NT / kWave];
 };
 
-// Words of eight 16-bit counts in a row of a sort block.
-__host__ __device__ constexpr int sort_row_words(int bins) { return bins < 8 ? 1 : bins / 8; }
-
 // One block's share of a stable counting-sort pass over n_items items (block blk of NT threads owns
 // items [blk*4*NT, +4*NT), each of its wavefronts 256 of them in order).  FOLDS: cnt holds the blocks'
 // own histograms as rows of 16-bit counts, and every block adds up its columns itself; else cnt[b][bin]
@@ -748,13 +745,6 @@ __global__ __launch_bounds__(NT) void k_group(
 
 static inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
-// Whether the scatter blocks add up the histograms' columns themselves, or a column-scan launch does it: every
-// block reads all rows, so the line lies at a number of 16-byte words of them.  Training steps, the launch
-// against the sums: 49 blocks of 64 words 87.4 / 84.1 us, 98 of 128 104.4 / 103.7, beside another batch's
-// arithmetic 49 of 256 121.1 / 122.8, 98 of 256 163.4 / 168.6 (and 245 of 64 even).
-constexpr int kFoldWords = 8192;
-static bool sort_folds(int blocks, int bins) { return (int64_t)blocks * sort_row_words(bins) <= kFoldWords; }
-
 // One of the three kernels of a pass.  clear: the first one also clears the tables that the steps
 // behind the sort add into (lookups have none).
 template <int NT>
@@ -762,12 +752,11 @@ static void sort_pass(const Plan& pl, const Workspace& ws, const SortKeys& sk, c
                       int pass, bool beside, bool clear, hipStream_t st, int which) {
   const int blocks = cdiv(B, sort_items(NT));
   const int shift = sk.low + pass * sk.per;
-  const int bits = std::min(sk.per, sk.bits - pass * sk.per);
-  const bool folds = sort_folds(blocks, 1 << bits);
+  const int bits = sk.bits_of(pass);
+  const bool folds = sort_folds(sk, B, pass, beside);
   const int in = (pass + 1) & 1;
   uint32_t *kin = ws.key[in], *vin = ws.val[in], *kout = ws.key[in ^ 1], *vout = ws.val[in ^ 1];
   if (which == 2) {
-    if (folds) return;
     k_sort_colscan<<<cdiv(1 << bits, kScanBins), kScanThreads, 0, st>>>(ws.cnt, ws.tot, blocks,
                                                                        1 << bits);
   } else if (which == 0) {
