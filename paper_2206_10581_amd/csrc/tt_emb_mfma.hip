@@ -525,10 +525,17 @@ __global__ __launch_bounds__(kMThreads, 2) void k_prefix_bwd_wide(
 
 // ---------------------------------------------------------------------------------------------
 // dPsum_q = sum over the unique ids u of prefix q of g_u G3[i3(u)]^T  (16 x D3 times D3 x R).
-// One wavefront per prefix, or where prefixes have many ids a block: its wavefronts take runs of MOST ids in
-// turn, their sums meet in LDS and are added in their order.  The ids of a prefix extend the contraction index:
-// 16 / D3 of them (a group) are one step, lane group kg holds four neighbours of a row of one id, so that a load
-// instruction brings 16 bytes a lane and as many lines as it has to.
+// One wavefront per prefix, or a block: its wavefronts take runs of MOST ids in turn, their sums meet in LDS and
+// are added in their order.  by_block gives every prefix to a block; else each wavefront has one, and those of
+// them with more than kLongIds ids are taken by all four afterwards.  The ids of a prefix extend the contraction
+// index: 16 / D3 of them (a group) are one step, lane group kg holds four neighbours of a row of one id, so that a
+// load instruction brings 16 bytes a lane and as many lines as it has to.
+//
+// A wavefront's long prefix is a chain of round trips that outlasts the kernel.  n = (400,400,2040), d = (4,4,8),
+// rank 64, this kernel with every prefix left to its wavefront / as it is: 6,000 ids, 2,000 of them of one prefix,
+// 444 / 119 us, 30,000 with 8 x 1,500 390 / 121, 40,000 with 300 x 60 75 / 75.  With 64 in place of 128, 200,000
+// ids of n = (160,160,500) with 72 a prefix took 163 us instead of 156.
+constexpr int kLongIds = 128;
 template <int R, int D3, int MOST>
 __device__ __forceinline__ void u_bwd_role(
     int block, int nblocks, bool by_block, f4 (*part)[R / 16][kWave], const float* __restrict__ g3,
@@ -538,81 +545,106 @@ __device__ __forceinline__ void u_bwd_role(
   constexpr int PN = 16 * R, S3 = R * D3, D = 16 * D3, NT = R / 16, KS = D3 / 4, IPG = 4 / KS;
   const int w = wave_value(threadIdx.x / kWave), lane = threadIdx.x % kWave;
   const int l16 = lane % 16, kg = lane / 16;
-  const int Q = ctr->Q;
-  const int step = by_block ? nblocks : nblocks * kMWaves, hop = by_block ? kMWaves * MOST : MOST;
-  for (int q = by_block ? block : block * kMWaves + w; q < Q; q += step) {
-    const int u0 = wave_value(q_us[q]), u1 = wave_value(q_us[q + 1]);
-    f4 acc[NT];
+  const int Q = ctr->Q, run = by_block ? 1 : kMWaves;  // prefixes of a block's turn
+  for (int q0 = block * run; q0 < Q; q0 += nblocks * run) {
+    int q = q0, u0 = 0, u1 = 0;
+    uint32_t whole = 1u;  // prefixes of the turn that the whole block takes
+    bool shared = by_block;
+    if (!by_block) {
+      int at[kMWaves + 1];  // one round trip, and none that waits for the last prefix's stores (scalar loads)
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[nt] = f4{0.f, 0.f, 0.f, 0.f};
-    const int first = u0 + (by_block ? w * MOST : 0);
-    auto id_of = [&](int ub) { return min(ub + lane % MOST, u1 - 1); };
-    int next_i3 = u_i3[id_of(first)], next_code = u_code[id_of(first)];
-    for (int ub = first; ub < u1; ub += hop) {
-      const int n = min(MOST, u1 - ub);
-      const int myi3 = next_i3, mycode = next_code;
-      next_i3 = u_i3[id_of(ub + hop)];  // on their way while this round's rows are
-      next_code = u_code[id_of(ub + hop)];
-      auto round = [&](auto groups, int i0) {
-        constexpr int NG = decltype(groups)::value;
-        f4 a[NG], b[NG][NT];
+      for (int k = 0; k <= kMWaves; ++k) at[k] = q_us[min(q0 + k, Q)];
+      whole = 0u;
 #pragma unroll
-        for (int x = 0; x < NG; ++x) {
-          const int i = min(i0 + x * IPG + kg / KS, n - 1);
-          const float* gp = grad_row_ptr(__shfl(mycode, i), grad, gsum, D) + l16 * D3 + kg % KS * 4;
-          const float* cp = g3 + (size_t)(uint32_t)__shfl(myi3, i) * S3 + l16 * D3 + kg % KS * 4;
-          a[x] = *(const f4*)gp;
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt) b[x][nt] = *(const f4*)(cp + nt * 16 * D3);
-        }
-        TT_LOADS_DONE();
-#pragma unroll
-        for (int x = 0; x < NG; ++x) {
-          // lanes without an id: both factors are zero, whatever the last one holds
-          if (i0 + (x + 1) * IPG > n) {
-            const bool on = i0 + x * IPG + kg / KS < n;
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-              a[x][s] = on ? a[x][s] : 0.f;
-#pragma unroll
-              for (int nt = 0; nt < NT; ++nt) b[x][nt][s] = on ? b[x][nt][s] : 0.f;
-            }
-          }
-#pragma unroll
-          for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) acc[nt] = mfma16(a[x][s], b[x][nt][s], acc[nt]);
-        }
-      };
-      if (MOST > IPG && n > MOST / 2) round(std::integral_constant<int, MOST / IPG>{}, 0);
-      else
-        for (int i0 = 0; i0 < n; i0 += IPG) round(std::integral_constant<int, 1>{}, i0);
+      for (int k = 0; k < kMWaves; ++k) {
+        whole |= at[k + 1] - at[k] > kLongIds ? 1u << k : 0u;
+        u0 = w == k ? at[k] : u0;
+        u1 = w == k ? at[k + 1] : u1;
+      }
+      q += w;
+      if (u1 - u0 > kLongIds) u1 = u0;
     }
-    if (by_block) {
+    for (;; shared = true) {
+      if (shared) {
+        if (whole == 0) break;
+        q = q0 + __ffs((int)whole) - 1;
+        whole &= whole - 1;
+        u0 = wave_value(q_us[q]);
+        u1 = wave_value(q_us[q + 1]);
+      }
+      if (u1 == u0) continue;
+      f4 acc[NT];
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) part[w][nt][lane] = acc[nt];
-      __syncthreads();
-      // wavefront w adds up and stores every kMWaves-th tile
+      for (int nt = 0; nt < NT; ++nt) acc[nt] = f4{0.f, 0.f, 0.f, 0.f};
+      const int first = u0 + (shared ? w * MOST : 0), hop = shared ? kMWaves * MOST : MOST;
+      auto id_of = [&](int ub) { return min(ub + lane % MOST, u1 - 1); };
+      int next_i3 = u_i3[id_of(first)], next_code = u_code[id_of(first)];
+      for (int ub = first; ub < u1; ub += hop) {
+        const int n = min(MOST, u1 - ub);
+        const int myi3 = next_i3, mycode = next_code;
+        next_i3 = u_i3[id_of(ub + hop)];  // on their way while this round's rows are
+        next_code = u_code[id_of(ub + hop)];
+        auto round = [&](auto groups, int i0) {
+          constexpr int NG = decltype(groups)::value;
+          f4 a[NG], b[NG][NT];
+#pragma unroll
+          for (int x = 0; x < NG; ++x) {
+            const int i = min(i0 + x * IPG + kg / KS, n - 1);
+            const float* gp = grad_row_ptr(__shfl(mycode, i), grad, gsum, D) + l16 * D3 + kg % KS * 4;
+            const float* cp = g3 + (size_t)(uint32_t)__shfl(myi3, i) * S3 + l16 * D3 + kg % KS * 4;
+            a[x] = *(const f4*)gp;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) b[x][nt] = *(const f4*)(cp + nt * 16 * D3);
+          }
+          TT_LOADS_DONE();
+#pragma unroll
+          for (int x = 0; x < NG; ++x) {
+            // lanes without an id: both factors are zero, whatever the last one holds
+            if (i0 + (x + 1) * IPG > n) {
+              const bool on = i0 + x * IPG + kg / KS < n;
+#pragma unroll
+              for (int s = 0; s < 4; ++s) {
+                a[x][s] = on ? a[x][s] : 0.f;
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) b[x][nt][s] = on ? b[x][nt][s] : 0.f;
+              }
+            }
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+              for (int nt = 0; nt < NT; ++nt) acc[nt] = mfma16(a[x][s], b[x][nt][s], acc[nt]);
+          }
+        };
+        if (MOST > IPG && n > MOST / 2) round(std::integral_constant<int, MOST / IPG>{}, 0);
+        else
+          for (int i0 = 0; i0 < n; i0 += IPG) round(std::integral_constant<int, 1>{}, i0);
+      }
+      if (shared) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) part[w][nt][lane] = acc[nt];
+        __syncthreads();
+        // wavefront w adds up and stores every kMWaves-th tile
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+          if (nt % kMWaves == w) {
+            f4 sum = part[0][nt][lane];
+#pragma unroll
+            for (int k = 1; k < kMWaves; ++k) sum += part[k][nt][lane];
+            acc[nt] = sum;
+          }
+        __syncthreads();
+      }
+      float* dst = dPsum + (size_t)q * PN;
+      bool inexact = false;
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt)
-        if (nt % kMWaves == w) {
-          f4 sum = part[0][nt][lane];
+        if (!shared || nt % kMWaves == w) {
+          inexact |= some_inexact<4>((const float*)&acc[nt]);
 #pragma unroll
-          for (int k = 1; k < kMWaves; ++k) sum += part[k][nt][lane];
-          acc[nt] = sum;
+          for (int v = 0; v < 4; ++v) dst[(4 * kg + v) * R + nt * 16 + l16] = acc[nt][v];
         }
-      __syncthreads();
+      if (__ballot(inexact) && lane == 0) atomicOr(&ctr->small, 1);
     }
-    float* dst = dPsum + (size_t)q * PN;
-    bool inexact = false;
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-      if (!by_block || nt % kMWaves == w) {
-        inexact |= some_inexact<4>((const float*)&acc[nt]);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) dst[(4 * kg + v) * R + nt * 16 + l16] = acc[nt][v];
-      }
-    if (__ballot(inexact) && lane == 0) atomicOr(&ctr->small, 1);
   }
 }
 
@@ -780,14 +812,20 @@ constexpr int kXcds = 8;
 
 // ---------------------------------------------------------------------------------------------
 // The two gradient steps that only need the per-id gradient sums in one launch: dPsum per prefix, and the
-// partial G3 gradients per by-i3 chunk, half of the blocks each.  Where prefixes have a few ids, the first is
-// bound by its stores (a product per prefix) and the second by its gathers (one per id), so that the roles
-// alternate, eight blocks at a time, one to an XCD; where they have many, a block takes a prefix, and that role
-// goes first: alternating, its blocks wait for compute units and are the kernel's end.
-//   ids, n, d, rank                                 alternating   one after the other
-//   500,000 Zipf, (480,500,500), (8,4,4), 128       1272          1490 us
-//   500,000 clustered, (480,480,482), (4,4,8), 64    233           207
-// Operands in 16-byte loads of several ids took the first line from 1700 us to this, the second from 231.
+// partial G3 gradients per by-i3 chunk.  The first is bound by its stores (a product per prefix) and the second by its
+// gathers (one per id), so that the roles have half of the blocks each and alternate, eight blocks at a time, one to
+// an XCD.  Few prefixes of many ids leave most wavefronts of the first role without one: there a block takes a prefix,
+// and that role has as many blocks as prefixes and goes first: alternating, its blocks wait for compute units and are
+// the kernel's end.  The line is a number of prefixes, and lower at d3 = 4, where rounds are shorter; fewer than
+// kManyIds ids each leave wavefronts of the block without any.  This kernel in us, a wavefront / a block a prefix,
+// n = (160,160,500):
+//   d, rank, ids                  prefixes
+//   (4,4,8),  64, 200,000           500: 130 / 124   2,000: 158 / 145   2,778: 157 / 153   4,167: 160 / 169
+//   (4,4,8), 128, 100,000           250: 152 / 112   1,000: 166 / 127   2,083: 161 / 161   4,167: 155 / 183
+//   (8,4,4),  64, 100,000 (slabs)   500:  75 /  66   1,000:  82 /  71   2,000: 101 / 104   2,778: 110 / 114
+//   (8,4,4), 128,  50,000 (slabs)   250:  91 /  66     500:  79 /  67   1,000:  89 /  92   1,389: 101 / 107
+// and with 2, 4, 8 and 16 ids to each of 2,000 prefixes, (4,4,8), rank 128: 16 / 23, 23 / 29, 35 / 41, 55 / 54.
+// 500,000 Zipf ids of (480,500,500) x (8,4,4) at rank 128: 1272 alternating, 1490 one after the other.
 constexpr int kManyIds = 16;  // ids per prefix of the batch
 
 template <int R, int D3>
@@ -801,15 +839,17 @@ __global__ __launch_bounds__(kMThreads) void k_id_bwd_mfma(
   constexpr int UB = R >= 128 ? 1 : 2;     // ids of a round of the other role (twice as many: rank 128 977 us a step,
                                            // against 967, at 100,000 uniform ids of 136^3 x (8,4,4))
   __shared__ f4 part[kMWaves][R / 16][kWave];
-  const bool many = ctr->U >= (int64_t)kManyIds * ctr->Q;
+  constexpr int kFewPrefixes = D3 == 8 ? 3072 : 1024;
+  const bool many = ctr->Q <= kFewPrefixes && ctr->U >= (int64_t)kManyIds * ctr->Q;
   const int b = blockIdx.x, half = gridDim.x / 2;  // a multiple of eight
-  const bool ids = many ? b < half : b / kXcds % 2 == 0;
-  const int block = many ? (ids ? b : b - half) : b / (2 * kXcds) * kXcds + b % kXcds;
+  const int first = many ? min((ctr->Q + kXcds - 1) / kXcds * kXcds, half) : half;  // blocks of the first role
+  const bool ids = many ? b < first : b / kXcds % 2 == 0;
+  const int block = many ? (ids ? b : b - first) : b / (2 * kXcds) * kXcds + b % kXcds;
   if (ids) {
-    u_bwd_role<R, D3, kIds>(block, half, many, part, g3, grad, gsum, u_code, u_i3, q_us, dPsum, ctr);
+    u_bwd_role<R, D3, kIds>(block, first, many, part, g3, grad, gsum, u_code, u_i3, q_us, dPsum, ctr);
   } else {
     const int nchunk = ctr->nchunk3;
-    for (int c = block * kMWaves + (int)threadIdx.x / kWave; c < nchunk; c += half * kMWaves)
+    for (int c = block * kMWaves + (int)threadIdx.x / kWave; c < nchunk; c += ((int)gridDim.x - first) * kMWaves)
       dg3_chunk_rows<R, D3, UB>(c, P, grad, gsum, c3_item, c3_desc, part3);
   }
 }
