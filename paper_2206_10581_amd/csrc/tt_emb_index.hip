@@ -136,13 +136,13 @@ struct ColumnSums {
   }
 };
 
-// Stable ranks of a block's items in their buckets.  Every wavefront holds up to 256 consecutive items,
+// Stable ranks of a block's items in their buckets, given to take(step, rank).  Every wavefront holds up to 256 consecutive items,
 // 64 a step (digit -1: no item); the wavefronts' runs follow each other.  wh: a row per wavefront, stride words
 // apart, of row_words words (both multiples of four), two 16-bit buckets a word: a wavefront owns 256 items and a
 // block at most 4096, so both fit.
-template <int NT>
+template <int NT, class F>
 __device__ __forceinline__ void block_ranks(uint32_t* wh, int stride, int row_words, const int (&digits)[kSteps],
-                                            uint32_t (&rank)[kSteps]) {
+                                            F take) {
   const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
   uint32_t* mine = wh + w * stride;
   // every wavefront clears its own counters, 16 bytes per lane and write (no barrier: nobody else
@@ -152,6 +152,7 @@ __device__ __forceinline__ void block_ranks(uint32_t* wh, int stride, int row_wo
   // Each wavefront walks its items in order, 64 at a time.  Lanes holding the same digit find each
   // other by ballots; the lowest of them advances the wavefront's bucket counter for all, which
   // gives every item its rank among the wavefront's items of that bucket.
+  uint32_t rank[kSteps];
   const unsigned long long lt_mask = (1ull << lane) - 1ull;
   unsigned long long peers[kSteps];
 #pragma unroll
@@ -193,7 +194,7 @@ __device__ __forceinline__ void block_ranks(uint32_t* wh, int stride, int row_wo
 #pragma unroll
   for (int step = 0; step < kSteps; ++step) {
     const int digit = digits[step];
-    if (digit >= 0) rank[step] += (mine[digit >> 1] >> (16 * (digit & 1))) & 0xffffu;
+    if (digit >= 0) take(step, rank[step] + ((mine[digit >> 1] >> (16 * (digit & 1))) & 0xffffu));
   }
 }
 
@@ -265,11 +266,8 @@ __device__ void stable_scatter_block(ScatterLds<NT, FOLDS>& L, int blk, int nblk
       else L.tot[bin] += earlier[k];
     }
   }
-  uint32_t rank[kSteps];
-  block_ranks<NT>(&L.wh[0][0], kMaxBins / 2, max((bins / 2 + 3) & ~3, 4), digits, rank);
-#pragma unroll
-  for (int step = 0; step < kSteps; ++step)
-    if (digits[step] >= 0) ops.emit(L.tot[digits[step]] + rank[step], items[step]);
+  block_ranks<NT>(&L.wh[0][0], kMaxBins / 2, max((bins / 2 + 3) & ~3, 4), digits,
+                  [&](int step, uint32_t rank) { ops.emit(L.tot[digits[step]] + rank, items[step]); });
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -707,15 +705,10 @@ __device__ void group_block(int blk, int nblk, int first, int count, int bins,
     chunk_desc[c] = make_int4(lo, 0, (int)min((uint32_t)chunk, tot[lo] - (c - aux[lo]) * (uint32_t)chunk), 0);
   }
   if (count == 0) return;  // uniform for the whole block
-  uint32_t rank[kSteps];
-  block_ranks<NT>(wh, row_words, row_words, digits, rank);
-#pragma unroll
-  for (int step = 0; step < kSteps; ++step) {
-    const int digit = digits[step];
-    if (digit < 0) continue;
-    const uint32_t in_bucket = before[digit] + rank[step];
-    ops.emit(aux[digit] + (in_bucket >> chunk_sh), in_bucket & (uint32_t)(chunk - 1), items[step]);
-  }
+  block_ranks<NT>(wh, row_words, row_words, digits, [&](int step, uint32_t rank) {
+    const uint32_t in_bucket = before[digits[step]] + rank;
+    ops.emit(aux[digits[step]] + (in_bucket >> chunk_sh), in_bucket & (uint32_t)(chunk - 1), items[step]);
+  });
 }
 
 // Blocks [0, ub): unique ids by i3; the nblk behind them: prefixes by i2.
