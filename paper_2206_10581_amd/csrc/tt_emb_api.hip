@@ -237,7 +237,7 @@ static size_t carve(const Plan& pl, char* base, Workspace* ws /* [kSets] or null
                  coarse_q = (size_t)cdiv64(pl.maxQ, sort_items(1024));
     char* counts = take(al(coarse_u * kMaxBins * 4) + al(coarse_u * s.n3 * 4) + al(coarse_q * s.n2 * 4));
     w.seg_rows = (uint16_t*)counts;
-    w.seg_base = (int4*)take(mB * 4);  // 16 bytes per 1024 rows or more
+    w.seg_base = (int4*)take((size_t)pl.slotBlocksMax * 16);
     w.c3_start = (int*)take(((size_t)s.n3 + 1) * 4);
     w.c3_desc = (int4*)take((size_t)pl.maxChunk3 * 16);
     w.c3_item = (int2*)take((size_t)pl.maxChunk3 * kChunk3 * 8);
@@ -248,10 +248,6 @@ static size_t carve(const Plan& pl, char* base, Workspace* ws /* [kSets] or null
     // g1_first[n1], g1_end[n1]: one stretch, cleared by the first sort pass
     w.g1_first = (int*)take((size_t)s.n1 * 8);
     w.g1_end = w.g1_first + s.n1;
-    // The largest batch that tt_emb_lookup_static takes follows from this size and is what it was when there were
-    // lists of ids and prefixes and an order of the chunks here.
-    off += al(((size_t)s.n3 + 1) * 4) + al(((size_t)s.n2 + 1) * 4) + al(mQ * 4) + al((size_t)pl.maxChunk3 * 4) +
-           al((size_t)s.n1 * 8 + 8192) - al((size_t)s.n1 * 8);
   }
   Workspace& w = set[0];
   const size_t arithmetic = off;
@@ -800,6 +796,14 @@ int tt_emb_materialize(tt_emb_t h, int64_t first_row, int64_t count, float* out,
 // Lookup for callers that cannot allocate: the workspace of the lookup-only forward (one index set
 // and the prefix products) lives in a file-scope device array instead of a caller's buffer.
 constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
+// What tt_emb_lookup_static counts for a batch: its workspace, and the lists of ids and prefixes and the order of
+// chunks that an index set once held.  They set the largest batch of each table, which callers rely on.
+static size_t static_need(const Plan& pl) {
+  auto al = [](size_t bytes) { return (bytes + 255) & ~size_t(255); };
+  const size_t mB = (size_t)pl.maxB, mQ = (size_t)pl.maxQ, n1 = pl.sh.n1, n2 = pl.sh.n2, n3 = pl.sh.n3;
+  return carve(pl, nullptr, nullptr, 1, true) + al(mB * 4) - al((size_t)pl.slotBlocksMax * 16) + al((n3 + 1) * 4) +
+         al((n2 + 1) * 4) + al(mQ * 4) + al((size_t)pl.maxChunk3 * 4) + al(n1 * 8 + 8192) - al(n1 * 8);
+}
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 constexpr int kStaticMaxDevices = 64;
 // device address of `scratch` on each device, looked up once per device (every device holds its
@@ -821,7 +825,7 @@ int tt_emb_lookup_static(const tt_emb_config* cfg, const float* g1, const float*
   Plan pl;
   int rc = make_plan(&c, &pl);
   if (rc != TT_EMB_OK) return rc;
-  if (carve(pl, nullptr, nullptr, 1, true) > kStaticScratchBytes) return TT_EMB_ENOSPC;
+  if (static_need(pl) > kStaticScratchBytes) return TT_EMB_ENOSPC;
   int dev = -1;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e);
