@@ -357,8 +357,9 @@ void launch_lookup(const Plan& pl, const Workspace& ws, const float* g1, const f
   };
   const int tile = lookup_tile(pl.sh, B);
   const bool ahead = B <= kAheadMost && (int64_t)B * pl.split <= kAheadSlabs;
-  auto by_d3 = [&](auto k4, auto k8) { pl.sh.d3 == 4 ? launch(k4, tile) : launch(k8, tile); };
-#define TT_TILE(R_, T_, A_) by_d3(k_lookup_mfma<R_, 4, T_, A_>, k_lookup_mfma<R_, 8, T_, A_>)
+  auto by_d3 = [&](auto k4, auto k8, int slots) { pl.sh.d3 == 4 ? launch(k4, slots) : launch(k8, slots); };
+  // the grid is made for the slots of the kernel that is launched
+#define TT_TILE(R_, T_, A_) by_d3(k_lookup_mfma<R_, 4, T_, A_>, k_lookup_mfma<R_, 8, T_, A_>, T_)
 #define TT_RANK(R_) \
   if (ahead) TT_TILE(R_, 16, true); else if (tile == 16) TT_TILE(R_, 16, false); else TT_TILE(R_, 32, false)
   switch (pl.sh.r1) {
