@@ -239,6 +239,7 @@ static size_t carve(const Plan& pl, char* base, Workspace* ws /* [kSets] or null
     w.seg_rows = (uint16_t*)counts;
     w.seg_base = (int4*)take((size_t)pl.slotBlocksMax * 16);
     w.c3_start = (int*)take(((size_t)s.n3 + 1) * 4);
+    w.walk3 = lookup_only ? nullptr : (int4*)take((size_t)s.n3 * 2 * 16);
     w.c3_desc = (int4*)take((size_t)pl.maxChunk3 * 16);
     w.c3_item = (int2*)take((size_t)pl.maxChunk3 * kChunk3 * 8);
     w.cnt = (uint32_t*)(shared ? (char*)w.c3_item : counts);

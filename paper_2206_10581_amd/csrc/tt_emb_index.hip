@@ -640,13 +640,15 @@ constexpr size_t group_lds(int threads, int bins) {
 // blk of nblk found.  rows: 16-bit counts per bucket of every block, `stride` apart.  Every bucket is cut
 // into chunks of `chunk` items (a power of two): chunk_desc[c] = {bucket, 0, item count, 0} for all chunks
 // c in bucket order, chunk_starts[bucket] the first chunk of each bucket (bins+1 entries), *n_chunks the
-// number of chunks; the item that is the t-th of chunk c goes to emit(c, t, item).
+// number of chunks; the item that is the t-th of chunk c goes to emit(c, t, item).  Block `publisher` writes the
+// tables of one entry per bucket; with walk (2*bins entries) also the columns of walk_chunks3.
 // The blocks add up the columns of `rows` themselves (ColumnSums): k_group, 100,000 uniform items of n3 = 56
 // 17 -> 7.4 us, 200,000 Zipf ids of n3 = 136 14.8 -> 8, 500,000 of n3 = 480 25.7 -> 15.5.
 template <int NT, class ItemOps>
 __device__ void group_block(int blk, int nblk, int first, int count, int bins,
                             const uint16_t* __restrict__ rows, int stride, ItemOps ops, int chunk,
-                            int* chunk_starts, int4* chunk_desc, int* n_chunks, int* most) {
+                            int publisher, int* chunk_starts, int4* chunk_desc, int* n_chunks, int4* walk,
+                            int* walk_cols, int* walk_steps) {
   extern __shared__ __attribute__((aligned(16))) uint32_t group_words[];
   __shared__ uint32_t ldsw[NT / kWave], most_chunks;
   const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
@@ -684,19 +686,42 @@ __device__ void group_block(int blk, int nblk, int first, int count, int bins,
     aux[bin] = (tot[bin] + chunk - 1) >> chunk_sh;
     my_most = max(my_most, aux[bin]);
   }
-  if (blk == 0 && my_most > 0) atomicMax(&most_chunks, my_most);
+  if (blk == publisher && my_most > 0) atomicMax(&most_chunks, my_most);
   __syncthreads();
   const uint32_t total_chunks = block_exclusive_scan(aux, bins, ldsw);
-  if (blk == 0) {
+  if (blk == publisher) {
     for (int bin = tid; bin < bins; bin += NT) chunk_starts[bin] = (int)aux[bin];
     if (tid == 0) {
       chunk_starts[bins] = (int)total_chunks;
       *n_chunks = (int)total_chunks;
-      if (most != nullptr) *most = (int)most_chunks;
+    }
+    if (walk != nullptr) {
+      auto chunks_of = [&](int bin) { return (bin + 1 < bins ? aux[bin + 1] : total_chunks) - aux[bin]; };
+      const uint32_t mean = (total_chunks + kXcds * bins - 1) / (kXcds * bins);  // of a bucket's eighth
+      const uint32_t steps = max(min((most_chunks + kXcds - 1) / kXcds, kWalkMeans * mean), 1u);
+      uint32_t* first_col = wh;  // free until block_ranks; at least two words a bucket
+      for (int bin = tid; bin < bins; bin += NT)
+        first_col[bin] = ((chunks_of(bin) + kXcds - 1) / kXcds + steps - 1) / steps;
+      __syncthreads();
+      const int cols = (int)block_exclusive_scan(first_col, bins, ldsw);
+      for (int c = tid; c < cols; c += NT) {
+        int lo = 0, hi = bins;  // last bucket whose first column is <= c
+        while (hi - lo > 1) {
+          const int mid = (lo + hi) >> 1;
+          if ((int)first_col[mid] <= c) lo = mid; else hi = mid;
+        }
+        const int next = lo + 1 < bins ? (int)first_col[lo + 1] : cols;
+        walk[c] = make_int4((int)aux[lo], (int)chunks_of(lo), c - (int)first_col[lo], next - (int)first_col[lo]);
+      }
+      if (tid == 0) {
+        *walk_cols = cols;
+        *walk_steps = (int)steps;
+      }
+      __syncthreads();  // block_ranks clears what the columns were counted in
     }
   }
-  // every block takes a share of the chunk descriptors
-  for (uint32_t c = (uint32_t)blk * NT + tid; c < total_chunks; c += (uint32_t)nblk * NT) {
+  // every block of slots takes a share of the chunk descriptors
+  for (uint32_t c = (uint32_t)blk * NT + tid; blk < nblk && c < total_chunks; c += (uint32_t)nblk * NT) {
     int lo = 0, hi = bins;  // last bucket whose first chunk is <= c
     while (hi - lo > 1) {
       const int mid = (lo + hi) >> 1;
@@ -711,25 +736,26 @@ __device__ void group_block(int blk, int nblk, int first, int count, int bins,
   });
 }
 
-// Blocks [0, ub): unique ids by i3; the nblk behind them: prefixes by i2.
+// Blocks [0, ub): unique ids by i3, a block per block of slots and one behind them that only writes the tables of
+// one entry per bucket; the nblk behind those: prefixes by i2.
 template <int NT>
 __global__ __launch_bounds__(NT) void k_group(
     Shape sh, int ub, int nblk, int chunk3, int p3, int p2, const int4* __restrict__ seg_base,
     const uint16_t* __restrict__ rows, const int* __restrict__ u_i3, const int* __restrict__ u_code,
     const int* __restrict__ u_q, const int* __restrict__ q_i2, const int* __restrict__ q_i1,
     const int* __restrict__ q_us, int* c3_start, int4* c3_desc, int2* c3_item, int* c2_start, int4* c2_desc,
-    int4* c2_item, Counters* ctr) {
+    int4* c2_item, int4* walk3, Counters* ctr) {
   const bool ids = (int)blockIdx.x < ub;
   const int blk = ids ? blockIdx.x : blockIdx.x - ub;
-  const int4 base = seg_base[blk];
+  const int4 base = blk < nblk ? seg_base[blk] : make_int4(0, 0, 0, 0);
   if (ids) {
     GroupOps3 ops{u_i3, u_code, u_q, c3_item};
-    group_block<NT>(blk, nblk, base.x, base.z, (int)sh.n3, rows, p3 + p2, ops, chunk3, c3_start, c3_desc,
-                    &ctr->nchunk3, &ctr->most3);
+    group_block<NT>(blk, nblk, base.x, base.z, (int)sh.n3, rows, p3 + p2, ops, chunk3, nblk, c3_start, c3_desc,
+                    &ctr->nchunk3, walk3, &ctr->walk_cols, &ctr->walk_steps);
   } else {
     GroupOps2 ops{q_i2, q_i1, q_us, c2_item};
-    group_block<NT>(blk, nblk, base.y, base.w, (int)sh.n2, rows + p3, p3 + p2, ops, kChunk2, c2_start, c2_desc,
-                    &ctr->nchunk2, nullptr);
+    group_block<NT>(blk, nblk, base.y, base.w, (int)sh.n2, rows + p3, p3 + p2, ops, kChunk2, 0, c2_start,
+                    c2_desc, &ctr->nchunk2, nullptr, nullptr, nullptr);
   }
 }
 
@@ -814,13 +840,13 @@ void launch_seg_write(const Plan& pl, const Workspace& ws, int B, hipStream_t st
 
 // prefixes_only: prefixes by i2, all a lookup needs, and not the unique ids by i3
 void launch_group(const Plan& pl, const Workspace& ws, int B, hipStream_t st, bool prefixes_only) {
-  const int span = slot_span(pl.sh, B), nblk = cdiv(B, span), ub = prefixes_only ? 0 : nblk;
+  const int span = slot_span(pl.sh, B), nblk = cdiv(B, span), ub = prefixes_only ? 0 : nblk + 1;
   const int p3 = up8(pl.sh.n3), p2 = up8(pl.sh.n2);
   auto launch = [&](auto kernel, int threads) {
     kernel<<<ub + nblk, threads, group_lds(threads, std::max(p3, p2)), st>>>(
         pl.sh, ub, nblk, chunk3_fill(B), p3, p2, ws.seg_base, ws.seg_rows, ws.u_i3, ws.u_code, ws.u_q, ws.q_i2,
         ws.q_i1, ws.q_us, ws.c3_start, ws.c3_desc, ws.c3_item, ws.c2_start, ws.c2_desc, ws.c2_item,
-        ws.ctr);
+        ws.walk3, ws.ctr);
   };
   switch (span) {
     case 1024: launch(k_group<256>, 256); break;

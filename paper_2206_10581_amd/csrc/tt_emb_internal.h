@@ -57,6 +57,10 @@ constexpr int kMaxBins = 2048;                            // digit / bucket coun
 // the next one, 50 -> 88.)
 constexpr int kEntrySlots = 1024;
 
+constexpr int kXcds = 8;
+// Most chunks of a column of walk_chunks3, in mean groups' eighths (both sides measured there).
+constexpr uint32_t kWalkMeans = 2;
+
 constexpr int kTileSlots = 32;   // sorted slots per wavefront tile in the row kernels
 constexpr int kChunk2 = 16;      // unique prefixes per partial sum of a G2 slice gradient
 
@@ -155,7 +159,7 @@ struct Counters {
   int nchunk2;  // partial-sum chunks over the by-i2 grouping of unique prefixes
   int err;      // nonzero: a kernel met an impossible index (bit mask of sites)
   int n_split;  // entries beyond the first of their id (U - n_split distinct ids)
-  int most3;    // chunks of the i3 with the most ids
+  int walk_cols, walk_steps;  // size of walk3, and how many chunks of a column an XCD takes
   int small;    // ranks 64 and 128: an operand of the prefix kernels is below 2^-102 and not zero
 };
 
@@ -212,6 +216,7 @@ struct Workspace {
   int* q_i2;          // prefix -> i2                    [maxQ]
   int* c3_start;      // first chunk of each i3 group [n3+1]
   int4* c3_desc;      // chunk -> {i3, 0, items, 0}  [maxChunk3]
+  int4* walk3;        // columns of walk_chunks3: {first chunk of its i3, chunks, which of its columns, of how many} [2*n3]
   int2* c3_item;      // chunk, t -> {gradient-row code, prefix} of its t-th id [maxChunk3][kChunk3]
   int* c2_start;      // [n2+1]
   int4* c2_desc;      // chunk -> {i2, 0, items, 0}  [maxChunk2]

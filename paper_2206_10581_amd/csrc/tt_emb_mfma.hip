@@ -808,8 +808,6 @@ __device__ __forceinline__ void dg3_chunk_rows(
     }
 }
 
-constexpr int kXcds = 8;
-
 // ---------------------------------------------------------------------------------------------
 // The two gradient steps that only need the per-id gradient sums in one launch: dPsum per prefix, and the
 // partial G3 gradients per by-i3 chunk.  The first is bound by its stores (a product per prefix) and the second by its
@@ -891,24 +889,26 @@ __global__ __launch_bounds__(kMThreads) void k_id_bwd_mfma(
 // Blocks past the by-i2 chunk range take the by-i3 chunks of the G3 gradient, one per wavefront, which gather a
 // prefix product per id.  A group's chunks are in prefix order: workgroups go to the eight XCDs round robin, and
 // XCD x takes the x-th eighth of every group and walks the eighths of all groups side by side, so that the
-// products it gathers at one time are few, and its own.  Against an eighth of all chunks in index order, training
-// steps: 200,000 Zipf ids of 136^3 at rank 32 172 -> 169 us, look-ahead 137.2 -> 135.7 (where a list of the chunks
-// by prefix, 4 to 6 us of the index pipeline, took 138), 500,000 of 480x480x482 at rank 16 376.1 -> 375.6, 50,000
-// uniform ids of (55,55,56) x (8,4,4) 101.7 -> 102.1.  Groups of very different sizes are walked in index order.
+// products it gathers at one time are few, and its own.  A group is a column, or several where its eighth is longer
+// than walk_steps (twice the mean, or the longest eighth if that is less): its chunks go to its columns in turn, so
+// that it keeps pace with the others and no wavefront waits for the one group that is left.  Steps in us with an
+// eighth of all chunks in index order / side by side, one column a group / as it is:
+//   200,000 ids of 136^3, rank 32, one group with 2.5 / 10 / 35 times the mean: 249 / 228 / 228, 260 / 245 / -,
+//     261 / 256 / -; look-ahead 214 / 196 / 197, 225 / 214 / 208, 226 / 224 / 214 (a list of the chunks by prefix, 4 to
+//     6 us of the index pipeline: 203, 215, 220)
+//   500,000 of 480x480x482, rank 16, the same: 478 / 471 / 472, 481 / 477 / -, 498 / 525 / -; look-ahead 450 / 443 /
+//     445, 453 / 451 / 449, 472 / 496 / 466
+//   Zipf ids, whose groups are alike: 172 -> 169 and 376.1 -> 375.6 from index order; look-ahead 122 and 330 either way
+// Columns of one mean instead of two: 500,000 uniform ids of 480x480x482 471 -> 480 us, the unequal groups 1 % less.
 template <class F>
-__device__ __forceinline__ void walk_chunks3(int xcd, int wave, int nwaves, int n3, const int* __restrict__ c3_start,
+__device__ __forceinline__ void walk_chunks3(int xcd, int wave, int nwaves, const int4* __restrict__ walk3,
                                              const Counters* __restrict__ ctr, F take) {
-  const int n = ctr->nchunk3, steps = (ctr->most3 + kXcds - 1) / kXcds;  // steps: chunks of a group's eighth
-  if ((long long)steps * kXcds * n3 <= 2ll * n) {
-    for (int i = wave; i < steps * n3; i += nwaves) {
-      const int j = (int)((uint32_t)i / (uint32_t)n3), i3 = i - j * n3;
-      const int s = c3_start[i3], cnt = c3_start[i3 + 1] - s;
-      const int c = s + cnt * xcd / kXcds + j;
-      if (c < s + cnt * (xcd + 1) / kXcds) take(c);
-    }
-  } else {
-    const int lo = (int)((long long)n * xcd / kXcds), hi = (int)((long long)n * (xcd + 1) / kXcds);
-    for (int c = lo + wave; c < hi; c += nwaves) take(c);
+  const int cols = ctr->walk_cols, n = ctr->walk_steps * cols;
+  for (int i = wave; i < n; i += nwaves) {
+    const int j = (int)((uint32_t)i / (uint32_t)cols);
+    const int4 col = walk3[i - j * cols];
+    const int c = col.x + col.y * xcd / kXcds + j * col.w + col.z;
+    if (c < col.x + col.y * (xcd + 1) / kXcds) take(c);
   }
 }
 
@@ -918,7 +918,7 @@ __global__ __launch_bounds__(WAVES * kWave, 6) void k_bwd_mid_mfma(
     const float* __restrict__ P, const float* __restrict__ grad, const float* __restrict__ gsum,
     const int* __restrict__ u_code, const int* __restrict__ u_i3, const int4* __restrict__ c2_item,
     const int4* __restrict__ c2_desc, const int2* __restrict__ c3_item,
-    const int4* __restrict__ c3_desc, const int* __restrict__ c3_start, int n3,
+    const int4* __restrict__ c3_desc, const int4* __restrict__ walk3,
     float* __restrict__ dg1part, float* __restrict__ part2, float* __restrict__ part3,
     int chunk_blocks, const Counters* __restrict__ ctr) {
   static_assert(R == 8 || R == 16 || R == 32, "the LDS tiles are sized for ranks up to 32");
@@ -932,8 +932,8 @@ __global__ __launch_bounds__(WAVES * kWave, 6) void k_bwd_mid_mfma(
   const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
   if ((int)blockIdx.x >= chunk_blocks) {
     const int rel = (int)blockIdx.x - chunk_blocks;
-    walk_chunks3((int)blockIdx.x % kXcds, rel / kXcds * WAVES + w, ((int)gridDim.x - chunk_blocks) / kXcds * WAVES, n3,
-                 c3_start, ctr, [&](int c) { dg3_chunk<R, D3, 4>(c, P, grad, gsum, c3_item, c3_desc, part3); });
+    walk_chunks3((int)blockIdx.x % kXcds, rel / kXcds * WAVES + w, ((int)gridDim.x - chunk_blocks) / kXcds * WAVES,
+                 walk3, ctr, [&](int c) { dg3_chunk<R, D3, 4>(c, P, grad, gsum, c3_item, c3_desc, part3); });
     return;
   }
   // records, descriptor and chunk count are read together (the grid never exceeds the tables)
@@ -1657,7 +1657,7 @@ void launch_bwd_mid_mfma(const Plan& pl, const Workspace& ws, const float* g1, c
   auto launch = [&](auto kernel) {
     kernel<<<chunk_blocks + dg3_blocks, waves * kWave, 0, st>>>(
         g1, g2, g3, ws.P, grad, ws.gsum, ws.u_code, ws.u_i3, ws.c2_item, ws.c2_desc, ws.c3_item, ws.c3_desc,
-        ws.c3_start, (int)pl.sh.n3, ws.dg1part, ws.part2, ws.part3, chunk_blocks, ws.ctr);
+        ws.walk3, ws.dg1part, ws.part2, ws.part3, chunk_blocks, ws.ctr);
   };
   if (pl.sh.r1 == 8) {
     if (narrow) pl.sh.d3 == 4 ? launch(k_bwd_mid_mfma<8, 4, 4>) : launch(k_bwd_mid_mfma<8, 8, 4>);

@@ -30,7 +30,7 @@ def test_every_byte_of_a_workspace_is_used(n, d, r, most, B):
     sets = (16 * b + 4 * b + 16 * b + 16 * b + 12 * q          # sort, slots, unique ids, prefixes
             + up(b, 1024) * 24 + 2048 * 4 + 8 * n1             # blocks of slots, digit totals, prefixes of an i1
             + up(b, 4096) * (8192 + 4 * n[2]) + up(q, 4096) * 4 * n[1]
-            + c3 * (16 + 16 * 8) + c2 * (16 + 16 * 16) + 4 * (n[2] + n[1]))
+            + 32 * n[2] + c3 * (16 + 16 * 8) + c2 * (16 + 16 * 16) + 4 * (n[2] + n[1]))
     arithmetic = 4 * (2 * q * pn + b * D + up(b, 32) * 2 * D + q * d1 * r + c3 * r * d[2] + c2 * r * d[1] * r)
     rc, nbytes = binding.tt_emb_workspace_bytes(make_config(n, d, (r, r), B, flags=binding.TT_EMB_FLAG_INDEXED_KERNELS))
     assert rc == 0
