@@ -650,7 +650,7 @@ __device__ void group_block(int blk, int nblk, int first, int count, int bins,
                             int publisher, int* chunk_starts, int4* chunk_desc, int* n_chunks, int4* walk,
                             int* walk_cols, int* walk_steps) {
   extern __shared__ __attribute__((aligned(16))) uint32_t group_words[];
-  __shared__ uint32_t ldsw[NT / kWave], most_chunks;
+  __shared__ uint32_t ldsw[NT / kWave], most_chunks, filled;
   const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
   const int words = (bins + 7) / 8, row_words = group_row_words(bins);
   uint32_t* wh = group_words;
@@ -669,7 +669,7 @@ __device__ void group_block(int blk, int nblk, int first, int count, int bins,
     items[step] = ops.load(max(first + min(i, count - 1), 0));
   }
   ColumnSums<8> sums;
-  sums.load(rows, stride, words, nblk, blk);
+  sums.load(rows, stride, words, nblk, count > 0 ? blk : 0);  // without items, nothing of the blocks before
   for (int i = tid; i < words * 16; i += NT) tot[i] = 0u;  // tot and before
 #pragma unroll
   for (int step = 0; step < kSteps; ++step) digits[step] = ops.digit(items[step]);
@@ -679,14 +679,22 @@ __device__ void group_block(int blk, int nblk, int first, int count, int bins,
     if (step >= per || wbase + step * kWave + lane >= count) digits[step] = -1;
   __syncthreads();
   sums.add_to(tot, before);
-  if (tid == 0) most_chunks = 0u;
+  if (tid == 0) most_chunks = filled = 0u;
   __syncthreads();
-  uint32_t my_most = 0;
+  uint32_t my_most = 0, my_filled = 0;
   for (int bin = tid; bin < bins; bin += NT) {
     aux[bin] = (tot[bin] + chunk - 1) >> chunk_sh;
     my_most = max(my_most, aux[bin]);
+    my_filled += aux[bin] > 0;
   }
-  if (blk == publisher && my_most > 0) atomicMax(&most_chunks, my_most);
+  if (blk == publisher && walk != nullptr) {
+    my_most = wave_max(my_most);
+    my_filled = wave_inclusive_scan(my_filled, lane);
+    if (lane == kWave - 1) {
+      atomicMax(&most_chunks, my_most);
+      atomicAdd(&filled, my_filled);
+    }
+  }
   __syncthreads();
   const uint32_t total_chunks = block_exclusive_scan(aux, bins, ldsw);
   if (blk == publisher) {
@@ -696,28 +704,32 @@ __device__ void group_block(int blk, int nblk, int first, int count, int bins,
       *n_chunks = (int)total_chunks;
     }
     if (walk != nullptr) {
-      auto chunks_of = [&](int bin) { return (bin + 1 < bins ? aux[bin + 1] : total_chunks) - aux[bin]; };
-      const uint32_t mean = (total_chunks + kXcds * bins - 1) / (kXcds * bins);  // of a bucket's eighth
-      const uint32_t steps = max(min((most_chunks + kXcds - 1) / kXcds, kWalkMeans * mean), 1u);
-      uint32_t* first_col = wh;  // free until block_ranks; at least two words a bucket
-      for (int bin = tid; bin < bins; bin += NT)
-        first_col[bin] = ((chunks_of(bin) + kXcds - 1) / kXcds + steps - 1) / steps;
-      __syncthreads();
-      const int cols = (int)block_exclusive_scan(first_col, bins, ldsw);
-      for (int c = tid; c < cols; c += NT) {
-        int lo = 0, hi = bins;  // last bucket whose first column is <= c
-        while (hi - lo > 1) {
-          const int mid = (lo + hi) >> 1;
-          if ((int)first_col[mid] <= c) lo = mid; else hi = mid;
+      auto chunks_of = [&](int bin) { return (int)((bin + 1 < bins ? aux[bin + 1] : total_chunks) - aux[bin]); };
+      const uint32_t longest = (most_chunks + kXcds - 1) / kXcds;  // of the buckets' eighths
+      uint32_t cols = 0, steps = longest;
+      if (total_chunks >= (uint32_t)(kWalkLeast * kXcds) * filled) {
+        if (bins < 2 * (int)filled && longest * bins <= kWalkMeans * (total_chunks / kXcds + bins)) {
+          // a column each, also for the empty ones
+          cols = (uint32_t)bins;
+          for (int bin = tid; bin < bins; bin += NT) walk[bin] = make_int4((int)aux[bin], chunks_of(bin), 0, 1);
+        } else {
+          steps = max(kWalkMeans * ((total_chunks + kXcds * bins - 1) / (kXcds * bins)), 1u);
+          uint32_t* first_col = wh;  // free until block_ranks; at least two words a bucket
+          for (int bin = tid; bin < bins; bin += NT)
+            first_col[bin] = ((chunks_of(bin) + kXcds - 1) / kXcds + steps - 1) / steps;
+          __syncthreads();
+          cols = block_exclusive_scan(first_col, bins, ldsw);
+          for (int bin = tid; bin < bins; bin += NT) {
+            const int first = (int)first_col[bin], n = (int)(bin + 1 < bins ? first_col[bin + 1] : cols) - first;
+            for (int k = 0; k < n; ++k) walk[first + k] = make_int4((int)aux[bin], chunks_of(bin), k, n);
+          }
+          __syncthreads();  // block_ranks clears what the columns were counted in
         }
-        const int next = lo + 1 < bins ? (int)first_col[lo + 1] : cols;
-        walk[c] = make_int4((int)aux[lo], (int)chunks_of(lo), c - (int)first_col[lo], next - (int)first_col[lo]);
       }
       if (tid == 0) {
-        *walk_cols = cols;
+        *walk_cols = (int)cols;
         *walk_steps = (int)steps;
       }
-      __syncthreads();  // block_ranks clears what the columns were counted in
     }
   }
   // every block of slots takes a share of the chunk descriptors
@@ -736,8 +748,8 @@ __device__ void group_block(int blk, int nblk, int first, int count, int bins,
   });
 }
 
-// Blocks [0, ub): unique ids by i3, a block per block of slots and one behind them that only writes the tables of
-// one entry per bucket; the nblk behind those: prefixes by i2.
+// Blocks [0, ub): unique ids by i3, first one that only writes the tables of one entry per bucket, then a block per
+// block of slots; the nblk behind those: prefixes by i2.
 template <int NT>
 __global__ __launch_bounds__(NT) void k_group(
     Shape sh, int ub, int nblk, int chunk3, int p3, int p2, const int4* __restrict__ seg_base,
@@ -746,7 +758,7 @@ __global__ __launch_bounds__(NT) void k_group(
     const int* __restrict__ q_us, int* c3_start, int4* c3_desc, int2* c3_item, int* c2_start, int4* c2_desc,
     int4* c2_item, int4* walk3, Counters* ctr) {
   const bool ids = (int)blockIdx.x < ub;
-  const int blk = ids ? blockIdx.x : blockIdx.x - ub;
+  const int blk = !ids ? blockIdx.x - ub : blockIdx.x == 0 ? nblk : blockIdx.x - 1;
   const int4 base = blk < nblk ? seg_base[blk] : make_int4(0, 0, 0, 0);
   if (ids) {
     GroupOps3 ops{u_i3, u_code, u_q, c3_item};

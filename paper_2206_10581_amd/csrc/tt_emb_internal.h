@@ -58,8 +58,10 @@ constexpr int kMaxBins = 2048;                            // digit / bucket coun
 constexpr int kEntrySlots = 1024;
 
 constexpr int kXcds = 8;
-// Most chunks of a column of walk_chunks3, in mean groups' eighths (both sides measured there).
+// walk_chunks3: most chunks of a column, in mean groups' eighths, and the chunks that a group has on average for each
+// XCD where groups are walked at all (both sides measured there).
 constexpr uint32_t kWalkMeans = 2;
+constexpr int kWalkLeast = 2;
 
 constexpr int kTileSlots = 32;   // sorted slots per wavefront tile in the row kernels
 constexpr int kChunk2 = 16;      // unique prefixes per partial sum of a G2 slice gradient
@@ -159,7 +161,7 @@ struct Counters {
   int nchunk2;  // partial-sum chunks over the by-i2 grouping of unique prefixes
   int err;      // nonzero: a kernel met an impossible index (bit mask of sites)
   int n_split;  // entries beyond the first of their id (U - n_split distinct ids)
-  int walk_cols, walk_steps;  // size of walk3, and how many chunks of a column an XCD takes
+  int walk_cols, walk_steps;  // columns in walk3 (none: chunks in index order), chunks of one that an XCD takes
   int small;    // ranks 64 and 128: an operand of the prefix kernels is below 2^-102 and not zero
 };
 
@@ -364,6 +366,15 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v, int lane) {
   const uint32_t r2 = (uint32_t)__builtin_amdgcn_readlane((int)v, 47);
   const int row = lane / 16;
   return v + (row >= 1 ? r0 : 0u) + (row >= 2 ? r1 : 0u) + (row >= 3 ? r2 : 0u);
+}
+
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+  v = max(v, row_shr_or_zero<1>(v));
+  v = max(v, row_shr_or_zero<2>(v));
+  v = max(v, row_shr_or_zero<4>(v));
+  v = max(v, row_shr_or_zero<8>(v));
+  auto row = [&](int last) { return (uint32_t)__builtin_amdgcn_readlane((int)v, last); };
+  return max(max(row(15), row(31)), max(row(47), row(63)));
 }
 
 // LDS writes of a wavefront become visible to its own later reads

@@ -900,15 +900,24 @@ __global__ __launch_bounds__(kMThreads) void k_id_bwd_mfma(
 //     445, 453 / 451 / 449, 472 / 496 / 466
 //   Zipf ids, whose groups are alike: 172 -> 169 and 376.1 -> 375.6 from index order; look-ahead 122 and 330 either way
 // Columns of one mean instead of two: 500,000 uniform ids of 480x480x482 471 -> 480 us, the unequal groups 1 % less.
+// Where groups have few chunks, places without one cost more than neighbours bring (index order / side by side, uniform
+// ids): 120x120x500, rank 32, 2 / 6 / 10 / 16 / 24 chunks a group 91 / 96, 108 / 110, 120 / 121, 137 / 135, 160 / 152;
+// (60,60,2000) x (8,4,4), rank 16, 6 / 12 / 16 chunks 113 / 118, 152 / 157, 172 / 176.
 template <class F>
 __device__ __forceinline__ void walk_chunks3(int xcd, int wave, int nwaves, const int4* __restrict__ walk3,
                                              const Counters* __restrict__ ctr, F take) {
-  const int cols = ctr->walk_cols, n = ctr->walk_steps * cols;
+  const int chunks = ctr->nchunk3, cols = ctr->walk_cols;
+  const int lo = (int)((int64_t)chunks * xcd / kXcds), hi = (int)((int64_t)chunks * (xcd + 1) / kXcds);
+  const int n = cols > 0 ? ctr->walk_steps * cols : hi - lo;
   for (int i = wave; i < n; i += nwaves) {
-    const int j = (int)((uint32_t)i / (uint32_t)cols);
-    const int4 col = walk3[i - j * cols];
-    const int c = col.x + col.y * xcd / kXcds + j * col.w + col.z;
-    if (c < col.x + col.y * (xcd + 1) / kXcds) take(c);
+    int c = lo + i, end = hi;
+    if (cols > 0) {
+      const int j = (int)((uint32_t)i / (uint32_t)cols);
+      const int4 col = walk3[i - j * cols];
+      c = col.x + col.y * xcd / kXcds + j * col.w + col.z;
+      end = col.x + col.y * (xcd + 1) / kXcds;
+    }
+    if (c < end) take(c);
   }
 }
 
