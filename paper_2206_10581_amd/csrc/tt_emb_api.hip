@@ -16,9 +16,9 @@ namespace ttemb {
 // launchers defined next to their kernels
 void launch_sort_pass(const Plan&, const Workspace&, const SortKeys&, const IdSource& src, int B, int pass,
                       bool beside, bool clear, hipStream_t, int which);
-void launch_seg_count(const Plan&, const Workspace&, int B, hipStream_t);
-void launch_seg_write(const Plan&, const Workspace&, int B, hipStream_t);
-void launch_group(const Plan&, const Workspace&, int B, hipStream_t, bool prefixes_only);
+void launch_seg_count(const Plan&, const Workspace&, int B, bool beside, hipStream_t);
+void launch_seg_write(const Plan&, const Workspace&, int B, bool beside, hipStream_t);
+void launch_group(const Plan&, const Workspace&, int B, bool beside, bool prefixes_only, hipStream_t);
 void launch_prefix_fwd(const Plan&, const Workspace&, const float* g1, const float* g2, int B,
                        hipStream_t);
 void launch_row_fwd(const Plan&, const Workspace&, const float* g3, int B, float* out, hipStream_t);
@@ -549,18 +549,19 @@ static int run_sort(tt_emb* h, const Workspace& ws, const SortKeys& sk, const Id
 }
 
 // Index pipeline of one batch into index set `set`, on stream st.
-// how: 0 = beside other work, as in tt_emb_prepare, with large sort blocks; 1 = on the caller's stream; 2 = a
+// how: 0 = beside other work, as in tt_emb_prepare, with large blocks; 1 = on the caller's stream; 2 = a
 // lookup there: the structures that only the backward pass reads (unique ids by i3) are not built.
 static int run_index(tt_emb* h, int set, const IdSource& src, int B, hipStream_t st, int how) {
   const Plan& pl = h->plan;
   const Workspace& ws = h->ws[set];
-  int rc = run_sort(h, ws, pl.keys, src, B, how == 0, true, st);
+  const bool beside = how == 0;
+  int rc = run_sort(h, ws, pl.keys, src, B, beside, true, st);
   if (rc) return rc;
-  rc = run_slot(h, kSlotSegCount, st, [&] { launch_seg_count(pl, ws, B, st); });
+  rc = run_slot(h, kSlotSegCount, st, [&] { launch_seg_count(pl, ws, B, beside, st); });
   if (rc) return rc;
-  rc = run_slot(h, kSlotSegWrite, st, [&] { launch_seg_write(pl, ws, B, st); });
+  rc = run_slot(h, kSlotSegWrite, st, [&] { launch_seg_write(pl, ws, B, beside, st); });
   if (rc) return rc;
-  return run_slot(h, kSlotGroup, st, [&] { launch_group(pl, ws, B, st, how == 2); });
+  return run_slot(h, kSlotGroup, st, [&] { launch_group(pl, ws, B, beside, how == 2, st); });
 }
 
 // Lookup of ids sorted by prefix: no index structures behind the sort, no products in memory.

@@ -81,7 +81,7 @@ static_assert((kChunk2 & (kChunk2 - 1)) == 0 && (kChunk3 & (kChunk3 - 1)) == 0 &
 // Column sums over the rows of 16-bit bucket counts that the nblk blocks of a pass left, `stride` counts
 // apart: per bucket the items of all blocks (tot) and those of blocks before blk (before).  Eight buckets are
 // one 16-byte load (`words` of them a row), so a row takes few threads, and the threads are dealt over the
-// rows too: all rows are under way at once, where one thread per bucket makes a chain of the rows.  No more
+// rows too, ROWS of them a thread under way at once, where one thread per bucket makes a chain of the rows.  No more
 // threads than that takes: their sums meet in LDS, and every further one is another atomic on the same words
 // (200,000 ids, 1024 threads in the grouping kernel: 176 us a step with all of them, 172 without).
 template <int ROWS>  // rows a thread has in flight
@@ -827,23 +827,23 @@ void launch_sort_pass(const Plan& pl, const Workspace& ws, const SortKeys& sk, c
 
 // The segment kernels of a batch of B items: 1024 threads with 1, 2 or 4 slots each.
 template <class F>
-static void with_slot_items(const Plan& pl, int B, F&& launch) {
-  const int span = slot_span(pl.sh, B), blocks = cdiv(B, span);
+static void with_slot_items(const Plan& pl, int B, bool beside, F&& launch) {
+  const int span = slot_span(pl.sh, B, beside), blocks = cdiv(B, span);
   if (span == kSegThreads) launch(std::integral_constant<int, 1>{}, blocks);
   else if (span == 2 * kSegThreads) launch(std::integral_constant<int, 2>{}, blocks);
   else launch(std::integral_constant<int, 4>{}, blocks);
 }
 
-void launch_seg_count(const Plan& pl, const Workspace& ws, int B, hipStream_t st) {
-  with_slot_items(pl, B, [&](auto items, int blocks) {
+void launch_seg_count(const Plan& pl, const Workspace& ws, int B, bool beside, hipStream_t st) {
+  with_slot_items(pl, B, beside, [&](auto items, int blocks) {
     k_seg_count<items()><<<blocks, kSegThreads, 0, st>>>(ws.key[pl.keys.sorted()], B, pl.sh.N, pl.sh.n3,
                                                          ws.seg_nu, ws.seg_nq);
   });
 }
 
-void launch_seg_write(const Plan& pl, const Workspace& ws, int B, hipStream_t st) {
+void launch_seg_write(const Plan& pl, const Workspace& ws, int B, bool beside, hipStream_t st) {
   const int f = pl.keys.sorted(), p3 = up8(pl.sh.n3), p2 = up8(pl.sh.n2);
-  with_slot_items(pl, B, [&](auto items, int blocks) {
+  with_slot_items(pl, B, beside, [&](auto items, int blocks) {
     k_seg_write<items()><<<blocks, kSegThreads, (p3 + p2) * 4, st>>>(
         ws.key[f], ws.val[f], B, pl.sh, p3, p2, ws.seg_nu, ws.seg_nq, ws.s_u, ws.s_rec, ws.u_rs, ws.u_i3, ws.u_q,
         ws.u_code, ws.q_us, ws.q_i1, ws.q_i2, ws.seg_base, ws.seg_rows, ws.g1_first, ws.g1_end, ws.ctr);
@@ -851,8 +851,8 @@ void launch_seg_write(const Plan& pl, const Workspace& ws, int B, hipStream_t st
 }
 
 // prefixes_only: prefixes by i2, all a lookup needs, and not the unique ids by i3
-void launch_group(const Plan& pl, const Workspace& ws, int B, hipStream_t st, bool prefixes_only) {
-  const int span = slot_span(pl.sh, B), nblk = cdiv(B, span), ub = prefixes_only ? 0 : nblk + 1;
+void launch_group(const Plan& pl, const Workspace& ws, int B, bool beside, bool prefixes_only, hipStream_t st) {
+  const int span = slot_span(pl.sh, B, beside), nblk = cdiv(B, span), ub = prefixes_only ? 0 : nblk + 1;
   const int p3 = up8(pl.sh.n3), p2 = up8(pl.sh.n2);
   auto launch = [&](auto kernel, int threads) {
     kernel<<<ub + nblk, threads, group_lds(threads, std::max(p3, p2)), st>>>(
