@@ -338,15 +338,12 @@ static int lookup_tile(const Shape& s, int B) {
   if (s.r1 <= 16) return B <= kSmallBatch ? 16 : 32;
   return B <= kSmallBatch / 16 ? 16 : B <= kSmallBatch ? 32 : 64;
 }
-// Up to kAheadMost ids and kAheadSlabs slabs the next batch's lines of G1 and the next product's slices of G3 are
-// loaded ahead: few wavefronts a compute unit, whose chain of loads is the time.  Above, other wavefronts fill the
-// waits, and what keeping loads in flight takes in instructions is lost.  Lookups in us without / with: rank 8,
-// 50,000 uniform ids of (55,55,56) x (8,4,4) 32.9 / 30.5, 120,000 clustered ones of 480x480x482 40.6 / 38.4; rank 16,
-// 20,000 Zipf ids of 136^3 36.2 / 34.5, 100,000 41.4 / 39.6, of (480,500,500) x (8,4,4) 80,000 Zipf ones 61.5 / 60.2
-// and uniform ones 130,000 82.8 / 84.1, 200,000 98 / 104; rank 32, 136^3, 12,000 Zipf ids 42.6 / 38.6, 120,000
-// uniform ones 64.8 / 63.5, 200,000 Zipf ones 79.5 / 89.
-constexpr int kAheadMost = 1 << 17, kAheadSlabs = 3 << 16;
-
+// The next batch's lines of G1 and the next product's slices of G3 are loaded ahead where tiles are short at rank 32: few
+// wavefronts a compute unit, whose chain of loads is the time.  Elsewhere other wavefronts fill the waits, and what
+// keeping loads in flight takes in instructions and registers is lost.  Lookups in us without / with, uniform ids: rank
+// 32, 8,500 ids of (480,500,500) x (8,4,4) 48.3 / 48.0, Zipf 49.1 / 48.4, of 60^3 x (16,4,4) 52.9 / 51.9, of 136^3 38.9 /
+// 39.0; longer tiles, 30,000 ids of 136^3 46.3 / 47.1, 90,000 52.2 / 63.1, of (480,500,500) x (8,4,4) 121 / 153; rank 16,
+// 90,000 of 136^3 38.4 / 41.2, rank 8 35.7 / 37.0.
 void launch_lookup(const Plan& pl, const Workspace& ws, const float* g1, const float* g2, const float* g3, int B,
                    float* out, hipStream_t st) {
   const int f = pl.lookup_keys.sorted();
@@ -356,18 +353,15 @@ void launch_lookup(const Plan& pl, const Workspace& ws, const float* g1, const f
         out, ws.ctr);
   };
   const int tile = lookup_tile(pl.sh, B);
-  const bool ahead = B <= kAheadMost && (int64_t)B * pl.split <= kAheadSlabs;
   auto by_d3 = [&](auto k4, auto k8, int slots) { pl.sh.d3 == 4 ? launch(k4, slots) : launch(k8, slots); };
   // the grid is made for the slots of the kernel that is launched
 #define TT_TILE(R_, T_, A_) by_d3(k_lookup_mfma<R_, 4, T_, A_>, k_lookup_mfma<R_, 8, T_, A_>, T_)
-#define TT_RANK(R_) \
-  if (ahead) TT_TILE(R_, 16, true); else if (tile == 16) TT_TILE(R_, 16, false); else TT_TILE(R_, 32, false)
+#define TT_RANK(R_) if (tile == 16) TT_TILE(R_, 16, false); else TT_TILE(R_, 32, false)
   switch (pl.sh.r1) {
     case 8: TT_RANK(8); break;
     case 16: TT_RANK(16); break;
     default:
-      if (tile == 16) TT_TILE(32, 16, true);  // d1 = 32 has eight slabs an id: 2^17 at most
-      else if (tile == 32 && ahead) TT_TILE(32, 32, true);
+      if (tile == 16) TT_TILE(32, 16, true);
       else if (tile == 32) TT_TILE(32, 32, false);
       else TT_TILE(32, 64, false);
   }

@@ -65,9 +65,10 @@ def test_slabs(r, d3, d1):
     _compare((41, 37, 19), (d1, 4, d3), r, 17_003, "uniform", reindex=True)
 
 
-# with and without loads ahead: the most ids and slabs that have them, and more; slabs in two rounds without
+# with and without loads ahead: the most ids that have them and one more, slabs in one round and in two; large batches
 @pytest.mark.parametrize("d1,r,d3,B", [(4, 32, 8, 131_072), (4, 16, 4, 131_073), (8, 8, 4, 98_304), (8, 32, 8, 98_305),
-                                       (20, 16, 4, 40_001)])
+                                       (20, 16, 4, 40_001), (4, 32, 8, 16_384), (8, 32, 4, 16_384), (20, 32, 4, 16_384),
+                                       (8, 32, 8, 16_385), (20, 32, 8, 16_385)])
 def test_loads_ahead(d1, r, d3, B):
     _compare((41, 37, 19), (d1, 4, d3), r, B, "hot")
 
