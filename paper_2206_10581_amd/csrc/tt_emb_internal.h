@@ -140,16 +140,16 @@ __host__ __device__ constexpr int up8(uint32_t n) { return (int)(n + 7) & ~7; }
 // Sorted slots of a block of the segment and grouping kernels, a quarter of them threads of the latter: few, for many
 // blocks, up to a block a compute unit and as long as a grouping block adds up the counts of all blocks, a row of
 // 16-byte words of eight buckets each, in five rounds of eight rows a group of threads.  Beside another batch's
-// arithmetic, which the loads of those rows disturb, up to a number of words in all.  Training steps in us with 1024 / 2048 / 4096 slots, uniform ids, rank 16, d = (4,4,4), n1 = 136, and the
-// rows of 1024 slots and their words:
+// arithmetic, which the loads of those rows disturb, up to a number of words in all.  Training steps in us with
+// 1024 / 2048 / 4096 slots, uniform ids, rank 16, d = (4,4,4), n1 = 136, and the rows of 1024 slots and their words:
 //   n2 = n3 = 136           100,000 ids, 98 x 17: 114 / 116 / 122       200,000, 196 x 17: 149 / 150 / 156
 //                           400,000, 391 x 17: 221 / 218 / 223          600,000, 586 x 17: 299 / 298 / 293
 //   n2 = 136, n3 = 480      150,000, 147 x 60: 138 / 140 / 145          250,000, 245 x 60: 176 / 173 / 178
 //                           500,000, 489 x 60: - / 258 / 262            600,000, 586 x 60: - / 309 / 305
 //   n2 = 100, n3 = 1000     90,000, 88 x 125: 118 / 118 / 124           150,000, 147 x 125: 141 / 140 / 146
-// and beside, 100,000 Zipf ids of 480x480x482 at rank 64 (98 x 60) 451 / - / 470, 200,000 of 136^3 at rank 32 (196 x 17)
-// 124 / 123 / 124, 400,000 uniform ones of 100^3 (391 x 13) 170 / 172 / 174, 100,000 of 50x100x2000 at rank 32 (98 x
-// 250) - / 109 / 106, 500,000 Zipf ids of 480x480x482 (489 x 60) 348 / 334 / 331, 800,000 510 / 479 / 472.
+// and beside, 100,000 Zipf ids of 480x480x482 at rank 64 (98 x 60) 451 / - / 470, 200,000 of 136^3 at rank 32
+// (196 x 17) 124 / 123 / 124, 400,000 uniform ones of 100^3 (391 x 13) 170 / 172 / 174, 100,000 of 50x100x2000 at
+// rank 32 (98 x 250) - / 109 / 106, 500,000 Zipf ids of 480x480x482 (489 x 60) 348 / 334 / 331, 800,000 510 / 479 / 472.
 // The counts lie in the memory that Workspace::seg_rows names, which holds at least 8192 + 4*n3 bytes per 4096 slots.
 constexpr int kSlotBlocks = 256, kSlotRounds = 5, kSlotWordsBeside = 8192;
 inline int slot_span(const Shape& sh, int64_t B, bool beside) {
@@ -231,7 +231,7 @@ struct Workspace {
   int* q_i2;          // prefix -> i2                    [maxQ]
   int* c3_start;      // first chunk of each i3 group [n3+1]
   int4* c3_desc;      // chunk -> {i3, 0, items, 0}  [maxChunk3]
-  int4* walk3;        // columns of walk_chunks3: {first chunk of its i3, chunks, which of its columns, of how many} [2*n3]
+  int4* walk3;        // columns of walk_chunks3: {first chunk of its i3, chunks, which column, of how many} [2*n3]
   int2* c3_item;      // chunk, t -> {gradient-row code, prefix} of its t-th id [maxChunk3][kChunk3]
   int* c2_start;      // [n2+1]
   int4* c2_desc;      // chunk -> {i2, 0, items, 0}  [maxChunk2]

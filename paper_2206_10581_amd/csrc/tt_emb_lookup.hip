@@ -338,12 +338,12 @@ static int lookup_tile(const Shape& s, int B) {
   if (s.r1 <= 16) return B <= kSmallBatch ? 16 : 32;
   return B <= kSmallBatch / 16 ? 16 : B <= kSmallBatch ? 32 : 64;
 }
-// The next batch's lines of G1 and the next product's slices of G3 are loaded ahead where tiles are short at rank 32: few
-// wavefronts a compute unit, whose chain of loads is the time.  Elsewhere other wavefronts fill the waits, and what
-// keeping loads in flight takes in instructions and registers is lost.  Lookups in us without / with, uniform ids: rank
-// 32, 8,500 ids of (480,500,500) x (8,4,4) 48.3 / 48.0, Zipf 49.1 / 48.4, of 60^3 x (16,4,4) 52.9 / 51.9, of 136^3 38.9 /
-// 39.0; longer tiles, 30,000 ids of 136^3 46.3 / 47.1, 90,000 52.2 / 63.1, of (480,500,500) x (8,4,4) 121 / 153; rank 16,
-// 90,000 of 136^3 38.4 / 41.2, rank 8 35.7 / 37.0.
+// The next batch's lines of G1 and the next product's slices of G3 are loaded ahead where tiles are short at rank
+// 32: few wavefronts a compute unit, whose chain of loads is the time.  Elsewhere other wavefronts fill the waits,
+// and what keeping loads in flight takes in instructions and registers is lost.  Lookups in us without / with,
+// uniform ids: rank 32, 8,500 ids of (480,500,500) x (8,4,4) 48.3 / 48.0, Zipf 49.1 / 48.4, of 60^3 x (16,4,4)
+// 52.9 / 51.9, of 136^3 38.9 / 39.0; longer tiles, 30,000 ids of 136^3 46.3 / 47.1, 90,000 52.2 / 63.1, of
+// (480,500,500) x (8,4,4) 121 / 153; rank 16, 90,000 of 136^3 38.4 / 41.2, rank 8 35.7 / 37.0.
 void launch_lookup(const Plan& pl, const Workspace& ws, const float* g1, const float* g2, const float* g3, int B,
                    float* out, hipStream_t st) {
   const int f = pl.lookup_keys.sorted();
